@@ -166,7 +166,8 @@ LOP_API int lop_plan_band_compute_rows(const lop_plan_t* plan, int band, int lay
 
 /* Work counts: operations of the whole layers (useful) and summed over the bands'
  * intervals (executed; > useful where halos are recomputed); bytes of device scratch one lane
- * holds (the slabs of one band plus the largest split-K workspace of a launch). */
+ * holds (the layer outputs that are live together, of one band or of the bands whose launches are
+ * merged, plus the largest split-K workspace of a launch). */
 LOP_API int lop_plan_stats(const lop_plan_t* plan, double* useful_flop, double* executed_flop,
                    size_t* scratch_bytes);
 /* Per layer and band: operations executed and algorithmic bytes moved (rows read of the
@@ -193,20 +194,30 @@ LOP_API int lop_plan_layer_work(const lop_plan_t* plan, int band, int layer, dou
 LOP_API int lop_run_band(lop_plan_t* plan, int band, const void* d_in, void* d_out, void* h_out,
                  void* compute_stream, void* copy_stream);
 
-/* Run every band: the lanes fork from compute_stream, each runs its bands in order, band b's
- * copy overlaps the kernels of the bands after it (Sec. IV-B), and compute_stream waits for
- * all lanes' kernels (not for the copies: those are complete after lop_synchronize). With
- * compute_stream == NULL there is nothing to order against: d_in must be complete when the
- * call is made, every lane appends its bands to its own stream and the lanes are not joined,
- * so the chains of consecutive calls overlap (give each chain in flight its own d_out /
- * h_out); results are complete after lop_synchronize. With timing != NULL the call records
- * events, waits for completion and fills *timing; otherwise it is asynchronous. */
+/* Run every band. Where all bands of the chain are run anyway, their launches of an operator are
+ * merged (operation batching, Sec. IV-D): bands that recompute halo rows run as one launch per
+ * layer that computes each band's rows on that band's slabs; bands that compute no row twice
+ * (LOP_FLAG_REUSE, chains without halos, one band) as one launch per layer over all their rows.
+ * That holds for chains whose layer outputs fit LOP_STATIC_SCRATCH_BYTES together (independent
+ * bands: in equal groups of bands that do); a merged chain runs on one lane and consecutive
+ * calls rotate over the lanes. Larger chains run band by band on the lanes, band b's copy
+ * overlapping the kernels of the bands after it (Sec. IV-B). Either way the rows computed are
+ * those of lop_run_band, which runs a single band, and the results agree with it up to the order
+ * of the fp32 sums.
+ * compute_stream waits for all kernels (not for the copies of a chain that runs band by band:
+ * those are complete after lop_synchronize). With compute_stream == NULL there is nothing to
+ * order against: d_in must be complete when the call is made, nothing is joined, and the chains of
+ * consecutive calls overlap (give each chain in flight its own d_out / h_out); results are
+ * complete after lop_synchronize. With timing != NULL the bands run one by one (with
+ * LOP_FLAG_BATCH_BANDS: merged), the call records events, waits for completion and fills
+ * *timing; otherwise it is asynchronous. */
 LOP_API int lop_run_chain(lop_plan_t* plan, const void* d_in, void* d_out, void* h_out,
                   void* compute_stream, lop_timing_t* timing);
 
 /* lop_run_chain for callers that cannot allocate device memory or create streams and events
  * where they run: code under HIP graph capture, tight serving loops, harnesses that forbid
- * hipMalloc. Enqueues the kernels of every band, bands in order, on `stream` alone (NULL = the
+ * hipMalloc. Enqueues the kernels of every band, merged as in lop_run_chain or band by band, on
+ * `stream` alone (NULL = the
  * null stream) and returns; no copy to the host, no event, no other stream. The band slabs and
  * the split-K partial sums do not live in the plan's allocations but in an array of
  * LOP_STATIC_SCRATCH_BYTES that is part of the library's code object: every GPU the library
@@ -360,7 +371,8 @@ LOP_API int lop_time_layer(lop_plan_t* plan, int band, int layer, const void* d_
 LOP_API int lop_plan_layer_kernel(const lop_plan_t* plan, int band, int layer, char* name, size_t size,
                                   int* k_slices);
 
-/* Run the whole chain `iters` times, bands in order on one stream, with a start and a stop
+/* Run the bands of the chain one by one (the launches of lop_run_band; with
+ * LOP_FLAG_BATCH_BANDS: the merged ones) `iters` times, in order on one stream, with a start and a stop
  * event attached to every kernel dispatch (the kernel's own duration, as a profiler's kernel
  * trace reports it), and write the mean milliseconds of each (band, layer) main kernel to
  * layer_ms[band * n_layers + layer] and of its splitk_finish_kernel (0 if none) to

@@ -2073,16 +2073,18 @@ bool convpool_applies(const OpLaunch& conv, const OpLaunch& pool) {
   return (conv.x.c * esz) % 128 == 0 && conv.y.c % ke == 0 && conv.k_pad == K;
 }
 
-// Whether the pooled launch is worth taking for this launch of the conv (its own rows, its
-// slabs' geometry): not where the conv alone would run on one of the operand-direct kernels
+// Whether the pooled launch is worth taking for this launch of the conv over n bands (their rows,
+// their slabs' geometry): not where the conv alone would run on one of the operand-direct kernels
 // (few pixels, a long reduction), which together with a separate pooling launch are faster
 // than the LDS kernel on so few tiles (8 + 4 us against 15-17 us on the 512-channel layers of
 // a banded VGG-16).
-bool convpool_pays(const OpLaunch& conv) {
-  const ConvParams p = make_params(conv);
-  if (p.M <= 0) return true;
-  const Choice c = choose(p, conv.dtype);
-  const DirectChoice d = choose_direct(p, conv.dtype, c.splits);
+bool convpool_pays_bands(const OpLaunch* convs, int n) {
+  ConvParams ps[kMaxBatch];
+  const int m = n >= 1 && n <= kMaxBatch ? group_of(convs, n, ps) : 0;
+  if (m == 0) return true;
+  const ConvParams p = group_params(ps, m);
+  const Choice c = choose(p, convs[0].dtype);
+  const DirectChoice d = choose_direct(p, convs[0].dtype, c.splits);
   return !(d.wk && d.narrow);
 }
 

@@ -96,7 +96,7 @@ int stem_describe_bands(const OpLaunch* Ls, int n, char* name, size_t size);
 // the pair qualifies (descriptors without slabs suffice), the launch (conv: input slab, weights,
 // hyper-parameters; pool: output slab, y2 and the pooled rows out_lo..out_hi) and its kernel name.
 bool convpool_applies(const OpLaunch& conv, const OpLaunch& pool);
-bool convpool_pays(const OpLaunch& conv);  // for one launch of the conv alone (rows and slab geometry set)
+bool convpool_pays_bands(const OpLaunch* convs, int n);  // for one launch of the conv alone (rows and slab geometry set)
 hipError_t launch_convpool(const OpLaunch& conv, const OpLaunch& pool, hipStream_t stream,
                            KernelEvents* ev = nullptr);
 int convpool_describe(const OpLaunch& conv, const OpLaunch& pool, char* name, size_t size);

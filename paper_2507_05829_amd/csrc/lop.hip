@@ -247,34 +247,138 @@ int upload_weights(lop_plan_t* P) {
   return LOP_OK;
 }
 
-void size_scratch(lop_plan_t* P) {
+bool layer_batchable(const lop_plan_t* P, int l);
+
+// Last launch (by the index of the layer it ends with) that reads layer l's output, under either
+// set of fused groups; l itself if nobody does.
+int last_reader(const lop_plan_t* P, int l) {
   const lop::Tables& t = P->t;
   const int nl = t.n_layers();
-  P->slab_off.assign(t.n_bands, std::vector<size_t>(nl, 0));
+  int last = l;
+  for (int j = l + 1; j < nl; ++j) {
+    if (t.layers[j].d.input_from != l && t.layers[j].d.residual_from != l) continue;
+    last = std::max(last, j);
+    for (const Fusion* F : {&P->fuse_band, &P->fuse_chain})
+      for (int q = j; q < nl; ++q)   // (a layer inside a group is read when the group's last layer runs)
+        if (F->head[q] >= 0 && F->head[q] <= j) last = std::max(last, q);
+  }
+  return last;
+}
+
+// Offsets for the layers' outputs in one arena: a buffer is live from its layer's launch to its
+// last reader's, and layers whose buffers are never live together share memory, so that what a
+// chain keeps between launches is a few layers' rows instead of all of them (the rows stay in
+// the caches, and a quarter of the memory holds a whole chain). size[l] == 0: no buffer.
+size_t place_slabs(const lop_plan_t* P, const std::vector<size_t>& size, std::vector<size_t>* off) {
+  const int nl = P->t.n_layers();
+  std::vector<int> last(nl);
+  for (int l = 0; l < nl; ++l) last[l] = last_reader(P, l);
   size_t worst = 0;
+  for (int l = 0; l + 1 < nl; ++l) {  // the last layer writes the caller's output
+    (*off)[l] = 0;
+    if (!size[l]) continue;
+    size_t at = 0;
+    for (bool moved = true; moved;) {   // the lowest place that touches no buffer still live
+      moved = false;
+      for (int k = 0; k < l; ++k)
+        if (size[k] && last[k] >= l && at < (*off)[k] + size[k] && (*off)[k] < at + size[l]) {
+          at = (*off)[k] + size[k];
+          moved = true;
+        }
+    }
+    (*off)[l] = at;
+    worst = std::max(worst, at + size[l]);
+  }
+  return worst;
+}
+
+// A chain's launches are merged over its bands (kGrouped, kWhole) while what it keeps between
+// launches fits this. It is the size of the static array, so that lop_run_chain_static, which has
+// no more than that, runs the launches lop_run_chain does; and it is a quarter of the 256 MB
+// Infinity Cache, so that four chains in flight keep their intermediate rows on the chip. Larger
+// chains run band by band: their launches are long enough by themselves, and one band's rows
+// stay closer to the compute units than a whole chain's.
+constexpr size_t kMergeMaxBytes = LOP_STATIC_SCRATCH_BYTES;
+// A chain of row-wise operators has no halo, and callers that stream matrix rows run its bands one
+// by one: below this many rows its chain runs the bands' own launches (same sums in the same
+// order as lop_run_band).
+constexpr int kMergeMinRows = 2048;
+
+void size_scratch(lop_plan_t* P) {
+  const lop::Tables& t = P->t;
+  const int nl = t.n_layers(), nb = t.n_bands;
+  P->slab_off.assign(nb + 1, std::vector<size_t>(nl, 0));
+  auto kept = [&](int l) { return !P->fuse_band.away[l] || !P->fuse_chain.away[l]; };
+  auto rows_bytes = [&](int l, int rows) {
+    return rows > 0 && kept(l) ? align_up((size_t)t.in.n * rows * t.row_elems(l) * t.esz(), 256) : (size_t)0;
+  };
+  auto band_bytes = [&](int b, int l) { return rows_bytes(l, t.bands[b].need[l + 1].hi - t.bands[b].need[l + 1].lo); };
+  std::vector<size_t> size(nl, 0);
+
+  // the whole chain on full-height buffers
+  for (int l = 0; l + 1 < nl; ++l) size[l] = rows_bytes(l, t.layers[l].h_out);
+  const size_t whole = place_slabs(P, size, &P->slab_off[nb]);
+  // the slabs of bands [b0, b1) at once: one block per layer, the bands' slabs one behind the other in it
+  auto place_bands = [&](int b0, int b1) {
+    for (int l = 0; l + 1 < nl; ++l) {
+      size[l] = 0;
+      for (int b = b0; b < b1; ++b) size[l] += band_bytes(b, l);
+    }
+    std::vector<size_t> block(nl, 0);
+    const size_t bytes = place_slabs(P, size, &block);
+    for (int l = 0; l + 1 < nl; ++l) {
+      size_t off = block[l];
+      for (int b = b0; b < b1; ++b) {
+        P->slab_off[b][l] = off;
+        off += band_bytes(b, l);
+      }
+    }
+    return bytes;
+  };
+  auto place_groups = [&](int per) {
+    size_t most = 0;
+    for (int b = 0; b < nb; b += per) most = std::max(most, place_bands(b, std::min(nb, b + per)));
+    return most;
+  };
+
+  const bool rows_only = t.in.w == 1 && t.in.n * t.in.h < kMergeMinRows;
+  P->sched = ChainSched::kPerBand;
+  P->group = nb;
+  size_t grouped = 0;
+  if (P->batched) {
+    P->sched = ChainSched::kGrouped;
+    grouped = place_groups(nb);
+  } else if (P->flags & LOP_FLAG_PLAN_ONLY || (rows_only && nb > 1)) {
+    P->sched = ChainSched::kPerBand;
+  } else if (t.disjoint()) {
+    P->sched = whole <= kMergeMaxBytes ? ChainSched::kWhole : ChainSched::kPerBand;
+  } else {
+    // all bands in one group if they fit, else in as few equal groups, one after another, as do
+    bool all = true;
+    for (int l = 0; l < nl; ++l) all = all && (P->fuse_chain.away[l] || layer_batchable(P, l));
+    for (int groups = 1; groups < nb; ++groups) {
+      const int per = (nb + groups - 1) / groups;
+      if (per < 2 || (groups > 1 && !all)) break;
+      grouped = place_groups(per);
+      if (grouped > kMergeMaxBytes) continue;
+      P->sched = ChainSched::kGrouped;
+      P->group = per;
+      break;
+    }
+  }
+
+  size_t worst = P->sched == ChainSched::kWhole ? whole : 0;
   if (t.reuse) {
-    // bands share one full-height buffer per layer (rows at their absolute position)
+    // bands share one full-height buffer per layer (rows at their absolute position), kept from
+    // band to band
     size_t off = 0;
     for (int l = 0; l + 1 < nl; ++l) {
-      for (int b = 0; b < t.n_bands; ++b) P->slab_off[b][l] = off;
-      if (P->fused_away[l]) continue;
-      off += align_up((size_t)t.in.n * t.layers[l].h_out * t.row_elems(l) * t.esz(), 256);
+      for (int b = 0; b < nb; ++b) P->slab_off[b][l] = off;
+      off += rows_bytes(l, t.layers[l].h_out);
     }
-    worst = off;
+    worst = std::max(worst, off);
   } else {
-    size_t base = 0;
-    for (int b = 0; b < t.n_bands; ++b) {
-      // (with batched launches all bands' slabs are live at once: one band's follow the other's)
-      size_t off = P->batched ? base : 0;
-      for (int l = 0; l + 1 < nl; ++l) {  // the last layer writes the caller's output
-        const lop_rows_t r = t.bands[b].need[l + 1];
-        P->slab_off[b][l] = off;
-        if (r.hi > r.lo && !P->fused_away[l])
-          off += align_up((size_t)t.in.n * (r.hi - r.lo) * t.row_elems(l) * t.esz(), 256);
-      }
-      worst = off > worst ? off : worst;
-      base = off;
-    }
+    worst = std::max(worst, P->sched == ChainSched::kGrouped ? grouped : place_groups(1));
   }
   P->arena_bytes = worst;
 }
@@ -285,26 +389,28 @@ lop::OpLaunch make_launch(const lop_plan_t* P, int band, int l, const void* d_in
 // sizes here, not the scratch addresses).
 void size_workspace(lop_plan_t* P) {
   P->conv_ws_bytes = 0;
-  for (int b = 0; b < P->t.n_bands; ++b)
-    for (int l = 0; l < P->t.n_layers(); ++l) {
-      if (P->t.layers[l].d.op != LOP_CONV2D || P->fused_away[l] || P->fuse_head[l] >= 0) continue;
-      const lop_rows_t rr = P->t.bands[b].compute[l];
-      if (rr.hi <= rr.lo) continue;
-      const lop::OpLaunch o = make_launch(P, b, l, nullptr, nullptr);
-      const size_t need = lop::pointwise_applies(o) ? 0 : lop::conv_workspace_bytes(o);
-      P->conv_ws_bytes = std::max(need, P->conv_ws_bytes);
-    }
-  if (P->batched)   // a layer's launch for all bands keeps every band's partial sums at once
-    for (int l = 0; l < P->t.n_layers(); ++l) {
-      if (P->t.layers[l].d.op != LOP_CONV2D || P->fused_away[l] || P->fuse_head[l] >= 0) continue;
-      std::vector<lop::OpLaunch> group;
-      for (int b = 0; b < P->t.n_bands; ++b) {
-        const lop_rows_t rr = P->t.bands[b].compute[l];
-        if (rr.hi > rr.lo) group.push_back(make_launch(P, b, l, nullptr, nullptr));
-      }
-      if (group.empty() || lop::pointwise_applies(group[0])) continue;
+  const int nb = P->t.n_bands;
+  for (int l = 0; l < P->t.n_layers(); ++l) {
+    if (P->t.layers[l].d.op != LOP_CONV2D) continue;
+    auto alone = [&](const Fusion& F) { return !F.away[l] && F.head[l] < 0; };
+    auto add = [&](const std::vector<lop::OpLaunch>& group) {
+      if (group.empty() || lop::pointwise_applies(group[0])) return;
       P->conv_ws_bytes = std::max(lop::conv_workspace_bytes_bands(group.data(), (int)group.size()), P->conv_ws_bytes);
+    };
+    if (alone(P->fuse_band))
+      for (int b = 0; b < nb; ++b)
+        if (P->t.bands[b].compute[l].hi > P->t.bands[b].compute[l].lo) add({make_launch(P, b, l, nullptr, nullptr)});
+    if (!alone(P->fuse_chain)) continue;
+    if (P->sched == ChainSched::kWhole) add({make_launch(P, nb, l, nullptr, nullptr)});
+    if (P->sched == ChainSched::kGrouped) {  // a launch for several bands keeps all their partial sums at once
+      std::vector<lop::OpLaunch> group;
+      for (int b = 0; b <= nb; ++b) {
+        if (b == nb || b % P->group == 0 || (int)group.size() == lop::kMaxBandsPerLaunch) { add(group); group.clear(); }
+        if (b < nb && P->t.bands[b].compute[l].hi > P->t.bands[b].compute[l].lo)
+          group.push_back(make_launch(P, b, l, nullptr, nullptr));
+      }
     }
+  }
 }
 
 // Whether every launch of the plan has a kernel form that takes several bands.
@@ -312,9 +418,9 @@ bool all_launches_batchable(const lop_plan_t* P) {
   const lop::Tables& t = P->t;
   if (t.n_bands > lop::kMaxBandsPerLaunch) return false;
   for (int l = 0; l < t.n_layers(); ++l) {
-    if (P->fused_away[l]) continue;
-    if (P->fuse_head[l] >= 0) {
-      if (P->fuse_head[l] != l - 1) return false;   // an inverted-residual block
+    if (P->fuse_chain.away[l]) continue;
+    if (P->fuse_chain.head[l] >= 0) {
+      if (P->fuse_chain.head[l] != l - 1) return false;   // an inverted-residual block
       continue;
     }
     if (!lop::op_batchable(lop::describe_layer(P, l))) return false;
@@ -414,15 +520,17 @@ using lop::describe_layer;
 
 // Groups of three layers that run as one launch (an inverted-residual block): layer h a 1x1
 // conv, h + 1 a depthwise conv reading only h, h + 2 a 1x1 conv reading only h + 1, and
-// nobody else reads h or h + 1.
-void find_fused_groups(lop_plan_t* P) {
+// nobody else reads h or h + 1. Then groups of two: a dense conv and the 2 x 2 stride-2 max
+// pooling that is its only reader, where that pays for launches of one band (merged false) or
+// of all bands (merged true).
+void find_fused_groups(lop_plan_t* P, bool merged, Fusion* F) {
   const lop::Tables& t = P->t;
   const int nl = t.n_layers();
-  P->fuse_head.assign(nl, -1);
-  P->fused_away.assign(nl, 0);
+  F->head.assign(nl, -1);
+  F->away.assign(nl, 0);
   if (P->flags & (LOP_FLAG_NO_FUSE | LOP_FLAG_PLAN_ONLY)) return;
   for (int h = 0; h + 2 < nl; ++h) {
-    if (P->fused_away[h] || P->fuse_head[h] >= 0) continue;
+    if (F->away[h] || F->head[h] >= 0) continue;
     const int m = h + 1, q = h + 2;
     if (t.layers[m].d.input_from != h || t.layers[q].d.input_from != m) continue;
     bool shared = false;
@@ -434,16 +542,16 @@ void find_fused_groups(lop_plan_t* P) {
     }
     if (shared) continue;
     if (!lop::mbconv_applies(describe_layer(P, h), describe_layer(P, m), describe_layer(P, q))) continue;
-    P->fuse_head[q] = h;
-    P->fused_away[h] = P->fused_away[m] = 1;
+    F->head[q] = h;
+    F->away[h] = F->away[m] = 1;
     h = q;
   }
-  // Groups of two: a dense conv and the 2 x 2 stride-2 max pooling that is its only reader.
-  // The pooling windows do not overlap, so the rows of the conv a band computes are exactly
-  // twice its pooled rows, in both modes (checked, since the launch derives them that way).
+  // The pooling windows do not overlap, so the rows of the conv a launch computes are exactly
+  // twice its pooled rows, in every mode (checked, since the launch derives them that way).
+  const bool whole = t.disjoint();
   for (int h = 0; h + 1 < nl; ++h) {
     const int q = h + 1;
-    if (P->fused_away[h] || P->fuse_head[h] >= 0 || P->fused_away[q] || P->fuse_head[q] >= 0) continue;
+    if (F->away[h] || F->head[h] >= 0 || F->away[q] || F->head[q] >= 0) continue;
     if (t.layers[q].d.input_from != h) continue;
     bool shared = false;
     for (int j = 0; j < nl; ++j) {
@@ -456,55 +564,67 @@ void find_fused_groups(lop_plan_t* P) {
     const lop::LayerInfo& C = t.layers[h];
     const size_t esz = t.esz();
     if ((size_t)C.n * C.h_in * C.w_in * C.d.c_in * esz >= ((size_t)1 << 31)) continue;  // 32-bit offsets
-    bool rows_match = true;
-    for (int b = 0; b < t.n_bands; ++b) {
+    bool fits = true;
+    std::vector<lop::OpLaunch> convs;
+    auto take = [&](int b) {
       const lop_rows_t pr = t.bands[b].compute[q], cr = t.bands[b].compute[h];
-      if (pr.hi <= pr.lo) rows_match = rows_match && cr.hi <= cr.lo;
-      else rows_match = rows_match && cr.lo == 2 * pr.lo && cr.hi == 2 * pr.hi &&
-                        lop::convpool_pays(make_launch(P, b, h, nullptr, nullptr));
+      if (pr.hi <= pr.lo) { fits = fits && cr.hi <= cr.lo; return; }
+      fits = fits && cr.lo == 2 * pr.lo && cr.hi == 2 * pr.hi;
+      if (fits) convs.push_back(make_launch(P, b, h, nullptr, nullptr));
+    };
+    if (merged && whole) take(t.whole());
+    else for (int b = 0; b < t.n_bands; ++b) take(b);
+    if (!fits) continue;
+    if (merged) {
+      for (size_t at = 0; at < convs.size(); at += lop::kMaxBandsPerLaunch)
+        fits = fits && lop::convpool_pays_bands(&convs[at], (int)std::min<size_t>(lop::kMaxBandsPerLaunch, convs.size() - at));
+    } else {
+      for (const auto& c : convs) fits = fits && lop::convpool_pays_bands(&c, 1);
     }
-    if (!rows_match) continue;
-    P->fuse_head[q] = h;
-    P->fused_away[h] = 1;
+    if (!fits) continue;
+    F->head[q] = h;
+    F->away[h] = 1;
   }
 }
 
+// The groups of a band's own launches; a plan that asks for batched launches describes those.
+const Fusion& band_fusion(const lop_plan_t* P) { return P->batched ? P->fuse_chain : P->fuse_band; }
+
 // Whether layer l ends a conv + pooling group (else, if it ends a group, an inverted-residual block).
-bool ends_convpool(const lop_plan_t* P, int l) { return P->fuse_head[l] >= 0 && P->fuse_head[l] == l - 1; }
+bool ends_convpool(const Fusion& F, int l) { return F.head[l] >= 0 && F.head[l] == l - 1; }
 
 // The two descriptors of a conv + pooling launch of one band.
 void convpool_launches(const lop_plan_t* P, int band, int l, const void* d_in, void* d_out,
                        lop::OpLaunch* conv, lop::OpLaunch* pool) {
-  const int h = P->fuse_head[l];
   *pool = make_launch(P, band, l, d_in, d_out);
-  *conv = make_launch(P, band, h, d_in, d_out);   // (its y slab is never used: the layer has no buffer)
+  *conv = make_launch(P, band, l - 1, d_in, d_out);   // (its y slab is never used: the layer has no buffer)
 }
 
 // Rows of layer l one launch of band `band` produces (none for a layer that is part of a
 // later layer's launch).
-lop_rows_t launch_rows(const lop_plan_t* P, int band, int l) {
-  if (P->fused_away[l]) return lop_rows_t{0, 0};
+lop_rows_t launch_rows(const lop_plan_t* P, const Fusion& F, int band, int l) {
+  if (F.away[l]) return lop_rows_t{0, 0};
   return P->t.bands[band].compute[l];
 }
 
-// Enqueue what produces layer l's rows of one band: its own kernel(s), or the fused launch
-// of the group it ends.
-hipError_t launch_layer(const lop_plan_t* P, int band, int l, const void* d_in, void* d_out,
+// Enqueue what produces layer l's rows of one band (or, band t.whole(), of the whole chain): its
+// own kernel(s), or the fused launch of the group it ends.
+hipError_t launch_layer(const lop_plan_t* P, const Fusion& F, int band, int l, const void* d_in, void* d_out,
                         hipStream_t cs, lop::KernelEvents* ev = nullptr, void* y2 = nullptr) {
-  const lop_rows_t r = launch_rows(P, band, l);
+  const lop_rows_t r = launch_rows(P, F, band, l);
   if (r.hi <= r.lo) return hipSuccess;
-  if (P->fuse_head[l] < 0) {
+  if (F.head[l] < 0) {
     lop::OpLaunch o = make_launch(P, band, l, d_in, d_out);
     o.y2 = y2;
     return lop::launch_op(o, cs, ev);
   }
-  if (ends_convpool(P, l)) {
+  if (ends_convpool(F, l)) {
     lop::OpLaunch conv, pool;
     convpool_launches(P, band, l, d_in, d_out, &conv, &pool);
     pool.y2 = y2;
     return lop::launch_convpool(conv, pool, cs, ev);
   }
-  const int h = P->fuse_head[l];
+  const int h = F.head[l];
   lop::OpLaunch e = describe_layer(P, h), d = describe_layer(P, h + 1);
   const lop::OpLaunch p = make_launch(P, band, l, d_in, d_out);
   e.x = slab_of(P, band, P->t.layers[h].d.input_from, d_in, d_out);
@@ -513,10 +633,11 @@ hipError_t launch_layer(const lop_plan_t* P, int band, int l, const void* d_in, 
 
 // Kernel name (and reduction slices) of that launch.
 int describe_layer_launch(const lop_plan_t* P, int band, int l, char* name, size_t size) {
-  const lop_rows_t r = launch_rows(P, band, l);
+  const Fusion& F = P->fuse_band;
+  const lop_rows_t r = launch_rows(P, F, band, l);
   if (r.hi <= r.lo) return 0;
-  if (P->fuse_head[l] < 0) return lop::describe_op(make_launch(P, band, l, nullptr, nullptr), name, size);
-  if (ends_convpool(P, l)) {
+  if (F.head[l] < 0) return lop::describe_op(make_launch(P, band, l, nullptr, nullptr), name, size);
+  if (ends_convpool(F, l)) {
     lop::OpLaunch conv, pool;
     convpool_launches(P, band, l, nullptr, nullptr, &conv, &pool);
     return lop::convpool_describe(conv, pool, name, size);
@@ -529,19 +650,20 @@ int describe_layer_launch(const lop_plan_t* P, int band, int l, char* name, size
 // bytes of the group's input rows, output rows, residual and weights only.
 void launch_work(const lop_plan_t* P, int band, int l, double* flop, double* bytes) {
   const lop::Tables& t = P->t;
-  const lop_rows_t r = launch_rows(P, band, l);
+  const Fusion& F = band_fusion(P);
+  const lop_rows_t r = launch_rows(P, F, band, l);
   *flop = 0.0;
   *bytes = 0.0;
   if (r.hi <= r.lo) return;
-  if (P->fuse_head[l] < 0) {
+  if (F.head[l] < 0) {
     *flop = t.layer_flop(l, r.hi - r.lo);
     *bytes = t.layer_bytes(band, l);
     return;
   }
-  if (ends_convpool(P, l)) {
+  if (ends_convpool(F, l)) {
     // the conv's operations on twice the pooled rows plus the comparisons; bytes of the conv's
     // input rows and weights and of the pooled rows only
-    const int h = P->fuse_head[l];
+    const int h = F.head[l];
     const lop::LayerInfo &C = t.layers[h], &Q = t.layers[l];
     const lop_rows_t rd = t.bands[band].reads[h];
     *flop = t.layer_flop(h, 2 * (r.hi - r.lo)) + t.layer_flop(l, r.hi - r.lo);
@@ -550,7 +672,7 @@ void launch_work(const lop_plan_t* P, int band, int l, double* flop, double* byt
              e * (double)C.d.c_out * C.d.c_in * C.d.kh * C.d.kw;
     return;
   }
-  const int h = P->fuse_head[l], m = h + 1;
+  const int h = F.head[l], m = h + 1;
   const lop::LayerInfo &E = t.layers[h], &D = t.layers[m], &Q = t.layers[l];
   const int in_lo = std::max(r.lo * D.d.sh - D.d.ph, 0);
   const int in_hi = std::min((r.hi - 1) * D.d.sh - D.d.ph + D.d.kh, D.h_in);
@@ -578,16 +700,19 @@ constexpr size_t kDirectHostStoreMax = 256 * 1024;
 constexpr int kCopyWorkgroups = 4;
 constexpr size_t kCopyLaneMaxBytes = (size_t)64 << 20;
 
-// Device view of h_out if band `band` can deliver its rows that way, else nullptr.
-void* direct_host_target(lop_plan_t* P, int band, void* h_out) {
+// Device view of h_out if the launches of one band (merged false), or those of the whole chain,
+// can deliver their rows that way, else nullptr. The bound is on the bytes per band in either
+// form: a chain's last launch stores the rows of all its bands.
+void* direct_host_target(lop_plan_t* P, int band, void* h_out, bool merged) {
   if (!h_out || (P->flags & (LOP_FLAG_NO_D2H | LOP_FLAG_DMA_COPY))) return nullptr;
   const lop::Tables& t = P->t;
   const int last = t.n_layers() - 1;
-  if (P->fuse_head[last] >= 0 && !ends_convpool(P, last)) return nullptr;
-  const lop_rows_t r = t.bands[band].need[t.n_layers()];
+  const Fusion& F = merged ? P->fuse_chain : P->fuse_band;
+  if (F.head[last] >= 0 && !ends_convpool(F, last)) return nullptr;
+  const lop_rows_t r = t.bands[merged ? 0 : band].need[t.n_layers()];   // (the first band is the longest)
   const size_t bytes = (size_t)t.in.n * (r.hi - r.lo) * t.row_elems(last) * t.esz();
   if (bytes == 0 || bytes > kDirectHostStoreMax) return nullptr;
-  if (!ends_convpool(P, last) &&   // (the pooled launch stores to both destinations)
+  if (!ends_convpool(F, last) &&   // (the pooled launch stores to both destinations)
       !lop::stores_second_output(make_launch(P, band, last, nullptr, nullptr)))
     return nullptr;
   return device_view_of_host(P, h_out);
@@ -613,7 +738,7 @@ int enqueue_band_kernels(lop_plan_t* P, int band, const void* d_in, void* d_out,
     LOP_HIP(lop::launch_fill_words(P->ws_of(band), P->conv_ws_bytes / 16 * 16, 0xFFFFFFFFu, cs));
   }
   for (int l = 0; l < nl; ++l)
-    LOP_HIP(launch_layer(P, band, l, d_in, d_out, cs, nullptr, l == nl - 1 ? y2 : nullptr));
+    LOP_HIP(launch_layer(P, P->fuse_band, band, l, d_in, d_out, cs, nullptr, l == nl - 1 ? y2 : nullptr));
   return LOP_OK;
 }
 
@@ -634,7 +759,8 @@ void* device_view_of_host(lop_plan_t* P, void* h_out) {
   return dev;
 }
 
-// Copy the band's final rows of every image to the host buffer (same NHWC layout).
+// Copy the final rows of a band (t.whole(): all rows) of every image to the host buffer (same
+// NHWC layout).
 int enqueue_band_copy(lop_plan_t* P, int band, const void* d_out, void* h_out, hipStream_t s) {
   const lop::Tables& t = P->t;
   const lop_rows_t r = t.bands[band].need[t.n_layers()];
@@ -642,7 +768,9 @@ int enqueue_band_copy(lop_plan_t* P, int band, const void* d_out, void* h_out, h
   const lop::LayerInfo& L = t.layers.back();
   const size_t row_b = (size_t)t.row_elems(t.n_layers() - 1) * t.esz();
   const size_t img_b = row_b * L.h_out;
-  const size_t off = row_b * r.lo, len = row_b * (r.hi - r.lo);
+  const bool all = r.hi - r.lo == L.h_out;   // (the images' rows are then one contiguous run)
+  const int n = all ? 1 : t.in.n;
+  const size_t off = row_b * r.lo, len = row_b * (r.hi - r.lo) * (all ? t.in.n : 1);
   // Mapped pinned host memory is written by a small kernel on the copy stream (no DMA
   // set-up cost per band, and it can be captured like any kernel); a plan made with
   // LOP_FLAG_DMA_COPY goes through the runtime's copy engines instead. Host memory that is
@@ -652,16 +780,15 @@ int enqueue_band_copy(lop_plan_t* P, int band, const void* d_out, void* h_out, h
   if (!mapped) return LOP_ERR_INVALID_ARG;
   if (P->flags & LOP_FLAG_DMA_COPY) mapped = nullptr;
   if (mapped) {
-    LOP_HIP(lop::launch_copy_rows((char*)mapped + off, (const char*)d_out + off, img_b, len,
-                                  t.in.n, s, kCopyWorkgroups));
+    LOP_HIP(lop::launch_copy_rows((char*)mapped + off, (const char*)d_out + off, img_b, len, n, s, kCopyWorkgroups));
     return LOP_OK;
   }
-  if (t.in.n == 1) {
+  if (n == 1) {
     LOP_HIP(hipMemcpyAsync((char*)h_out + off, (const char*)d_out + off, len,
                            hipMemcpyDeviceToHost, s));
   } else {
-    LOP_HIP(hipMemcpy2DAsync((char*)h_out + off, img_b, (const char*)d_out + off, img_b, len,
-                             t.in.n, hipMemcpyDeviceToHost, s));
+    LOP_HIP(hipMemcpy2DAsync((char*)h_out + off, img_b, (const char*)d_out + off, img_b, len, n,
+                             hipMemcpyDeviceToHost, s));
   }
   return LOP_OK;
 }
@@ -688,7 +815,9 @@ int setup_device(lop_plan_t* P) {
   for (int b = 0; b < nb; ++b) live += band_empty(P, b) ? 0 : 1;
   int want = (int)((P->flags >> 8) & 0xff);
   if (want == 0) want = LOP_DEFAULT_LANES;
-  const int n_lanes = P->t.reuse || P->batched ? std::max(1, want) : std::max(1, std::min(want, live));
+  // (chains that run on one lane each rotate over all of them, however few bands they have)
+  const bool by_chain = P->t.reuse || P->sched != ChainSched::kPerBand;
+  const int n_lanes = by_chain ? std::max(1, want) : std::max(1, std::min(want, live));
   P->lanes.assign(n_lanes, Lane{});
   // Long band copies (stores into host memory, paced by the link) get a lane of their own.
   // On a compute lane a copy holds up that lane's next band, and because the bands are equal
@@ -709,7 +838,7 @@ int setup_device(lop_plan_t* P) {
   // output per call: 215 calls/s with the copy lane, 350 with copies on every lane, which
   // together reach the link's rate). The plan does not know the kernels' time; the bound on the
   // bytes stands for it.
-  P->copy_lane = !P->t.reuse && !P->batched && n_lanes >= 3 && longest_copy > kDirectHostStoreMax &&
+  P->copy_lane = !by_chain && n_lanes >= 3 && longest_copy > kDirectHostStoreMax &&
                  all_copies <= kCopyLaneMaxBytes &&
                  !(P->flags & (LOP_FLAG_NO_D2H | LOP_FLAG_DMA_COPY));
   for (Lane& L : P->lanes) {
@@ -743,7 +872,7 @@ int enqueue_band(lop_plan_t* P, int band, const void* d_in, void* d_out, void* h
   if (P->copied_valid[band] && !capturing)
     LOP_HIP(hipStreamWaitEvent(cs, P->ev_copied[band], 0));
   if (timing) LOP_HIP(hipEventRecord(P->ev_c0[band], cs));
-  void* const direct = direct_host_target(P, band, h_out);
+  void* const direct = direct_host_target(P, band, h_out, false);
   int rc = enqueue_band_kernels(P, band, d_in, d_out, cs, direct);
   if (rc != LOP_OK) return rc;
   if (timing) LOP_HIP(hipEventRecord(P->ev_c1[band], cs));
@@ -828,22 +957,18 @@ int enqueue_chain_reuse(lop_plan_t* P, const void* d_in, void* d_out, void* h_ou
   return LOP_OK;
 }
 
-// The descriptors of layer l's launch for all bands (convs: the conv of a conv + pooling group,
-// else empty). y2 of band b is its direct host target when h_out is given (last layer only).
-void batched_group(lop_plan_t* P, int l, const void* d_in, void* d_out, void* h_out,
-                   std::vector<lop::OpLaunch>* group, std::vector<lop::OpLaunch>* convs,
-                   std::vector<char>* direct) {
+// The descriptors of layer l's launch for bands [first, last) (convs: the conv of a conv + pooling
+// group, else empty).
+void batched_group(const lop_plan_t* P, int l, int first, int last, const void* d_in, void* d_out, void* y2,
+                   std::vector<lop::OpLaunch>* group, std::vector<lop::OpLaunch>* convs) {
   group->clear();
   convs->clear();
-  for (int b = 0; b < P->t.n_bands; ++b) {
-    const lop_rows_t r = launch_rows(P, b, l);
+  for (int b = first; b < last; ++b) {
+    const lop_rows_t r = launch_rows(P, P->fuse_chain, b, l);
     if (r.hi <= r.lo) continue;
     lop::OpLaunch o = make_launch(P, b, l, d_in, d_out);
-    if (h_out) {
-      o.y2 = direct_host_target(P, b, h_out);
-      if (direct) (*direct)[b] = o.y2 != nullptr;
-    }
-    if (ends_convpool(P, l)) {
+    o.y2 = y2;
+    if (ends_convpool(P->fuse_chain, l)) {
       lop::OpLaunch conv, pool;
       convpool_launches(P, b, l, d_in, d_out, &conv, &pool);
       pool.y2 = o.y2;
@@ -855,24 +980,44 @@ void batched_group(lop_plan_t* P, int l, const void* d_in, void* d_out, void* h_
   }
 }
 
-// One launch (plus its finish kernel, if the reduction is cut) for layer l of every band.
-hipError_t launch_layer_batched(lop_plan_t* P, int l, const void* d_in, void* d_out, hipStream_t cs,
-                                lop::KernelEvents* ev, void* h_out, std::vector<char>* direct) {
-  if (P->fused_away[l]) return hipSuccess;
-  std::vector<lop::OpLaunch> group, convs;
-  batched_group(P, l, d_in, d_out, h_out, &group, &convs, direct);
-  if (group.empty()) return hipSuccess;
-  if (ends_convpool(P, l)) return lop::launch_convpool_bands(convs.data(), group.data(), (int)group.size(), cs, ev);
-  return lop::launch_op_bands(group.data(), (int)group.size(), cs, ev);
+// Whether the launch that ends with layer l has a form that takes several bands.
+bool layer_batchable(const lop_plan_t* P, int l) {
+  if (P->fuse_chain.head[l] >= 0) return ends_convpool(P->fuse_chain, l);
+  return lop::op_batchable(describe_layer(P, l));
 }
 
-// Kernel name and reduction slices of that launch.
-int describe_layer_batched(const lop_plan_t* P, int l, char* name, size_t size) {
-  if (P->fused_away[l]) return 0;
+// Layer l of bands [first, last): one launch (plus its finish kernel, if the reduction is cut) per
+// kMaxBandsPerLaunch bands; one per band where the kernel takes no more.
+hipError_t launch_layer_batched(const lop_plan_t* P, int l, int first, int last, const void* d_in, void* d_out, hipStream_t cs,
+                                lop::KernelEvents* ev, void* y2) {
+  if (P->fuse_chain.away[l]) return hipSuccess;
+  if (!layer_batchable(P, l)) {
+    for (int b = first; b < last; ++b) {
+      const hipError_t e = launch_layer(P, P->fuse_chain, b, l, d_in, d_out, cs, ev, y2);
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+  }
   std::vector<lop::OpLaunch> group, convs;
-  batched_group(const_cast<lop_plan_t*>(P), l, nullptr, nullptr, nullptr, &group, &convs, nullptr);
+  for (; first < last; first += lop::kMaxBandsPerLaunch) {
+    batched_group(P, l, first, std::min(last, first + lop::kMaxBandsPerLaunch), d_in, d_out, y2, &group, &convs);
+    if (group.empty()) continue;
+    const hipError_t e = ends_convpool(P->fuse_chain, l)
+                             ? lop::launch_convpool_bands(convs.data(), group.data(), (int)group.size(), cs, ev)
+                             : lop::launch_op_bands(group.data(), (int)group.size(), cs, ev);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
+// Kernel name and reduction slices of that launch (of a plan made with LOP_FLAG_BATCH_BANDS).
+int describe_layer_batched(const lop_plan_t* P, int l, char* name, size_t size) {
+  if (P->fuse_chain.away[l]) return 0;
+  std::vector<lop::OpLaunch> group, convs;
+  batched_group(P, l, 0, P->t.n_bands, nullptr, nullptr, nullptr, &group, &convs);
   if (group.empty()) return 0;
-  if (ends_convpool(P, l)) return lop::convpool_describe_bands(convs.data(), group.data(), (int)group.size(), name, size);
+  if (ends_convpool(P->fuse_chain, l))
+    return lop::convpool_describe_bands(convs.data(), group.data(), (int)group.size(), name, size);
   return lop::describe_op_bands(group.data(), (int)group.size(), name, size);
 }
 
@@ -880,21 +1025,46 @@ int describe_layer_batched(const lop_plan_t* P, int l, char* name, size_t size) 
 // band that computes rows of it (-1: nobody does).
 int batched_owner(const lop_plan_t* P, int l) {
   for (int b = 0; b < P->t.n_bands; ++b) {
-    const lop_rows_t r = launch_rows(P, b, l);
+    const lop_rows_t r = launch_rows(P, P->fuse_chain, b, l);
     if (r.hi > r.lo) return b;
   }
   return -1;
 }
 
-// A chain whose launches are batched over the bands (Sec. IV-D operation batching), on one
-// lane: per layer one launch that computes every band's rows on that band's slabs, then the
-// bands' rows to the host (through the last launch's own stores where a band is small enough,
-// else by copies behind it).
-int enqueue_chain_batched(lop_plan_t* P, const void* d_in, void* d_out, void* h_out, bool timing,
-                          bool capturing) {
-  Lane& L = P->lanes[P->cur_lane];
-  hipStream_t cs = L.stream;
-  const int nb = P->t.n_bands, nl = P->t.n_layers();
+// Scratch of a chain while it is enqueued: a lane's, or the static array's.
+struct ChainScratch {
+  lop_plan_t* P;
+  ChainScratch(lop_plan_t* plan, void* arena, void* ws) : P(plan) { P->arena_override = arena; P->ws_override = ws; }
+  ~ChainScratch() { P->arena_override = nullptr; P->ws_override = nullptr; }
+};
+
+// The kernels of a chain whose launches are merged over the bands (kGrouped, kWhole), on one
+// stream, with the scratch set by the caller. y2: where the last launch also stores its rows.
+int enqueue_merged_kernels(lop_plan_t* P, const void* d_in, void* d_out, hipStream_t cs, void* y2) {
+  const int nl = P->t.n_layers(), whole = P->t.whole();
+  if (P->flags & LOP_FLAG_POISON_SCRATCH) {
+    LOP_HIP(lop::launch_fill_words(P->arena_of(0), align_up(P->arena_bytes, 256), 0xFFFFFFFFu, cs));
+    LOP_HIP(lop::launch_fill_words(P->ws_of(0), P->conv_ws_bytes / 16 * 16, 0xFFFFFFFFu, cs));
+  }
+  const int nb = P->t.n_bands;
+  if (P->sched == ChainSched::kWhole) {
+    for (int l = 0; l < nl; ++l)
+      LOP_HIP(launch_layer(P, P->fuse_chain, whole, l, d_in, d_out, cs, nullptr, l == nl - 1 ? y2 : nullptr));
+    return LOP_OK;
+  }
+  for (int b = 0; b < nb; b += P->group)
+    for (int l = 0; l < nl; ++l)
+      LOP_HIP(launch_layer_batched(P, l, b, std::min(nb, b + P->group), d_in, d_out, cs, nullptr,
+                                   l == nl - 1 ? y2 : nullptr));
+  return LOP_OK;
+}
+
+// A chain whose launches are merged over the bands (Sec. IV-D operation batching), on one lane's
+// scratch and on stream `cs`: per layer one launch for the rows of all bands, then the rows to
+// the host (through the last launch's own stores where they are few, else by a copy behind it).
+int enqueue_chain_merged(lop_plan_t* P, Lane& L, const void* d_in, void* d_out, void* h_out, hipStream_t cs,
+                         bool timing, bool capturing) {
+  const int nb = P->t.n_bands;
   const bool copy = h_out && !(P->flags & LOP_FLAG_NO_D2H);
   if (!capturing)
     for (int b = 0; b < nb; ++b)
@@ -902,32 +1072,51 @@ int enqueue_chain_batched(lop_plan_t* P, const void* d_in, void* d_out, void* h_
         LOP_HIP(hipStreamWaitEvent(cs, P->ev_copied[b], 0));
         P->copied_valid[b] = 0;
       }
-  if (P->flags & LOP_FLAG_POISON_SCRATCH) {
-    LOP_HIP(lop::launch_fill_words(P->arena_of(0), align_up(P->arena_bytes, 256), 0xFFFFFFFFu, cs));
-    LOP_HIP(lop::launch_fill_words(P->ws_of(0), P->conv_ws_bytes / 16 * 16, 0xFFFFFFFFu, cs));
-  }
   if (timing)
     for (int b = 0; b < nb; ++b)
       if (!band_empty(P, b)) LOP_HIP(hipEventRecord(P->ev_c0[b], cs));
-  std::vector<char> direct(nb, 0);
-  for (int l = 0; l < nl; ++l)
-    LOP_HIP(launch_layer_batched(P, l, d_in, d_out, cs, nullptr, l == nl - 1 && copy ? h_out : nullptr, &direct));
-  for (int b = 0; b < nb; ++b) {
-    if (band_empty(P, b)) continue;
-    if (timing) {
-      LOP_HIP(hipEventRecord(P->ev_c1[b], cs));
-      LOP_HIP(hipEventRecord(P->ev_d0[b], cs));
-    }
-    if (copy && !direct[b]) {
-      int rc = enqueue_band_copy(P, b, d_out, h_out, cs);
-      if (rc != LOP_OK) return rc;
-    }
-    if (timing) LOP_HIP(hipEventRecord(P->ev_d1[b], cs));
-    if (copy && !capturing) {
-      LOP_HIP(hipEventRecord(P->ev_copied[b], cs));
-      P->copied_valid[b] = 1;
-    }
+  ChainScratch scratch(P, L.arena, L.conv_ws);
+  const int any = P->sched == ChainSched::kWhole ? P->t.whole() : 0;
+  void* const direct = copy ? direct_host_target(P, any, h_out, true) : nullptr;
+  int rc = enqueue_merged_kernels(P, d_in, d_out, cs, direct);
+  if (rc != LOP_OK) return rc;
+  if (timing)
+    for (int b = 0; b < nb; ++b)
+      if (!band_empty(P, b)) {
+        LOP_HIP(hipEventRecord(P->ev_c1[b], cs));
+        LOP_HIP(hipEventRecord(P->ev_d0[b], cs));
+      }
+  if (copy && !direct) {
+    rc = enqueue_band_copy(P, P->t.whole(), d_out, h_out, cs);
+    if (rc != LOP_OK) return rc;
   }
+  if (timing)
+    for (int b = 0; b < nb; ++b)
+      if (!band_empty(P, b)) LOP_HIP(hipEventRecord(P->ev_d1[b], cs));
+  return LOP_OK;
+}
+
+// Orders stream `s` behind everything that may still use the lane's scratch, or still copies out
+// of the output buffer that is about to be written, and notes that `s` uses the scratch next.
+int take_lane(lop_plan_t* P, Lane& L, hipStream_t s, const void* d_out) {
+  for (Lane& O : P->lanes) {
+    const bool mine = &O == &L;
+    if (!mine && (!O.copying || O.copying != d_out)) continue;
+    if (!O.user) {
+      if (s == O.stream) continue;   // (stream order)
+      LOP_HIP(hipEventRecord(O.ev_join, O.stream));
+    }
+    LOP_HIP(hipStreamWaitEvent(s, O.ev_join, 0));
+    if (!mine) O.copying = nullptr;
+  }
+  L.user = s == L.stream ? nullptr : s;
+  L.copying = nullptr;
+  return LOP_OK;
+}
+
+// Marks the end of a use of the lane's scratch on a stream that is not the lane's own.
+int leave_lane(Lane& L) {
+  if (L.user) LOP_HIP(hipEventRecord(L.ev_join, L.user));
   return LOP_OK;
 }
 
@@ -942,13 +1131,39 @@ int enqueue_lane(lop_plan_t* P, int lane, const void* d_in, void* d_out, void* h
   return LOP_OK;
 }
 
+hipGraphExec_t find_graph(const lop_plan_t* P, const void* d_in, const void* d_out, const void* h_out, int lane,
+                          int band) {
+  for (const auto& g : P->graphs)
+    if (g.d_in == d_in && g.d_out == d_out && g.h_out == h_out && g.lane == lane && g.band == band) return g.exec;
+  return nullptr;
+}
+
+// Instantiates what was captured (rc, e: how enqueueing and ending the capture went) and keeps it.
+int keep_graph(lop_plan_t* P, int rc, hipError_t e, hipGraph_t graph, const void* d_in, void* d_out, void* h_out,
+               int lane, int band, hipGraphExec_t* exec) {
+  if (rc != LOP_OK) {
+    if (graph) (void)hipGraphDestroy(graph);
+    return rc;
+  }
+  if (e != hipSuccess) return hip_fail(e);
+  e = hipGraphInstantiate(exec, graph, nullptr, nullptr, 0);
+  (void)hipGraphDestroy(graph);
+  if (e != hipSuccess) return hip_fail(e);
+  if (P->graphs.size() >= 128) {  // bounded cache: drop the oldest
+    (void)hipGraphExecDestroy(P->graphs.front().exec);
+    P->graphs.erase(P->graphs.begin());
+  }
+  P->graphs.push_back({d_in, d_out, h_out, lane, band, *exec});
+  return LOP_OK;
+}
+
 // lane_only >= 0 (independent mode): the graph holds that lane's bands only and runs on the
 // lane's stream `ms`; -1: the whole chain forked from and joined into `ms`.
 // band_only >= 0: the graph holds that band's kernels and nothing else (its copy is the
 // caller's business).
 int launch_graph(lop_plan_t* P, const void* d_in, void* d_out, void* h_out, hipStream_t ms,
                  int lane_only = -1, int band_only = -1) {
-  const int lane = P->t.reuse || P->batched ? P->cur_lane : (lane_only >= 0 ? lane_only : -1);
+  const int lane = lane_only >= 0 ? lane_only : P->t.reuse ? P->cur_lane : -1;
   // an eager run may still have copies of the output rows in flight (on a copy stream that the
   // graph's stream is not ordered behind): a replay, and the first capture, wait for them
   for (int b = 0; b < P->t.n_bands; ++b)
@@ -956,37 +1171,70 @@ int launch_graph(lop_plan_t* P, const void* d_in, void* d_out, void* h_out, hipS
       LOP_HIP(hipStreamWaitEvent(ms, P->ev_copied[b], 0));
       P->copied_valid[b] = 0;
     }
-  for (const auto& g : P->graphs)
-    if (g.d_in == d_in && g.d_out == d_out && g.h_out == h_out && g.lane == lane &&
-        g.band == band_only) {
-      LOP_HIP(hipGraphLaunch(g.exec, ms));
-      return LOP_OK;
-    }
+  if (hipGraphExec_t exec = find_graph(P, d_in, d_out, h_out, lane, band_only)) {
+    LOP_HIP(hipGraphLaunch(exec, ms));
+    return LOP_OK;
+  }
   if (h_out) (void)device_view_of_host(P, h_out);  // query before capture starts
   hipGraph_t graph = nullptr;
   LOP_HIP(hipStreamBeginCapture(ms, hipStreamCaptureModeThreadLocal));
   int rc = band_only >= 0 ? enqueue_band_kernels(P, band_only, d_in, d_out, ms)
-           : P->batched  ? enqueue_chain_batched(P, d_in, d_out, h_out, false, true)
            : P->t.reuse  ? enqueue_chain_reuse(P, d_in, d_out, h_out, false, true)
            : lane_only >= 0 ? enqueue_lane(P, lane_only, d_in, d_out, h_out, true)
                             : enqueue_chain(P, d_in, d_out, h_out, ms, false, true);
   hipError_t e = hipStreamEndCapture(ms, &graph);
-  if (rc != LOP_OK) {
-    if (graph) (void)hipGraphDestroy(graph);
-    return rc;
-  }
-  if (e != hipSuccess) return hip_fail(e);
   hipGraphExec_t exec = nullptr;
-  e = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
-  (void)hipGraphDestroy(graph);
-  if (e != hipSuccess) return hip_fail(e);
-  if (P->graphs.size() >= 128) {  // bounded cache: drop the oldest
-    (void)hipGraphExecDestroy(P->graphs.front().exec);
-    P->graphs.erase(P->graphs.begin());
-  }
-  P->graphs.push_back({d_in, d_out, h_out, lane, band_only, exec});
+  rc = keep_graph(P, rc, e, graph, d_in, d_out, h_out, lane, band_only, &exec);
+  if (rc != LOP_OK) return rc;
   LOP_HIP(hipGraphLaunch(exec, ms));
   return LOP_OK;
+}
+
+// A merged chain as a graph: captured on lane `lane`'s own stream (with that lane's scratch),
+// replayed on `s`.
+int launch_graph_merged(lop_plan_t* P, int lane, const void* d_in, void* d_out, void* h_out, hipStream_t s) {
+  Lane& L = P->lanes[lane];
+  for (int b = 0; b < P->t.n_bands; ++b)   // copies of single bands that an earlier call has in flight
+    if (P->copied_valid[b]) {
+      LOP_HIP(hipStreamWaitEvent(s, P->ev_copied[b], 0));
+      P->copied_valid[b] = 0;
+    }
+  hipGraphExec_t exec = find_graph(P, d_in, d_out, h_out, lane, -1);
+  if (!exec) {
+    if (h_out) (void)device_view_of_host(P, h_out);  // query before capture starts
+    hipGraph_t graph = nullptr;
+    LOP_HIP(hipStreamBeginCapture(L.stream, hipStreamCaptureModeThreadLocal));
+    int rc = enqueue_chain_merged(P, L, d_in, d_out, h_out, L.stream, false, true);
+    const hipError_t e = hipStreamEndCapture(L.stream, &graph);
+    rc = keep_graph(P, rc, e, graph, d_in, d_out, h_out, lane, -1, &exec);
+    if (rc != LOP_OK) return rc;
+  }
+  LOP_HIP(hipGraphLaunch(exec, s));
+  return LOP_OK;
+}
+
+// One merged chain: picks a lane, orders the chain behind what it must not overtake and enqueues
+// it on the caller's stream, or on the lane's own where there is none to order against (chains
+// of consecutive calls then overlap).
+int run_merged(lop_plan_t* P, const void* d_in, void* d_out, void* h_out, hipStream_t user, bool timing) {
+  int lane = P->next_lane;
+  if (user)   // (a caller's stream runs its chains one after another: it stays on the lane it used last)
+    for (int k = 0; k < (int)P->lanes.size(); ++k)
+      if (P->lanes[k].user == user) lane = k;
+  if (lane == P->next_lane) P->next_lane = (P->next_lane + 1) % (int)P->lanes.size();
+  P->cur_lane = lane;
+  Lane& L = P->lanes[lane];
+  hipStream_t s = user ? user : L.stream;
+  int rc = take_lane(P, L, s, d_out);
+  if (rc != LOP_OK) return rc;
+  if (timing) LOP_HIP(hipEventRecord(P->ev_t0, s));
+  rc = (P->flags & LOP_FLAG_GRAPH) && !timing ? launch_graph_merged(P, lane, d_in, d_out, h_out, s)
+                                              : enqueue_chain_merged(P, L, d_in, d_out, h_out, s, timing, false);
+  if (rc != LOP_OK) return rc;
+  if (timing) LOP_HIP(hipEventRecord(P->ev_t1, s));
+  const int any = P->sched == ChainSched::kWhole ? P->t.whole() : 0;
+  if (h_out && !(P->flags & LOP_FLAG_NO_D2H) && !direct_host_target(P, any, h_out, true)) L.copying = d_out;
+  return leave_lane(L);
 }
 
 // Copy-lane schedule of one band: its kernels on compute stream `cs` (as a graph of their own
@@ -1041,7 +1289,8 @@ int lop_plan(const lop_layer_t* layers, int n_layers, const lop_tensor_desc_t* i
     P->has_wstem[l] = lop::stem_shape_applies(d.c_in, d.c_out, d.kh, d.kw, d.sw, d.dh, d.dw,
                                               d.residual_from != LOP_NO_RESIDUAL);
   }
-  find_fused_groups(P);
+  find_fused_groups(P, false, &P->fuse_band);
+  find_fused_groups(P, true, &P->fuse_chain);
   if (flags & LOP_FLAG_BATCH_BANDS) {
     if (flags & LOP_FLAG_REUSE) { delete P; return LOP_ERR_INVALID_ARG; }
     if (!all_launches_batchable(P)) { delete P; return LOP_ERR_UNSUPPORTED; }
@@ -1213,7 +1462,10 @@ int lop_run_band(lop_plan_t* P, int band, const void* d_in, void* d_out, void* h
   hipStream_t cs = compute_stream ? (hipStream_t)compute_stream : P->lane_of(band).stream;
   hipStream_t ds = copy_stream ? (hipStream_t)copy_stream : P->s_copy;
   if (compute_stream) P->last_user_stream = cs;
-  return enqueue_band(P, band, d_in, d_out, h_out, cs, ds, false);
+  Lane& L = P->lane_of(band);
+  int rc = take_lane(P, L, cs, nullptr);
+  if (rc == LOP_OK) rc = enqueue_band(P, band, d_in, d_out, h_out, cs, ds, false);
+  return rc == LOP_OK ? leave_lane(L) : rc;
 }
 
 int lop_run_chain(lop_plan_t* P, const void* d_in, void* d_out, void* h_out, void* compute_stream,
@@ -1242,7 +1494,18 @@ int lop_run_chain(lop_plan_t* P, const void* d_in, void* d_out, void* h_out, voi
     }
     return LOP_OK;
   }
-  if (P->t.reuse || P->batched) {
+  // (with timing the bands of a plan that did not ask for batched launches run one by one, so
+  // that each has a start and an end of its own)
+  const bool merged = P->sched != ChainSched::kPerBand && (!timing || P->batched);
+  if (!merged)
+    for (Lane& L : P->lanes) {   // a merged chain of the caller's stream may still use a lane's scratch
+      int rc = take_lane(P, L, L.stream, nullptr);
+      if (rc != LOP_OK) return rc;
+    }
+  if (merged) {
+    int rc = run_merged(P, d_in, d_out, h_out, compute_stream ? ms : nullptr, timing != nullptr);
+    if (rc != LOP_OK) return rc;
+  } else if (P->t.reuse) {
     // the whole chain runs on one lane; chains of consecutive calls rotate over the lanes
     // and overlap unless the caller's stream orders them
     P->cur_lane = P->next_lane;
@@ -1255,8 +1518,7 @@ int lop_run_chain(lop_plan_t* P, const void* d_in, void* d_out, void* h_out, voi
     if (timing) LOP_HIP(hipEventRecord(P->ev_t0, L.stream));
     int rc = ((P->flags & LOP_FLAG_GRAPH) && !timing)
                  ? launch_graph(P, d_in, d_out, h_out, L.stream)
-                 : P->batched ? enqueue_chain_batched(P, d_in, d_out, h_out, timing != nullptr, false)
-                              : enqueue_chain_reuse(P, d_in, d_out, h_out, timing != nullptr, false);
+                 : enqueue_chain_reuse(P, d_in, d_out, h_out, timing != nullptr, false);
     if (rc != LOP_OK) return rc;
     if (timing) LOP_HIP(hipEventRecord(P->ev_t1, L.stream));
     if (compute_stream) {
@@ -1314,13 +1576,11 @@ int lop_run_chain_static(lop_plan_t* P, const void* d_in, void* d_out, void* str
   // Nothing in the array has to start at zero: a band's slabs are written by the layer that
   // produces them before any layer reads them, and a launch's partial sums by its slices
   // before its finish kernel adds them, so the contents left by the last call do not matter.
-  P->arena_override = base;
-  P->ws_override = P->conv_ws_bytes ? base + arena : nullptr;
+  ChainScratch scratch(P, base, P->conv_ws_bytes ? base + arena : nullptr);
+  if (P->sched != ChainSched::kPerBand) return enqueue_merged_kernels(P, d_in, d_out, (hipStream_t)stream, nullptr);
   int rc = LOP_OK;
   for (int b = 0; b < P->t.n_bands && rc == LOP_OK; ++b)
     if (!band_empty(P, b)) rc = enqueue_band_kernels(P, b, d_in, d_out, (hipStream_t)stream);
-  P->arena_override = nullptr;
-  P->ws_override = nullptr;
   return rc;
 }
 
@@ -1329,6 +1589,7 @@ int lop_synchronize(lop_plan_t* P) {
   if (!P->ready) return LOP_ERR_NOT_READY;
   if (P->last_user_stream) LOP_HIP(hipStreamSynchronize(P->last_user_stream));
   for (Lane& L : P->lanes) {
+    if (L.user) LOP_HIP(hipEventSynchronize(L.ev_join));
     LOP_HIP(hipStreamSynchronize(L.stream));
     LOP_HIP(hipStreamSynchronize(L.copy));
   }
@@ -1345,14 +1606,14 @@ int lop_time_layer(lop_plan_t* P, int band, int layer, const void* d_in, void* d
     return LOP_ERR_BAND_RANGE;
   if (!P->ready) return LOP_ERR_NOT_READY;
   *ms_per_launch = 0.f;
-  const lop_rows_t r = launch_rows(P, band, layer);
+  const lop_rows_t r = launch_rows(P, band_fusion(P), band, layer);
   if (r.hi <= r.lo) return LOP_OK;
   int rc = ensure_timing_events(P);
   if (rc != LOP_OK) return rc;
   hipStream_t cs = P->s_main;
-  LOP_HIP(launch_layer(P, band, layer, d_in, d_out, cs));  // warm-up
+  LOP_HIP(launch_layer(P, band_fusion(P), band, layer, d_in, d_out, cs));  // warm-up
   LOP_HIP(hipEventRecord(P->ev_c0[0], cs));
-  for (int i = 0; i < iters; ++i) LOP_HIP(launch_layer(P, band, layer, d_in, d_out, cs));
+  for (int i = 0; i < iters; ++i) LOP_HIP(launch_layer(P, band_fusion(P), band, layer, d_in, d_out, cs));
   LOP_HIP(hipEventRecord(P->ev_c1[0], cs));
   LOP_HIP(hipStreamSynchronize(cs));
   float ms = 0.f;
@@ -1402,15 +1663,15 @@ int lop_profile_chain(lop_plan_t* P, const void* d_in, void* d_out, int iters, f
     for (int it = 0; it < iters; ++it) {
       for (int b = 0; b < nb; ++b)
         for (int l = 0; l < nl; ++l) {
-          const lop_rows_t r = launch_rows(P, b, l);
+          const lop_rows_t r = launch_rows(P, band_fusion(P), b, l);
           if (r.hi <= r.lo) continue;
           if (P->batched && batched_owner(P, l) != b) continue;  // (timed with the band that owns the launch)
           const size_t i = ((size_t)b * nl + l) * 4;
           lop::KernelEvents ke;
           ke.start[0] = ev[i]; ke.stop[0] = ev[i + 1];
           ke.start[1] = ev[i + 2]; ke.stop[1] = ev[i + 3];
-          if (P->batched) LOP_HIP(launch_layer_batched(P, l, d_in, d_out, cs, &ke, nullptr, nullptr));
-          else LOP_HIP(launch_layer(P, b, l, d_in, d_out, cs, &ke));
+          if (P->batched) LOP_HIP(launch_layer_batched(P, l, 0, nb, d_in, d_out, cs, &ke, nullptr));
+          else LOP_HIP(launch_layer(P, P->fuse_band, b, l, d_in, d_out, cs, &ke));
           used[b * nl + l] = ke.n;
         }
       LOP_HIP(hipStreamSynchronize(cs));

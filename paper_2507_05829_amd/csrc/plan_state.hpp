@@ -25,9 +25,30 @@ int hip_fail(hipError_t e);
 struct Lane {
   hipStream_t stream = nullptr;
   hipStream_t copy = nullptr;  // reuse mode: this lane's copies overlap its next band
-  void* arena = nullptr;    // scratch slabs of one band at a time
+  void* arena = nullptr;    // scratch slabs of one band (or of one whole chain) at a time
   void* conv_ws = nullptr;  // split-K partial sums of one launch at a time
   hipEvent_t ev_join = nullptr;
+  // The stream of the caller's that last used this lane's scratch (ev_join was recorded behind
+  // that use), or nullptr when the lane's own stream did.
+  hipStream_t user = nullptr;
+  // Output buffer that the lane's last chain still copies to the host with a kernel behind its
+  // last layer, or nullptr: another lane must not overwrite it before that.
+  const void* copying = nullptr;
+};
+
+// Layers that run as one launch: head[t] = first layer of the group whose last layer is t
+// (else -1); away[l] = 1 for the layers of a group before its last (no launch of their own).
+struct Fusion {
+  std::vector<int> head;
+  std::vector<char> away;
+};
+
+// How lop_run_chain (without timing) and lop_run_chain_static run a chain.
+enum class ChainSched {
+  kPerBand,  // a launch per band and layer, the bands dealt to the lanes
+  kGrouped,  // a launch per layer that computes a group of bands, each band on its own slabs
+  kWhole     // a launch per layer that computes the rows of all bands once (only where the bands
+             // compute no row twice: reuse mode, chains without halos, one band)
 };
 
 struct lop_plan_s {
@@ -39,18 +60,19 @@ struct lop_plan_s {
   std::vector<void*> d_wd;     // dense conv weights in MFMA operand order, or nullptr
   std::vector<void*> d_wd16;   // ... in the operand order of 16 x 16 tiles, or nullptr
   std::vector<void*> d_wstem;  // ... as fp32 [c_out / 4][k][4] for the first-layer kernel, or nullptr
-  // Layers that run as one launch: fuse_head[t] = first layer of the group whose last layer is
-  // t (else -1); fused_away[l] = 1 for the layers of a group before its last (no launch, no
-  // buffer of their own).
-  std::vector<int> fuse_head;
-  std::vector<char> fused_away;
+  Fusion fuse_band;   // groups of the launches that compute one band
+  Fusion fuse_chain;  // groups of the launches that compute all bands (kGrouped, kWhole)
+  ChainSched sched = ChainSched::kPerBand;
+  int group = 0;  // kGrouped: bands per group; the groups of a chain run one after another
   std::vector<float*> d_bias;  // per layer bias (device) or nullptr
   std::vector<int> k_pad;
   std::vector<char> has_wd, has_wd16;  // which of the two operand-order packings a layer gets
   std::vector<char> has_wstem;         // ... and whether it gets the first-layer packing
   size_t conv_ws_bytes = 0;
   size_t arena_bytes = 0;
-  std::vector<std::vector<size_t>> slab_off;  // [band][layer] byte offset into a lane's arena
+  // [band][layer] byte offset into a lane's arena; entry n_bands: the full-height buffers of a
+  // chain that runs as a whole
+  std::vector<std::vector<size_t>> slab_off;
   std::vector<Lane> lanes;
   hipStream_t s_main = nullptr, s_copy = nullptr;
   hipStream_t last_user_stream = nullptr;
@@ -84,8 +106,8 @@ struct lop_plan_s {
   int lane_index(int band) const { return t.reuse || batched ? cur_lane : band % n_lanes(); }
   Lane& lane_of(int band) { return lanes[lane_index(band)]; }
   const Lane& lane_of(int band) const { return lanes[lane_index(band)]; }
-  // While lop_run_chain_static enqueues, scratch comes from the library's static device array
-  // instead of the lanes' allocations.
+  // While a whole chain is enqueued, scratch is that of the lane the chain was given, or the
+  // library's static device array (lop_run_chain_static).
   void* arena_override = nullptr;
   void* ws_override = nullptr;
   void* arena_of(int band) const {

@@ -139,8 +139,9 @@ int build_tables(const lop_layer_t* layers, int n_layers, const lop_tensor_desc_
   // ---- bands on the last layer's rows, then backwards
   std::vector<lop_rows_t> out_rows;
   split_rows(t.layers.back().h_out, n_bands, out_rows);
-  t.bands.assign(n_bands, BandRows{});
-  for (int b = 0; b < n_bands; ++b) {
+  out_rows.push_back(lop_rows_t{0, t.layers.back().h_out});
+  t.bands.assign(n_bands + 1, BandRows{});
+  for (int b = 0; b <= n_bands; ++b) {
     BandRows& B = t.bands[b];
     B.need.assign(n_layers + 1, lop_rows_t{0, 0});
     B.reads.assign(n_layers, lop_rows_t{0, 0});
@@ -158,13 +159,13 @@ int build_tables(const lop_layer_t* layers, int n_layers, const lop_tensor_desc_
   // the image with the band index, so "rows some earlier band produced" is everything
   // below the highest `hi` seen so far; rows of need[] below that mark are already there.
   std::vector<int> done_hi(n_layers, 0);
-  for (int b = 0; b < n_bands; ++b) {
+  for (int b = 0; b <= n_bands; ++b) {
     BandRows& B = t.bands[b];
     B.compute.assign(n_layers, lop_rows_t{0, 0});
     for (int i = 0; i < n_layers; ++i) {
       lop_rows_t c = B.need[i + 1];
       if (empty(c)) continue;
-      if (reuse) {
+      if (reuse && b < n_bands) {
         c.lo = std::max(c.lo, done_hi[i]);
         if (c.hi <= c.lo) { c = {0, 0}; }
         done_hi[i] = std::max(done_hi[i], B.need[i + 1].hi);
@@ -174,6 +175,15 @@ int build_tables(const lop_layer_t* layers, int n_layers, const lop_tensor_desc_
     }
   }
   return LOP_OK;
+}
+
+bool Tables::disjoint() const {
+  for (int l = 0; l < n_layers(); ++l) {
+    long rows = 0;
+    for (int b = 0; b < n_bands; ++b) rows += bands[b].compute[l].hi - bands[b].compute[l].lo;
+    if (rows > bands[whole()].compute[l].hi - bands[whole()].compute[l].lo) return false;
+  }
+  return true;
 }
 
 }  // namespace lop

@@ -33,7 +33,13 @@ struct Tables {
   int n_bands = 0;
   bool reuse = false;
   std::vector<LayerInfo> layers;
-  std::vector<BandRows> bands;
+  std::vector<BandRows> bands;  // one entry per band, then one for the whole chain as a band
+
+  // The index of that last entry: every output row, and of every layer the rows they need.
+  int whole() const { return n_bands; }
+  // Whether no row of any layer is computed by two bands, so that a launch over all bands' rows
+  // does the same work as the bands' launches together.
+  bool disjoint() const;
 
   int n_layers() const { return (int)layers.size(); }
   size_t esz() const { return in.dtype == LOP_BF16 ? 2 : 4; }

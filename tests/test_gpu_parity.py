@@ -1301,3 +1301,44 @@ def test_two_party_random_chains(oracle, dtype, base):
         assert st.bytes_to_m == ost.bytes_to("M") and st.bytes_to_r == ost.bytes_to("R"), (desc, sched)
         assert st.transfers == len(ost.transfers)
         done += 1
+
+
+# ---- lop_run_chain merges the launches of the bands; lop_run_band runs one ----
+@pytest.mark.parametrize("name,kw,flags", [
+    ("detector720p", dict(h=128, w=96, n_bands=20), 0),                        # more bands than one launch takes
+    ("detector720p", dict(h=640, w=1280, n_bands=16), 0),                      # slabs in two groups of bands
+    ("vgg16", dict(h=64, w=64, n_bands=3), lop.LOP_FLAG_REUSE),                # one launch over all rows
+    ("mbv2", dict(h=64, w=48, n=2, n_bands=4), 0),                             # launches that take one band each
+])
+@pytest.mark.parametrize("graph", [0, lop.LOP_FLAG_GRAPH])
+def test_merged_chain_agrees_with_its_bands(oracle, name, kw, flags, graph):
+    """Whole chains on the plan's own streams, on two caller streams in turn and band by band, on
+    the same plan and with calls of different kinds right behind each other."""
+    chain = workloads.CONFIGS[name](**kw)
+    t = workloads.make_tensors(chain, zero_bias=False)
+    plan = lop.Plan(chain, t, None, flags | graph)
+    try:
+        d_in = to_device_nhwc(t.x, chain.dtype)
+        outs = [(empty_out(plan.out_shape(), chain.dtype), empty_out(plan.out_shape(), chain.dtype, pinned=True))
+                for _ in range(7)]
+        streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+        for d_out, h_out in outs[:2]:
+            plan.run_chain(d_in, d_out, h_out)
+        for i, (d_out, h_out) in enumerate(outs[2:6]):
+            plan.run_chain(d_in, d_out, h_out, compute_stream=streams[i % 2])
+        for b in range(plan.n_bands):
+            plan.run_band(b, d_in, *outs[6])
+        plan.synchronize()
+        torch.cuda.synchronize()
+        check_margins(*[x for pair in outs for x in pair])
+        bands = to_nchw(outs[6][0])
+        if np.prod(chain.in_shape) < 1 << 20:
+            assert rel_err(bands, oracle.run_chain(chain, t)) <= TOL[chain.dtype]
+        first = to_nchw(outs[0][0])
+        for d_out, h_out in outs[:6]:
+            np.testing.assert_array_equal(to_nchw(d_out), first)
+            np.testing.assert_array_equal(to_nchw(h_out), first)
+        np.testing.assert_array_equal(to_nchw(outs[6][1]), bands)
+        assert rel_err(first, bands) <= TOL[chain.dtype]
+    finally:
+        plan.destroy()
