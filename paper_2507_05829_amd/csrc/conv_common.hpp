@@ -1,0 +1,99 @@
+// Pieces the dense convolution kernels share: operand vectors and matrix products, division by
+// numbers only the host knows, and the order in which workgroups take tiles.
+#pragma once
+#include <hip/hip_runtime.h>
+
+#include "kernels.hpp"
+
+namespace lop {
+namespace {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+// 16 bytes in registers: a native vector, so that copies of it are loads and stores the
+// optimiser can keep in registers (copies of HIP's uint4 struct are memcpy calls, and an
+// array of them that is filled from memory stays in private memory)
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+
+// Division of a pixel index by a width or a row count that only the host knows: q = (mulhi(n,
+// mul) + n) >> shift for 0 <= n < 2^31 (Granlund and Montgomery's division by an invariant
+// integer), three instructions where the integer division of two registers takes about forty,
+// and a wavefront issues one instruction in four cycles or more.
+struct FastDiv { unsigned mul; int shift; };
+inline FastDiv make_fastdiv(int d) {
+  FastDiv f{1u, 0};
+  if (d < 1) return f;
+  while ((1L << f.shift) < d) ++f.shift;
+  f.mul = (unsigned)((((unsigned long long)1 << 32) * (((unsigned long long)1 << f.shift) - (unsigned long long)d)) / (unsigned long long)d + 1);
+  return f;
+}
+__device__ __forceinline__ int fastdiv(int n, const FastDiv& f) {
+  return (int)((__umulhi((unsigned)n, f.mul) + (unsigned)n) >> f.shift);
+}
+
+__device__ __forceinline__ float to_f32(float v) { return v; }
+__device__ __forceinline__ float to_f32(__bf16 v) { return (float)v; }
+
+template <typename T> __device__ __forceinline__ T from_f32(float v);
+template <> __device__ __forceinline__ float from_f32<float>(float v) { return v; }
+template <> __device__ __forceinline__ __bf16 from_f32<__bf16>(float v) { return (__bf16)v; }
+
+template <typename T>
+__device__ __forceinline__ void mma(const u32x4& wa, const u32x4& px, f32x16& acc);
+
+template <>
+__device__ __forceinline__ void mma<__bf16>(const u32x4& wa, const u32x4& px, f32x16& acc) {
+  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, wa),
+                                                __builtin_bit_cast(bf16x8, px), acc, 0, 0, 0);
+}
+
+template <>
+__device__ __forceinline__ void mma<float>(const u32x4& wa, const u32x4& px, f32x16& acc) {
+  const f32x4 a = __builtin_bit_cast(f32x4, wa), b = __builtin_bit_cast(f32x4, px);
+  acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[0], b[0], acc, 0, 0, 0);
+  acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[1], b[1], acc, 0, 0, 0);
+  acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[2], b[2], acc, 0, 0, 0);
+  acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[3], b[3], acc, 0, 0, 0);
+}
+
+// Which tile a workgroup takes. The hardware hands workgroups to the 8 XCDs round-robin in
+// launch order (x fastest), and every XCD has an L2 of its own: in launch order the 64
+// workgroups that are resident on one XCD at a time would be scattered over the whole grid
+// and each would pull its own pixel tile and weight tile through that L2. Instead XCD k takes
+// the k-th contiguous eighth of a walk over the tiles that goes down groups of kGroupM pixel
+// tiles and then across the channel tiles, so its resident workgroups form a block of about
+// 8 x 8 tiles that shares 8 pixel tiles and 8 weight tiles. Reduction slices are outermost.
+struct TileId { int m, n, z; };
+constexpr int kXcds = 8, kGroupM = 8;
+// (by_group: division by kGroupM * ny, made on the host; the other divisions of this walk are by
+// constants or lie behind conditions that hold for few workgroups)
+__device__ __forceinline__ TileId xcd_tile(int bx, int mx, int ny, int nz, const FastDiv& by_group) {
+  const int total = mx * ny * nz;
+  const int launch = bx + mx * (blockIdx.y + ny * blockIdx.z);
+  const int xcd = launch % kXcds, slot = launch / kXcds;
+  const int q = total / kXcds, r = total % kXcds;
+  const int v = xcd * q + min(xcd, r) + slot;  // XCD k owns q (+1 for the first r) consecutive tiles
+  int z = 0, t = v;
+  if (nz > 1) {
+    const int per_z = mx * ny;
+    z = v / per_z;
+    t = v - z * per_z;
+  }
+  const int group = fastdiv(t, by_group), in_group = t - group * (kGroupM * ny);
+  const int first = group * kGroupM;
+  const int gm = min(kGroupM, mx - first);
+  TileId id;
+  id.z = z;
+  id.n = gm == kGroupM ? in_group / kGroupM : in_group / gm;
+  id.m = first + in_group - id.n * gm;
+  return id;
+}
+
+// s_waitcnt immediate that waits until at most n vector-memory operations are outstanding
+// and leaves the other counters alone (gfx9 encoding: vmcnt in bits 3:0 and 15:14).
+constexpr int vmcnt_imm(int n) { return (n & 0xf) | ((n >> 4) << 14) | (0x7 << 4) | (0xf << 8); }
+
+
+}  // namespace
+}  // namespace lop

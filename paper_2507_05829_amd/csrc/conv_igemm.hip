@@ -21,36 +21,13 @@
 #include <cstdio>
 
 #include "act.hpp"
+#include "conv_common.hpp"
 #include "kernels.hpp"
 #include "launch.hpp"
 #include "lop.h"
 
 namespace lop {
 namespace {
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-// 16 bytes in registers: a native vector, so that copies of it are loads and stores the
-// optimiser can keep in registers (copies of HIP's uint4 struct are memcpy calls, and an
-// array of them that is filled from memory stays in private memory)
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-
-// Division of a pixel index by a width or a row count that only the host knows: q = (mulhi(n,
-// mul) + n) >> shift for 0 <= n < 2^31 (Granlund and Montgomery's division by an invariant
-// integer), three instructions where the integer division of two registers takes about forty,
-// and a wavefront issues one instruction in four cycles or more.
-struct FastDiv { unsigned mul; int shift; };
-inline FastDiv make_fastdiv(int d) {
-  FastDiv f{1u, 0};
-  if (d < 1) return f;
-  while ((1L << f.shift) < d) ++f.shift;
-  f.mul = (unsigned)((((unsigned long long)1 << 32) * (((unsigned long long)1 << f.shift) - (unsigned long long)d)) / (unsigned long long)d + 1);
-  return f;
-}
-__device__ __forceinline__ int fastdiv(int n, const FastDiv& f) {
-  return (int)((__umulhi((unsigned)n, f.mul) + (unsigned)n) >> f.shift);
-}
 
 struct ConvParams {
   const void* x;
@@ -78,31 +55,6 @@ static_assert(sizeof(Batch<ConvParams>) <= 4096, "the parameters of all bands of
 
 __device__ __forceinline__ float apply_act(float v, int act) {
   return clamp_act(v, make_clamp(act));
-}
-
-__device__ __forceinline__ float to_f32(float v) { return v; }
-__device__ __forceinline__ float to_f32(__bf16 v) { return (float)v; }
-
-template <typename T> __device__ __forceinline__ T from_f32(float v);
-template <> __device__ __forceinline__ float from_f32<float>(float v) { return v; }
-template <> __device__ __forceinline__ __bf16 from_f32<__bf16>(float v) { return (__bf16)v; }
-
-template <typename T>
-__device__ __forceinline__ void mma(const u32x4& wa, const u32x4& px, f32x16& acc);
-
-template <>
-__device__ __forceinline__ void mma<__bf16>(const u32x4& wa, const u32x4& px, f32x16& acc) {
-  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, wa),
-                                                __builtin_bit_cast(bf16x8, px), acc, 0, 0, 0);
-}
-
-template <>
-__device__ __forceinline__ void mma<float>(const u32x4& wa, const u32x4& px, f32x16& acc) {
-  const f32x4 a = __builtin_bit_cast(f32x4, wa), b = __builtin_bit_cast(f32x4, px);
-  acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[0], b[0], acc, 0, 0, 0);
-  acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[1], b[1], acc, 0, 0, 0);
-  acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[2], b[2], acc, 0, 0, 0);
-  acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[3], b[3], acc, 0, 0, 0);
 }
 
 // LDS traffic inside one wavefront needs no barrier (the hardware keeps a wavefront's LDS
@@ -201,39 +153,6 @@ __device__ __forceinline__ void finish_vec(const ConvParams& p, int m, int co, f
   for (int j = 0; j < VE; ++j) o[j] = from_f32<T>(apply_act(v[j], p.act));
   *(u32x4*)((T*)p.y + pa.y + co) = *(const u32x4*)o;
   if (p.y2) *(u32x4*)((T*)p.y2 + pa.y + co) = *(const u32x4*)o;
-}
-
-// Which tile a workgroup takes. The hardware hands workgroups to the 8 XCDs round-robin in
-// launch order (x fastest), and every XCD has an L2 of its own: in launch order the 64
-// workgroups that are resident on one XCD at a time would be scattered over the whole grid
-// and each would pull its own pixel tile and weight tile through that L2. Instead XCD k takes
-// the k-th contiguous eighth of a walk over the tiles that goes down groups of kGroupM pixel
-// tiles and then across the channel tiles, so its resident workgroups form a block of about
-// 8 x 8 tiles that shares 8 pixel tiles and 8 weight tiles. Reduction slices are outermost.
-struct TileId { int m, n, z; };
-constexpr int kXcds = 8, kGroupM = 8;
-// (by_group: division by kGroupM * ny, made on the host; the other divisions of this walk are by
-// constants or lie behind conditions that hold for few workgroups)
-__device__ __forceinline__ TileId xcd_tile(int bx, int mx, int ny, int nz, const FastDiv& by_group) {
-  const int total = mx * ny * nz;
-  const int launch = bx + mx * (blockIdx.y + ny * blockIdx.z);
-  const int xcd = launch % kXcds, slot = launch / kXcds;
-  const int q = total / kXcds, r = total % kXcds;
-  const int v = xcd * q + min(xcd, r) + slot;  // XCD k owns q (+1 for the first r) consecutive tiles
-  int z = 0, t = v;
-  if (nz > 1) {
-    const int per_z = mx * ny;
-    z = v / per_z;
-    t = v - z * per_z;
-  }
-  const int group = fastdiv(t, by_group), in_group = t - group * (kGroupM * ny);
-  const int first = group * kGroupM;
-  const int gm = min(kGroupM, mx - first);
-  TileId id;
-  id.z = z;
-  id.n = gm == kGroupM ? in_group / kGroupM : in_group / gm;
-  id.m = first + in_group - id.n * gm;
-  return id;
 }
 
 // BM pixels x BN channels per workgroup; WM x WN wavefronts; BKB bytes of the reduction
@@ -849,10 +768,6 @@ __global__ __launch_bounds__(64 * WK) void conv_direct_kernel_bands(const Batch<
 // non-decreasing, so the maximum of the rounded values is the rounded value of the maximum) and
 // stores pooled pixels: the convolution's own output never exists in memory.
 static __device__ __attribute__((aligned(256))) unsigned char g_zero_line[256];
-
-// s_waitcnt immediate that waits until at most n vector-memory operations are outstanding
-// and leaves the other counters alone (gfx9 encoding: vmcnt in bits 3:0 and 15:14).
-constexpr int vmcnt_imm(int n) { return (n & 0xf) | ((n >> 4) << 14) | (0x7 << 4) | (0xf << 8); }
 
 //
 // TPS: taps per stage. 1: C_in * sizeof(T) is a multiple of 128. 2: it is 64, a stage's 128
@@ -1961,7 +1876,7 @@ int group_of(const OpLaunch* Ls, int n, ConvParams* ps) {
 }  // namespace
 
 size_t conv_workspace_bytes_bands(const OpLaunch* Ls, int n) {
-  if (n < 1 || n > kMaxBatch || stem_applies(Ls[0])) return 0;
+  if (n < 1 || n > kMaxBatch || stem_applies(Ls[0]) || patch_applies(Ls, nullptr, n)) return 0;
   ConvParams ps[kMaxBatch];
   const int m = group_of(Ls, n, ps);
   if (m == 0) return 0;
@@ -1982,6 +1897,7 @@ hipError_t launch_conv_igemm_bands(const OpLaunch* Ls, int n, hipStream_t stream
   ConvParams ps[kMaxBatch];
   const int m = group_of(Ls, n, ps);
   if (m == 0) return hipSuccess;
+  if (patch_applies(Ls, nullptr, n)) return launch_patch(Ls, nullptr, n, stream, ev);
   return Ls[0].dtype == LOP_BF16 ? launch_typed<__bf16>(ps, m, Ls[0].dtype, (float*)Ls[0].ws, stream, ev)
                                  : launch_typed<float>(ps, m, Ls[0].dtype, (float*)Ls[0].ws, stream, ev);
 }
@@ -1998,6 +1914,7 @@ int conv_igemm_describe_bands(const OpLaunch* Ls, int n, char* name, size_t size
     if (name && size) name[0] = 0;
     return 0;
   }
+  if (patch_applies(Ls, nullptr, n)) return patch_describe(Ls, nullptr, n, name, size);
   const OpLaunch& L = Ls[0];
   const ConvParams p = group_params(ps, m);
   const char* const form = m > 1 ? "_bands" : "";
@@ -2103,6 +2020,7 @@ hipError_t launch_convpool_bands(const OpLaunch* convs, const OpLaunch* pools, i
     ps[m++] = p;
   }
   if (m == 0) return hipSuccess;
+  if (patch_applies(convs, pools, n)) return launch_patch(convs, pools, n, stream, ev);
   const LdsChoice ld = choose_pooled(group_params(ps, m), convs[0].dtype);
   if (convs[0].dtype == LOP_BF16) {
     if (ld.bm == 32 && ld.bn == 32) return launch_lds<__bf16, 32, 32, kLdsStagesBf16>(ps, m, stream, ev);
@@ -2129,6 +2047,7 @@ int convpool_describe_bands(const OpLaunch* convs, const OpLaunch* pools, int n,
     if (name && size) name[0] = 0;
     return 0;
   }
+  if (patch_applies(convs, pools, n)) return patch_describe(convs, pools, n, name, size);
   const LdsChoice ld = choose_pooled(group_params(ps, m), convs[0].dtype);
   const bool bf = convs[0].dtype == LOP_BF16;
   if (name && size)

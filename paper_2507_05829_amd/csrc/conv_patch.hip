@@ -1,0 +1,566 @@
+// Dense 3 x 3 convolution on a row interval, the LDS-staged kernel in its patch form.
+//
+// conv_lds_kernel of conv_igemm.hip fetches every tap of every pixel of its tile: nine times the
+// input under a 3 x 3 filter, through a load path that hands a compute unit about 30 bytes per
+// clock, and that rate is what bounds it. Here a workgroup owns a rectangle of output pixels x BN
+// channels and fetches the input pixels under that rectangle once per 128 bytes of channels (a
+// "patch": 180 pixels for 8 x 16 outputs, 1.4 x the outputs instead of 9 x); all nine taps are then
+// read from LDS at offsets from each other. The filter is not staged at all: it comes straight
+// from memory in MFMA operand order (OpLaunch::wd), a contiguous KiB per wavefront load, nine taps
+// ahead of its use.
+//
+//  - The four wavefronts split the reduction inside a patch (wavefront w multiplies the w-th 32
+//    bytes of every pixel) and each accumulates the whole tile, so that no filter byte is loaded
+//    twice by a workgroup and no barrier is needed between taps: one per 128 bytes of channels,
+//    where the next patch, fetched meanwhile, takes over. Their partial tiles are added through
+//    LDS in wavefront order.
+//  - A pixel of the patch takes 144 bytes of LDS: with an odd number of 16-byte slots per pixel the
+//    16 lanes that read a slot of 16 neighbouring pixels at a time touch every bank once, and a tap is
+//    a constant number of bytes away from another. (global -> LDS loads fill consecutive slots, so
+//    every ninth lane of them fetches nothing.)
+//  - The input slab is a buffer resource: a pixel outside the image or the slab is a load past its
+//    end, which puts zeros into LDS without touching memory.
+//  - S == 2: the patch keeps the even and the odd columns of a row apart, so that neighbouring
+//    output pixels read neighbouring slots there, too.
+//  - POOL: the 2 x 2 stride-2 max pooling behind the convolution is part of the launch. The lanes take
+//    the tile's pixels window by window, so that a window is four neighbouring lanes of the summed
+//    tile: the maximum is taken between them before bias, activation and rounding (all of them
+//    non-decreasing) and the convolution's own output never exists in memory.
+//
+// (What it is worth, measured: see choose_patch.)
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <cstdio>
+#include <cstdlib>
+
+#include "act.hpp"
+#include "conv_common.hpp"
+#include "kernels.hpp"
+#include "launch.hpp"
+#include "lop.h"
+
+namespace lop {
+namespace {
+
+struct PatchParams {
+  const void* x;
+  void* y;
+  void* y2;         // second destination with y's layout, or nullptr
+  const void* res;
+  const void* wd;   // weights in MFMA operand order
+  const float* bias;
+  int x_row0, x_rows, W, C_in;
+  int y_row0, y_rows, W_out, C_out;  // of the tensor that is stored (POOL: the pooled one)
+  int r_row0, r_rows;
+  int ph, pw, act, k_steps;          // k_steps: MFMA steps of a packed weight row
+  int out_lo, R, N;                  // output rows of the convolution itself
+  int Wc;                            // its columns
+  int th, tw, nty, ntx;              // tile of output pixels, tiles per image in either direction
+  int pitch, ph_rows;                // pixel slots per row of the patch (S == 2: even columns, then odd), its rows
+  FastDiv by_ntx, by_nty, by_tw, by_pitch, by_group;
+};
+static_assert(sizeof(Batch<PatchParams>) <= 4096, "the parameters of all bands of a launch travel as kernel arguments");
+
+constexpr int kPixelBytes = 144, kPixelSlots = 9;
+constexpr unsigned kOutside = 0x80000000u;
+
+// TP x 32 pixels x NT x 32 channels per workgroup; NI: load instructions per wavefront and patch.
+template <typename T, int TP, int NT, int NI, bool POOL, int S>
+__device__ __forceinline__ void patch_body(const PatchParams& p, const int bx, const int gx) {
+  constexpr int KE = 16 / (int)sizeof(T);
+  constexpr int BUF = NI * 4096;            // bytes of a patch in LDS
+  constexpr int UNITS = TP * 4;             // (32 pixels x 8 channels) pieces of a 32-channel tile
+  constexpr int SMEM = 2 * BUF > 4 * UNITS * 1024 ? 2 * BUF : 4 * UNITS * 1024;
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[SMEM];
+
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int px = lane & 31, half = lane >> 5;
+  const TileId tile = xcd_tile(bx, gx, gridDim.y, 1, p.by_group);
+  const int co0 = tile.n * (32 * NT);
+  const int q = fastdiv(tile.m, p.by_ntx), tx = tile.m - q * p.ntx;
+  const int n = fastdiv(q, p.by_nty), ty = q - n * p.nty;
+  const int r0 = ty * p.th, c0 = tx * p.tw;            // the tile's first row of the launch and first column
+  const int row_bytes = p.C_in * (int)sizeof(T);
+  const int chunks = row_bytes / 128;
+
+  const __amdgpu_buffer_rsrc_t xbuf = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<void*>(p.x), 0, (int)((size_t)p.N * p.x_rows * p.W * row_bytes), 0x00020000);
+  // ---- the slots this lane fetches of every patch
+  unsigned src[NI];
+  {
+    const int ih0 = (p.out_lo + r0) * S - p.ph, iw0 = c0 * S - p.pw;
+    const int half_cols = p.pitch >> 1;
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const int slot = (i * 4 + wave) * 64 + lane;
+      const int pix = slot / kPixelSlots, k = slot - pix * kPixelSlots;
+      const int pr = fastdiv(pix, p.by_pitch), pc = pix - pr * p.pitch;
+      const int col = S == 1 ? pc : (pc < half_cols ? 2 * pc : 2 * (pc - half_cols) + 1);
+      const int ih = ih0 + pr, iw = iw0 + col;
+      const bool ok = (k < 8) & (pr < p.ph_rows) & (ih >= p.x_row0) & (ih < p.x_row0 + p.x_rows) & (iw >= 0) & (iw < p.W);
+      src[i] = ok ? (unsigned)(((n * p.x_rows + ih - p.x_row0) * p.W + iw) * row_bytes + k * 16) : kOutside;
+    }
+  }
+  auto fetch_patch = [&](int c) __attribute__((always_inline)) {
+    unsigned char* const dst = smem + (c & 1) * BUF;
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(xbuf, (__attribute__((address_space(3))) void*)(dst + (i * 4 + wave) * 1024),
+                                               16, (int)src[i], c * 128, 0, 0);
+    // (the filter loads behind these stay behind them: the waits below count on that order)
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // ---- the filter: [32 channels][step][lane] 16 bytes; this wavefront's step of a tap and patch
+  const u32x4* wsrc[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+    wsrc[t] = (const u32x4*)p.wd + ((size_t)(tile.n * NT + t) * p.k_steps + wave) * 64 + lane;
+  const int tap_steps = p.C_in / (2 * KE) * 64;
+  u32x4 wreg[9][NT];
+  auto fetch_tap = [&](int c, int t) __attribute__((always_inline)) {
+#pragma unroll
+    for (int k = 0; k < NT; ++k) wreg[t][k] = wsrc[k][(size_t)(t * tap_steps + c * 256)];
+  };
+
+  fetch_patch(0);
+#pragma unroll
+  for (int t = 0; t < 9; ++t) fetch_tap(0, t);
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+
+  // ---- this lane's pixel of every 32-pixel fragment: row and column inside the tile, and where the
+  // first tap of it lies in a patch
+  int at[TP];
+  const unsigned lds0 = (unsigned)(unsigned long)(__attribute__((address_space(3))) unsigned char*)smem;
+  auto pixel = [&](int f, int& r, int& c) __attribute__((always_inline)) {
+    const int i = f * 32 + px;
+    if constexpr (POOL) {
+      const int v = i >> 2, vr = fastdiv(v, p.by_tw), vc = v - vr * (p.tw >> 1);   // (by_tw divides by tw / 2)
+      r = vr * 2 + ((i >> 1) & 1);
+      c = vc * 2 + (i & 1);
+    } else {
+      r = fastdiv(i, p.by_tw);
+      c = i - r * p.tw;
+    }
+  };
+#pragma unroll
+  for (int f = 0; f < TP; ++f) {
+    int r, c;
+    pixel(f, r, c);
+    r = min(r, p.th - 1);                   // (lanes past the tile compute its last row again; they store nothing)
+    at[f] = (int)lds0 + ((r * S) * p.pitch + c) * kPixelBytes + wave * 32 + half * 16;
+  }
+  const int tap_row = p.pitch * kPixelBytes;
+  const int tap_odd = S == 1 ? kPixelBytes : (p.pitch >> 1) * kPixelBytes;
+
+  f32x16 acc[NT][TP];
+#pragma unroll
+  for (int a = 0; a < NT; ++a)
+#pragma unroll
+    for (int b = 0; b < TP; ++b)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.f;
+
+  // Pixel fragments are read with instructions of our own: reads the compiler can see would make
+  // it wait for every load in flight to LDS.
+  u32x4 pa[TP], pb[TP];
+  auto read_tap = [&](int buf, int t, u32x4 (&d)[TP]) __attribute__((always_inline)) {
+    const int a = t / 3, b = t % 3;
+    const int off = buf + a * tap_row + (S == 2 && b == 1 ? tap_odd : 0);
+    constexpr int step = S == 1 ? kPixelBytes : kPixelBytes / 2;   // (S == 2: two taps further is the next even column)
+#pragma unroll
+    for (int f = 0; f < TP; ++f) {
+      const int addr = at[f] + off;
+      if (b == 0 || (S == 2 && b == 1)) asm volatile("ds_read_b128 %0, %1" : "=v"(d[f]) : "v"(addr) : "memory");
+      else if (b == 1) asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(d[f]) : "v"(addr), "n"(step) : "memory");
+      else asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(d[f]) : "v"(addr), "n"(2 * step) : "memory");
+    }
+  };
+  auto wait_reads = [&](u32x4 (&d)[TP]) __attribute__((always_inline)) {
+    if constexpr (TP == 4) asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(d[0]), "+v"(d[1]), "+v"(d[2]), "+v"(d[3]) :: "memory");
+    else if constexpr (TP == 2) asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(d[0]), "+v"(d[1]) :: "memory");
+    else { static_assert(TP == 1, "tiles of 32, 64 or 128 pixels"); asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(d[0]) :: "memory"); }
+  };
+  // One patch: nine taps, the fragments of the next tap on their way while one is multiplied; MORE:
+  // another patch follows, a tap's filter registers are refilled for it as soon as they are free.
+  auto run_patch = [&](int c, bool more) __attribute__((always_inline)) {
+    const int buf = (c & 1) * BUF;
+    read_tap(buf, 0, pa);
+    wait_reads(pa);
+#pragma unroll
+    for (int t = 0; t < 9; ++t) {
+      u32x4 (&now)[TP] = (t & 1) ? pb : pa;
+      u32x4 (&nxt)[TP] = (t & 1) ? pa : pb;
+      if (t < 8) read_tap(buf, t + 1, nxt);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int a = 0; a < NT; ++a)
+#pragma unroll
+        for (int f = 0; f < TP; ++f) mma<T>(wreg[t][a], now[f], acc[a][f]);
+      __builtin_amdgcn_sched_barrier(0);
+      if (more) fetch_tap(c + 1, t);
+      __builtin_amdgcn_sched_barrier(0);
+      if (t < 8) wait_reads(nxt);
+    }
+  };
+  auto patch_barrier = [&]() __attribute__((always_inline)) {
+    // this wavefront's part of the patch has arrived: only the nine taps' filter loads are younger
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(9 * NT));
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  int c = 0;
+  for (; c + 1 < chunks; ++c) {
+    patch_barrier();
+    fetch_patch(c + 1);      // (into the buffer every wavefront was done with at the barrier)
+    run_patch(c, true);
+  }
+  patch_barrier();
+  run_patch(c, false);
+
+  // ---- the four partial tiles, added in wavefront order through LDS: wavefront w finishes pieces
+  // w TP .. (w + 1) TP of the UNITS pieces (piece u: fragment u / 4, channels (u % 4) * 8 ..)
+  u32x4* const part = (u32x4*)smem;
+  const Clamp cl = make_clamp(p.act);
+  // where they go, and what is added to them: all loads issued here, ahead of the sums
+  int r, cc;
+  pixel(wave * TP / 4, r, cc);             // (a wavefront's pieces all lie in one fragment)
+  const int row = r0 + r, col = c0 + cc;
+  bool live = (r < p.th) & (row < p.R) & (col < p.Wc);
+  const int cb = co0 + ((wave * TP) & 3) * 8;   // first channel of this wavefront's pieces
+  f32x4 bias[NT][TP];
+#pragma unroll
+  for (int a = 0; a < NT; ++a)
+#pragma unroll
+    for (int i = 0; i < TP; ++i) bias[a][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  if (p.bias) {
+#pragma unroll
+    for (int a = 0; a < NT; ++a)
+#pragma unroll
+      for (int i = 0; i < TP; ++i) {
+        const int co = cb + a * 32 + i * 8 + half * 4;
+        bias[a][i] = *(const f32x4*)(p.bias + (co < p.C_out ? co : 0));
+      }
+  }
+  typedef unsigned raw_t __attribute__((ext_vector_type(sizeof(T))));   // four elements
+  raw_t res[NT][TP];
+  if constexpr (!POOL) {
+    if (p.res) {
+      const size_t ra = live ? ((size_t)(n * p.r_rows + p.out_lo + row - p.r_row0) * p.W_out + col) * p.C_out : 0;
+#pragma unroll
+      for (int a = 0; a < NT; ++a)
+#pragma unroll
+        for (int i = 0; i < TP; ++i) {
+          const int co = cb + a * 32 + i * 8 + half * 4;
+          res[a][i] = *(const raw_t*)((const T*)p.res + ra + (co < p.C_out ? co : 0));
+        }
+    } else {
+#pragma unroll
+      for (int a = 0; a < NT; ++a)
+#pragma unroll
+        for (int i = 0; i < TP; ++i) res[a][i] = raw_t(0u);
+    }
+  }
+#pragma unroll
+  for (int a = 0; a < NT; ++a) {
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < UNITS; ++u) {
+      const f32x16& s = acc[a][u / 4];
+      const int g = (u % 4) * 4;
+      part[(wave * UNITS + u) * 64 + lane] = __builtin_bit_cast(u32x4, f32x4{s[g], s[g + 1], s[g + 2], s[g + 3]});
+    }
+    __syncthreads();
+    f32x4 sum[TP];
+#pragma unroll
+    for (int i = 0; i < TP; ++i) {
+      sum[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int s = 0; s < 4; ++s) sum[i] += __builtin_bit_cast(f32x4, part[(s * UNITS + wave * TP + i) * 64 + lane]);
+    }
+    // ---- pooling, bias, residual, activation, the one rounding
+    size_t ya;
+    if constexpr (POOL) {
+#pragma unroll
+      for (int i = 0; i < TP; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          float v = sum[i][j];
+          v = fmaxf(v, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0xB1, 0xf, 0xf, true)));  // lane ^ 1
+          v = fmaxf(v, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x4E, 0xf, 0xf, true)));  // lane ^ 2
+          sum[i][j] = v;
+        }
+      live = live & ((lane & 3) == 0);
+      ya = ((size_t)(n * p.y_rows + ((p.out_lo + row) >> 1) - p.y_row0) * p.W_out + (col >> 1)) * p.C_out;
+    } else {
+      ya = ((size_t)(n * p.y_rows + p.out_lo + row - p.y_row0) * p.W_out + col) * p.C_out;
+    }
+#pragma unroll
+    for (int i = 0; i < TP; ++i) {
+      sum[i] += bias[a][i];
+      if constexpr (!POOL) {
+        alignas(16) T rr[4];
+        *(raw_t*)rr = res[a][i];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) sum[i][j] += to_f32(rr[j]);
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j) sum[i][j] = clamp_act(sum[i][j], cl);
+    }
+    if constexpr (sizeof(T) == 4) {
+#pragma unroll
+      for (int i = 0; i < TP; ++i) {
+        const int co = cb + a * 32 + i * 8 + half * 4;
+        if (live && co < p.C_out) {
+          *(f32x4*)((T*)p.y + ya + co) = sum[i];
+          if (p.y2) *(f32x4*)((T*)p.y2 + ya + co) = sum[i];
+        }
+      }
+    } else {
+      auto pack = [&](int i) {
+        alignas(8) __bf16 o[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) o[j] = (__bf16)sum[i][j];
+        return *(const uint2*)o;
+      };
+      if constexpr (TP == 1) {
+        const uint2 o = pack(0);
+        const int co = cb + a * 32 + half * 4;
+        if (live && co < p.C_out) {
+          *(uint2*)((T*)p.y + ya + co) = o;
+          if (p.y2) *(uint2*)((T*)p.y2 + ya + co) = o;
+        }
+      } else {
+        // two pieces hold 16 channels of a pixel in two lanes, 4 + 4 interleaved: exchanged between
+        // the lane halves so that each ends with 8 consecutive ones (one 16-byte store)
+#pragma unroll
+        for (int i = 0; i < TP; i += 2) {
+          const uint2 e = pack(i), o = pack(i + 1);
+          const auto s0 = __builtin_amdgcn_permlane32_swap(e.x, o.x, false, false);
+          const auto s1 = __builtin_amdgcn_permlane32_swap(e.y, o.y, false, false);
+          const u32x4 v = u32x4{(unsigned)s0[0], (unsigned)s1[0], (unsigned)s0[1], (unsigned)s1[1]};
+          const int co = cb + a * 32 + i * 8 + half * 8;
+          if (live && co < p.C_out) {
+            *(u32x4*)((T*)p.y + ya + co) = v;
+            if (p.y2) *(u32x4*)((T*)p.y2 + ya + co) = v;
+          }
+        }
+      }
+    }
+  }
+}
+
+// Load instructions per wavefront and patch: the patch of a tile has at most NI * 256 / 9 pixels.
+constexpr int patch_loads(int tp, int s) { return s == 1 ? (tp == 4 ? 7 : tp == 2 ? 4 : 3) : (tp == 4 ? 20 : tp == 2 ? 11 : 6); }
+
+template <typename T, int BM, int BN, int NST, bool POOL, int S>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void conv_lds_kernel(const PatchParams p) {
+  patch_body<T, BM / 32, BN / 32, patch_loads(BM / 32, S), POOL, S>(p, blockIdx.x, gridDim.x);
+}
+// The same for several bands of one layer in one grid (band b owns blocks first[b] .. first[b + 1] of x).
+template <typename T, int BM, int BN, int NST, bool POOL, int S>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void conv_lds_kernel_bands(const Batch<PatchParams> t) {
+  const int b = batch_find(t, blockIdx.x);
+  patch_body<T, BM / 32, BN / 32, patch_loads(BM / 32, S), POOL, S>(t.p[b], blockIdx.x - t.first[b], t.first[b + 1] - t.first[b]);
+}
+
+// The convolution's own output rows and columns behind a launch (pooled: twice the pooled ones).
+struct PatchWork { int R, Wc, N; };
+PatchWork patch_work(const OpLaunch& c, const OpLaunch* pool) {
+  if (pool) return {2 * (pool->out_hi - pool->out_lo), 2 * pool->y.w, c.x.n};
+  return {c.out_hi - c.out_lo, c.y.w, c.x.n};
+}
+
+// The rectangle of at most 32 tp output pixels for R x W of them: the fewest tiles, then the
+// smallest patch, over widths that split the columns evenly.
+struct PatchTile { int th = 0, tw = 0; long tiles = 0; int patch = 0; };
+PatchTile find_tile(const PatchWork& w, int tp, int s, bool pool) {
+  const int pixels = tp * 32, room = patch_loads(tp, s) * 256 / kPixelSlots, step = pool ? 2 : 1;
+  PatchTile best;
+  for (int target = 64; target >= 2; target /= 2) {
+    const int k = (w.Wc + target - 1) / target;
+    int tw = (w.Wc + k - 1) / k;
+    tw = (tw + step - 1) / step * step;
+    if (tw > pixels) continue;
+    int th = std::min(pixels / tw, w.R) / step * step;
+    const int cols = s == 1 ? tw + 2 : 2 * (tw + 1);
+    while (th >= step && ((th - 1) * s + 3) * cols > room) th -= step;
+    if (th < step) continue;
+    const long tiles = (long)((w.R + th - 1) / th) * ((w.Wc + tw - 1) / tw) * w.N;
+    const int patch = ((th - 1) * s + 3) * cols;
+    if (!best.th || tiles < best.tiles || (tiles == best.tiles && patch < best.patch)) best = {th, tw, tiles, patch};
+  }
+  return best;
+}
+// (Every launch asks for the same few rectangles again and again: the last ones are remembered per thread.)
+PatchTile tile_for(const PatchWork& w, int tp, int s, bool pool) {
+  struct Entry { PatchWork w; int tp, s; bool pool; PatchTile t; };
+  thread_local Entry memo[64] = {};
+  Entry& e = memo[(unsigned)(w.R * 31 + w.Wc * 7 + w.N * 3 + tp * 5 + s * 2 + pool) % 64];
+  if (e.w.R != w.R || e.w.Wc != w.Wc || e.w.N != w.N || e.tp != tp || e.s != s || e.pool != pool || !e.t.th)
+    e = {w, tp, s, pool, find_tile(w, tp, s, pool)};
+  return e.t;
+}
+
+bool patch_shape(const OpLaunch& L) {
+  const int esz = L.dtype == LOP_BF16 ? 2 : 4, ke = 16 / esz;
+  if (L.op != LOP_CONV2D || !L.wd || L.kh != 3 || L.kw != 3 || L.dh != 1 || L.dw != 1) return false;
+  if (L.sh != L.sw || (L.sh != 1 && L.sh != 2)) return false;
+  if (L.x.c * esz % 128 != 0 || L.y.c % ke != 0) return false;
+  return (size_t)L.x.n * L.x.rows * L.x.w * L.x.c * esz < ((size_t)1 << 31);
+}
+
+// The tile of a launch over the bands of a group, or bm == 0 when another kernel is the faster one.
+// What a tile costs was fitted to measured launches of the three backbones, one image and all bands
+// together (cycles; chunk: 128 bytes of channels): a compute unit that has several tiles to do gets
+// through them at `chunk` each plus `rest` per tile (the L2s deliver 16-19 TB/s to the whole chip, which
+// a larger tile asks less of per product: 256 -> 256 channels on 14 300 pixels take 22.7 us with
+// 128 x 64 tiles, 26.1 with 64 x 32 and 38.0 on the kernel that fetches every tap), and no
+// launch is faster than one tile from beginning to end (`first` + `alone` per chunk: 512 -> 512
+// channels on 196 pixels 5.6 us with 32 x 32 tiles, 6.5 with 64 x 32, 15.6 with 128 x 64, 16.1 before).
+struct PatchChoice { int bm = 0, bn = 0; };
+struct PatchCost { int bm, bn; double chunk, rest, alone, first; };
+constexpr PatchCost kBf16Costs[] = {
+    {128, 64, 5800, 4900, 3300, 7000}, {64, 64, 3200, 2750, 1800, 4500}, {64, 32, 1860, 840, 1100, 3500}, {32, 32, 1200, 620, 750, 3000}};
+// fp32: bound by its matrix instructions (2 304 cycles per chunk of a 32 x 32 tile)
+constexpr PatchCost kF32Costs[] = {{64, 32, 4700, 1500, 4900, 5000}, {32, 32, 2400, 900, 2500, 4000}};
+constexpr int kPatchUnits = 256;
+// fp32 launches of fewer tiles are left to the kernels that cut the reduction finer (16 x 16 tiles, or
+// slices across workgroups): 256 -> 512 channels, stride 2, on 49 pixels 11.7 us there against 12.9
+constexpr long kF32MinTiles = 100;
+// bf16: a handful of compute units cannot stream megabytes of filter (7 x 7 x 512 channels is 32 tiles: 5.6 us
+// here, 8.9 there)
+constexpr long kBf16MinTiles = 24;
+// Stride 2: a patch is four times the outputs, so the tile's memory holds one workgroup per compute
+// unit; the kernel that fetches taps (2.25 per output) wins once there is more than one each
+// (64 -> 128 channels on 14 400 pixels 8.3 us there, 10.4 here; 128 -> 256 on 143 5.9 there, 4.1 here)
+constexpr long kStride2MaxTiles = kPatchUnits;
+
+PatchChoice choose_patch(const OpLaunch* convs, const OpLaunch* pools, int n) {
+  const OpLaunch& L = convs[0];
+  for (int b = 0; b < n; ++b)
+    if (!patch_shape(convs[b])) return {};
+  const bool bf = L.dtype == LOP_BF16;
+  auto tiles = [&](int bm, int bn) {
+    long t = 0;
+    for (int b = 0; b < n; ++b) {
+      const PatchWork w = patch_work(convs[b], pools ? &pools[b] : nullptr);
+      if (w.R <= 0) continue;
+      const PatchTile pt = tile_for(w, bm / 32, L.sh, pools != nullptr);
+      if (!pt.th) return 0L;
+      t += pt.tiles;
+    }
+    return t * ((L.y.c + bn - 1) / bn);
+  };
+  const long small = tiles(32, 32);
+  if (small < (bf ? kBf16MinTiles : kF32MinTiles)) return {};
+  if (L.sh == 2) return !pools && small <= (bf ? kStride2MaxTiles : 4 * kStride2MaxTiles) ? PatchChoice{32, 32} : PatchChoice{};
+  const double chunks = L.x.c * (bf ? 2 : 4) / 128;
+  PatchChoice best;
+  double best_cost = 0;
+  auto weigh = [&](const PatchCost& c) {
+    const long t = tiles(c.bm, c.bn);
+    if (t == 0) return;
+    const double share = (double)t / kPatchUnits;
+    const double cost = std::max(share * (chunks * c.chunk + c.rest) + c.first / 2, chunks * c.alone + c.first);
+    if (!best.bm || cost < best_cost) { best = {c.bm, c.bn}; best_cost = cost; }
+  };
+  if (bf) for (const PatchCost& c : kBf16Costs) weigh(c);
+  else for (const PatchCost& c : kF32Costs) weigh(c);
+  return best;
+}
+
+PatchParams make_patch(const OpLaunch& c, const OpLaunch* pool, int bm, int bn, unsigned gy, unsigned* gx) {
+  PatchParams p;
+  const Slab& y = pool ? pool->y : c.y;
+  const PatchWork w = patch_work(c, pool);
+  const int ke = c.dtype == LOP_BF16 ? 8 : 4;
+  p.x = c.x.ptr; p.y = y.ptr; p.y2 = pool ? pool->y2 : c.y2; p.res = c.res.ptr; p.wd = c.wd; p.bias = c.bias;
+  p.x_row0 = c.x.row0; p.x_rows = c.x.rows; p.W = c.x.w; p.C_in = c.x.c;
+  p.y_row0 = y.row0; p.y_rows = y.rows; p.W_out = y.w; p.C_out = c.y.c;
+  p.r_row0 = c.res.row0; p.r_rows = c.res.rows;
+  p.ph = c.ph; p.pw = c.pw; p.act = c.act; p.k_steps = c.k_pad / (2 * ke);
+  p.out_lo = pool ? 2 * pool->out_lo : c.out_lo;
+  p.R = w.R; p.N = w.N; p.Wc = w.Wc;
+  const PatchTile t = tile_for(w, bm / 32, c.sh, pool != nullptr);
+  p.th = t.th; p.tw = t.tw;
+  p.nty = (w.R + t.th - 1) / t.th; p.ntx = (w.Wc + t.tw - 1) / t.tw;
+  p.pitch = c.sh == 1 ? t.tw + 2 : 2 * (t.tw + 1);
+  p.ph_rows = (t.th - 1) * c.sh + 3;
+  p.by_ntx = make_fastdiv(p.ntx); p.by_nty = make_fastdiv(p.nty);
+  p.by_tw = make_fastdiv(pool ? t.tw / 2 : t.tw);
+  p.by_pitch = make_fastdiv(p.pitch);
+  p.by_group = make_fastdiv(kGroupM * (int)gy);
+  *gx = (unsigned)t.tiles;
+  return p;
+}
+
+template <typename T, int BM, int BN>
+hipError_t launch_tile(const OpLaunch* convs, const OpLaunch* pools, int n, hipStream_t s, KernelEvents* ev) {
+  PatchParams ps[kMaxBatch];
+  unsigned gx[kMaxBatch];
+  const unsigned gy = (unsigned)((convs[0].y.c + BN - 1) / BN);
+  if ((int)gy * BN > conv_cout_pad(convs[0].y.c)) return hipErrorInvalidValue;  // unguarded weight loads
+  int m = 0;
+  for (int b = 0; b < n; ++b) {
+    const PatchWork w = patch_work(convs[b], pools ? &pools[b] : nullptr);
+    if (w.R <= 0) continue;
+    ps[m] = make_patch(convs[b], pools ? &pools[b] : nullptr, BM, BN, gy, &gx[m]);
+    const int room = patch_loads(BM / 32, convs[b].sh) * 256 / kPixelSlots;
+    if (ps[m].th < 1 || ps[m].ph_rows * ps[m].pitch > room || ps[m].th * ps[m].tw > BM) return hipErrorInvalidValue;
+    ++m;
+  }
+  if (m == 0) return hipSuccess;
+  if (convs[0].sh == 1) {
+    if (pools)
+      return launch_group(conv_lds_kernel<T, BM, BN, 2, true, 1>, conv_lds_kernel_bands<T, BM, BN, 2, true, 1>, ps, m, gx, gy, 1,
+                          dim3(256), s, ev);
+    return launch_group(conv_lds_kernel<T, BM, BN, 2, false, 1>, conv_lds_kernel_bands<T, BM, BN, 2, false, 1>, ps, m, gx, gy, 1,
+                        dim3(256), s, ev);
+  }
+  if constexpr (BM == 128) {
+    return hipErrorInvalidValue;
+  } else {
+    if (pools) return hipErrorInvalidValue;
+    return launch_group(conv_lds_kernel<T, BM, BN, 2, false, 2>, conv_lds_kernel_bands<T, BM, BN, 2, false, 2>, ps, m, gx, gy, 1,
+                        dim3(256), s, ev);
+  }
+}
+
+}  // namespace
+
+bool patch_applies(const OpLaunch* convs, const OpLaunch* pools, int n) {
+  return n >= 1 && n <= kMaxBatch && choose_patch(convs, pools, n).bm != 0;
+}
+
+hipError_t launch_patch(const OpLaunch* convs, const OpLaunch* pools, int n, hipStream_t s, KernelEvents* ev) {
+  if (n < 1 || n > kMaxBatch) return hipErrorInvalidValue;
+  const PatchChoice c = choose_patch(convs, pools, n);
+  if (convs[0].dtype == LOP_BF16) {
+    if (c.bm == 128 && c.bn == 64) return launch_tile<__bf16, 128, 64>(convs, pools, n, s, ev);
+    if (c.bm == 128) return launch_tile<__bf16, 128, 32>(convs, pools, n, s, ev);
+    if (c.bm == 64 && c.bn == 64) return launch_tile<__bf16, 64, 64>(convs, pools, n, s, ev);
+    if (c.bm == 64) return launch_tile<__bf16, 64, 32>(convs, pools, n, s, ev);
+    if (c.bm == 32) return launch_tile<__bf16, 32, 32>(convs, pools, n, s, ev);
+    return hipErrorInvalidValue;
+  }
+  if (c.bm == 64 && c.bn == 64) return launch_tile<float, 64, 64>(convs, pools, n, s, ev);
+  if (c.bm == 64) return launch_tile<float, 64, 32>(convs, pools, n, s, ev);
+  if (c.bm == 32) return launch_tile<float, 32, 32>(convs, pools, n, s, ev);
+  return hipErrorInvalidValue;
+}
+
+int patch_describe(const OpLaunch* convs, const OpLaunch* pools, int n, char* name, size_t size) {
+  const PatchChoice c = choose_patch(convs, pools, n);
+  if (name && size)
+    snprintf(name, size, "conv_lds_kernel%s<%s, %d, %d, 2, %s, %d>", n > 1 ? "_bands" : "",
+             convs[0].dtype == LOP_BF16 ? "__bf16" : "float", c.bm, c.bn, pools ? "true" : "false", convs[0].sh);
+  return 1;
+}
+
+}  // namespace lop

@@ -92,6 +92,11 @@ bool stem_applies(const OpLaunch& L);
 hipError_t launch_stem(const OpLaunch& L, hipStream_t stream, KernelEvents* ev = nullptr);
 int stem_describe(const OpLaunch& L, char* name, size_t size);
 int stem_describe_bands(const OpLaunch* Ls, int n, char* name, size_t size);
+// The patch form of the LDS-staged kernel (3 x 3 filters; pools: the max pooling behind each band's
+// convolution, or nullptr): whether a group of bands takes it, the launch and its kernel name.
+bool patch_applies(const OpLaunch* convs, const OpLaunch* pools, int n);
+hipError_t launch_patch(const OpLaunch* convs, const OpLaunch* pools, int n, hipStream_t stream, KernelEvents* ev);
+int patch_describe(const OpLaunch* convs, const OpLaunch* pools, int n, char* name, size_t size);
 // A dense convolution and the 2 x 2 stride-2 max pooling that reads it, as one launch: whether
 // the pair qualifies (descriptors without slabs suffice), the launch (conv: input slab, weights,
 // hyper-parameters; pool: output slab, y2 and the pooled rows out_lo..out_hi) and its kernel name.
