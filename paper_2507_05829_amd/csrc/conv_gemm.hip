@@ -1,0 +1,343 @@
+// Dense 1 x 1 convolution (any stride; the row-wise operator of Eq. 1) as a tiled matrix product
+// with both operands travelling global -> LDS without passing through registers.
+//
+// A workgroup of WM x WN wavefronts owns BM pixels x BN channels; NST stages of 128 bytes of the
+// reduction per row sit in LDS, fetched by loads that cover 8 rows x 128 bytes each. What the loop is
+// built around: a compute unit's matrix cores need both wavefronts of a SIMD to have an MFMA ready
+// all the time, so
+//  - the fragments of the next 32 bytes of the reduction are read from LDS while the current ones are
+//    multiplied, across stages, too: the barrier that opens the next stage stands in front of the last
+//    multiply of the current one, and behind it the next stage's first fragments are already on their
+//    way;
+//  - one barrier per stage. Behind it no wavefront reads the current stage any more (its last
+//    fragments are in registers), so its memory is refilled at once with the stage NST further on;
+//  - the reads are instructions of our own (reads the compiler can see make it wait for every load
+//    to LDS that is in flight), the waits are placed by hand.
+// A row's 16-byte chunks are stored at chunk ^ (row / 2 mod 8): the 16 lanes that read one chunk of 16
+// neighbouring rows at a time touch every LDS bank once. A row past the launch's pixels or a chunk past
+// the end of the reduction is a load past the end of the buffer resource and arrives as zeros.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <cstdio>
+
+#include "act.hpp"
+#include "conv_common.hpp"
+#include "kernels.hpp"
+#include "launch.hpp"
+#include "lop.h"
+
+namespace lop {
+namespace {
+
+struct GemmParams {
+  const void* x;
+  void* y;
+  void* y2;        // second destination with y's layout, or nullptr
+  const void* res;
+  const void* w;   // [c_out_pad][k_pad]
+  const float* bias;
+  int x_row0, x_rows, W, K;          // K: channels in
+  int y_row0, y_rows, W_out, C_out;
+  int r_row0, r_rows;
+  int sh, sw, ph, pw, act, k_pad;
+  int out_lo, R, N, M;               // M = N * R * W_out
+  FastDiv by_w, by_r, by_group;
+};
+static_assert(sizeof(Batch<GemmParams>) <= 4096, "the parameters of all bands of a launch travel as kernel arguments");
+
+constexpr unsigned kOutside = 0x80000000u;
+
+template <typename T, int BM, int BN, int WM, int WN, int NST>
+__device__ __forceinline__ void gemm_body(const GemmParams& p, const int bx, const int gx) {
+  constexpr int KE = 16 / (int)sizeof(T);   // elements per 16-byte chunk
+  constexpr int NW = WM * WN;
+  constexpr int TM = BM / (32 * WM), TN = BN / (32 * WN);
+  constexpr int A_LD = BM / (8 * NW), B_LD = BN / (8 * NW), LPS = A_LD + B_LD;   // load instructions per wavefront and stage
+  constexpr int A_BYTES = BM * 128, STAGE = (BM + BN) * 128;
+  constexpr int CPW = TN * 32 + 4;          // fp32 pitch of a wavefront's staged output tile
+  static_assert(A_LD >= 1 && B_LD >= 1 && (NST - 2) * LPS < 64 && NST >= 2, "tile shape");
+  constexpr int SMEM = NST * STAGE > NW * 32 * CPW * 4 ? NST * STAGE : NW * 32 * CPW * 4;
+  static_assert(SMEM <= 160 * 1024, "LDS");
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[SMEM];
+
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wave % WM, wn = wave / WM;
+  const TileId tile = xcd_tile(bx, gx, gridDim.y, 1, p.by_group);
+  const int m0 = tile.m * BM, co0 = tile.n * BN;
+  const int row_bytes = p.K * (int)sizeof(T), w_bytes = p.k_pad * (int)sizeof(T);
+  const int ns = w_bytes / 128;
+
+  // ---- what this lane fetches: row lane / 8 of the 8-row groups wave, wave + NW, ..., chunk
+  // (lane & 7) ^ (row / 2 mod 8)
+  const __amdgpu_buffer_rsrc_t xbuf = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<void*>(p.x), 0, (int)(unsigned)((size_t)p.N * p.x_rows * p.W * row_bytes), 0x00020000);
+  const __amdgpu_buffer_rsrc_t wbuf = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<void*>(p.w), 0, 0x7fffffff, 0x00020000);
+  const int chunk = (lane & 7) ^ ((4 * (wave & 1) + (lane >> 4)) & 7);
+  static_assert(NW % 2 == 0, "a wavefront's groups have one parity");
+  unsigned a_off[A_LD], b_off[B_LD];
+#pragma unroll
+  for (int i = 0; i < A_LD; ++i) {
+    const int m = m0 + (wave + NW * i) * 8 + (lane >> 3);
+    const bool ok = m < p.M;
+    const int mm = ok ? m : 0;
+    const int q = fastdiv(mm, p.by_w), ow = mm - q * p.W_out;
+    const int n = fastdiv(q, p.by_r), r = q - n * p.R;
+    const int ih = (p.out_lo + r) * p.sh - p.ph, iw = ow * p.sw - p.pw;
+    const bool in = ok & (ih >= p.x_row0) & (ih < p.x_row0 + p.x_rows) & (iw >= 0) & (iw < p.W);
+    a_off[i] = in ? (unsigned)(((n * p.x_rows + ih - p.x_row0) * p.W + iw) * row_bytes + chunk * 16) : kOutside;
+  }
+#pragma unroll
+  for (int i = 0; i < B_LD; ++i) b_off[i] = (unsigned)((co0 + (wave + NW * i) * 8 + (lane >> 3)) * w_bytes + chunk * 16);
+  // the chunk lies past the end of the reduction in the last stage
+  const bool past = (ns - 1) * 128 + chunk * 16 >= row_bytes;
+  auto issue = [&](int s, int j) __attribute__((always_inline)) {   // load instruction j of stage s
+    unsigned char* const dst = smem + (s % NST) * STAGE;
+    if (j < A_LD) {
+      const unsigned off = past & (s == ns - 1) ? kOutside : a_off[j];
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(xbuf, (__attribute__((address_space(3))) void*)(dst + (wave + NW * j) * 1024), 16,
+                                               (int)off, s * 128, 0, 0);
+    } else {
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(
+          wbuf, (__attribute__((address_space(3))) void*)(dst + A_BYTES + (wave + NW * (j - A_LD)) * 1024), 16, (int)b_off[j - A_LD],
+          s * 128, 0, 0);
+    }
+  };
+
+  f32x16 acc[TN][TM];
+#pragma unroll
+  for (int a = 0; a < TN; ++a)
+#pragma unroll
+    for (int b = 0; b < TM; ++b)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.f;
+
+  // ---- fragments: row lane & 31 of a 32-row tile, chunk 2 ks + (lane >> 5); two sets, one being
+  // multiplied while the other is read
+  const int frow = lane & 31, key = (frow >> 1) & 7;
+  const unsigned lds0 = (unsigned)(unsigned long)(__attribute__((address_space(3))) unsigned char*)smem;
+  const unsigned a_at = lds0 + (unsigned)(wm * TM * 4096 + frow * 128), b_at = lds0 + (unsigned)(A_BYTES + wn * TN * 4096 + frow * 128);
+  u32x4 fa[2][TM], fb[2][TN];
+  auto read = [&](int s, int ks, u32x4 (&a)[TM], u32x4 (&b)[TN]) __attribute__((always_inline)) {
+    const unsigned off = (unsigned)((s % NST) * STAGE) + (unsigned)(((2 * ks + (lane >> 5)) ^ key) * 16);
+    const unsigned aa = a_at + off, bb = b_at + off;
+#pragma unroll
+    for (int i = 0; i < TN; ++i) asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(b[i]) : "v"(bb), "n"(i * 4096) : "memory");
+#pragma unroll
+    for (int i = 0; i < TM; ++i) asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(a[i]) : "v"(aa), "n"(i * 4096) : "memory");
+  };
+  auto wait_reads = [&](u32x4 (&a)[TM], u32x4 (&b)[TN]) __attribute__((always_inline)) {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+    for (int i = 0; i < TM; ++i) asm volatile("" : "+v"(a[i]));
+#pragma unroll
+    for (int i = 0; i < TN; ++i) asm volatile("" : "+v"(b[i]));
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto barrier = [&]() __attribute__((always_inline)) {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+
+  for (int s = 0; s < NST; ++s)
+    if (s < ns)
+#pragma unroll
+      for (int j = 0; j < LPS; ++j) issue(s, j);
+  if (ns >= NST) __builtin_amdgcn_s_waitcnt(vmcnt_imm((NST - 1) * LPS));
+  else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+  barrier();
+  read(0, 0, fa[0], fb[0]);
+  wait_reads(fa[0], fb[0]);
+
+  auto multiply = [&](u32x4 (&a)[TM], u32x4 (&b)[TN], int s, bool loads) __attribute__((always_inline)) {
+    constexpr int NM = TM * TN;
+#pragma unroll
+    for (int i = 0; i < (NM > LPS ? NM : LPS); ++i) {
+      if (i < NM) {
+        mma<T>(b[i / TM], a[i % TM], acc[i / TM][i % TM]);
+        if (loads) __builtin_amdgcn_sched_barrier(0);
+      }
+      if (loads && i < LPS) {
+        issue(s, i);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // One stage: four 32-byte steps. (Steps 0..3 use the fragment sets 0, 1, 0, 1.)
+  auto stage = [&](int s, bool next, bool refill) __attribute__((always_inline)) {
+#pragma unroll
+    for (int ks = 0; ks < 3; ++ks) {
+      read(s, ks + 1, fa[(ks + 1) & 1], fb[(ks + 1) & 1]);
+      __builtin_amdgcn_sched_barrier(0);
+      multiply(fa[ks & 1], fb[ks & 1], 0, false);
+      wait_reads(fa[(ks + 1) & 1], fb[(ks + 1) & 1]);
+    }
+    if (next) {
+      if (refill) __builtin_amdgcn_s_waitcnt(vmcnt_imm((NST - 2) * LPS));
+      else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+      barrier();
+      read(s + 1, 0, fa[0], fb[0]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    multiply(fa[1], fb[1], s + NST, refill);
+    if (next) wait_reads(fa[0], fb[0]);
+  };
+  int s = 0;
+  for (; s + NST < ns; ++s) stage(s, true, true);
+  for (; s + 1 < ns; ++s) stage(s, true, false);
+  stage(s, false, false);
+
+  // ---- epilogue: one 32-pixel tile of the wavefront at a time through LDS, so that consecutive lanes
+  // own consecutive 16-byte pieces of a pixel's channels
+  constexpr int VE = KE;
+  constexpr int CPR = TN * 32 / VE;          // pieces per pixel of the wavefront's tile
+  float* const Cw = (float*)smem + wave * (32 * CPW);
+  const Clamp cl = make_clamp(p.act);
+  __syncthreads();
+#pragma unroll
+  for (int tm = 0; tm < TM; ++tm) {
+    constexpr int PIECES = 32 * CPR / 64;
+    // the residual's pieces (and where they go) first: their latency passes under the exchange
+    size_t ya[PIECES];
+    u32x4 rr[PIECES];
+    bool ok[PIECES];
+#pragma unroll
+    for (int i = 0; i < PIECES; ++i) {
+      const int slot = lane + i * 64, row = slot / CPR, c = (slot % CPR) * VE;
+      const int m = m0 + (wm * TM + tm) * 32 + row, co = co0 + wn * TN * 32 + c;
+      ok[i] = (m < p.M) & (co < p.C_out);
+      const int mm = ok[i] ? m : 0;
+      const int q = fastdiv(mm, p.by_w), ow = mm - q * p.W_out;
+      const int n = fastdiv(q, p.by_r), oh = p.out_lo + q - n * p.R;
+      ya[i] = ((size_t)(n * p.y_rows + oh - p.y_row0) * p.W_out + ow) * p.C_out + co;
+      rr[i] = u32x4{0u, 0u, 0u, 0u};
+      if (p.res && ok[i]) rr[i] = *(const u32x4*)((const T*)p.res + ((size_t)(n * p.r_rows + oh - p.r_row0) * p.W_out + ow) * p.C_out + co);
+    }
+#pragma unroll
+    for (int tn = 0; tn < TN; ++tn)
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+        *(f32x4*)(Cw + (lane & 31) * CPW + tn * 32 + g * 8 + (lane >> 5) * 4) =
+            f32x4{acc[tn][tm][g * 4], acc[tn][tm][g * 4 + 1], acc[tn][tm][g * 4 + 2], acc[tn][tm][g * 4 + 3]};
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+    for (int i = 0; i < PIECES; ++i) {
+      const int slot = lane + i * 64, row = slot / CPR, c = (slot % CPR) * VE;
+      if (!ok[i]) continue;
+      alignas(16) T in[VE], o[VE];
+      *(u32x4*)in = rr[i];
+#pragma unroll
+      for (int j = 0; j < VE; j += 4) {
+        f32x4 v = *(const f32x4*)(Cw + row * CPW + c + j);
+        if (p.bias) v += *(const f32x4*)(p.bias + co0 + wn * TN * 32 + c + j);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) o[j + k] = from_f32<T>(clamp_act(v[k] + to_f32(in[j + k]), cl));
+      }
+      *(u32x4*)((T*)p.y + ya[i]) = *(const u32x4*)o;
+      if (p.y2) *(u32x4*)((T*)p.y2 + ya[i]) = *(const u32x4*)o;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  }
+}
+
+template <typename T, int BM, int BN, int WM, int WN, int NST>
+__global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(2))) void conv_gemm_kernel(const GemmParams p) {
+  gemm_body<T, BM, BN, WM, WN, NST>(p, blockIdx.x, gridDim.x);
+}
+// The same for several bands of one layer in one grid (band b owns blocks first[b] .. first[b + 1] of x).
+template <typename T, int BM, int BN, int WM, int WN, int NST>
+__global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(2))) void conv_gemm_kernel_bands(const Batch<GemmParams> t) {
+  const int b = batch_find(t, blockIdx.x);
+  gemm_body<T, BM, BN, WM, WN, NST>(t.p[b], blockIdx.x - t.first[b], t.first[b + 1] - t.first[b]);
+}
+
+GemmParams make_gemm(const OpLaunch& L) {
+  GemmParams p;
+  p.x = L.x.ptr; p.y = L.y.ptr; p.y2 = L.y2; p.res = L.res.ptr; p.w = L.w; p.bias = L.bias;
+  p.x_row0 = L.x.row0; p.x_rows = L.x.rows; p.W = L.x.w; p.K = L.x.c;
+  p.y_row0 = L.y.row0; p.y_rows = L.y.rows; p.W_out = L.y.w; p.C_out = L.y.c;
+  p.r_row0 = L.res.row0; p.r_rows = L.res.rows;
+  p.sh = L.sh; p.sw = L.sw; p.ph = L.ph; p.pw = L.pw; p.act = L.act; p.k_pad = L.k_pad;
+  p.out_lo = L.out_lo; p.R = L.out_hi - L.out_lo; p.N = L.x.n;
+  p.M = p.N * p.R * p.W_out;
+  p.by_w = make_fastdiv(p.W_out); p.by_r = make_fastdiv(p.R); p.by_group = make_fastdiv(1);
+  return p;
+}
+
+bool gemm_shape(const OpLaunch& L) {
+  const int esz = L.dtype == LOP_BF16 ? 2 : 4, ke = 16 / esz;
+  if (L.op != LOP_CONV2D || L.kh != 1 || L.kw != 1 || L.x.c % ke != 0 || L.y.c % ke != 0) return false;
+  if (L.x.c * esz < 256) return false;                                    // (at least two stages)
+  if ((size_t)L.k_pad * esz * conv_cout_pad(L.y.c) >= ((size_t)1 << 31)) return false;
+  return (size_t)L.x.n * L.x.rows * L.x.w * L.x.c * esz < ((size_t)1 << 31);
+}
+
+struct GemmChoice { int bm = 0, bn = 0; };
+
+GemmChoice choose_gemm(const OpLaunch* Ls, int n) {
+  for (int b = 0; b < n; ++b)
+    if (!gemm_shape(Ls[b])) return {};
+  static const char* force = getenv("LOP_GEMM");
+  if (!force) return {};
+  int bm = 0, bn = 0;
+  if (sscanf(force, "%d,%d", &bm, &bn) != 2) return {};
+  if (Ls[0].dtype != LOP_BF16 && bm == 256) return {};
+  return {bm, bn};
+}
+
+template <typename T, int BM, int BN, int WM, int WN, int NST>
+hipError_t launch_tile(const OpLaunch* Ls, int n, hipStream_t s, KernelEvents* ev) {
+  GemmParams ps[kMaxBatch];
+  unsigned gx[kMaxBatch];
+  const unsigned gy = (unsigned)((Ls[0].y.c + BN - 1) / BN);
+  if ((int)gy * BN > conv_cout_pad(Ls[0].y.c)) return hipErrorInvalidValue;  // unguarded weight loads
+  int m = 0;
+  for (int b = 0; b < n; ++b) {
+    ps[m] = make_gemm(Ls[b]);
+    if (ps[m].M <= 0) continue;
+    ps[m].by_group = make_fastdiv(kGroupM * (int)gy);
+    gx[m] = (unsigned)((ps[m].M + BM - 1) / BM);
+    ++m;
+  }
+  if (m == 0) return hipSuccess;
+  return launch_group(conv_gemm_kernel<T, BM, BN, WM, WN, NST>, conv_gemm_kernel_bands<T, BM, BN, WM, WN, NST>, ps, m, gx, gy, 1,
+                      dim3(64 * WM * WN), s, ev);
+}
+
+}  // namespace
+
+bool gemm_applies(const OpLaunch* Ls, int n) { return n >= 1 && n <= kMaxBatch && choose_gemm(Ls, n).bm != 0; }
+
+hipError_t launch_gemm(const OpLaunch* Ls, int n, hipStream_t s, KernelEvents* ev) {
+  if (n < 1 || n > kMaxBatch) return hipErrorInvalidValue;
+  const GemmChoice c = choose_gemm(Ls, n);
+  if (Ls[0].dtype == LOP_BF16) {
+    if (c.bm == 256) return launch_tile<__bf16, 256, 256, 2, 4, 2>(Ls, n, s, ev);
+    if (c.bm == 128 && c.bn == 256) return launch_tile<__bf16, 128, 256, 2, 4, 3>(Ls, n, s, ev);
+    if (c.bm == 128 && c.bn == 128) return launch_tile<__bf16, 128, 128, 2, 2, 2>(Ls, n, s, ev);
+    if (c.bm == 64) return launch_tile<__bf16, 64, 64, 2, 2, 3>(Ls, n, s, ev);
+    return hipErrorInvalidValue;
+  }
+  if (c.bm == 128 && c.bn == 128) return launch_tile<float, 128, 128, 2, 2, 2>(Ls, n, s, ev);
+  if (c.bm == 128) return launch_tile<float, 128, 64, 2, 2, 3>(Ls, n, s, ev);
+  if (c.bm == 64 && c.bn == 64) return launch_tile<float, 64, 64, 2, 2, 3>(Ls, n, s, ev);
+  return hipErrorInvalidValue;
+}
+
+int gemm_describe(const OpLaunch* Ls, int n, char* name, size_t size) {
+  const GemmChoice c = choose_gemm(Ls, n);
+  if (name && size)
+    snprintf(name, size, "conv_gemm_kernel%s<%s, %d, %d>", n > 1 ? "_bands" : "", Ls[0].dtype == LOP_BF16 ? "__bf16" : "float", c.bm, c.bn);
+  return 1;
+}
+
+}  // namespace lop

@@ -32,7 +32,6 @@
 
 #include <algorithm>
 #include <cstdio>
-#include <cstdlib>
 
 #include "act.hpp"
 #include "conv_common.hpp"
@@ -356,7 +355,7 @@ __device__ __forceinline__ void patch_body(const PatchParams& p, const int bx, c
 }
 
 // Load instructions per wavefront and patch: the patch of a tile has at most NI * 256 / 9 pixels.
-constexpr int patch_loads(int tp, int s) { return s == 1 ? (tp == 4 ? 7 : tp == 2 ? 4 : 3) : (tp == 4 ? 20 : tp == 2 ? 11 : 6); }
+constexpr int patch_loads(int tp, int s) { return s == 1 ? (tp == 4 ? 7 : tp == 2 ? 4 : 3) : 6; }
 
 template <typename T, int BM, int BN, int NST, bool POOL, int S>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void conv_lds_kernel(const PatchParams p) {
@@ -426,7 +425,7 @@ bool patch_shape(const OpLaunch& L) {
 struct PatchChoice { int bm = 0, bn = 0; };
 struct PatchCost { int bm, bn; double chunk, rest, alone, first; };
 constexpr PatchCost kBf16Costs[] = {
-    {128, 64, 5800, 4900, 3300, 7000}, {64, 64, 3200, 2750, 1800, 4500}, {64, 32, 1860, 840, 1100, 3500}, {32, 32, 1200, 620, 750, 3000}};
+    {128, 64, 5800, 4900, 3300, 7000}, {64, 32, 1860, 840, 1100, 3500}, {32, 32, 1200, 620, 750, 3000}};
 // fp32: bound by its matrix instructions (2 304 cycles per chunk of a 32 x 32 tile)
 constexpr PatchCost kF32Costs[] = {{64, 32, 4700, 1500, 4900, 5000}, {32, 32, 2400, 900, 2500, 4000}};
 constexpr int kPatchUnits = 256;
@@ -523,7 +522,7 @@ hipError_t launch_tile(const OpLaunch* convs, const OpLaunch* pools, int n, hipS
     return launch_group(conv_lds_kernel<T, BM, BN, 2, false, 1>, conv_lds_kernel_bands<T, BM, BN, 2, false, 1>, ps, m, gx, gy, 1,
                         dim3(256), s, ev);
   }
-  if constexpr (BM == 128) {
+  if constexpr (BM != 32) {
     return hipErrorInvalidValue;
   } else {
     if (pools) return hipErrorInvalidValue;
@@ -542,14 +541,11 @@ hipError_t launch_patch(const OpLaunch* convs, const OpLaunch* pools, int n, hip
   if (n < 1 || n > kMaxBatch) return hipErrorInvalidValue;
   const PatchChoice c = choose_patch(convs, pools, n);
   if (convs[0].dtype == LOP_BF16) {
-    if (c.bm == 128 && c.bn == 64) return launch_tile<__bf16, 128, 64>(convs, pools, n, s, ev);
-    if (c.bm == 128) return launch_tile<__bf16, 128, 32>(convs, pools, n, s, ev);
-    if (c.bm == 64 && c.bn == 64) return launch_tile<__bf16, 64, 64>(convs, pools, n, s, ev);
+    if (c.bm == 128) return launch_tile<__bf16, 128, 64>(convs, pools, n, s, ev);
     if (c.bm == 64) return launch_tile<__bf16, 64, 32>(convs, pools, n, s, ev);
     if (c.bm == 32) return launch_tile<__bf16, 32, 32>(convs, pools, n, s, ev);
     return hipErrorInvalidValue;
   }
-  if (c.bm == 64 && c.bn == 64) return launch_tile<float, 64, 64>(convs, pools, n, s, ev);
   if (c.bm == 64) return launch_tile<float, 64, 32>(convs, pools, n, s, ev);
   if (c.bm == 32) return launch_tile<float, 32, 32>(convs, pools, n, s, ev);
   return hipErrorInvalidValue;

@@ -97,6 +97,11 @@ int stem_describe_bands(const OpLaunch* Ls, int n, char* name, size_t size);
 bool patch_applies(const OpLaunch* convs, const OpLaunch* pools, int n);
 hipError_t launch_patch(const OpLaunch* convs, const OpLaunch* pools, int n, hipStream_t stream, KernelEvents* ev);
 int patch_describe(const OpLaunch* convs, const OpLaunch* pools, int n, char* name, size_t size);
+// The matrix-product kernel of 1 x 1 convolutions: whether a group of bands takes it, the launch and
+// its kernel name.
+bool gemm_applies(const OpLaunch* Ls, int n);
+hipError_t launch_gemm(const OpLaunch* Ls, int n, hipStream_t stream, KernelEvents* ev);
+int gemm_describe(const OpLaunch* Ls, int n, char* name, size_t size);
 // A dense convolution and the 2 x 2 stride-2 max pooling that reads it, as one launch: whether
 // the pair qualifies (descriptors without slabs suffice), the launch (conv: input slab, weights,
 // hyper-parameters; pool: output slab, y2 and the pooled rows out_lo..out_hi) and its kernel name.

@@ -1342,3 +1342,53 @@ def test_merged_chain_agrees_with_its_bands(oracle, name, kw, flags, graph):
         assert rel_err(first, bands) <= TOL[chain.dtype]
     finally:
         plan.destroy()
+
+
+PATCH_GRID = [
+    # dtype, c_in, c_out, stride, pooled, shape(n,h,w), residual, the tile expected
+    ("bf16", 128, 128, 1, False, (2, 97, 211), True, "<__bf16, 128, 64, 2, false, 1>"),   # ragged in both directions, batch 2
+    ("bf16", 256, 72, 1, False, (1, 50, 70), False, "<__bf16, 64, 32, 2, false, 1>"),     # channels end inside a tile, four patches
+    ("bf16", 64, 200, 1, False, (1, 29, 31), False, "<__bf16, 32, 32, 2, false, 1>"),     # one patch, no next one
+    ("bf16", 64, 64, 1, False, (1, 1500, 2), True, "<__bf16, 32, 32, 2, false, 1>"),      # an image two pixels wide
+    ("bf16", 128, 136, 2, False, (1, 27, 45), False, "<__bf16, 32, 32, 2, false, 2>"),    # stride 2: even and odd columns apart
+    ("f32", 32, 40, 1, False, (1, 47, 61), False, "<float, 32, 32, 2, false, 1>"),
+    ("f32", 64, 64, 1, False, (2, 150, 170), True, "<float, 64, 32, 2, false, 1>"),
+    ("f32", 32, 64, 2, False, (1, 117, 107), False, "<float, 32, 32, 2, false, 2>"),
+    ("bf16", 64, 64, 1, True, (1, 131, 133), False, "<__bf16, 64, 32, 2, true, 1>"),      # odd sizes: last row and column unused
+    ("bf16", 128, 128, 1, True, (2, 181, 183), False, "<__bf16, 128, 64, 2, true, 1>"),
+    ("bf16", 512, 256, 1, True, (1, 15, 17), False, "<__bf16, 32, 32, 2, true, 1>"),
+    ("f32", 32, 40, 1, True, (1, 61, 67), False, "<float, 32, 32, 2, true, 1>"),
+    ("f32", 64, 64, 1, True, (2, 130, 150), False, "<float, 64, 32, 2, true, 1>"),
+]
+
+
+@pytest.mark.parametrize("cfg", PATCH_GRID)
+def test_patch_form_of_the_lds_staged_kernel(oracle, cfg):
+    """3 x 3 convolutions whose input is staged once per tile: every tile, checked by name, against
+    the oracle in one band, with all bands in one launch and with shared rows; small integers bit
+    for bit."""
+    dtype, c_in, c_out, stride, pooled, shape, residual, tile = cfg
+    chain = workloads.Chain("patch", (shape[0], c_in, shape[1], shape[2]), dtype, 3)
+    first = chain.add(workloads.CONV, c_in, c_out, 1, stride, 0, act="none") if residual else workloads.NO_RESIDUAL
+    chain.add(workloads.CONV, c_in, c_out, 3, stride, 1, act="relu", input_from=workloads.CHAIN_INPUT, residual_from=first)
+    if pooled:
+        chain.add(workloads.MAXPOOL, c_out, c_out, 2, 2, 0)
+    t = workloads.make_tensors(chain, zero_bias=False, seed=29)
+    plan = lop.Plan(chain, t, 1)
+    try:
+        assert plan.layer_kernel(0, plan.n_layers - 1)[0] == "conv_lds_kernel" + tile
+    finally:
+        plan.destroy()
+    want = oracle.run_chain(chain, t)
+    ti = workloads.small_int_tensors(chain, seed=3)
+    if dtype == "bf16":
+        ti.weights = [w if w is None else np.sign(w) * (np.abs(w) > 1) * (np.arange(w.size).reshape(w.shape) % 5 == 0) for w in ti.weights]
+    want_int = oracle.run_chain(chain, ti)
+    exact = np.abs(want_int).max() <= (256 if dtype == "bf16" else 2 ** 24)
+    for bands, flags in ((1, 0), (3, 0), (3, lop.LOP_FLAG_REUSE)):
+        dev, host = run_gpu(chain, t, n_bands=bands, flags=flags)
+        np.testing.assert_array_equal(dev, host)
+        assert rel_err(dev, want) <= TOL[dtype], (bands, flags)
+        if exact:
+            dev, _ = run_gpu(chain, ti, n_bands=bands, flags=flags)
+            np.testing.assert_array_equal(dev, want_int)
