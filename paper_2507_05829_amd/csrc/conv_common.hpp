@@ -57,6 +57,19 @@ __device__ __forceinline__ void mma<float>(const u32x4& wa, const u32x4& px, f32
   acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[3], b[3], acc, 0, 0, 0);
 }
 
+// The matrix instructions of one operand pair (bf16: one, fp32: four), one at a time: a loop over
+// several accumulators issues each accumulator's next one only after the others' current ones, so none
+// waits for the result of the one before it.
+template <typename T> constexpr int kMmaParts = sizeof(T) == 4 ? 4 : 1;
+template <typename T>
+__device__ __forceinline__ void mma_part(const u32x4& wa, const u32x4& px, f32x16& acc, int e) {
+  if constexpr (sizeof(T) == 2) {
+    mma<T>(wa, px, acc);
+  } else {
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__builtin_bit_cast(f32x4, wa)[e], __builtin_bit_cast(f32x4, px)[e], acc, 0, 0, 0);
+  }
+}
+
 // Which tile a workgroup takes. The hardware hands workgroups to the 8 XCDs round-robin in
 // launch order (x fastest), and every XCD has an L2 of its own: in launch order the 64
 // workgroups that are resident on one XCD at a time would be scattered over the whole grid

@@ -154,11 +154,12 @@ __device__ __forceinline__ void gemm_body(const GemmParams& p, const int bx, con
   wait_reads(fa[0], fb[0]);
 
   auto multiply = [&](u32x4 (&a)[TM], u32x4 (&b)[TN], int s, bool loads) __attribute__((always_inline)) {
-    constexpr int NM = TM * TN;
+    constexpr int NT = TM * TN, NM = NT * kMmaParts<T>;
 #pragma unroll
     for (int i = 0; i < (NM > LPS ? NM : LPS); ++i) {
       if (i < NM) {
-        mma<T>(b[i / TM], a[i % TM], acc[i / TM][i % TM]);
+        const int t = i % NT;
+        mma_part<T>(b[t / TM], a[t % TM], acc[t / TM][t % TM], i / NT);
         if (loads) __builtin_amdgcn_sched_barrier(0);
       }
       if (loads && i < LPS) {
@@ -281,17 +282,39 @@ bool gemm_shape(const OpLaunch& L) {
   return (size_t)L.x.n * L.x.rows * L.x.w * L.x.c * esz < ((size_t)1 << 31);
 }
 
+// The tile of a launch over the bands of a group, or bm == 0 where there is too little of it for these
+// tiles and the mid-size kernels, which split the reduction over the wavefronts, are faster.
+// Measured, in us before -> after: bf16 8192 x 1024 -> 4096 (512 tiles of 256 x 256) 94 -> 76, 8192 x 4096 ->
+// 1024 (128 of them) 88 -> 93 alone but 1 396 -> 1 059 for both layers on four streams, since only the
+// 256-wide tile asks the L2s for little enough while other launches run beside it; 5422 x 984 -> 1040
+// (215 tiles of 128 x 256) 31 -> 24; 4096 x 4096 -> 1024 (512 of 128 x 64) 89 -> 43, against 53 with 128 tiles
+// of 128 x 256; 1000 x 2048 -> 512 (64 of 128 x 64) 11 there, 16 here. fp32 3001 x 512 -> 2048 (1 504 tiles of
+// 64 x 64) 85 -> 64 and 2048 -> 512 (376) 87 -> 78; 1500 x 1024 -> 256 (96) 18 there, 23 here; 8000 x 1000 -> 3000
+// (1 512 tiles of 128 x 128) 479 -> 432, against 455 with 64 x 64.
 struct GemmChoice { int bm = 0, bn = 0; };
+constexpr long kBigTiles = 128;        // 256 x 256, bf16
+constexpr long kWideTiles = 192;       // 128 x 256, bf16
+constexpr long kNarrowTiles = 384;     // 128 x 64, bf16
+constexpr long kF32BigTiles = 1024;    // 128 x 128, fp32
+constexpr long kF32Tiles = 320;        // 64 x 64, fp32
 
 GemmChoice choose_gemm(const OpLaunch* Ls, int n) {
   for (int b = 0; b < n; ++b)
     if (!gemm_shape(Ls[b])) return {};
-  static const char* force = getenv("LOP_GEMM");
-  if (!force) return {};
-  int bm = 0, bn = 0;
-  if (sscanf(force, "%d,%d", &bm, &bn) != 2) return {};
-  if (Ls[0].dtype != LOP_BF16 && bm == 256) return {};
-  return {bm, bn};
+  const int c_out = Ls[0].y.c;
+  auto tiles = [&](int bm, int bn) {
+    if ((c_out + bn - 1) / bn * bn > conv_cout_pad(c_out)) return 0L;
+    long t = 0;
+    for (int b = 0; b < n; ++b) t += ((long)Ls[b].x.n * std::max(Ls[b].out_hi - Ls[b].out_lo, 0) * Ls[b].y.w + bm - 1) / bm;
+    return t * ((c_out + bn - 1) / bn);
+  };
+  if (Ls[0].dtype == LOP_BF16) {
+    if (tiles(256, 256) >= kBigTiles) return {256, 256};
+    if (tiles(128, 64) < kNarrowTiles) return {};
+    return tiles(128, 256) >= kWideTiles ? GemmChoice{128, 256} : GemmChoice{128, 64};
+  }
+  if (tiles(128, 128) >= kF32BigTiles) return {128, 128};
+  return tiles(64, 64) >= kF32Tiles ? GemmChoice{64, 64} : GemmChoice{};
 }
 
 template <typename T, int BM, int BN, int WM, int WN, int NST>
@@ -323,13 +346,11 @@ hipError_t launch_gemm(const OpLaunch* Ls, int n, hipStream_t s, KernelEvents* e
   if (Ls[0].dtype == LOP_BF16) {
     if (c.bm == 256) return launch_tile<__bf16, 256, 256, 2, 4, 2>(Ls, n, s, ev);
     if (c.bm == 128 && c.bn == 256) return launch_tile<__bf16, 128, 256, 2, 4, 3>(Ls, n, s, ev);
-    if (c.bm == 128 && c.bn == 128) return launch_tile<__bf16, 128, 128, 2, 2, 2>(Ls, n, s, ev);
-    if (c.bm == 64) return launch_tile<__bf16, 64, 64, 2, 2, 3>(Ls, n, s, ev);
+    if (c.bm == 128) return launch_tile<__bf16, 128, 64, 2, 2, 3>(Ls, n, s, ev);
     return hipErrorInvalidValue;
   }
-  if (c.bm == 128 && c.bn == 128) return launch_tile<float, 128, 128, 2, 2, 2>(Ls, n, s, ev);
-  if (c.bm == 128) return launch_tile<float, 128, 64, 2, 2, 3>(Ls, n, s, ev);
-  if (c.bm == 64 && c.bn == 64) return launch_tile<float, 64, 64, 2, 2, 3>(Ls, n, s, ev);
+  if (c.bm == 128) return launch_tile<float, 128, 128, 2, 2, 2>(Ls, n, s, ev);
+  if (c.bm == 64) return launch_tile<float, 64, 64, 2, 2, 3>(Ls, n, s, ev);
   return hipErrorInvalidValue;
 }
 

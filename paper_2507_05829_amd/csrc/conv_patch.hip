@@ -196,9 +196,11 @@ __device__ __forceinline__ void patch_body(const PatchParams& p, const int bx, c
       if (t < 8) read_tap(buf, t + 1, nxt);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int a = 0; a < NT; ++a)
+      for (int e = 0; e < kMmaParts<T>; ++e)
 #pragma unroll
-        for (int f = 0; f < TP; ++f) mma<T>(wreg[t][a], now[f], acc[a][f]);
+        for (int a = 0; a < NT; ++a)
+#pragma unroll
+          for (int f = 0; f < TP; ++f) mma_part<T>(wreg[t][a], now[f], acc[a][f], e);
       __builtin_amdgcn_sched_barrier(0);
       if (more) fetch_tap(c + 1, t);
       __builtin_amdgcn_sched_barrier(0);

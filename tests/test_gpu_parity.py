@@ -1392,3 +1392,56 @@ def test_patch_form_of_the_lds_staged_kernel(oracle, cfg):
         if exact:
             dev, _ = run_gpu(chain, ti, n_bands=bands, flags=flags)
             np.testing.assert_array_equal(dev, want_int)
+
+
+GEMM_GRID = [
+    # dtype, m, k, n, residual, the tile expected
+    ("bf16", 8 * 256 * 2 + 37, 136, 8 * 256 - 8, True, "<__bf16, 256, 256>"),   # ragged rows and channels, the last stage holds one chunk
+    ("bf16", 4300, 328, 1288, False, "<__bf16, 128, 256>"),                      # three stages, as many as are kept in flight
+    ("bf16", 9000, 512, 360, True, "<__bf16, 128, 64>"),
+    ("f32", 1300, 72, 1300, True, "<float, 64, 64>"),
+    ("f32", 4100, 92, 4100, False, "<float, 128, 128>"),
+]
+
+
+@pytest.mark.parametrize("cfg", GEMM_GRID)
+def test_matrix_product_kernel(oracle, cfg):
+    """Matrix products whose operands go straight to LDS: every tile, checked by name, against the
+    oracle and small integers bit for bit."""
+    dtype, m, k, n, residual, tile = cfg
+    chain = workloads.RowChain("gemm", m, k, dtype, 1)
+    if residual:
+        chain.add(n, "none").add(n, "relu", residual_from=0, input_from=-1)
+    else:
+        chain.add(n, "relu")
+    t = workloads.make_row_tensors(chain, zero_bias=False, seed=37)
+    want = oracle.run_row_chain(chain, t)
+    dev, host, names = _run_rows(chain, t)
+    assert names == {"conv_gemm_kernel" + tile}, names
+    np.testing.assert_array_equal(dev, host)
+    assert rel_err(dev, want) <= TOL[dtype]
+    rng = np.random.Generator(np.random.PCG64(14))
+    ti = workloads.Tensors(rng.integers(-1, 2, (m, k)).astype(np.float32),
+                           [rng.integers(-1, 2, (L.n, L.k)).astype(np.float32) for L in chain.layers],
+                           [rng.integers(-3, 4, L.n).astype(np.float32) for L in chain.layers])
+    want = oracle.run_row_chain(chain, ti)
+    assert np.abs(want).max() <= 256
+    dev, _, _ = _run_rows(chain, ti)
+    np.testing.assert_array_equal(dev, want)
+
+
+def test_matrix_product_kernel_on_images(oracle):
+    """The same kernel as a strided 1 x 1 convolution over a batch, in bands and with all bands in one
+    launch."""
+    chain = workloads.Chain("gemm", (2, 128, 141, 133), "bf16", 3)
+    chain.add(workloads.CONV, 128, 640, 1, 2, 0, act="relu")
+    t = workloads.make_tensors(chain, zero_bias=False, seed=41)
+    want = oracle.run_chain(chain, t)
+    for bands, flags in ((1, 0), (3, 0), (3, lop.LOP_FLAG_BATCH_BANDS)):
+        plan = lop.Plan(chain, t, bands, flags)
+        name = plan.layer_kernel(0, 0)[0]
+        plan.destroy()
+        assert name.startswith("conv_gemm_kernel") or bands == 3, name
+        dev, host = run_gpu(chain, t, n_bands=bands, flags=flags)
+        np.testing.assert_array_equal(dev, host)
+        assert rel_err(dev, want) <= TOL["bf16"]
