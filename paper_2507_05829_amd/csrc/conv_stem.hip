@@ -357,6 +357,7 @@ hipError_t launch_stem_bands(const OpLaunch* Ls, int n, hipStream_t stream, Kern
   const OpLaunch& L = Ls[0];
   const int kj = stem_kj(L);
   const bool bf = L.dtype == LOP_BF16;
+  if (stem_mfma_applies(L)) return launch_stem_mfma(Ls, n, stem_lane_pays(ps, m), stream, ev);
   if (stem_lane_pays(ps, m)) {
     if (stem_cpl(ps[0].C_out) == 32)
       return bf ? launch_stem_lane<__bf16, 32>(ps, m, kj, stream, ev) : launch_stem_lane<float, 32>(ps, m, kj, stream, ev);
@@ -376,7 +377,8 @@ int stem_describe_bands(const OpLaunch* Ls, int n, char* name, size_t size) {
   const char* const form = m > 1 ? "_bands" : "";
   const char* const type = L.dtype == LOP_BF16 ? "__bf16" : "float";
   if (name && size) {
-    if (m > 0 && stem_lane_pays(ps, m))
+    if (stem_mfma_applies(L)) stem_mfma_describe(L, m > 0 && stem_lane_pays(ps, m), form, name, size);
+    else if (m > 0 && stem_lane_pays(ps, m))
       snprintf(name, size, "conv_stem_lane_kernel%s<%s, %d, %d>", form, type, stem_kj(L), stem_cpl(L.y.c));
     else
       snprintf(name, size, "conv_stem_kernel%s<%s, %d>", form, type, stem_kj(L));

@@ -92,6 +92,16 @@ bool stem_applies(const OpLaunch& L);
 hipError_t launch_stem(const OpLaunch& L, hipStream_t stream, KernelEvents* ev = nullptr);
 int stem_describe(const OpLaunch& L, char* name, size_t size);
 int stem_describe_bands(const OpLaunch* Ls, int n, char* name, size_t size);
+// Its forms on the matrix cores (3 x 3 and 7 x 7 over three channels): whether a layer of this shape
+// gets the packing, where that lies behind the fp32 ones in OpLaunch::wstem, its size, the packing
+// itself; whether a launch takes them (large: the form for many tiles), the launch and its name.
+bool stem_mfma_shape(int c_in, int c_out, int kh, int kw);
+size_t stem_mfma_offset(int c_in, int c_out, int kh, int kw);
+size_t stem_mfma_bytes(int c_out, int kh, int dtype);
+void stem_mfma_pack(const unsigned char* src, int row_pitch, int c_out, int kh, int dtype, unsigned char* dst);
+bool stem_mfma_applies(const OpLaunch& L);
+hipError_t launch_stem_mfma(const OpLaunch* Ls, int n, bool large, hipStream_t stream, KernelEvents* ev);
+void stem_mfma_describe(const OpLaunch& L, bool large, const char* form, char* name, size_t size);
 // The patch form of the LDS-staged kernel (3 x 3 filters; pools: the max pooling behind each band's
 // convolution, or nullptr): whether a group of bands takes it, the launch and its kernel name.
 bool patch_applies(const OpLaunch* convs, const OpLaunch* pools, int n);

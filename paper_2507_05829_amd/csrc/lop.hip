@@ -189,6 +189,11 @@ int upload_weights(lop_plan_t* P) {
             q[((size_t)(co / 4) * K + k) * 4 + co % 4] = v;
             q[(size_t)d.c_out * K + ((size_t)(co / 16) * K + k) * 16 + co % 16] = v;
           }
+        if (lop::stem_mfma_shape(d.c_in, d.c_out, d.kh, d.kw)) {   // ... and in the order of the matrix cores
+          const size_t at = q.size();
+          q.resize(at + lop::stem_mfma_bytes(d.c_out, d.kh, t.in.dtype) / 4, 0.f);
+          lop::stem_mfma_pack(host.data(), kp, d.c_out, d.kh, t.in.dtype, (unsigned char*)(q.data() + at));
+        }
         LOP_HIP(lop::dev_alloc(&P->d_wstem[l], q.size() * 4));
         LOP_HIP(hipMemcpy(P->d_wstem[l], q.data(), q.size() * 4, hipMemcpyHostToDevice));
       }

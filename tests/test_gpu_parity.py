@@ -1445,3 +1445,27 @@ def test_matrix_product_kernel_on_images(oracle):
         dev, host = run_gpu(chain, t, n_bands=bands, flags=flags)
         np.testing.assert_array_equal(dev, host)
         assert rel_err(dev, want) <= TOL["bf16"]
+
+
+@pytest.mark.parametrize("cfg", [
+    ("bf16", 96, 3, 1, 1, (2, 21, 131), 2),     # three channel tiles; rows end three pixels into a column tile
+    ("bf16", 64, 7, 1, 3, (1, 20, 70), 3),      # 7 x 7 stride 1: shifted copy, groups of two filter rows in a step
+    ("bf16", 32, 3, 1, 0, (1, 9, 66), 1),       # exactly one column tile, no padding
+    ("f32", 64, 3, 2, 1, (1, 33, 140), 2),
+    ("f32", 32, 7, 1, 2, (2, 17, 67), 2),
+])
+def test_first_layer_on_the_matrix_cores(oracle, cfg):
+    """Odd sizes of the matrix-core first-layer forms; and an infinite pixel reaches exactly the
+    windows it lies in (what is read behind a window's end is cleared)."""
+    dtype, c_out, k, s_, p_, shape, bands = cfg
+    chain = workloads.Chain("stem", (shape[0], 3, shape[1], shape[2]), dtype, bands)
+    chain.add(workloads.CONV, 3, c_out, k, s_, p_, 1, "none")
+    t = workloads.make_tensors(chain, zero_bias=False, seed=43)
+    want = oracle.run_chain(chain, t)
+    dev, host = run_gpu(chain, t)
+    np.testing.assert_array_equal(dev, host)
+    assert rel_err(dev, want) <= TOL[dtype]
+    t.x[0, 1, shape[1] // 2, shape[2] // 2] = np.inf
+    hit = ~np.isfinite(oracle.run_chain(chain, t))
+    dev, _ = run_gpu(chain, t)
+    np.testing.assert_array_equal(~np.isfinite(dev), hit)
