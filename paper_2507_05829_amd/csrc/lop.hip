@@ -692,10 +692,11 @@ void launch_work(const lop_plan_t* P, int band, int l, double* flop, double* byt
 
 void* device_view_of_host(lop_plan_t* P, void* h_out);
 
-// Small band outputs leave through the last layer's own stores: its kernel writes every
-// element to the device tensor and to the mapped host buffer, so there is no copy launch to
-// wait for on the lane. Larger outputs keep the paced copy kernel (stores over PCIe from a
-// whole grid hold up the HBM writes of the kernels beside them).
+// Small outputs (of a band, or of a chain whose bands run as merged launches) leave through the
+// last layer's own stores: its kernel writes every element to the device tensor and to the mapped
+// host buffer, so there is no copy launch to wait for on the lane. Larger outputs keep the paced copy kernel (stores over PCIe from a
+// whole grid hold up the HBM writes of the kernels beside them: the 720p chain in reuse mode, 1.8 MB
+// out, 90 us with the last layer's own stores, 72 with the copy kernel behind it, 60 without a copy).
 constexpr size_t kDirectHostStoreMax = 256 * 1024;
 // Workgroups of a band copy that shares a stream with kernels: its stores are paced by the
 // link, and many of them in flight hold up the HBM writes of the kernels running beside the
@@ -706,15 +707,14 @@ constexpr int kCopyWorkgroups = 4;
 constexpr size_t kCopyLaneMaxBytes = (size_t)64 << 20;
 
 // Device view of h_out if the launches of one band (merged false), or those of the whole chain,
-// can deliver their rows that way, else nullptr. The bound is on the bytes per band in either
-// form: a chain's last launch stores the rows of all its bands.
+// can deliver their rows that way, else nullptr.
 void* direct_host_target(lop_plan_t* P, int band, void* h_out, bool merged) {
   if (!h_out || (P->flags & (LOP_FLAG_NO_D2H | LOP_FLAG_DMA_COPY))) return nullptr;
   const lop::Tables& t = P->t;
   const int last = t.n_layers() - 1;
   const Fusion& F = merged ? P->fuse_chain : P->fuse_band;
   if (F.head[last] >= 0 && !ends_convpool(F, last)) return nullptr;
-  const lop_rows_t r = t.bands[merged ? 0 : band].need[t.n_layers()];   // (the first band is the longest)
+  const lop_rows_t r = t.bands[merged ? t.whole() : band].need[t.n_layers()];
   const size_t bytes = (size_t)t.in.n * (r.hi - r.lo) * t.row_elems(last) * t.esz();
   if (bytes == 0 || bytes > kDirectHostStoreMax) return nullptr;
   if (!ends_convpool(F, last) &&   // (the pooled launch stores to both destinations)
@@ -1064,58 +1064,22 @@ int enqueue_merged_kernels(lop_plan_t* P, const void* d_in, void* d_out, hipStre
   return LOP_OK;
 }
 
-// A chain whose launches are merged over the bands (Sec. IV-D operation batching), on one lane's
-// scratch and on stream `cs`: per layer one launch for the rows of all bands, then the rows to
-// the host (through the last launch's own stores where they are few, else by a copy behind it).
-int enqueue_chain_merged(lop_plan_t* P, Lane& L, const void* d_in, void* d_out, void* h_out, hipStream_t cs,
-                         bool timing, bool capturing) {
-  const int nb = P->t.n_bands;
-  const bool copy = h_out && !(P->flags & LOP_FLAG_NO_D2H);
-  if (!capturing)
-    for (int b = 0; b < nb; ++b)
-      if (P->copied_valid[b]) {  // these rows of d_out may still be on their way to the host
-        LOP_HIP(hipStreamWaitEvent(cs, P->ev_copied[b], 0));
-        P->copied_valid[b] = 0;
-      }
-  if (timing)
-    for (int b = 0; b < nb; ++b)
-      if (!band_empty(P, b)) LOP_HIP(hipEventRecord(P->ev_c0[b], cs));
+// The kernels of a chain whose launches are merged over the bands (Sec. IV-D operation batching), on
+// one lane's scratch and on stream `cs`: per layer one launch for the rows of all bands. direct:
+// where the last one also stores its rows (device view of the host buffer), or nullptr.
+int enqueue_chain_merged(lop_plan_t* P, Lane& L, const void* d_in, void* d_out, void* direct, hipStream_t cs) {
   ChainScratch scratch(P, L.arena, L.conv_ws);
-  const int any = P->sched == ChainSched::kWhole ? P->t.whole() : 0;
-  void* const direct = copy ? direct_host_target(P, any, h_out, true) : nullptr;
-  int rc = enqueue_merged_kernels(P, d_in, d_out, cs, direct);
-  if (rc != LOP_OK) return rc;
-  if (timing)
-    for (int b = 0; b < nb; ++b)
-      if (!band_empty(P, b)) {
-        LOP_HIP(hipEventRecord(P->ev_c1[b], cs));
-        LOP_HIP(hipEventRecord(P->ev_d0[b], cs));
-      }
-  if (copy && !direct) {
-    rc = enqueue_band_copy(P, P->t.whole(), d_out, h_out, cs);
-    if (rc != LOP_OK) return rc;
-  }
-  if (timing)
-    for (int b = 0; b < nb; ++b)
-      if (!band_empty(P, b)) LOP_HIP(hipEventRecord(P->ev_d1[b], cs));
-  return LOP_OK;
+  return enqueue_merged_kernels(P, d_in, d_out, cs, direct);
 }
 
-// Orders stream `s` behind everything that may still use the lane's scratch, or still copies out
-// of the output buffer that is about to be written, and notes that `s` uses the scratch next.
-int take_lane(lop_plan_t* P, Lane& L, hipStream_t s, const void* d_out) {
-  for (Lane& O : P->lanes) {
-    const bool mine = &O == &L;
-    if (!mine && (!O.copying || O.copying != d_out)) continue;
-    if (!O.user) {
-      if (s == O.stream) continue;   // (stream order)
-      LOP_HIP(hipEventRecord(O.ev_join, O.stream));
-    }
-    LOP_HIP(hipStreamWaitEvent(s, O.ev_join, 0));
-    if (!mine) O.copying = nullptr;
+// Orders stream `s` behind everything that may still use the lane's scratch and notes that `s` uses it
+// next.
+int take_lane(Lane& L, hipStream_t s) {
+  if (L.user || s != L.stream) {   // (else stream order does it)
+    if (!L.user) LOP_HIP(hipEventRecord(L.ev_join, L.stream));
+    LOP_HIP(hipStreamWaitEvent(s, L.ev_join, 0));
   }
   L.user = s == L.stream ? nullptr : s;
-  L.copying = nullptr;
   return LOP_OK;
 }
 
@@ -1195,23 +1159,17 @@ int launch_graph(lop_plan_t* P, const void* d_in, void* d_out, void* h_out, hipS
   return LOP_OK;
 }
 
-// A merged chain as a graph: captured on lane `lane`'s own stream (with that lane's scratch),
-// replayed on `s`.
-int launch_graph_merged(lop_plan_t* P, int lane, const void* d_in, void* d_out, void* h_out, hipStream_t s) {
+// A merged chain's kernels as a graph: captured on lane `lane`'s own stream (with that lane's
+// scratch), replayed on `s`.
+int launch_graph_merged(lop_plan_t* P, int lane, const void* d_in, void* d_out, void* direct, hipStream_t s) {
   Lane& L = P->lanes[lane];
-  for (int b = 0; b < P->t.n_bands; ++b)   // copies of single bands that an earlier call has in flight
-    if (P->copied_valid[b]) {
-      LOP_HIP(hipStreamWaitEvent(s, P->ev_copied[b], 0));
-      P->copied_valid[b] = 0;
-    }
-  hipGraphExec_t exec = find_graph(P, d_in, d_out, h_out, lane, -1);
+  hipGraphExec_t exec = find_graph(P, d_in, d_out, direct, lane, -1);
   if (!exec) {
-    if (h_out) (void)device_view_of_host(P, h_out);  // query before capture starts
     hipGraph_t graph = nullptr;
     LOP_HIP(hipStreamBeginCapture(L.stream, hipStreamCaptureModeThreadLocal));
-    int rc = enqueue_chain_merged(P, L, d_in, d_out, h_out, L.stream, false, true);
+    int rc = enqueue_chain_merged(P, L, d_in, d_out, direct, L.stream);
     const hipError_t e = hipStreamEndCapture(L.stream, &graph);
-    rc = keep_graph(P, rc, e, graph, d_in, d_out, h_out, lane, -1, &exec);
+    rc = keep_graph(P, rc, e, graph, d_in, d_out, direct, lane, -1, &exec);
     if (rc != LOP_OK) return rc;
   }
   LOP_HIP(hipGraphLaunch(exec, s));
@@ -1230,15 +1188,36 @@ int run_merged(lop_plan_t* P, const void* d_in, void* d_out, void* h_out, hipStr
   P->cur_lane = lane;
   Lane& L = P->lanes[lane];
   hipStream_t s = user ? user : L.stream;
-  int rc = take_lane(P, L, s, d_out);
+  int rc = take_lane(L, s);
   if (rc != LOP_OK) return rc;
+  const int nb = P->t.n_bands;
+  for (int b = 0; b < nb; ++b)
+    if (P->copied_valid[b]) {  // copies of single bands of an earlier call that may still read d_out
+      LOP_HIP(hipStreamWaitEvent(s, P->ev_copied[b], 0));
+      P->copied_valid[b] = 0;
+    }
+  auto stamp = [&](std::vector<hipEvent_t>& ev) -> int {   // (the bands of a merged chain start and end together)
+    if (timing)
+      for (int b = 0; b < nb; ++b)
+        if (!band_empty(P, b)) LOP_HIP(hipEventRecord(ev[b], s));
+    return LOP_OK;
+  };
   if (timing) LOP_HIP(hipEventRecord(P->ev_t0, s));
-  rc = (P->flags & LOP_FLAG_GRAPH) && !timing ? launch_graph_merged(P, lane, d_in, d_out, h_out, s)
-                                              : enqueue_chain_merged(P, L, d_in, d_out, h_out, s, timing, false);
+  if ((rc = stamp(P->ev_c0)) != LOP_OK) return rc;
+  const bool copy = h_out && !(P->flags & LOP_FLAG_NO_D2H);
+  void* const direct = copy ? direct_host_target(P, P->sched == ChainSched::kWhole ? P->t.whole() : 0, h_out, true) : nullptr;
+  rc = (P->flags & LOP_FLAG_GRAPH) && !timing ? launch_graph_merged(P, lane, d_in, d_out, direct, s)
+                                              : enqueue_chain_merged(P, L, d_in, d_out, direct, s);
   if (rc != LOP_OK) return rc;
+  if ((rc = stamp(P->ev_c1)) != LOP_OK || (rc = stamp(P->ev_d0)) != LOP_OK) return rc;
+  if (copy && !direct) {
+    // (behind the graph, not a node of it: as a node of every lane's graph it held up the other
+    // lanes' graphs, 198 against 161 us on a batch of two through the inverted-residual chain)
+    rc = enqueue_band_copy(P, P->t.whole(), d_out, h_out, s);
+    if (rc != LOP_OK) return rc;
+  }
+  if ((rc = stamp(P->ev_d1)) != LOP_OK) return rc;
   if (timing) LOP_HIP(hipEventRecord(P->ev_t1, s));
-  const int any = P->sched == ChainSched::kWhole ? P->t.whole() : 0;
-  if (h_out && !(P->flags & LOP_FLAG_NO_D2H) && !direct_host_target(P, any, h_out, true)) L.copying = d_out;
   return leave_lane(L);
 }
 
@@ -1468,7 +1447,7 @@ int lop_run_band(lop_plan_t* P, int band, const void* d_in, void* d_out, void* h
   hipStream_t ds = copy_stream ? (hipStream_t)copy_stream : P->s_copy;
   if (compute_stream) P->last_user_stream = cs;
   Lane& L = P->lane_of(band);
-  int rc = take_lane(P, L, cs, nullptr);
+  int rc = take_lane(L, cs);
   if (rc == LOP_OK) rc = enqueue_band(P, band, d_in, d_out, h_out, cs, ds, false);
   return rc == LOP_OK ? leave_lane(L) : rc;
 }
@@ -1504,7 +1483,7 @@ int lop_run_chain(lop_plan_t* P, const void* d_in, void* d_out, void* h_out, voi
   const bool merged = P->sched != ChainSched::kPerBand && (!timing || P->batched);
   if (!merged)
     for (Lane& L : P->lanes) {   // a merged chain of the caller's stream may still use a lane's scratch
-      int rc = take_lane(P, L, L.stream, nullptr);
+      int rc = take_lane(L, L.stream);
       if (rc != LOP_OK) return rc;
     }
   if (merged) {

@@ -31,9 +31,6 @@ struct Lane {
   // The stream of the caller's that last used this lane's scratch (ev_join was recorded behind
   // that use), or nullptr when the lane's own stream did.
   hipStream_t user = nullptr;
-  // Output buffer that the lane's last chain still copies to the host with a kernel behind its
-  // last layer, or nullptr: another lane must not overwrite it before that.
-  const void* copying = nullptr;
 };
 
 // Layers that run as one launch: head[t] = first layer of the group whose last layer is t
