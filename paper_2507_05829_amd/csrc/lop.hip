@@ -27,10 +27,12 @@ hipError_t launch_copy_rows(void* dst, const void* src, size_t pitch, size_t len
 hipError_t launch_fill_words(void* dst, size_t bytes, unsigned word, hipStream_t stream);
 
 hipError_t launch_pointwise(const OpLaunch& L, hipStream_t stream, KernelEvents* ev);
+size_t mbconv_bands_bytes(int c, int s);
+void mbconv_pack_bands(const float* w, int c, int s, unsigned short* dst);
 bool mbconv_applies(const OpLaunch& e, const OpLaunch& d, const OpLaunch& p);
 int mbconv_describe(const OpLaunch& d, const OpLaunch& p, char* name, size_t size);
-hipError_t launch_mbconv(const OpLaunch& e, const OpLaunch& d, const OpLaunch& p, hipStream_t stream,
-                         KernelEvents* ev);
+hipError_t launch_mbconv_bands(const OpLaunch* es, const OpLaunch& d, const OpLaunch* ps, int n, hipStream_t stream,
+                               KernelEvents* ev);
 int pointwise_describe(const OpLaunch& L, char* name, size_t size);
 int conv_igemm_describe(const OpLaunch& L, char* name, size_t size);
 int rowwise_describe(const OpLaunch& L, char* name, size_t size);
@@ -241,6 +243,12 @@ int upload_weights(lop_plan_t* P) {
           }
           host[(size_t)tap * d.c_in + c] = v;
         }
+      if (bf && d.c_in % 32 == 0 && d.kh == 3 && d.kw == 3 && d.sh == d.sw && (d.sh == 1 || d.sh == 2)) {
+        // ... and behind it the same weights as the fused block kernel's matrix operands
+        const size_t at = host.size();
+        host.resize(at + lop::mbconv_bands_bytes(d.c_in, d.sh) / 4);
+        lop::mbconv_pack_bands(host.data(), d.c_in, d.sh, (unsigned short*)(host.data() + at));
+      }
       LOP_HIP(lop::dev_alloc(&P->d_w[l], host.size() * 4));
       LOP_HIP(hipMemcpy(P->d_w[l], host.data(), host.size() * 4, hipMemcpyHostToDevice));
     }
@@ -252,7 +260,13 @@ int upload_weights(lop_plan_t* P) {
   return LOP_OK;
 }
 
-bool layer_batchable(const lop_plan_t* P, int l);
+// The images a merged chain's launches work on while it is enqueued: they lie from image `first` on
+// in the caller's tensors, and from the buffers' beginning in the arena.
+struct ChainPass {
+  lop_plan_t* P;
+  ChainPass(lop_plan_t* plan, int first, int images) : P(plan) { P->pass_first = first; P->pass_images = images; }
+  ~ChainPass() { P->pass_first = 0; P->pass_images = 0; }
+};
 
 // Last launch (by the index of the layer it ends with) that reads layer l's output, under either
 // set of fused groups; l itself if nobody does.
@@ -297,12 +311,12 @@ size_t place_slabs(const lop_plan_t* P, const std::vector<size_t>& size, std::ve
   return worst;
 }
 
-// A chain's launches are merged over its bands (kGrouped, kWhole) while what it keeps between
-// launches fits this. It is the size of the static array, so that lop_run_chain_static, which has
-// no more than that, runs the launches lop_run_chain does; and it is a quarter of the 256 MB
-// Infinity Cache, so that four chains in flight keep their intermediate rows on the chip. Larger
-// chains run band by band: their launches are long enough by themselves, and one band's rows
-// stay closer to the compute units than a whole chain's.
+// What a merged chain (kGrouped, kWhole) keeps between launches fits this: images of a batch, and
+// then bands, are dealt to passes of equal size, as few as do. It is the size of the static array,
+// so that lop_run_chain_static, which has no more than that, runs the launches lop_run_chain does;
+// and it is a quarter of the 256 MB Infinity Cache, so that four chains in flight keep their
+// intermediate rows on the chip. A chain too large even for one image (or one band of one image)
+// runs band by band: its launches are long enough by themselves.
 constexpr size_t kMergeMaxBytes = LOP_STATIC_SCRATCH_BYTES;
 // A chain of row-wise operators has no halo, and callers that stream matrix rows run its bands one
 // by one: below this many rows its chain runs the bands' own launches (same sums in the same
@@ -311,81 +325,87 @@ constexpr int kMergeMinRows = 2048;
 
 void size_scratch(lop_plan_t* P) {
   const lop::Tables& t = P->t;
-  const int nl = t.n_layers(), nb = t.n_bands;
-  P->slab_off.assign(nb + 1, std::vector<size_t>(nl, 0));
+  const int nl = t.n_layers(), nb = t.n_bands, n = t.in.n;
   auto kept = [&](int l) { return !P->fuse_band.away[l] || !P->fuse_chain.away[l]; };
-  auto rows_bytes = [&](int l, int rows) {
-    return rows > 0 && kept(l) ? align_up((size_t)t.in.n * rows * t.row_elems(l) * t.esz(), 256) : (size_t)0;
+  auto rows_bytes = [&](int images, int l, int rows) {
+    return rows > 0 && kept(l) ? align_up((size_t)images * rows * t.row_elems(l) * t.esz(), 256) : (size_t)0;
   };
-  auto band_bytes = [&](int b, int l) { return rows_bytes(l, t.bands[b].need[l + 1].hi - t.bands[b].need[l + 1].lo); };
+  auto band_rows = [&](int b, int l) { return t.bands[b].need[l + 1].hi - t.bands[b].need[l + 1].lo; };
   std::vector<size_t> size(nl, 0);
-
-  // the whole chain on full-height buffers
-  for (int l = 0; l + 1 < nl; ++l) size[l] = rows_bytes(l, t.layers[l].h_out);
-  const size_t whole = place_slabs(P, size, &P->slab_off[nb]);
+  // full-height buffers of a whole chain
+  auto place_whole = [&](int images, std::vector<size_t>* off) {
+    for (int l = 0; l + 1 < nl; ++l) size[l] = rows_bytes(images, l, t.layers[l].h_out);
+    return place_slabs(P, size, off);
+  };
   // the slabs of bands [b0, b1) at once: one block per layer, the bands' slabs one behind the other in it
-  auto place_bands = [&](int b0, int b1) {
+  auto place_bands = [&](int images, int b0, int b1, std::vector<std::vector<size_t>>* off) {
     for (int l = 0; l + 1 < nl; ++l) {
       size[l] = 0;
-      for (int b = b0; b < b1; ++b) size[l] += band_bytes(b, l);
+      for (int b = b0; b < b1; ++b) size[l] += rows_bytes(images, l, band_rows(b, l));
     }
     std::vector<size_t> block(nl, 0);
     const size_t bytes = place_slabs(P, size, &block);
     for (int l = 0; l + 1 < nl; ++l) {
-      size_t off = block[l];
+      size_t at = block[l];
       for (int b = b0; b < b1; ++b) {
-        P->slab_off[b][l] = off;
-        off += band_bytes(b, l);
+        (*off)[b][l] = at;
+        at += rows_bytes(images, l, band_rows(b, l));
       }
     }
     return bytes;
   };
-  auto place_groups = [&](int per) {
+  auto place_groups = [&](int images, int per, std::vector<std::vector<size_t>>* off) {
     size_t most = 0;
-    for (int b = 0; b < nb; b += per) most = std::max(most, place_bands(b, std::min(nb, b + per)));
+    for (int b = 0; b < nb; b += per) most = std::max(most, place_bands(images, b, std::min(nb, b + per), off));
     return most;
   };
 
-  const bool rows_only = t.in.w == 1 && t.in.n * t.in.h < kMergeMinRows;
+  P->chain_off.assign(nb + 1, std::vector<size_t>(nl, 0));
   P->sched = ChainSched::kPerBand;
   P->group = nb;
-  size_t grouped = 0;
+  P->images = n;
+  size_t merged = 0;
+  const bool rows_only = t.in.w == 1 && n * t.in.h < kMergeMinRows;
   if (P->batched) {
     P->sched = ChainSched::kGrouped;
-    grouped = place_groups(nb);
-  } else if (P->flags & LOP_FLAG_PLAN_ONLY || (rows_only && nb > 1)) {
-    P->sched = ChainSched::kPerBand;
-  } else if (t.disjoint()) {
-    P->sched = whole <= kMergeMaxBytes ? ChainSched::kWhole : ChainSched::kPerBand;
-  } else {
-    // all bands in one group if they fit, else in as few equal groups, one after another, as do
-    bool all = true;
-    for (int l = 0; l < nl; ++l) all = all && (P->fuse_chain.away[l] || layer_batchable(P, l));
-    for (int groups = 1; groups < nb; ++groups) {
-      const int per = (nb + groups - 1) / groups;
-      if (per < 2 || (groups > 1 && !all)) break;
-      grouped = place_groups(per);
-      if (grouped > kMergeMaxBytes) continue;
-      P->sched = ChainSched::kGrouped;
-      P->group = per;
-      break;
+    merged = place_groups(n, nb, &P->chain_off);
+  } else if (!(P->flags & LOP_FLAG_PLAN_ONLY) && !(rows_only && nb > 1)) {
+    const bool whole = t.disjoint();
+    int images = 0;
+    for (int passes = 1; P->sched == ChainSched::kPerBand && images != 1; ++passes) {
+      images = (n + passes - 1) / passes;
+      merged = whole ? place_whole(images, &P->chain_off[nb]) : place_groups(images, nb, &P->chain_off);
+      if (merged <= kMergeMaxBytes) P->sched = whole ? ChainSched::kWhole : ChainSched::kGrouped;
     }
+    int per = nb;
+    // A pass over few rows whose launches take one band each is a crowd of small launches on one lane: eight bands
+    // and eight images of the inverted-residual chain layer by layer took 3.3 ms that way, band by band 2.2.
+    bool all = true;
+    for (int l = 0; l < nl; ++l)
+      all = all && (P->fuse_chain.away[l] || P->fuse_chain.head[l] >= 0 || lop::op_batchable(lop::describe_layer(P, l)));
+    if (!whole && !all && images != n) P->sched = ChainSched::kPerBand;
+    for (int groups = 2; !whole && all && P->sched == ChainSched::kPerBand && per != 1; ++groups) {
+      per = (nb + groups - 1) / groups;
+      merged = place_groups(1, per, &P->chain_off);
+      if (merged <= kMergeMaxBytes) P->sched = ChainSched::kGrouped;
+    }
+    if (P->sched != ChainSched::kPerBand) { P->group = per; P->images = images; }
+    else merged = 0;
   }
 
-  size_t worst = P->sched == ChainSched::kWhole ? whole : 0;
+  // bands that run one by one: in reuse mode on one full-height buffer per layer (rows at their
+  // absolute position), kept from band to band
+  P->slab_off.assign(nb + 1, std::vector<size_t>(nl, 0));   // (descriptors of the whole chain are made outside of a pass, too)
+  size_t single = 0;
   if (t.reuse) {
-    // bands share one full-height buffer per layer (rows at their absolute position), kept from
-    // band to band
-    size_t off = 0;
     for (int l = 0; l + 1 < nl; ++l) {
-      for (int b = 0; b < nb; ++b) P->slab_off[b][l] = off;
-      off += rows_bytes(l, t.layers[l].h_out);
+      for (int b = 0; b < nb; ++b) P->slab_off[b][l] = single;
+      single += rows_bytes(n, l, t.layers[l].h_out);
     }
-    worst = std::max(worst, off);
   } else {
-    worst = std::max(worst, P->sched == ChainSched::kGrouped ? grouped : place_groups(1));
+    single = place_groups(n, 1, &P->slab_off);
   }
-  P->arena_bytes = worst;
+  P->arena_bytes = std::max(single, merged);
 }
 
 lop::OpLaunch make_launch(const lop_plan_t* P, int band, int l, const void* d_in, void* d_out);
@@ -406,6 +426,7 @@ void size_workspace(lop_plan_t* P) {
       for (int b = 0; b < nb; ++b)
         if (P->t.bands[b].compute[l].hi > P->t.bands[b].compute[l].lo) add({make_launch(P, b, l, nullptr, nullptr)});
     if (!alone(P->fuse_chain)) continue;
+    const ChainPass pass(P, 0, P->images);
     if (P->sched == ChainSched::kWhole) add({make_launch(P, nb, l, nullptr, nullptr)});
     if (P->sched == ChainSched::kGrouped) {  // a launch for several bands keeps all their partial sums at once
       std::vector<lop::OpLaunch> group;
@@ -437,20 +458,23 @@ lop::Slab slab_of(const lop_plan_t* P, int band, int tensor, const void* d_in, v
   const lop::Tables& t = P->t;
   const int nl = t.n_layers();
   lop::Slab s;
-  s.n = t.in.n;
+  s.n = P->pass_images ? P->pass_images : t.in.n;
   s.h = t.tensor_h(tensor);
+  auto from_pass = [&](const void* base) -> void* {   // a caller's tensor, from the pass's first image on
+    return base ? (char*)const_cast<void*>(base) + (size_t)P->pass_first * s.h * t.row_elems(tensor) * t.esz() : nullptr;
+  };
   if (tensor < 0) {
-    s.ptr = const_cast<void*>(d_in);
+    s.ptr = from_pass(d_in);
     s.w = t.in.w; s.c = t.in.c; s.row0 = 0; s.rows = t.in.h;
   } else {
     s.w = t.layers[tensor].w_out;
     s.c = t.layers[tensor].d.c_out;
     if (tensor == nl - 1) {
-      s.ptr = d_out; s.row0 = 0; s.rows = s.h;
+      s.ptr = from_pass(d_out); s.row0 = 0; s.rows = s.h;
     } else {
       // (no arena yet while the plan is being sized, and none at all in a plan-only plan)
       char* const arena = (char*)P->arena_of(band);
-      s.ptr = arena ? arena + P->slab_off[band][tensor] : nullptr;
+      s.ptr = arena ? arena + (P->pass_images ? P->chain_off : P->slab_off)[band][tensor] : nullptr;
       if (t.reuse) {
         s.row0 = 0; s.rows = s.h;
       } else {
@@ -605,6 +629,15 @@ void convpool_launches(const lop_plan_t* P, int band, int l, const void* d_in, v
   *conv = make_launch(P, band, l - 1, d_in, d_out);   // (its y slab is never used: the layer has no buffer)
 }
 
+// The first and the last operator of an inverted-residual block's launch of one band: the block's
+// input slab, its output slab, residual and rows.
+void mbconv_launches(const lop_plan_t* P, int head, int band, int l, const void* d_in, void* d_out, lop::OpLaunch* e,
+                     lop::OpLaunch* p) {
+  *e = describe_layer(P, head);
+  e->x = slab_of(P, band, P->t.layers[head].d.input_from, d_in, d_out);
+  *p = make_launch(P, band, l, d_in, d_out);
+}
+
 // Rows of layer l one launch of band `band` produces (none for a layer that is part of a
 // later layer's launch).
 lop_rows_t launch_rows(const lop_plan_t* P, const Fusion& F, int band, int l) {
@@ -629,11 +662,9 @@ hipError_t launch_layer(const lop_plan_t* P, const Fusion& F, int band, int l, c
     pool.y2 = y2;
     return lop::launch_convpool(conv, pool, cs, ev);
   }
-  const int h = F.head[l];
-  lop::OpLaunch e = describe_layer(P, h), d = describe_layer(P, h + 1);
-  const lop::OpLaunch p = make_launch(P, band, l, d_in, d_out);
-  e.x = slab_of(P, band, P->t.layers[h].d.input_from, d_in, d_out);
-  return lop::launch_mbconv(e, d, p, cs, ev);
+  lop::OpLaunch e, p;
+  mbconv_launches(P, F.head[l], band, l, d_in, d_out, &e, &p);
+  return lop::launch_mbconv_bands(&e, describe_layer(P, F.head[l] + 1), &p, 1, cs, ev);
 }
 
 // Kernel name (and reduction slices) of that launch.
@@ -962,54 +993,51 @@ int enqueue_chain_reuse(lop_plan_t* P, const void* d_in, void* d_out, void* h_ou
   return LOP_OK;
 }
 
-// The descriptors of layer l's launch for bands [first, last) (convs: the conv of a conv + pooling
-// group, else empty).
+// The descriptors of layer l's launch for bands [first, last) (heads: the conv of a conv + pooling
+// group or the expand operator of an inverted-residual block, else empty).
 void batched_group(const lop_plan_t* P, int l, int first, int last, const void* d_in, void* d_out, void* y2,
-                   std::vector<lop::OpLaunch>* group, std::vector<lop::OpLaunch>* convs) {
+                   std::vector<lop::OpLaunch>* group, std::vector<lop::OpLaunch>* heads) {
   group->clear();
-  convs->clear();
+  heads->clear();
+  const Fusion& F = P->fuse_chain;
   for (int b = first; b < last; ++b) {
-    const lop_rows_t r = launch_rows(P, P->fuse_chain, b, l);
+    const lop_rows_t r = launch_rows(P, F, b, l);
     if (r.hi <= r.lo) continue;
-    lop::OpLaunch o = make_launch(P, b, l, d_in, d_out);
-    o.y2 = y2;
-    if (ends_convpool(P->fuse_chain, l)) {
-      lop::OpLaunch conv, pool;
-      convpool_launches(P, b, l, d_in, d_out, &conv, &pool);
-      pool.y2 = o.y2;
-      convs->push_back(conv);
-      group->push_back(pool);
+    lop::OpLaunch head, o;
+    if (F.head[l] < 0) {
+      o = make_launch(P, b, l, d_in, d_out);
     } else {
-      group->push_back(o);
+      if (ends_convpool(F, l)) convpool_launches(P, b, l, d_in, d_out, &head, &o);
+      else mbconv_launches(P, F.head[l], b, l, d_in, d_out, &head, &o);
+      heads->push_back(head);
     }
+    o.y2 = y2;
+    group->push_back(o);
   }
-}
-
-// Whether the launch that ends with layer l has a form that takes several bands.
-bool layer_batchable(const lop_plan_t* P, int l) {
-  if (P->fuse_chain.head[l] >= 0) return ends_convpool(P->fuse_chain, l);
-  return lop::op_batchable(describe_layer(P, l));
 }
 
 // Layer l of bands [first, last): one launch (plus its finish kernel, if the reduction is cut) per
 // kMaxBandsPerLaunch bands; one per band where the kernel takes no more.
 hipError_t launch_layer_batched(const lop_plan_t* P, int l, int first, int last, const void* d_in, void* d_out, hipStream_t cs,
                                 lop::KernelEvents* ev, void* y2) {
-  if (P->fuse_chain.away[l]) return hipSuccess;
-  if (!layer_batchable(P, l)) {
+  const Fusion& F = P->fuse_chain;
+  if (F.away[l]) return hipSuccess;
+  if (F.head[l] < 0 && !lop::op_batchable(lop::describe_layer(P, l))) {
     for (int b = first; b < last; ++b) {
-      const hipError_t e = launch_layer(P, P->fuse_chain, b, l, d_in, d_out, cs, ev, y2);
+      const hipError_t e = launch_layer(P, F, b, l, d_in, d_out, cs, ev, y2);
       if (e != hipSuccess) return e;
     }
     return hipSuccess;
   }
-  std::vector<lop::OpLaunch> group, convs;
+  std::vector<lop::OpLaunch> group, heads;
   for (; first < last; first += lop::kMaxBandsPerLaunch) {
-    batched_group(P, l, first, std::min(last, first + lop::kMaxBandsPerLaunch), d_in, d_out, y2, &group, &convs);
-    if (group.empty()) continue;
-    const hipError_t e = ends_convpool(P->fuse_chain, l)
-                             ? lop::launch_convpool_bands(convs.data(), group.data(), (int)group.size(), cs, ev)
-                             : lop::launch_op_bands(group.data(), (int)group.size(), cs, ev);
+    batched_group(P, l, first, std::min(last, first + lop::kMaxBandsPerLaunch), d_in, d_out, y2, &group, &heads);
+    const int n = (int)group.size();
+    if (n == 0) continue;
+    const hipError_t e = F.head[l] < 0 ? lop::launch_op_bands(group.data(), n, cs, ev)
+                         : ends_convpool(F, l)
+                             ? lop::launch_convpool_bands(heads.data(), group.data(), n, cs, ev)
+                             : lop::launch_mbconv_bands(heads.data(), describe_layer(P, F.head[l] + 1), group.data(), n, cs, ev);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
@@ -1051,16 +1079,21 @@ int enqueue_merged_kernels(lop_plan_t* P, const void* d_in, void* d_out, hipStre
     LOP_HIP(lop::launch_fill_words(P->arena_of(0), align_up(P->arena_bytes, 256), 0xFFFFFFFFu, cs));
     LOP_HIP(lop::launch_fill_words(P->ws_of(0), P->conv_ws_bytes / 16 * 16, 0xFFFFFFFFu, cs));
   }
-  const int nb = P->t.n_bands;
-  if (P->sched == ChainSched::kWhole) {
-    for (int l = 0; l < nl; ++l)
-      LOP_HIP(launch_layer(P, P->fuse_chain, whole, l, d_in, d_out, cs, nullptr, l == nl - 1 ? y2 : nullptr));
-    return LOP_OK;
+  const int nb = P->t.n_bands, n = P->t.in.n;
+  const size_t out_bytes = (size_t)P->t.layers.back().h_out * P->t.row_elems(nl - 1) * P->t.esz();   // of one image
+  for (int i = 0; i < n; i += P->images) {
+    const ChainPass pass(P, i, std::min(P->images, n - i));
+    void* const second = y2 ? (char*)y2 + i * out_bytes : nullptr;
+    if (P->sched == ChainSched::kWhole) {
+      for (int l = 0; l < nl; ++l)
+        LOP_HIP(launch_layer(P, P->fuse_chain, whole, l, d_in, d_out, cs, nullptr, l == nl - 1 ? second : nullptr));
+      continue;
+    }
+    for (int b = 0; b < nb; b += P->group)
+      for (int l = 0; l < nl; ++l)
+        LOP_HIP(launch_layer_batched(P, l, b, std::min(nb, b + P->group), d_in, d_out, cs, nullptr,
+                                     l == nl - 1 ? second : nullptr));
   }
-  for (int b = 0; b < nb; b += P->group)
-    for (int l = 0; l < nl; ++l)
-      LOP_HIP(launch_layer_batched(P, l, b, std::min(nb, b + P->group), d_in, d_out, cs, nullptr,
-                                   l == nl - 1 ? y2 : nullptr));
   return LOP_OK;
 }
 
@@ -1654,6 +1687,7 @@ int lop_profile_chain(lop_plan_t* P, const void* d_in, void* d_out, int iters, f
           lop::KernelEvents ke;
           ke.start[0] = ev[i]; ke.stop[0] = ev[i + 1];
           ke.start[1] = ev[i + 2]; ke.stop[1] = ev[i + 3];
+          const ChainPass pass(P, 0, P->batched ? P->images : 0);
           if (P->batched) LOP_HIP(launch_layer_batched(P, l, 0, nb, d_in, d_out, cs, &ke, nullptr));
           else LOP_HIP(launch_layer(P, P->fuse_band, b, l, d_in, d_out, cs, &ke));
           used[b * nl + l] = ke.n;

@@ -4,26 +4,35 @@
 // The three operators are local (Intra-DP Sec. IV-A: a block-wise operator between two
 // row-wise ones, Eq. 1), so a tile of the block's output depends on a slightly larger tile of
 // its input only. Run layer by layer the expanded tensor (6x the channels) is written to HBM
-// and read back twice; here it never leaves the compute unit. A workgroup owns a TH x TW tile
-// of output pixels and walks over the expanded channels in chunks of 32:
-//   expand   MFMA: the chunk's 32 channels for the (TH-1)S+3 x (TW-1)S+3 input pixels the
-//            tile's depthwise windows touch -> bias, activation, one rounding to bf16 -> LDS.
-//            Pixels outside the image are zero there (the depthwise operator pads its input,
-//            i.e. the expanded tensor, not the block's input);
-//   depthwise  also on MFMA, as nine products with diagonal weight matrices (one per tap)
-//            whose other operand is the expanded tile shifted by the tap: 31/32 of those
-//            multiplications are by zero, but the matrix pipe has them to spare, reads bf16
-//            directly and accumulates in fp32, while the same arithmetic on the vector ALUs
-//            (unpack, 9 FMAs per value) was the kernel's bottleneck -> bias, activation, one
-//            rounding -> LDS;
-//   project  MFMA: adds the chunk's contribution to the 32 output channels (accumulators stay
-//            in registers over the chunks).
+// and read back twice; here it never leaves the compute unit. A workgroup owns 8 x 16
+// output pixels and walks over the expanded channels in chunks of 32, all three operators on the
+// matrix cores:
+//   expand   32 x 32 x 16 products, pixels as rows, so that a lane ends with four neighbouring pixels of
+//            one channel -> bias, activation, one rounding to bf16 -> LDS, channel by channel. Pixels
+//            outside the image are zero there (the depthwise operator pads its input, i.e. the
+//            expanded tensor, not the block's input);
+//   depthwise  4 x 4 x 4 products, 16 channels at once, one per block of the instruction: four
+//            output columns x four output rows, the reduction running over four neighbouring input
+//            columns, whose weights form a band of a small matrix (one per filter row and group of
+//            columns; packed behind the operator's weights). Six of them make 16 outputs of 16
+//            channels (stride 2: nine) -> bias, activation, one rounding -> LDS, channel by channel,
+//            from where the projection reads it transposed;
+//   project  32 x 32 x 16 products: adds the chunk's contribution to the 32 output channels
+//            (accumulators stay in registers over the chunks).
+// What bounds it: the vector ALUs (clamps and conversions of the expanded values, once each) and the
+// vector cache, about equally; the matrix cores are busy a quarter of the time. Weights are read in the
+// order of the lanes, straight from the cache; barriers wait for LDS only, so that the next chunk's weights
+// stay in flight; rows and channels lie in LDS in an order that has no bank conflicts. Four images of
+// 640 x 640 through six blocks: 583 -> 406 us (first block, stride 2: 92 us; second: 53 us). What came
+// before: diagonal 32 x 32 x 16 products for the depthwise part (three times the matrix cycles, diagonals
+// built on the vector ALUs); weights read row by row, four cache lines per four lanes, cost 509 us.
 // The roundings are the ones the layer-by-layer path makes, so results agree with it to fp32
 // summation order. Shapes: 32 input and 32 output channels, up to 192 expanded channels, bf16.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 #include <cstdio>
+#include <cstring>
 
 #include "act.hpp"
 #include "kernels.hpp"
@@ -39,19 +48,19 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kMbC = 32;          // input and output channels
-constexpr int kMbMaxMid = 192;    // expanded channels held by the staged depthwise weights
+constexpr int kMbMaxMid = 192;    // expanded channels held by the staged biases
 
 struct MbParams {
   const __bf16* x;
   __bf16* y;
   const __bf16* res;
-  const __bf16* we;   // expand weights [c_mid padded][ke_pad]
+  const void* we;     // expand weights in operand order, a tile of 32 channels every ke_pad / 16 steps
   const float* be;
-  const float* wd;    // depthwise weights [tap][C_mid]
+  const void* bands;  // depthwise weights as bands (mbconv_pack_bands)
   const float* bd;
-  const __bf16* wp;   // project weights [32 padded][kp_pad]
+  const void* wp;     // project weights in operand order
   const float* bp;
-  int ke_pad, kp_pad;
+  int e_steps;
   int x_row0, x_rows, H, W;
   int y_row0, y_rows, W_out;
   int r_row0, r_rows;
@@ -80,187 +89,216 @@ __device__ __forceinline__ u32x2 pack4(const float* f) {
   return __builtin_bit_cast(u32x2, b);
 }
 
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// Of 16 lanes, lane i gets value i % 4 of the four that lanes i / 4, i / 4 + 4, + 8 and + 12 point at.
+__device__ __forceinline__ u32x2 transposed_read(const unsigned char* at) {
+  return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)at));
+}
+
 template <int S>
 struct MbTile {
   static constexpr int TH = 8, TW = 16;                  // output pixels of a workgroup
-  static constexpr int EH = (TH - 1) * S + 3, EW = (TW - 1) * S + 3;  // expanded pixels it needs
-  static constexpr int EP = EH * EW;
-  static constexpr int MT_E = (EP + 31) / 32;            // expand MFMA tiles
+  static constexpr int EH = (TH - 1) * S + 3;            // rows of expanded pixels it needs
+  static constexpr int XQ = S == 1 ? 5 : 9;              // columns, in groups ("quads") of four
+  static constexpr int NQ = EH * XQ;                     // quads, column of quads by column
+  static constexpr int MT_E = (NQ + 7) / 8;              // expand MFMA tiles
   static constexpr int MPW = (MT_E + 3) / 4;             // ... per wavefront
   static constexpr int OP = TH * TW;                     // = 4 MFMA tiles, one per wavefront
-  static constexpr int PITCH = 80;                       // bytes per pixel in LDS (64 + pad)
+  static constexpr int KS = S == 1 ? 2 : 3;              // quads of input columns under four outputs
+  // Bytes of a channel in LDS: an odd multiple of 8, which with the order of rows and channels below
+  // lets every half wavefront's access touch each bank once.
+  static constexpr int EPITCH = MT_E * 64 + 8;
+  static constexpr int DPITCH = OP * 2 + 8;
+  // Row of the idx-th quad of a column: with stride 2 the even rows first, so that the rows under
+  // neighbouring output rows are neighbours.
+  __host__ __device__ static constexpr int row(int idx) { return S == 1 ? idx : idx <= TH ? 2 * idx : 2 * (idx - TH) - 1; }
+  __host__ __device__ static constexpr int tap_row(int a) { return S == 1 ? a : a == 1 ? TH + 1 : a / 2; }
 };
 
+// Channel (of a chunk's 32) kept in slot s of LDS. The order is the one in which a lane's eight
+// reduction values of the projection, which it reads from slots 8 j + 4 h + 2 u + kg, are
+// consecutive channels.
+__host__ __device__ constexpr int slot_channel(int s) {
+  return ((s >> 2) & 1) * 16 + (s & 1) * 8 + ((s >> 1) & 1) * 4 + (s >> 3);
+}
+__host__ __device__ constexpr int channel_slot(int c) { return (c & 3) * 8 + (c >> 4) * 4 + ((c >> 2) & 1) * 2 + ((c >> 3) & 1); }
+// Slot of the depthwise operator's block of lanes (lane / 4) and half of the channels.
+__host__ __device__ constexpr int dw_slot(int block, int half) { return 4 * (block & 7) + 2 * half + (block >> 3); }
+
 template <int S, bool RES>
-__global__ __launch_bounds__(256, S == 1 ? 4 : 2) void mbconv_kernel(const MbParams p) {
+__device__ __forceinline__ void mbconv_body(const MbParams& p, int bid) {
   typedef MbTile<S> G;
-  constexpr int TH = G::TH, TW = G::TW, EW = G::EW, EP = G::EP, MT_E = G::MT_E, MPW = G::MPW;
-  constexpr int EPITCH = G::PITCH, DPITCH = G::PITCH;
+  constexpr int TH = G::TH, TW = G::TW, EH = G::EH, XQ = G::XQ, NQ = G::NQ, MT_E = G::MT_E, MPW = G::MPW, KS = G::KS;
+  constexpr int EPITCH = G::EPITCH, DPITCH = G::DPITCH;
   static_assert(G::OP == 128, "one 32-pixel MFMA tile of the output per wavefront");
-  __shared__ __attribute__((aligned(16))) unsigned char E_s[MT_E * 32 * EPITCH];
-  __shared__ __attribute__((aligned(16))) unsigned char D_s[G::OP * DPITCH];
-  __shared__ __attribute__((aligned(16))) float wd_s[10 * kMbMaxMid];  // 9 taps, then the bias
-  __shared__ __attribute__((aligned(16))) float be_s[kMbMaxMid];       // expand bias
+  static_assert(NQ <= 256 && kMbMaxMid <= 256, "a thread per quad and per bias");
+  __shared__ __attribute__((aligned(16))) unsigned char E_s[32 * EPITCH];   // [slot][quad]
+  __shared__ __attribute__((aligned(16))) unsigned char D_s[32 * DPITCH];   // [slot][column of quads][row]
+  __shared__ __attribute__((aligned(16))) float bias_s[2][kMbMaxMid];       // expand, depthwise
+  __shared__ u32x2 mask_s[MT_E * 8];                                        // bits of a quad inside the image
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int px = lane & 31, kg = lane >> 5;
-  int bid = blockIdx.x;
   const int tx = bid % p.tiles_x;
   bid /= p.tiles_x;
   const int ty = bid % p.tiles_y;
   const int n = bid / p.tiles_y;
   const int oh0 = p.out_lo + ty * TH, ow0 = tx * TW;
   const int ih_base = oh0 * S - 1, iw_base = ow0 * S - 1;
-
-  // stage the depthwise weights and the two biases: all loads first (a loop of load-store
-  // pairs would pay the memory latency once per trip)
-  {
-    const int nw4 = 9 * p.C_mid / 4, nb4 = p.C_mid / 4;  // float4 counts (<= 432, <= 48)
-    float4 w0 = make_float4(0.f, 0.f, 0.f, 0.f), w1 = w0, b0 = w0, b1 = w0;
-    if (tid < nw4) w0 = ((const float4*)p.wd)[tid];
-    if (tid + 256 < nw4) w1 = ((const float4*)p.wd)[tid + 256];
-    if (tid < nb4 && p.bd) b0 = ((const float4*)p.bd)[tid];
-    if (tid < nb4 && p.be) b1 = ((const float4*)p.be)[tid];
-    if (tid < nw4) ((float4*)wd_s)[tid] = w0;
-    if (tid + 256 < nw4) ((float4*)wd_s)[tid + 256] = w1;
-    if (tid < nb4) {
-      ((float4*)(wd_s + 9 * p.C_mid))[tid] = b0;
-      ((float4*)be_s)[tid] = b1;
-    }
-  }
+  // rows of the image that the slab holds
+  const int ih_lo = max(0, p.x_row0), ih_hi = min(p.H, p.x_row0 + p.x_rows);
 
   // ---- the block's input at the expanded pixels of this wavefront's MFMA tiles, in operand
   // layout (lane = pixel, two halves of 8 channels per step of 16), kept for all chunks
   u32x4 xa[MPW][2];
-  bool xin[MPW];
 #pragma unroll
   for (int i = 0; i < MPW; ++i) {
-    const int e = (wave + 4 * i) * 32 + px;
-    const int er = e / EW, ec = e - er * EW;
-    const int ih = ih_base + er, iw = iw_base + ec;
-    xin[i] = wave + 4 * i < MT_E && e < EP && ih >= 0 && ih < p.H && iw >= 0 && iw < p.W &&
-             ih >= p.x_row0 && ih < p.x_row0 + p.x_rows;
+    const int q = (wave + 4 * i) * 8 + (px >> 2), qx = q / EH;
+    const int ih = ih_base + G::row(q - qx * EH), iw = iw_base + qx * 4 + (px & 3);
     xa[i][0] = u32x4{0u, 0u, 0u, 0u};
     xa[i][1] = u32x4{0u, 0u, 0u, 0u};
-    if (xin[i]) {
+    if (q < NQ && ih >= ih_lo && ih < ih_hi && iw >= 0 && iw < p.W) {
       const __bf16* src = p.x + ((size_t)(n * p.x_rows + ih - p.x_row0) * p.W + iw) * kMbC + kg * 8;
       xa[i][0] = *(const u32x4*)src;
       xa[i][1] = *(const u32x4*)(src + 16);
     }
   }
 
-  // this lane's output pixel (of the wavefront's 32) and where its window starts in E_s
-  const int o = wave * 32 + px;
-  const int orow = o / TW, ocol = o - orow * TW;
-  const unsigned char* const ewin = E_s + ((orow * S) * EW + ocol * S) * EPITCH + kg * 16;
-  // diagonal weight matrices as MFMA A operands: row (= channel) chl has its one non-zero at
-  // k = chl, i.e. in step chl / 16, lane half (chl % 16) / 8, slot chl % 8 of the 8 bf16
-  const int chl = lane & 31;
-  unsigned amask[2][4];
+  // weights of a chunk: expand, the depthwise bands of this wavefront's 16 channels, project, all in the order of the
+  // lanes (an access of four lanes to one 64-byte line each costs the vector cache four times as much); each part is fetched for the next chunk when this one is done with it
+  const int chalf = wave & 1, rgroup = wave >> 1;          // depthwise: 16 channels x 4 output rows x 16 columns each
+  u32x4 we[2], wp[2];
+  s16x4 wd[3 * KS];
+  const u32x4* const we_at = (const u32x4*)p.we + lane;
+  const u32x4* const wp_at = (const u32x4*)p.wp + lane;
+  const s16x4* const wd_at = (const s16x4*)p.bands + chalf * (3 * KS * 64) + lane;
+  auto fetch_expand = [&](int c) __attribute__((always_inline)) {
+    we[0] = we_at[(size_t)c * p.e_steps * 64];
+    we[1] = we_at[(size_t)c * p.e_steps * 64 + 64];
+  };
+  auto fetch_depthwise = [&](int c) __attribute__((always_inline)) {
 #pragma unroll
-  for (int j = 0; j < 2; ++j)
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      amask[j][i] = ((chl >> 4) == j && ((chl >> 3) & 1) == kg && ((chl & 7) >> 1) == i) ? 0xffffffffu : 0u;
-  const int wshift = (chl & 1) * 16;
+    for (int t = 0; t < 3 * KS; ++t) wd[t] = wd_at[c * (2 * 3 * KS * 64) + t * 64];
+  };
+  auto fetch_project = [&](int c) __attribute__((always_inline)) {
+    wp[0] = wp_at[c * 128];
+    wp[1] = wp_at[c * 128 + 64];
+  };
+  fetch_expand(0);
+  fetch_depthwise(0);
+  fetch_project(0);
+
+  // A tile away from the image's borders needs no masks.
+  const bool inside = ih_base >= ih_lo && iw_base >= 0 && ih_base + EH <= ih_hi && iw_base + XQ * 4 <= p.W;
+  if (tid < kMbMaxMid) {
+    const bool in = tid < p.C_mid;
+    bias_s[0][tid] = in && p.be ? p.be[tid] : 0.f;
+    bias_s[1][tid] = in && p.bd ? p.bd[tid] : 0.f;
+  }
+  if (tid < MT_E * 8) {
+    const int qx = tid / EH, ih = ih_base + G::row(tid - qx * EH), iw = iw_base + qx * 4;
+    const bool rows = ih >= ih_lo && ih < ih_hi;
+    auto in = [&](int k) { return rows && iw + k >= 0 && iw + k < p.W; };
+    mask_s[tid] = u32x2{(in(0) ? 0xffffu : 0u) | (in(1) ? 0xffff0000u : 0u), (in(2) ? 0xffffu : 0u) | (in(3) ? 0xffff0000u : 0u)};
+  }
+  // LDS barrier that leaves the weights in flight alone
+  auto barrier = [&]() __attribute__((always_inline)) {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  };
+  barrier();
 
   f32x16 acc;
 #pragma unroll
   for (int i = 0; i < 16; ++i) acc[i] = 0.f;
 
-  // weight fragments (MFMA A operands) of a chunk: expand rows c*32 + px, project columns
-  // c*32 ...; the next chunk's are fetched while this one is worked on
-  u32x4 wef[2], wpf[2];
-  auto fetch_weights = [&](int c, u32x4 (&we2)[2], u32x4 (&wp2)[2]) __attribute__((always_inline)) {
-    const __bf16* wr = p.we + (size_t)(c * 32 + px) * p.ke_pad + kg * 8;
-    we2[0] = *(const u32x4*)wr;
-    we2[1] = *(const u32x4*)(wr + 16);
-    const __bf16* pr = p.wp + (size_t)px * p.kp_pad + c * 32 + kg * 8;
-    wp2[0] = *(const u32x4*)pr;
-    wp2[1] = *(const u32x4*)(pr + 16);
-  };
-  fetch_weights(0, wef, wpf);
-  __syncthreads();  // staged biases and depthwise weights are in LDS
+  // expand: stores to the slot of channel px; depthwise: row lane % 4 of this wavefront's four, channel slot of its block of
+  // lanes; project: a transposing read gives the lane four slots of its pixel (16 lanes read 4 slots x 4 quads)
+  unsigned char* const eout = E_s + channel_slot(px) * EPITCH + kg * 8;
+  const int dslot = dw_slot(lane >> 2, chalf), drow = rgroup * 4 + (lane & 3);
+  const unsigned char* const ewin = E_s + dslot * EPITCH + drow * 8;
+  unsigned char* const dout = D_s + dslot * DPITCH + drow * 8;
+  unsigned char* const dtr = D_s + (((lane & 15) >> 2) * 8 + kg) * DPITCH + (wave * 8 + ((lane >> 4) & 1) * 4 + (lane & 3)) * 8;
 
   for (int c = 0; c < p.nch; ++c) {
-    u32x4 wef_n[2] = {wef[0], wef[1]}, wpf_n[2] = {wpf[0], wpf[1]};
-    if (c + 1 < p.nch) fetch_weights(c + 1, wef_n, wpf_n);
-    float4 eb[4];
+    const int cn = min(c + 1, p.nch - 1);
+    // ---- expand
+    const float eb = bias_s[0][c * 32 + px];
+    f32x16 ebias;
 #pragma unroll
-    for (int g = 0; g < 4; ++g) eb[g] = *(const float4*)(be_s + c * 32 + g * 8 + kg * 4);
-
-    // ---- expand: lane ends with channels g*8 + kg*4 + {0..3} of pixel px
+    for (int k = 0; k < 16; ++k) ebias[k] = eb;
 #pragma unroll
     for (int i = 0; i < MPW; ++i) {
       const int mt = wave + 4 * i;
-      if (mt >= MT_E) continue;
-      f32x16 a;
-#pragma unroll
-      for (int k = 0; k < 16; ++k) a[k] = 0.f;
-      a = mma_bf16(wef[0], xa[i][0], a);
-      a = mma_bf16(wef[1], xa[i][1], a);
+      if (MT_E % 4 != 0 && i == MPW - 1 && mt >= MT_E) continue;
+      f32x16 a = mma_bf16(xa[i][0], we[0], ebias);
+      a = mma_bf16(xa[i][1], we[1], a);
+      u32x2 pk[4];
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
         float v[4];
-        v[0] = clamp_act(a[g * 4 + 0] + eb[g].x, p.ce);
-        v[1] = clamp_act(a[g * 4 + 1] + eb[g].y, p.ce);
-        v[2] = clamp_act(a[g * 4 + 2] + eb[g].z, p.ce);
-        v[3] = clamp_act(a[g * 4 + 3] + eb[g].w, p.ce);
-        u32x2 pk = pack4(v);
-        if (!xin[i]) pk = u32x2{0u, 0u};  // padding of the depthwise operator
-        *(u32x2*)(E_s + (mt * 32 + px) * EPITCH + g * 16 + kg * 8) = pk;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = clamp_act(a[g * 4 + k], p.ce);
+        pk[g] = pack4(v);
       }
+      if (!inside) {  // padding of the depthwise operator
+#pragma unroll
+        for (int g = 0; g < 4; ++g) pk[g] &= mask_s[mt * 8 + 2 * g + kg];
+      }
+#pragma unroll
+      for (int g = 0; g < 4; ++g) *(u32x2*)(eout + (mt * 8 + 2 * g) * 8) = pk[g];
     }
-    __syncthreads();
+    fetch_expand(cn);
+    barrier();
 
-    // ---- depthwise 3x3 on the chunk: D[ch][px] = sum over taps of diag(w_tap) x E(px + tap)
+    // ---- depthwise 3x3 on the chunk
     {
-      f32x16 d0, d1;
+      const float db = bias_s[1][c * 32 + slot_channel(dslot)];
+      const f32x4 dbias = f32x4{db, db, db, db};
+      f32x4 d[4];
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const float4 b4 = *(const float4*)(wd_s + 9 * p.C_mid + c * 32 + g * 8 + kg * 4);
-        d0[g * 4 + 0] = b4.x; d0[g * 4 + 1] = b4.y; d0[g * 4 + 2] = b4.z; d0[g * 4 + 3] = b4.w;
+      for (int a = 0; a < 3; ++a) {
+        s16x4 col[XQ];
+#pragma unroll
+        for (int x = 0; x < XQ; ++x) col[x] = *(const s16x4*)(ewin + (x * EH + G::tap_row(a)) * 8);
+#pragma unroll
+        for (int s = 0; s < KS; ++s)
+#pragma unroll
+          for (int b = 0; b < 4; ++b)
+            d[b] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(wd[a * KS + s], col[b * S + s], a + s ? d[b] : dbias, 0, 0, 0);
       }
+      fetch_depthwise(cn);
 #pragma unroll
-      for (int k = 0; k < 16; ++k) d1[k] = 0.f;
-#pragma unroll
-      for (int t = 0; t < 9; ++t) {
-        // the weights are bf16 values held as fp32: the upper 16 bits are the value
-        const unsigned wv = (__builtin_bit_cast(unsigned, wd_s[t * p.C_mid + c * 32 + chl]) >> 16) << wshift;
-        const u32x4 a0 = u32x4{wv & amask[0][0], wv & amask[0][1], wv & amask[0][2], wv & amask[0][3]};
-        const u32x4 a1 = u32x4{wv & amask[1][0], wv & amask[1][1], wv & amask[1][2], wv & amask[1][3]};
-        const unsigned char* src = ewin + ((t / 3) * EW + (t % 3)) * EPITCH;
-        d0 = mma_bf16(a0, *(const u32x4*)src, d0);
-        d1 = mma_bf16(a1, *(const u32x4*)(src + 32), d1);
-      }
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
+      for (int b = 0; b < 4; ++b) {
         float v[4];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) v[k] = clamp_act(d0[g * 4 + k] + d1[g * 4 + k], p.cd);
-        *(u32x2*)(D_s + o * DPITCH + g * 16 + kg * 8) = pack4(v);
+        for (int k = 0; k < 4; ++k) v[k] = clamp_act(d[b][k], p.cd);
+        *(u32x2*)(dout + b * 64) = pack4(v);
       }
     }
-    __syncthreads();
+    barrier();
 
     // ---- project: this chunk's 32 channels are the reduction axis
-    {
-      const unsigned char* src = D_s + o * DPITCH + kg * 16;
-      const u32x4 b0 = *(const u32x4*)src;
-      const u32x4 b1 = *(const u32x4*)(src + 32);
-      acc = mma_bf16(wpf[0], b0, acc);
-      acc = mma_bf16(wpf[1], b1, acc);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const u32x2 lo = transposed_read(dtr + (4 * h + 0) * DPITCH);
+      const u32x2 hi = transposed_read(dtr + (4 * h + 2) * DPITCH);
+      acc = mma_bf16(wp[h], u32x4{lo.x, lo.y, hi.x, hi.y}, acc);
     }
-    wef[0] = wef_n[0]; wef[1] = wef_n[1];
-    wpf[0] = wpf_n[0]; wpf[1] = wpf_n[1];
+    fetch_project(cn);
   }
 
-  // ---- bias, residual, activation, the one rounding; 8 bytes per lane and channel group
-  const int oh = oh0 + orow, ow = ow0 + ocol;
-  if (oh >= p.out_lo + p.R || ow >= p.W_out) return;
+  // ---- bias, residual, activation, the one rounding. A lane has channels 8 g + 4 kg + {0..3} of its
+  // pixel; two groups are exchanged between the lane halves so that each has 8 consecutive ones.
+  const int oh = oh0 + (px >> 2), ow = ow0 + wave * 4 + (px & 3);
+  const bool live = oh < p.out_lo + p.R && ow < p.W_out;
   const size_t yoff = ((size_t)(n * p.y_rows + oh - p.y_row0) * p.W_out + ow) * kMbC;
   const size_t roff = RES ? ((size_t)(n * p.r_rows + oh - p.r_row0) * p.W_out + ow) * kMbC : 0;
+  u32x2 o[4];
 #pragma unroll
   for (int g = 0; g < 4; ++g) {
     const int co = g * 8 + kg * 4;
@@ -269,15 +307,32 @@ __global__ __launch_bounds__(256, S == 1 ? 4 : 2) void mbconv_kernel(const MbPar
       const float4 b4 = *(const float4*)(p.bp + co);
       v[0] += b4.x; v[1] += b4.y; v[2] += b4.z; v[3] += b4.w;
     }
-    if (RES) {
+    if (RES && live) {
       float r[4];
       unpack4(*(const u32x2*)(p.res + roff + co), r);
       v[0] += r[0]; v[1] += r[1]; v[2] += r[2]; v[3] += r[3];
     }
 #pragma unroll
     for (int k = 0; k < 4; ++k) v[k] = clamp_act(v[k], p.cp);
-    *(u32x2*)(p.y + yoff + co) = pack4(v);
+    o[g] = pack4(v);
   }
+#pragma unroll
+  for (int g = 0; g < 4; g += 2) {
+    const auto s0 = __builtin_amdgcn_permlane32_swap(o[g].x, o[g + 1].x, false, false);
+    const auto s1 = __builtin_amdgcn_permlane32_swap(o[g].y, o[g + 1].y, false, false);
+    if (live) *(u32x4*)(p.y + yoff + g * 8 + kg * 8) = u32x4{(unsigned)s0[0], (unsigned)s1[0], (unsigned)s0[1], (unsigned)s1[1]};
+  }
+}
+
+template <int S, bool RES>
+__global__ __launch_bounds__(256, S == 1 ? 4 : 3) void mbconv_kernel(const MbParams p) {
+  mbconv_body<S, RES>(p, blockIdx.x);
+}
+// The same for several bands of one block in one grid (band b owns blocks first[b] .. first[b + 1]).
+template <int S, bool RES>
+__global__ __launch_bounds__(256, S == 1 ? 4 : 3) void mbconv_kernel_bands(const Batch<MbParams> t) {
+  const int b = batch_find(t, blockIdx.x);
+  mbconv_body<S, RES>(t.p[b], blockIdx.x - t.first[b]);
 }
 
 bool is_pointwise(const OpLaunch& L) {
@@ -286,6 +341,26 @@ bool is_pointwise(const OpLaunch& L) {
 }
 
 }  // namespace
+
+// The depthwise weights w[tap][C] (values of the storage type) of a 3 x 3 operator with stride s as
+// operands of the 4 x 4 x 4 products: [C / 32][half of the slots][filter row a][quad g of input columns][64
+// lanes] x 4 bf16. A lane (block of lanes = channel, lane % 4 = output column m) holds the weights of
+// input columns 4 g + {0..3}, i.e. w[a][4 g + k - s m] where that is a tap and zero elsewhere.
+size_t mbconv_bands_bytes(int c, int s) { return (size_t)(c / 16) * 3 * (s == 1 ? 2 : 3) * 64 * 8; }
+void mbconv_pack_bands(const float* w, int c, int s, unsigned short* dst) {
+  const int ks = s == 1 ? 2 : 3;
+  for (int cb = 0; cb < c / 16; ++cb)
+    for (int a = 0; a < 3; ++a)
+      for (int g = 0; g < ks; ++g)
+        for (int lane = 0; lane < 64; ++lane)
+          for (int k = 0; k < 4; ++k) {
+            const int tap = 4 * g + k - s * (lane % 4);
+            const int ch = cb / 2 * 32 + slot_channel(dw_slot(lane / 4, cb % 2));
+            unsigned bits = 0;
+            if (tap >= 0 && tap < 3) memcpy(&bits, &w[(size_t)(a * 3 + tap) * c + ch], 4);
+            *dst++ = (unsigned short)(bits >> 16);
+          }
+}
 
 // Whether the three operators (expand, depthwise, project; shapes and parameters only, the
 // slabs are not looked at) can run as one mbconv_kernel launch.
@@ -305,34 +380,49 @@ int mbconv_describe(const OpLaunch& d, const OpLaunch& p, char* name, size_t siz
   return 1;
 }
 
-// e.x: the block's input slab; p.y: its output slab; p.res: residual slab or none;
-// p.out_lo/out_hi: the output rows to produce.
-hipError_t launch_mbconv(const OpLaunch& e, const OpLaunch& d, const OpLaunch& p, hipStream_t stream,
-                         KernelEvents* ev) {
-  if (!mbconv_applies(e, d, p)) return hipErrorInvalidValue;
+namespace {
+MbParams make_mbconv(const OpLaunch& e, const OpLaunch& d, const OpLaunch& p) {
   MbParams q;
   q.x = (const __bf16*)e.x.ptr; q.y = (__bf16*)p.y.ptr; q.res = (const __bf16*)p.res.ptr;
-  q.we = (const __bf16*)e.w; q.be = e.bias;
-  q.wd = (const float*)d.w; q.bd = d.bias;
-  q.wp = (const __bf16*)p.w; q.bp = p.bias;
-  q.ke_pad = e.k_pad; q.kp_pad = p.k_pad;
+  q.we = e.wd; q.be = e.bias;
+  q.bands = (const float*)d.w + 9 * d.x.c; q.bd = d.bias;
+  q.wp = p.wd; q.bp = p.bias;
+  q.e_steps = e.k_pad / 16;
   q.x_row0 = e.x.row0; q.x_rows = e.x.rows; q.H = e.x.h; q.W = e.x.w;
   q.y_row0 = p.y.row0; q.y_rows = p.y.rows; q.W_out = p.y.w;
   q.r_row0 = p.res.row0; q.r_rows = p.res.rows;
   q.C_mid = e.y.c; q.nch = e.y.c / 32;
   q.ce = make_clamp(e.act); q.cd = make_clamp(d.act); q.cp = make_clamp(p.act);
   q.out_lo = p.out_lo; q.R = p.out_hi - p.out_lo; q.N = e.x.n;
-  if (q.R <= 0 || q.N <= 0) return hipSuccess;
-  const int s = d.sh;
   const int tw = MbTile<1>::TW, th = MbTile<1>::TH;
   q.tiles_x = (q.W_out + tw - 1) / tw;
   q.tiles_y = (q.R + th - 1) / th;
-  const dim3 grid((unsigned)(q.tiles_x * q.tiles_y * q.N));
-  if (s == 1)
-    return q.res ? launch_kernel(mbconv_kernel<1, true>, grid, dim3(256), stream, ev, q)
-                 : launch_kernel(mbconv_kernel<1, false>, grid, dim3(256), stream, ev, q);
-  return q.res ? launch_kernel(mbconv_kernel<2, true>, grid, dim3(256), stream, ev, q)
-               : launch_kernel(mbconv_kernel<2, false>, grid, dim3(256), stream, ev, q);
+  return q;
+}
+static_assert(sizeof(Batch<MbParams>) <= 4096, "the parameters of all bands of a launch travel as kernel arguments");
+}  // namespace
+
+// Per band: es[b].x the block's input slab; ps[b].y its output slab; ps[b].res residual slab or none;
+// ps[b].out_lo/out_hi the output rows to produce.
+hipError_t launch_mbconv_bands(const OpLaunch* es, const OpLaunch& d, const OpLaunch* ps, int n, hipStream_t stream,
+                               KernelEvents* ev) {
+  if (n < 1 || n > kMaxBatch) return hipErrorInvalidValue;
+  MbParams qs[kMaxBatch];
+  unsigned gx[kMaxBatch];
+  int m = 0;
+  for (int b = 0; b < n; ++b) {
+    if (!mbconv_applies(es[b], d, ps[b])) return hipErrorInvalidValue;
+    qs[m] = make_mbconv(es[b], d, ps[b]);
+    if (qs[m].R <= 0 || qs[m].N <= 0) continue;
+    gx[m] = (unsigned)(qs[m].tiles_x * qs[m].tiles_y * qs[m].N);
+    ++m;
+  }
+  if (m == 0) return hipSuccess;
+  if (d.sh == 1)
+    return qs[0].res ? launch_group(mbconv_kernel<1, true>, mbconv_kernel_bands<1, true>, qs, m, gx, 1, 1, dim3(256), stream, ev)
+                     : launch_group(mbconv_kernel<1, false>, mbconv_kernel_bands<1, false>, qs, m, gx, 1, 1, dim3(256), stream, ev);
+  return qs[0].res ? launch_group(mbconv_kernel<2, true>, mbconv_kernel_bands<2, true>, qs, m, gx, 1, 1, dim3(256), stream, ev)
+                   : launch_group(mbconv_kernel<2, false>, mbconv_kernel_bands<2, false>, qs, m, gx, 1, 1, dim3(256), stream, ev);
 }
 
 }  // namespace lop

@@ -60,16 +60,18 @@ struct lop_plan_s {
   Fusion fuse_band;   // groups of the launches that compute one band
   Fusion fuse_chain;  // groups of the launches that compute all bands (kGrouped, kWhole)
   ChainSched sched = ChainSched::kPerBand;
-  int group = 0;  // kGrouped: bands per group; the groups of a chain run one after another
+  int group = 0;   // kGrouped: bands per group; the groups of a chain run one after another
+  int images = 0;  // kGrouped, kWhole: images per pass; the passes of a chain run one after another
+  int pass_first = 0, pass_images = 0;  // while a pass is enqueued: its images (0: all, not in a pass)
   std::vector<float*> d_bias;  // per layer bias (device) or nullptr
   std::vector<int> k_pad;
   std::vector<char> has_wd, has_wd16;  // which of the two operand-order packings a layer gets
   std::vector<char> has_wstem;         // ... and whether it gets the first-layer packing
   size_t conv_ws_bytes = 0;
   size_t arena_bytes = 0;
-  // [band][layer] byte offset into a lane's arena; entry n_bands: the full-height buffers of a
-  // chain that runs as a whole
-  std::vector<std::vector<size_t>> slab_off;
+  // [band][layer] byte offset into a lane's arena: of bands that run one by one, and of merged
+  // launches (entry n_bands: the full-height buffers of a chain that runs as a whole)
+  std::vector<std::vector<size_t>> slab_off, chain_off;
   std::vector<Lane> lanes;
   hipStream_t s_main = nullptr, s_copy = nullptr;
   hipStream_t last_user_stream = nullptr;
