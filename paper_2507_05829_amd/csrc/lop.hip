@@ -729,12 +729,13 @@ void* device_view_of_host(lop_plan_t* P, void* h_out);
 // whole grid hold up the HBM writes of the kernels beside them: the 720p chain in reuse mode, 1.8 MB
 // out, 90 us with the last layer's own stores, 72 with the copy kernel behind it, 60 without a copy).
 constexpr size_t kDirectHostStoreMax = 256 * 1024;
-// Workgroups of a band copy that shares a stream with kernels: its stores are paced by the
-// link, and many of them in flight hold up the HBM writes of the kernels running beside the
-// copy (4 workgroups move about 30 GB/s; with 64 the copy was 1.7x faster and the other
-// streams lost more than that; on a lane of its own 8 and 16 workgroups cost the chains beside
-// it 8 % and 13 %).
-constexpr int kCopyWorkgroups = 4;
+// Workgroups of a band copy that shares the chip with kernels: its stores are paced by the link, and
+// many of them in flight hold up the kernels beside the copy, first of all those on the compute units
+// that the copy's workgroups share. Two workgroups of 512 move as much as four of 256 (about 30 GB/s),
+// from half the compute units: 13 MB results of the inverted-residual chain 631 -> 591 us a chain,
+// in reuse mode 505 -> 470; 1.8 MB ones the same. Eight and sixteen of 256 cost 698 and 785 us, one
+// of 512 684 (the copies themselves then take longest), the copy engines 676.
+constexpr int kCopyWorkgroups = 2;
 constexpr size_t kCopyLaneMaxBytes = (size_t)64 << 20;
 
 // Device view of h_out if the launches of one band (merged false), or those of the whole chain,

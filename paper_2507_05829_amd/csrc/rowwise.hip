@@ -378,19 +378,20 @@ namespace {
 // travel over PCIe while other streams compute. Non-temporal in both directions: nobody reads
 // either side again here, and rows on their way to the host that go through the caches push out
 // what the kernels beside the copy use (the 720p chain in reuse mode 77 -> 72 us).
-__global__ __launch_bounds__(256) void copy_rows_kernel(char* __restrict__ dst,
+constexpr int kCopyThreads = 512;
+__global__ __launch_bounds__(kCopyThreads) void copy_rows_kernel(char* __restrict__ dst,
                                                         const char* __restrict__ src,
                                                         size_t pitch, size_t len, int n) {
   typedef unsigned vec_t __attribute__((ext_vector_type(4)));
   const size_t vec = len / 16;
-  const size_t stride = (size_t)gridDim.x * 256;
+  const size_t stride = (size_t)gridDim.x * kCopyThreads;
   for (int i = 0; i < n; ++i) {
     const vec_t* s = (const vec_t*)(src + i * pitch);
     vec_t* d = (vec_t*)(dst + i * pitch);
-    for (size_t j = (size_t)blockIdx.x * 256 + threadIdx.x; j < vec; j += stride)
+    for (size_t j = (size_t)blockIdx.x * kCopyThreads + threadIdx.x; j < vec; j += stride)
       __builtin_nontemporal_store(__builtin_nontemporal_load(s + j), d + j);
     // tail bytes (len is a multiple of the element size, not necessarily of 16)
-    for (size_t j = vec * 16 + (size_t)blockIdx.x * 256 + threadIdx.x; j < len; j += stride)
+    for (size_t j = vec * 16 + (size_t)blockIdx.x * kCopyThreads + threadIdx.x; j < len; j += stride)
       dst[i * pitch + j] = src[i * pitch + j];
   }
 }
@@ -415,11 +416,9 @@ hipError_t launch_copy_rows(void* dst, const void* src, size_t pitch, size_t len
                             hipStream_t stream, int workgroups) {
   if (len == 0 || n <= 0) return hipSuccess;
   const size_t vec = (len + 15) / 16;
-  // Few workgroups on purpose: the stores are paced by PCIe, and many of them in flight
-  // hold up the HBM writes of the kernels running beside the copy (4 workgroups still move
-  // about 30 GB/s; with 64 the copy was 1.7x faster and the other streams lost more than that).
-  const unsigned grid = (unsigned)std::min<size_t>((vec + 255) / 256, (size_t)std::max(1, workgroups));
-  hipLaunchKernelGGL(copy_rows_kernel, dim3(grid), dim3(256), 0, stream, (char*)dst,
+  // Few workgroups on purpose (see the caller's number)
+  const unsigned grid = (unsigned)std::min<size_t>((vec + kCopyThreads - 1) / kCopyThreads, (size_t)std::max(1, workgroups));
+  hipLaunchKernelGGL(copy_rows_kernel, dim3(grid), dim3(kCopyThreads), 0, stream, (char*)dst,
                      (const char*)src, pitch, len, n);
   return hipGetLastError();
 }
