@@ -1876,7 +1876,7 @@ int group_of(const OpLaunch* Ls, int n, ConvParams* ps) {
 }  // namespace
 
 size_t conv_workspace_bytes_bands(const OpLaunch* Ls, int n) {
-  if (n < 1 || n > kMaxBatch || stem_applies(Ls[0]) || patch_applies(Ls, nullptr, n) || gemm_applies(Ls, n)) return 0;
+  if (n < 1 || n > kMaxBatch || stem_applies(Ls[0]) || narrow_applies(Ls, n) || patch_applies(Ls, nullptr, n) || gemm_applies(Ls, n)) return 0;
   ConvParams ps[kMaxBatch];
   const int m = group_of(Ls, n, ps);
   if (m == 0) return 0;
@@ -1897,6 +1897,7 @@ hipError_t launch_conv_igemm_bands(const OpLaunch* Ls, int n, hipStream_t stream
   ConvParams ps[kMaxBatch];
   const int m = group_of(Ls, n, ps);
   if (m == 0) return hipSuccess;
+  if (narrow_applies(Ls, n)) return launch_narrow(Ls, n, stream, ev);
   if (patch_applies(Ls, nullptr, n)) return launch_patch(Ls, nullptr, n, stream, ev);
   if (gemm_applies(Ls, n)) return launch_gemm(Ls, n, stream, ev);
   return Ls[0].dtype == LOP_BF16 ? launch_typed<__bf16>(ps, m, Ls[0].dtype, (float*)Ls[0].ws, stream, ev)
@@ -1915,6 +1916,7 @@ int conv_igemm_describe_bands(const OpLaunch* Ls, int n, char* name, size_t size
     if (name && size) name[0] = 0;
     return 0;
   }
+  if (narrow_applies(Ls, n)) return narrow_describe(Ls, n, name, size);
   if (patch_applies(Ls, nullptr, n)) return patch_describe(Ls, nullptr, n, name, size);
   if (gemm_applies(Ls, n)) return gemm_describe(Ls, n, name, size);
   const OpLaunch& L = Ls[0];
@@ -2001,6 +2003,7 @@ bool convpool_pays_bands(const OpLaunch* convs, int n) {
   ConvParams ps[kMaxBatch];
   const int m = n >= 1 && n <= kMaxBatch ? group_of(convs, n, ps) : 0;
   if (m == 0 || patch_applies(convs, nullptr, n)) return true;
+  if (narrow_applies(convs, n)) return false;
   const ConvParams p = group_params(ps, m);
   const Choice c = choose(p, convs[0].dtype);
   const DirectChoice d = choose_direct(p, convs[0].dtype, c.splits);

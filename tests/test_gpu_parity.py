@@ -1394,6 +1394,44 @@ def test_patch_form_of_the_lds_staged_kernel(oracle, cfg):
             np.testing.assert_array_equal(dev, want_int)
 
 
+NARROW_GRID = [
+    # c_in, c_out, stride, shape(n,h,w), residual, the form expected in one band
+    (128, 128, 1, (1, 9, 13), True, "<float, 5, 49152>"),        # slices of four and five steps
+    (144, 20, 1, (3, 1, 1), False, "<float, 9, 49152>"),         # one pixel an image, channels end inside a tile
+    (128, 36, 2, (1, 29, 9), False, "<float, 5, 49152>"),        # stride 2
+    (272, 132, 2, (2, 13, 11), False, "<float, 9, 81920>"),      # the large patch, slices of nine and ten steps
+    (512, 64, 1, (1, 19, 17), True, "<float, 9, 81920>"),        # two rounds of filter vectors, ragged tiles
+    (256, 160, 1, (1, 33, 15), True, "<float, 9, 49152>"),       # more workgroups than compute units
+]
+
+
+@pytest.mark.parametrize("cfg", NARROW_GRID)
+def test_patch_form_of_the_narrow_kernel(oracle, cfg):
+    """fp32 3 x 3 convolutions of few pixels, 16 x 16 tiles with the input staged once: every form,
+    checked by name, against the oracle in one band, with all bands in one launch and with shared rows;
+    small integers bit for bit."""
+    c_in, c_out, stride, shape, residual, form = cfg
+    chain = workloads.Chain("narrow", (shape[0], c_in, shape[1], shape[2]), "f32", 3)
+    first = chain.add(workloads.CONV, c_in, c_out, 1, stride, 0, act="none") if residual else workloads.NO_RESIDUAL
+    chain.add(workloads.CONV, c_in, c_out, 3, stride, 1, act="relu", input_from=workloads.CHAIN_INPUT, residual_from=first)
+    t = workloads.make_tensors(chain, zero_bias=False, seed=29)
+    plan = lop.Plan(chain, t, 1)
+    try:
+        assert plan.layer_kernel(0, plan.n_layers - 1)[0] == "conv_narrow_kernel" + form
+    finally:
+        plan.destroy()
+    want = oracle.run_chain(chain, t)
+    ti = workloads.small_int_tensors(chain, seed=3)
+    want_int = oracle.run_chain(chain, ti)
+    for bands, flags in ((1, 0), (3, 0), (3, lop.LOP_FLAG_REUSE)):
+        dev, host = run_gpu(chain, t, n_bands=bands, flags=flags)
+        np.testing.assert_array_equal(dev, host)
+        assert rel_err(dev, want) <= TOL["f32"], (bands, flags)
+        if np.abs(want_int).max() <= 2 ** 24:
+            dev, _ = run_gpu(chain, ti, n_bands=bands, flags=flags)
+            np.testing.assert_array_equal(dev, want_int)
+
+
 GEMM_GRID = [
     # dtype, m, k, n, residual, the tile expected
     ("bf16", 8 * 256 * 2 + 37, 136, 8 * 256 - 8, True, "<__bf16, 256, 256>"),   # ragged rows and channels, the last stage holds one chunk
