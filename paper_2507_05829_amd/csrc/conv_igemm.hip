@@ -1131,219 +1131,6 @@ __device__ __forceinline__ void mma16<float>(const u32x4& wa, const u32x4& px, f
   acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[3], b[3], acc, 0, 0, 0);
 }
 
-// Layers whose pixels are 64 bytes (32 bf16 channels in) under a 3 x 3 filter of horizontal
-// stride 1 at hundreds of thousands of pixels: the second layer of the 720p chain when all its
-// bands are one launch. The tiled kernels spend such a launch fetching: every workgroup pulls
-// the taps of its pixels (nine times the layer's input) and the filter through the L2s for a
-// reduction loop of five stages. Here a wavefront keeps the filter of 32 output channels in
-// registers as MFMA operands (18 vectors of 16 bytes) and walks over tiles of 16 consecutive
-// pixels of an input row; per tile and filter row it loads those 16 pixels once, straight into
-// the other operand, multiplies them with each of the row's three filter columns into sums kept
-// per column, and puts an output pixel together from the column sums of three neighbouring
-// lanes: 14 output pixels per tile. No LDS, no barrier; the four wavefronts of a workgroup
-// only share the filter's cache lines. Workgroups walk the tiles with a stride (XCD k over the k-th
-// eighth of them, so that an XCD's L2 holds neighbouring image rows), which spreads the cost
-// of loading the filter over several tiles. Measured on 856 000 pixels (32 -> 32 channels):
-// 36 us against 91 us on the LDS-staged kernel (44 us in a form that loaded the two pixels
-// behind a tile as well and shifted copies of the input between lanes). It is bound by the
-// instructions around the 36 MFMAs of a round, not by memory (the loop with no load, store or
-// MFMA in it takes two thirds of the time), so launches of one band (tens of thousands of
-// pixels, where it measured no faster) stay on the LDS-staged kernel.
-constexpr int kRegwTilePixels = 14;     // output pixels of a tile: 16 loaded pixels less the filter's two extra columns
-constexpr int kRegwTiles = 8;           // tiles per workgroup and round: two per wavefront
-constexpr int kRegwWorkgroups = 768;    // three per compute unit: all resident at once
-constexpr int kRegwMinPixels = 1 << 17;
-
-// rounds of workgroups it takes to cover a launch
-__host__ __device__ inline int regw_groups(const ConvParams& p) {
-  const int tiles = p.N * p.R * ((p.W_out + kRegwTilePixels - 1) / kRegwTilePixels);
-  return (tiles + kRegwTiles - 1) / kRegwTiles;
-}
-
-__device__ __forceinline__ void conv_regw_kernel_body(const ConvParams& p, const int bx, const int gx) {
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  // 16 x 16 x 32 MFMAs: lane (pxl, kq) holds channels 8 kq + {0..7} in of a pixel (or of an
-  // output channel's filter tap), so the four lanes of a pixel read its 64 bytes together and a
-  // wavefront's load covers 16 whole pixels
-  const int pxl = lane & 15, kq = lane >> 4;
-  const int co0 = blockIdx.y * 32;
-  // The input slab as a buffer: a load whose offset lies beyond the buffer returns zeros without
-  // touching memory, which is how a tap outside the image or the slab reads here (a select per
-  // loaded register would cost as many instructions as the MFMAs take cycles).
-  const __amdgpu_buffer_rsrc_t xbuf = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<void*>(p.x), 0, (int)((size_t)p.N * p.x_rows * p.W * 64), 0x00020000);
-  constexpr unsigned kOutside = 0x80000000u;
-  u32x4 wt[9][2];   // tap, half of the 32 output channels
-  float bias[2][4];
-#pragma unroll
-  for (int cb = 0; cb < 2; ++cb) {
-    const int co = co0 + cb * 16;
-    const unsigned char* wrow = (const unsigned char*)p.w + ((size_t)(co + pxl) * p.k_pad + kq * 8) * 2;
-#pragma unroll
-    for (int t = 0; t < 9; ++t) wt[t][cb] = *(const u32x4*)(wrow + t * 64);
-    const float4 b4 = p.bias ? *(const float4*)(p.bias + co + kq * 4) : make_float4(0.f, 0.f, 0.f, 0.f);
-    bias[cb][0] = b4.x; bias[cb][1] = b4.y; bias[cb][2] = b4.z; bias[cb][3] = b4.w;
-  }
-  const Clamp cl = make_clamp(p.act);
-  // A tile is 14 consecutive pixels of ONE output row (16 loaded ones), so that image, row and
-  // the three row offsets of a tile are the same for the whole wavefront (scalar arithmetic)
-  // and a lane only adds its column; the last tile of a row may hang over its end. Eight tiles
-  // per workgroup and round, two per wavefront.
-  const int tpr = (p.W_out + kRegwTilePixels - 1) / kRegwTilePixels;
-  const int groups = regw_groups(p);
-  int grp = bx, step = gx, end = groups;
-  if (gx % kXcds == 0) {   // (the hardware hands workgroups to the XCDs round-robin)
-    const int per = (groups + kXcds - 1) / kXcds, xcd = bx % kXcds;
-    grp = xcd * per + bx / kXcds;
-    step = gx / kXcds;
-    end = min(groups, (xcd + 1) * per);
-  }
-  // the tiles of this wavefront as (image, row of the launch, tile of the row), stepped from
-  // round to round without a division; a tile past the end has an image index past the last
-  int tcol[2], row[2], img[2];
-#pragma unroll
-  for (int tile = 0; tile < 2; ++tile) {
-    const int t = grp * kRegwTiles + wave * 2 + tile;
-    const int q = t / tpr;
-    tcol[tile] = t - q * tpr;
-    img[tile] = q / p.R;
-    row[tile] = q - img[tile] * p.R;
-  }
-  const int adv = step * kRegwTiles;
-  const int adv_q = adv / tpr, adv_col = adv - adv_q * tpr;
-  const int adv_img = adv_q / p.R, adv_row = adv_q - adv_img * p.R;
-  const int lane_in = (pxl - p.pw) * 64 + kq * 16;   // this lane's bytes in a row of the slab, from the tile's first column
-  for (; grp < end; grp += step) {
-    // Per tile and filter row ONE load: 16 consecutive pixels of the input row, the first of
-    // them the first tap of the tile's first output pixel. Every filter column keeps sums of its
-    // own over the three rows (the products of column b with the pixel a lane loaded), and
-    // output pixel j is column 0's sum of lane j + column 1's of lane j + 1 + column 2's of lane
-    // j + 2: two lane shifts per accumulator register instead of shifted copies of the input,
-    // and 14 finished pixels per 16 loaded. A column outside the image loads as zeros like a
-    // row outside. (The L1 hands a wavefront's 16-byte load over in about 33 cycles however its
-    // lines hit: with nine loads per tile the kernel ran at the speed of that path.)
-    u32x4 px[2][3];
-    int ow[2];
-#pragma unroll
-    for (int tile = 0; tile < 2; ++tile) {
-      ow[tile] = tcol[tile] * kRegwTilePixels + pxl;
-      const bool live = img[tile] < p.N;                       // (the same for the whole wavefront)
-      const int ih0 = (p.out_lo + row[tile]) * p.sh - p.ph;    // (... and so are the rows of the taps)
-      const int iw = ow[tile] - p.pw;                          // column of the pixel this lane loads
-      const unsigned off_a = (iw >= 0) & (iw < p.W) ? (unsigned)(tcol[tile] * (kRegwTilePixels * 64) + lane_in) : kOutside;
-#pragma unroll
-      for (int a = 0; a < 3; ++a) {
-        const int ih = ih0 + a * p.dh;
-        const bool row_ok = live & (ih >= p.x_row0) & (ih < p.x_row0 + p.x_rows);
-        const int row_base = row_ok ? ((img[tile] * p.x_rows - p.x_row0 + ih) * p.W) * 64 : 0;
-        px[tile][a] = __builtin_amdgcn_raw_buffer_load_b128(xbuf, row_ok ? off_a : kOutside, row_base, 0);
-      }
-    }
-    f32x4 acc[2][2];
-#pragma unroll
-    for (int tile = 0; tile < 2; ++tile) {
-      f32x4 col[3][2];
-#pragma unroll
-      for (int b = 0; b < 3; ++b)
-#pragma unroll
-        for (int cb = 0; cb < 2; ++cb) col[b][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int a = 0; a < 3; ++a)
-#pragma unroll
-        for (int b = 0; b < 3; ++b)
-#pragma unroll
-          for (int cb = 0; cb < 2; ++cb) mma16<__bf16>(wt[a * 3 + b][cb], px[tile][a], col[b][cb]);
-#pragma unroll
-      for (int cb = 0; cb < 2; ++cb)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          // (row_shl: lane j reads lane j + 1 / j + 2 of its row of 16; the last lanes read zero
-          // and finish no pixel)
-          // (the elements are copied out first: __builtin_bit_cast applied to an element of a
-          // vector reads the vector's first element whatever the index)
-          const float f1 = col[1][cb][i], f2 = col[2][cb][i];
-          const float c1 = __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, f1), 0x101, 0xf, 0xf, true));
-          const float c2 = __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, f2), 0x102, 0xf, 0xf, true));
-          acc[tile][cb][i] = (col[0][cb][i] + c1) + c2;
-        }
-    }
-    // bias + residual + activation + the one rounding: a lane holds channels
-    // co0 + 16 cb + 4 kq + {0..3} of its pixel of either tile
-#pragma unroll
-    for (int tile = 0; tile < 2; ++tile) {
-      if (img[tile] < p.N && pxl < kRegwTilePixels && ow[tile] < p.W_out) {
-        const int oh = p.out_lo + row[tile];
-        const long yrow = ((long)(img[tile] * p.y_rows + oh - p.y_row0) * p.W_out) * p.C_out + co0;
-        const long rrow = p.res ? ((long)(img[tile] * p.r_rows + oh - p.r_row0) * p.W_out) * p.C_out + co0 : 0;
-        const int in_row = ow[tile] * p.C_out + kq * 4;
-#pragma unroll
-        for (int cb = 0; cb < 2; ++cb) {
-          float v[4];
-#pragma unroll
-          for (int i = 0; i < 4; ++i) v[i] = acc[tile][cb][i] + bias[cb][i];
-          if (p.res) {
-            alignas(8) __bf16 rr[4];
-            *(uint2*)rr = *(const uint2*)((const __bf16*)p.res + rrow + in_row + cb * 16);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) v[i] += (float)rr[i];
-          }
-          alignas(8) __bf16 o[4];
-#pragma unroll
-          for (int i = 0; i < 4; ++i) o[i] = (__bf16)clamp_act(v[i], cl);
-          *(uint2*)((__bf16*)p.y + yrow + in_row + cb * 16) = *(const uint2*)o;
-          if (p.y2) *(uint2*)((__bf16*)p.y2 + yrow + in_row + cb * 16) = *(const uint2*)o;
-        }
-      }
-      // the same wavefront's tile of the next round
-      tcol[tile] += adv_col;
-      const int c1 = tcol[tile] >= tpr;
-      tcol[tile] -= c1 ? tpr : 0;
-      row[tile] += adv_row + c1;
-      const int c2 = row[tile] >= p.R;
-      row[tile] -= c2 ? p.R : 0;
-      img[tile] += adv_img + c2;
-    }
-  }
-}
-
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void conv_regw_kernel(const ConvParams p) {
-  conv_regw_kernel_body(p, blockIdx.x, gridDim.x);
-}
-// The same for several bands of one layer in one grid (band b owns blocks first[b] .. first[b + 1] of x).
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void conv_regw_kernel_bands(const Batch<ConvParams> t) {
-  const int b = batch_find(t, blockIdx.x);
-  conv_regw_kernel_body(t.p[b], blockIdx.x - t.first[b], t.first[b + 1] - t.first[b]);
-}
-
-// Whether the filter-in-registers kernel takes a launch (judged on all bands of a group together).
-bool regw_applies(const ConvParams& p, int dtype) {
-  if (dtype != LOP_BF16 || p.C_in != 32 || p.kh != 3 || p.kw != 3 || p.C_out % 32 != 0) return false;
-  if (p.sw != 1 || p.dw != 1) return false;   // (a lane's taps are its neighbours' pixels)
-  if (p.M < kRegwMinPixels || p.pool) return false;
-  // 32-bit signed byte offsets into the input slab
-  return (size_t)p.N * p.x_rows * p.W * p.C_in * 2 < ((size_t)1 << 31);
-}
-
-hipError_t launch_regw(const ConvParams* ps, int n, hipStream_t s, KernelEvents* ev) {
-  const ConvParams& p = ps[0];
-  const unsigned gy = (unsigned)(p.C_out / 32);
-  long all = 0;
-  for (int b = 0; b < n; ++b) all += regw_groups(ps[b]);
-  if (all <= 0 || (int)gy * 32 > conv_cout_pad(p.C_out)) return hipErrorInvalidValue;
-  // every band gets its share of the resident workgroups (a multiple of the XCD count, or all
-  // of its pixel groups when those are fewer)
-  unsigned gx[kMaxBatch];
-  for (int b = 0; b < n; ++b) {
-    if ((size_t)ps[b].N * ps[b].x_rows * ps[b].W * ps[b].C_in * 2 >= ((size_t)1 << 31)) return hipErrorInvalidValue;
-    const long groups = regw_groups(ps[b]);
-    long share = (long)kRegwWorkgroups / gy * groups / all;
-    share = share / kXcds * kXcds;
-    gx[b] = (unsigned)(share >= kXcds && share < groups ? share : groups);
-  }
-  return launch_group(conv_regw_kernel, conv_regw_kernel_bands, ps, n, gx, gy, 1, dim3(256), s, ev);
-}
-
 constexpr int kNarrowWaves = 16;
 // Stages of 128 bytes per row in LDS per workgroup. fp32: eight while the launch has at most one
 // workgroup per compute unit (nothing else hides a workgroup's latency), four beyond that: with
@@ -1749,15 +1536,6 @@ ConvParams group_params(const ConvParams* ps, int n) {
   return g;
 }
 
-// Whether the filter-in-registers kernel takes a group of bands: the layer and the group's
-// pixels qualify and every band's slab is within reach of its 32-bit offsets.
-bool regw_takes(const ConvParams* ps, int n, int dtype) {
-  if (!regw_applies(group_params(ps, n), dtype)) return false;
-  for (int b = 0; b < n; ++b)
-    if ((size_t)ps[b].N * ps[b].x_rows * ps[b].W * ps[b].C_in * 2 >= ((size_t)1 << 31)) return false;
-  return true;
-}
-
 // Split-K partial sums of the bands of a group, one region after the other in the workspace.
 size_t assign_workspace(ConvParams* ps, int n, int splits, int kc_per_split, float* ws) {
   size_t at = 0;
@@ -1778,12 +1556,6 @@ hipError_t launch_typed(ConvParams* ps, int n, int dtype, float* ws, hipStream_t
   for (int b = 0; b < n; ++b)
     if ((size_t)ps[b].N * ps[b].x_rows * ps[b].W * ps[b].C_in * sizeof(T) >= ((size_t)1 << 32)) return hipErrorInvalidValue;
   const ConvParams g = group_params(ps, n);
-  if constexpr (sizeof(T) == 2) {
-    if (regw_takes(ps, n, dtype)) {
-      for (int b = 0; b < n; ++b) ps[b].ws = nullptr;
-      return launch_regw(ps, n, s, ev);
-    }
-  }
   const Choice c = choose(g, dtype);
   const DirectChoice d = choose_direct(g, dtype, c.splits);
   const LdsChoice ld = lds_applies(g, dtype, c, d);
@@ -1876,13 +1648,12 @@ int group_of(const OpLaunch* Ls, int n, ConvParams* ps) {
 }  // namespace
 
 size_t conv_workspace_bytes_bands(const OpLaunch* Ls, int n) {
-  if (n < 1 || n > kMaxBatch || stem_applies(Ls[0]) || narrow_applies(Ls, n) || patch_applies(Ls, nullptr, n) || gemm_applies(Ls, n)) return 0;
+  if (n < 1 || n > kMaxBatch || stem_applies(Ls[0]) || walk_applies(Ls, nullptr, n) || narrow_applies(Ls, n) || patch_applies(Ls, nullptr, n) || gemm_applies(Ls, n)) return 0;
   ConvParams ps[kMaxBatch];
   const int m = group_of(Ls, n, ps);
   if (m == 0) return 0;
   const int dtype = Ls[0].dtype;
   const ConvParams g = group_params(ps, m);
-  if (regw_takes(ps, m, dtype)) return 0;
   const Choice c = choose(g, dtype);
   const DirectChoice d = choose_direct(g, dtype, c.splits);
   if (lds_applies(g, dtype, c, d).bm) return 0;
@@ -1897,6 +1668,7 @@ hipError_t launch_conv_igemm_bands(const OpLaunch* Ls, int n, hipStream_t stream
   ConvParams ps[kMaxBatch];
   const int m = group_of(Ls, n, ps);
   if (m == 0) return hipSuccess;
+  if (walk_applies(Ls, nullptr, n)) return launch_walk(Ls, nullptr, n, stream, ev);
   if (narrow_applies(Ls, n)) return launch_narrow(Ls, n, stream, ev);
   if (patch_applies(Ls, nullptr, n)) return launch_patch(Ls, nullptr, n, stream, ev);
   if (gemm_applies(Ls, n)) return launch_gemm(Ls, n, stream, ev);
@@ -1916,6 +1688,7 @@ int conv_igemm_describe_bands(const OpLaunch* Ls, int n, char* name, size_t size
     if (name && size) name[0] = 0;
     return 0;
   }
+  if (walk_applies(Ls, nullptr, n)) return walk_describe(Ls, nullptr, n, name, size);
   if (narrow_applies(Ls, n)) return narrow_describe(Ls, n, name, size);
   if (patch_applies(Ls, nullptr, n)) return patch_describe(Ls, nullptr, n, name, size);
   if (gemm_applies(Ls, n)) return gemm_describe(Ls, n, name, size);
@@ -1924,10 +1697,6 @@ int conv_igemm_describe_bands(const OpLaunch* Ls, int n, char* name, size_t size
   const char* const form = m > 1 ? "_bands" : "";
   const bool bf = L.dtype == LOP_BF16;
   const bool vec = p.C_in % (bf ? 8 : 4) == 0;
-  if (regw_takes(ps, m, L.dtype)) {
-    if (name && size) snprintf(name, size, "conv_regw_kernel%s", form);
-    return 1;
-  }
   const Choice c = choose(p, L.dtype);
   static const int wm[] = {2, 2, 2, 4, 2}, wn[] = {2, 2, 2, 1, 4};
   const DirectChoice d = choose_direct(p, L.dtype, c.splits);
@@ -2002,7 +1771,7 @@ bool convpool_applies(const OpLaunch& conv, const OpLaunch& pool) {
 bool convpool_pays_bands(const OpLaunch* convs, int n) {
   ConvParams ps[kMaxBatch];
   const int m = n >= 1 && n <= kMaxBatch ? group_of(convs, n, ps) : 0;
-  if (m == 0 || patch_applies(convs, nullptr, n)) return true;
+  if (m == 0 || walk_applies(convs, nullptr, n) || patch_applies(convs, nullptr, n)) return true;
   if (narrow_applies(convs, n)) return false;
   const ConvParams p = group_params(ps, m);
   const Choice c = choose(p, convs[0].dtype);
@@ -2025,6 +1794,7 @@ hipError_t launch_convpool_bands(const OpLaunch* convs, const OpLaunch* pools, i
     ps[m++] = p;
   }
   if (m == 0) return hipSuccess;
+  if (walk_applies(convs, pools, n)) return launch_walk(convs, pools, n, stream, ev);
   if (patch_applies(convs, pools, n)) return launch_patch(convs, pools, n, stream, ev);
   const LdsChoice ld = choose_pooled(group_params(ps, m), convs[0].dtype);
   if (convs[0].dtype == LOP_BF16) {
@@ -2052,6 +1822,7 @@ int convpool_describe_bands(const OpLaunch* convs, const OpLaunch* pools, int n,
     if (name && size) name[0] = 0;
     return 0;
   }
+  if (walk_applies(convs, pools, n)) return walk_describe(convs, pools, n, name, size);
   if (patch_applies(convs, pools, n)) return patch_describe(convs, pools, n, name, size);
   const LdsChoice ld = choose_pooled(group_params(ps, m), convs[0].dtype);
   const bool bf = convs[0].dtype == LOP_BF16;

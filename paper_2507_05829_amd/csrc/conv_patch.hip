@@ -35,6 +35,7 @@
 
 #include "act.hpp"
 #include "conv_common.hpp"
+#include "conv_tiles.hpp"
 #include "kernels.hpp"
 #include "launch.hpp"
 #include "lop.h"
@@ -42,27 +43,7 @@
 namespace lop {
 namespace {
 
-struct PatchParams {
-  const void* x;
-  void* y;
-  void* y2;         // second destination with y's layout, or nullptr
-  const void* res;
-  const void* wd;   // weights in MFMA operand order
-  const float* bias;
-  int x_row0, x_rows, W, C_in;
-  int y_row0, y_rows, W_out, C_out;  // of the tensor that is stored (POOL: the pooled one)
-  int r_row0, r_rows;
-  int ph, pw, act, k_steps;          // k_steps: MFMA steps of a packed weight row
-  int out_lo, R, N;                  // output rows of the convolution itself
-  int Wc;                            // its columns
-  int th, tw, nty, ntx;              // tile of output pixels, tiles per image in either direction
-  int pitch, ph_rows;                // pixel slots per row of the patch (S == 2: even columns, then odd), its rows
-  FastDiv by_ntx, by_nty, by_tw, by_pitch, by_group;
-};
-static_assert(sizeof(Batch<PatchParams>) <= 4096, "the parameters of all bands of a launch travel as kernel arguments");
-
 constexpr int kPixelBytes = 144, kPixelSlots = 9;
-constexpr unsigned kOutside = 0x80000000u;
 
 // TP x 32 pixels x NT x 32 channels per workgroup; NI: load instructions per wavefront and patch.
 template <typename T, int TP, int NT, int NI, bool POOL, int S>
@@ -358,6 +339,7 @@ __device__ __forceinline__ void patch_body(const PatchParams& p, const int bx, c
 
 // Load instructions per wavefront and patch: the patch of a tile has at most NI * 256 / 9 pixels.
 constexpr int patch_loads(int tp, int s) { return s == 1 ? (tp == 4 ? 7 : tp == 2 ? 4 : 3) : 6; }
+constexpr int patch_room(int bm, int s) { return patch_loads(bm / 32, s) * 256 / kPixelSlots; }
 
 template <typename T, int BM, int BN, int NST, bool POOL, int S>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void conv_lds_kernel(const PatchParams p) {
@@ -368,44 +350,6 @@ template <typename T, int BM, int BN, int NST, bool POOL, int S>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void conv_lds_kernel_bands(const Batch<PatchParams> t) {
   const int b = batch_find(t, blockIdx.x);
   patch_body<T, BM / 32, BN / 32, patch_loads(BM / 32, S), POOL, S>(t.p[b], blockIdx.x - t.first[b], t.first[b + 1] - t.first[b]);
-}
-
-// The convolution's own output rows and columns behind a launch (pooled: twice the pooled ones).
-struct PatchWork { int R, Wc, N; };
-PatchWork patch_work(const OpLaunch& c, const OpLaunch* pool) {
-  if (pool) return {2 * (pool->out_hi - pool->out_lo), 2 * pool->y.w, c.x.n};
-  return {c.out_hi - c.out_lo, c.y.w, c.x.n};
-}
-
-// The rectangle of at most 32 tp output pixels for R x W of them: the fewest tiles, then the
-// smallest patch, over widths that split the columns evenly.
-struct PatchTile { int th = 0, tw = 0; long tiles = 0; int patch = 0; };
-PatchTile find_tile(const PatchWork& w, int tp, int s, bool pool) {
-  const int pixels = tp * 32, room = patch_loads(tp, s) * 256 / kPixelSlots, step = pool ? 2 : 1;
-  PatchTile best;
-  for (int target = 64; target >= 2; target /= 2) {
-    const int k = (w.Wc + target - 1) / target;
-    int tw = (w.Wc + k - 1) / k;
-    tw = (tw + step - 1) / step * step;
-    if (tw > pixels) continue;
-    int th = std::min(pixels / tw, w.R) / step * step;
-    const int cols = s == 1 ? tw + 2 : 2 * (tw + 1);
-    while (th >= step && ((th - 1) * s + 3) * cols > room) th -= step;
-    if (th < step) continue;
-    const long tiles = (long)((w.R + th - 1) / th) * ((w.Wc + tw - 1) / tw) * w.N;
-    const int patch = ((th - 1) * s + 3) * cols;
-    if (!best.th || tiles < best.tiles || (tiles == best.tiles && patch < best.patch)) best = {th, tw, tiles, patch};
-  }
-  return best;
-}
-// (Every launch asks for the same few rectangles again and again: the last ones are remembered per thread.)
-PatchTile tile_for(const PatchWork& w, int tp, int s, bool pool) {
-  struct Entry { PatchWork w; int tp, s; bool pool; PatchTile t; };
-  thread_local Entry memo[64] = {};
-  Entry& e = memo[(unsigned)(w.R * 31 + w.Wc * 7 + w.N * 3 + tp * 5 + s * 2 + pool) % 64];
-  if (e.w.R != w.R || e.w.Wc != w.Wc || e.w.N != w.N || e.tp != tp || e.s != s || e.pool != pool || !e.t.th)
-    e = {w, tp, s, pool, find_tile(w, tp, s, pool)};
-  return e.t;
 }
 
 bool patch_shape(const OpLaunch& L) {
@@ -452,7 +396,7 @@ PatchChoice choose_patch(const OpLaunch* convs, const OpLaunch* pools, int n) {
     for (int b = 0; b < n; ++b) {
       const PatchWork w = patch_work(convs[b], pools ? &pools[b] : nullptr);
       if (w.R <= 0) continue;
-      const PatchTile pt = tile_for(w, bm / 32, L.sh, pools != nullptr);
+      const PatchTile pt = tile_for(w, bm, patch_room(bm, L.sh), L.sh, pools != nullptr);
       if (!pt.th) return 0L;
       t += pt.tiles;
     }
@@ -476,31 +420,6 @@ PatchChoice choose_patch(const OpLaunch* convs, const OpLaunch* pools, int n) {
   return best;
 }
 
-PatchParams make_patch(const OpLaunch& c, const OpLaunch* pool, int bm, int bn, unsigned gy, unsigned* gx) {
-  PatchParams p;
-  const Slab& y = pool ? pool->y : c.y;
-  const PatchWork w = patch_work(c, pool);
-  const int ke = c.dtype == LOP_BF16 ? 8 : 4;
-  p.x = c.x.ptr; p.y = y.ptr; p.y2 = pool ? pool->y2 : c.y2; p.res = c.res.ptr; p.wd = c.wd; p.bias = c.bias;
-  p.x_row0 = c.x.row0; p.x_rows = c.x.rows; p.W = c.x.w; p.C_in = c.x.c;
-  p.y_row0 = y.row0; p.y_rows = y.rows; p.W_out = y.w; p.C_out = c.y.c;
-  p.r_row0 = c.res.row0; p.r_rows = c.res.rows;
-  p.ph = c.ph; p.pw = c.pw; p.act = c.act; p.k_steps = c.k_pad / (2 * ke);
-  p.out_lo = pool ? 2 * pool->out_lo : c.out_lo;
-  p.R = w.R; p.N = w.N; p.Wc = w.Wc;
-  const PatchTile t = tile_for(w, bm / 32, c.sh, pool != nullptr);
-  p.th = t.th; p.tw = t.tw;
-  p.nty = (w.R + t.th - 1) / t.th; p.ntx = (w.Wc + t.tw - 1) / t.tw;
-  p.pitch = c.sh == 1 ? t.tw + 2 : 2 * (t.tw + 1);
-  p.ph_rows = (t.th - 1) * c.sh + 3;
-  p.by_ntx = make_fastdiv(p.ntx); p.by_nty = make_fastdiv(p.nty);
-  p.by_tw = make_fastdiv(pool ? t.tw / 2 : t.tw);
-  p.by_pitch = make_fastdiv(p.pitch);
-  p.by_group = make_fastdiv(kGroupM * (int)gy);
-  *gx = (unsigned)t.tiles;
-  return p;
-}
-
 template <typename T, int BM, int BN>
 hipError_t launch_tile(const OpLaunch* convs, const OpLaunch* pools, int n, hipStream_t s, KernelEvents* ev) {
   PatchParams ps[kMaxBatch];
@@ -511,8 +430,8 @@ hipError_t launch_tile(const OpLaunch* convs, const OpLaunch* pools, int n, hipS
   for (int b = 0; b < n; ++b) {
     const PatchWork w = patch_work(convs[b], pools ? &pools[b] : nullptr);
     if (w.R <= 0) continue;
-    ps[m] = make_patch(convs[b], pools ? &pools[b] : nullptr, BM, BN, gy, &gx[m]);
-    const int room = patch_loads(BM / 32, convs[b].sh) * 256 / kPixelSlots;
+    ps[m] = make_patch(convs[b], pools ? &pools[b] : nullptr, BM, patch_room(BM, convs[b].sh), gy, &gx[m]);
+    const int room = patch_room(BM, convs[b].sh);
     if (ps[m].th < 1 || ps[m].ph_rows * ps[m].pitch > room || ps[m].th * ps[m].tw > BM) return hipErrorInvalidValue;
     ++m;
   }

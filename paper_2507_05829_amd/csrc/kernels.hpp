@@ -107,6 +107,11 @@ void stem_mfma_describe(const OpLaunch& L, bool large, const char* form, char* n
 bool patch_applies(const OpLaunch* convs, const OpLaunch* pools, int n);
 hipError_t launch_patch(const OpLaunch* convs, const OpLaunch* pools, int n, hipStream_t stream, KernelEvents* ev);
 int patch_describe(const OpLaunch* convs, const OpLaunch* pools, int n, char* name, size_t size);
+// The kernel that walks over tiles with the filter in registers (bf16, 3 x 3 filters, 32 or 64 channels in; pools as
+// above): whether a group of bands takes it, the launch and its kernel name.
+bool walk_applies(const OpLaunch* convs, const OpLaunch* pools, int n);
+hipError_t launch_walk(const OpLaunch* convs, const OpLaunch* pools, int n, hipStream_t stream, KernelEvents* ev);
+int walk_describe(const OpLaunch* convs, const OpLaunch* pools, int n, char* name, size_t size);
 // The 16 x 16-tile kernel in its patch form (fp32, 3 x 3 filters, few pixels): whether a group of bands takes it,
 // the launch and its kernel name.
 bool narrow_applies(const OpLaunch* Ls, int n);

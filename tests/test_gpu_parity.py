@@ -1394,6 +1394,47 @@ def test_patch_form_of_the_lds_staged_kernel(oracle, cfg):
             np.testing.assert_array_equal(dev, want_int)
 
 
+WALK_GRID = [
+    # c_in, c_out, stride, pooled, shape(n,h,w), residual, the form expected in one band
+    (64, 64, 1, False, (1, 211, 205), True, "<128, 1, 2, false>"),     # ragged tiles in both directions
+    (64, 192, 1, False, (3, 70, 71), False, "<128, 1, 2, false>"),     # three blocks of channels, batch 3
+    (64, 64, 1, True, (1, 213, 207), False, "<128, 1, 2, true>"),      # odd sizes: last row and column unused
+    (32, 64, 2, False, (1, 243, 235), True, "<64, 2, 2, false>"),      # stride 2: even and odd columns apart
+    (32, 128, 2, False, (3, 5, 1801), False, "<64, 2, 2, false>"),     # an image three rows high
+    (64, 128, 2, False, (2, 119, 121), False, "<128, 2, 4, false>"),
+]
+
+
+@pytest.mark.parametrize("cfg", WALK_GRID)
+def test_walking_kernel(oracle, cfg):
+    """3 x 3 convolutions of 32 or 64 channels with the filter in registers: every form, checked by
+    name, against the oracle in one band, with all bands in one launch and with shared rows; small
+    integers bit for bit."""
+    c_in, c_out, stride, pooled, shape, residual, form = cfg
+    chain = workloads.Chain("walk", (shape[0], c_in, shape[1], shape[2]), "bf16", 3)
+    first = chain.add(workloads.CONV, c_in, c_out, 1, stride, 0, act="none") if residual else workloads.NO_RESIDUAL
+    chain.add(workloads.CONV, c_in, c_out, 3, stride, 1, act="relu", input_from=workloads.CHAIN_INPUT, residual_from=first)
+    if pooled:
+        chain.add(workloads.MAXPOOL, c_out, c_out, 2, 2, 0)
+    t = workloads.make_tensors(chain, zero_bias=False, seed=29)
+    plan = lop.Plan(chain, t, 1)
+    try:
+        assert plan.layer_kernel(0, plan.n_layers - 1)[0] == "conv_walk_kernel" + form
+    finally:
+        plan.destroy()
+    want = oracle.run_chain(chain, t)
+    ti = workloads.small_int_tensors(chain, seed=3)
+    ti.weights = [w if w is None else np.sign(w) * (np.abs(w) > 1) * (np.arange(w.size).reshape(w.shape) % 5 == 0) for w in ti.weights]
+    want_int = oracle.run_chain(chain, ti)
+    for bands, flags in ((1, 0), (3, 0), (3, lop.LOP_FLAG_REUSE)):
+        dev, host = run_gpu(chain, t, n_bands=bands, flags=flags)
+        np.testing.assert_array_equal(dev, host)
+        assert rel_err(dev, want) <= TOL["bf16"], (bands, flags)
+        if np.abs(want_int).max() <= 256:
+            dev, _ = run_gpu(chain, ti, n_bands=bands, flags=flags)
+            np.testing.assert_array_equal(dev, want_int)
+
+
 NARROW_GRID = [
     # c_in, c_out, stride, shape(n,h,w), residual, the form expected in one band
     (128, 128, 1, (1, 9, 13), True, "<float, 5, 49152>"),        # slices of four and five steps
