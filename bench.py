@@ -172,6 +172,19 @@ def weight_bytes(chain, l):
     return float(esz * L.c_out * (L.c_in // groups) * L.k[0] * L.k[1])
 
 
+def merged_twin(case, torch, lop, workloads, a):
+    """The plan whose launches are the ones run_chain enqueues for `case`: all bands of a layer in one launch
+    (independent bands: the batched plan, if its launches have such a form; shared rows: one band),
+    or None where the case's own per-band launches are all there is."""
+    if case.mode == "batched":
+        return None
+    try:
+        return Case(torch, lop, workloads, case.name, "batched" if case.mode == "independent" else "reuse", a,
+                    None if case.mode == "independent" else 1, case.nofuse, n_buf=1)
+    except lop.LopError:
+        return None
+
+
 def launch_rows(case, iters):
     """Every (layer, band) launch of one chain, timed on one stream, one lane, with a start and
     a stop HIP event attached to the dispatch itself (the kernel's own duration, as a
@@ -328,7 +341,10 @@ def measure(torch, lop, workloads, name, mode, a, steps, warmup, link_gbs, nofus
     res["d2h"]["single_request_extra_us"] = round(extra_us, 2)
     res["d2h"]["hidden_single_vs_link_rate"] = round(1.0 - max(0.0, extra_us) / copy_us_link, 4)
     res["d2h"]["hidden_single_bound"] = round((plan.n_bands - 1) / plan.n_bands, 4)
-    rows, ridge, mf_peak = launch_rows(case, a.profile_iters)
+    twin = merged_twin(case, torch, lop, workloads, a)
+    rows, ridge, mf_peak = launch_rows(twin or case, a.profile_iters)
+    if twin:
+        twin.close()
     groups = kernel_groups(rows, chain.dtype)
     res["kernels"] = strip(groups)
     res["roofline"] = dominant_roofline(groups, ridge, mf_peak, f"{case.tag().replace(':', '_')}_{mode}")
@@ -427,8 +443,9 @@ def main():
     if a.only_kernel_table:
         name, _, nf = a.workload.partition(":")
         case = Case(torch, lop, workloads, name, a.mode, a, a.bands, nf == "nofuse")
-        case.plan.profile_chain(case.d_in, case.d_out[0], 3)
-        rows, _, _ = launch_rows(case, a.profile_iters)
+        twin = merged_twin(case, torch, lop, workloads, a) or case
+        twin.plan.profile_chain(twin.d_in, twin.d_out[0], 3)
+        rows, _, _ = launch_rows(twin, a.profile_iters)
         print(json.dumps(dict(workload=case.tag(), mode=a.mode, n_bands=case.plan.n_bands,
                               kernels=strip(kernel_groups(rows, case.chain.dtype)), launches=strip(rows))))
         case.close()
