@@ -1676,6 +1676,22 @@ hipError_t launch_conv_igemm_bands(const OpLaunch* Ls, int n, hipStream_t stream
                                  : launch_typed<float>(ps, m, Ls[0].dtype, (float*)Ls[0].ws, stream, ev);
 }
 
+bool siblings_apply(const OpLaunch* convs, const OpLaunch* sibs, int n) {
+  if (n < 1 || n > kMaxBatch) return false;
+  for (int b = 0; b < n; ++b) {   // the 1 x 1 one's pixels are the centre taps of the other's
+    const OpLaunch &c = convs[b], &q = sibs[b];
+    if (c.op != LOP_CONV2D || q.op != LOP_CONV2D || c.kh != 3 || c.kw != 3 || c.ph != 1 || c.pw != 1 || c.dh != 1 || c.dw != 1) return false;
+    if (q.kh != 1 || q.kw != 1 || q.ph != 0 || q.pw != 0 || q.sh != c.sh || q.sw != c.sw || q.y.w != c.y.w) return false;
+    if (c.res.ptr || q.res.ptr || c.x.ptr != q.x.ptr || q.out_lo < c.out_lo || q.out_hi > c.out_hi) return false;
+  }
+  if (walk_applies(convs, nullptr, n)) return false;
+  return narrow_takes_sibling(convs, sibs, n) || patch_takes_sibling(convs, sibs, n);
+}
+hipError_t launch_siblings(const OpLaunch* convs, const OpLaunch* sibs, int n, hipStream_t stream, KernelEvents* ev) {
+  return narrow_takes_sibling(convs, sibs, n) ? launch_narrow_siblings(convs, sibs, n, stream, ev)
+                                              : launch_patch_siblings(convs, sibs, n, stream, ev);
+}
+
 hipError_t launch_conv_igemm(const OpLaunch& L, hipStream_t stream, KernelEvents* ev) {
   return launch_conv_igemm_bands(&L, 1, stream, ev);
 }

@@ -21,6 +21,7 @@
 
 #include "act.hpp"
 #include "conv_common.hpp"
+#include "conv_tiles.hpp"
 #include "kernels.hpp"
 #include "launch.hpp"
 #include "lop.h"
@@ -42,8 +43,12 @@ struct NarrowParams {
   int out_lo, R, N;
   int th, tw, nty, ntx;              // tile of output pixels, tiles per image in either direction
   int pitch, ph_rows;                // pixels per row of the patch, its rows
-  int steps, per_wave;               // steps of 16 reduction elements: of the operator, of a wavefront
-  FastDiv by_ntx, by_nty, by_tw, by_pitch, by_group, by_slots, by_tap;
+  // a 1 x 1 convolution of the same input and stride, in the channel tiles from b_first on (see Sibling)
+  const void* b_wd16;
+  float* b_y;
+  const float* b_bias;
+  int b_w_steps, b_y_row0, b_y_rows, b_C_out, b_act, b_lo, b_hi, b_first;
+  FastDiv by_ntx, by_nty, by_tw, by_pitch, by_group, by_slots;
 };
 static_assert(sizeof(Batch<NarrowParams>) <= 4096, "the parameters of all bands of a launch travel as kernel arguments");
 
@@ -62,7 +67,6 @@ constexpr int kMinSteps = 64, kMaxSteps = 288;
 // 49 pixels 9.8 us against 14.1, on 126 pixels 17.4 against 24.1).
 constexpr long kTilesAlways = 256, kTilesOverCut = 1024;
 constexpr int kPartPitch = 20;          // fp32 pitch of a staged partial tile
-constexpr unsigned kOutside = 0x80000000u;
 
 template <int AHEAD, int LDS>
 __device__ __forceinline__ void narrow_body(const NarrowParams& p, const int bx, const int gx) {
@@ -73,7 +77,8 @@ __device__ __forceinline__ void narrow_body(const NarrowParams& p, const int bx,
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int px = lane & 15, kq = lane >> 4;
   const TileId tile = xcd_tile(bx, gx, gridDim.y, 1, p.by_group);
-  const int co0 = tile.n * 16;
+  const bool second = tile.n >= p.b_first;
+  const int tile_n = second ? tile.n - p.b_first : tile.n, co0 = tile_n * 16;
   const int q = fastdiv(tile.m, p.by_ntx), tx = tile.m - q * p.ntx;
   const int n = fastdiv(q, p.by_nty), ty = q - n * p.nty;
   const int r0 = ty * p.th, c0 = tx * p.tw;
@@ -100,18 +105,19 @@ __device__ __forceinline__ void narrow_body(const NarrowParams& p, const int bx,
   __builtin_amdgcn_sched_barrier(0);
 
   // ---- this wavefront's slice of the reduction: steps s0 .. s1, its filter vectors AHEAD steps ahead
-  const int s0 = wave * p.per_wave, s1 = min(p.steps, s0 + p.per_wave);
-  const u32x4* const wsrc = (const u32x4*)p.wd16 + (size_t)tile.n * p.w_steps * 64 + lane;
+  const int tap_steps = p.C_in / 16, steps = second ? tap_steps : 9 * tap_steps, per_wave = (steps + kWaves - 1) / kWaves;
+  const int s0 = min(steps, wave * per_wave), s1 = min(steps, s0 + per_wave);
+  const u32x4* const wsrc = (const u32x4*)(second ? p.b_wd16 : p.wd16) + (size_t)tile_n * (second ? p.b_w_steps : p.w_steps) * 64 + lane;
   u32x4 w[AHEAD];
-  auto fetch = [&](int s) __attribute__((always_inline)) { return wsrc[(size_t)min(s, p.steps - 1) * 64]; };
+  auto fetch = [&](int s) __attribute__((always_inline)) { return wsrc[(size_t)min(s, steps - 1) * 64]; };
 #pragma unroll
   for (int u = 0; u < AHEAD; ++u) w[u] = fetch(s0 + u);
   asm volatile("" ::: "memory");
   __builtin_amdgcn_sched_barrier(0);
 
-  const int tap_steps = p.C_in / 16;
-  int tap = fastdiv(s0, p.by_tap), ci = (s0 - tap * tap_steps) * 64;   // ci: bytes into the pixel
-  int ta = tap / 3, tb = tap - ta * 3;
+  int tap = s0 / tap_steps, ci = (s0 - tap * tap_steps) * 64;   // ci: bytes into the pixel
+  if (second) tap = 4;
+  int ta = min(tap / 3, 2), tb = tap - tap / 3 * 3;
   const int pixel_bytes = slots * 16;
   int at;
   {
@@ -160,18 +166,21 @@ __device__ __forceinline__ void narrow_body(const NarrowParams& p, const int bx,
   if (wave != 0) return;
   const int e_px = lane >> 2, co = co0 + (lane & 3) * 4;
   const int r = fastdiv(e_px, p.by_tw), col = c0 + e_px - r * p.tw, row = r0 + r;
-  if (r >= p.th || row >= p.R || col >= p.W_out || co >= p.C_out) return;
+  const int C_out = second ? p.b_C_out : p.C_out;
+  if (r >= p.th || row >= p.R || col >= p.W_out || co >= C_out) return;
+  if (second && (p.out_lo + row < p.b_lo || p.out_lo + row >= p.b_hi)) return;
   f32x4 v = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int s = 0; s < kWaves; ++s) v += *(const f32x4*)(part + s * (16 * kPartPitch) + e_px * kPartPitch + (lane & 3) * 4);
-  if (p.bias) v += *(const f32x4*)(p.bias + co);
-  if (p.res) v += *(const f32x4*)(p.res + ((size_t)(n * p.r_rows + p.out_lo + row - p.r_row0) * p.W_out + col) * p.C_out + co);
-  const Clamp cl = make_clamp(p.act);
+  const float* const bias = second ? p.b_bias : p.bias;
+  if (bias) v += *(const f32x4*)(bias + co);
+  if (p.res && !second) v += *(const f32x4*)(p.res + ((size_t)(n * p.r_rows + p.out_lo + row - p.r_row0) * p.W_out + col) * p.C_out + co);
+  const Clamp cl = make_clamp(second ? p.b_act : p.act);
 #pragma unroll
   for (int j = 0; j < 4; ++j) v[j] = clamp_act(v[j], cl);
-  const size_t ya = ((size_t)(n * p.y_rows + p.out_lo + row - p.y_row0) * p.W_out + col) * p.C_out + co;
-  *(f32x4*)(p.y + ya) = v;
-  if (p.y2) *(f32x4*)(p.y2 + ya) = v;
+  const size_t ya = ((size_t)(n * (second ? p.b_y_rows : p.y_rows) + p.out_lo + row - (second ? p.b_y_row0 : p.y_row0)) * p.W_out + col) * C_out + co;
+  *(f32x4*)((second ? p.b_y : p.y) + ya) = v;
+  if (p.y2 && !second) *(f32x4*)(p.y2 + ya) = v;
 }
 
 template <typename T, int AHEAD, int LDS>
@@ -234,11 +243,10 @@ NarrowParams make_narrow(const OpLaunch& L, unsigned gy, unsigned* gx) {
   p.th = t.th; p.tw = t.tw;
   p.nty = (p.R + t.th - 1) / t.th; p.ntx = (p.W_out + t.tw - 1) / t.tw;
   p.pitch = (t.tw - 1) * p.s + 3; p.ph_rows = (t.th - 1) * p.s + 3;
-  p.steps = 9 * p.C_in / 16;
-  p.per_wave = (p.steps + kWaves - 1) / kWaves;
+  p.b_first = kNoSibling;
   p.by_ntx = make_fastdiv(p.ntx); p.by_nty = make_fastdiv(p.nty); p.by_tw = make_fastdiv(t.tw);
   p.by_pitch = make_fastdiv(p.pitch); p.by_group = make_fastdiv(kGroupM * (int)gy);
-  p.by_slots = make_fastdiv(p.C_in / 4 + 1); p.by_tap = make_fastdiv(p.C_in / 16);
+  p.by_slots = make_fastdiv(p.C_in / 4 + 1);
   *gx = (unsigned)t.tiles;
   return p;
 }
@@ -257,10 +265,12 @@ bool narrow_applies(const OpLaunch* Ls, int n) {
   return t >= 1 && (t <= kTilesAlways || (t <= kTilesOverCut && !patch_applies(Ls, nullptr, n)));
 }
 
-hipError_t launch_narrow(const OpLaunch* Ls, int n, hipStream_t s, KernelEvents* ev) {
+// sibs: per band the 1 x 1 convolution that the launch computes as well, or nullptr
+hipError_t launch_narrow_siblings(const OpLaunch* Ls, const OpLaunch* sibs, int n, hipStream_t s, KernelEvents* ev) {
   if (n < 1 || n > kMaxBatch) return hipErrorInvalidValue;
-  const unsigned gy = (unsigned)((Ls[0].y.c + 15) / 16);
-  if ((int)gy * 16 > conv_cout_pad(Ls[0].y.c)) return hipErrorInvalidValue;  // unguarded weight loads
+  const unsigned gy1 = (unsigned)((Ls[0].y.c + 15) / 16), gy2 = sibs ? (unsigned)((sibs[0].y.c + 15) / 16) : 0, gy = gy1 + gy2;
+  if ((int)gy1 * 16 > conv_cout_pad(Ls[0].y.c)) return hipErrorInvalidValue;  // unguarded weight loads
+  if (sibs && (!sibs[0].wd16 || (int)gy2 * 16 > conv_cout_pad(sibs[0].y.c))) return hipErrorInvalidValue;
   NarrowParams ps[kMaxBatch];
   unsigned gx[kMaxBatch];
   int m = 0;
@@ -270,6 +280,13 @@ hipError_t launch_narrow(const OpLaunch* Ls, int n, hipStream_t s, KernelEvents*
     if (Ls[b].out_hi <= Ls[b].out_lo) continue;
     ps[m] = make_narrow(Ls[b], gy, &gx[m]);
     if (ps[m].th < 1 || ps[m].th * ps[m].tw > 16) return hipErrorInvalidValue;
+    if (sibs) {
+      const OpLaunch& q = sibs[b];
+      NarrowParams& p = ps[m];
+      p.b_wd16 = q.wd16; p.b_y = (float*)q.y.ptr; p.b_bias = q.bias; p.b_w_steps = q.k_pad / 16;
+      p.b_y_row0 = q.y.row0; p.b_y_rows = q.y.rows; p.b_C_out = q.y.c; p.b_act = q.act;
+      p.b_lo = q.out_lo; p.b_hi = q.out_hi; p.b_first = (int)gy1;
+    }
     patch = std::max(patch, patch_bytes(ps[m]));
     ++m;
   }
@@ -278,9 +295,16 @@ hipError_t launch_narrow(const OpLaunch* Ls, int n, hipStream_t s, KernelEvents*
   if (patch > (size_t)kMaxPatch) return hipErrorInvalidValue;
   if (patch > (size_t)kSmallPatch)
     return launch_group(conv_narrow_kernel<float, 9, kMaxPatch>, conv_narrow_kernel_bands<float, 9, kMaxPatch>, ps, m, gx, gy, 1, block, s, ev);
-  if (ps[0].steps > kShortSteps)
+  if (9 * ps[0].C_in / 16 > kShortSteps)
     return launch_group(conv_narrow_kernel<float, 9, kSmallPatch>, conv_narrow_kernel_bands<float, 9, kSmallPatch>, ps, m, gx, gy, 1, block, s, ev);
   return launch_group(conv_narrow_kernel<float, 5, kSmallPatch>, conv_narrow_kernel_bands<float, 5, kSmallPatch>, ps, m, gx, gy, 1, block, s, ev);
+}
+
+hipError_t launch_narrow(const OpLaunch* Ls, int n, hipStream_t s, KernelEvents* ev) {
+  return launch_narrow_siblings(Ls, nullptr, n, s, ev);
+}
+bool narrow_takes_sibling(const OpLaunch* Ls, const OpLaunch* sibs, int n) {
+  return narrow_applies(Ls, n) && sibs[0].wd16 && sibs[0].y.c % 4 == 0;
 }
 
 int narrow_describe(const OpLaunch* Ls, int n, char* name, size_t size) {

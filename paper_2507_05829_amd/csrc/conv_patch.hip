@@ -58,7 +58,8 @@ __device__ __forceinline__ void patch_body(const PatchParams& p, const int bx, c
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int px = lane & 31, half = lane >> 5;
   const TileId tile = xcd_tile(bx, gx, gridDim.y, 1, p.by_group);
-  const int co0 = tile.n * (32 * NT);
+  const bool second = S == 2 && tile.n >= p.sib.first;
+  const int tile_n = second ? tile.n - p.sib.first : tile.n, co0 = tile_n * (32 * NT);
   const int q = fastdiv(tile.m, p.by_ntx), tx = tile.m - q * p.ntx;
   const int n = fastdiv(q, p.by_nty), ty = q - n * p.nty;
   const int r0 = ty * p.th, c0 = tx * p.tw;            // the tile's first row of the launch and first column
@@ -97,7 +98,7 @@ __device__ __forceinline__ void patch_body(const PatchParams& p, const int bx, c
   const u32x4* wsrc[NT];
 #pragma unroll
   for (int t = 0; t < NT; ++t)
-    wsrc[t] = (const u32x4*)p.wd + ((size_t)(tile.n * NT + t) * p.k_steps + wave) * 64 + lane;
+    wsrc[t] = (const u32x4*)(second ? p.sib.wd : p.wd) + ((size_t)(tile_n * NT + t) * (second ? p.sib.k_steps : p.k_steps) + wave) * 64 + lane;
   const int tap_steps = p.C_in / (2 * KE) * 64;
   u32x4 wreg[9][NT];
   auto fetch_tap = [&](int c, int t) __attribute__((always_inline)) {
@@ -106,8 +107,10 @@ __device__ __forceinline__ void patch_body(const PatchParams& p, const int bx, c
   };
 
   fetch_patch(0);
+  if (!second) {
 #pragma unroll
-  for (int t = 0; t < 9; ++t) fetch_tap(0, t);
+    for (int t = 0; t < 9; ++t) fetch_tap(0, t);
+  }
   asm volatile("" ::: "memory");
   __builtin_amdgcn_sched_barrier(0);
 
@@ -196,43 +199,69 @@ __device__ __forceinline__ void patch_body(const PatchParams& p, const int bx, c
     asm volatile("" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
   };
-  int c = 0;
-  for (; c + 1 < chunks; ++c) {
+  if (second) {   // one tap, the centre
+    for (int c = 0; c < chunks; ++c) {
+      u32x4 w1[NT];
+#pragma unroll
+      for (int k = 0; k < NT; ++k) w1[k] = wsrc[k][(size_t)(c * 256)];
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_sched_barrier(0);
+      if (c + 1 < chunks) fetch_patch(c + 1);
+      read_tap((c & 1) * BUF, 4, pa);
+      wait_reads(pa);
+#pragma unroll
+      for (int e = 0; e < kMmaParts<T>; ++e)
+#pragma unroll
+        for (int a = 0; a < NT; ++a)
+#pragma unroll
+          for (int f = 0; f < TP; ++f) mma_part<T>(w1[a], pa[f], acc[a][f], e);
+    }
+  } else {
+    int c = 0;
+    for (; c + 1 < chunks; ++c) {
+      patch_barrier();
+      fetch_patch(c + 1);      // (into the buffer every wavefront was done with at the barrier)
+      run_patch(c, true);
+    }
     patch_barrier();
-    fetch_patch(c + 1);      // (into the buffer every wavefront was done with at the barrier)
-    run_patch(c, true);
+    run_patch(c, false);
   }
-  patch_barrier();
-  run_patch(c, false);
 
   // ---- the four partial tiles, added in wavefront order through LDS: wavefront w finishes pieces
   // w TP .. (w + 1) TP of the UNITS pieces (piece u: fragment u / 4, channels (u % 4) * 8 ..)
   u32x4* const part = (u32x4*)smem;
-  const Clamp cl = make_clamp(p.act);
+  const Clamp cl = make_clamp(second ? p.sib.act : p.act);
+  const int C_out = second ? p.sib.C_out : p.C_out;
+  const float* const bias_at = second ? p.sib.bias : p.bias;
+  T* const y = (T*)(second ? p.sib.y : p.y);
+  T* const y2 = second ? nullptr : (T*)p.y2;
   // where they go, and what is added to them: all loads issued here, ahead of the sums
   int r, cc;
   pixel(wave * TP / 4, r, cc);             // (a wavefront's pieces all lie in one fragment)
   const int row = r0 + r, col = c0 + cc;
   bool live = (r < p.th) & (row < p.R) & (col < p.Wc);
+  if (second) live = live & (p.out_lo + row >= p.sib.lo) & (p.out_lo + row < p.sib.hi);
   const int cb = co0 + ((wave * TP) & 3) * 8;   // first channel of this wavefront's pieces
   f32x4 bias[NT][TP];
 #pragma unroll
   for (int a = 0; a < NT; ++a)
 #pragma unroll
     for (int i = 0; i < TP; ++i) bias[a][i] = f32x4{0.f, 0.f, 0.f, 0.f};
-  if (p.bias) {
+  if (bias_at) {
 #pragma unroll
     for (int a = 0; a < NT; ++a)
 #pragma unroll
       for (int i = 0; i < TP; ++i) {
         const int co = cb + a * 32 + i * 8 + half * 4;
-        bias[a][i] = *(const f32x4*)(p.bias + (co < p.C_out ? co : 0));
+        bias[a][i] = *(const f32x4*)(bias_at + (co < C_out ? co : 0));
       }
   }
   typedef unsigned raw_t __attribute__((ext_vector_type(sizeof(T))));   // four elements
   raw_t res[NT][TP];
   if constexpr (!POOL) {
-    if (p.res) {
+    if (p.res && !second) {
       const size_t ra = live ? ((size_t)(n * p.r_rows + p.out_lo + row - p.r_row0) * p.W_out + col) * p.C_out : 0;
 #pragma unroll
       for (int a = 0; a < NT; ++a)
@@ -280,7 +309,7 @@ __device__ __forceinline__ void patch_body(const PatchParams& p, const int bx, c
       live = live & ((lane & 3) == 0);
       ya = ((size_t)(n * p.y_rows + ((p.out_lo + row) >> 1) - p.y_row0) * p.W_out + (col >> 1)) * p.C_out;
     } else {
-      ya = ((size_t)(n * p.y_rows + p.out_lo + row - p.y_row0) * p.W_out + col) * p.C_out;
+      ya = ((size_t)(n * (second ? p.sib.y_rows : p.y_rows) + p.out_lo + row - (second ? p.sib.y_row0 : p.y_row0)) * p.W_out + col) * C_out;
     }
 #pragma unroll
     for (int i = 0; i < TP; ++i) {
@@ -298,9 +327,9 @@ __device__ __forceinline__ void patch_body(const PatchParams& p, const int bx, c
 #pragma unroll
       for (int i = 0; i < TP; ++i) {
         const int co = cb + a * 32 + i * 8 + half * 4;
-        if (live && co < p.C_out) {
-          *(f32x4*)((T*)p.y + ya + co) = sum[i];
-          if (p.y2) *(f32x4*)((T*)p.y2 + ya + co) = sum[i];
+        if (live && co < C_out) {
+          *(f32x4*)(y + ya + co) = sum[i];
+          if (y2) *(f32x4*)(y2 + ya + co) = sum[i];
         }
       }
     } else {
@@ -313,9 +342,9 @@ __device__ __forceinline__ void patch_body(const PatchParams& p, const int bx, c
       if constexpr (TP == 1) {
         const uint2 o = pack(0);
         const int co = cb + a * 32 + half * 4;
-        if (live && co < p.C_out) {
-          *(uint2*)((T*)p.y + ya + co) = o;
-          if (p.y2) *(uint2*)((T*)p.y2 + ya + co) = o;
+        if (live && co < C_out) {
+          *(uint2*)(y + ya + co) = o;
+          if (y2) *(uint2*)(y2 + ya + co) = o;
         }
       } else {
         // two pieces hold 16 channels of a pixel in two lanes, 4 + 4 interleaved: exchanged between
@@ -327,9 +356,9 @@ __device__ __forceinline__ void patch_body(const PatchParams& p, const int bx, c
           const auto s1 = __builtin_amdgcn_permlane32_swap(e.y, o.y, false, false);
           const u32x4 v = u32x4{(unsigned)s0[0], (unsigned)s1[0], (unsigned)s0[1], (unsigned)s1[1]};
           const int co = cb + a * 32 + i * 8 + half * 8;
-          if (live && co < p.C_out) {
-            *(u32x4*)((T*)p.y + ya + co) = v;
-            if (p.y2) *(u32x4*)((T*)p.y2 + ya + co) = v;
+          if (live && co < C_out) {
+            *(u32x4*)(y + ya + co) = v;
+            if (y2) *(u32x4*)(y2 + ya + co) = v;
           }
         }
       }
@@ -420,17 +449,23 @@ PatchChoice choose_patch(const OpLaunch* convs, const OpLaunch* pools, int n) {
   return best;
 }
 
+// sibs: per band the 1 x 1 convolution that the launch computes as well, or nullptr
 template <typename T, int BM, int BN>
-hipError_t launch_tile(const OpLaunch* convs, const OpLaunch* pools, int n, hipStream_t s, KernelEvents* ev) {
+hipError_t launch_tile(const OpLaunch* convs, const OpLaunch* pools, const OpLaunch* sibs, int n, hipStream_t s, KernelEvents* ev) {
   PatchParams ps[kMaxBatch];
   unsigned gx[kMaxBatch];
-  const unsigned gy = (unsigned)((convs[0].y.c + BN - 1) / BN);
-  if ((int)gy * BN > conv_cout_pad(convs[0].y.c)) return hipErrorInvalidValue;  // unguarded weight loads
+  const unsigned gy1 = (unsigned)((convs[0].y.c + BN - 1) / BN), gy2 = sibs ? (unsigned)((sibs[0].y.c + BN - 1) / BN) : 0, gy = gy1 + gy2;
+  if ((int)gy1 * BN > conv_cout_pad(convs[0].y.c)) return hipErrorInvalidValue;  // unguarded weight loads
+  if (sibs && (convs[0].sh != 2 || (int)gy2 * BN > conv_cout_pad(sibs[0].y.c))) return hipErrorInvalidValue;
   int m = 0;
   for (int b = 0; b < n; ++b) {
     const PatchWork w = patch_work(convs[b], pools ? &pools[b] : nullptr);
     if (w.R <= 0) continue;
     ps[m] = make_patch(convs[b], pools ? &pools[b] : nullptr, BM, patch_room(BM, convs[b].sh), gy, &gx[m]);
+    if (sibs) {
+      const OpLaunch& q = sibs[b];
+      ps[m].sib = Sibling{q.wd, q.y.ptr, q.bias, q.k_pad / (32 / (int)sizeof(T)), q.y.row0, q.y.rows, q.y.c, q.act, q.out_lo, q.out_hi, (int)gy1};
+    }
     const int room = patch_room(BM, convs[b].sh);
     if (ps[m].th < 1 || ps[m].ph_rows * ps[m].pitch > room || ps[m].th * ps[m].tw > BM) return hipErrorInvalidValue;
     ++m;
@@ -462,14 +497,25 @@ hipError_t launch_patch(const OpLaunch* convs, const OpLaunch* pools, int n, hip
   if (n < 1 || n > kMaxBatch) return hipErrorInvalidValue;
   const PatchChoice c = choose_patch(convs, pools, n);
   if (convs[0].dtype == LOP_BF16) {
-    if (c.bm == 128) return launch_tile<__bf16, 128, 64>(convs, pools, n, s, ev);
-    if (c.bm == 64) return launch_tile<__bf16, 64, 32>(convs, pools, n, s, ev);
-    if (c.bm == 32) return launch_tile<__bf16, 32, 32>(convs, pools, n, s, ev);
+    if (c.bm == 128) return launch_tile<__bf16, 128, 64>(convs, pools, nullptr, n, s, ev);
+    if (c.bm == 64) return launch_tile<__bf16, 64, 32>(convs, pools, nullptr, n, s, ev);
+    if (c.bm == 32) return launch_tile<__bf16, 32, 32>(convs, pools, nullptr, n, s, ev);
     return hipErrorInvalidValue;
   }
-  if (c.bm == 64) return launch_tile<float, 64, 32>(convs, pools, n, s, ev);
-  if (c.bm == 32) return launch_tile<float, 32, 32>(convs, pools, n, s, ev);
+  if (c.bm == 64) return launch_tile<float, 64, 32>(convs, pools, nullptr, n, s, ev);
+  if (c.bm == 32) return launch_tile<float, 32, 32>(convs, pools, nullptr, n, s, ev);
   return hipErrorInvalidValue;
+}
+
+// A 3 x 3 convolution of stride 2 and the 1 x 1 one beside it, where the former takes this kernel.
+bool patch_takes_sibling(const OpLaunch* convs, const OpLaunch* sibs, int n) {
+  if (n < 1 || n > kMaxBatch || convs[0].sh != 2 || !sibs[0].wd || sibs[0].y.c % (convs[0].dtype == LOP_BF16 ? 8 : 4) != 0) return false;
+  return choose_patch(convs, nullptr, n).bm == 32;
+}
+hipError_t launch_patch_siblings(const OpLaunch* convs, const OpLaunch* sibs, int n, hipStream_t s, KernelEvents* ev) {
+  if (!patch_takes_sibling(convs, sibs, n)) return hipErrorInvalidValue;
+  return convs[0].dtype == LOP_BF16 ? launch_tile<__bf16, 32, 32>(convs, nullptr, sibs, n, s, ev)
+                                    : launch_tile<float, 32, 32>(convs, nullptr, sibs, n, s, ev);
 }
 
 int patch_describe(const OpLaunch* convs, const OpLaunch* pools, int n, char* name, size_t size) {

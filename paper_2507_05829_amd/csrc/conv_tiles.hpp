@@ -15,6 +15,18 @@ namespace {
 
 constexpr unsigned kOutside = 0x80000000u;   // a byte offset past every slab: a load from there puts zeros into LDS
 
+// A 1 x 1 convolution of the same input with the same stride (a block's shortcut), computed by the channel tiles
+// of the launch from `first` on: its weights are the centre tap of a 3 x 3 filter.
+struct Sibling {
+  const void* wd;
+  void* y;
+  const float* bias;
+  int k_steps, y_row0, y_rows, C_out, act;
+  int lo, hi;      // its output rows, among those of the launch
+  int first;
+};
+constexpr int kNoSibling = 0x7fffffff;
+
 struct PatchParams {
   const void* x;
   void* y;
@@ -31,6 +43,7 @@ struct PatchParams {
   int th, tw, nty, ntx;              // tile of output pixels, tiles per image in either direction
   int pitch, ph_rows;                // pixel slots per row of the patch (S == 2: even columns, then odd), its rows
   FastDiv by_ntx, by_nty, by_tw, by_pitch, by_group;
+  Sibling sib;
 };
 static_assert(sizeof(Batch<PatchParams>) <= 4096, "the parameters of all bands of a launch travel as kernel arguments");
 
@@ -93,6 +106,7 @@ inline PatchParams make_patch(const OpLaunch& c, const OpLaunch* pool, int pixel
   p.by_tw = make_fastdiv(pool ? t.tw / 2 : t.tw);
   p.by_pitch = make_fastdiv(p.pitch);
   p.by_group = make_fastdiv(kGroupM * (int)gy);
+  p.sib = Sibling{nullptr, nullptr, nullptr, 0, 0, 0, 0, 0, 0, 0, kNoSibling};
   *tiles = (unsigned)t.tiles;
   return p;
 }

@@ -117,6 +117,14 @@ int walk_describe(const OpLaunch* convs, const OpLaunch* pools, int n, char* nam
 bool narrow_applies(const OpLaunch* Ls, int n);
 hipError_t launch_narrow(const OpLaunch* Ls, int n, hipStream_t stream, KernelEvents* ev);
 int narrow_describe(const OpLaunch* Ls, int n, char* name, size_t size);
+// A 3 x 3 convolution and a 1 x 1 one of the same input and stride (a block's shortcut) as one launch: whether a
+// group of bands takes it (both descriptors with slabs and rows) and the launch.
+bool patch_takes_sibling(const OpLaunch* convs, const OpLaunch* sibs, int n);
+hipError_t launch_patch_siblings(const OpLaunch* convs, const OpLaunch* sibs, int n, hipStream_t stream, KernelEvents* ev);
+bool narrow_takes_sibling(const OpLaunch* convs, const OpLaunch* sibs, int n);
+hipError_t launch_narrow_siblings(const OpLaunch* convs, const OpLaunch* sibs, int n, hipStream_t stream, KernelEvents* ev);
+bool siblings_apply(const OpLaunch* convs, const OpLaunch* sibs, int n);
+hipError_t launch_siblings(const OpLaunch* convs, const OpLaunch* sibs, int n, hipStream_t stream, KernelEvents* ev = nullptr);
 // The matrix-product kernel of 1 x 1 convolutions: whether a group of bands takes it, the launch and
 // its kernel name.
 bool gemm_applies(const OpLaunch* Ls, int n);

@@ -1072,6 +1072,20 @@ struct ChainScratch {
   ~ChainScratch() { P->arena_override = nullptr; P->ws_override = nullptr; }
 };
 
+// Whether layers l and l + 1 are a convolution and the 1 x 1 shortcut beside it, which a merged chain computes
+// in one launch where a kernel takes both (a launch more costs a chain 4 us, and the small
+// shortcut leaves most of the chip idle). The second one's output is then written while the first is computed, so
+// neither may read anything else: every buffer still needed then keeps its memory.
+bool siblings(const lop_plan_t* P, int l) {
+  const lop::Tables& t = P->t;
+  if (l + 2 >= t.n_layers()) return false;
+  const lop_layer_t &a = t.layers[l].d, &b = t.layers[l + 1].d;
+  if (a.op != LOP_CONV2D || b.op != LOP_CONV2D || a.input_from != b.input_from || a.kh != 3 || b.kh != 1) return false;
+  if (a.residual_from != LOP_NO_RESIDUAL || b.residual_from != LOP_NO_RESIDUAL || last_reader(P, l) <= l + 1) return false;
+  const Fusion& F = P->fuse_chain;
+  return !F.away[l] && !F.away[l + 1] && F.head[l] < 0 && F.head[l + 1] < 0 && !(P->flags & LOP_FLAG_NO_FUSE);
+}
+
 // The kernels of a chain whose launches are merged over the bands (kGrouped, kWhole), on one
 // stream, with the scratch set by the caller. y2: where the last launch also stores its rows.
 int enqueue_merged_kernels(lop_plan_t* P, const void* d_in, void* d_out, hipStream_t cs, void* y2) {
@@ -1086,14 +1100,35 @@ int enqueue_merged_kernels(lop_plan_t* P, const void* d_in, void* d_out, hipStre
     const ChainPass pass(P, i, std::min(P->images, n - i));
     void* const second = y2 ? (char*)y2 + i * out_bytes : nullptr;
     if (P->sched == ChainSched::kWhole) {
-      for (int l = 0; l < nl; ++l)
+      for (int l = 0; l < nl; ++l) {
+        if (siblings(P, l)) {
+          const lop::OpLaunch a = make_launch(P, whole, l, d_in, d_out), q = make_launch(P, whole, l + 1, d_in, d_out);
+          if (a.out_hi > a.out_lo && lop::siblings_apply(&a, &q, 1)) {
+            LOP_HIP(lop::launch_siblings(&a, &q, 1, cs));
+            ++l;
+            continue;
+          }
+        }
         LOP_HIP(launch_layer(P, P->fuse_chain, whole, l, d_in, d_out, cs, nullptr, l == nl - 1 ? second : nullptr));
+      }
       continue;
     }
-    for (int b = 0; b < nb; b += P->group)
-      for (int l = 0; l < nl; ++l)
-        LOP_HIP(launch_layer_batched(P, l, b, std::min(nb, b + P->group), d_in, d_out, cs, nullptr,
-                                     l == nl - 1 ? second : nullptr));
+    for (int b = 0; b < nb; b += P->group) {
+      const int end = std::min(nb, b + P->group);
+      for (int l = 0; l < nl; ++l) {
+        if (end - b <= lop::kMaxBandsPerLaunch && siblings(P, l)) {
+          std::vector<lop::OpLaunch> as, qs, none;
+          batched_group(P, l, b, end, d_in, d_out, nullptr, &as, &none);
+          batched_group(P, l + 1, b, end, d_in, d_out, nullptr, &qs, &none);
+          if ((int)as.size() == end - b && qs.size() == as.size() && lop::siblings_apply(as.data(), qs.data(), end - b)) {
+            LOP_HIP(lop::launch_siblings(as.data(), qs.data(), end - b, cs));
+            ++l;
+            continue;
+          }
+        }
+        LOP_HIP(launch_layer_batched(P, l, b, end, d_in, d_out, cs, nullptr, l == nl - 1 ? second : nullptr));
+      }
+    }
   }
   return LOP_OK;
 }

@@ -1435,6 +1435,40 @@ def test_walking_kernel(oracle, cfg):
             np.testing.assert_array_equal(dev, want_int)
 
 
+@pytest.mark.parametrize("cfg", [
+    # dtype, c_in, c_out, shape(n,h,w): a stride-2 block's convolution and shortcut in one launch
+    ("bf16", 64, 72, (1, 27, 45)),      # channels end inside a tile
+    ("bf16", 128, 256, (2, 13, 11)),    # two patches, batch 2
+    ("f32", 32, 64, (1, 61, 47)),
+    ("f32", 96, 40, (1, 45, 71)),       # three patches
+    ("f32", 128, 36, (1, 29, 9)),       # 16 x 16 tiles, half the wavefronts idle in the shortcut
+    ("f32", 256, 512, (1, 14, 14)),     # ... the large patch, more slots than compute units
+])
+def test_shortcut_beside_its_convolution(oracle, cfg):
+    """A 3 x 3 convolution of stride 2 and the 1 x 1 shortcut of the same input, which merged chains
+    compute in one launch: against the oracle and against separate launches, in one band, with all
+    bands in one launch and with shared rows; small integers bit for bit."""
+    dtype, c_in, c_out, shape = cfg
+    chain = workloads.Chain("block", (shape[0], c_in, shape[1], shape[2]), dtype, 3)
+    a = chain.add(workloads.CONV, c_in, c_in, 3, 1, 1, act="relu")
+    b = chain.add(workloads.CONV, c_in, c_out, 3, 2, 1, act="relu", input_from=a)
+    sc = chain.add(workloads.CONV, c_in, c_out, 1, 2, 0, act="none", input_from=a)
+    chain.add(workloads.CONV, c_out, c_out, 3, 1, 1, act="relu", input_from=b, residual_from=sc)
+    t = workloads.make_tensors(chain, zero_bias=False, seed=29)
+    want = oracle.run_chain(chain, t)
+    ti = workloads.small_int_tensors(chain, seed=3)
+    ti.weights = [w if w is None else np.sign(w) * (np.abs(w) > 1) * (np.arange(w.size).reshape(w.shape) % 11 == 0) for w in ti.weights]
+    want_int = oracle.run_chain(chain, ti)
+    exact = np.abs(want_int).max() <= (256 if dtype == "bf16" else 2 ** 24)
+    for bands, flags in ((1, 0), (3, 0), (3, lop.LOP_FLAG_REUSE), (3, lop.LOP_FLAG_NO_FUSE)):
+        dev, host = run_gpu(chain, t, n_bands=bands, flags=flags)
+        np.testing.assert_array_equal(dev, host)
+        assert rel_err(dev, want) <= TOL[dtype], (bands, flags)
+        if exact:
+            dev, _ = run_gpu(chain, ti, n_bands=bands, flags=flags)
+            np.testing.assert_array_equal(dev, want_int)
+
+
 NARROW_GRID = [
     # c_in, c_out, stride, shape(n,h,w), residual, the form expected in one band
     (128, 128, 1, (1, 9, 13), True, "<float, 5, 49152>"),        # slices of four and five steps
