@@ -678,7 +678,9 @@ int describe_layer_launch(const lop_plan_t* P, int band, int l, char* name, size
     convpool_launches(P, band, l, nullptr, nullptr, &conv, &pool);
     return lop::convpool_describe(conv, pool, name, size);
   }
-  return lop::mbconv_describe(describe_layer(P, l - 1), describe_layer(P, l), name, size);
+  lop::OpLaunch p = make_launch(P, band, l, nullptr, nullptr);
+  p.res = describe_layer(P, l).res;   // (a residual from the chain's input has no address here)
+  return lop::mbconv_describe(describe_layer(P, l - 1), p, name, size);
 }
 
 // Algorithmic work of that launch. A fused group: the three layers' operations on the rows

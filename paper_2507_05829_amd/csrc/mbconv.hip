@@ -5,7 +5,7 @@
 // row-wise ones, Eq. 1), so a tile of the block's output depends on a slightly larger tile of
 // its input only. Run layer by layer the expanded tensor (6x the channels) is written to HBM
 // and read back twice; here it never leaves the compute unit. A workgroup owns 8 x 16
-// output pixels and walks over the expanded channels in chunks of 32, all three operators on the
+// output pixels (16 x 16 in large launches of stride 1: see mb_rows) and walks over the expanded channels in chunks of 32, all three operators on the
 // matrix cores:
 //   expand   32 x 32 x 16 products, pixels as rows, so that a lane ends with four neighbouring pixels of
 //            one channel -> bias, activation, one rounding to bf16 -> LDS, channel by channel. Pixels
@@ -97,15 +97,16 @@ __device__ __forceinline__ u32x2 transposed_read(const unsigned char* at) {
   return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)at));
 }
 
-template <int S>
+template <int S, int ROWS>
 struct MbTile {
-  static constexpr int TH = 8, TW = 16;                  // output pixels of a workgroup
+  static constexpr int TH = ROWS, TW = 16;               // output pixels of a workgroup
   static constexpr int EH = (TH - 1) * S + 3;            // rows of expanded pixels it needs
   static constexpr int XQ = S == 1 ? 5 : 9;              // columns, in groups ("quads") of four
   static constexpr int NQ = EH * XQ;                     // quads, column of quads by column
   static constexpr int MT_E = (NQ + 7) / 8;              // expand MFMA tiles
   static constexpr int MPW = (MT_E + 3) / 4;             // ... per wavefront
-  static constexpr int OP = TH * TW;                     // = 4 MFMA tiles, one per wavefront
+  static constexpr int OP = TH * TW;
+  static constexpr int RG = TH / 8;                      // groups of 8 rows: MFMA tiles of the output per wavefront
   static constexpr int KS = S == 1 ? 2 : 3;              // quads of input columns under four outputs
   // Bytes of a channel in LDS: an odd multiple of 8, which with the order of rows and channels below
   // lets every half wavefront's access touch each bank once.
@@ -127,12 +128,12 @@ __host__ __device__ constexpr int channel_slot(int c) { return (c & 3) * 8 + (c 
 // Slot of the depthwise operator's block of lanes (lane / 4) and half of the channels.
 __host__ __device__ constexpr int dw_slot(int block, int half) { return 4 * (block & 7) + 2 * half + (block >> 3); }
 
-template <int S, bool RES>
+template <int S, bool RES, int ROWS>
 __device__ __forceinline__ void mbconv_body(const MbParams& p, int bid) {
-  typedef MbTile<S> G;
-  constexpr int TH = G::TH, TW = G::TW, EH = G::EH, XQ = G::XQ, NQ = G::NQ, MT_E = G::MT_E, MPW = G::MPW, KS = G::KS;
+  typedef MbTile<S, ROWS> G;
+  constexpr int TH = G::TH, TW = G::TW, EH = G::EH, XQ = G::XQ, NQ = G::NQ, MT_E = G::MT_E, MPW = G::MPW, KS = G::KS, RG = G::RG;
   constexpr int EPITCH = G::EPITCH, DPITCH = G::DPITCH;
-  static_assert(G::OP == 128, "one 32-pixel MFMA tile of the output per wavefront");
+  static_assert(TH == 8 || TH == 16, "groups of 8 rows");
   static_assert(NQ <= 256 && kMbMaxMid <= 256, "a thread per quad and per bias");
   __shared__ __attribute__((aligned(16))) unsigned char E_s[32 * EPITCH];   // [slot][quad]
   __shared__ __attribute__((aligned(16))) unsigned char D_s[32 * DPITCH];   // [slot][column of quads][row]
@@ -169,7 +170,7 @@ __device__ __forceinline__ void mbconv_body(const MbParams& p, int bid) {
 
   // weights of a chunk: expand, the depthwise bands of this wavefront's 16 channels, project, all in the order of the
   // lanes (an access of four lanes to one 64-byte line each costs the vector cache four times as much); each part is fetched for the next chunk when this one is done with it
-  const int chalf = wave & 1, rgroup = wave >> 1;          // depthwise: 16 channels x 4 output rows x 16 columns each
+  const int chalf = wave & 1, rgroup = wave >> 1;          // depthwise: 16 channels x 4 rows of every 8 x 16 columns each
   u32x4 we[2], wp[2];
   s16x4 wd[3 * KS];
   const u32x4* const we_at = (const u32x4*)p.we + lane;
@@ -212,9 +213,11 @@ __device__ __forceinline__ void mbconv_body(const MbParams& p, int bid) {
   };
   barrier();
 
-  f32x16 acc;
+  f32x16 acc[RG];
 #pragma unroll
-  for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+  for (int g = 0; g < RG; ++g)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[g][i] = 0.f;
 
   // expand: stores to the slot of channel px; depthwise: row lane % 4 of this wavefront's four, channel slot of its block of
   // lanes; project: a transposing read gives the lane four slots of its pixel (16 lanes read 4 slots x 4 quads)
@@ -222,7 +225,7 @@ __device__ __forceinline__ void mbconv_body(const MbParams& p, int bid) {
   const int dslot = dw_slot(lane >> 2, chalf), drow = rgroup * 4 + (lane & 3);
   const unsigned char* const ewin = E_s + dslot * EPITCH + drow * 8;
   unsigned char* const dout = D_s + dslot * DPITCH + drow * 8;
-  unsigned char* const dtr = D_s + (((lane & 15) >> 2) * 8 + kg) * DPITCH + (wave * 8 + ((lane >> 4) & 1) * 4 + (lane & 3)) * 8;
+  unsigned char* const dtr = D_s + (((lane & 15) >> 2) * 8 + kg) * DPITCH + (wave * RG * 8 + ((lane >> 4) & 1) * 4 + (lane & 3)) * 8;
 
   for (int c = 0; c < p.nch; ++c) {
     const int cn = min(c + 1, p.nch - 1);
@@ -259,80 +262,89 @@ __device__ __forceinline__ void mbconv_body(const MbParams& p, int bid) {
     {
       const float db = bias_s[1][c * 32 + slot_channel(dslot)];
       const f32x4 dbias = f32x4{db, db, db, db};
-      f32x4 d[4];
 #pragma unroll
-      for (int a = 0; a < 3; ++a) {
-        s16x4 col[XQ];
+      for (int r = 0; r < RG; ++r) {
+        f32x4 d[4];
 #pragma unroll
-        for (int x = 0; x < XQ; ++x) col[x] = *(const s16x4*)(ewin + (x * EH + G::tap_row(a)) * 8);
+        for (int a = 0; a < 3; ++a) {
+          s16x4 col[XQ];
 #pragma unroll
-        for (int s = 0; s < KS; ++s)
+          for (int x = 0; x < XQ; ++x) col[x] = *(const s16x4*)(ewin + (x * EH + G::tap_row(a) + r * 8) * 8);
 #pragma unroll
-          for (int b = 0; b < 4; ++b)
-            d[b] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(wd[a * KS + s], col[b * S + s], a + s ? d[b] : dbias, 0, 0, 0);
-      }
-      fetch_depthwise(cn);
+          for (int s = 0; s < KS; ++s)
 #pragma unroll
-      for (int b = 0; b < 4; ++b) {
-        float v[4];
+            for (int b = 0; b < 4; ++b)
+              d[b] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(wd[a * KS + s], col[b * S + s], a + s ? d[b] : dbias, 0, 0, 0);
+        }
+        if (r == RG - 1) fetch_depthwise(cn);
 #pragma unroll
-        for (int k = 0; k < 4; ++k) v[k] = clamp_act(d[b][k], p.cd);
-        *(u32x2*)(dout + b * 64) = pack4(v);
+        for (int b = 0; b < 4; ++b) {
+          float v[4];
+#pragma unroll
+          for (int k = 0; k < 4; ++k) v[k] = clamp_act(d[b][k], p.cd);
+          *(u32x2*)(dout + (b * TH + r * 8) * 8) = pack4(v);
+        }
       }
     }
     barrier();
 
     // ---- project: this chunk's 32 channels are the reduction axis
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const u32x2 lo = transposed_read(dtr + (4 * h + 0) * DPITCH);
-      const u32x2 hi = transposed_read(dtr + (4 * h + 2) * DPITCH);
-      acc = mma_bf16(wp[h], u32x4{lo.x, lo.y, hi.x, hi.y}, acc);
-    }
+    for (int g = 0; g < RG; ++g)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const u32x2 lo = transposed_read(dtr + (4 * h + 0) * DPITCH + g * 64);
+        const u32x2 hi = transposed_read(dtr + (4 * h + 2) * DPITCH + g * 64);
+        acc[g] = mma_bf16(wp[h], u32x4{lo.x, lo.y, hi.x, hi.y}, acc[g]);
+      }
     fetch_project(cn);
   }
 
   // ---- bias, residual, activation, the one rounding. A lane has channels 8 g + 4 kg + {0..3} of its
   // pixel; two groups are exchanged between the lane halves so that each has 8 consecutive ones.
-  const int oh = oh0 + (px >> 2), ow = ow0 + wave * 4 + (px & 3);
-  const bool live = oh < p.out_lo + p.R && ow < p.W_out;
-  const size_t yoff = ((size_t)(n * p.y_rows + oh - p.y_row0) * p.W_out + ow) * kMbC;
-  const size_t roff = RES ? ((size_t)(n * p.r_rows + oh - p.r_row0) * p.W_out + ow) * kMbC : 0;
-  u32x2 o[4];
 #pragma unroll
-  for (int g = 0; g < 4; ++g) {
-    const int co = g * 8 + kg * 4;
-    float v[4] = {acc[g * 4 + 0], acc[g * 4 + 1], acc[g * 4 + 2], acc[g * 4 + 3]};
-    if (p.bp) {
-      const float4 b4 = *(const float4*)(p.bp + co);
-      v[0] += b4.x; v[1] += b4.y; v[2] += b4.z; v[3] += b4.w;
+  for (int t = 0; t < RG; ++t) {
+    const int tile = wave * RG + t;   // 8 rows x 4 columns
+    const int oh = oh0 + tile % RG * 8 + (px >> 2), ow = ow0 + tile / RG * 4 + (px & 3);
+    const bool live = oh < p.out_lo + p.R && ow < p.W_out;
+    const size_t yoff = ((size_t)(n * p.y_rows + oh - p.y_row0) * p.W_out + ow) * kMbC;
+    const size_t roff = RES ? ((size_t)(n * p.r_rows + oh - p.r_row0) * p.W_out + ow) * kMbC : 0;
+    u32x2 o[4];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const int co = g * 8 + kg * 4;
+      float v[4] = {acc[t][g * 4 + 0], acc[t][g * 4 + 1], acc[t][g * 4 + 2], acc[t][g * 4 + 3]};
+      if (p.bp) {
+        const float4 b4 = *(const float4*)(p.bp + co);
+        v[0] += b4.x; v[1] += b4.y; v[2] += b4.z; v[3] += b4.w;
+      }
+      if (RES && live) {
+        float r[4];
+        unpack4(*(const u32x2*)(p.res + roff + co), r);
+        v[0] += r[0]; v[1] += r[1]; v[2] += r[2]; v[3] += r[3];
+      }
+#pragma unroll
+      for (int k = 0; k < 4; ++k) v[k] = clamp_act(v[k], p.cp);
+      o[g] = pack4(v);
     }
-    if (RES && live) {
-      float r[4];
-      unpack4(*(const u32x2*)(p.res + roff + co), r);
-      v[0] += r[0]; v[1] += r[1]; v[2] += r[2]; v[3] += r[3];
+#pragma unroll
+    for (int g = 0; g < 4; g += 2) {
+      const auto s0 = __builtin_amdgcn_permlane32_swap(o[g].x, o[g + 1].x, false, false);
+      const auto s1 = __builtin_amdgcn_permlane32_swap(o[g].y, o[g + 1].y, false, false);
+      if (live) *(u32x4*)(p.y + yoff + g * 8 + kg * 8) = u32x4{(unsigned)s0[0], (unsigned)s1[0], (unsigned)s0[1], (unsigned)s1[1]};
     }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) v[k] = clamp_act(v[k], p.cp);
-    o[g] = pack4(v);
-  }
-#pragma unroll
-  for (int g = 0; g < 4; g += 2) {
-    const auto s0 = __builtin_amdgcn_permlane32_swap(o[g].x, o[g + 1].x, false, false);
-    const auto s1 = __builtin_amdgcn_permlane32_swap(o[g].y, o[g + 1].y, false, false);
-    if (live) *(u32x4*)(p.y + yoff + g * 8 + kg * 8) = u32x4{(unsigned)s0[0], (unsigned)s1[0], (unsigned)s0[1], (unsigned)s1[1]};
   }
 }
 
-template <int S, bool RES>
-__global__ __launch_bounds__(256, S == 1 ? 4 : 3) void mbconv_kernel(const MbParams p) {
-  mbconv_body<S, RES>(p, blockIdx.x);
+template <int S, bool RES, int ROWS>
+__global__ __launch_bounds__(256, S == 1 && ROWS == 8 ? 4 : 3) void mbconv_kernel(const MbParams p) {
+  mbconv_body<S, RES, ROWS>(p, blockIdx.x);
 }
 // The same for several bands of one block in one grid (band b owns blocks first[b] .. first[b + 1]).
-template <int S, bool RES>
-__global__ __launch_bounds__(256, S == 1 ? 4 : 3) void mbconv_kernel_bands(const Batch<MbParams> t) {
+template <int S, bool RES, int ROWS>
+__global__ __launch_bounds__(256, S == 1 && ROWS == 8 ? 4 : 3) void mbconv_kernel_bands(const Batch<MbParams> t) {
   const int b = batch_find(t, blockIdx.x);
-  mbconv_body<S, RES>(t.p[b], blockIdx.x - t.first[b]);
+  mbconv_body<S, RES, ROWS>(t.p[b], blockIdx.x - t.first[b]);
 }
 
 bool is_pointwise(const OpLaunch& L) {
@@ -374,14 +386,30 @@ bool mbconv_applies(const OpLaunch& e, const OpLaunch& d, const OpLaunch& p) {
   return e.res.ptr == nullptr && d.res.ptr == nullptr;
 }
 
+// Rows of a workgroup's tile: 16 (stride 1) where that does less work - such a tile costs 1.75 of an 8-row one, having
+// a smaller halo, no idle wavefront in the expand part and half the weights to read per pixel - and leaves two
+// workgroups per compute unit, 8 otherwise.
+static int mb_rows(const OpLaunch& d, const OpLaunch* ps, int n) {
+  if (d.sh != 1) return 8;
+  long tiles16 = 0, tiles8 = 0;
+  for (int b = 0; b < n; ++b) {
+    const int R = ps[b].out_hi - ps[b].out_lo;
+    if (R <= 0) continue;
+    const long row = (long)((ps[b].y.w + 15) / 16) * ps[b].x.n;
+    tiles16 += (R + 15) / 16 * row;
+    tiles8 += (R + 7) / 8 * row;
+  }
+  return tiles16 >= 512 && 7 * tiles16 < 4 * tiles8 ? 16 : 8;
+}
+
 int mbconv_describe(const OpLaunch& d, const OpLaunch& p, char* name, size_t size) {
   if (name && size)
-    snprintf(name, size, "mbconv_kernel<%d, %s>", d.sh, p.res.ptr ? "true" : "false");
+    snprintf(name, size, "mbconv_kernel<%d, %s, %d>", d.sh, p.res.ptr ? "true" : "false", mb_rows(d, &p, 1));
   return 1;
 }
 
 namespace {
-MbParams make_mbconv(const OpLaunch& e, const OpLaunch& d, const OpLaunch& p) {
+MbParams make_mbconv(const OpLaunch& e, const OpLaunch& d, const OpLaunch& p, int th) {
   MbParams q;
   q.x = (const __bf16*)e.x.ptr; q.y = (__bf16*)p.y.ptr; q.res = (const __bf16*)p.res.ptr;
   q.we = e.wd; q.be = e.bias;
@@ -394,7 +422,7 @@ MbParams make_mbconv(const OpLaunch& e, const OpLaunch& d, const OpLaunch& p) {
   q.C_mid = e.y.c; q.nch = e.y.c / 32;
   q.ce = make_clamp(e.act); q.cd = make_clamp(d.act); q.cp = make_clamp(p.act);
   q.out_lo = p.out_lo; q.R = p.out_hi - p.out_lo; q.N = e.x.n;
-  const int tw = MbTile<1>::TW, th = MbTile<1>::TH;
+  const int tw = MbTile<1, 8>::TW;
   q.tiles_x = (q.W_out + tw - 1) / tw;
   q.tiles_y = (q.R + th - 1) / th;
   return q;
@@ -410,19 +438,24 @@ hipError_t launch_mbconv_bands(const OpLaunch* es, const OpLaunch& d, const OpLa
   MbParams qs[kMaxBatch];
   unsigned gx[kMaxBatch];
   int m = 0;
+  const int rows = mb_rows(d, ps, n);
   for (int b = 0; b < n; ++b) {
     if (!mbconv_applies(es[b], d, ps[b])) return hipErrorInvalidValue;
-    qs[m] = make_mbconv(es[b], d, ps[b]);
+    qs[m] = make_mbconv(es[b], d, ps[b], rows);
     if (qs[m].R <= 0 || qs[m].N <= 0) continue;
     gx[m] = (unsigned)(qs[m].tiles_x * qs[m].tiles_y * qs[m].N);
     ++m;
   }
   if (m == 0) return hipSuccess;
-  if (d.sh == 1)
-    return qs[0].res ? launch_group(mbconv_kernel<1, true>, mbconv_kernel_bands<1, true>, qs, m, gx, 1, 1, dim3(256), stream, ev)
-                     : launch_group(mbconv_kernel<1, false>, mbconv_kernel_bands<1, false>, qs, m, gx, 1, 1, dim3(256), stream, ev);
-  return qs[0].res ? launch_group(mbconv_kernel<2, true>, mbconv_kernel_bands<2, true>, qs, m, gx, 1, 1, dim3(256), stream, ev)
-                   : launch_group(mbconv_kernel<2, false>, mbconv_kernel_bands<2, false>, qs, m, gx, 1, 1, dim3(256), stream, ev);
+  const dim3 block(256);
+  if (d.sh == 2)
+    return qs[0].res ? launch_group(mbconv_kernel<2, true, 8>, mbconv_kernel_bands<2, true, 8>, qs, m, gx, 1, 1, block, stream, ev)
+                     : launch_group(mbconv_kernel<2, false, 8>, mbconv_kernel_bands<2, false, 8>, qs, m, gx, 1, 1, block, stream, ev);
+  if (rows == 16)
+    return qs[0].res ? launch_group(mbconv_kernel<1, true, 16>, mbconv_kernel_bands<1, true, 16>, qs, m, gx, 1, 1, block, stream, ev)
+                     : launch_group(mbconv_kernel<1, false, 16>, mbconv_kernel_bands<1, false, 16>, qs, m, gx, 1, 1, block, stream, ev);
+  return qs[0].res ? launch_group(mbconv_kernel<1, true, 8>, mbconv_kernel_bands<1, true, 8>, qs, m, gx, 1, 1, block, stream, ev)
+                   : launch_group(mbconv_kernel<1, false, 8>, mbconv_kernel_bands<1, false, 8>, qs, m, gx, 1, 1, block, stream, ev);
 }
 
 }  // namespace lop

@@ -446,6 +446,25 @@ def test_inverted_residual_block_one_launch(oracle, cfg, reuse):
     assert rel_err(dev, unfused) <= 2.0 ** -7
 
 
+@pytest.mark.parametrize("cfg", [
+    dict(stride=1, residual=True, c_mid=64, shape=(2, 250, 250), n_bands=1),      # ragged tiles in both directions
+    dict(stride=1, residual=False, c_mid=96, shape=(3, 173, 245), n_bands=3),
+])
+def test_inverted_residual_block_on_tall_tiles(oracle, cfg):
+    """The fused launch's tiles of 16 rows (checked by name) against the oracle, in one band, with all bands in
+    one launch and with shared rows."""
+    chain = _mbconv_block(**cfg)
+    t = workloads.make_tensors(chain, zero_bias=False, seed=19)
+    plan = lop.Plan(chain, t, 1)
+    assert plan.layer_kernel(0, 3)[0].endswith(", 16>")
+    plan.destroy()
+    want = oracle.run_chain(chain, t)
+    for bands, flags in ((1, 0), (3, 0), (3, lop.LOP_FLAG_REUSE)):
+        dev, host = run_gpu(chain, t, n_bands=bands, flags=flags)
+        np.testing.assert_array_equal(dev, host)
+        assert rel_err(dev, want) <= TOL["bf16"], (bands, flags)
+
+
 def test_inverted_residual_block_small_integers_bit_exact(oracle):
     chain = _mbconv_block(stride=1, residual=True, c_mid=64, shape=(1, 12, 18), acts=("relu6", "relu6", "none"))
     t = workloads.small_int_tensors(chain, seed=5)
