@@ -200,7 +200,8 @@ LOP_API int lop_run_band(lop_plan_t* plan, int band, const void* d_in, void* d_o
  * (LOP_FLAG_REUSE, chains without halos, one band) as one launch per layer over all their rows.
  * That holds for chains whose layer outputs fit LOP_STATIC_SCRATCH_BYTES together, in equal passes
  * over the images of a batch (independent bands whose operators all have launches for several bands:
- * then over groups of bands) if not all at once; a merged chain runs on one lane and consecutive
+ * then over groups of bands; chains of row-wise operators: over the rows of groups of bands) if not all at
+ * once; a merged chain runs on one lane and consecutive
  * calls rotate over the lanes. Larger chains run band by band on the lanes, band b's copy
  * overlapping the kernels of the bands after it (Sec. IV-B). Either way the rows computed are
  * those of lop_run_band, which runs a single band, and the results agree with it up to the order

@@ -5,6 +5,7 @@
 #include <cstdint>
 
 #include <algorithm>
+#include <climits>
 #include <chrono>
 #include <cstring>
 #include <mutex>
@@ -261,11 +262,14 @@ int upload_weights(lop_plan_t* P) {
 }
 
 // The images a merged chain's launches work on while it is enqueued: they lie from image `first` on
-// in the caller's tensors, and from the buffers' beginning in the arena.
+// in the caller's tensors, and from the buffers' beginning in the arena. rows: the pass's rows, where
+// those are a part of the chain's.
 struct ChainPass {
   lop_plan_t* P;
-  ChainPass(lop_plan_t* plan, int first, int images) : P(plan) { P->pass_first = first; P->pass_images = images; }
-  ~ChainPass() { P->pass_first = 0; P->pass_images = 0; }
+  ChainPass(lop_plan_t* plan, int first, int images, lop_rows_t rows = {0, 0}) : P(plan) {
+    P->pass_first = first; P->pass_images = images; P->pass_rows = rows;
+  }
+  ~ChainPass() { P->pass_first = 0; P->pass_images = 0; P->pass_rows = {0, 0}; }
 };
 
 // Last launch (by the index of the layer it ends with) that reads layer l's output, under either
@@ -311,6 +315,23 @@ size_t place_slabs(const lop_plan_t* P, const std::vector<size_t>& size, std::ve
   return worst;
 }
 
+// Whether every layer's output row depends on that row of its input only (chains of row-wise operators).
+bool keeps_to_rows(const lop_plan_t* P) {
+  for (const lop::LayerInfo& L : P->t.layers)
+    if (L.d.op == LOP_MAXPOOL2D || L.d.kh != 1 || L.d.sh != 1 || L.d.ph != 0) return false;
+  return true;
+}
+// The result rows of bands [first, last).
+lop_rows_t pass_rows(const lop_plan_t* P, int first, int last) {
+  lop_rows_t r = {0, 0};
+  for (int b = first; b < last; ++b) {
+    const lop_rows_t q = P->t.bands[b].need[P->t.n_layers()];
+    if (q.hi <= q.lo) continue;
+    r = r.hi <= r.lo ? q : lop_rows_t{std::min(r.lo, q.lo), std::max(r.hi, q.hi)};
+  }
+  return r;
+}
+
 // What a merged chain (kGrouped, kWhole) keeps between launches fits this: images of a batch, and
 // then bands, are dealt to passes of equal size, as few as do. It is the size of the static array,
 // so that lop_run_chain_static, which has no more than that, runs the launches lop_run_chain does;
@@ -332,9 +353,9 @@ void size_scratch(lop_plan_t* P) {
   };
   auto band_rows = [&](int b, int l) { return t.bands[b].need[l + 1].hi - t.bands[b].need[l + 1].lo; };
   std::vector<size_t> size(nl, 0);
-  // full-height buffers of a whole chain
-  auto place_whole = [&](int images, std::vector<size_t>* off) {
-    for (int l = 0; l + 1 < nl; ++l) size[l] = rows_bytes(images, l, t.layers[l].h_out);
+  // buffers of a whole chain, of at most `rows` rows
+  auto place_whole = [&](int images, int rows, std::vector<size_t>* off) {
+    for (int l = 0; l + 1 < nl; ++l) size[l] = rows_bytes(images, l, std::min(rows, t.layers[l].h_out));
     return place_slabs(P, size, off);
   };
   // the slabs of bands [b0, b1) at once: one block per layer, the bands' slabs one behind the other in it
@@ -374,7 +395,7 @@ void size_scratch(lop_plan_t* P) {
     int images = 0;
     for (int passes = 1; P->sched == ChainSched::kPerBand && images != 1; ++passes) {
       images = (n + passes - 1) / passes;
-      merged = whole ? place_whole(images, &P->chain_off[nb]) : place_groups(images, nb, &P->chain_off);
+      merged = whole ? place_whole(images, INT_MAX, &P->chain_off[nb]) : place_groups(images, nb, &P->chain_off);
       if (merged <= kMergeMaxBytes) P->sched = whole ? ChainSched::kWhole : ChainSched::kGrouped;
     }
     int per = nb;
@@ -388,6 +409,18 @@ void size_scratch(lop_plan_t* P) {
       per = (nb + groups - 1) / groups;
       merged = place_groups(1, per, &P->chain_off);
       if (merged <= kMergeMaxBytes) P->sched = ChainSched::kGrouped;
+    }
+    // a chain whose layers keep to their rows: passes over the rows of as many bands as fit, if two do (the launches of
+    // one band at a time are better off on four lanes: alone 1 150 against 1 390 us on 65 536 x 1024 -> 4096 -> 1024).
+    // Band by band the launches leave their last rounds of tiles to compete: 16 425 x 816 -> 2552 -> 816
+    // in five bands 271 -> 176 us a chain, 32 768 x 1024 -> 4096 -> 1024 in eight 785 -> 552.
+    for (int passes = 2; whole && keeps_to_rows(P) && P->sched == ChainSched::kPerBand; ++passes) {
+      per = (nb + passes - 1) / passes;
+      if (per < 2) break;
+      int rows = 0;
+      for (int b = 0; b < nb; b += per) { const lop_rows_t r = pass_rows(P, b, std::min(nb, b + per)); rows = std::max(rows, r.hi - r.lo); }
+      merged = place_whole(images, rows, &P->chain_off[nb]);
+      if (merged <= kMergeMaxBytes) P->sched = ChainSched::kWhole;
     }
     if (P->sched != ChainSched::kPerBand) { P->group = per; P->images = images; }
     else merged = 0;
@@ -426,8 +459,12 @@ void size_workspace(lop_plan_t* P) {
       for (int b = 0; b < nb; ++b)
         if (P->t.bands[b].compute[l].hi > P->t.bands[b].compute[l].lo) add({make_launch(P, b, l, nullptr, nullptr)});
     if (!alone(P->fuse_chain)) continue;
+    if (P->sched == ChainSched::kWhole)
+      for (int b = 0; b < nb; b += P->group) {
+        const ChainPass pass(P, 0, P->images, P->group < nb ? pass_rows(P, b, std::min(nb, b + P->group)) : lop_rows_t{0, 0});
+        add({make_launch(P, nb, l, nullptr, nullptr)});
+      }
     const ChainPass pass(P, 0, P->images);
-    if (P->sched == ChainSched::kWhole) add({make_launch(P, nb, l, nullptr, nullptr)});
     if (P->sched == ChainSched::kGrouped) {  // a launch for several bands keeps all their partial sums at once
       std::vector<lop::OpLaunch> group;
       for (int b = 0; b <= nb; ++b) {
@@ -475,7 +512,9 @@ lop::Slab slab_of(const lop_plan_t* P, int band, int tensor, const void* d_in, v
       // (no arena yet while the plan is being sized, and none at all in a plan-only plan)
       char* const arena = (char*)P->arena_of(band);
       s.ptr = arena ? arena + (P->pass_images ? P->chain_off : P->slab_off)[band][tensor] : nullptr;
-      if (t.reuse) {
+      if (P->pass_rows.hi > P->pass_rows.lo) {
+        s.row0 = P->pass_rows.lo; s.rows = P->pass_rows.hi - P->pass_rows.lo;
+      } else if (t.reuse) {
         s.row0 = 0; s.rows = s.h;
       } else {
         const lop_rows_t r = t.bands[band].need[tensor + 1];
@@ -512,8 +551,9 @@ lop::OpLaunch make_launch(const lop_plan_t* P, int band, int l, const void* d_in
   o.kh = L.d.kh; o.kw = L.d.kw; o.sh = L.d.sh; o.sw = L.d.sw;
   o.ph = L.d.ph; o.pw = L.d.pw; o.dh = L.d.dh; o.dw = L.d.dw;
   o.act = L.d.act;
-  o.out_lo = t.bands[band].compute[l].lo;
-  o.out_hi = t.bands[band].compute[l].hi;
+  const lop_rows_t rows = P->pass_rows.hi > P->pass_rows.lo ? P->pass_rows : t.bands[band].compute[l];
+  o.out_lo = rows.lo;
+  o.out_hi = rows.hi;
   o.ws = P->ws_of(band);
   return o;
 }
@@ -1099,22 +1139,28 @@ int enqueue_merged_kernels(lop_plan_t* P, const void* d_in, void* d_out, hipStre
   const int nb = P->t.n_bands, n = P->t.in.n;
   const size_t out_bytes = (size_t)P->t.layers.back().h_out * P->t.row_elems(nl - 1) * P->t.esz();   // of one image
   for (int i = 0; i < n; i += P->images) {
-    const ChainPass pass(P, i, std::min(P->images, n - i));
     void* const second = y2 ? (char*)y2 + i * out_bytes : nullptr;
+    const int images = std::min(P->images, n - i);
     if (P->sched == ChainSched::kWhole) {
-      for (int l = 0; l < nl; ++l) {
-        if (siblings(P, l)) {
-          const lop::OpLaunch a = make_launch(P, whole, l, d_in, d_out), q = make_launch(P, whole, l + 1, d_in, d_out);
-          if (a.out_hi > a.out_lo && lop::siblings_apply(&a, &q, 1)) {
-            LOP_HIP(lop::launch_siblings(&a, &q, 1, cs));
-            ++l;
-            continue;
+      for (int b = 0; b < nb; b += P->group) {
+        const lop_rows_t rows = P->group < nb ? pass_rows(P, b, std::min(nb, b + P->group)) : lop_rows_t{0, 0};
+        if (P->group < nb && rows.hi <= rows.lo) continue;
+        const ChainPass pass(P, i, images, rows);
+        for (int l = 0; l < nl; ++l) {
+          if (siblings(P, l)) {
+            const lop::OpLaunch a = make_launch(P, whole, l, d_in, d_out), q = make_launch(P, whole, l + 1, d_in, d_out);
+            if (a.out_hi > a.out_lo && lop::siblings_apply(&a, &q, 1)) {
+              LOP_HIP(lop::launch_siblings(&a, &q, 1, cs));
+              ++l;
+              continue;
+            }
           }
+          LOP_HIP(launch_layer(P, P->fuse_chain, whole, l, d_in, d_out, cs, nullptr, l == nl - 1 ? second : nullptr));
         }
-        LOP_HIP(launch_layer(P, P->fuse_chain, whole, l, d_in, d_out, cs, nullptr, l == nl - 1 ? second : nullptr));
       }
       continue;
     }
+    const ChainPass pass(P, i, images);
     for (int b = 0; b < nb; b += P->group) {
       const int end = std::min(nb, b + P->group);
       for (int l = 0; l < nl; ++l) {

@@ -63,6 +63,7 @@ struct lop_plan_s {
   int group = 0;   // kGrouped: bands per group; the groups of a chain run one after another
   int images = 0;  // kGrouped, kWhole: images per pass; the passes of a chain run one after another
   int pass_first = 0, pass_images = 0;  // while a pass is enqueued: its images (0: all, not in a pass)
+  lop_rows_t pass_rows = {0, 0};        // ... and, of a chain whose layers keep to their rows, its rows (empty: all)
   std::vector<float*> d_bias;  // per layer bias (device) or nullptr
   std::vector<int> k_pad;
   std::vector<char> has_wd, has_wd16;  // which of the two operand-order packings a layer gets

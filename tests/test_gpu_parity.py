@@ -872,6 +872,26 @@ def test_rowwise_full_size_sampled_rows(oracle):
     assert rel_err(dev[rows], want) <= TOL["bf16"]
 
 
+@pytest.mark.parametrize("dtype,bands,flags", [("bf16", 5, 0), ("bf16", 7, lop.LOP_FLAG_REUSE | lop.LOP_FLAG_GRAPH), ("f32", 8, lop.LOP_FLAG_GRAPH)])
+def test_rowwise_chain_in_passes_over_its_rows(oracle, dtype, bands, flags):
+    """A chain of matrix products too large for one merged pass: passes of several bands' rows, the
+    last one shorter. Sampled rows (the borders of bands among them) against the oracle, all rows
+    against the bands one by one."""
+    m, k, hidden = (20011, 64, 1704) if dtype == "bf16" else (12011, 64, 1704)
+    chain = workloads.RowChain("rows", m, k, dtype, bands)
+    chain.add(hidden, "relu").add(k, "none", residual_from=-1)
+    t = workloads.make_row_tensors(chain, zero_bias=False, seed=31)
+    dev, host, _ = _run_rows(chain, t, flags=flags)
+    np.testing.assert_array_equal(dev, host)
+    one_by_one, _, _ = _run_rows(chain, t, flags=flags, order=list(range(bands)))
+    assert rel_err(dev, one_by_one) <= TOL[dtype]
+    rows = np.unique(np.concatenate([np.random.Generator(np.random.PCG64(1)).choice(m, 48, replace=False), [0, m - 1]] +
+                                    [[m * b // bands - 1, m * b // bands, m * b // bands + 1] for b in range(1, bands)]))
+    sub = workloads.RowChain("sub", len(rows), k, dtype, 1, chain.layers)
+    want = oracle.run_row_chain(sub, workloads.Tensors(np.ascontiguousarray(t.x[rows]), t.weights, t.biases))
+    assert rel_err(dev[rows], want) <= TOL[dtype]
+
+
 # ---- seeded random shapes: every kernel choice the library can make, against the oracle ----
 
 _SKIP_RANDOM_F32 = (
