@@ -1549,7 +1549,7 @@ size_t assign_workspace(ConvParams* ps, int n, int splits, int kc_per_split, flo
 }
 
 template <typename T>
-hipError_t launch_typed(ConvParams* ps, int n, int dtype, float* ws, hipStream_t s, KernelEvents* ev) {
+hipError_t launch_typed(ConvParams* ps, int n, int dtype, float* ws, size_t ws_bytes, hipStream_t s, KernelEvents* ev) {
   constexpr int KE = 16 / (int)sizeof(T);
   const bool vec_a = ps[0].C_in % KE == 0;
   // the kernels address a slab with 32-bit byte offsets
@@ -1578,14 +1578,12 @@ hipError_t launch_typed(ConvParams* ps, int n, int dtype, float* ws, hipStream_t
     }
   }
   if (d.wk) {
-    if (d.z > 1 && !ws) return hipErrorInvalidValue;
-    assign_workspace(ps, n, d.z, d.per_z, ws);
+    if (assign_workspace(ps, n, d.z, d.per_z, ws) > (ws ? ws_bytes : 0)) return hipErrorInvalidValue;
     const hipError_t e = launch_direct_any<T>(ps, n, d, s, ev);
     if (e != hipSuccess || !ps[0].ws) return e;
     return launch_finish<T>(ps, n, s, ev);
   }
-  if (c.splits > 1 && !ws) return hipErrorInvalidValue;
-  assign_workspace(ps, n, c.splits, c.kc_per_split, ws);
+  if (assign_workspace(ps, n, c.splits, c.kc_per_split, ws) > (ws ? ws_bytes : 0)) return hipErrorInvalidValue;
   if (c.shape == S256x256) {
     if constexpr (sizeof(T) == 2) {
       if (n != 1) return hipErrorInvalidValue;   // (chosen for single launches of at least 256 tiles only)
@@ -1672,8 +1670,8 @@ hipError_t launch_conv_igemm_bands(const OpLaunch* Ls, int n, hipStream_t stream
   if (narrow_applies(Ls, n)) return launch_narrow(Ls, n, stream, ev);
   if (patch_applies(Ls, nullptr, n)) return launch_patch(Ls, nullptr, n, stream, ev);
   if (gemm_applies(Ls, n)) return launch_gemm(Ls, n, stream, ev);
-  return Ls[0].dtype == LOP_BF16 ? launch_typed<__bf16>(ps, m, Ls[0].dtype, (float*)Ls[0].ws, stream, ev)
-                                 : launch_typed<float>(ps, m, Ls[0].dtype, (float*)Ls[0].ws, stream, ev);
+  return Ls[0].dtype == LOP_BF16 ? launch_typed<__bf16>(ps, m, Ls[0].dtype, (float*)Ls[0].ws, Ls[0].ws_bytes, stream, ev)
+                                 : launch_typed<float>(ps, m, Ls[0].dtype, (float*)Ls[0].ws, Ls[0].ws_bytes, stream, ev);
 }
 
 bool siblings_apply(const OpLaunch* convs, const OpLaunch* sibs, int n) {

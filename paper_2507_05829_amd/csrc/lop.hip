@@ -443,37 +443,65 @@ void size_scratch(lop_plan_t* P) {
 
 lop::OpLaunch make_launch(const lop_plan_t* P, int band, int l, const void* d_in, void* d_out);
 
-// Largest split-K workspace any launch of the plan needs (the launch descriptors only need
-// sizes here, not the scratch addresses).
-void size_workspace(lop_plan_t* P) {
-  P->conv_ws_bytes = 0;
-  const int nb = P->t.n_bands;
+// Split-K workspace of the launch that computes layer l (a dense convolution of its own) for these bands.
+size_t group_workspace(const std::vector<lop::OpLaunch>& group) {
+  if (group.empty() || lop::pointwise_applies(group[0])) return 0;
+  return lop::conv_workspace_bytes_bands(group.data(), (int)group.size());
+}
+bool launches_alone(const lop_plan_t* P, const Fusion& F, int l) {
+  return P->t.layers[l].d.op == LOP_CONV2D && !F.away[l] && F.head[l] < 0;
+}
+
+// Largest split-K workspace of the launches that compute one band (the launch descriptors only
+// need sizes here, not the scratch addresses).
+size_t band_workspace(const lop_plan_t* P) {
+  size_t most = 0;
   for (int l = 0; l < P->t.n_layers(); ++l) {
-    if (P->t.layers[l].d.op != LOP_CONV2D) continue;
-    auto alone = [&](const Fusion& F) { return !F.away[l] && F.head[l] < 0; };
-    auto add = [&](const std::vector<lop::OpLaunch>& group) {
-      if (group.empty() || lop::pointwise_applies(group[0])) return;
-      P->conv_ws_bytes = std::max(lop::conv_workspace_bytes_bands(group.data(), (int)group.size()), P->conv_ws_bytes);
-    };
-    if (alone(P->fuse_band))
-      for (int b = 0; b < nb; ++b)
-        if (P->t.bands[b].compute[l].hi > P->t.bands[b].compute[l].lo) add({make_launch(P, b, l, nullptr, nullptr)});
-    if (!alone(P->fuse_chain)) continue;
-    if (P->sched == ChainSched::kWhole)
-      for (int b = 0; b < nb; b += P->group) {
-        const ChainPass pass(P, 0, P->images, P->group < nb ? pass_rows(P, b, std::min(nb, b + P->group)) : lop_rows_t{0, 0});
-        add({make_launch(P, nb, l, nullptr, nullptr)});
-      }
-    const ChainPass pass(P, 0, P->images);
-    if (P->sched == ChainSched::kGrouped) {  // a launch for several bands keeps all their partial sums at once
-      std::vector<lop::OpLaunch> group;
-      for (int b = 0; b <= nb; ++b) {
-        if (b == nb || b % P->group == 0 || (int)group.size() == lop::kMaxBandsPerLaunch) { add(group); group.clear(); }
-        if (b < nb && P->t.bands[b].compute[l].hi > P->t.bands[b].compute[l].lo)
-          group.push_back(make_launch(P, b, l, nullptr, nullptr));
-      }
+    if (!launches_alone(P, P->fuse_band, l) && !(P->batched && launches_alone(P, P->fuse_chain, l))) continue;
+    for (int b = 0; b < P->t.n_bands; ++b) {
+      const lop_rows_t r = P->t.bands[b].compute[l];
+      if (r.hi > r.lo) most = std::max(most, group_workspace({make_launch(P, b, l, nullptr, nullptr)}));
     }
   }
+  return most;
+}
+
+// ... and of the launches of a merged chain (kGrouped, kWhole), over the passes that enqueue_merged_kernels
+// makes. A last pass over fewer images is looked at by itself: fewer pixels can mean more slices, or a kernel
+// that cuts the reduction where the larger launch has one that does not.
+size_t merged_workspace(lop_plan_t* P) {
+  const int nb = P->t.n_bands, rest = P->t.in.n % P->images;
+  size_t most = 0;
+  auto pass = [&](int images, int first, int last) {
+    const bool whole = P->sched == ChainSched::kWhole;
+    const lop_rows_t rows = whole && P->group < nb ? pass_rows(P, first, last) : lop_rows_t{0, 0};
+    if (whole && P->group < nb && rows.hi <= rows.lo) return;
+    const ChainPass sized(P, 0, images, rows);
+    std::vector<lop::OpLaunch> group;
+    for (int l = 0; l < P->t.n_layers(); ++l) {
+      if (!launches_alone(P, P->fuse_chain, l)) continue;
+      if (whole) {
+        most = std::max(most, group_workspace({make_launch(P, P->t.whole(), l, nullptr, nullptr)}));
+        continue;
+      }
+      for (int b = first; b < last; b += lop::kMaxBandsPerLaunch) {   // (a launch keeps all its bands' partial sums at once)
+        group.clear();
+        for (int k = b; k < std::min(last, b + lop::kMaxBandsPerLaunch); ++k)
+          if (P->t.bands[k].compute[l].hi > P->t.bands[k].compute[l].lo) group.push_back(make_launch(P, k, l, nullptr, nullptr));
+        most = std::max(most, group_workspace(group));
+      }
+    }
+  };
+  for (int b = 0; b < nb; b += P->group) {
+    pass(P->images, b, std::min(nb, b + P->group));
+    if (rest) pass(rest, b, std::min(nb, b + P->group));
+  }
+  return most;
+}
+
+void size_workspace(lop_plan_t* P) {
+  P->conv_ws_bytes = band_workspace(P);
+  if (P->sched != ChainSched::kPerBand) P->conv_ws_bytes = std::max(P->conv_ws_bytes, merged_workspace(P));
 }
 
 // Whether every launch of the plan has a kernel form that takes several bands.
@@ -555,6 +583,7 @@ lop::OpLaunch make_launch(const lop_plan_t* P, int band, int l, const void* d_in
   o.out_lo = rows.lo;
   o.out_hi = rows.hi;
   o.ws = P->ws_of(band);
+  o.ws_bytes = P->conv_ws_bytes;
   return o;
 }
 

@@ -187,7 +187,7 @@ extern "C" int lop_run_two_party(lop_plan_t* P, const void* d_in, void* d_out, c
   }
   for (int d = 0; d < 2; ++d) {
     if (ws_bytes) LOP_HIP(lop::dev_alloc(&S.party[d].ws, ws_bytes));
-    for (auto& o : launch[d]) o.ws = S.party[d].ws;
+    for (auto& o : launch[d]) { o.ws = S.party[d].ws; o.ws_bytes = ws_bytes; }
   }
   S.party[0].held[0].push_back(Piece{0, rows_of(-1)});  // the client holds the whole input
 

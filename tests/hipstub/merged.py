@@ -1,0 +1,113 @@
+"""Checks of merged chains (the launches of all bands, or of several images' bands, in one) against
+the stand-in HIP runtime: what a merged chain asks of its scratch and of the launchers, compared
+with the same plan's bands run one by one. Run as `python merged.py <stub dir> <check>` with the
+AddressSanitizer runtime preloaded (see build_stub.py). Kernels do nothing here, so tensors are
+addresses only.
+"""
+import os
+import sys
+import types
+
+stub_dir, check = sys.argv[1], sys.argv[2]
+HERE = os.path.dirname(os.path.abspath(__file__))
+sys.path[:0] = [stub_dir, os.path.dirname(os.path.dirname(HERE))]
+sys.modules["torch"] = types.ModuleType("torch")   # the binding imports it only for its runtime
+
+import numpy as np  # noqa: E402
+
+import workloads  # noqa: E402
+from paper_2507_05829_amd import lop  # noqa: E402
+
+assert lop.LIB_PATH.startswith(stub_dir), lop.LIB_PATH
+_room = np.zeros(64, np.uint8)
+TENSOR = (_room.ctypes.data + 15) & ~15
+
+
+def conv_chain(dtype, shape, bands, layers):
+    """layers: (c_out, k, stride, dilation), padded to keep the size at stride 1."""
+    chain = workloads.Chain("merged", shape, dtype, bands)
+    c = shape[1]
+    for c_out, k, s, d in layers:
+        chain.add(workloads.CONV, c, c_out, k, s, d * (k // 2), d, "relu")
+        c = c_out
+    return chain
+
+
+def shrinking(dtype, shape, bands, c0, s1, s2, c1, k=5):
+    """Three convolutions at growing stride and two with a large filter and few pixels behind them."""
+    return conv_chain(dtype, shape, bands, [(c0, 3, 1, 1), (c0, 3, 1, 1), (128, 3, s1, 1), (c1, 3, s2, 1),
+                                            (c1, k, 1, 1), (c1, k, 1, 1)])
+
+
+class ZeroWeights:
+    """Weights of a chain's shapes without values (one block of zeros serves every layer)."""
+
+    def __init__(self, chain):
+        shapes = [(L.c_out, L.c_in // L.groups) + tuple(L.k) for L in chain.layers]
+        block = np.zeros(max(int(np.prod(s)) for s in shapes), np.float32)
+        self.weights = [block[:int(np.prod(s))].reshape(s) if L.has_weight else None
+                        for s, L in zip(shapes, chain.layers)]
+        self.biases = [None] * len(shapes)
+
+
+def make(chain, flags):
+    return lop.Plan(chain, ZeroWeights(chain), None, flags | lop.LOP_FLAG_LANES(1))
+
+
+def status(call):
+    try:
+        call()
+    except lop.LopError as e:
+        return e.code
+    return 0
+
+
+def run_both_ways(chain, flags):
+    """Status of the whole chain, and of its bands run one by one."""
+    plan = make(chain, flags)
+    whole = status(lambda: plan.run_chain(TENSOR, TENSOR))
+    bands = [status(lambda: plan.run_band(b, TENSOR, TENSOR)) for b in range(plan.n_bands)]
+    plan.synchronize()
+    plan.destroy()
+    return whole, min(bands)
+
+
+def random_chain(rng):
+    dtype = str(rng.choice(["f32", "bf16"]))
+    reuse = bool(rng.random() < 0.4)
+    c0, c1 = int(rng.choice([12, 16, 24, 32, 40, 64])), int(rng.choice([72, 128, 192, 256]))
+    n, bands = int(rng.choice([1, 2, 3, 5, 7, 8])), int(rng.integers(1, 8))
+    h, w = int(rng.integers(48, 400)), int(rng.integers(48, 400))
+    layers = [(c0, 3, 1, 1)]
+    for _ in range(int(rng.integers(1, 5))):
+        layers.append((int(rng.choice([c0, c1, 128])), int(rng.choice([1, 3, 3, 5, 7])), int(rng.choice([1, 2, 2, 4])),
+                       int(rng.choice([1, 1, 2]))))
+    layers.append((c1, int(rng.choice([5, 7])), 1, 1))
+    return conv_chain(dtype, (n, int(rng.choice([3, 16, 24])), h, w), bands, layers), lop.LOP_FLAG_REUSE if reuse else 0
+
+
+def workspace():
+    """The partial sums of every launch a chain makes fit the workspace its plan holds: also those of
+    a last pass over fewer images, which can be cut into more slices than the passes before it."""
+    named = [("bf16", (3, 16, 240, 409), 5, 0, 32, 2, 4, 384, 5), ("f32", (8, 16, 119, 113), 5, 0, 64, 2, 4, 512, 5),
+             ("f32", (5, 16, 336, 315), 5, lop.LOP_FLAG_REUSE, 16, 4, 4, 256, 7),
+             ("bf16", (9, 16, 372, 406), 2, 0, 32, 2, 4, 256, 5)]
+    bad = []
+    for dtype, shape, bands, flags, *rest in named:
+        got = run_both_ways(shrinking(dtype, shape, bands, *rest), flags)
+        if got != (0, 0):
+            bad.append((dtype, shape, got))
+    rng = np.random.default_rng(77)
+    for i in range(120):
+        chain, flags = random_chain(rng)
+        got = run_both_ways(chain, flags)
+        if got[0] != got[1]:
+            bad.append((i, chain, flags, got))
+    return bad
+
+
+bad = {"workspace": workspace}[check]()
+for b in bad:
+    print("FAILED", b, flush=True)
+print("CHECK %s" % ("FAILED" if bad else "OK"), flush=True)
+sys.exit(1 if bad else 0)

@@ -1383,6 +1383,21 @@ def test_merged_chain_agrees_with_its_bands(oracle, name, kw, flags, graph):
         plan.destroy()
 
 
+@pytest.mark.parametrize("shape,bands", [((9, 16, 213, 236), 1), ((7, 16, 254, 246), 3)])
+def test_last_pass_over_fewer_images(oracle, shape, bands):
+    """A batch that does not divide into passes, and behind it a layer of few pixels and a long
+    reduction: the last pass cuts that reduction into more slices than the passes before it."""
+    chain = workloads.Chain("passes", shape, "f32", bands)
+    for c_in, c_out, k, s, d in ((16, 16, 3, 1, 1), (16, 16, 3, 1, 1), (16, 256, 3, 4, 1), (256, 256, 5, 4, 2)):
+        chain.add(workloads.CONV, c_in, c_out, k, s, d * (k // 2), d, "relu")
+    t = workloads.make_tensors(chain, zero_bias=False)
+    want = oracle.run_chain(chain, t)
+    for flags in (0, lop.LOP_FLAG_POISON_SCRATCH):
+        dev, host = run_gpu(chain, t, None, True, flags)
+        assert rel_err(dev, want) <= TOL["f32"]
+        np.testing.assert_array_equal(host, dev)
+
+
 PATCH_GRID = [
     # dtype, c_in, c_out, stride, pooled, shape(n,h,w), residual, the tile expected
     ("bf16", 128, 128, 1, False, (2, 97, 211), True, "<__bf16, 128, 64, 2, false, 1>"),   # ragged in both directions, batch 2
