@@ -1434,6 +1434,10 @@ constexpr int kStages = 3;      // steps of global loads kept in flight
 // holds 256 of them at a time against 512 of the smaller tile, so the last, partly filled round
 // of workgroups weighs more. With t the time a compute unit needs for its two concurrent
 // 128 x 128 tiles, a round of the big tile (four tile areas) takes 4 / 2 / 1.2 = 5/3 t.
+// The rule holds for launches of several bands, by the pixels of all of them: their form of this tile
+// spills 16 registers (parameters it reads by the band's number), and a chain of two layers still takes
+// 103 us with it against 106 with 128 x 128 tiles (24 -> 256 channels on 512 x 512 pixels in eight bands),
+// 132 against 136 (40 -> 192 in four), 118 against 121 (64 -> 256, 5 x 5, on 320 x 320).
 bool big_tile_pays(long blocks256, long blocks128) {
   const long rounds256 = (blocks256 + kComputeUnits - 1) / kComputeUnits;
   const long rounds128 = (blocks128 + 2 * kComputeUnits - 1) / (2 * kComputeUnits);
@@ -1505,7 +1509,7 @@ hipError_t launch_finish(const ConvParams* ps, int n, hipStream_t s, KernelEvent
   return launch_group(splitk_finish_kernel<T>, splitk_finish_kernel_bands<T>, ps, n, gx, 1, 1, dim3(256), s, ev);
 }
 
-template <typename T, int BM, int BN, int WM, int WN>
+template <typename T, int BM, int BN, int WM, int WN, int BKB = kBKB>
 hipError_t launch_shape(const ConvParams* ps_in, int n, bool vec_a, hipStream_t s, KernelEvents* ev) {
   if (n < 1 || n > kMaxBatch) return hipErrorInvalidValue;
   const ConvParams& p = ps_in[0];
@@ -1517,13 +1521,15 @@ hipError_t launch_shape(const ConvParams* ps_in, int n, bool vec_a, hipStream_t 
   const dim3 block(64 * WM * WN);
   // weight loads are unguarded: the channel tiles must end inside the padded packing
   if ((int)gy * BN > conv_cout_pad(p.C_out)) return hipErrorInvalidValue;
-  const hipError_t e =
-      vec_a ? launch_group(conv_igemm_kernel<T, BM, BN, WM, WN, kBKB, kStages, true>,
-                           conv_igemm_kernel_bands<T, BM, BN, WM, WN, kBKB, kStages, true>, ps, n, gx, gy,
-                           (unsigned)p.splits, block, s, ev)
-            : launch_group(conv_igemm_kernel<T, BM, BN, WM, WN, kBKB, kStages, false>,
-                           conv_igemm_kernel_bands<T, BM, BN, WM, WN, kBKB, kStages, false>, ps, n, gx, gy,
-                           (unsigned)p.splits, block, s, ev);
+  hipError_t e;
+  if (vec_a) {
+    e = launch_group(conv_igemm_kernel<T, BM, BN, WM, WN, BKB, kStages, true>,
+                     conv_igemm_kernel_bands<T, BM, BN, WM, WN, BKB, kStages, true>, ps, n, gx, gy, (unsigned)p.splits, block, s, ev);
+  } else {
+    if constexpr (BKB != kBKB) return hipErrorInvalidValue;   // (the widest tile is chosen for whole vectors only)
+    else e = launch_group(conv_igemm_kernel<T, BM, BN, WM, WN, BKB, kStages, false>,
+                          conv_igemm_kernel_bands<T, BM, BN, WM, WN, BKB, kStages, false>, ps, n, gx, gy, (unsigned)p.splits, block, s, ev);
+  }
   if (e != hipSuccess || !p.ws) return e;
   return launch_finish<T>(ps, n, s, ev);
 }
@@ -1585,14 +1591,7 @@ hipError_t launch_typed(ConvParams* ps, int n, int dtype, float* ws, size_t ws_b
   }
   if (assign_workspace(ps, n, c.splits, c.kc_per_split, ws) > (ws ? ws_bytes : 0)) return hipErrorInvalidValue;
   if (c.shape == S256x256) {
-    if constexpr (sizeof(T) == 2) {
-      if (n != 1) return hipErrorInvalidValue;   // (chosen for single launches of at least 256 tiles only)
-      dim3 grid((ps[0].M + 255) / 256, (ps[0].C_out + 255) / 256, 1);
-      ConvParams p;
-      with_tile_walk(ps, 1, grid.y, &p);
-      if ((int)grid.y * 256 > conv_cout_pad(p.C_out)) return hipErrorInvalidValue;
-      return launch_kernel(conv_igemm_kernel<T, 256, 256, 2, 4, kBigBKB, kStages, true>, grid, dim3(512), s, ev, p);
-    }
+    if constexpr (sizeof(T) == 2) return launch_shape<T, 256, 256, 2, 4, kBigBKB>(ps, n, vec_a, s, ev);
     return hipErrorInvalidValue;
   }
   switch (c.shape) {

@@ -106,7 +106,22 @@ def workspace():
     return bad
 
 
-bad = {"workspace": workspace}[check]()
+def wide_tiles():
+    """Bands that together are large enough for the widest tile, in a layer that only the tiled kernel takes
+    (channel counts that are no multiple of 32, filters of 5 x 5, dilation)."""
+    bad = []
+    for shape, bands, layers in (((1, 24, 512, 512), 8, [(24, 3, 1, 1), (256, 3, 1, 1)]),
+                                 ((1, 40, 512, 512), 4, [(40, 3, 1, 1), (192, 3, 1, 1)]),
+                                 ((1, 64, 320, 320), 4, [(64, 3, 1, 1), (256, 5, 1, 1)]),
+                                 ((2, 256, 224, 224), 4, [(256, 3, 1, 1), (256, 3, 1, 2)])):
+        for flags in (0, lop.LOP_FLAG_GRAPH, lop.LOP_FLAG_REUSE, lop.LOP_FLAG_BATCH_BANDS):
+            got = run_both_ways(conv_chain("bf16", shape, bands, layers), flags)
+            if got != (0, 0):
+                bad.append((shape, layers, flags, got))
+    return bad
+
+
+bad = {"workspace": workspace, "wide_tiles": wide_tiles}[check]()
 for b in bad:
     print("FAILED", b, flush=True)
 print("CHECK %s" % ("FAILED" if bad else "OK"), flush=True)

@@ -1261,6 +1261,32 @@ def test_big_tile_conv3x3_with_residual(oracle):
     assert rel_err(dev, want) <= TOL["bf16"]
 
 
+def test_big_tile_over_several_bands(oracle):
+    """The 256 x 256 tile in launches of three bands: pixels and channels that end inside a tile, a
+    residual, captured and replayed."""
+    chain = workloads.Chain("bands256", (1, 24, 255, 257), "bf16", 3)
+    chain.add(workloads.CONV, 24, 136, 3, 1, 1, 1, "relu")
+    chain.add(workloads.CONV, 136, 136, 3, 1, 1, 1, "relu6", residual_from=0)
+    t = workloads.make_tensors(chain, zero_bias=False)
+    want = oracle.run_chain(chain, t)
+    dev, host = run_gpu(chain, t)
+    assert rel_err(dev, want) <= TOL["bf16"]
+    np.testing.assert_array_equal(host, dev)
+    again, _, names = _run_batched(chain, t, graph=1)
+    assert names[1][0].startswith("conv_igemm_kernel_bands<__bf16, 256, 256,"), names
+    np.testing.assert_array_equal(again, dev)
+    plan = lop.Plan(chain, t)
+    try:
+        d_in, d_out = to_device_nhwc(t.x, "bf16"), empty_out(plan.out_shape(), "bf16")
+        for b in (2, 0, 1):
+            plan.run_band(b, d_in, d_out)
+        plan.synchronize()
+        check_margins(d_out)
+        assert rel_err(to_nchw(d_out), want) <= TOL["bf16"]
+    finally:
+        plan.destroy()
+
+
 def test_measured_ceilings_are_below_the_published_peaks():
     """The copy and the MFMA-only loops behind the bench's `measured_peak`: each lands between a
     fraction of the published peak and the peak itself (8 TB/s, 2.5 PFLOP/s bf16, 157.3 TFLOP/s
