@@ -198,7 +198,8 @@ LOP_API int lop_run_band(lop_plan_t* plan, int band, const void* d_in, void* d_o
  * merged (operation batching, Sec. IV-D): bands that recompute halo rows run as one launch per
  * layer that computes each band's rows on that band's slabs; bands that compute no row twice
  * (LOP_FLAG_REUSE, chains without halos, one band) as one launch per layer over all their rows.
- * That holds for chains whose layer outputs fit LOP_STATIC_SCRATCH_BYTES together, in equal passes
+ * That holds for chains whose scratch (the layer outputs that are live together and the split-K
+ * workspace of the merged launches) fits LOP_STATIC_SCRATCH_BYTES, in equal passes
  * over the images of a batch (independent bands whose operators all have launches for several bands:
  * then over groups of bands; chains of row-wise operators: over the rows of groups of bands) if not all at
  * once; a merged chain runs on one lane and consecutive

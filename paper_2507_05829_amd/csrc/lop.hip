@@ -332,115 +332,6 @@ lop_rows_t pass_rows(const lop_plan_t* P, int first, int last) {
   return r;
 }
 
-// What a merged chain (kGrouped, kWhole) keeps between launches fits this: images of a batch, and
-// then bands, are dealt to passes of equal size, as few as do. It is the size of the static array,
-// so that lop_run_chain_static, which has no more than that, runs the launches lop_run_chain does;
-// and it is a quarter of the 256 MB Infinity Cache, so that four chains in flight keep their
-// intermediate rows on the chip. A chain too large even for one image (or one band of one image)
-// runs band by band: its launches are long enough by themselves.
-constexpr size_t kMergeMaxBytes = LOP_STATIC_SCRATCH_BYTES;
-// A chain of row-wise operators has no halo, and callers that stream matrix rows run its bands one
-// by one: below this many rows its chain runs the bands' own launches (same sums in the same
-// order as lop_run_band).
-constexpr int kMergeMinRows = 2048;
-
-void size_scratch(lop_plan_t* P) {
-  const lop::Tables& t = P->t;
-  const int nl = t.n_layers(), nb = t.n_bands, n = t.in.n;
-  auto kept = [&](int l) { return !P->fuse_band.away[l] || !P->fuse_chain.away[l]; };
-  auto rows_bytes = [&](int images, int l, int rows) {
-    return rows > 0 && kept(l) ? align_up((size_t)images * rows * t.row_elems(l) * t.esz(), 256) : (size_t)0;
-  };
-  auto band_rows = [&](int b, int l) { return t.bands[b].need[l + 1].hi - t.bands[b].need[l + 1].lo; };
-  std::vector<size_t> size(nl, 0);
-  // buffers of a whole chain, of at most `rows` rows
-  auto place_whole = [&](int images, int rows, std::vector<size_t>* off) {
-    for (int l = 0; l + 1 < nl; ++l) size[l] = rows_bytes(images, l, std::min(rows, t.layers[l].h_out));
-    return place_slabs(P, size, off);
-  };
-  // the slabs of bands [b0, b1) at once: one block per layer, the bands' slabs one behind the other in it
-  auto place_bands = [&](int images, int b0, int b1, std::vector<std::vector<size_t>>* off) {
-    for (int l = 0; l + 1 < nl; ++l) {
-      size[l] = 0;
-      for (int b = b0; b < b1; ++b) size[l] += rows_bytes(images, l, band_rows(b, l));
-    }
-    std::vector<size_t> block(nl, 0);
-    const size_t bytes = place_slabs(P, size, &block);
-    for (int l = 0; l + 1 < nl; ++l) {
-      size_t at = block[l];
-      for (int b = b0; b < b1; ++b) {
-        (*off)[b][l] = at;
-        at += rows_bytes(images, l, band_rows(b, l));
-      }
-    }
-    return bytes;
-  };
-  auto place_groups = [&](int images, int per, std::vector<std::vector<size_t>>* off) {
-    size_t most = 0;
-    for (int b = 0; b < nb; b += per) most = std::max(most, place_bands(images, b, std::min(nb, b + per), off));
-    return most;
-  };
-
-  P->chain_off.assign(nb + 1, std::vector<size_t>(nl, 0));
-  P->sched = ChainSched::kPerBand;
-  P->group = nb;
-  P->images = n;
-  size_t merged = 0;
-  const bool rows_only = t.in.w == 1 && n * t.in.h < kMergeMinRows;
-  if (P->batched) {
-    P->sched = ChainSched::kGrouped;
-    merged = place_groups(n, nb, &P->chain_off);
-  } else if (!(P->flags & LOP_FLAG_PLAN_ONLY) && !(rows_only && nb > 1)) {
-    const bool whole = t.disjoint();
-    int images = 0;
-    for (int passes = 1; P->sched == ChainSched::kPerBand && images != 1; ++passes) {
-      images = (n + passes - 1) / passes;
-      merged = whole ? place_whole(images, INT_MAX, &P->chain_off[nb]) : place_groups(images, nb, &P->chain_off);
-      if (merged <= kMergeMaxBytes) P->sched = whole ? ChainSched::kWhole : ChainSched::kGrouped;
-    }
-    int per = nb;
-    // A pass over few rows whose launches take one band each is a crowd of small launches on one lane: eight bands
-    // and eight images of the inverted-residual chain layer by layer took 3.3 ms that way, band by band 2.2.
-    bool all = true;
-    for (int l = 0; l < nl; ++l)
-      all = all && (P->fuse_chain.away[l] || P->fuse_chain.head[l] >= 0 || lop::op_batchable(lop::describe_layer(P, l)));
-    if (!whole && !all && images != n) P->sched = ChainSched::kPerBand;
-    for (int groups = 2; !whole && all && P->sched == ChainSched::kPerBand && per != 1; ++groups) {
-      per = (nb + groups - 1) / groups;
-      merged = place_groups(1, per, &P->chain_off);
-      if (merged <= kMergeMaxBytes) P->sched = ChainSched::kGrouped;
-    }
-    // a chain whose layers keep to their rows: passes over the rows of as many bands as fit, if two do (the launches of
-    // one band at a time are better off on four lanes: alone 1 150 against 1 390 us on 65 536 x 1024 -> 4096 -> 1024).
-    // Band by band the launches leave their last rounds of tiles to compete: 16 425 x 816 -> 2552 -> 816
-    // in five bands 271 -> 176 us a chain, 32 768 x 1024 -> 4096 -> 1024 in eight 785 -> 552.
-    for (int passes = 2; whole && keeps_to_rows(P) && P->sched == ChainSched::kPerBand; ++passes) {
-      per = (nb + passes - 1) / passes;
-      if (per < 2) break;
-      int rows = 0;
-      for (int b = 0; b < nb; b += per) { const lop_rows_t r = pass_rows(P, b, std::min(nb, b + per)); rows = std::max(rows, r.hi - r.lo); }
-      merged = place_whole(images, rows, &P->chain_off[nb]);
-      if (merged <= kMergeMaxBytes) P->sched = ChainSched::kWhole;
-    }
-    if (P->sched != ChainSched::kPerBand) { P->group = per; P->images = images; }
-    else merged = 0;
-  }
-
-  // bands that run one by one: in reuse mode on one full-height buffer per layer (rows at their
-  // absolute position), kept from band to band
-  P->slab_off.assign(nb + 1, std::vector<size_t>(nl, 0));   // (descriptors of the whole chain are made outside of a pass, too)
-  size_t single = 0;
-  if (t.reuse) {
-    for (int l = 0; l + 1 < nl; ++l) {
-      for (int b = 0; b < nb; ++b) P->slab_off[b][l] = single;
-      single += rows_bytes(n, l, t.layers[l].h_out);
-    }
-  } else {
-    single = place_groups(n, 1, &P->slab_off);
-  }
-  P->arena_bytes = std::max(single, merged);
-}
-
 lop::OpLaunch make_launch(const lop_plan_t* P, int band, int l, const void* d_in, void* d_out);
 
 // Split-K workspace of the launch that computes layer l (a dense convolution of its own) for these bands.
@@ -499,9 +390,127 @@ size_t merged_workspace(lop_plan_t* P) {
   return most;
 }
 
-void size_workspace(lop_plan_t* P) {
+// The scratch of a merged chain (kGrouped, kWhole), what it keeps between launches and the largest workspace
+// of a launch, fits this: images of a batch, and then bands, are dealt to passes of equal size, as few as
+// do. It is the size of the static array, so that lop_run_chain_static, which has no more than that, runs
+// the launches lop_run_chain does and takes every plan whose bands fit there one by one;
+// and it is a quarter of the 256 MB Infinity Cache, so that four chains in flight keep their
+// intermediate rows on the chip. A chain too large even for one image (or one band of one image)
+// runs band by band: its launches are long enough by themselves.
+constexpr size_t kMergeMaxBytes = LOP_STATIC_SCRATCH_BYTES;
+// A chain of row-wise operators has no halo, and callers that stream matrix rows run its bands one
+// by one: below this many rows its chain runs the bands' own launches (same sums in the same
+// order as lop_run_band).
+constexpr int kMergeMinRows = 2048;
+
+void size_scratch(lop_plan_t* P) {
+  const lop::Tables& t = P->t;
+  const int nl = t.n_layers(), nb = t.n_bands, n = t.in.n;
+  // (a buffer in the bands' own slabs, and one of a merged chain, for the layers that store their rows there; the
+  // measurement aids of a plan with batched launches run those layer by layer on the bands' slabs)
+  auto band_keeps = [&](int l) { return !P->fuse_band.away[l] || (P->batched && !P->fuse_chain.away[l]); };
+  auto chain_keeps = [&](int l) { return !P->fuse_chain.away[l]; };
+  auto rows_bytes = [&](int images, int l, int rows) {
+    return rows > 0 ? align_up((size_t)images * rows * t.row_elems(l) * t.esz(), 256) : (size_t)0;
+  };
+  auto band_rows = [&](int b, int l) { return t.bands[b].need[l + 1].hi - t.bands[b].need[l + 1].lo; };
+  std::vector<size_t> size(nl, 0);
+  // buffers of a whole chain, of at most `rows` rows
+  auto place_whole = [&](int images, int rows) {
+    for (int l = 0; l + 1 < nl; ++l) size[l] = chain_keeps(l) ? rows_bytes(images, l, std::min(rows, t.layers[l].h_out)) : 0;
+    return place_slabs(P, size, &P->chain_off[nb]);
+  };
+  // the slabs of bands [b0, b1) at once: one block per layer, the bands' slabs one behind the other in it
+  auto place_bands = [&](int images, int b0, int b1, auto keeps, std::vector<std::vector<size_t>>* off) {
+    for (int l = 0; l + 1 < nl; ++l) {
+      size[l] = 0;
+      for (int b = b0; b < b1 && keeps(l); ++b) size[l] += rows_bytes(images, l, band_rows(b, l));
+    }
+    std::vector<size_t> block(nl, 0);
+    const size_t bytes = place_slabs(P, size, &block);
+    for (int l = 0; l + 1 < nl; ++l) {
+      size_t at = block[l];
+      for (int b = b0; b < b1 && keeps(l); ++b) {
+        (*off)[b][l] = at;
+        at += rows_bytes(images, l, band_rows(b, l));
+      }
+    }
+    return bytes;
+  };
+  auto place_groups = [&](int images, int per, auto keeps, std::vector<std::vector<size_t>>* off) {
+    size_t most = 0;
+    for (int b = 0; b < nb; b += per) most = std::max(most, place_bands(images, b, std::min(nb, b + per), keeps, off));
+    return most;
+  };
+
+  // bands that run one by one: in reuse mode on one full-height buffer per layer (rows at their
+  // absolute position), kept from band to band
+  P->sched = ChainSched::kPerBand;
+  P->group = nb;
+  P->images = n;
+  P->slab_off.assign(nb + 1, std::vector<size_t>(nl, 0));   // (descriptors of the whole chain are made outside of a pass, too)
+  P->chain_off.assign(nb + 1, std::vector<size_t>(nl, 0));
+  P->arena_bytes = 0;
+  if (t.reuse) {
+    for (int l = 0; l + 1 < nl; ++l) {
+      for (int b = 0; b < nb; ++b) P->slab_off[b][l] = P->arena_bytes;
+      if (band_keeps(l)) P->arena_bytes += rows_bytes(n, l, t.layers[l].h_out);
+    }
+  } else {
+    P->arena_bytes = place_groups(n, 1, band_keeps, &P->slab_off);
+  }
   P->conv_ws_bytes = band_workspace(P);
-  if (P->sched != ChainSched::kPerBand) P->conv_ws_bytes = std::max(P->conv_ws_bytes, merged_workspace(P));
+
+  // Merged launches in place of them, if they fit: one plan holds one arena and one workspace for both.
+  const size_t arena = P->arena_bytes, ws = P->conv_ws_bytes;
+  const bool bands_fit = align_up(arena, 256) + ws <= kMergeMaxBytes;
+  auto merge = [&](ChainSched sched, int images, int per, size_t merged, bool always) {
+    P->sched = sched; P->images = images; P->group = per;
+    if (always || merged <= kMergeMaxBytes) {
+      const size_t merged_ws = merged_workspace(P), both = std::max(arena, merged), both_ws = std::max(ws, merged_ws);
+      if (always || (bands_fit ? align_up(both, 256) + both_ws : align_up(merged, 256) + merged_ws) <= kMergeMaxBytes) {
+        P->arena_bytes = both;
+        P->conv_ws_bytes = both_ws;
+        return true;
+      }
+    }
+    P->sched = ChainSched::kPerBand; P->images = n; P->group = nb;
+    return false;
+  };
+  if (P->batched) {
+    merge(ChainSched::kGrouped, n, nb, place_groups(n, nb, chain_keeps, &P->chain_off), true);
+    return;
+  }
+  const bool rows_only = t.in.w == 1 && n * t.in.h < kMergeMinRows;
+  if ((P->flags & LOP_FLAG_PLAN_ONLY) || (rows_only && nb > 1)) return;
+  const bool whole = t.disjoint();
+  // A pass over few rows whose launches take one band each is a crowd of small launches on one lane: eight bands
+  // and eight images of the inverted-residual chain layer by layer took 3.3 ms that way, band by band 2.2.
+  bool all = true;
+  for (int l = 0; l < nl; ++l)
+    all = all && (P->fuse_chain.away[l] || P->fuse_chain.head[l] >= 0 || lop::op_batchable(lop::describe_layer(P, l)));
+  for (int passes = 1, images = 0; images != 1; ++passes) {
+    images = (n + passes - 1) / passes;
+    if (!whole && !all && images != n) return;
+    if (whole ? merge(ChainSched::kWhole, images, nb, place_whole(images, INT_MAX), false)
+              : merge(ChainSched::kGrouped, images, nb, place_groups(images, nb, chain_keeps, &P->chain_off), false))
+      return;
+  }
+  for (int groups = 2, per = nb; !whole && all && per != 1; ++groups) {
+    per = (nb + groups - 1) / groups;
+    if (merge(ChainSched::kGrouped, 1, per, place_groups(1, per, chain_keeps, &P->chain_off), false)) return;
+  }
+  // a chain whose layers keep to their rows: passes over the rows of as many bands as fit, if two do (the launches of
+  // one band at a time are better off on four lanes: alone 1 150 against 1 390 us on 65 536 x 1024 -> 4096 -> 1024).
+  // Band by band the launches leave their last rounds of tiles to compete: 16 425 x 816 -> 2552 -> 816
+  // in five bands 271 -> 176 us a chain, 32 768 x 1024 -> 4096 -> 1024 in eight 785 -> 552.
+  for (int passes = 2; whole && keeps_to_rows(P); ++passes) {
+    const int per = (nb + passes - 1) / passes;
+    if (per < 2) return;
+    int rows = 0;
+    for (int b = 0; b < nb; b += per) { const lop_rows_t r = pass_rows(P, b, std::min(nb, b + per)); rows = std::max(rows, r.hi - r.lo); }
+    if (merge(ChainSched::kWhole, 1, per, place_whole(1, rows), false)) return;
+  }
 }
 
 // Whether every launch of the plan has a kernel form that takes several bands.
@@ -1427,7 +1436,6 @@ int lop_plan(const lop_layer_t* layers, int n_layers, const lop_tensor_desc_t* i
     P->batched = true;
   }
   size_scratch(P);
-  size_workspace(P);
   if (!(flags & LOP_FLAG_PLAN_ONLY)) {
     rc = setup_device(P);
     if (rc != LOP_OK) { lop_plan_destroy(P); return rc; }

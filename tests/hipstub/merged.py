@@ -121,7 +121,34 @@ def wide_tiles():
     return bad
 
 
-bad = {"workspace": workspace, "wide_tiles": wide_tiles}[check]()
+def static_scratch():
+    """lop_run_chain_static takes every plan whose bands, one by one, fit the static array, and no other;
+    lop_plan_stats says which. (A plan-only plan merges nothing, and these chains have no fused layers.)"""
+    bad = []
+    rng = np.random.default_rng(78)
+    chains = [(shrinking("bf16", (2, 16, 201, 348), 3, 16, 2, 2, 256), 0)]
+    for _ in range(150):
+        d, n, h, w = str(rng.choice(["f32", "bf16"])), int(rng.integers(1, 9)), int(rng.integers(80, 420)), int(rng.integers(80, 420))
+        chains.append((shrinking(d, (n, 16, h, w), int(rng.integers(1, 7)), int(rng.choice([16, 32, 64])), int(rng.choice([2, 4])),
+                                 int(rng.choice([2, 4])), int(rng.choice([192, 256])), int(rng.choice([5, 7]))),
+                       int(rng.choice([0, lop.LOP_FLAG_REUSE]))))
+    taken = 0
+    for chain, flags in chains:
+        one_by_one = lop.Plan(chain, None, None, flags)
+        fits = one_by_one.stats()[2] <= lop.LOP_STATIC_SCRATCH_BYTES
+        one_by_one.destroy()
+        plan = make(chain, flags)
+        said = plan.stats()[2] <= lop.LOP_STATIC_SCRATCH_BYTES
+        got = status(lambda: plan.run_chain_static(TENSOR, TENSOR))
+        plan.destroy()
+        taken += got == 0
+        if got != (0 if fits else lop.LOP_ERR_TOO_LARGE) or said != fits:
+            bad.append((chain, flags, fits, said, got))
+    print(taken, "of", len(chains), "plans taken", flush=True)
+    return bad
+
+
+bad = {"workspace": workspace, "wide_tiles": wide_tiles, "static_scratch": static_scratch}[check]()
 for b in bad:
     print("FAILED", b, flush=True)
 print("CHECK %s" % ("FAILED" if bad else "OK"), flush=True)

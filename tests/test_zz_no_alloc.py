@@ -53,6 +53,18 @@ def test_static_scratch_bf16_chains(oracle):
         assert rel_err(got, oracle.run_chain(chain, t)) <= TOL[chain.dtype]
 
 
+def test_static_scratch_holds_the_partial_sums_of_all_bands(oracle):
+    """Layers of few pixels and long reductions: merged launches keep the partial sums of all bands at
+    once, more than the array has room for beside the slabs. The bands one by one fit, so the call runs."""
+    chain = workloads.Chain("sums", (2, 16, 201, 348), "bf16", 3)
+    for c_in, c_out, k, s in ((16, 16, 3, 1), (16, 16, 3, 1), (16, 128, 3, 2), (128, 256, 3, 2), (256, 256, 5, 1), (256, 256, 5, 1)):
+        chain.add(workloads.CONV, c_in, c_out, k, s, k // 2, 1, "relu")
+    t = workloads.make_tensors(chain, zero_bias=False)
+    ref, got = _both(chain, t)
+    np.testing.assert_array_equal(got, ref)
+    assert rel_err(got, oracle.run_chain(chain, t)) <= TOL[chain.dtype]
+
+
 def test_static_scratch_rejects_a_plan_that_does_not_fit():
     chain = workloads.mbv2_chain(h=640, w=640, n=2, n_bands=2)     # layer by layer: > 64 MiB of slabs
     t = workloads.make_tensors(chain)
