@@ -1623,6 +1623,14 @@ int lop_run_chain(lop_plan_t* P, const void* d_in, void* d_out, void* h_out, voi
     if (rc != LOP_OK) return rc;
   }
   const auto t0 = std::chrono::steady_clock::now();
+  // (with timing the bands of a plan that did not ask for batched launches run one by one, so
+  // that each has a start and an end of its own)
+  const bool merged = P->sched != ChainSched::kPerBand && (!timing || P->batched);
+  if (!merged)
+    for (Lane& L : P->lanes) {   // a band or a merged chain on a caller's stream may still use a lane's scratch
+      int rc = take_lane(L, L.stream);
+      if (rc != LOP_OK) return rc;
+    }
   if (P->copy_lane && copy && !compute_stream && !timing) {
     // Compute lanes run free, as below; every band's copy goes to the copy lane.
     for (int b = 0; b < nb; ++b) {
@@ -1632,14 +1640,6 @@ int lop_run_chain(lop_plan_t* P, const void* d_in, void* d_out, void* h_out, voi
     }
     return LOP_OK;
   }
-  // (with timing the bands of a plan that did not ask for batched launches run one by one, so
-  // that each has a start and an end of its own)
-  const bool merged = P->sched != ChainSched::kPerBand && (!timing || P->batched);
-  if (!merged)
-    for (Lane& L : P->lanes) {   // a merged chain of the caller's stream may still use a lane's scratch
-      int rc = take_lane(L, L.stream);
-      if (rc != LOP_OK) return rc;
-    }
   if (merged) {
     int rc = run_merged(P, d_in, d_out, h_out, compute_stream ? ms : nullptr, timing != nullptr);
     if (rc != LOP_OK) return rc;

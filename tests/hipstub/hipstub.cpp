@@ -11,6 +11,7 @@
 #define __HIP_PLATFORM_AMD__ 1
 #include <hip/hip_runtime_api.h>
 
+#include <algorithm>
 #include <cstdarg>
 #include <cstdio>
 #include <cstdlib>
@@ -24,11 +25,18 @@ namespace {
 enum Kind { kStream, kEvent, kGraph, kExec, kAlloc, kKinds };
 const char* const kKindName[kKinds] = {"stream", "event", "graph", "graph exec", "allocation"};
 
+// What of every stream's work is known to be done before: stream -> number of its launches.
+typedef std::map<const void*, long> Clock;
+void join(Clock& c, const Clock& with) {
+  for (const auto& kv : with) c[kv.first] = std::max(c[kv.first], kv.second);
+}
+
 struct Handle {
   Kind kind;
   bool alive = true;
   bool recorded = false;   // event
   bool capturing = false;  // stream
+  Clock clock;             // stream: what its next launch is ordered behind; event: the stream's when it was recorded
   const void* on = nullptr; // event: the stream it was last recorded on
   size_t bytes = 0;        // allocation
 };
@@ -39,6 +47,9 @@ std::map<const void*, Handle> g_handles;  // every handle ever handed out (addre
                                           // quarantined by the sanitizer)
 std::map<const void*, size_t> g_pinned;   // host ranges registered as mapped pinned memory
 long g_launches = 0, g_created[kKinds] = {0}, g_live[kKinds] = {0};
+Clock g_host;                             // what the host has waited for
+const void* g_marked = nullptr;           // hipstub_mark: the stream, how far it was, launches not ordered behind that
+long g_marked_at = 0, g_unordered = 0;
 
 [[noreturn]] void die(const char* fmt, ...) {
   va_list ap;
@@ -79,6 +90,15 @@ Handle* use_stream(hipStream_t s, const char* what) {
   return s ? &use(s, kStream, what) : nullptr;
 }
 
+// Work on a stream (a kernel, or a whole graph), for the order of things; null stream: not followed.
+void tick(Handle* s, const void* stream) {
+  if (!s || s->capturing) return;
+  join(s->clock, g_host);
+  if (g_marked && stream != g_marked && s->clock[g_marked] < g_marked_at) ++g_unordered;
+  ++s->clock[stream];
+}
+void wait_on_host(const Clock& c) { join(g_host, c); }
+
 thread_local struct { dim3 grid, block; size_t shmem; hipStream_t stream; } t_cfg;
 
 }  // namespace
@@ -90,6 +110,12 @@ void hipstub_pin(void* p, size_t bytes) { std::lock_guard<std::mutex> l(g_mu); g
 void hipstub_unpin(void* p) { std::lock_guard<std::mutex> l(g_mu); g_pinned.erase(p); }
 long hipstub_live(int kind) { std::lock_guard<std::mutex> l(g_mu); return kind >= 0 && kind < kKinds ? g_live[kind] : -1; }
 long hipstub_created(int kind) { std::lock_guard<std::mutex> l(g_mu); return kind >= 0 && kind < kKinds ? g_created[kind] : -1; }
+// From here on, count the launches on other streams that are not ordered behind what `s` holds now.
+void hipstub_mark(const void* s) {
+  std::lock_guard<std::mutex> l(g_mu);
+  g_marked = s; g_marked_at = s ? use(s, kStream, "hipstub_mark").clock[s] : 0; g_unordered = 0;
+}
+long hipstub_unordered(void) { std::lock_guard<std::mutex> l(g_mu); return g_unordered; }
 long hipstub_launches(void) { std::lock_guard<std::mutex> l(g_mu); return g_launches; }
 
 // ---- what hipcc's host code calls around a kernel launch
@@ -109,7 +135,7 @@ hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* shmem, hip
 static hipError_t launch(const void* fn, dim3 grid, dim3 block, hipStream_t s, const char* what) {
   std::lock_guard<std::mutex> l(g_mu);
   if (!fn) die("%s: null kernel", what);
-  use_stream(s, what);
+  tick(use_stream(s, what), s);
   if (!grid.x || !grid.y || !grid.z || !block.x || !block.y || !block.z) die("%s: empty grid or block", what);
   if ((size_t)block.x * block.y * block.z > 1024) die("%s: block of more than 1024 threads", what);
   if (grid.y > 65535 || grid.z > 65535) die("%s: grid.y or grid.z above 65535", what);
@@ -137,6 +163,8 @@ hipError_t hipDeviceSynchronize(void) {
   for (auto& kv : g_handles)
     if (kv.second.kind == kStream && kv.second.alive && kv.second.capturing)
       die("hipDeviceSynchronize while stream %p is capturing", kv.first);
+  for (auto& kv : g_handles)
+    if (kv.second.kind == kStream && kv.second.alive) wait_on_host(kv.second.clock);
   return hipSuccess;
 }
 hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t attr, int) {
@@ -231,12 +259,14 @@ hipError_t hipStreamSynchronize(hipStream_t s) {
   std::lock_guard<std::mutex> l(g_mu);
   Handle* h = use_stream(s, "hipStreamSynchronize");
   if (h && h->capturing) die("hipStreamSynchronize of capturing stream %p", (void*)s);
+  if (h) wait_on_host(h->clock);
   return hipSuccess;
 }
 hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned) {
   std::lock_guard<std::mutex> l(g_mu);
-  use_stream(s, "hipStreamWaitEvent");
-  use(e, kEvent, "hipStreamWaitEvent");
+  Handle* h = use_stream(s, "hipStreamWaitEvent");
+  const Handle& ev = use(e, kEvent, "hipStreamWaitEvent");
+  if (h && !h->capturing) join(h->clock, ev.clock);
   return hipSuccess;
 }
 hipError_t hipStreamBeginCapture(hipStream_t s, hipStreamCaptureMode) {
@@ -269,15 +299,16 @@ hipError_t hipEventDestroy(hipEvent_t e) {
 }
 hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) {
   std::lock_guard<std::mutex> l(g_mu);
-  use_stream(s, "hipEventRecord");
+  const Handle* st = use_stream(s, "hipEventRecord");
   Handle& h = use(e, kEvent, "hipEventRecord");
   h.recorded = true;
+  if (st && !st->capturing) h.clock = st->clock;
   h.on = s;
   return hipSuccess;
 }
 hipError_t hipEventSynchronize(hipEvent_t e) {
   std::lock_guard<std::mutex> l(g_mu);
-  use(e, kEvent, "hipEventSynchronize");
+  wait_on_host(use(e, kEvent, "hipEventSynchronize").clock);
   return hipSuccess;
 }
 hipError_t hipEventElapsedTime(float* ms, hipEvent_t a, hipEvent_t b) {
@@ -298,7 +329,7 @@ hipError_t hipGraphInstantiate(hipGraphExec_t* x, hipGraph_t g, hipGraphNode_t*,
 hipError_t hipGraphLaunch(hipGraphExec_t x, hipStream_t s) {
   std::lock_guard<std::mutex> l(g_mu);
   use(x, kExec, "hipGraphLaunch");
-  use_stream(s, "hipGraphLaunch");
+  tick(use_stream(s, "hipGraphLaunch"), s);
   return hipSuccess;
 }
 hipError_t hipGraphDestroy(hipGraph_t g) {

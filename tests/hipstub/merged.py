@@ -4,6 +4,7 @@ with the same plan's bands run one by one. Run as `python merged.py <stub dir> <
 AddressSanitizer runtime preloaded (see build_stub.py). Kernels do nothing here, so tensors are
 addresses only.
 """
+import ctypes
 import os
 import sys
 import types
@@ -19,6 +20,11 @@ import workloads  # noqa: E402
 from paper_2507_05829_amd import lop  # noqa: E402
 
 assert lop.LIB_PATH.startswith(stub_dir), lop.LIB_PATH
+stub = ctypes.CDLL(os.path.join(stub_dir, "paper_2507_05829_amd", "libhipstub.so"))
+stub.hipstub_unordered.restype = ctypes.c_long
+stub.hipstub_mark.argtypes = [ctypes.c_void_p]
+stub.hipStreamCreateWithFlags.argtypes = [ctypes.c_void_p, ctypes.c_uint]
+stub.hipStreamDestroy.argtypes = [ctypes.c_void_p]
 _room = np.zeros(64, np.uint8)
 TENSOR = (_room.ctypes.data + 15) & ~15
 
@@ -148,7 +154,47 @@ def static_scratch():
     return bad
 
 
-bad = {"workspace": workspace, "wide_tiles": wide_tiles, "static_scratch": static_scratch}[check]()
+def new_stream():
+    s = ctypes.c_void_p()
+    assert stub.hipStreamCreateWithFlags(ctypes.byref(s), 1) == 0
+    return s.value
+
+
+def layer_by_layer(n):
+    """A batch of the inverted-residual chain whose launches take one band each: its bands run one by
+    one, and where `n` makes their results long, leave through the copy lane."""
+    return workloads.mbv2_chain(h=192, w=192, n=n, n_bands=4)
+
+
+def order_of_streams():
+    """Bands that lop_run_band runs on a caller's stream use the lanes' scratch: whatever lop_run_chain
+    launches next waits for that stream, with the copies on their own lane and without."""
+    bad = []
+    for chain, flags, copy in ((layer_by_layer(8), lop.LOP_FLAG_NO_FUSE, True), (layer_by_layer(8), lop.LOP_FLAG_NO_FUSE, False),
+                               (layer_by_layer(2), lop.LOP_FLAG_NO_FUSE, True), (workloads.tiny_chain(), 0, False)):
+        for graph in (0, lop.LOP_FLAG_GRAPH):
+            plan = lop.Plan(chain, ZeroWeights(chain), None, flags | graph)
+            on, oc, oh, ow = plan.out_shape()
+            h_out = np.zeros(on * oc * oh * ow * 4 + 16, np.uint8)
+            stub.hipstub_pin(ctypes.c_void_p(h_out.ctypes.data), ctypes.c_size_t(h_out.nbytes))
+            host = (h_out.ctypes.data + 15) & ~15 if copy else None
+            user = new_stream()
+            for first in (True, False):
+                for b in range(plan.n_bands):
+                    plan.run_band(b, TENSOR, TENSOR, None, user)
+                    if b == plan.n_bands - 4:      # (no lane's last band is earlier)
+                        stub.hipstub_mark(user)
+                plan.run_chain(TENSOR, TENSOR, host)
+                if stub.hipstub_unordered():
+                    bad.append((chain.name, chain.in_shape, flags | graph, copy, first, stub.hipstub_unordered()))
+            stub.hipstub_mark(None)
+            plan.destroy()
+            stub.hipstub_unpin(ctypes.c_void_p(h_out.ctypes.data))
+            stub.hipStreamDestroy(user)
+    return bad
+
+
+bad = {"order_of_streams": order_of_streams, "workspace": workspace, "wide_tiles": wide_tiles, "static_scratch": static_scratch}[check]()
 for b in bad:
     print("FAILED", b, flush=True)
 print("CHECK %s" % ("FAILED" if bad else "OK"), flush=True)

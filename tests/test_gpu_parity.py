@@ -592,11 +592,12 @@ def test_long_band_copies_on_the_copy_lane(oracle, graph):
     """Independent bands whose copies are long (more than 256 KiB per band) leave through the
     copy lane: three calls in a row on the same buffers (the second and third must wait for the
     copies of the call before), then one into a second pair of buffers, every host result
-    equal to the device result and to the oracle."""
+    equal to the device result and to the oracle. Layer by layer, since a batch whose launches take
+    one band each is the one that runs band by band (with its blocks fused this chain is merged)."""
     chain = workloads.mbv2_chain(h=192, w=192, n=8, n_bands=4)
     t = workloads.make_tensors(chain, zero_bias=False)
     want = oracle.run_chain(chain, t)
-    plan = lop.Plan(chain, t, None, lop.LOP_FLAG_GRAPH if graph else 0)
+    plan = lop.Plan(chain, t, None, lop.LOP_FLAG_NO_FUSE | (lop.LOP_FLAG_GRAPH if graph else 0))
     try:
         n, c, h, w = plan.out_shape()
         assert n * c * h * w * 2 // 4 > 256 * 1024
@@ -605,7 +606,13 @@ def test_long_band_copies_on_the_copy_lane(oracle, graph):
                  for _ in range(2)]
         for d_out, h_out in (pairs[0], pairs[0], pairs[0], pairs[1]):
             plan.run_chain(d_in, d_out, h_out)
+        # bands on a caller's stream use the lanes' scratch; the chain behind them waits for it
+        user, third = torch.cuda.Stream(), empty_out(plan.out_shape(), chain.dtype)
+        for b in range(plan.n_bands):
+            plan.run_band(b, d_in, third, None, user)
+        plan.run_chain(d_in, *pairs[1])
         plan.synchronize()
+        assert rel_err(to_nchw(third), want) <= TOL[chain.dtype]
         for d_out, h_out in pairs:
             dev, host = to_nchw(d_out), to_nchw(h_out)
             np.testing.assert_array_equal(host, dev)
