@@ -1626,9 +1626,12 @@ int lop_run_chain(lop_plan_t* P, const void* d_in, void* d_out, void* h_out, voi
   // (with timing the bands of a plan that did not ask for batched launches run one by one, so
   // that each has a start and an end of its own)
   const bool merged = P->sched != ChainSched::kPerBand && (!timing || P->batched);
+  // (one graph of all bands runs on `ms` itself, with every lane's scratch)
+  const bool lanes_in_graph = !merged && !P->t.reuse && (P->flags & LOP_FLAG_GRAPH) && !timing &&
+                              (compute_stream || P->n_lanes() == 1) && !(P->copy_lane && copy && !compute_stream);
   if (!merged)
-    for (Lane& L : P->lanes) {   // a band or a merged chain on a caller's stream may still use a lane's scratch
-      int rc = take_lane(L, L.stream);
+    for (Lane& L : P->lanes) {   // a band or a chain on a caller's stream may still use a lane's scratch
+      int rc = take_lane(L, lanes_in_graph ? ms : L.stream);
       if (rc != LOP_OK) return rc;
     }
   if (P->copy_lane && copy && !compute_stream && !timing) {
@@ -1677,7 +1680,14 @@ int lop_run_chain(lop_plan_t* P, const void* d_in, void* d_out, void* h_out, voi
       }
       return LOP_OK;
     }
-    if ((P->flags & LOP_FLAG_GRAPH) && !timing) return launch_graph(P, d_in, d_out, h_out, ms);
+    if (lanes_in_graph) {
+      int rc = launch_graph(P, d_in, d_out, h_out, ms);
+      for (Lane& L : P->lanes) {   // (also after an error: a capture may have used the lanes' events)
+        const int left = leave_lane(L);
+        rc = rc == LOP_OK ? left : rc;
+      }
+      return rc;
+    }
     if (timing) LOP_HIP(hipEventRecord(P->ev_t0, ms));
     int rc = enqueue_chain(P, d_in, d_out, h_out, ms, timing != nullptr, false);
     if (rc != LOP_OK) return rc;

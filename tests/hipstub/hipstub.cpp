@@ -35,7 +35,8 @@ struct Handle {
   Kind kind;
   bool alive = true;
   bool recorded = false;   // event
-  bool capturing = false;  // stream
+  bool capturing = false;  // stream: being captured, itself or forked from the stream that began it
+  const void* origin = nullptr;  // ... that stream; event: recorded in that stream's capture (nullptr: outside)
   Clock clock;             // stream: what its next launch is ordered behind; event: the stream's when it was recorded
   const void* on = nullptr; // event: the stream it was last recorded on
   size_t bytes = 0;        // allocation
@@ -266,7 +267,12 @@ hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned) {
   std::lock_guard<std::mutex> l(g_mu);
   Handle* h = use_stream(s, "hipStreamWaitEvent");
   const Handle& ev = use(e, kEvent, "hipStreamWaitEvent");
-  if (h && !h->capturing) join(h->clock, ev.clock);
+  if (h && ev.origin) {   // the stream joins the capture
+    h->capturing = true;
+    h->origin = ev.origin;
+  } else if (h && !h->capturing) {
+    join(h->clock, ev.clock);
+  }
   return hipSuccess;
 }
 hipError_t hipStreamBeginCapture(hipStream_t s, hipStreamCaptureMode) {
@@ -274,13 +280,15 @@ hipError_t hipStreamBeginCapture(hipStream_t s, hipStreamCaptureMode) {
   Handle& h = use(s, kStream, "hipStreamBeginCapture");
   if (h.capturing) die("hipStreamBeginCapture: %p is capturing already", (void*)s);
   h.capturing = true;
+  h.origin = s;
   return hipSuccess;
 }
 hipError_t hipStreamEndCapture(hipStream_t s, hipGraph_t* g) {
   std::lock_guard<std::mutex> l(g_mu);
   Handle& h = use(s, kStream, "hipStreamEndCapture");
   if (!h.capturing) die("hipStreamEndCapture: %p is not capturing", (void*)s);
-  h.capturing = false;
+  for (auto& kv : g_handles)   // (events stay what they were recorded as)
+    if (kv.second.kind == kStream && kv.second.origin == (const void*)s) kv.second.capturing = false, kv.second.origin = nullptr;
   *g = (hipGraph_t)make(kGraph);
   return hipSuccess;
 }
@@ -302,6 +310,7 @@ hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) {
   const Handle* st = use_stream(s, "hipEventRecord");
   Handle& h = use(e, kEvent, "hipEventRecord");
   h.recorded = true;
+  h.origin = st && st->capturing ? st->origin : nullptr;
   if (st && !st->capturing) h.clock = st->clock;
   h.on = s;
   return hipSuccess;

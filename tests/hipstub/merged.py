@@ -178,7 +178,7 @@ def order_of_streams():
             h_out = np.zeros(on * oc * oh * ow * 4 + 16, np.uint8)
             stub.hipstub_pin(ctypes.c_void_p(h_out.ctypes.data), ctypes.c_size_t(h_out.nbytes))
             host = (h_out.ctypes.data + 15) & ~15 if copy else None
-            user = new_stream()
+            user, other = new_stream(), None
             for first in (True, False):
                 for b in range(plan.n_bands):
                     plan.run_band(b, TENSOR, TENSOR, None, user)
@@ -187,10 +187,24 @@ def order_of_streams():
                 plan.run_chain(TENSOR, TENSOR, host)
                 if stub.hipstub_unordered():
                     bad.append((chain.name, chain.in_shape, flags | graph, copy, first, stub.hipstub_unordered()))
+            # chains on two callers' streams in turn, and one on the plan's own (a replayed graph of a chain that
+            # runs band by band uses every lane's scratch on the caller's stream; a merged chain one lane's)
+            if chain.in_shape[0] == 8:
+                other = new_stream()
+                for mine, then in ((user, other), (other, user), (user, None)):
+                    plan.run_chain(TENSOR, TENSOR, None, mine)
+                    stub.hipstub_mark(mine)
+                    plan.run_chain(TENSOR, TENSOR, host, then)
+                    if stub.hipstub_unordered():
+                        bad.append((chain.in_shape, flags | graph, copy, "chains", mine == user, then is None))
+                stub.hipstub_mark(None)
+            plan.synchronize()
             stub.hipstub_mark(None)
             plan.destroy()
             stub.hipstub_unpin(ctypes.c_void_p(h_out.ctypes.data))
-            stub.hipStreamDestroy(user)
+            for s in (user, other):
+                if s:
+                    stub.hipStreamDestroy(s)
     return bad
 
 

@@ -611,6 +611,9 @@ def test_long_band_copies_on_the_copy_lane(oracle, graph):
         for b in range(plan.n_bands):
             plan.run_band(b, d_in, third, None, user)
         plan.run_chain(d_in, *pairs[1])
+        # the same chain on two callers' streams in turn and on the plan's own, all on the lanes' scratch
+        for k, stream in enumerate((user, torch.cuda.Stream(), None)):
+            plan.run_chain(d_in, *pairs[k % 2], stream)
         plan.synchronize()
         assert rel_err(to_nchw(third), want) <= TOL[chain.dtype]
         for d_out, h_out in pairs:
