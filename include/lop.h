@@ -120,7 +120,7 @@ typedef struct {
                                  one launch that keeps the expanded tensor on chip; results
                                  agree with the layer-by-layer path to fp32 summation order */
 #define LOP_FLAG_POISON_SCRATCH 64u /* debug aid: before a band's kernels (reuse mode: before a chain's
-                                 first band) its scratch slabs and split-K workspace are filled
+                                 first band; a merged chain: before every pass) its scratch slabs and split-K workspace are filled
                                  with NaN bit patterns, so any read of a scratch row that the
                                  band's own launches did not write first poisons the output  */
 #define LOP_FLAG_LANES(n) (((unsigned)(n) & 0xffu) << 8) /* bands are dealt round robin to n

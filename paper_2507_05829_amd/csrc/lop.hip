@@ -1170,10 +1170,12 @@ bool siblings(const lop_plan_t* P, int l) {
 // stream, with the scratch set by the caller. y2: where the last launch also stores its rows.
 int enqueue_merged_kernels(lop_plan_t* P, const void* d_in, void* d_out, hipStream_t cs, void* y2) {
   const int nl = P->t.n_layers(), whole = P->t.whole();
-  if (P->flags & LOP_FLAG_POISON_SCRATCH) {
+  auto begin_pass = [&]() -> int {
+    if (!(P->flags & LOP_FLAG_POISON_SCRATCH)) return LOP_OK;
     LOP_HIP(lop::launch_fill_words(P->arena_of(0), align_up(P->arena_bytes, 256), 0xFFFFFFFFu, cs));
     LOP_HIP(lop::launch_fill_words(P->ws_of(0), P->conv_ws_bytes / 16 * 16, 0xFFFFFFFFu, cs));
-  }
+    return LOP_OK;
+  };
   const int nb = P->t.n_bands, n = P->t.in.n;
   const size_t out_bytes = (size_t)P->t.layers.back().h_out * P->t.row_elems(nl - 1) * P->t.esz();   // of one image
   for (int i = 0; i < n; i += P->images) {
@@ -1183,6 +1185,7 @@ int enqueue_merged_kernels(lop_plan_t* P, const void* d_in, void* d_out, hipStre
       for (int b = 0; b < nb; b += P->group) {
         const lop_rows_t rows = P->group < nb ? pass_rows(P, b, std::min(nb, b + P->group)) : lop_rows_t{0, 0};
         if (P->group < nb && rows.hi <= rows.lo) continue;
+        if (const int rc = begin_pass(); rc != LOP_OK) return rc;
         const ChainPass pass(P, i, images, rows);
         for (int l = 0; l < nl; ++l) {
           if (siblings(P, l)) {
@@ -1201,6 +1204,7 @@ int enqueue_merged_kernels(lop_plan_t* P, const void* d_in, void* d_out, hipStre
     const ChainPass pass(P, i, images);
     for (int b = 0; b < nb; b += P->group) {
       const int end = std::min(nb, b + P->group);
+      if (const int rc = begin_pass(); rc != LOP_OK) return rc;
       for (int l = 0; l < nl; ++l) {
         if (end - b <= lop::kMaxBandsPerLaunch && siblings(P, l)) {
           std::vector<lop::OpLaunch> as, qs, none;

@@ -208,7 +208,31 @@ def order_of_streams():
     return bad
 
 
-bad = {"order_of_streams": order_of_streams, "workspace": workspace, "wide_tiles": wide_tiles, "static_scratch": static_scratch}[check]()
+def poison():
+    """LOP_FLAG_POISON_SCRATCH fills the scratch before every pass of a merged chain: what a pass left
+    behind is not there for the next one to read."""
+    bad = []
+    stub.hipstub_launches.restype = ctypes.c_long
+
+    def launches(chain, flags):
+        plan = make(chain, flags)
+        before = stub.hipstub_launches()
+        plan.run_chain(TENSOR, TENSOR)
+        count = stub.hipstub_launches() - before
+        plan.destroy()
+        return count
+
+    layers = [(64, 3, 1, 1)] * 3          # (one launch each, without partial sums)
+    for shape, bands, flags, least in (((8, 64, 300, 300), 1, 0, 2), ((8, 64, 300, 300), 3, 0, 2), ((7, 64, 300, 300), 3, lop.LOP_FLAG_REUSE, 2),
+                                       ((1, 64, 800, 1000), 9, 0, 2), ((1, 64, 64, 64), 2, 0, 1)):
+        chain = conv_chain("bf16", shape, bands, layers)
+        plain, poisoned = launches(chain, flags), launches(chain, flags | lop.LOP_FLAG_POISON_SCRATCH)
+        if plain < 3 * least or plain % 3 or poisoned - plain != plain // 3:
+            bad.append((shape, bands, flags, plain, poisoned))
+    return bad
+
+
+bad = {"poison": poison, "order_of_streams": order_of_streams, "workspace": workspace, "wide_tiles": wide_tiles, "static_scratch": static_scratch}[check]()
 for b in bad:
     print("FAILED", b, flush=True)
 print("CHECK %s" % ("FAILED" if bad else "OK"), flush=True)
