@@ -288,18 +288,33 @@ inline bool dw3_applies(const RowParams& p, int op, int vec) {
          p.res == nullptr;
 }
 
+// One launch, unless its (image, chunk of rows) pairs outnumber the grid's second dimension: then one
+// per group of images, or per group of rows of an image.
+constexpr int kMaxGridY = 65535;
 template <typename T, int VEC>
 hipError_t launch_dw3(const RowParams& p, hipStream_t s, KernelEvents* ev) {
-  if (p.R <= 0) return hipSuccess;
-  Dw3Params q;
-  q.r = p;
-  const int cv = p.C / VEC;
-  q.cols_per_block = std::max(1, 256 / cv);
-  const int rpt = dw_rows_per_thread(p.sh);
-  q.chunks = (p.R + rpt - 1) / rpt;
-  dim3 grid((p.W_out + q.cols_per_block - 1) / q.cols_per_block, q.chunks * p.N);
-  return p.sh == 1 ? launch_kernel(dwconv3x3_kernel<T, VEC, 1>, grid, dim3(256), s, ev, q)
-                   : launch_kernel(dwconv3x3_kernel<T, VEC, 2>, grid, dim3(256), s, ev, q);
+  if (p.R <= 0 || p.N <= 0) return hipSuccess;
+  const int cv = p.C / VEC, rpt = dw_rows_per_thread(p.sh);
+  const size_t x_img = (size_t)p.x_rows * p.W * p.C * sizeof(T), y_img = (size_t)p.y_rows * p.W_out * p.C * sizeof(T);
+  const int rows = std::min(p.R, kMaxGridY * rpt), images = std::max(1, kMaxGridY / ((rows + rpt - 1) / rpt));
+  for (int n = 0; n < p.N; n += images)
+    for (int r = 0; r < p.R; r += rows) {
+      Dw3Params q;
+      q.r = p;
+      q.r.x = (const char*)p.x + n * x_img;
+      q.r.y = (char*)p.y + n * y_img;
+      q.r.y2 = p.y2 ? (char*)p.y2 + n * y_img : nullptr;
+      q.r.N = std::min(images, p.N - n);
+      q.r.out_lo = p.out_lo + r;
+      q.r.R = std::min(rows, p.R - r);
+      q.cols_per_block = std::max(1, 256 / cv);
+      q.chunks = (q.r.R + rpt - 1) / rpt;
+      const dim3 grid((p.W_out + q.cols_per_block - 1) / q.cols_per_block, q.chunks * q.r.N);
+      const hipError_t e = p.sh == 1 ? launch_kernel(dwconv3x3_kernel<T, VEC, 1>, grid, dim3(256), s, ev, q)
+                                     : launch_kernel(dwconv3x3_kernel<T, VEC, 2>, grid, dim3(256), s, ev, q);
+      if (e != hipSuccess) return e;
+    }
+  return hipSuccess;
 }
 
 // Channel vector per thread of the sliding-window kernel (0: it does not apply).

@@ -232,7 +232,22 @@ def poison():
     return bad
 
 
-bad = {"poison": poison, "order_of_streams": order_of_streams, "workspace": workspace, "wide_tiles": wide_tiles, "static_scratch": static_scratch}[check]()
+def grids():
+    """Depthwise layers whose bands' launches fit the grid's second dimension, and whose launch over all
+    rows would not (the stand-in ends the process on a grid that the runtime refuses)."""
+    bad = []
+    for dtype, shape, s in (("f32", (600, 4, 1030, 2), 1), ("bf16", (3000, 8, 90, 3), 2), ("f32", (1, 4, 600000, 1), 1)):
+        for flags in (0, lop.LOP_FLAG_REUSE):
+            chain = workloads.Chain("depthwise", shape, dtype, 4)
+            for _ in range(2):
+                chain.add(workloads.DWCONV, shape[1], shape[1], 3, s, 1, 1, "relu6")
+            got = run_both_ways(chain, flags)
+            if got != (0, 0):
+                bad.append((shape, flags, got))
+    return bad
+
+
+bad = {"grids": grids, "poison": poison, "order_of_streams": order_of_streams, "workspace": workspace, "wide_tiles": wide_tiles, "static_scratch": static_scratch}[check]()
 for b in bad:
     print("FAILED", b, flush=True)
 print("CHECK %s" % ("FAILED" if bad else "OK"), flush=True)

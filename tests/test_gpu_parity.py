@@ -1419,6 +1419,19 @@ def test_merged_chain_agrees_with_its_bands(oracle, name, kw, flags, graph):
         plan.destroy()
 
 
+@pytest.mark.parametrize("dtype,shape,s", [("f32", (600, 4, 1030, 1), 1), ("bf16", (1, 4, 530000, 1), 1), ("f32", (1500, 4, 400, 1), 2)])
+def test_depthwise_launch_of_more_rows_than_a_grid_takes(oracle, dtype, shape, s):
+    """More than 65 535 chunks of rows in a batch, and in one image."""
+    chain = workloads.Chain("tall", shape, dtype, 4)
+    chain.add(workloads.DWCONV, 4, 4, 3, s, 1, 1, "relu6")
+    t = workloads.make_tensors(chain, zero_bias=False)
+    want = oracle.run_chain(chain, t)
+    for flags in (0, lop.LOP_FLAG_REUSE):
+        dev, host = run_gpu(chain, t, flags=flags)
+        assert rel_err(dev, want) <= TOL[dtype]
+        np.testing.assert_array_equal(host, dev)
+
+
 @pytest.mark.parametrize("shape,bands", [((9, 16, 213, 236), 1), ((7, 16, 254, 246), 3)])
 def test_last_pass_over_fewer_images(oracle, shape, bands):
     """A batch that does not divide into passes, and behind it a layer of few pixels and a long
