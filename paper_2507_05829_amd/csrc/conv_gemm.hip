@@ -356,8 +356,12 @@ hipError_t launch_gemm(const OpLaunch* Ls, int n, hipStream_t s, KernelEvents* e
 
 int gemm_describe(const OpLaunch* Ls, int n, char* name, size_t size) {
   const GemmChoice c = choose_gemm(Ls, n);
-  if (name && size)
-    snprintf(name, size, "conv_gemm_kernel%s<%s, %d, %d>", n > 1 ? "_bands" : "", Ls[0].dtype == LOP_BF16 ? "__bf16" : "float", c.bm, c.bn);
+  const bool bf = Ls[0].dtype == LOP_BF16;
+  int m = 0;
+  for (int b = 0; b < n; ++b) m += make_gemm(Ls[b]).M > 0;
+  if (name && size)   // (tile, wavefronts in either direction, stages: as launch_gemm takes them)
+    snprintf(name, size, "conv_gemm_kernel%s<%s, %d, %d, 2, %d, %d>", m > 1 ? "_bands" : "", bf ? "__bf16" : "float", c.bm, c.bn,
+             bf && c.bn == 256 ? 4 : 2, c.bm == 256 || (!bf && c.bm == 128) ? 2 : 3);
   return 1;
 }
 

@@ -11,7 +11,7 @@
 // launch or of another chain): 20.4 -> 17.4 us for 320 tiles of 512 -> 512 channels. What is left is the
 // launch, that round of latency and, with 4 608 reduction elements, 4.4 us of matrix instructions.
 //
-// conv_narrow_kernel of conv_igemm.hip, which this form replaces where the patch fits, gathers every
+// conv_narrow_patch_kernel of conv_igemm.hip, which this form replaces where the patch fits, gathers every
 // tap of every pixel straight into operand registers: four lanes of such a load touch four cache lines, which
 // costs the vector cache four times the cycles of a contiguous one, nine times over.
 #include <hip/hip_runtime.h>
@@ -184,12 +184,12 @@ __device__ __forceinline__ void narrow_body(const NarrowParams& p, const int bx,
 }
 
 template <typename T, int AHEAD, int LDS>
-__global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(8))) void conv_narrow_kernel(const NarrowParams p) {
+__global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(8))) void conv_narrow_patch_kernel(const NarrowParams p) {
   narrow_body<AHEAD, LDS>(p, blockIdx.x, gridDim.x);
 }
 // The same for several bands of one layer in one grid (band b owns blocks first[b] .. first[b + 1] of x).
 template <typename T, int AHEAD, int LDS>
-__global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(8))) void conv_narrow_kernel_bands(const Batch<NarrowParams> t) {
+__global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(8))) void conv_narrow_patch_kernel_bands(const Batch<NarrowParams> t) {
   const int b = batch_find(t, blockIdx.x);
   narrow_body<AHEAD, LDS>(t.p[b], blockIdx.x - t.first[b], t.first[b + 1] - t.first[b]);
 }
@@ -294,10 +294,10 @@ hipError_t launch_narrow_siblings(const OpLaunch* Ls, const OpLaunch* sibs, int 
   const dim3 block(64 * kWaves);
   if (patch > (size_t)kMaxPatch) return hipErrorInvalidValue;
   if (patch > (size_t)kSmallPatch)
-    return launch_group(conv_narrow_kernel<float, 9, kMaxPatch>, conv_narrow_kernel_bands<float, 9, kMaxPatch>, ps, m, gx, gy, 1, block, s, ev);
+    return launch_group(conv_narrow_patch_kernel<float, 9, kMaxPatch>, conv_narrow_patch_kernel_bands<float, 9, kMaxPatch>, ps, m, gx, gy, 1, block, s, ev);
   if (9 * ps[0].C_in / 16 > kShortSteps)
-    return launch_group(conv_narrow_kernel<float, 9, kSmallPatch>, conv_narrow_kernel_bands<float, 9, kSmallPatch>, ps, m, gx, gy, 1, block, s, ev);
-  return launch_group(conv_narrow_kernel<float, 5, kSmallPatch>, conv_narrow_kernel_bands<float, 5, kSmallPatch>, ps, m, gx, gy, 1, block, s, ev);
+    return launch_group(conv_narrow_patch_kernel<float, 9, kSmallPatch>, conv_narrow_patch_kernel_bands<float, 9, kSmallPatch>, ps, m, gx, gy, 1, block, s, ev);
+  return launch_group(conv_narrow_patch_kernel<float, 5, kSmallPatch>, conv_narrow_patch_kernel_bands<float, 5, kSmallPatch>, ps, m, gx, gy, 1, block, s, ev);
 }
 
 hipError_t launch_narrow(const OpLaunch* Ls, int n, hipStream_t s, KernelEvents* ev) {
@@ -318,7 +318,7 @@ int narrow_describe(const OpLaunch* Ls, int n, char* name, size_t size) {
   }
   const bool big = patch > (size_t)kSmallPatch;
   if (name && size)
-    snprintf(name, size, "conv_narrow_kernel%s<float, %d, %d>", m > 1 ? "_bands" : "", big || 9 * Ls[0].x.c / 16 > kShortSteps ? 9 : 5,
+    snprintf(name, size, "conv_narrow_patch_kernel%s<float, %d, %d>", m > 1 ? "_bands" : "", big || 9 * Ls[0].x.c / 16 > kShortSteps ? 9 : 5,
              big ? kMaxPatch : kSmallPatch);
   return 1;
 }

@@ -370,13 +370,13 @@ __device__ __forceinline__ void patch_body(const PatchParams& p, const int bx, c
 constexpr int patch_loads(int tp, int s) { return s == 1 ? (tp == 4 ? 7 : tp == 2 ? 4 : 3) : 6; }
 constexpr int patch_room(int bm, int s) { return patch_loads(bm / 32, s) * 256 / kPixelSlots; }
 
-template <typename T, int BM, int BN, int NST, bool POOL, int S>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void conv_lds_kernel(const PatchParams p) {
+template <typename T, int BM, int BN, bool POOL, int S>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void conv_patch_kernel(const PatchParams p) {
   patch_body<T, BM / 32, BN / 32, patch_loads(BM / 32, S), POOL, S>(p, blockIdx.x, gridDim.x);
 }
 // The same for several bands of one layer in one grid (band b owns blocks first[b] .. first[b + 1] of x).
-template <typename T, int BM, int BN, int NST, bool POOL, int S>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void conv_lds_kernel_bands(const Batch<PatchParams> t) {
+template <typename T, int BM, int BN, bool POOL, int S>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void conv_patch_kernel_bands(const Batch<PatchParams> t) {
   const int b = batch_find(t, blockIdx.x);
   patch_body<T, BM / 32, BN / 32, patch_loads(BM / 32, S), POOL, S>(t.p[b], blockIdx.x - t.first[b], t.first[b + 1] - t.first[b]);
 }
@@ -473,16 +473,16 @@ hipError_t launch_tile(const OpLaunch* convs, const OpLaunch* pools, const OpLau
   if (m == 0) return hipSuccess;
   if (convs[0].sh == 1) {
     if (pools)
-      return launch_group(conv_lds_kernel<T, BM, BN, 2, true, 1>, conv_lds_kernel_bands<T, BM, BN, 2, true, 1>, ps, m, gx, gy, 1,
+      return launch_group(conv_patch_kernel<T, BM, BN, true, 1>, conv_patch_kernel_bands<T, BM, BN, true, 1>, ps, m, gx, gy, 1,
                           dim3(256), s, ev);
-    return launch_group(conv_lds_kernel<T, BM, BN, 2, false, 1>, conv_lds_kernel_bands<T, BM, BN, 2, false, 1>, ps, m, gx, gy, 1,
+    return launch_group(conv_patch_kernel<T, BM, BN, false, 1>, conv_patch_kernel_bands<T, BM, BN, false, 1>, ps, m, gx, gy, 1,
                         dim3(256), s, ev);
   }
   if constexpr (BM != 32) {
     return hipErrorInvalidValue;
   } else {
     if (pools) return hipErrorInvalidValue;
-    return launch_group(conv_lds_kernel<T, BM, BN, 2, false, 2>, conv_lds_kernel_bands<T, BM, BN, 2, false, 2>, ps, m, gx, gy, 1,
+    return launch_group(conv_patch_kernel<T, BM, BN, false, 2>, conv_patch_kernel_bands<T, BM, BN, false, 2>, ps, m, gx, gy, 1,
                         dim3(256), s, ev);
   }
 }
@@ -520,8 +520,10 @@ hipError_t launch_patch_siblings(const OpLaunch* convs, const OpLaunch* sibs, in
 
 int patch_describe(const OpLaunch* convs, const OpLaunch* pools, int n, char* name, size_t size) {
   const PatchChoice c = choose_patch(convs, pools, n);
+  int m = 0;
+  for (int b = 0; b < n; ++b) m += patch_work(convs[b], pools ? &pools[b] : nullptr).R > 0;
   if (name && size)
-    snprintf(name, size, "conv_lds_kernel%s<%s, %d, %d, 2, %s, %d>", n > 1 ? "_bands" : "",
+    snprintf(name, size, "conv_patch_kernel%s<%s, %d, %d, %s, %d>", m > 1 ? "_bands" : "",
              convs[0].dtype == LOP_BF16 ? "__bf16" : "float", c.bm, c.bn, pools ? "true" : "false", convs[0].sh);
   return 1;
 }

@@ -206,20 +206,20 @@ __device__ __forceinline__ void stem_body(const StemMfmaParams& p, const int bx)
 // stage 1.1 to 1.6 x the rows they need instead of 1.5 to 4.5 x (4 rows measured like 2 on the launches
 // between: 7 x 7 fp32 on 640 x 112 pixels 19.7 us against 19.3).
 template <typename T, int KJ, int S, int NT>
-__global__ __launch_bounds__(256) void conv_stem_kernel(const StemMfmaParams p) {
+__global__ __launch_bounds__(256) void conv_stem_mfma_kernel(const StemMfmaParams p) {
   stem_body<T, KJ / 3, S, NT, 2>(p, blockIdx.x);
 }
 template <typename T, int KJ, int S, int NT>
-__global__ __launch_bounds__(256) void conv_stem_kernel_bands(const Batch<StemMfmaParams> t) {
+__global__ __launch_bounds__(256) void conv_stem_mfma_kernel_bands(const Batch<StemMfmaParams> t) {
   const int b = batch_find(t, blockIdx.x);
   stem_body<T, KJ / 3, S, NT, 2>(t.p[b], blockIdx.x - t.first[b]);
 }
 template <typename T, int KJ, int S, int NT>
-__global__ __launch_bounds__(256) void conv_stem_lane_kernel(const StemMfmaParams p) {
+__global__ __launch_bounds__(256) void conv_stem_mfma_tall_kernel(const StemMfmaParams p) {
   stem_body<T, KJ / 3, S, NT, 8>(p, blockIdx.x);
 }
 template <typename T, int KJ, int S, int NT>
-__global__ __launch_bounds__(256) void conv_stem_lane_kernel_bands(const Batch<StemMfmaParams> t) {
+__global__ __launch_bounds__(256) void conv_stem_mfma_tall_kernel_bands(const Batch<StemMfmaParams> t) {
   const int b = batch_find(t, blockIdx.x);
   stem_body<T, KJ / 3, S, NT, 8>(t.p[b], blockIdx.x - t.first[b]);
 }
@@ -248,8 +248,8 @@ hipError_t launch_form(const OpLaunch* Ls, int n, bool large, hipStream_t s, Ker
   if (m == 0) return hipSuccess;
   const unsigned gy = (unsigned)(Ls[0].y.c / (32 * NT));
   if (large)
-    return launch_group(conv_stem_lane_kernel<T, 3 * KH, S, NT>, conv_stem_lane_kernel_bands<T, 3 * KH, S, NT>, ps, m, gx, gy, 1, dim3(256), s, ev);
-  return launch_group(conv_stem_kernel<T, 3 * KH, S, NT>, conv_stem_kernel_bands<T, 3 * KH, S, NT>, ps, m, gx, gy, 1, dim3(256), s, ev);
+    return launch_group(conv_stem_mfma_tall_kernel<T, 3 * KH, S, NT>, conv_stem_mfma_tall_kernel_bands<T, 3 * KH, S, NT>, ps, m, gx, gy, 1, dim3(256), s, ev);
+  return launch_group(conv_stem_mfma_kernel<T, 3 * KH, S, NT>, conv_stem_mfma_kernel_bands<T, 3 * KH, S, NT>, ps, m, gx, gy, 1, dim3(256), s, ev);
 }
 
 // 32-channel tiles per wavefront: the filter has to fit in registers (7 x 7 in fp32 is 84 per tile)
@@ -308,7 +308,7 @@ hipError_t launch_stem_mfma(const OpLaunch* Ls, int n, bool large, hipStream_t s
 }
 
 void stem_mfma_describe(const OpLaunch& L, bool large, const char* form, char* name, size_t size) {
-  snprintf(name, size, "conv_stem_%skernel%s<%s, %d, %d, %d>", large ? "lane_" : "", form, L.dtype == LOP_BF16 ? "__bf16" : "float",
+  snprintf(name, size, "conv_stem_mfma_%skernel%s<%s, %d, %d, %d>", large ? "tall_" : "", form, L.dtype == LOP_BF16 ? "__bf16" : "float",
            3 * L.kh, L.sh, stem_nt(L));
 }
 

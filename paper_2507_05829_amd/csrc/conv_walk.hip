@@ -261,14 +261,6 @@ __device__ __forceinline__ void walk_body(const PatchParams& p, const int bx, co
   store_out();
 }
 
-// The name of the form that takes pixels of 64 bytes, stride 1.
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void conv_regw_kernel(const PatchParams p) {
-  walk_body<64, 1, 1, false>(p, blockIdx.x, gridDim.x);
-}
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void conv_regw_kernel_bands(const Batch<PatchParams> t) {
-  const int b = batch_find(t, blockIdx.x);
-  walk_body<64, 1, 1, false>(t.p[b], blockIdx.x - t.first[b], t.first[b + 1] - t.first[b]);
-}
 template <int PIXB, int S, int WCO, bool POOL>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(PIXB == 64 ? 3 : 2))) void conv_walk_kernel(const PatchParams p) {
   walk_body<PIXB, S, WCO, POOL>(p, blockIdx.x, gridDim.x);
@@ -355,7 +347,8 @@ hipError_t launch_walk(const OpLaunch* convs, const OpLaunch* pools, int n, hipS
     gx[b] = (unsigned)(share >= kXcds && share < tiles ? share : tiles);
   }
   const dim3 block(256);
-  if (f.pixb == 64 && f.s == 1) return launch_group(conv_regw_kernel, conv_regw_kernel_bands, ps, m, gx, gy, 1, block, s, ev);
+  if (f.pixb == 64 && f.s == 1)
+    return launch_group(conv_walk_kernel<64, 1, 1, false>, conv_walk_kernel_bands<64, 1, 1, false>, ps, m, gx, gy, 1, block, s, ev);
   if (f.pixb == 64)
     return launch_group(conv_walk_kernel<64, 2, 2, false>, conv_walk_kernel_bands<64, 2, 2, false>, ps, m, gx, gy, 1, block, s, ev);
   if (f.s == 2)
@@ -370,10 +363,7 @@ int walk_describe(const OpLaunch* convs, const OpLaunch* pools, int n, char* nam
   int m = 0;
   for (int b = 0; b < n; ++b) m += patch_work(convs[b], pools ? &pools[b] : nullptr).R > 0;
   const char* const form = m > 1 ? "_bands" : "";
-  if (name && size) {
-    if (f.pixb == 64 && f.s == 1) snprintf(name, size, "conv_regw_kernel%s", form);
-    else snprintf(name, size, "conv_walk_kernel%s<%d, %d, %d, %s>", form, f.pixb, f.s, f.wco, pools ? "true" : "false");
-  }
+  if (name && size) snprintf(name, size, "conv_walk_kernel%s<%d, %d, %d, %s>", form, f.pixb, f.s, f.wco, pools ? "true" : "false");
   return 1;
 }
 

@@ -60,6 +60,7 @@ CONV_GRID = [
     (40, 24, 5, 1, 4, 2, (1, 12, 9)),      # dilated 5x5, K = 1000: half-filled last step
     (512, 24, 3, 1, 1, 1, (1, 30, 9)),     # K = 4608 on ~90 pixels: fp32 cut, bf16 16x16 tiles
     (1024, 40, 3, 1, 1, 1, (1, 6, 5)),     # K = 9216: cut across workgroups in both types
+    (128, 40, 3, 1, 2, 2, (1, 6, 5)),      # dilated: fp32 16x16 tiles whose input is fetched tap by tap
 ]
 
 
@@ -97,22 +98,32 @@ def test_conv_random_within_tolerance(oracle, cfg, dtype):
 
 
 LDS_GRID = [
-    # dtype, c_in, c_out, k, s, p, d, shape(n,h,w), residual
-    ("bf16", 64, 128, 3, 1, 1, 1, (1, 82, 106), False),    # 64 x 64 tiles, ragged last pixel tile
-    ("bf16", 128, 72, 3, 1, 1, 1, (2, 60, 74), True),      # channels not a multiple of the tile, residual, batch 2
-    ("bf16", 64, 256, 3, 2, 1, 1, (1, 127, 100), False),   # stride 2
-    ("bf16", 192, 64, 1, 2, 0, 1, (1, 180, 140), False),   # 1 x 1 stride 2: 3 stages (tail only), 32 x 64 tiles
-    ("bf16", 64, 64, 3, 1, 2, 2, (1, 100, 88), False),     # dilation 2
-    ("bf16", 64, 64, 3, 1, 1, 1, (1, 60, 120), True),      # 32 x 64 tiles with residual
-    ("f32", 32, 64, 3, 1, 1, 1, (1, 74, 90), True),        # fp32: 32 x 32 tiles, K = 288
-    ("f32", 64, 96, 3, 2, 1, 1, (2, 90, 80), False),
-    ("f32", 96, 32, 5, 1, 2, 1, (1, 80, 94), False),       # 5 x 5: 75 stages
-    ("bf16", 32, 32, 3, 1, 1, 1, (1, 90, 128), True),      # rows of 64 bytes: two taps per stage, 9 taps = 4.5 stages; 64 x 32 tiles
-    ("bf16", 32, 64, 3, 2, 1, 1, (2, 101, 77), False),     # ... stride 2, batch 2
-    ("bf16", 32, 96, 1, 2, 0, 1, (1, 140, 180), False),    # ... 1 x 1 stride 2: one tap, half a stage
-    ("bf16", 32, 64, 5, 1, 2, 1, (1, 60, 64), False),      # ... 5 x 5: 25 taps, kw odd
-    ("bf16", 32, 64, 3, 1, 2, 2, (1, 64, 60), False),      # ... dilation 2
-    ("f32", 16, 64, 3, 1, 1, 1, (1, 70, 66), False),       # fp32 rows of 64 bytes
+    # dtype, c_in, c_out, k, s, p, d, shape(n,h,w), residual, the kernel expected
+    ("bf16", 64, 128, 3, 1, 1, 1, (1, 82, 106), False, "conv_patch_kernel<__bf16, 64, 32, false, 1>"),   # (3 x 3 filters: the patch form)
+    ("bf16", 128, 72, 3, 1, 1, 1, (2, 60, 74), True, "conv_patch_kernel<__bf16, 64, 32, false, 1>"),
+    ("bf16", 64, 64, 3, 1, 1, 1, (1, 60, 120), True, "conv_patch_kernel<__bf16, 32, 32, false, 1>"),
+    ("f32", 32, 64, 3, 1, 1, 1, (1, 74, 90), True, "conv_patch_kernel<float, 32, 32, false, 1>"),
+    ("f32", 64, 96, 3, 2, 1, 1, (2, 90, 80), False, "conv_patch_kernel<float, 32, 32, false, 2>"),
+    ("bf16", 64, 128, 3, 1, 2, 2, (1, 82, 106), False, "conv_lds_kernel<__bf16, 64, 64, 4, false, 1>"),  # ragged last pixel tile
+    ("bf16", 128, 72, 5, 1, 2, 1, (2, 60, 74), True, "conv_lds_kernel<__bf16, 64, 64, 4, false, 1>"),    # channels not a multiple of the tile, residual, batch 2
+    ("bf16", 64, 256, 3, 2, 1, 1, (1, 127, 100), False, "conv_lds_kernel<__bf16, 32, 64, 4, false, 1>"),  # stride 2
+    ("bf16", 192, 64, 1, 2, 0, 1, (1, 180, 140), False, "conv_lds_kernel<__bf16, 32, 32, 4, false, 1>"),  # 1 x 1 stride 2: 3 stages (tail only)
+    ("bf16", 64, 64, 3, 1, 2, 2, (1, 100, 88), False, "conv_lds_kernel<__bf16, 32, 64, 4, false, 1>"),    # dilation 2
+    ("bf16", 64, 64, 3, 1, 2, 2, (1, 60, 120), True, "conv_lds_kernel<__bf16, 32, 32, 4, false, 1>"),     # with residual
+    ("bf16", 64, 24, 3, 1, 2, 2, (1, 131, 157), False, "conv_lds_kernel<__bf16, 64, 32, 4, false, 1>"),   # narrow layer, many pixels
+    ("f32", 32, 64, 3, 1, 2, 2, (1, 74, 90), True, "conv_lds_kernel<float, 32, 32, 8, false, 1>"),        # fp32: 32 x 32 tiles, K = 288
+    ("f32", 64, 96, 5, 2, 2, 1, (2, 90, 80), False, "conv_lds_kernel<float, 32, 32, 8, false, 1>"),
+    ("f32", 96, 32, 5, 1, 2, 1, (1, 80, 94), False, "conv_lds_kernel<float, 32, 32, 8, false, 1>"),       # 5 x 5: 75 stages
+    ("f32", 32, 24, 5, 1, 2, 1, (1, 131, 157), False, "conv_lds_kernel<float, 32, 32, 4, false, 1>"),     # more than one workgroup per compute unit
+    ("bf16", 32, 32, 3, 1, 1, 1, (1, 90, 128), True, "conv_lds_kernel<__bf16, 32, 32, 4, false, 2>"),     # rows of 64 bytes: two taps per stage, 9 taps = 4.5 stages
+    ("bf16", 32, 64, 3, 2, 1, 1, (2, 101, 77), False, "conv_lds_kernel<__bf16, 32, 32, 4, false, 2>"),    # ... stride 2, batch 2
+    ("bf16", 32, 96, 1, 2, 0, 1, (1, 140, 180), False, "conv_lds_kernel<__bf16, 32, 64, 4, false, 2>"),   # ... 1 x 1 stride 2: one tap, half a stage
+    ("bf16", 32, 64, 5, 1, 2, 1, (1, 60, 64), False, "conv_lds_kernel<__bf16, 32, 32, 4, false, 2>"),     # ... 5 x 5: 25 taps, kw odd
+    ("bf16", 32, 64, 3, 1, 2, 2, (1, 64, 60), False, "conv_lds_kernel<__bf16, 32, 32, 4, false, 2>"),     # ... dilation 2
+    ("bf16", 32, 24, 5, 1, 2, 1, (1, 131, 157), False, "conv_lds_kernel<__bf16, 64, 32, 4, false, 2>"),
+    ("bf16", 32, 72, 5, 1, 2, 1, (1, 101, 99), False, "conv_lds_kernel<__bf16, 64, 64, 4, false, 2>"),
+    ("f32", 16, 64, 3, 1, 1, 1, (1, 70, 66), False, "conv_lds_kernel<float, 32, 32, 8, false, 2>"),       # fp32 rows of 64 bytes
+    ("f32", 16, 24, 5, 1, 2, 1, (1, 131, 157), False, "conv_lds_kernel<float, 32, 32, 4, false, 2>"),
 ]
 
 
@@ -121,7 +132,7 @@ def test_lds_staged_kernel(oracle, cfg):
     """The mid-size kernel (global -> LDS loads, reduction split over the wavefronts): shapes
     that select it, checked by name, random values against the oracle within tolerance and small
     integers bit for bit, banded and in one band."""
-    dtype, c_in, c_out, k, s_, p_, d, shape, residual = cfg
+    dtype, c_in, c_out, k, s_, p_, d, shape, residual, kernel = cfg
     chain = _single(workloads.CONV, c_in, c_out, k, s_, p_, d, "relu", dtype, shape, n_bands=2,
                     residual=residual and c_in == c_out)
     if residual and c_in != c_out:       # a residual needs a same-shape source: 1 x 1 producer
@@ -135,7 +146,7 @@ def test_lds_staged_kernel(oracle, cfg):
         names = {plan.layer_kernel(b, l)[0] for b in range(plan.n_bands) for l in range(plan.n_layers)}
     finally:
         plan.destroy()
-    assert any(nm.startswith("conv_lds_kernel<") for nm in names), names
+    assert kernel in names, names
     want = oracle.run_chain(chain, t)
     for bands in (None, 1):
         dev, host = run_gpu(chain, t, n_bands=bands)
@@ -159,17 +170,16 @@ REGW_GRID = [
 
 @pytest.mark.parametrize("cfg", REGW_GRID)
 def test_filter_in_registers_kernel(oracle, cfg):
-    """The kernel for 64-byte pixels under a 3 x 3 filter at hundreds of thousands of pixels
-    (filter in registers, first tap straight from memory, the others from neighbouring lanes):
-    shapes that select it in one band and with all bands in one launch, checked by name, random
-    values against the oracle within tolerance and small integers bit for bit."""
+    """The walking kernel's form for 64-byte pixels under a 3 x 3 filter of stride 1 at hundreds of
+    thousands of pixels: shapes that select it in one band and with all bands in one launch, checked
+    by name, random values against the oracle within tolerance and small integers bit for bit."""
     c_out, p_, shape, residual, bands = cfg
     chain = _single(workloads.CONV, 32, c_out, 3, 1, p_, 1, "relu", "bf16", shape, n_bands=bands,
                     residual=residual)
     t = workloads.make_tensors(chain, zero_bias=False, seed=13)
     plan = lop.Plan(chain, t, 1)
     try:
-        assert plan.layer_kernel(0, plan.n_layers - 1)[0] == "conv_regw_kernel"
+        assert plan.layer_kernel(0, plan.n_layers - 1)[0] == "conv_walk_kernel<64, 1, 1, false>"
     finally:
         plan.destroy()
     want = oracle.run_chain(chain, t)
@@ -177,7 +187,7 @@ def test_filter_in_registers_kernel(oracle, cfg):
     np.testing.assert_array_equal(dev, host)
     assert rel_err(dev, want) <= TOL["bf16"]
     dev, host, names = _run_batched(chain, t, graph=0)
-    assert names[-1][0] == "conv_regw_kernel_bands", names
+    assert names[-1][0] == "conv_walk_kernel_bands<64, 1, 1, false>", names
     np.testing.assert_array_equal(dev, host)
     assert rel_err(dev, want) <= TOL["bf16"]
     ti = workloads.small_int_tensors(chain, seed=5)
@@ -194,14 +204,18 @@ def test_filter_in_registers_kernel(oracle, cfg):
 
 
 POOLED_GRID = [
-    # dtype, c_in, c_out, k, s, p, shape(n,h,w), bands, then a third layer behind the pooling?
-    ("bf16", 64, 128, 3, 1, 1, (1, 82, 106), 3, False),   # 64 x 64 tiles, ragged last tile
-    ("bf16", 64, 64, 3, 1, 1, (2, 37, 53), 2, True),      # odd height and width: last row and column unused; batch 2
-    ("bf16", 128, 72, 3, 1, 1, (1, 28, 28), 4, False),    # few pixels: 32 x 64 tiles; channels not a multiple of the tile
-    ("bf16", 64, 64, 1, 1, 0, (1, 40, 64), 2, True),      # 1 x 1: a single stage
-    ("bf16", 64, 96, 3, 2, 1, (1, 90, 70), 2, False),     # stride-2 conv in front of the pooling
-    ("f32", 32, 64, 3, 1, 1, (1, 50, 66), 2, True),       # fp32: 32 x 32 tiles
-    ("f32", 64, 40, 3, 1, 1, (2, 30, 34), 5, False),
+    # dtype, c_in, c_out, k, s, p, shape(n,h,w), bands, then a third layer behind the pooling?, the kernel expected
+    ("bf16", 64, 128, 3, 1, 1, (1, 82, 106), 3, False, "conv_patch_kernel<__bf16, 32, 32, true, 1>"),
+    ("bf16", 64, 64, 3, 1, 1, (2, 37, 53), 2, True, "conv_patch_kernel<__bf16, 32, 32, true, 1>"),       # odd height and width: last row and column unused; batch 2
+    ("f32", 32, 64, 3, 1, 1, (1, 50, 66), 2, True, "conv_patch_kernel<float, 32, 32, true, 1>"),
+    ("bf16", 128, 72, 3, 1, 1, (1, 28, 28), 4, False, "conv_lds_kernel<__bf16, 32, 32, 4, true, 1>"),    # few pixels; channels not a multiple of the tile
+    ("bf16", 64, 64, 1, 1, 0, (1, 40, 64), 2, True, "conv_lds_kernel<__bf16, 32, 32, 4, true, 1>"),      # 1 x 1: a single stage
+    ("bf16", 64, 96, 3, 2, 1, (1, 90, 70), 2, False, "conv_lds_kernel<__bf16, 32, 32, 4, true, 1>"),     # stride-2 conv in front of the pooling
+    ("bf16", 64, 72, 5, 1, 2, (1, 101, 99), 2, False, "conv_lds_kernel<__bf16, 64, 64, 4, true, 1>"),    # ragged last tile, odd sizes
+    ("bf16", 64, 24, 5, 1, 2, (1, 131, 157), 2, False, "conv_lds_kernel<__bf16, 64, 32, 4, true, 1>"),
+    ("bf16", 64, 128, 5, 1, 2, (1, 70, 66), 2, True, "conv_lds_kernel<__bf16, 32, 64, 4, true, 1>"),
+    ("f32", 64, 40, 3, 1, 1, (2, 30, 34), 5, False, "conv_lds_kernel<float, 32, 32, 8, true, 1>"),       # fp32: 32 x 32 tiles
+    ("f32", 32, 24, 5, 1, 2, (1, 131, 157), 2, False, "conv_lds_kernel<float, 32, 32, 4, true, 1>"),     # more than one workgroup per compute unit
 ]
 
 
@@ -212,7 +226,7 @@ def test_conv_with_pooling_in_one_launch(oracle, cfg, reuse):
     name; the conv itself launches nothing): random values against the oracle within tolerance,
     small integers bit for bit, equal to the layer-by-layer path within tolerance, as the
     chain's last layers (rows straight to the host) and with a layer behind them, in both modes."""
-    dtype, c_in, c_out, k, s_, p_, shape, bands, tail = cfg
+    dtype, c_in, c_out, k, s_, p_, shape, bands, tail, kernel = cfg
     chain = workloads.Chain("convpool", (shape[0], c_in, shape[1], shape[2]), dtype, bands)
     chain.add(workloads.CONV, c_in, c_out, k, s_, p_, 1, "relu")
     chain.add(workloads.MAXPOOL, c_out, c_out, 2, 2, 0)
@@ -224,8 +238,7 @@ def test_conv_with_pooling_in_one_launch(oracle, cfg, reuse):
     try:
         for b in range(plan.n_bands):
             assert plan.layer_kernel(b, 0)[0] == ""
-            nm = plan.layer_kernel(b, 1)[0]
-            assert nm.startswith("conv_lds_kernel<") and nm.endswith(", true, 1>"), nm
+            assert plan.layer_kernel(b, 1)[0] == kernel, b
     finally:
         plan.destroy()
     want = oracle.run_chain(chain, t)
@@ -250,7 +263,20 @@ STEM_GRID = [
     ("f32", 1, 32, 3, 1, 0, (1, 30, 40), 2),      # one input channel, no padding
     ("bf16", 4, 48, 3, 2, 0, (1, 51, 77), 1),     # four input channels, one band
     ("f32", 3, 32, 1, 1, 0, (1, 20, 30), 2),      # 1 x 1 over RGB
+    ("f32", 3, 16, 7, 2, 3, (1, 33, 70), 2),      # channels in 16s stay on the vector ALUs: unrolled row of 21
+    ("bf16", 3, 48, 7, 1, 3, (1, 30, 67), 2),
+    ("f32", 3, 48, 3, 1, 1, (2, 21, 66), 3),      # ... row of 9
+    ("bf16", 3, 16, 3, 2, 1, (1, 41, 70), 2),
 ]
+
+
+def _stem_kernel(cfg, large):
+    """Name (without its parameters) of the first-layer kernel of a grid row: on the matrix cores for 3 x 3
+    and 7 x 7 filters over three channels into a multiple of 32, else on the vector ALUs."""
+    c_in, c_out, k = cfg[1:4]
+    if c_in == 3 and c_out % 32 == 0 and k in (3, 7):
+        return "conv_stem_mfma_tall_kernel" if large else "conv_stem_mfma_kernel"
+    return "conv_stem_lane_kernel" if large else "conv_stem_kernel"
 
 
 STEM_LANE_GRID = [
@@ -260,13 +286,15 @@ STEM_LANE_GRID = [
     ("bf16", 3, 64, 3, 1, 1, (1, 500, 520), 4),    # stride 1, rows end 8 pixels into a tile
     ("f32", 3, 16, 5, 1, 2, (2, 300, 500), 2),     # 5 x 5: the generic loop, 16 channels per lane
     ("f32", 1, 32, 3, 1, 0, (1, 600, 500), 3),     # one input channel, no padding
+    ("f32", 3, 48, 7, 2, 3, (1, 700, 600), 2),     # channels in 16s stay on the vector ALUs: unrolled row of 21
+    ("bf16", 3, 48, 3, 2, 1, (1, 700, 602), 3),    # ... row of 9
 ]
 
 
 @pytest.mark.parametrize("cfg", STEM_LANE_GRID)
 def test_first_layer_kernel_at_large_sizes(oracle, cfg):
-    """First layers with thousands of 64-pixel tiles run on the form in which a lane owns a
-    pixel (checked by name), in one band and with all bands in one launch: random values against
+    """First layers with thousands of 64-pixel tiles run on the forms for large launches (taller tiles
+    on the matrix cores, else a lane per pixel; checked by name), in one band and with all bands in one launch: random values against
     the oracle within tolerance, small integers bit for bit."""
     dtype, c_in, c_out, k, s_, p_, shape, bands = cfg
     chain = workloads.Chain("stem", (shape[0], c_in, shape[1], shape[2]), dtype, bands)
@@ -274,7 +302,7 @@ def test_first_layer_kernel_at_large_sizes(oracle, cfg):
     t = workloads.make_tensors(chain, zero_bias=False, seed=37)
     plan = lop.Plan(chain, t, 1)
     try:
-        assert plan.layer_kernel(0, 0)[0].startswith("conv_stem_lane_kernel<"), plan.layer_kernel(0, 0)
+        assert plan.layer_kernel(0, 0)[0].startswith(_stem_kernel(cfg, True) + "<"), plan.layer_kernel(0, 0)
     finally:
         plan.destroy()
     want = oracle.run_chain(chain, t)
@@ -282,7 +310,7 @@ def test_first_layer_kernel_at_large_sizes(oracle, cfg):
     np.testing.assert_array_equal(dev, host)
     assert rel_err(dev, want) <= TOL[dtype]
     dev, host, names = _run_batched(chain, t, graph=0)
-    assert names[0][0].startswith("conv_stem_lane_kernel_bands<"), names
+    assert names[0][0].startswith(_stem_kernel(cfg, True) + "_bands<"), names
     np.testing.assert_array_equal(dev, host)
     assert rel_err(dev, want) <= TOL[dtype]
     ti = workloads.small_int_tensors(chain, seed=9)
@@ -297,7 +325,7 @@ def test_first_layer_kernel_at_large_sizes(oracle, cfg):
 @pytest.mark.parametrize("reuse", [0, 1])
 @pytest.mark.parametrize("cfg", STEM_GRID)
 def test_first_layer_kernel(oracle, cfg, reuse):
-    """Dense convs over at most four input channels run on the first-layer kernel (checked by
+    """Dense convs over at most four input channels run on the first-layer kernels (checked by
     name): random values against the oracle within tolerance, small integers bit for bit, alone
     (rows straight to the host) and with a layer behind, in both modes."""
     dtype, c_in, c_out, k, s_, p_, shape, bands = cfg
@@ -311,7 +339,7 @@ def test_first_layer_kernel(oracle, cfg, reuse):
         plan = lop.Plan(chain, t, None, flags)
         try:
             for b in range(plan.n_bands):
-                assert plan.layer_kernel(b, 0)[0].startswith("conv_stem_kernel<"), plan.layer_kernel(b, 0)
+                assert plan.layer_kernel(b, 0)[0].startswith(_stem_kernel(cfg, False) + "<"), plan.layer_kernel(b, 0)
         finally:
             plan.destroy()
         want = oracle.run_chain(chain, t)
@@ -339,7 +367,7 @@ def test_small_layer_kernel_is_selected():
                     name, slices = plan.layer_kernel(b, 0)
                     if name.startswith("conv_direct_kernel"):
                         seen.add((dtype, "cut" if slices > 1 else "one launch"))
-                    if name.startswith("conv_narrow_kernel"):
+                    if name.startswith("conv_narrow_kernel<"):
                         seen.add((dtype, "16x16 tiles"))
             finally:
                 plan.destroy()
@@ -1449,19 +1477,19 @@ def test_last_pass_over_fewer_images(oracle, shape, bands):
 
 PATCH_GRID = [
     # dtype, c_in, c_out, stride, pooled, shape(n,h,w), residual, the tile expected
-    ("bf16", 128, 128, 1, False, (2, 97, 211), True, "<__bf16, 128, 64, 2, false, 1>"),   # ragged in both directions, batch 2
-    ("bf16", 256, 72, 1, False, (1, 50, 70), False, "<__bf16, 64, 32, 2, false, 1>"),     # channels end inside a tile, four patches
-    ("bf16", 64, 200, 1, False, (1, 29, 31), False, "<__bf16, 32, 32, 2, false, 1>"),     # one patch, no next one
-    ("bf16", 64, 64, 1, False, (1, 1500, 2), True, "<__bf16, 32, 32, 2, false, 1>"),      # an image two pixels wide
-    ("bf16", 128, 136, 2, False, (1, 27, 45), False, "<__bf16, 32, 32, 2, false, 2>"),    # stride 2: even and odd columns apart
-    ("f32", 32, 40, 1, False, (1, 47, 61), False, "<float, 32, 32, 2, false, 1>"),
-    ("f32", 64, 64, 1, False, (2, 150, 170), True, "<float, 64, 32, 2, false, 1>"),
-    ("f32", 32, 64, 2, False, (1, 117, 107), False, "<float, 32, 32, 2, false, 2>"),
-    ("bf16", 64, 64, 1, True, (1, 131, 133), False, "<__bf16, 64, 32, 2, true, 1>"),      # odd sizes: last row and column unused
-    ("bf16", 128, 128, 1, True, (2, 181, 183), False, "<__bf16, 128, 64, 2, true, 1>"),
-    ("bf16", 512, 256, 1, True, (1, 15, 17), False, "<__bf16, 32, 32, 2, true, 1>"),
-    ("f32", 32, 40, 1, True, (1, 61, 67), False, "<float, 32, 32, 2, true, 1>"),
-    ("f32", 64, 64, 1, True, (2, 130, 150), False, "<float, 64, 32, 2, true, 1>"),
+    ("bf16", 128, 128, 1, False, (2, 97, 211), True, "<__bf16, 128, 64, false, 1>"),   # ragged in both directions, batch 2
+    ("bf16", 256, 72, 1, False, (1, 50, 70), False, "<__bf16, 64, 32, false, 1>"),     # channels end inside a tile, four patches
+    ("bf16", 64, 200, 1, False, (1, 29, 31), False, "<__bf16, 32, 32, false, 1>"),     # one patch, no next one
+    ("bf16", 64, 64, 1, False, (1, 1500, 2), True, "<__bf16, 32, 32, false, 1>"),      # an image two pixels wide
+    ("bf16", 128, 136, 2, False, (1, 27, 45), False, "<__bf16, 32, 32, false, 2>"),    # stride 2: even and odd columns apart
+    ("f32", 32, 40, 1, False, (1, 47, 61), False, "<float, 32, 32, false, 1>"),
+    ("f32", 64, 64, 1, False, (2, 150, 170), True, "<float, 64, 32, false, 1>"),
+    ("f32", 32, 64, 2, False, (1, 117, 107), False, "<float, 32, 32, false, 2>"),
+    ("bf16", 64, 64, 1, True, (1, 131, 133), False, "<__bf16, 64, 32, true, 1>"),      # odd sizes: last row and column unused
+    ("bf16", 128, 128, 1, True, (2, 181, 183), False, "<__bf16, 128, 64, true, 1>"),
+    ("bf16", 512, 256, 1, True, (1, 15, 17), False, "<__bf16, 32, 32, true, 1>"),
+    ("f32", 32, 40, 1, True, (1, 61, 67), False, "<float, 32, 32, true, 1>"),
+    ("f32", 64, 64, 1, True, (2, 130, 150), False, "<float, 64, 32, true, 1>"),
 ]
 
 
@@ -1479,7 +1507,7 @@ def test_patch_form_of_the_lds_staged_kernel(oracle, cfg):
     t = workloads.make_tensors(chain, zero_bias=False, seed=29)
     plan = lop.Plan(chain, t, 1)
     try:
-        assert plan.layer_kernel(0, plan.n_layers - 1)[0] == "conv_lds_kernel" + tile
+        assert plan.layer_kernel(0, plan.n_layers - 1)[0] == "conv_patch_kernel" + tile
     finally:
         plan.destroy()
     want = oracle.run_chain(chain, t)
@@ -1595,7 +1623,7 @@ def test_patch_form_of_the_narrow_kernel(oracle, cfg):
     t = workloads.make_tensors(chain, zero_bias=False, seed=29)
     plan = lop.Plan(chain, t, 1)
     try:
-        assert plan.layer_kernel(0, plan.n_layers - 1)[0] == "conv_narrow_kernel" + form
+        assert plan.layer_kernel(0, plan.n_layers - 1)[0] == "conv_narrow_patch_kernel" + form
     finally:
         plan.destroy()
     want = oracle.run_chain(chain, t)
@@ -1612,11 +1640,11 @@ def test_patch_form_of_the_narrow_kernel(oracle, cfg):
 
 GEMM_GRID = [
     # dtype, m, k, n, residual, the tile expected
-    ("bf16", 8 * 256 * 2 + 37, 136, 8 * 256 - 8, True, "<__bf16, 256, 256>"),   # ragged rows and channels, the last stage holds one chunk
-    ("bf16", 4300, 328, 1288, False, "<__bf16, 128, 256>"),                      # three stages, as many as are kept in flight
-    ("bf16", 9000, 512, 360, True, "<__bf16, 128, 64>"),
-    ("f32", 1300, 72, 1300, True, "<float, 64, 64>"),
-    ("f32", 4100, 92, 4100, False, "<float, 128, 128>"),
+    ("bf16", 8 * 256 * 2 + 37, 136, 8 * 256 - 8, True, "<__bf16, 256, 256, 2, 4, 2>"),   # ragged rows and channels, the last stage holds one chunk
+    ("bf16", 4300, 328, 1288, False, "<__bf16, 128, 256, 2, 4, 3>"),                      # three stages, as many as are kept in flight
+    ("bf16", 9000, 512, 360, True, "<__bf16, 128, 64, 2, 2, 3>"),
+    ("f32", 1300, 72, 1300, True, "<float, 64, 64, 2, 2, 3>"),
+    ("f32", 4100, 92, 4100, False, "<float, 128, 128, 2, 2, 2>"),
 ]
 
 
