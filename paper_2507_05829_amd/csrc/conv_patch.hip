@@ -410,9 +410,13 @@ constexpr long kF32MinTiles = 100;
 // bf16: a handful of compute units cannot stream megabytes of filter (7 x 7 x 512 channels is 32 tiles: 5.6 us
 // here, 8.9 there)
 constexpr long kBf16MinTiles = 24;
-// Stride 2: a patch is four times the outputs, so the tile's memory holds one workgroup per compute
-// unit; the kernel that fetches taps (2.25 per output) wins once there is more than one each
-// (64 -> 128 channels on 14 400 pixels 8.3 us there, 10.4 here; 128 -> 256 on 143 5.9 there, 4.1 here)
+// Stride 2: a patch is four times the outputs, so a tile fetches nearly twice what the kernel that fetches taps does per
+// output (2.25 of them) and gains by waiting for them once instead of nine times. bf16 launches use this form up to
+// one tile per compute unit, fp32 ones up to four. Measured alone, there -> here (us): bf16 128 -> 256 channels on 1 800
+// pixels (456 tiles) 7.7 -> 5.7, 3 600 (904) 9.7 -> 9.3, 7 200 (1 800) 12.9 -> 15.6; 256 -> 512 on 900 (464) 12.0 -> 8.0, on
+// 1 800 (912) 15.6 -> 13.2; 64 -> 64 on 7 200 (450) 5.0 -> 4.5. fp32 64 -> 128 on 10 400 (1 300) 28.2 -> 23.0, on
+// 25 600 (3 200) 55.8 -> 47.5; 256 -> 512 on 4 900 (2 464) 187 -> 125. So both lines lie lower than where the two are level
+// (bf16 about 900 tiles, fp32 above 3 200). The tile's memory is not what draws them: three workgroups fit a compute unit.
 constexpr long kStride2MaxTiles = kPatchUnits;
 
 PatchChoice choose_patch(const OpLaunch* convs, const OpLaunch* pools, int n) {
