@@ -9,9 +9,11 @@ region is exactly --steps steps between two full synchronisations; it is repeate
 five times and until half a second has been timed) and the median region is reported.
 
 The headline is the 224 x 224 ResNet-18-style chain in four INDEPENDENT row bands (every band
-recomputes its halo rows); the same chain in reuse mode, the 720p encoder in both modes, the
-other chains, the one-band reference and single-request latency of each, the per-launch
-roofline table and the CPU oracle's speed are fields of the same JSON line.
+recomputes its halo rows). The one JSON line on stdout holds it with its roofline, latency and
+copy figures, the images per second of the other chains and modes, and the CPU oracle's speed, in
+less than 2 000 characters (what reads it may keep no more than the end of the output).
+--detail FILE writes everything measured: every result, its per-launch roofline table and the
+one-band references.
 """
 import argparse
 import hashlib
@@ -53,6 +55,7 @@ def parse():
     ap.add_argument("--only-kernel-table", action="store_true",
                     help="run only the one-lane pass that times every launch (the command the "
                          "rocprofv3 kernel-trace summaries under profiles/ are taken with)")
+    ap.add_argument("--detail", metavar="FILE", help="write every result with its per-launch tables there (JSON)")
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--cpu-seconds", type=float, default=12.0)
     ap.add_argument("--profile-iters", type=int, default=10)
@@ -111,6 +114,7 @@ class Case:
             n_buf = 2
         self.d_out = [torch.zeros((n, h, w, c), dtype=td, device="cuda") for _ in range(n_buf)]
         self.h_out = [torch.zeros((n, h, w, c), dtype=td, pin_memory=True) for _ in range(n_buf)]
+        self.lanes = a.lanes or 4   # (LOP_DEFAULT_LANES)
         self.images = 1 if rowwise else self.chain.in_shape[0]   # a matrix counts as one image
         torch.cuda.synchronize()
 
@@ -174,8 +178,9 @@ def weight_bytes(chain, l):
 
 def merged_twin(case, torch, lop, workloads, a):
     """The plan whose launches are the ones run_chain enqueues for `case`: all bands of a layer in one launch
-    (independent bands: the batched plan, if its launches have such a form; shared rows: one band),
-    or None where the case's own per-band launches are all there is."""
+    (independent bands: the batched plan, if there can be one; shared rows: one band). None: the table
+    times the launches of single bands. That is what a chain that runs band by band makes; a chain with
+    inverted-residual blocks merges its bands in passes over the images, which no plan's table times."""
     if case.mode == "batched":
         return None
     try:
@@ -274,22 +279,37 @@ def strip(rows):
 
 
 def single_request(case, n=30):
-    """One chain at a time, host clock around launch .. last byte on the host."""
+    """One chain at a time, host clock around call .. last byte on the host: the launches that the
+    stream of chains above makes. A timed call runs the bands of most plans one by one, each with a
+    start and an end of its own: band_by_band is that schedule's latency and when its first and
+    its last band are on the host."""
     plan = case.plan
-    lat, lat_nc, first, last = [], [], [], []
+
+    def once(host):
+        t0 = time.perf_counter()
+        plan.run_chain(case.d_in, case.d_out[0], host)
+        plan.synchronize()
+        return (time.perf_counter() - t0) * 1e3
+
+    for host in (case.h_out[0], None):
+        for _ in range(2 * case.lanes):   # (a graph per lane and set of buffers is captured first)
+            once(host)
+    lat, lat_nc, banded, first, last = [], [], [], [], []
+    for _ in range(n):
+        lat.append(once(case.h_out[0]))
+        lat_nc.append(once(None))
     for _ in range(n):
         tm = plan.run_chain(case.d_in, case.d_out[0], case.h_out[0], timing=True)
-        lat.append(tm.wall_ms)
+        banded.append(tm.wall_ms)
         ready = [tm.band_ready_ms[b] for b in range(plan.n_bands) if tm.band_ready_ms[b] > 0]
         first.append(min(ready))
         last.append(max(ready))
-        tm = plan.run_chain(case.d_in, case.d_out[0], None, timing=True)
-        lat_nc.append(tm.wall_ms)
     q = lambda v, f: sorted(v)[min(len(v) - 1, int(len(v) * f))]
     return dict(latency_ms=round(statistics.median(lat), 4), latency_ms_p10=round(q(lat, 0.1), 4),
                 latency_ms_p90=round(q(lat, 0.9), 4), latency_ms_no_d2h=round(statistics.median(lat_nc), 4),
-                first_band_on_host_ms=round(statistics.median(first), 4),
-                last_band_on_host_ms=round(statistics.median(last), 4))
+                band_by_band=dict(latency_ms=round(statistics.median(banded), 4),
+                                  first_band_on_host_ms=round(statistics.median(first), 4),
+                                  last_band_on_host_ms=round(statistics.median(last), 4)))
 
 
 def measure(torch, lop, workloads, name, mode, a, steps, warmup, link_gbs, nofuse=False, tables=True,
@@ -340,9 +360,9 @@ def measure(torch, lop, workloads, name, mode, a, steps, warmup, link_gbs, nofus
     extra_us = (s["latency_ms"] - s["latency_ms_no_d2h"]) * 1e3
     res["d2h"]["single_request_extra_us"] = round(extra_us, 2)
     res["d2h"]["hidden_single_vs_link_rate"] = round(1.0 - max(0.0, extra_us) / copy_us_link, 4)
-    res["d2h"]["hidden_single_bound"] = round((plan.n_bands - 1) / plan.n_bands, 4)
     twin = merged_twin(case, torch, lop, workloads, a)
     rows, ridge, mf_peak = launch_rows(twin or case, a.profile_iters)
+    res["table_times"] = "merged launches" if twin or mode == "batched" else "launches of single bands"
     if twin:
         twin.close()
     groups = kernel_groups(rows, chain.dtype)
@@ -510,6 +530,10 @@ def main():
 
     chain = head_case.chain
     dense = head.get("dense_conv", {})
+    modes = {a.mode: head, **seconds}
+    roof = {k: head["roofline"][k] for k in ("bound", "achieved", "peak", "unit", "frac", "traffic", "kernel", "avg_us",
+                                             "measured_peak", "frac_of_measured", "frac_ceiling_at_this_launch_size")}
+    single = head["single_request"]
     line = {
         "metric": "images/sec for banded conv chain (independent row bands, steady state, per-band D2H pipelined)",
         "value": head["images_per_s"], "unit": "images/s",
@@ -519,15 +543,11 @@ def main():
         "dtype": "f32" if chain.dtype == "f32" else "bf16", "data": "synthetic",
         "config": {"workload": f"{a.workload} {'x'.join(map(str, chain.in_shape))} {chain.dtype}, "
                                f"{head['n_bands']} row bands, {head['n_layers']} layers",
-                   "mode": {"independent": "independent: every band recomputes its halos, one launch per band and layer",
-                            "batched": "independent bands (every band recomputes its halos), one launch per layer for "
-                                       "all bands (operation batching, Sec. IV-D)",
-                            "reuse": "reuse: bands in order, rows produced by earlier bands are reused"}[a.mode],
-                   "chains_per_step": head["chains_per_step"], "images_per_chain": head["images_per_chain"],
-                   "timed_region": f"{a.steps} steps, median of {head['repeats']} repeats",
+                   "mode": a.mode, "chains_per_step": head["chains_per_step"],
+                   "images_per_chain": head["images_per_chain"], "repeats": head["repeats"],
                    "executed_over_useful_flop": head["executed_over_useful"],
                    "hip_graph": bool(a.graph), "lanes": a.lanes or "default"},
-        "roofline": head["roofline"],
+        "roofline": roof,
         # the other two figures the metric names: algorithmic FLOP of the dense convolutions over
         # their kernel time against the matrix-core peak of the type, and the share of the
         # output's link time (bytes / measured D2H rate) that did not lengthen the chain
@@ -536,15 +556,23 @@ def main():
         # image is 1-2 us at the link's rate, which a difference of two timed runs cannot resolve)
         "d2h_hidden": None if head["d2h"]["within_noise"] else head["d2h"]["hidden_vs_link_rate"],
         "d2h_exposed_us_per_chain": head["d2h"]["exposed_us_per_chain"],
+        "latency_ms": single["latency_ms"], "latency_ms_no_d2h": single["latency_ms_no_d2h"],
+        "first_band_on_host_ms": single["band_by_band"]["first_band_on_host_ms"],
         # the same independent bands with every layer launched once for all bands (operation
-        # batching, Sec. IV-D), and reuse mode: detail under "modes"
-        "images_per_s_by_mode": {m: r["images_per_s"] for m, r in {a.mode: head, **seconds}.items()},
-        "measured_ceilings": ceil,
-        "modes": {a.mode: head, **seconds},
-        "also": also,
+        # batching, Sec. IV-D), and reuse mode
+        "images_per_s_by_mode": {m: r["images_per_s"] for m, r in modes.items()},
+        "also_images_per_s": {e: {m: r["images_per_s"] for m, r in per.items()} for e, per in also.items()},
     }
     if not a.no_cpu_baseline:
-        line["cpu_baseline"] = cpu_baseline(chain, head_case.tensors, a.cpu_seconds)
+        cpu = cpu_baseline(chain, head_case.tensors, a.cpu_seconds)
+        line["cpu_baseline"] = {k: cpu[k] for k in ("value", "unit", "cores", "kind")}
+    if a.detail:
+        with open(a.detail, "w") as f:
+            json.dump({**line, "roofline": head["roofline"], "measured_ceilings": ceil, "modes": modes, "also": also,
+                       "cpu_baseline": None if a.no_cpu_baseline else cpu}, f)
+    for extra in ("also_images_per_s", "first_band_on_host_ms"):   # (names of other workloads can be longer)
+        if len(json.dumps(line)) >= 2000:
+            del line[extra]
     print(json.dumps(line))
 
 
