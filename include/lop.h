@@ -111,9 +111,9 @@ typedef struct {
                                  its rows for every band (each band on its own slabs), and chains
                                  of consecutive calls rotate over the lanes. The bands' rows leave
                                  behind the last layer's launch. Not with LOP_FLAG_REUSE; at most
-                                 16 bands; LOP_ERR_UNSUPPORTED if an operator of the chain has no
-                                 kernel form that takes several bands (the inverted-residual
-                                 block, the 1x1 streaming and 3x3 depthwise kernels)      */
+                                 16 bands; LOP_ERR_UNSUPPORTED if the chain has an inverted-residual
+                                 block or an operator whose kernel takes one band at a time
+                                 (the 1x1 streaming and 3x3 depthwise kernels)            */
 #define LOP_FLAG_NO_FUSE 32u  /* run every layer as a launch of its own. By default a 1x1 conv,
                                  a 3x3 depthwise conv and a 1x1 conv in a row whose middle
                                  tensors nobody else reads (an inverted-residual block) run as
