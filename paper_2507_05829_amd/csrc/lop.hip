@@ -1742,6 +1742,8 @@ int lop_synchronize(lop_plan_t* P) {
   if (!P) return LOP_ERR_INVALID_ARG;
   if (!P->ready) return LOP_ERR_NOT_READY;
   if (P->last_user_stream) LOP_HIP(hipStreamSynchronize(P->last_user_stream));
+  for (int b = 0; b < P->t.n_bands; ++b)   // copies of single bands, on streams of the caller's
+    if (P->copied_valid[b]) LOP_HIP(hipEventSynchronize(P->ev_copied[b]));
   for (Lane& L : P->lanes) {
     if (L.user) LOP_HIP(hipEventSynchronize(L.ev_join));
     LOP_HIP(hipStreamSynchronize(L.stream));

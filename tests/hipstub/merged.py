@@ -247,7 +247,34 @@ def grids():
     return bad
 
 
-bad = {"grids": grids, "poison": poison, "order_of_streams": order_of_streams, "workspace": workspace, "wide_tiles": wide_tiles, "static_scratch": static_scratch}[check]()
+def pinned(nbytes):
+    buf = np.zeros(nbytes + 16, np.uint8)
+    stub.hipstub_pin(ctypes.c_void_p(buf.ctypes.data), ctypes.c_size_t(buf.nbytes))
+    return buf, (buf.ctypes.data + 15) & ~15
+
+
+def copy_streams():
+    """lop_synchronize also waits for the copy streams that lop_run_band was given."""
+    chain = layer_by_layer(8)
+    plan, probe = lop.Plan(chain, ZeroWeights(chain), None, lop.LOP_FLAG_NO_FUSE), make(workloads.tiny_chain(), 0)
+    buf, host = pinned(int(np.prod(plan.out_shape())) * 4)
+    compute, copies = new_stream(), new_stream()
+    for b in range(plan.n_bands):
+        plan.run_band(b, TENSOR, TENSOR, host, compute, copies)
+    stub.hipstub_mark(copies)
+    plan.synchronize()
+    probe.run_chain(TENSOR, TENSOR)       # whatever comes after the wait is behind the copies
+    bad = [stub.hipstub_unordered()] if stub.hipstub_unordered() else []
+    stub.hipstub_mark(None)
+    probe.destroy()
+    plan.destroy()
+    stub.hipstub_unpin(ctypes.c_void_p(buf.ctypes.data))
+    for s in (compute, copies):
+        stub.hipStreamDestroy(s)
+    return bad
+
+
+bad = {"copy_streams": copy_streams, "grids": grids, "poison": poison, "order_of_streams": order_of_streams, "workspace": workspace, "wide_tiles": wide_tiles, "static_scratch": static_scratch}[check]()
 for b in bad:
     print("FAILED", b, flush=True)
 print("CHECK %s" % ("FAILED" if bad else "OK"), flush=True)
