@@ -1765,6 +1765,7 @@ int lop_time_layer(lop_plan_t* P, int band, int layer, const void* d_in, void* d
   const lop_rows_t r = launch_rows(P, band_fusion(P), band, layer);
   if (r.hi <= r.lo) return LOP_OK;
   int rc = ensure_timing_events(P);
+  if (rc == LOP_OK) rc = lop_synchronize(P);   // (a chain in flight may be using the lane's scratch)
   if (rc != LOP_OK) return rc;
   hipStream_t cs = P->s_main;
   LOP_HIP(launch_layer(P, band_fusion(P), band, layer, d_in, d_out, cs));  // warm-up

@@ -274,7 +274,21 @@ def copy_streams():
     return bad
 
 
-bad = {"copy_streams": copy_streams, "grids": grids, "poison": poison, "order_of_streams": order_of_streams, "workspace": workspace, "wide_tiles": wide_tiles, "static_scratch": static_scratch}[check]()
+def timed_layer():
+    """lop_time_layer waits for what the plan has in flight before it uses a lane's scratch."""
+    chain = layer_by_layer(2)
+    plan, user = lop.Plan(chain, ZeroWeights(chain)), new_stream()
+    plan.run_chain(TENSOR, TENSOR, None, user)
+    stub.hipstub_mark(user)
+    plan.time_layer(0, plan.n_layers - 1, TENSOR, TENSOR, 2)
+    bad = [stub.hipstub_unordered()] if stub.hipstub_unordered() else []
+    stub.hipstub_mark(None)
+    plan.destroy()
+    stub.hipStreamDestroy(user)
+    return bad
+
+
+bad = {"copy_streams": copy_streams, "timed_layer": timed_layer, "grids": grids, "poison": poison, "order_of_streams": order_of_streams, "workspace": workspace, "wide_tiles": wide_tiles, "static_scratch": static_scratch}[check]()
 for b in bad:
     print("FAILED", b, flush=True)
 print("CHECK %s" % ("FAILED" if bad else "OK"), flush=True)
