@@ -1234,11 +1234,15 @@ int enqueue_chain_merged(lop_plan_t* P, Lane& L, const void* d_in, void* d_out, 
 }
 
 // Orders stream `s` behind everything that may still use the lane's scratch and notes that `s` uses it
-// next.
-int take_lane(Lane& L, hipStream_t s) {
+// next. waited (optional): the event that `s` waited for last, so that lanes sharing one cost one wait.
+int take_lane(Lane& L, hipStream_t s, hipEvent_t* waited = nullptr) {
   if (L.user || s != L.stream) {   // (else stream order does it)
-    if (!L.user) LOP_HIP(hipEventRecord(L.ev_join, L.stream));
-    LOP_HIP(hipStreamWaitEvent(s, L.ev_join, 0));
+    if (!L.user) {
+      LOP_HIP(hipEventRecord(L.ev_join, L.stream));
+      L.left = L.ev_join;
+    }
+    if (!waited || *waited != L.left) LOP_HIP(hipStreamWaitEvent(s, L.left, 0));
+    if (waited) *waited = L.left;
   }
   L.user = s == L.stream ? nullptr : s;
   return LOP_OK;
@@ -1246,8 +1250,17 @@ int take_lane(Lane& L, hipStream_t s) {
 
 // Marks the end of a use of the lane's scratch on a stream that is not the lane's own.
 int leave_lane(Lane& L) {
-  if (L.user) LOP_HIP(hipEventRecord(L.ev_join, L.user));
+  if (!L.user) return LOP_OK;
+  LOP_HIP(hipEventRecord(L.ev_join, L.user));
+  L.left = L.ev_join;
   return LOP_OK;
+}
+
+// ... and of a use of all lanes by one stream.
+int leave_lanes(lop_plan_t* P) {
+  const int rc = leave_lane(P->lanes[0]);
+  for (Lane& L : P->lanes) L.left = P->lanes[0].left;
+  return rc;
 }
 
 // The bands of lane `lane` of an independent-mode chain, in order, on that lane's stream.
@@ -1635,9 +1648,10 @@ int lop_run_chain(lop_plan_t* P, const void* d_in, void* d_out, void* h_out, voi
   // (one graph of all bands runs on `ms` itself, with every lane's scratch)
   const bool lanes_in_graph = !merged && !P->t.reuse && (P->flags & LOP_FLAG_GRAPH) && !timing &&
                               (compute_stream || P->n_lanes() == 1) && !(P->copy_lane && copy && !compute_stream);
+  hipEvent_t waited = nullptr;
   if (!merged)
     for (Lane& L : P->lanes) {   // a band or a chain on a caller's stream may still use a lane's scratch
-      int rc = take_lane(L, lanes_in_graph ? ms : L.stream);
+      int rc = lanes_in_graph ? take_lane(L, ms, &waited) : take_lane(L, L.stream);
       if (rc != LOP_OK) return rc;
     }
   if (P->copy_lane && copy && !compute_stream && !timing) {
@@ -1688,11 +1702,8 @@ int lop_run_chain(lop_plan_t* P, const void* d_in, void* d_out, void* h_out, voi
     }
     if (lanes_in_graph) {
       int rc = launch_graph(P, d_in, d_out, h_out, ms);
-      for (Lane& L : P->lanes) {   // (also after an error: a capture may have used the lanes' events)
-        const int left = leave_lane(L);
-        rc = rc == LOP_OK ? left : rc;
-      }
-      return rc;
+      const int left = leave_lanes(P);   // (also after an error: a capture may have used the lanes' events)
+      return rc == LOP_OK ? left : rc;
     }
     if (timing) LOP_HIP(hipEventRecord(P->ev_t0, ms));
     int rc = enqueue_chain(P, d_in, d_out, h_out, ms, timing != nullptr, false);
@@ -1745,7 +1756,7 @@ int lop_synchronize(lop_plan_t* P) {
   for (int b = 0; b < P->t.n_bands; ++b)   // copies of single bands, on streams of the caller's
     if (P->copied_valid[b]) LOP_HIP(hipEventSynchronize(P->ev_copied[b]));
   for (Lane& L : P->lanes) {
-    if (L.user) LOP_HIP(hipEventSynchronize(L.ev_join));
+    if (L.user) LOP_HIP(hipEventSynchronize(L.left));
     LOP_HIP(hipStreamSynchronize(L.stream));
     LOP_HIP(hipStreamSynchronize(L.copy));
   }

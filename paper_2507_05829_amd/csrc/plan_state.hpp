@@ -28,9 +28,11 @@ struct Lane {
   void* arena = nullptr;    // scratch slabs of one band (or of one whole chain) at a time
   void* conv_ws = nullptr;  // split-K partial sums of one launch at a time
   hipEvent_t ev_join = nullptr;
-  // The stream of the caller's that last used this lane's scratch (ev_join was recorded behind
-  // that use), or nullptr when the lane's own stream did.
+  // The stream of the caller's that last used this lane's scratch, or nullptr when the lane's own stream
+  // did; left: the event recorded behind that use, this lane's ev_join or, of a use of all lanes, the
+  // first one's (which is recorded again only behind whatever comes after that use on the first lane).
   hipStream_t user = nullptr;
+  hipEvent_t left = nullptr;
 };
 
 // Layers that run as one launch: head[t] = first layer of the group whose last layer is t
