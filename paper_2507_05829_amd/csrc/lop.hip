@@ -399,11 +399,12 @@ size_t merged_workspace(lop_plan_t* P) {
 // runs band by band: its launches are long enough by themselves.
 constexpr size_t kMergeMaxBytes = LOP_STATIC_SCRATCH_BYTES;
 // A chain of row-wise operators has no halo, and callers that stream matrix rows run its bands one
-// by one: below this many rows its chain runs the bands' own launches, so that its sums are those of
-// lop_run_band in the same order. That is the only reason: merged it would be faster at every size below
-// the line (us a call with calls in flight, band by band -> merged; bf16 1024 -> 4096 -> 1024 columns in four
-// bands: 256 rows 61 -> 20, 1 000 68 -> 32, 2 047 85 -> 58; fp32 512 -> 2048 -> 512: 1 000 rows 70 -> 43).
-constexpr int kMergeMinRows = 2048;
+// by one: a chain of few products (rows x columns in x columns out of its largest layer) runs the bands' own
+// launches, so that its sums are those of lop_run_band in the same order. That is the only reason: merged it
+// is faster at every size (us a call with calls in flight, band by band -> merged; bf16 1024 -> 4096 -> 1024
+// columns in four bands: 256 rows 61 -> 20, 1 000 68 -> 32, 2 047 85 -> 58; fp32 512 -> 2048 -> 512: 1 000 rows
+// 70 -> 43).
+constexpr size_t kMergeMinProducts = (size_t)1 << 27;
 
 void size_scratch(lop_plan_t* P) {
   const lop::Tables& t = P->t;
@@ -483,8 +484,10 @@ void size_scratch(lop_plan_t* P) {
     merge(ChainSched::kGrouped, n, nb, place_groups(n, nb, chain_keeps, &P->chain_off), true);
     return;
   }
-  const bool rows_only = t.in.w == 1 && n * t.in.h < kMergeMinRows;
-  if ((P->flags & LOP_FLAG_PLAN_ONLY) || (rows_only && nb > 1)) return;
+  size_t products = 0;
+  for (const lop::LayerInfo& L : t.layers) products = std::max(products, (size_t)n * L.h_out * L.d.c_in * L.d.c_out);
+  const bool few_rows = t.in.w == 1 && products < kMergeMinProducts;
+  if ((P->flags & LOP_FLAG_PLAN_ONLY) || (few_rows && nb > 1)) return;
   const bool whole = t.disjoint();
   // A pass over few rows whose launches take one band each is a crowd of small launches on one lane: eight bands
   // and eight images of the inverted-residual chain layer by layer took 3.3 ms that way, band by band 2.2.

@@ -930,6 +930,23 @@ def test_rowwise_chain_in_passes_over_its_rows(oracle, dtype, bands, flags):
     assert rel_err(dev[rows], want) <= TOL[dtype]
 
 
+@pytest.mark.parametrize("dtype,shape,flags", [("f32", (257, 512, 1028, 5), 0), ("bf16", (300, 256, 2048, 7), lop.LOP_FLAG_REUSE),
+                                               ("bf16", (1031, 1000, 136, 8), lop.LOP_FLAG_GRAPH)])
+def test_rowwise_chain_of_few_rows_is_merged(oracle, dtype, shape, flags):
+    """Few rows, but just more than 2^27 products in the largest layer: one launch per layer. Against
+    the oracle, and against the bands one by one."""
+    m, k, hidden, bands = shape
+    assert 1 << 27 <= m * k * hidden < 1.25 * (1 << 27)
+    chain = workloads.RowChain("rows", m, k, dtype, bands)
+    chain.add(hidden, "relu").add(k, "none", residual_from=-1)
+    t = workloads.make_row_tensors(chain, zero_bias=False, seed=37)
+    dev, host, _ = _run_rows(chain, t, flags=flags)
+    np.testing.assert_array_equal(dev, host)
+    assert rel_err(dev, oracle.run_row_chain(chain, t)) <= TOL[dtype]
+    one_by_one, _, _ = _run_rows(chain, t, flags=flags, order=list(range(bands)))
+    assert rel_err(dev, one_by_one) <= TOL[dtype]
+
+
 # ---- seeded random shapes: every kernel choice the library can make, against the oracle ----
 
 _SKIP_RANDOM_F32 = (
