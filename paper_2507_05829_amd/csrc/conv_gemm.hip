@@ -23,6 +23,7 @@
 
 #include "act.hpp"
 #include "conv_common.hpp"
+#include "conv_split.hpp"
 #include "kernels.hpp"
 #include "launch.hpp"
 #include "lop.h"
@@ -36,6 +37,7 @@ struct GemmParams {
   void* y2;        // second destination with y's layout, or nullptr
   const void* res;
   const void* w;   // [c_out_pad][k_pad]
+  const void* w3;  // the same weights as three bf16 parts in operand order (fp32 layers)
   const float* bias;
   int x_row0, x_rows, W, K;          // K: channels in
   int y_row0, y_rows, W_out, C_out;
@@ -47,6 +49,67 @@ struct GemmParams {
 static_assert(sizeof(Batch<GemmParams>) <= 4096, "the parameters of all bands of a launch travel as kernel arguments");
 
 constexpr unsigned kOutside = 0x80000000u;
+constexpr int gemm_pitch(int tn) { return tn * 32 + 4; }   // fp32 elements of a row of a wavefront's staged output tile
+
+// What follows the sums: one 32-pixel tile of the wavefront at a time through LDS, so that consecutive lanes
+// own consecutive 16-byte pieces of a pixel's channels. (The caller's barrier lies between smem's last readers and this.)
+template <typename T, int TM, int TN>
+__device__ __forceinline__ void gemm_epilogue(const GemmParams& p, unsigned char* smem, const f32x16 (&acc)[TN][TM], int m0, int co0,
+                                              int wave, int wm, int wn, int lane) {
+  constexpr int CPW = gemm_pitch(TN);
+  constexpr int VE = 16 / (int)sizeof(T);
+  constexpr int CPR = TN * 32 / VE;          // pieces per pixel of the wavefront's tile
+  float* const Cw = (float*)smem + wave * (32 * CPW);
+  const Clamp cl = make_clamp(p.act);
+#pragma unroll
+  for (int tm = 0; tm < TM; ++tm) {
+    constexpr int PIECES = 32 * CPR / 64;
+    // the residual's pieces (and where they go) first: their latency passes under the exchange
+    size_t ya[PIECES];
+    u32x4 rr[PIECES];
+    bool ok[PIECES];
+#pragma unroll
+    for (int i = 0; i < PIECES; ++i) {
+      const int slot = lane + i * 64, row = slot / CPR, c = (slot % CPR) * VE;
+      const int m = m0 + (wm * TM + tm) * 32 + row, co = co0 + wn * TN * 32 + c;
+      ok[i] = (m < p.M) & (co < p.C_out);
+      const int mm = ok[i] ? m : 0;
+      const int q = fastdiv(mm, p.by_w), ow = mm - q * p.W_out;
+      const int n = fastdiv(q, p.by_r), oh = p.out_lo + q - n * p.R;
+      ya[i] = ((size_t)(n * p.y_rows + oh - p.y_row0) * p.W_out + ow) * p.C_out + co;
+      rr[i] = u32x4{0u, 0u, 0u, 0u};
+      if (p.res && ok[i]) rr[i] = *(const u32x4*)((const T*)p.res + ((size_t)(n * p.r_rows + oh - p.r_row0) * p.W_out + ow) * p.C_out + co);
+    }
+#pragma unroll
+    for (int tn = 0; tn < TN; ++tn)
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+        *(f32x4*)(Cw + (lane & 31) * CPW + tn * 32 + g * 8 + (lane >> 5) * 4) =
+            f32x4{acc[tn][tm][g * 4], acc[tn][tm][g * 4 + 1], acc[tn][tm][g * 4 + 2], acc[tn][tm][g * 4 + 3]};
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+    for (int i = 0; i < PIECES; ++i) {
+      const int slot = lane + i * 64, row = slot / CPR, c = (slot % CPR) * VE;
+      if (!ok[i]) continue;
+      alignas(16) T in[VE], o[VE];
+      *(u32x4*)in = rr[i];
+#pragma unroll
+      for (int j = 0; j < VE; j += 4) {
+        f32x4 v = *(const f32x4*)(Cw + row * CPW + c + j);
+        if (p.bias) v += *(const f32x4*)(p.bias + co0 + wn * TN * 32 + c + j);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) o[j + k] = from_f32<T>(clamp_act(v[k] + to_f32(in[j + k]), cl));
+      }
+      *(u32x4*)((T*)p.y + ya[i]) = *(const u32x4*)o;
+      if (p.y2) *(u32x4*)((T*)p.y2 + ya[i]) = *(const u32x4*)o;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  }
+}
 
 template <typename T, int BM, int BN, int WM, int WN, int NST>
 __device__ __forceinline__ void gemm_body(const GemmParams& p, const int bx, const int gx) {
@@ -55,9 +118,8 @@ __device__ __forceinline__ void gemm_body(const GemmParams& p, const int bx, con
   constexpr int TM = BM / (32 * WM), TN = BN / (32 * WN);
   constexpr int A_LD = BM / (8 * NW), B_LD = BN / (8 * NW), LPS = A_LD + B_LD;   // load instructions per wavefront and stage
   constexpr int A_BYTES = BM * 128, STAGE = (BM + BN) * 128;
-  constexpr int CPW = TN * 32 + 4;          // fp32 pitch of a wavefront's staged output tile
   static_assert(A_LD >= 1 && B_LD >= 1 && (NST - 2) * LPS < 64 && NST >= 2, "tile shape");
-  constexpr int SMEM = NST * STAGE > NW * 32 * CPW * 4 ? NST * STAGE : NW * 32 * CPW * 4;
+  constexpr int SMEM = NST * STAGE > NW * 32 * gemm_pitch(TN) * 4 ? NST * STAGE : NW * 32 * gemm_pitch(TN) * 4;
   static_assert(SMEM <= 160 * 1024, "LDS");
   __shared__ __attribute__((aligned(1024))) unsigned char smem[SMEM];
 
@@ -193,61 +255,8 @@ __device__ __forceinline__ void gemm_body(const GemmParams& p, const int bx, con
   for (; s + 1 < ns; ++s) stage(s, true, false);
   stage(s, false, false);
 
-  // ---- epilogue: one 32-pixel tile of the wavefront at a time through LDS, so that consecutive lanes
-  // own consecutive 16-byte pieces of a pixel's channels
-  constexpr int VE = KE;
-  constexpr int CPR = TN * 32 / VE;          // pieces per pixel of the wavefront's tile
-  float* const Cw = (float*)smem + wave * (32 * CPW);
-  const Clamp cl = make_clamp(p.act);
   __syncthreads();
-#pragma unroll
-  for (int tm = 0; tm < TM; ++tm) {
-    constexpr int PIECES = 32 * CPR / 64;
-    // the residual's pieces (and where they go) first: their latency passes under the exchange
-    size_t ya[PIECES];
-    u32x4 rr[PIECES];
-    bool ok[PIECES];
-#pragma unroll
-    for (int i = 0; i < PIECES; ++i) {
-      const int slot = lane + i * 64, row = slot / CPR, c = (slot % CPR) * VE;
-      const int m = m0 + (wm * TM + tm) * 32 + row, co = co0 + wn * TN * 32 + c;
-      ok[i] = (m < p.M) & (co < p.C_out);
-      const int mm = ok[i] ? m : 0;
-      const int q = fastdiv(mm, p.by_w), ow = mm - q * p.W_out;
-      const int n = fastdiv(q, p.by_r), oh = p.out_lo + q - n * p.R;
-      ya[i] = ((size_t)(n * p.y_rows + oh - p.y_row0) * p.W_out + ow) * p.C_out + co;
-      rr[i] = u32x4{0u, 0u, 0u, 0u};
-      if (p.res && ok[i]) rr[i] = *(const u32x4*)((const T*)p.res + ((size_t)(n * p.r_rows + oh - p.r_row0) * p.W_out + ow) * p.C_out + co);
-    }
-#pragma unroll
-    for (int tn = 0; tn < TN; ++tn)
-#pragma unroll
-      for (int g = 0; g < 4; ++g)
-        *(f32x4*)(Cw + (lane & 31) * CPW + tn * 32 + g * 8 + (lane >> 5) * 4) =
-            f32x4{acc[tn][tm][g * 4], acc[tn][tm][g * 4 + 1], acc[tn][tm][g * 4 + 2], acc[tn][tm][g * 4 + 3]};
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll
-    for (int i = 0; i < PIECES; ++i) {
-      const int slot = lane + i * 64, row = slot / CPR, c = (slot % CPR) * VE;
-      if (!ok[i]) continue;
-      alignas(16) T in[VE], o[VE];
-      *(u32x4*)in = rr[i];
-#pragma unroll
-      for (int j = 0; j < VE; j += 4) {
-        f32x4 v = *(const f32x4*)(Cw + row * CPW + c + j);
-        if (p.bias) v += *(const f32x4*)(p.bias + co0 + wn * TN * 32 + c + j);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) o[j + k] = from_f32<T>(clamp_act(v[k] + to_f32(in[j + k]), cl));
-      }
-      *(u32x4*)((T*)p.y + ya[i]) = *(const u32x4*)o;
-      if (p.y2) *(u32x4*)((T*)p.y2 + ya[i]) = *(const u32x4*)o;
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  }
+  gemm_epilogue<T, TM, TN>(p, smem, acc, m0, co0, wave, wm, wn, lane);
 }
 
 template <typename T, int BM, int BN, int WM, int WN, int NST>
@@ -261,9 +270,219 @@ __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(2)
   gemm_body<T, BM, BN, WM, WN, NST>(t.p[b], blockIdx.x - t.first[b], t.first[b + 1] - t.first[b]);
 }
 
+// fp32 products on the bf16 matrix cores, which are 16 times as fast as the fp32 ones. A value is the sum of
+// three bf16 values (24 bits of mantissa are 8 + 8 + 8, split_bf16), a product of two values the sum of the
+// six partial products that are not below 2^-26 of it; bf16 products are exact in fp32, and the five small
+// partial products have an accumulator of their own. Against 64 bits the result is closer than that of the
+// fp32 matrix instructions, which round after every second product: rel. error over reductions of 64 / 576 /
+// 4608 normal x uniform values 1.5e-7 / 4.3e-7 / 1.2e-6 there, 4.7e-8 / 1.3e-7 / 4.1e-7 here.
+// An infinity, a NaN or a value that rounds to infinity in bf16 leaves a sum that is not finite; a wavefront
+// that ends with one computes its tile again on the fp32 instructions, which give what they always did.
+//
+//  - The input is split once per workgroup, on its way from memory through registers to LDS: stages of 32
+//    elements a row, loaded four stages ahead; a row takes 13 16-byte slots, an odd number, so that 16 neighbouring rows'
+//    reads touch every bank once. The weights are split when the plan is made and come straight from memory in
+//    operand order, two stages ahead; no two wavefronts load the same ones, since the vector cache hands a
+//    compute unit 30 bytes a cycle and that is what bounds the loop (32 KB a stage against 768 cycles of matrix
+//    instructions a SIMD; with 2 x 2 instead of 1 x 4 wavefronts 870 instead of 757 us on 8192 x 1024 -> 4096 -> 1024).
+//  - Half of the wavefronts take the first 16 elements of every stage, half the others: a tile is done in half
+//    the time where there are few of them, and the sums are added at the end through LDS.
+//  - A stage's fragments are read from LDS during the stage before it, the next but one stage's input is split and
+//    stored between the matrix instructions.
+template <int BM, int BN, int WM, int WN>
+__device__ __forceinline__ void gemm_split_body(const GemmParams& p, const int bx, const int gx) {
+  constexpr int NW = WM * WN, TM = BM / (32 * WM), TN = BN / (32 * WN);   // NW wavefronts for each step of a stage
+  constexpr int PIECES = BM * 8 / (128 * NW);   // 16-byte pieces of a stage's input per lane
+  constexpr int PITCH = 208, BUF = BM * PITCH;
+  constexpr int SUMS = NW * TM * 4096;          // the other half's sums of one of TN channel tiles
+  constexpr int OUT = NW * 32 * gemm_pitch(TN) * 4;
+  constexpr int SMEM = 2 * BUF > SUMS ? (2 * BUF > OUT ? 2 * BUF : OUT) : (SUMS > OUT ? SUMS : OUT);
+  static_assert(PIECES >= 1, "tile shape");
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[SMEM];
+
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int step = wave / NW, wm = wave % NW % WM, wn = wave % NW / WM;   // this wavefront's step of every stage, and its part of the tile
+  const TileId tile = xcd_tile(bx, gx, gridDim.y, 1, p.by_group);
+  const int m0 = tile.m * BM, co0 = tile.n * BN;
+  const int row_bytes = p.K * 4, ns = p.k_pad / 32;
+  const __amdgpu_buffer_rsrc_t xbuf = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<void*>(p.x), 0, (int)(unsigned)((size_t)p.N * p.x_rows * p.W * row_bytes), 0x00020000);
+  auto pixel_offset = [&](int m) -> unsigned {   // of a pixel's first channel, or outside
+    const bool ok = m < p.M;
+    const int mm = ok ? m : 0;
+    const int q = fastdiv(mm, p.by_w), ow = mm - q * p.W_out;
+    const int n = fastdiv(q, p.by_r), r = q - n * p.R;
+    const int ih = (p.out_lo + r) * p.sh - p.ph, iw = ow * p.sw - p.pw;
+    const bool in = ok & (ih >= p.x_row0) & (ih < p.x_row0 + p.x_rows) & (iw >= 0) & (iw < p.W);
+    return in ? (unsigned)(((n * p.x_rows + ih - p.x_row0) * p.W + iw) * row_bytes) : kOutside;
+  };
+  // ---- this lane's pieces of a stage: four elements from 4 c4 on of row tid / 8 + 16 NW i
+  const int c4 = threadIdx.x & 7;
+  unsigned src[PIECES];
+#pragma unroll
+  for (int i = 0; i < PIECES; ++i) {
+    const unsigned at = pixel_offset(m0 + (int)(threadIdx.x >> 3) + i * 16 * NW);
+    src[i] = at == kOutside ? kOutside : at + c4 * 16;
+  }
+  const bool past = (ns - 1) * 128 + c4 * 16 >= row_bytes;   // the piece lies past the end of the reduction in the last stage
+  u32x4 raw[2][PIECES];                                      // of the next two stages
+  // (Loads are issued for stages past the last one, too, from outside the buffer or of the last weights again: a
+  // load under a condition would make every wait one for all loads in flight.)
+  auto fetch = [&](int s, u32x4 (&d)[PIECES]) __attribute__((always_inline)) {
+    const bool out = (past & (s == ns - 1)) | (s >= ns);
+#pragma unroll
+    for (int i = 0; i < PIECES; ++i) d[i] = __builtin_amdgcn_raw_buffer_load_b128(xbuf, (int)(out ? kOutside : src[i]), s * 128, 0);
+  };
+  // [row][step][part][half] x 16 bytes
+  unsigned char* const put = smem + (threadIdx.x >> 3) * PITCH + (c4 >> 2) * 96 + ((c4 >> 1) & 1) * 16 + (c4 & 1) * 8;
+  auto store = [&](int buf, int i, u32x4 (&d)[PIECES]) __attribute__((always_inline)) {
+    uint2 parts[3];
+    split_bf16(__builtin_bit_cast(f32x4, d[i]), parts);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) *(uint2*)(put + buf * BUF + i * 16 * NW * PITCH + k * 32) = parts[k];
+  };
+  // ---- the weights: [32 channels][step of 16][part][lane] x 16 bytes
+  const u32x4* wsrc[TN];
+#pragma unroll
+  for (int t = 0; t < TN; ++t) wsrc[t] = (const u32x4*)p.w3 + ((size_t)(co0 / 32 + wn * TN + t) * (2 * ns) + step) * 192 + lane;
+  u32x4 w[2][TN][3];
+  auto fetch_weights = [&](int s, u32x4 (&d)[TN][3]) __attribute__((always_inline)) {
+    const int at = min(s, ns - 1) * 384;
+#pragma unroll
+    for (int t = 0; t < TN; ++t)
+#pragma unroll
+      for (int k = 0; k < 3; ++k) d[t][k] = wsrc[t][(size_t)(at + k * 64)];
+  };
+
+  f32x16 acc[TN][TM], low[TN][TM];
+#pragma unroll
+  for (int a = 0; a < TN; ++a)
+#pragma unroll
+    for (int b = 0; b < TM; ++b)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[a][b][i] = low[a][b][i] = 0.f;
+
+  const unsigned char* const get = smem + (wm * TM * 32 + (lane & 31)) * PITCH + step * 96 + (lane >> 5) * 16;
+  auto read = [&](int buf, u32x4 (&d)[TM][3]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+#pragma unroll
+      for (int b = 0; b < TM; ++b) d[b][k] = *(const u32x4*)(get + buf * BUF + b * 32 * PITCH + k * 32);
+  };
+  auto barrier = [&]() __attribute__((always_inline)) {   // (for LDS only: loads from memory stay in flight)
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  };
+  fetch(0, raw[0]);
+  fetch_weights(0, w[0]);
+  fetch(1, raw[1]);
+  fetch_weights(1, w[1]);
+#pragma unroll
+  for (int set = 0; set < 2; ++set) {
+#pragma unroll
+    for (int i = 0; i < PIECES; ++i) store(set, i, raw[set]);
+    fetch(set + 2, raw[set]);
+  }
+  u32x4 x[2][TM][3];
+  barrier();
+  read(0, x[0]);
+  // One stage (even ones set 0): its products. Meanwhile the next stage's fragments come out of LDS, and the
+  // input of the stage behind that goes into the memory this stage's fragments were read from before the barrier.
+  auto stage = [&](int s, int set) __attribute__((always_inline)) {
+    barrier();
+    read(set ^ 1, x[set ^ 1]);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int e = 0; e < 6; ++e) {
+      mma_split_part<TN, TM>(w[set], x[set], acc, low, e);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = e * PIECES / 6; i < (e + 1) * PIECES / 6; ++i) store(set, i, raw[set]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    fetch(s + 4, raw[set]);
+    fetch_weights(s + 2, w[set]);
+  };
+  int s = 0;
+  for (; s + 1 < ns; s += 2) {
+    stage(s, 0);
+    stage(s + 1, 1);
+  }
+  if (s < ns) stage(s, 0);
+
+  // ---- the two halves of the reduction: the second half's wavefronts hand their sums over through LDS
+#pragma unroll
+  for (int a = 0; a < TN; ++a) {
+    f32x4* const at = (f32x4*)smem + (wave % NW) * TM * 256 + lane;
+    __syncthreads();
+    if (step == 1) {
+#pragma unroll
+      for (int b = 0; b < TM; ++b) {
+        acc[a][b] += low[a][b];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) at[(b * 4 + g) * 64] = f32x4{acc[a][b][g * 4], acc[a][b][g * 4 + 1], acc[a][b][g * 4 + 2], acc[a][b][g * 4 + 3]};
+      }
+    }
+    __syncthreads();
+    if (step == 0) {
+#pragma unroll
+      for (int b = 0; b < TM; ++b) {
+        acc[a][b] += low[a][b];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const f32x4 v = at[(b * 4 + g) * 64];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) acc[a][b][g * 4 + i] += v[i];
+        }
+      }
+    }
+  }
+  __syncthreads();
+  if (step == 1) return;
+  float odd = 0.f;   // NaN if a sum is not finite
+#pragma unroll
+  for (int a = 0; a < TN; ++a)
+#pragma unroll
+    for (int b = 0; b < TM; ++b)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) odd += acc[a][b][i] - acc[a][b][i];
+  if (__builtin_amdgcn_ballot_w64(!(odd == 0.f))) {
+#pragma unroll
+    for (int b = 0; b < TM; ++b) {
+      const unsigned at = pixel_offset(m0 + (wm * TM + b) * 32 + (lane & 31));
+#pragma unroll
+      for (int a = 0; a < TN; ++a) {
+        const float* const wrow = (const float*)p.w + (size_t)(co0 + (wn * TN + a) * 32 + (lane & 31)) * p.k_pad;
+        f32x16 sum;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) sum[i] = 0.f;
+        for (int k = (lane >> 5) * 4; k < p.k_pad; k += 8) {
+          const u32x4 xv = __builtin_amdgcn_raw_buffer_load_b128(xbuf, (int)(at == kOutside || k >= p.K ? kOutside : at + k * 4), 0, 0);
+          mma<float>(*(const u32x4*)(wrow + k), xv, sum);
+        }
+        acc[a][b] = sum;
+      }
+    }
+  }
+  gemm_epilogue<float, TM, TN>(p, smem, acc, m0, co0, wave, wm, wn, lane);
+}
+
+template <int BM, int BN, int WM, int WN>
+__global__ __launch_bounds__(128 * WM * WN) __attribute__((amdgpu_waves_per_eu(2))) void conv_gemm_split_kernel(const GemmParams p) {
+  gemm_split_body<BM, BN, WM, WN>(p, blockIdx.x, gridDim.x);
+}
+// The same for several bands of one layer in one grid (band b owns blocks first[b] .. first[b + 1] of x).
+template <int BM, int BN, int WM, int WN>
+__global__ __launch_bounds__(128 * WM * WN) __attribute__((amdgpu_waves_per_eu(2))) void conv_gemm_split_kernel_bands(const Batch<GemmParams> t) {
+  const int b = batch_find(t, blockIdx.x);
+  gemm_split_body<BM, BN, WM, WN>(t.p[b], blockIdx.x - t.first[b], t.first[b + 1] - t.first[b]);
+}
+
 GemmParams make_gemm(const OpLaunch& L) {
   GemmParams p;
-  p.x = L.x.ptr; p.y = L.y.ptr; p.y2 = L.y2; p.res = L.res.ptr; p.w = L.w; p.bias = L.bias;
+  p.x = L.x.ptr; p.y = L.y.ptr; p.y2 = L.y2; p.res = L.res.ptr; p.w = L.w; p.w3 = L.w3; p.bias = L.bias;
   p.x_row0 = L.x.row0; p.x_rows = L.x.rows; p.W = L.x.w; p.K = L.x.c;
   p.y_row0 = L.y.row0; p.y_rows = L.y.rows; p.W_out = L.y.w; p.C_out = L.y.c;
   p.r_row0 = L.res.row0; p.r_rows = L.res.rows;
@@ -291,12 +510,20 @@ bool gemm_shape(const OpLaunch& L) {
 // of 128 x 256; 1000 x 2048 -> 512 (64 of 128 x 64) 11 there, 16 here. fp32 3001 x 512 -> 2048 (1 504 tiles of
 // 64 x 64) 85 -> 64 and 2048 -> 512 (376) 87 -> 78; 1500 x 1024 -> 256 (96) 18 there, 23 here; 8000 x 1000 -> 3000
 // (1 512 tiles of 128 x 128) 479 -> 432, against 455 with 64 x 64.
-struct GemmChoice { int bm = 0, bn = 0; };
+struct GemmChoice { int bm = 0, bn = 0; bool split = false; };
 constexpr long kBigTiles = 128;        // 256 x 256, bf16
 constexpr long kWideTiles = 192;       // 128 x 256, bf16
 constexpr long kNarrowTiles = 384;     // 128 x 64, bf16
 constexpr long kF32BigTiles = 1024;    // 128 x 128, fp32
 constexpr long kF32Tiles = 320;        // 64 x 64, fp32
+// 64 x 128, fp32 on the bf16 matrix cores. Before -> here, us a launch: 3001 x 512 -> 2048 (752 tiles) 64 -> 46, 2048 -> 512 (188)
+// 78 -> 47, 1500 x 1024 -> 512 (96) 26.2 -> 25.4, 600 x 512 -> 2048 (160) 22.6 -> 17.1; one stage after the other they
+// take 0.55 us a stage whatever runs beside them (24 KB of weights come to a compute unit at 30 bytes a cycle), so
+// that few tiles are slower alone: 256 x 512 -> 2048 (64) 11.5 -> 14.8, 600 x 2048 -> 512 (40) 33 -> 40; but they
+// leave the chip to other launches: 1000 x 512 -> 2048 -> 512 (256 and 64) 46 -> 28 a call with calls in flight,
+// 76 -> 78 alone. Short reductions have nothing to gain: 3001 x 128 -> 256 7.0 -> 8.9.
+constexpr long kSplitTiles = 64;
+constexpr int kSplitMinK = 192;
 
 GemmChoice choose_gemm(const OpLaunch* Ls, int n) {
   for (int b = 0; b < n; ++b)
@@ -313,12 +540,15 @@ GemmChoice choose_gemm(const OpLaunch* Ls, int n) {
     if (tiles(128, 64) < kNarrowTiles) return {};
     return tiles(128, 256) >= kWideTiles ? GemmChoice{128, 256} : GemmChoice{128, 64};
   }
+  if (Ls[0].w3 && tiles(64, 128) >= kSplitTiles) return {64, 128, true};
   if (tiles(128, 128) >= kF32BigTiles) return {128, 128};
   return tiles(64, 64) >= kF32Tiles ? GemmChoice{64, 64} : GemmChoice{};
 }
 
-template <typename T, int BM, int BN, int WM, int WN, int NST>
-hipError_t launch_tile(const OpLaunch* Ls, int n, hipStream_t s, KernelEvents* ev) {
+// single, bands: a kernel of BM x BN tiles and THREADS threads, for one band and for several
+template <int BM, int BN, int THREADS>
+hipError_t launch_tile(void (*single)(const GemmParams), void (*bands)(const Batch<GemmParams>), const OpLaunch* Ls, int n, hipStream_t s,
+                       KernelEvents* ev) {
   GemmParams ps[kMaxBatch];
   unsigned gx[kMaxBatch];
   const unsigned gy = (unsigned)((Ls[0].y.c + BN - 1) / BN);
@@ -332,11 +562,20 @@ hipError_t launch_tile(const OpLaunch* Ls, int n, hipStream_t s, KernelEvents* e
     ++m;
   }
   if (m == 0) return hipSuccess;
-  return launch_group(conv_gemm_kernel<T, BM, BN, WM, WN, NST>, conv_gemm_kernel_bands<T, BM, BN, WM, WN, NST>, ps, m, gx, gy, 1,
-                      dim3(64 * WM * WN), s, ev);
+  return launch_group(single, bands, ps, m, gx, gy, 1, dim3(THREADS), s, ev);
+}
+template <typename T, int BM, int BN, int WM, int WN, int NST>
+hipError_t launch_direct(const OpLaunch* Ls, int n, hipStream_t s, KernelEvents* ev) {
+  return launch_tile<BM, BN, 64 * WM * WN>(conv_gemm_kernel<T, BM, BN, WM, WN, NST>, conv_gemm_kernel_bands<T, BM, BN, WM, WN, NST>, Ls, n, s, ev);
+}
+template <int BM, int BN, int WM, int WN>
+hipError_t launch_split(const OpLaunch* Ls, int n, hipStream_t s, KernelEvents* ev) {
+  return launch_tile<BM, BN, 128 * WM * WN>(conv_gemm_split_kernel<BM, BN, WM, WN>, conv_gemm_split_kernel_bands<BM, BN, WM, WN>, Ls, n, s, ev);
 }
 
 }  // namespace
+
+bool split_shape(int c_in, int c_out, int kh, int kw) { return kh == 1 && kw == 1 && c_in >= kSplitMinK && c_in % 4 == 0 && c_out % 4 == 0; }
 
 bool gemm_applies(const OpLaunch* Ls, int n) { return n >= 1 && n <= kMaxBatch && choose_gemm(Ls, n).bm != 0; }
 
@@ -344,13 +583,14 @@ hipError_t launch_gemm(const OpLaunch* Ls, int n, hipStream_t s, KernelEvents* e
   if (n < 1 || n > kMaxBatch) return hipErrorInvalidValue;
   const GemmChoice c = choose_gemm(Ls, n);
   if (Ls[0].dtype == LOP_BF16) {
-    if (c.bm == 256) return launch_tile<__bf16, 256, 256, 2, 4, 2>(Ls, n, s, ev);
-    if (c.bm == 128 && c.bn == 256) return launch_tile<__bf16, 128, 256, 2, 4, 3>(Ls, n, s, ev);
-    if (c.bm == 128) return launch_tile<__bf16, 128, 64, 2, 2, 3>(Ls, n, s, ev);
+    if (c.bm == 256) return launch_direct<__bf16, 256, 256, 2, 4, 2>(Ls, n, s, ev);
+    if (c.bm == 128 && c.bn == 256) return launch_direct<__bf16, 128, 256, 2, 4, 3>(Ls, n, s, ev);
+    if (c.bm == 128) return launch_direct<__bf16, 128, 64, 2, 2, 3>(Ls, n, s, ev);
     return hipErrorInvalidValue;
   }
-  if (c.bm == 128) return launch_tile<float, 128, 128, 2, 2, 2>(Ls, n, s, ev);
-  if (c.bm == 64) return launch_tile<float, 64, 64, 2, 2, 3>(Ls, n, s, ev);
+  if (c.split) return launch_split<64, 128, 1, 4>(Ls, n, s, ev);
+  if (c.bm == 128) return launch_direct<float, 128, 128, 2, 2, 2>(Ls, n, s, ev);
+  if (c.bm == 64) return launch_direct<float, 64, 64, 2, 2, 3>(Ls, n, s, ev);
   return hipErrorInvalidValue;
 }
 
@@ -359,7 +599,9 @@ int gemm_describe(const OpLaunch* Ls, int n, char* name, size_t size) {
   const bool bf = Ls[0].dtype == LOP_BF16;
   int m = 0;
   for (int b = 0; b < n; ++b) m += make_gemm(Ls[b]).M > 0;
-  if (name && size)   // (tile, wavefronts in either direction, stages: as launch_gemm takes them)
+  if (name && size && c.split)
+    snprintf(name, size, "conv_gemm_split_kernel%s<%d, %d, 1, 4>", m > 1 ? "_bands" : "", c.bm, c.bn);
+  else if (name && size)   // (tile, wavefronts in either direction, stages: as launch_gemm takes them)
     snprintf(name, size, "conv_gemm_kernel%s<%s, %d, %d, 2, %d, %d>", m > 1 ? "_bands" : "", bf ? "__bf16" : "float", c.bm, c.bn,
              bf && c.bn == 256 ? 4 : 2, c.bm == 256 || (!bf && c.bm == 128) ? 2 : 3);
   return 1;

@@ -24,6 +24,7 @@ struct OpLaunch {
   const void* w = nullptr;      // device, kernel layout (see pack_* below)
   const void* wd = nullptr;     // dense conv: the weights in operand order, or nullptr
   const void* wd16 = nullptr;   // dense conv: ... in the operand order of 16 x 16 tiles, or nullptr
+  const void* w3 = nullptr;     // dense fp32 conv: the weights as three bf16 parts in operand order, or nullptr
   const void* wstem = nullptr;  // dense conv over very few input channels: fp32 weights
                                 // [c_out / 4][k][4] for the first-layer kernel, or nullptr
   const float* bias = nullptr;  // device or nullptr
@@ -45,6 +46,9 @@ struct OpLaunch {
 // w[co][step*MK + half*KE ... + KE) of the first packing. A third one serves 16 x 16 tiles:
 // [c_out_pad / 16][k_pad / MK16][64 lanes] x 16 bytes, MK16 = 4 vectors, lane = quarter*16 +
 // (co % 16) holds w[co][step*MK16 + quarter*KE ... + KE).
+// fp32 layers whose reduction is long enough for the bf16 matrix cores (split_shape) get their weights as
+// sums of three bf16 values, too: [c_out_pad / 32][k_pad / 16][part][64 lanes] x 16 bytes, lane = half*32 +
+// (co % 32) holds part of w[co][step*16 + half*8 ... + 8).
 // The row count is padded to the widest channel tile that can take the layer: 128, and 256 once
 // there are more than 128 channels (the 256-wide tile is never chosen below that), so the last
 // channel tile of any kernel reads rows that exist.
@@ -54,6 +58,9 @@ inline int conv_cout_pad(int c_out) {
   const int unit = c_out > kConvCoutPad ? 2 * kConvCoutPad : kConvCoutPad;
   return (c_out + unit - 1) / unit * unit;
 }
+
+// Whether a dense fp32 conv gets that packing.
+bool split_shape(int c_in, int c_out, int kh, int kw);
 
 // Bytes of split-K scratch the dense conv launch needs (0: none).
 size_t conv_workspace_bytes(const OpLaunch& L);

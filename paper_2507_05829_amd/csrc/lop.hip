@@ -142,6 +142,14 @@ inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 namespace {
 
+// Rounded to the nearest bfloat16, ties to even; a NaN stays one.
+unsigned short bf16_bits(float v) {
+  unsigned u;
+  std::memcpy(&u, &v, 4);
+  if ((u & 0x7fffffffu) > 0x7f800000u) return (unsigned short)(u >> 16 | 0x40);
+  return (unsigned short)((u + 0x7fffu + (u >> 16 & 1)) >> 16);
+}
+
 int upload_weights(lop_plan_t* P) {
   const lop::Tables& t = P->t;
   const int nl = t.n_layers();
@@ -149,6 +157,7 @@ int upload_weights(lop_plan_t* P) {
   P->d_w.assign(nl, nullptr);
   P->d_wd.assign(nl, nullptr);
   P->d_wd16.assign(nl, nullptr);
+  P->d_w3.assign(nl, nullptr);
   P->d_wstem.assign(nl, nullptr);
   P->d_bias.assign(nl, nullptr);
   for (int l = 0; l < nl; ++l) {
@@ -227,6 +236,26 @@ int upload_weights(lop_plan_t* P) {
           LOP_HIP(lop::dev_alloc(&P->d_wd16[l], ord.size()));
           LOP_HIP(hipMemcpy(P->d_wd16[l], ord.data(), ord.size(), hipMemcpyHostToDevice));
         }
+      }
+      if (P->has_w3[l]) {
+        // fp32 values as sums of three bf16 ones: [co / 32][step of 16][part][half*32 + co % 32] x 8 elements
+        std::vector<unsigned short> parts((size_t)cp * kp * 3);
+        const float* const row = (const float*)host.data();
+        for (int co = 0; co < d.c_out; ++co)
+          for (int k = 0; k < kp; ++k) {
+            float left = row[(size_t)co * kp + k];
+            if (left == 0.f) continue;
+            unsigned short* const at = &parts[(((size_t)(co / 32) * (kp / 16) + k / 16) * 192 + (k / 8 % 2) * 32 + co % 32) * 8 + k % 8];
+            for (int part = 0; part < 3; ++part) {
+              at[part * 512] = bf16_bits(left);
+              const unsigned u = (unsigned)at[part * 512] << 16;
+              float v;
+              std::memcpy(&v, &u, 4);
+              left -= v;
+            }
+          }
+        LOP_HIP(lop::dev_alloc(&P->d_w3[l], parts.size() * 2));
+        LOP_HIP(hipMemcpy(P->d_w3[l], parts.data(), parts.size() * 2, hipMemcpyHostToDevice));
       }
     } else if (d.op == LOP_DWCONV2D) {
       if (!d.weight) return LOP_ERR_INVALID_ARG;
@@ -580,6 +609,7 @@ lop::OpLaunch make_launch(const lop_plan_t* P, int band, int l, const void* d_in
     o.w = P->d_w[l];
     o.wd = P->d_wd[l];
     o.wd16 = P->d_wd16[l];
+    o.w3 = P->d_w3[l];
     o.wstem = P->d_wstem[l];
     o.bias = P->d_bias[l];
   } else {
@@ -587,6 +617,7 @@ lop::OpLaunch make_launch(const lop_plan_t* P, int band, int l, const void* d_in
     // is never dereferenced stands for each that upload_weights would make
     o.wd = P->has_wd[l] ? (const void*)P : nullptr;
     o.wd16 = P->has_wd16[l] ? (const void*)P : nullptr;
+    o.w3 = P->has_w3[l] ? (const void*)P : nullptr;
     o.wstem = P->has_wstem[l] ? (const void*)P : nullptr;
   }
   o.k_pad = P->k_pad[l];
@@ -613,10 +644,11 @@ OpLaunch describe_layer(const lop_plan_s* P, int l) {
   o.x.n = o.y.n = P->t.in.n;
   if (L.d.residual_from != LOP_NO_RESIDUAL) o.res.ptr = const_cast<lop_plan_t*>(P);
   if (!P->d_w.empty()) {  // uploaded (not a plan-only plan)
-    o.w = P->d_w[l]; o.wd = P->d_wd[l]; o.wd16 = P->d_wd16[l]; o.wstem = P->d_wstem[l]; o.bias = P->d_bias[l];
+    o.w = P->d_w[l]; o.wd = P->d_wd[l]; o.wd16 = P->d_wd16[l]; o.w3 = P->d_w3[l]; o.wstem = P->d_wstem[l]; o.bias = P->d_bias[l];
   } else {
     o.wd = P->has_wd[l] ? (const void*)P : nullptr;
     o.wd16 = P->has_wd16[l] ? (const void*)P : nullptr;
+    o.w3 = P->has_w3[l] ? (const void*)P : nullptr;
     o.wstem = P->has_wstem[l] ? (const void*)P : nullptr;
   }
   o.k_pad = P->k_pad[l];
@@ -1439,6 +1471,7 @@ int lop_plan(const lop_layer_t* layers, int n_layers, const lop_tensor_desc_t* i
   P->k_pad.assign((size_t)n_layers, 0);  // padded reduction length of every dense conv
   P->has_wd.assign((size_t)n_layers, 0);
   P->has_wd16.assign((size_t)n_layers, 0);
+  P->has_w3.assign((size_t)n_layers, 0);
   P->has_wstem.assign((size_t)n_layers, 0);
   const int ke = 16 / (int)P->t.esz();
   for (int l = 0; l < n_layers; ++l) {
@@ -1447,6 +1480,7 @@ int lop_plan(const lop_layer_t* layers, int n_layers, const lop_tensor_desc_t* i
     P->k_pad[l] = lop::conv_k_pad(d.c_in, d.kh, d.kw, in->dtype);
     P->has_wd[l] = d.c_in % ke == 0 && d.c_out % ke == 0;
     P->has_wd16[l] = P->has_wd[l] && P->k_pad[l] % (4 * ke) == 0;
+    P->has_w3[l] = in->dtype == LOP_F32 && lop::split_shape(d.c_in, d.c_out, d.kh, d.kw);
     P->has_wstem[l] = lop::stem_shape_applies(d.c_in, d.c_out, d.kh, d.kw, d.sw, d.dh, d.dw,
                                               d.residual_from != LOP_NO_RESIDUAL);
   }
@@ -1504,6 +1538,7 @@ void lop_plan_destroy(lop_plan_t* P) {
   for (void* w : P->d_w) if (w) (void)lop::dev_free(w);
   for (void* w : P->d_wd) if (w) (void)lop::dev_free(w);
   for (void* w : P->d_wd16) if (w) (void)lop::dev_free(w);
+  for (void* w : P->d_w3) if (w) (void)lop::dev_free(w);
   for (void* w : P->d_wstem) if (w) (void)lop::dev_free(w);
   for (float* b : P->d_bias) if (b) (void)lop::dev_free(b);
   for (auto* v : {&P->ev_done, &P->ev_copied, &P->ev_c0, &P->ev_c1, &P->ev_d0, &P->ev_d1})

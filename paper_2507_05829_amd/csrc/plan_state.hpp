@@ -58,6 +58,7 @@ struct lop_plan_s {
   std::vector<void*> d_w;      // per layer packed weights (device) or nullptr
   std::vector<void*> d_wd;     // dense conv weights in MFMA operand order, or nullptr
   std::vector<void*> d_wd16;   // ... in the operand order of 16 x 16 tiles, or nullptr
+  std::vector<void*> d_w3;     // ... of fp32 layers as three bf16 parts in operand order, or nullptr
   std::vector<void*> d_wstem;  // ... as fp32 [c_out / 4][k][4] for the first-layer kernel, or nullptr
   Fusion fuse_band;   // groups of the launches that compute one band
   Fusion fuse_chain;  // groups of the launches that compute all bands (kGrouped, kWhole)
@@ -69,6 +70,7 @@ struct lop_plan_s {
   std::vector<float*> d_bias;  // per layer bias (device) or nullptr
   std::vector<int> k_pad;
   std::vector<char> has_wd, has_wd16;  // which of the two operand-order packings a layer gets
+  std::vector<char> has_w3;            // ... whether it gets the packing as three bf16 parts
   std::vector<char> has_wstem;         // ... and whether it gets the first-layer packing
   size_t conv_ws_bytes = 0;
   size_t arena_bytes = 0;

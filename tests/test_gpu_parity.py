@@ -1691,6 +1691,74 @@ def test_matrix_product_kernel(oracle, cfg):
     np.testing.assert_array_equal(dev, want)
 
 
+def _split_chain(m, k, n, residual, bands=1):
+    chain = workloads.RowChain("split", m, k, "f32", bands)
+    if residual:
+        chain.add(n, "none").add(n, "relu", residual_from=0, input_from=-1)
+    else:
+        chain.add(n, "relu")
+    return chain
+
+
+@pytest.mark.parametrize("cfg", [
+    (64 * 63 + 1, 192, 132, True),     # the shortest reduction; rows and channels end just inside a tile
+    (700, 2052, 768, False),           # a last stage of four elements; an odd number of stages
+    (1111, 260, 1028, True),
+])
+def test_fp32_products_on_the_bf16_matrix_cores(oracle, cfg):
+    """fp32 matrix products as sums of bf16 ones: within fp32 rounding of the 64-bit result (a partial product
+    is dropped below 2^-26, an accumulator is rounded once per 16 elements), and exact on small integers; in one
+    band, band by band and with all bands merged."""
+    m, k, n, residual = cfg
+    chain = _split_chain(m, k, n, residual)
+    t = workloads.make_row_tensors(chain, zero_bias=False, seed=43)
+    dev, host, names = _run_rows(chain, t)
+    assert names == {"conv_gemm_split_kernel<64, 128, 1, 4>"}, names
+    np.testing.assert_array_equal(dev, host)
+    x = t.x.astype(np.float64)
+    want = x @ t.weights[0].astype(np.float64).T + t.biases[0]
+    if residual:
+        want = want + x @ t.weights[1].astype(np.float64).T + t.biases[1]
+    want = np.maximum(want, 0)
+    # k / 16 roundings of 2^-24 of sums that grow like sqrt(k): well below sqrt(k / 16) 2^-24 of the result's scale
+    assert np.linalg.norm(dev - want) <= 2 * np.sqrt(k / 16) * 2.0 ** -24 * np.linalg.norm(want)
+    rng = np.random.Generator(np.random.PCG64(14))
+    ti = workloads.Tensors(rng.integers(-3, 4, (m, k)).astype(np.float32),
+                           [rng.integers(-3, 4, (L.n, L.k)).astype(np.float32) for L in chain.layers],
+                           [rng.integers(-3, 4, L.n).astype(np.float32) for L in chain.layers])
+    want = oracle.run_row_chain(chain, ti)
+    for bands in (1, 3):
+        dev, _, _ = _run_rows(_split_chain(m, k, n, residual, bands), ti)
+        np.testing.assert_array_equal(dev, want)
+
+
+@pytest.mark.parametrize("where", ["input", "weights"])
+def test_fp32_products_with_values_that_are_not_finite(where):
+    """Infinities, NaN and values too large for bf16 on the way to the bf16 matrix cores: every element is
+    what the fp32 instructions make of it, which compute the same rows in bands of few."""
+    m, k, n, bands = 1500, 200, 516, 60
+    chain = workloads.RowChain("split", m, k, "f32", bands)
+    chain.add(n, "none")
+    t = workloads.make_row_tensors(chain, zero_bias=False, seed=47)
+    a = t.x if where == "input" else t.weights[0]
+    a[3, 5], a[70, 7], a[71, k - 1], a[200, 0], a[300, 9] = np.inf, -np.inf, np.nan, 3.4e38, 1e-40
+    a[301, 3], a[301, 4] = np.inf, -np.inf
+    b = t.weights[0] if where == "input" else t.x
+    b[:, 5] = np.where(np.arange(len(b)) % 3 == 0, 0.0, b[:, 5])
+    b[:, 0] = np.where(np.arange(len(b)) % 2 == 0, 0.5, 0.25)
+    plan = lop.Plan.rowwise(workloads.RowChain("split", m, k, "f32", 1, chain.layers), t)
+    assert plan.layer_kernel(0, 0)[0] == "conv_gemm_split_kernel<64, 128, 1, 4>"
+    plan.destroy()
+    dev, _, names = _run_rows(chain, t)
+    assert not any("split" in name for name in names), names
+    want, _, _ = _run_rows(chain, t, order=list(range(bands)))
+    np.testing.assert_array_equal(np.isfinite(dev), np.isfinite(want))
+    ok = np.isfinite(want)
+    assert 0.5 < ok.mean() < 1
+    np.testing.assert_array_equal(dev[~ok], want[~ok])
+    assert (np.abs(dev[ok] - want[ok]) <= 1e-5 * np.maximum(np.abs(want[ok]), 10)).all()
+
+
 def test_matrix_product_kernel_on_images(oracle):
     """The same kernel as a strided 1 x 1 convolution over a batch, in bands and with all bands in one
     launch."""
