@@ -3,6 +3,8 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "kernels.hpp"
 
 namespace lop {
@@ -103,6 +105,14 @@ __device__ __forceinline__ TileId xcd_tile(int bx, int mx, int ny, int nz, const
   return id;
 }
 
+// f(integral_constant<0>) ... f(integral_constant<N - 1>): loops whose body needs its index as a constant
+template <int N, int I = 0, typename F>
+__device__ __forceinline__ void unroll(F&& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    unroll<N, I + 1>(f);
+  }
+}
 // s_waitcnt immediate that waits until at most n vector-memory operations are outstanding
 // and leaves the other counters alone (gfx9 encoding: vmcnt in bits 3:0 and 15:14).
 constexpr int vmcnt_imm(int n) { return (n & 0xf) | ((n >> 4) << 14) | (0x7 << 4) | (0xf << 8); }

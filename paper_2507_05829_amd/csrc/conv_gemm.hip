@@ -480,6 +480,19 @@ __global__ __launch_bounds__(128 * WM * WN) __attribute__((amdgpu_waves_per_eu(2
   gemm_split_body<BM, BN, WM, WN>(t.p[b], blockIdx.x - t.first[b], t.first[b + 1] - t.first[b]);
 }
 
+// [c_out_pad][k_pad] fp32 -> [c_out_pad / 32][k_pad / 16][part][half*32 + c_out % 32] x 8 elements
+__global__ __launch_bounds__(256) void split_weights_kernel(const float* w, int k_pad, unsigned pieces, u32x4* w3) {
+  const unsigned i = blockIdx.x * 256 + threadIdx.x;
+  if (i >= pieces) return;
+  const unsigned lane = i & 63, steps = (unsigned)k_pad / 16, step = (i >> 6) % steps, group = (i >> 6) / steps;
+  const float* const from = w + (size_t)(group * 32 + (lane & 31)) * k_pad + step * 16 + (lane >> 5) * 8;
+  uint2 lo[3], hi[3];
+  split_bf16(*(const f32x4*)from, lo);
+  split_bf16(*(const f32x4*)(from + 4), hi);
+#pragma unroll
+  for (int k = 0; k < 3; ++k) w3[(size_t)(i >> 6) * 192 + k * 64 + lane] = u32x4{lo[k].x, lo[k].y, hi[k].x, hi[k].y};
+}
+
 GemmParams make_gemm(const OpLaunch& L) {
   GemmParams p;
   p.x = L.x.ptr; p.y = L.y.ptr; p.y2 = L.y2; p.res = L.res.ptr; p.w = L.w; p.w3 = L.w3; p.bias = L.bias;
@@ -575,7 +588,11 @@ hipError_t launch_split(const OpLaunch* Ls, int n, hipStream_t s, KernelEvents* 
 
 }  // namespace
 
-bool split_shape(int c_in, int c_out, int kh, int kw) { return kh == 1 && kw == 1 && c_in >= kSplitMinK && c_in % 4 == 0 && c_out % 4 == 0; }
+bool split_shape(int c_in, int kh, int kw) { return kh == 1 && kw == 1 && c_in >= kSplitMinK; }
+hipError_t launch_split_weights(const void* w, int c_out_pad, int k_pad, void* w3, hipStream_t stream) {
+  const unsigned pieces = (unsigned)((size_t)c_out_pad * k_pad / 8);
+  return launch_kernel(split_weights_kernel, dim3((pieces + 255) / 256), dim3(256), stream, nullptr, (const float*)w, k_pad, pieces, (u32x4*)w3);
+}
 
 bool gemm_applies(const OpLaunch* Ls, int n) { return n >= 1 && n <= kMaxBatch && choose_gemm(Ls, n).bm != 0; }
 

@@ -27,7 +27,7 @@
 //    tile: the maximum is taken between them before bias, activation and rounding (all of them
 //    non-decreasing) and the convolution's own output never exists in memory.
 //
-// (What it is worth, measured: see choose_patch.)
+// (What it is worth, measured: see choose_patch. fp32 has a form of its own: patch_split_body.)
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -35,6 +35,7 @@
 
 #include "act.hpp"
 #include "conv_common.hpp"
+#include "conv_split.hpp"
 #include "conv_tiles.hpp"
 #include "kernels.hpp"
 #include "launch.hpp"
@@ -45,24 +46,201 @@ namespace {
 
 constexpr int kPixelBytes = 144, kPixelSlots = 9;
 
+// Row and column, inside the tile, of its pixel i.
+template <bool POOL>
+__device__ __forceinline__ void tile_pixel(const PatchParams& p, int i, int& r, int& c) {
+  if constexpr (POOL) {
+    const int v = i >> 2, vr = fastdiv(v, p.by_tw), vc = v - vr * (p.tw >> 1);   // (by_tw divides by tw / 2)
+    r = vr * 2 + ((i >> 1) & 1);
+    c = vc * 2 + (i & 1);
+  } else {
+    r = fastdiv(i, p.by_tw);
+    c = i - r * p.tw;
+  }
+}
+
+// Where a workgroup's tile lies: its first row of the launch and first column, its image and its channel tile;
+// second: a channel tile of the 1 x 1 convolution beside the launch's own.
+struct PatchAt { int n, r0, c0, tile_n; bool second; };
+__device__ __forceinline__ PatchAt patch_at(const PatchParams& p, int bx, int gx, bool siblings) {
+  const TileId tile = xcd_tile(bx, gx, gridDim.y, 1, p.by_group);
+  PatchAt a;
+  a.second = siblings && tile.n >= p.sib.first;
+  a.tile_n = a.second ? tile.n - p.sib.first : tile.n;
+  const int q = fastdiv(tile.m, p.by_ntx), tx = tile.m - q * p.ntx;
+  a.n = fastdiv(q, p.by_nty);
+  a.r0 = (q - a.n * p.nty) * p.th;
+  a.c0 = tx * p.tw;
+  return a;
+}
+
+// The four partial tiles, added in wavefront order through LDS, and what follows the sums. again(f, sum): this
+// wavefront's pieces of fragment f once more, for sums that are not finite.
+template <typename T, int TP, int NT, bool POOL, typename Again>
+__device__ __forceinline__ void patch_finish(const PatchParams& p, unsigned char* smem, const f32x16 (&acc)[NT][TP], const PatchAt& t,
+                                             int lane, int wave, Again&& again) {
+  constexpr int UNITS = TP * 4;             // (32 pixels x 8 channels) pieces of a 32-channel tile
+  const int half = lane >> 5, n = t.n, co0 = t.tile_n * (32 * NT);
+  const bool second = t.second;
+  // wavefront w finishes pieces
+  // w TP .. (w + 1) TP of the UNITS pieces (piece u: fragment u / 4, channels (u % 4) * 8 ..)
+  u32x4* const part = (u32x4*)smem;
+  const Clamp cl = make_clamp(second ? p.sib.act : p.act);
+  const int C_out = second ? p.sib.C_out : p.C_out;
+  const float* const bias_at = second ? p.sib.bias : p.bias;
+  T* const y = (T*)(second ? p.sib.y : p.y);
+  T* const y2 = second ? nullptr : (T*)p.y2;
+  // where they go, and what is added to them: all loads issued here, ahead of the sums
+  int r, cc;
+  tile_pixel<POOL>(p, wave * TP / 4 * 32 + (lane & 31), r, cc);             // (a wavefront's pieces all lie in one fragment)
+  const int row = t.r0 + r, col = t.c0 + cc;
+  bool live = (r < p.th) & (row < p.R) & (col < p.Wc);
+  if (second) live = live & (p.out_lo + row >= p.sib.lo) & (p.out_lo + row < p.sib.hi);
+  const int cb = co0 + ((wave * TP) & 3) * 8;   // first channel of this wavefront's pieces
+  f32x4 bias[NT][TP];
+#pragma unroll
+  for (int a = 0; a < NT; ++a)
+#pragma unroll
+    for (int i = 0; i < TP; ++i) bias[a][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  if (bias_at) {
+#pragma unroll
+    for (int a = 0; a < NT; ++a)
+#pragma unroll
+      for (int i = 0; i < TP; ++i) {
+        const int co = cb + a * 32 + i * 8 + half * 4;
+        bias[a][i] = *(const f32x4*)(bias_at + (co < C_out ? co : 0));
+      }
+  }
+  typedef unsigned raw_t __attribute__((ext_vector_type(sizeof(T))));   // four elements
+  raw_t res[NT][TP];
+  if constexpr (!POOL) {
+    if (p.res && !second) {
+      const size_t ra = live ? ((size_t)(n * p.r_rows + p.out_lo + row - p.r_row0) * p.W_out + col) * p.C_out : 0;
+#pragma unroll
+      for (int a = 0; a < NT; ++a)
+#pragma unroll
+        for (int i = 0; i < TP; ++i) {
+          const int co = cb + a * 32 + i * 8 + half * 4;
+          res[a][i] = *(const raw_t*)((const T*)p.res + ra + (co < p.C_out ? co : 0));
+        }
+    } else {
+#pragma unroll
+      for (int a = 0; a < NT; ++a)
+#pragma unroll
+        for (int i = 0; i < TP; ++i) res[a][i] = raw_t(0u);
+    }
+  }
+#pragma unroll
+  for (int a = 0; a < NT; ++a) {
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < UNITS; ++u) {
+      const f32x16& s = acc[a][u / 4];
+      const int g = (u % 4) * 4;
+      part[(wave * UNITS + u) * 64 + lane] = __builtin_bit_cast(u32x4, f32x4{s[g], s[g + 1], s[g + 2], s[g + 3]});
+    }
+    __syncthreads();
+    f32x4 sum[TP];
+#pragma unroll
+    for (int i = 0; i < TP; ++i) {
+      sum[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int s = 0; s < 4; ++s) sum[i] += __builtin_bit_cast(f32x4, part[(s * UNITS + wave * TP + i) * 64 + lane]);
+    }
+    if constexpr (sizeof(T) == 4) {
+      float odd = 0.f;   // NaN if a sum is not finite
+#pragma unroll
+      for (int i = 0; i < TP; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) odd += sum[i][j] - sum[i][j];
+      if (__builtin_amdgcn_ballot_w64(!(odd == 0.f))) again(wave * TP / 4, sum);
+    }
+    // ---- pooling, bias, residual, activation, the one rounding
+    size_t ya;
+    if constexpr (POOL) {
+#pragma unroll
+      for (int i = 0; i < TP; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          float v = sum[i][j];
+          v = fmaxf(v, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0xB1, 0xf, 0xf, true)));  // lane ^ 1
+          v = fmaxf(v, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x4E, 0xf, 0xf, true)));  // lane ^ 2
+          sum[i][j] = v;
+        }
+      live = live & ((lane & 3) == 0);
+      ya = ((size_t)(n * p.y_rows + ((p.out_lo + row) >> 1) - p.y_row0) * p.W_out + (col >> 1)) * p.C_out;
+    } else {
+      ya = ((size_t)(n * (second ? p.sib.y_rows : p.y_rows) + p.out_lo + row - (second ? p.sib.y_row0 : p.y_row0)) * p.W_out + col) * C_out;
+    }
+#pragma unroll
+    for (int i = 0; i < TP; ++i) {
+      sum[i] += bias[a][i];
+      if constexpr (!POOL) {
+        alignas(16) T rr[4];
+        *(raw_t*)rr = res[a][i];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) sum[i][j] += to_f32(rr[j]);
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j) sum[i][j] = clamp_act(sum[i][j], cl);
+    }
+    if constexpr (sizeof(T) == 4) {
+#pragma unroll
+      for (int i = 0; i < TP; ++i) {
+        const int co = cb + a * 32 + i * 8 + half * 4;
+        if (live && co < C_out) {
+          *(f32x4*)(y + ya + co) = sum[i];
+          if (y2) *(f32x4*)(y2 + ya + co) = sum[i];
+        }
+      }
+    } else {
+      auto pack = [&](int i) {
+        alignas(8) __bf16 o[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) o[j] = (__bf16)sum[i][j];
+        return *(const uint2*)o;
+      };
+      if constexpr (TP == 1) {
+        const uint2 o = pack(0);
+        const int co = cb + a * 32 + half * 4;
+        if (live && co < C_out) {
+          *(uint2*)(y + ya + co) = o;
+          if (y2) *(uint2*)(y2 + ya + co) = o;
+        }
+      } else {
+        // two pieces hold 16 channels of a pixel in two lanes, 4 + 4 interleaved: exchanged between
+        // the lane halves so that each ends with 8 consecutive ones (one 16-byte store)
+#pragma unroll
+        for (int i = 0; i < TP; i += 2) {
+          const uint2 e = pack(i), o = pack(i + 1);
+          const auto s0 = __builtin_amdgcn_permlane32_swap(e.x, o.x, false, false);
+          const auto s1 = __builtin_amdgcn_permlane32_swap(e.y, o.y, false, false);
+          const u32x4 v = u32x4{(unsigned)s0[0], (unsigned)s1[0], (unsigned)s0[1], (unsigned)s1[1]};
+          const int co = cb + a * 32 + i * 8 + half * 8;
+          if (live && co < C_out) {
+            *(u32x4*)(y + ya + co) = v;
+            if (y2) *(u32x4*)(y2 + ya + co) = v;
+          }
+        }
+      }
+    }
+  }
+}
+
 // TP x 32 pixels x NT x 32 channels per workgroup; NI: load instructions per wavefront and patch.
 template <typename T, int TP, int NT, int NI, bool POOL, int S>
 __device__ __forceinline__ void patch_body(const PatchParams& p, const int bx, const int gx) {
   constexpr int KE = 16 / (int)sizeof(T);
   constexpr int BUF = NI * 4096;            // bytes of a patch in LDS
-  constexpr int UNITS = TP * 4;             // (32 pixels x 8 channels) pieces of a 32-channel tile
-  constexpr int SMEM = 2 * BUF > 4 * UNITS * 1024 ? 2 * BUF : 4 * UNITS * 1024;
+  constexpr int SMEM = 2 * BUF > TP * 16384 ? 2 * BUF : TP * 16384;
   __shared__ __attribute__((aligned(1024))) unsigned char smem[SMEM];
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int px = lane & 31, half = lane >> 5;
-  const TileId tile = xcd_tile(bx, gx, gridDim.y, 1, p.by_group);
-  const bool second = S == 2 && tile.n >= p.sib.first;
-  const int tile_n = second ? tile.n - p.sib.first : tile.n, co0 = tile_n * (32 * NT);
-  const int q = fastdiv(tile.m, p.by_ntx), tx = tile.m - q * p.ntx;
-  const int n = fastdiv(q, p.by_nty), ty = q - n * p.nty;
-  const int r0 = ty * p.th, c0 = tx * p.tw;            // the tile's first row of the launch and first column
+  const PatchAt tile = patch_at(p, bx, gx, S == 2);
+  const bool second = tile.second;
+  const int tile_n = tile.tile_n, n = tile.n, r0 = tile.r0, c0 = tile.c0;
   const int row_bytes = p.C_in * (int)sizeof(T);
   const int chunks = row_bytes / 128;
 
@@ -118,21 +296,10 @@ __device__ __forceinline__ void patch_body(const PatchParams& p, const int bx, c
   // first tap of it lies in a patch
   int at[TP];
   const unsigned lds0 = (unsigned)(unsigned long)(__attribute__((address_space(3))) unsigned char*)smem;
-  auto pixel = [&](int f, int& r, int& c) __attribute__((always_inline)) {
-    const int i = f * 32 + px;
-    if constexpr (POOL) {
-      const int v = i >> 2, vr = fastdiv(v, p.by_tw), vc = v - vr * (p.tw >> 1);   // (by_tw divides by tw / 2)
-      r = vr * 2 + ((i >> 1) & 1);
-      c = vc * 2 + (i & 1);
-    } else {
-      r = fastdiv(i, p.by_tw);
-      c = i - r * p.tw;
-    }
-  };
 #pragma unroll
   for (int f = 0; f < TP; ++f) {
     int r, c;
-    pixel(f, r, c);
+    tile_pixel<POOL>(p, f * 32 + px, r, c);
     r = min(r, p.th - 1);                   // (lanes past the tile compute its last row again; they store nothing)
     at[f] = (int)lds0 + ((r * S) * p.pitch + c) * kPixelBytes + wave * 32 + half * 16;
   }
@@ -229,141 +396,205 @@ __device__ __forceinline__ void patch_body(const PatchParams& p, const int bx, c
     run_patch(c, false);
   }
 
-  // ---- the four partial tiles, added in wavefront order through LDS: wavefront w finishes pieces
-  // w TP .. (w + 1) TP of the UNITS pieces (piece u: fragment u / 4, channels (u % 4) * 8 ..)
-  u32x4* const part = (u32x4*)smem;
-  const Clamp cl = make_clamp(second ? p.sib.act : p.act);
-  const int C_out = second ? p.sib.C_out : p.C_out;
-  const float* const bias_at = second ? p.sib.bias : p.bias;
-  T* const y = (T*)(second ? p.sib.y : p.y);
-  T* const y2 = second ? nullptr : (T*)p.y2;
-  // where they go, and what is added to them: all loads issued here, ahead of the sums
-  int r, cc;
-  pixel(wave * TP / 4, r, cc);             // (a wavefront's pieces all lie in one fragment)
-  const int row = r0 + r, col = c0 + cc;
-  bool live = (r < p.th) & (row < p.R) & (col < p.Wc);
-  if (second) live = live & (p.out_lo + row >= p.sib.lo) & (p.out_lo + row < p.sib.hi);
-  const int cb = co0 + ((wave * TP) & 3) * 8;   // first channel of this wavefront's pieces
-  f32x4 bias[NT][TP];
+  patch_finish<T, TP, NT, POOL>(p, smem, acc, tile, lane, wave, [](int, f32x4 (&)[TP]) {});
+}
+
+// The fp32 form: products on the bf16 matrix cores (conv_gemm.hip says how, and how precise). A pixel of the patch is
+// split into its three bf16 parts on the way from memory through registers to LDS, 208 bytes for 32 channels
+// (an odd number of 16-byte slots again); the filter comes from memory as it is, a patch ahead, and every wavefront splits
+// what it multiplies: parts made beforehand are 6 bytes a weight instead of 4, and the vector cache's 30 bytes a cycle were
+// what bounded that (133 against 128 us a chain of the fp32 backbone). Of the 18 steps of 16 channels that a patch has per
+// pixel, wavefronts 0 and 2 take the first 16 channels and 1 and 3 the second, 0 and 1 five taps and 2 and 3 four of an
+// even patch, the other way round of an odd one. A patch is 864 TP cycles of matrix instructions (2 304 TP on the fp32
+// ones), 1 150 + 150 TP of vector instructions and 1 600 of loads, shared by the two or three workgroups of a compute unit;
+// alone it takes 2 500 (TP = 1) or 3 400.
+template <int TP, int NI, bool POOL, int S>
+__device__ __forceinline__ void patch_split_body(const PatchParams& p, const int bx, const int gx) {
+  constexpr int PB = 208, BUF = NI * 32 * PB;
+  constexpr int SMEM = 2 * BUF > TP * 16384 ? 2 * BUF : TP * 16384;
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[SMEM];
+
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int px = lane & 31, half = lane >> 5, step = wave & 1;
+  const PatchAt tile = patch_at(p, bx, gx, S == 2);
+  const bool second = tile.second;
+  const int row_bytes = p.C_in * 4, chunks = p.C_in / 32;
+  const __amdgpu_buffer_rsrc_t xbuf = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<void*>(p.x), 0, (int)((size_t)p.N * p.x_rows * p.W * row_bytes), 0x00020000);
+  const int ih0 = (p.out_lo + tile.r0) * S - p.ph, iw0 = tile.c0 * S - p.pw;
+  auto input = [&](int ih, int iw) -> unsigned {   // of a pixel's first channel, or outside
+    const bool ok = (ih >= p.x_row0) & (ih < p.x_row0 + p.x_rows) & (iw >= 0) & (iw < p.W);
+    return ok ? (unsigned)(((tile.n * p.x_rows + ih - p.x_row0) * p.W + iw) * row_bytes) : kOutside;
+  };
+  // ---- the pieces this lane moves of every patch: channels 4 k .. 4 k + 3 of pixel threadIdx.x / 8 + 32 i
+  const int k4 = threadIdx.x & 7;
+  unsigned src[NI];
 #pragma unroll
-  for (int a = 0; a < NT; ++a)
+  for (int i = 0; i < NI; ++i) {
+    const int pix = i * 32 + (int)(threadIdx.x >> 3);
+    const int pr = fastdiv(pix, p.by_pitch), pc = pix - pr * p.pitch, half_cols = p.pitch >> 1;
+    const int col = S == 1 ? pc : (pc < half_cols ? 2 * pc : 2 * (pc - half_cols) + 1);
+    const unsigned at = pr < p.ph_rows ? input(ih0 + pr, iw0 + col) : kOutside;
+    src[i] = at == kOutside ? kOutside : at + k4 * 16;
+  }
+  u32x4 raw[2][NI];   // of the next two patches
+  // (Loads are issued for patches past the last one, too, from outside the buffer or of the last filter again: a
+  // load under a condition would make every wait one for all loads in flight.)
+  auto fetch_patch = [&](int c, u32x4 (&d)[NI]) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < TP; ++i) bias[a][i] = f32x4{0.f, 0.f, 0.f, 0.f};
-  if (bias_at) {
+    for (int i = 0; i < NI; ++i)
+      d[i] = __builtin_amdgcn_raw_buffer_load_b128(xbuf, (int)(c < chunks ? src[i] : kOutside), c * 128, 0);
+  };
+  unsigned char* const put = smem + (threadIdx.x >> 3) * PB + (k4 >> 2) * 96 + (k4 & 1) * 16 + (k4 >> 1 & 1) * 8;
+  auto store = [&](int buf, int i, u32x4 (&d)[NI]) __attribute__((always_inline)) {
+    uint2 parts[3];
+    split_bf16(__builtin_bit_cast(f32x4, d[i]), parts);
 #pragma unroll
-    for (int a = 0; a < NT; ++a)
+    for (int k = 0; k < 3; ++k) *(uint2*)(put + buf * BUF + i * 32 * PB + k * 32) = parts[k];
+  };
+  // ---- the filter: five taps (four, and one of them twice) of a patch, two pieces of eight channels' fp32 values each
+  const int k_steps = second ? p.sib.k_steps : p.k_steps;
+  const u32x4* const wd = (const u32x4*)(second ? p.sib.wd : p.wd) + (size_t)tile.tile_n * k_steps * 64 + lane;
+  const int tap_stride = p.C_in / 8 * 64;
+  auto first_tap = [&](int c) { return (wave >> 1 ^ c) & 1 ? 5 : 0; };
+  u32x4 w[5][2];
+  auto fetch_tap = [&](int c, int j) __attribute__((always_inline)) {
+    const int cc = min(c, chunks - 1);
+    const u32x4* const from = wd + (size_t)(min(first_tap(cc) + j, 8) * tap_stride + (cc * 4 + 2 * step) * 64);
 #pragma unroll
-      for (int i = 0; i < TP; ++i) {
-        const int co = cb + a * 32 + i * 8 + half * 4;
-        bias[a][i] = *(const f32x4*)(bias_at + (co < C_out ? co : 0));
+    for (int k = 0; k < 2; ++k) w[j][k] = from[k * 64];
+  };
+
+  fetch_patch(0, raw[0]);
+  if (!second) {
+#pragma unroll
+    for (int j = 0; j < 5; ++j) fetch_tap(0, j);
+  }
+  fetch_patch(1, raw[1]);
+
+  // ---- this lane's pixel of every 32-pixel fragment: where the first tap of it lies in a patch
+  int at[TP];
+#pragma unroll
+  for (int f = 0; f < TP; ++f) {
+    int r, c;
+    tile_pixel<POOL>(p, f * 32 + px, r, c);
+    r = min(r, p.th - 1);                   // (lanes past the tile compute its last row again; they store nothing)
+    at[f] = ((r * S) * p.pitch + c) * PB + step * 96 + half * 16;
+  }
+  f32x16 acc[1][TP], low[1][TP];
+#pragma unroll
+  for (int f = 0; f < TP; ++f)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[0][f][i] = low[0][f][i] = 0.f;
+
+  auto read_tap = [&](int buf, int t, u32x4 (&d)[TP][3]) __attribute__((always_inline)) {
+    const int a = t >= 6 ? 2 : t >= 3 ? 1 : 0, b = t - 3 * a;
+    // (S == 2: an odd column lies half a row further, two columns further is the next even one)
+    const int off = buf + (a * p.pitch + (S == 1 ? b : b == 1 ? p.pitch >> 1 : b >> 1)) * PB;
+#pragma unroll
+    for (int f = 0; f < TP; ++f)
+#pragma unroll
+      for (int k = 0; k < 3; ++k) d[f][k] = *(const u32x4*)(smem + at[f] + off + k * 32);
+  };
+#pragma unroll
+  for (int i = 0; i < NI; ++i) store(0, i, raw[0]);
+  fetch_patch(2, raw[0]);
+  u32x4 x[2][TP][3], parts[2][1][3];
+  auto barrier = [&]() __attribute__((always_inline)) {   // (for LDS only: loads from memory stay in flight)
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  };
+  auto multiply = [&](int j) __attribute__((always_inline)) {
+#pragma unroll
+    for (int e = 0; e < 6; ++e) mma_split_part<1, TP>(parts[j & 1], x[j & 1], acc, low, e);
+  };
+  // One patch (even ones in the first half of LDS, set 0). While a tap is multiplied, the next one's pixels come out of
+  // LDS, its filter is split, and the next patch is split and stored into the memory that every wavefront was
+  // done with at the barrier: vector instructions between the matrix instructions, which keep their pipe busy for
+  // 32 cycles each.
+  auto run_patch = [&](int c, int set) __attribute__((always_inline)) {
+    barrier();
+    const int buf = set * BUF, t0 = first_tap(c);
+    read_tap(buf, t0, x[0]);
+    split_bf16(w[0][0], w[0][1], parts[0][0]);
+    fetch_tap(c + 1, 0);
+#pragma unroll
+    for (int j = 0; j < 5; ++j) {
+      __builtin_amdgcn_sched_barrier(0);
+      if (j < 4) {
+        read_tap(buf, min(t0 + j + 1, 8), x[(j + 1) & 1]);
+        multiply(j);
+        split_bf16(w[j + 1][0], w[j + 1][1], parts[(j + 1) & 1][0]);
+        fetch_tap(c + 1, j + 1);
       }
-  }
-  typedef unsigned raw_t __attribute__((ext_vector_type(sizeof(T))));   // four elements
-  raw_t res[NT][TP];
-  if constexpr (!POOL) {
-    if (p.res && !second) {
-      const size_t ra = live ? ((size_t)(n * p.r_rows + p.out_lo + row - p.r_row0) * p.W_out + col) * p.C_out : 0;
 #pragma unroll
-      for (int a = 0; a < NT; ++a)
+      for (int i = j * NI / 5; i < (j + 1) * NI / 5; ++i) store(set ^ 1, i, raw[set ^ 1]);
+      if (j < 4) {
 #pragma unroll
-        for (int i = 0; i < TP; ++i) {
-          const int co = cb + a * 32 + i * 8 + half * 4;
-          res[a][i] = *(const raw_t*)((const T*)p.res + ra + (co < p.C_out ? co : 0));
+        for (int i = 0; i < 6 * TP; ++i) {
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // one matrix instruction,
+          __builtin_amdgcn_sched_group_barrier(0x002, 8, 0);   // eight vector instructions
         }
-    } else {
-#pragma unroll
-      for (int a = 0; a < NT; ++a)
-#pragma unroll
-        for (int i = 0; i < TP; ++i) res[a][i] = raw_t(0u);
+      }
     }
+    fetch_patch(c + 3, raw[set ^ 1]);
+    __builtin_amdgcn_sched_barrier(0);
+    if (t0 == 0) multiply(4);
+  };
+  if (second) {   // one tap, the centre
+    for (int c = 0; c < chunks; ++c) {
+#pragma unroll
+      for (int k = 0; k < 2; ++k) w[0][k] = wd[(size_t)(c * 4 + 2 * step + k) * 64];
+      split_bf16(w[0][0], w[0][1], parts[0][0]);
+      barrier();
+      if (wave < 2) {
+        read_tap((c & 1) * BUF, 4, x[0]);
+        multiply(0);
+      }
+      fetch_patch(c + 1, raw[0]);
+#pragma unroll
+      for (int i = 0; i < NI; ++i) store((c & 1) ^ 1, i, raw[0]);
+    }
+  } else {
+    int c = 0;
+    for (; c + 1 < chunks; c += 2) {
+      run_patch(c, 0);
+      run_patch(c + 1, 1);
+    }
+    if (c < chunks) run_patch(c, 0);
   }
 #pragma unroll
-  for (int a = 0; a < NT; ++a) {
-    __syncthreads();
+  for (int f = 0; f < TP; ++f) acc[0][f] += low[0][f];
+
+  // fp32 instructions, on operands straight from memory: the wavefront's fragment with all its channels
+  auto again = [&](int f, f32x4 (&sum)[TP]) __attribute__((always_inline)) {
+    int r, c;
+    tile_pixel<POOL>(p, f * 32 + px, r, c);
+    f32x16 all;
 #pragma unroll
-    for (int u = 0; u < UNITS; ++u) {
-      const f32x16& s = acc[a][u / 4];
-      const int g = (u % 4) * 4;
-      part[(wave * UNITS + u) * 64 + lane] = __builtin_bit_cast(u32x4, f32x4{s[g], s[g + 1], s[g + 2], s[g + 3]});
+    for (int i = 0; i < 16; ++i) all[i] = 0.f;
+    for (int t = second ? 4 : 0; t < (second ? 5 : 9); ++t) {
+      const unsigned from = input(ih0 + r * S + t / 3, iw0 + c * S + t % 3);
+      for (int s = 0; s < p.C_in / 8; ++s) {
+        const u32x4 xv = __builtin_amdgcn_raw_buffer_load_b128(xbuf, (int)(from == kOutside ? kOutside : from + s * 32 + half * 16), 0, 0);
+        mma<float>(wd[(size_t)((second ? 0 : t * (p.C_in / 8)) + s) * 64], xv, all);
+      }
     }
-    __syncthreads();
-    f32x4 sum[TP];
 #pragma unroll
     for (int i = 0; i < TP; ++i) {
-      sum[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+      const int g = (wave * TP + i) % 4;
 #pragma unroll
-      for (int s = 0; s < 4; ++s) sum[i] += __builtin_bit_cast(f32x4, part[(s * UNITS + wave * TP + i) * 64 + lane]);
-    }
-    // ---- pooling, bias, residual, activation, the one rounding
-    size_t ya;
-    if constexpr (POOL) {
+      for (int j = 0; j < 4; ++j) {
+        float v = all[j];
 #pragma unroll
-      for (int i = 0; i < TP; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          float v = sum[i][j];
-          v = fmaxf(v, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0xB1, 0xf, 0xf, true)));  // lane ^ 1
-          v = fmaxf(v, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x4E, 0xf, 0xf, true)));  // lane ^ 2
-          sum[i][j] = v;
-        }
-      live = live & ((lane & 3) == 0);
-      ya = ((size_t)(n * p.y_rows + ((p.out_lo + row) >> 1) - p.y_row0) * p.W_out + (col >> 1)) * p.C_out;
-    } else {
-      ya = ((size_t)(n * (second ? p.sib.y_rows : p.y_rows) + p.out_lo + row - (second ? p.sib.y_row0 : p.y_row0)) * p.W_out + col) * C_out;
-    }
-#pragma unroll
-    for (int i = 0; i < TP; ++i) {
-      sum[i] += bias[a][i];
-      if constexpr (!POOL) {
-        alignas(16) T rr[4];
-        *(raw_t*)rr = res[a][i];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) sum[i][j] += to_f32(rr[j]);
-      }
-#pragma unroll
-      for (int j = 0; j < 4; ++j) sum[i][j] = clamp_act(sum[i][j], cl);
-    }
-    if constexpr (sizeof(T) == 4) {
-#pragma unroll
-      for (int i = 0; i < TP; ++i) {
-        const int co = cb + a * 32 + i * 8 + half * 4;
-        if (live && co < C_out) {
-          *(f32x4*)(y + ya + co) = sum[i];
-          if (y2) *(f32x4*)(y2 + ya + co) = sum[i];
-        }
-      }
-    } else {
-      auto pack = [&](int i) {
-        alignas(8) __bf16 o[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) o[j] = (__bf16)sum[i][j];
-        return *(const uint2*)o;
-      };
-      if constexpr (TP == 1) {
-        const uint2 o = pack(0);
-        const int co = cb + a * 32 + half * 4;
-        if (live && co < C_out) {
-          *(uint2*)(y + ya + co) = o;
-          if (y2) *(uint2*)(y2 + ya + co) = o;
-        }
-      } else {
-        // two pieces hold 16 channels of a pixel in two lanes, 4 + 4 interleaved: exchanged between
-        // the lane halves so that each ends with 8 consecutive ones (one 16-byte store)
-#pragma unroll
-        for (int i = 0; i < TP; i += 2) {
-          const uint2 e = pack(i), o = pack(i + 1);
-          const auto s0 = __builtin_amdgcn_permlane32_swap(e.x, o.x, false, false);
-          const auto s1 = __builtin_amdgcn_permlane32_swap(e.y, o.y, false, false);
-          const u32x4 v = u32x4{(unsigned)s0[0], (unsigned)s1[0], (unsigned)s0[1], (unsigned)s1[1]};
-          const int co = cb + a * 32 + i * 8 + half * 8;
-          if (live && co < C_out) {
-            *(u32x4*)(y + ya + co) = v;
-            if (y2) *(u32x4*)(y2 + ya + co) = v;
-          }
-        }
+        for (int q = 1; q < 4; ++q) v = g == q ? all[q * 4 + j] : v;
+        sum[i][j] = v;
       }
     }
-  }
+  };
+  patch_finish<float, TP, 1, POOL>(p, smem, acc, tile, lane, wave, again);
 }
 
 // Load instructions per wavefront and patch: the patch of a tile has at most NI * 256 / 9 pixels.
@@ -371,18 +602,29 @@ constexpr int patch_loads(int tp, int s) { return s == 1 ? (tp == 4 ? 7 : tp == 
 constexpr int patch_room(int bm, int s) { return patch_loads(bm / 32, s) * 256 / kPixelSlots; }
 
 template <typename T, int BM, int BN, bool POOL, int S>
+__device__ __forceinline__ void patch_tile(const PatchParams& p, const int bx, const int gx) {
+  if constexpr (sizeof(T) == 4) {
+    static_assert(BN == 32, "the fp32 form has one channel tile");
+    patch_split_body<BM / 32, patch_loads(BM / 32, S), POOL, S>(p, bx, gx);
+  } else {
+    patch_body<T, BM / 32, BN / 32, patch_loads(BM / 32, S), POOL, S>(p, bx, gx);
+  }
+}
+
+template <typename T, int BM, int BN, bool POOL, int S>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void conv_patch_kernel(const PatchParams p) {
-  patch_body<T, BM / 32, BN / 32, patch_loads(BM / 32, S), POOL, S>(p, blockIdx.x, gridDim.x);
+  patch_tile<T, BM, BN, POOL, S>(p, blockIdx.x, gridDim.x);
 }
 // The same for several bands of one layer in one grid (band b owns blocks first[b] .. first[b + 1] of x).
 template <typename T, int BM, int BN, bool POOL, int S>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void conv_patch_kernel_bands(const Batch<PatchParams> t) {
   const int b = batch_find(t, blockIdx.x);
-  patch_body<T, BM / 32, BN / 32, patch_loads(BM / 32, S), POOL, S>(t.p[b], blockIdx.x - t.first[b], t.first[b + 1] - t.first[b]);
+  patch_tile<T, BM, BN, POOL, S>(t.p[b], blockIdx.x - t.first[b], t.first[b + 1] - t.first[b]);
 }
 
 bool patch_shape(const OpLaunch& L) {
-  const int esz = L.dtype == LOP_BF16 ? 2 : 4, ke = 16 / esz;
+  const bool bf = L.dtype == LOP_BF16;
+  const int esz = bf ? 2 : 4, ke = 16 / esz;
   if (L.op != LOP_CONV2D || !L.wd || L.kh != 3 || L.kw != 3 || L.dh != 1 || L.dw != 1) return false;
   if (L.sh != L.sw || (L.sh != 1 && L.sh != 2)) return false;
   if (L.x.c * esz % 128 != 0 || L.y.c % ke != 0) return false;
@@ -401,22 +643,26 @@ struct PatchChoice { int bm = 0, bn = 0; };
 struct PatchCost { int bm, bn; double chunk, rest, alone, first; };
 constexpr PatchCost kBf16Costs[] = {
     {128, 64, 5800, 4900, 3300, 7000}, {64, 32, 1860, 840, 1100, 3500}, {32, 32, 1200, 620, 750, 3000}};
-// fp32: bound by its matrix instructions (2 304 cycles per chunk of a 32 x 32 tile)
-constexpr PatchCost kF32Costs[] = {{64, 32, 4700, 1500, 4900, 5000}, {32, 32, 2400, 900, 2500, 4000}};
+// fp32, fitted alike (chunk: 32 channels); 64 x 32 against 32 x 32 tiles: 64 -> 64 channels on 12 500 pixels 11.7 and 13.4 us,
+// on 3 100 7.4 and 6.1; 256 -> 256 on 1 600 18.9 and 20.5, on 784 17.0 and 14.1. On the fp32 instructions the
+// best of them were 14.0, 5.4, 23.9 and 14.1: what the bf16 ones save, one tile to a compute unit spends on instructions
+// (about 500 a wavefront and chunk), several share.
+constexpr PatchCost kF32Costs[] = {{64, 32, 5100, 3500, 3450, 4500}, {32, 32, 3400, 500, 2780, 2800}};
 constexpr int kPatchUnits = 256;
 // fp32 launches of fewer tiles are left to the kernels that cut the reduction finer (16 x 16 tiles, or
-// slices across workgroups): 256 -> 512 channels, stride 2, on 49 pixels 11.7 us there against 12.9
+// slices across workgroups). Alone the two are level at about 120 tiles (128 -> 128 channels on 784 pixels, 100 tiles: 8.2 us
+// here and there; 256 -> 256 on 400, 104: 12.9 and 11.1), with other launches beside them this one is ahead from
+// fewer on: the fp32 backbone with shared rows, three launches of 100 tiles, 58.5 us a chain, and 64.3 without.
 constexpr long kF32MinTiles = 100;
 // bf16: a handful of compute units cannot stream megabytes of filter (7 x 7 x 512 channels is 32 tiles: 5.6 us
 // here, 8.9 there)
 constexpr long kBf16MinTiles = 24;
 // Stride 2: a patch is four times the outputs, so a tile fetches nearly twice what the kernel that fetches taps does per
-// output (2.25 of them) and gains by waiting for them once instead of nine times. bf16 launches use this form up to
-// one tile per compute unit, fp32 ones up to four. Measured alone, there -> here (us): bf16 128 -> 256 channels on 1 800
-// pixels (456 tiles) 7.7 -> 5.7, 3 600 (904) 9.7 -> 9.3, 7 200 (1 800) 12.9 -> 15.6; 256 -> 512 on 900 (464) 12.0 -> 8.0, on
-// 1 800 (912) 15.6 -> 13.2; 64 -> 64 on 7 200 (450) 5.0 -> 4.5. fp32 64 -> 128 on 10 400 (1 300) 28.2 -> 23.0, on
-// 25 600 (3 200) 55.8 -> 47.5; 256 -> 512 on 4 900 (2 464) 187 -> 125. So both lines lie lower than where the two are level
-// (bf16 about 900 tiles, fp32 above 3 200). The tile's memory is not what draws them: three workgroups fit a compute unit.
+// output (2.25 of them) and gains by waiting for them once instead of nine times. fp32 launches always do (there -> here,
+// us alone: 64 -> 128 channels on 3 136 pixels 11.6 -> 10.0, on 12 800 31.5 -> 30.1; 256 -> 512 on 1 568 62 -> 46). bf16
+// ones up to one tile per compute unit: beyond that they are ahead alone up to about four (128 -> 256 on 3 600 pixels, 904
+// tiles, 9.6 -> 8.9; on 6 400, 1 600 tiles, 12.3 -> 13.2), but not with other launches beside them (detector encoder with
+// shared rows, one launch of 904 tiles: 63.9 -> 64.9 us a chain).
 constexpr long kStride2MaxTiles = kPatchUnits;
 
 PatchChoice choose_patch(const OpLaunch* convs, const OpLaunch* pools, int n) {
@@ -437,7 +683,7 @@ PatchChoice choose_patch(const OpLaunch* convs, const OpLaunch* pools, int n) {
   };
   const long small = tiles(32, 32);
   if (small < (bf ? kBf16MinTiles : kF32MinTiles)) return {};
-  if (L.sh == 2) return !pools && small <= (bf ? kStride2MaxTiles : 4 * kStride2MaxTiles) ? PatchChoice{32, 32} : PatchChoice{};
+  if (L.sh == 2) return !pools && (!bf || small <= kStride2MaxTiles) ? PatchChoice{32, 32} : PatchChoice{};
   const double chunks = L.x.c * (bf ? 2 : 4) / 128;
   PatchChoice best;
   double best_cost = 0;

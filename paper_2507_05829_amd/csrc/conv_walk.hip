@@ -46,14 +46,6 @@ struct WalkTile {
   static constexpr int BUF = NI * 4096;
 };
 
-// f(integral_constant<0>) ... f(integral_constant<N - 1>): what the loads' immediate offsets need
-template <int N, int I = 0, typename F>
-__device__ __forceinline__ void unroll(F&& f) {
-  if constexpr (I < N) {
-    f(std::integral_constant<int, I>{});
-    unroll<N, I + 1>(f);
-  }
-}
 template <int OFF>
 __device__ __forceinline__ void lds_read(u32x4& d, int addr) {
   // (reads of our own: those the compiler can see would make it wait for every load in flight to LDS)

@@ -1,7 +1,7 @@
 // Launch interface of the gfx950 kernels. Every kernel works on row slabs: a tensor is
 // N x rows x W x C (NHWC) holding rows [row0, row0 + rows) of an image of height h.
 #pragma once
-#include <hip/hip_runtime_api.h>
+#include <hip/hip_runtime.h>
 
 #include <cstddef>
 #include <cstdint>
@@ -48,19 +48,21 @@ struct OpLaunch {
 // (co % 16) holds w[co][step*MK16 + quarter*KE ... + KE).
 // fp32 layers whose reduction is long enough for the bf16 matrix cores (split_shape) get their weights as
 // sums of three bf16 values, too: [c_out_pad / 32][k_pad / 16][part][64 lanes] x 16 bytes, lane = half*32 +
-// (co % 32) holds part of w[co][step*16 + half*8 ... + 8).
+// (co % 32) holds part of w[co][step*16 + half*8 ... + 8), directly behind the operand-order packing.
 // The row count is padded to the widest channel tile that can take the layer: 128, and 256 once
 // there are more than 128 channels (the 256-wide tile is never chosen below that), so the last
 // channel tile of any kernel reads rows that exist.
 constexpr int kConvCoutPad = 128;
 int conv_k_pad(int c_in, int kh, int kw, int dtype);
-inline int conv_cout_pad(int c_out) {
+__host__ __device__ inline int conv_cout_pad(int c_out) {
   const int unit = c_out > kConvCoutPad ? 2 * kConvCoutPad : kConvCoutPad;
   return (c_out + unit - 1) / unit * unit;
 }
 
-// Whether a dense fp32 conv gets that packing.
-bool split_shape(int c_in, int c_out, int kh, int kw);
+// Whether a dense fp32 conv that has the operand-order packing gets the one as three bf16 parts, and that packing,
+// from the first one on the device.
+bool split_shape(int c_in, int kh, int kw);
+hipError_t launch_split_weights(const void* w, int c_out_pad, int k_pad, void* w3, hipStream_t stream);
 
 // Bytes of split-K scratch the dense conv launch needs (0: none).
 size_t conv_workspace_bytes(const OpLaunch& L);

@@ -142,14 +142,6 @@ inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 namespace {
 
-// Rounded to the nearest bfloat16, ties to even; a NaN stays one.
-unsigned short bf16_bits(float v) {
-  unsigned u;
-  std::memcpy(&u, &v, 4);
-  if ((u & 0x7fffffffu) > 0x7f800000u) return (unsigned short)(u >> 16 | 0x40);
-  return (unsigned short)((u + 0x7fffu + (u >> 16 & 1)) >> 16);
-}
-
 int upload_weights(lop_plan_t* P) {
   const lop::Tables& t = P->t;
   const int nl = t.n_layers();
@@ -221,8 +213,13 @@ int upload_weights(lop_plan_t* P) {
               const size_t dst = (((size_t)(co / 32) * steps + st) * 64 + half * 32 + co % 32) * ke;
               std::memcpy(&ord[dst * esz], &host[src * esz], 16);
             }
-        LOP_HIP(lop::dev_alloc(&P->d_wd[l], ord.size()));
+        // (fp32 layers: and behind them as three bf16 parts)
+        LOP_HIP(lop::dev_alloc(&P->d_wd[l], ord.size() + (P->has_w3[l] ? (size_t)cp * kp * 6 : 0)));
         LOP_HIP(hipMemcpy(P->d_wd[l], ord.data(), ord.size(), hipMemcpyHostToDevice));
+        if (P->has_w3[l]) {
+          P->d_w3[l] = (char*)P->d_wd[l] + ord.size();
+          LOP_HIP(lop::launch_split_weights(P->d_w[l], cp, kp, P->d_w3[l], nullptr));
+        }
         if (P->has_wd16[l]) {
           // ... and in the order of 16 x 16 tiles: [co / 16][step][quarter*16 + co % 16] x 16 B
           const size_t steps16 = (size_t)kp / (4 * ke);
@@ -236,26 +233,6 @@ int upload_weights(lop_plan_t* P) {
           LOP_HIP(lop::dev_alloc(&P->d_wd16[l], ord.size()));
           LOP_HIP(hipMemcpy(P->d_wd16[l], ord.data(), ord.size(), hipMemcpyHostToDevice));
         }
-      }
-      if (P->has_w3[l]) {
-        // fp32 values as sums of three bf16 ones: [co / 32][step of 16][part][half*32 + co % 32] x 8 elements
-        std::vector<unsigned short> parts((size_t)cp * kp * 3);
-        const float* const row = (const float*)host.data();
-        for (int co = 0; co < d.c_out; ++co)
-          for (int k = 0; k < kp; ++k) {
-            float left = row[(size_t)co * kp + k];
-            if (left == 0.f) continue;
-            unsigned short* const at = &parts[(((size_t)(co / 32) * (kp / 16) + k / 16) * 192 + (k / 8 % 2) * 32 + co % 32) * 8 + k % 8];
-            for (int part = 0; part < 3; ++part) {
-              at[part * 512] = bf16_bits(left);
-              const unsigned u = (unsigned)at[part * 512] << 16;
-              float v;
-              std::memcpy(&v, &u, 4);
-              left -= v;
-            }
-          }
-        LOP_HIP(lop::dev_alloc(&P->d_w3[l], parts.size() * 2));
-        LOP_HIP(hipMemcpy(P->d_w3[l], parts.data(), parts.size() * 2, hipMemcpyHostToDevice));
       }
     } else if (d.op == LOP_DWCONV2D) {
       if (!d.weight) return LOP_ERR_INVALID_ARG;
@@ -1480,7 +1457,7 @@ int lop_plan(const lop_layer_t* layers, int n_layers, const lop_tensor_desc_t* i
     P->k_pad[l] = lop::conv_k_pad(d.c_in, d.kh, d.kw, in->dtype);
     P->has_wd[l] = d.c_in % ke == 0 && d.c_out % ke == 0;
     P->has_wd16[l] = P->has_wd[l] && P->k_pad[l] % (4 * ke) == 0;
-    P->has_w3[l] = in->dtype == LOP_F32 && lop::split_shape(d.c_in, d.c_out, d.kh, d.kw);
+    P->has_w3[l] = in->dtype == LOP_F32 && P->has_wd[l] && lop::split_shape(d.c_in, d.kh, d.kw);
     P->has_wstem[l] = lop::stem_shape_applies(d.c_in, d.c_out, d.kh, d.kw, d.sw, d.dh, d.dw,
                                               d.residual_from != LOP_NO_RESIDUAL);
   }
@@ -1538,7 +1515,6 @@ void lop_plan_destroy(lop_plan_t* P) {
   for (void* w : P->d_w) if (w) (void)lop::dev_free(w);
   for (void* w : P->d_wd) if (w) (void)lop::dev_free(w);
   for (void* w : P->d_wd16) if (w) (void)lop::dev_free(w);
-  for (void* w : P->d_w3) if (w) (void)lop::dev_free(w);
   for (void* w : P->d_wstem) if (w) (void)lop::dev_free(w);
   for (float* b : P->d_bias) if (b) (void)lop::dev_free(b);
   for (auto* v : {&P->ev_done, &P->ev_copied, &P->ev_c0, &P->ev_c1, &P->ev_d0, &P->ev_d1})

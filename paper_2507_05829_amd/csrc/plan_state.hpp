@@ -58,7 +58,7 @@ struct lop_plan_s {
   std::vector<void*> d_w;      // per layer packed weights (device) or nullptr
   std::vector<void*> d_wd;     // dense conv weights in MFMA operand order, or nullptr
   std::vector<void*> d_wd16;   // ... in the operand order of 16 x 16 tiles, or nullptr
-  std::vector<void*> d_w3;     // ... of fp32 layers as three bf16 parts in operand order, or nullptr
+  std::vector<void*> d_w3;     // ... of fp32 layers as three bf16 parts, in d_wd's allocation behind the others, or nullptr
   std::vector<void*> d_wstem;  // ... as fp32 [c_out / 4][k][4] for the first-layer kernel, or nullptr
   Fusion fuse_band;   // groups of the launches that compute one band
   Fusion fuse_chain;  // groups of the launches that compute all bands (kGrouped, kWhole)

@@ -1584,6 +1584,58 @@ def test_walking_kernel(oracle, cfg):
 
 
 @pytest.mark.parametrize("cfg", [
+    # c_in, c_out, stride, pooled, shape(n,h,w), residual, the tile expected
+    (96, 40, 1, False, (1, 61, 67), True, "<float, 32, 32, false, 1>"),      # three patches: an odd number; channels end inside a tile
+    (32, 64, 1, True, (1, 77, 62), False, "<float, 32, 32, true, 1>"),       # one patch; pooling
+    (128, 64, 1, False, (2, 80, 83), True, "<float, 64, 32, false, 1>"),     # four patches
+    (64, 72, 2, False, (1, 121, 119), False, "<float, 32, 32, false, 2>"),   # stride 2
+])
+def test_fp32_patch_form_precision(cfg):
+    """fp32 3 x 3 convolutions on the bf16 matrix cores: within fp32 rounding of the 64-bit result, and around
+    values that are not finite what the fp32 instructions make of them."""
+    c_in, c_out, stride, pooled, shape, residual, tile = cfg
+    chain = workloads.Chain("patch", (shape[0], c_in, shape[1], shape[2]), "f32", 1)
+    first = chain.add(workloads.CONV, c_in, c_out, 1, stride, 0, act="none") if residual else workloads.NO_RESIDUAL
+    chain.add(workloads.CONV, c_in, c_out, 3, stride, 1, act="relu", input_from=workloads.CHAIN_INPUT, residual_from=first)
+    if pooled:
+        chain.add(workloads.MAXPOOL, c_out, c_out, 2, 2, 0)
+    t = workloads.make_tensors(chain, zero_bias=False, seed=31)
+    plan = lop.Plan(chain, t, 1)
+    try:
+        assert plan.layer_kernel(0, plan.n_layers - 1)[0] == "conv_patch_kernel" + tile
+    finally:
+        plan.destroy()
+
+    def reference(x):
+        f = lambda a: torch.from_numpy(np.asarray(a, np.float64))
+        conv = 1 if residual else 0
+        y = torch.nn.functional.conv2d(f(x), f(t.weights[conv]), f(t.biases[conv]), stride, 1)
+        if residual:
+            y = y + torch.nn.functional.conv2d(f(x), f(t.weights[0]), f(t.biases[0]), stride)
+        y = y.relu()
+        return (torch.nn.functional.max_pool2d(y, 2) if pooled else y).numpy()
+
+    want = reference(t.x)
+    dev, host = run_gpu(chain, t)
+    np.testing.assert_array_equal(dev, host)
+    # 9 c_in / 16 roundings of 2^-24 of sums that grow like their square root, as in the matrix products
+    assert np.linalg.norm(dev - want) <= 2 * np.sqrt(9 * c_in / 16) * 2.0 ** -24 * np.linalg.norm(want)
+    # one pixel of every kind in a corner; nothing it does not reach changes by more than rounding
+    for value in (np.inf, -np.inf, 3.4e38):
+        x = t.x.copy()
+        x[0, 5, 9, 11] = value
+        t_odd = workloads.Tensors(x, t.weights, t.biases)
+        dev, _ = run_gpu(chain, t_odd)
+        with np.errstate(invalid="ignore", over="ignore"):
+            odd = reference(x).astype(np.float32)
+        assert np.isfinite(odd).mean() > 0.9 and not np.array_equal(odd, want.astype(np.float32))
+        ok = np.isfinite(odd) & (np.abs(odd) < 1e30)
+        assert (np.abs(dev[ok] - odd[ok]) <= 1e-5 * np.maximum(np.abs(odd[ok]), 1)).all()
+        large = np.isposinf(odd) | (np.isfinite(odd) & ~ok)
+        np.testing.assert_allclose(dev[large], odd[large], rtol=1e-5)
+
+
+@pytest.mark.parametrize("cfg", [
     # dtype, c_in, c_out, shape(n,h,w): a stride-2 block's convolution and shortcut in one launch
     ("bf16", 64, 72, (1, 27, 45)),      # channels end inside a tile
     ("bf16", 128, 256, (2, 13, 11)),    # two patches, batch 2
