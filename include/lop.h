@@ -112,8 +112,8 @@ typedef struct {
                                  of consecutive calls rotate over the lanes. The bands' rows leave
                                  behind the last layer's launch. Not with LOP_FLAG_REUSE; at most
                                  16 bands; LOP_ERR_UNSUPPORTED if the chain has an inverted-residual
-                                 block or an operator whose kernel takes one band at a time
-                                 (the 1x1 streaming and 3x3 depthwise kernels)            */
+                                 block, or a layer that runs on the 1x1 streaming or the 3x3
+                                 depthwise kernel by itself                               */
 #define LOP_FLAG_NO_FUSE 32u  /* run every layer as a launch of its own. By default a 1x1 conv,
                                  a 3x3 depthwise conv and a 1x1 conv in a row whose middle
                                  tensors nobody else reads (an inverted-residual block) run as
@@ -125,8 +125,9 @@ typedef struct {
                                  band's own launches did not write first poisons the output  */
 #define LOP_FLAG_LANES(n) (((unsigned)(n) & 0xffu) << 8) /* bands are dealt round robin to n
                                  compute streams ("lanes", each with its own scratch) that run
-                                 concurrently; 0 = LOP_DEFAULT_LANES, capped at the number of
-                                 non-empty bands. With three or more lanes, independent
+                                 concurrently; 0 = LOP_DEFAULT_LANES (two of them for bands whose
+                                 slabs take more than 192 MiB, if nothing is copied), capped at the
+                                 number of non-empty bands. With three or more lanes, independent
                                  bands whose copies are long (more than 256 KiB per band,
                                  at most 64 MiB per chain) leave one lane to the copies:
                                  n - 1 lanes compute, and a lop_run_chain without
@@ -200,9 +201,9 @@ LOP_API int lop_run_band(lop_plan_t* plan, int band, const void* d_in, void* d_o
  * (LOP_FLAG_REUSE, chains without halos, one band) as one launch per layer over all their rows.
  * That holds for chains whose scratch (the layer outputs that are live together and the split-K
  * workspace of the merged launches) fits LOP_STATIC_SCRATCH_BYTES, in equal passes
- * over the images of a batch (independent bands whose operators all have launches for several bands:
- * then over groups of bands; chains of row-wise operators: over the rows of groups of bands) if not all at
- * once; a merged chain runs on one lane and consecutive
+ * over the images of a batch (independent bands: then over groups of bands; chains of row-wise operators: over the rows of
+ * groups of bands) if not all at once; chains with layers on the 1x1 streaming or the 3x3 depthwise kernel only if
+ * those passes are no more than a lane has bands; a merged chain runs on one lane and consecutive
  * calls rotate over the lanes. Larger chains run band by band on the lanes, band b's copy
  * overlapping the kernels of the bands after it (Sec. IV-B). Either way the rows computed are
  * those of lop_run_band, which runs a single band, and the results agree with it up to the order

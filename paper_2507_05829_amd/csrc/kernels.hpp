@@ -82,10 +82,10 @@ struct KernelEvents {
 hipError_t launch_op(const OpLaunch& L, hipStream_t stream, KernelEvents* ev = nullptr);
 // The same operator on several bands of one layer as one launch (the operation batching of
 // Sec. IV-D): n descriptors that differ in slabs and rows only; bands that compute nothing are
-// skipped. op_batchable: whether the operator's kernel has such a form (the 1x1 streaming kernel
-// and the register-blocked depthwise kernel take one band at a time).
+// skipped. op_streams: whether the operator's kernel is one of those that stream memory (the 1x1 streaming kernel
+// and the register-blocked depthwise kernel).
 constexpr int kMaxBandsPerLaunch = 16;
-bool op_batchable(const OpLaunch& L);
+bool op_streams(const OpLaunch& L);
 hipError_t launch_op_bands(const OpLaunch* Ls, int n, hipStream_t stream, KernelEvents* ev = nullptr);
 int describe_op_bands(const OpLaunch* Ls, int n, char* name, size_t size);
 size_t conv_workspace_bytes_bands(const OpLaunch* Ls, int n);

@@ -27,27 +27,27 @@ hipError_t launch_copy_rows(void* dst, const void* src, size_t pitch, size_t len
                             hipStream_t stream, int workgroups);
 hipError_t launch_fill_words(void* dst, size_t bytes, unsigned word, hipStream_t stream);
 
-hipError_t launch_pointwise(const OpLaunch& L, hipStream_t stream, KernelEvents* ev);
+hipError_t launch_pointwise(const OpLaunch* Ls, int n, hipStream_t stream, KernelEvents* ev);
 size_t mbconv_bands_bytes(int c, int s);
 void mbconv_pack_bands(const float* w, int c, int s, unsigned short* dst);
 bool mbconv_applies(const OpLaunch& e, const OpLaunch& d, const OpLaunch& p);
 int mbconv_describe(const OpLaunch& d, const OpLaunch& p, char* name, size_t size);
 hipError_t launch_mbconv_bands(const OpLaunch* es, const OpLaunch& d, const OpLaunch* ps, int n, hipStream_t stream,
                                KernelEvents* ev);
-int pointwise_describe(const OpLaunch& L, char* name, size_t size);
+int pointwise_describe(const OpLaunch* Ls, int n, char* name, size_t size);
 int conv_igemm_describe(const OpLaunch& L, char* name, size_t size);
 int rowwise_describe(const OpLaunch& L, char* name, size_t size);
 hipError_t launch_conv_igemm_bands(const OpLaunch* Ls, int n, hipStream_t stream, KernelEvents* ev);
 int conv_igemm_describe_bands(const OpLaunch* Ls, int n, char* name, size_t size);
 hipError_t launch_rowwise_bands(const OpLaunch* Ls, int n, hipStream_t stream, KernelEvents* ev);
-bool rowwise_batchable(const OpLaunch& L);
+bool dw3_takes(const OpLaunch& L);
 hipError_t launch_stem_bands(const OpLaunch* Ls, int n, hipStream_t stream, KernelEvents* ev);
 
 hipError_t launch_op(const OpLaunch& L, hipStream_t stream, KernelEvents* ev) {
   if (L.out_hi <= L.out_lo) return hipSuccess;
   if (L.op == LOP_CONV2D) {
     if (stem_applies(L)) return launch_stem(L, stream, ev);
-    return pointwise_applies(L) ? launch_pointwise(L, stream, ev) : launch_conv_igemm(L, stream, ev);
+    return pointwise_applies(L) ? launch_pointwise(&L, 1, stream, ev) : launch_conv_igemm(L, stream, ev);
   }
   return launch_rowwise_op(L, stream, ev);
 }
@@ -56,22 +56,23 @@ bool stores_second_output(const OpLaunch& L) {
   return L.op != LOP_CONV2D || stem_applies(L) || !pointwise_applies(L);
 }
 
-bool op_batchable(const OpLaunch& L) {
-  if (L.op == LOP_CONV2D) return stem_applies(L) || !pointwise_applies(L);
-  return rowwise_batchable(L);
+bool op_streams(const OpLaunch& L) {
+  return L.op == LOP_CONV2D ? !stem_applies(L) && pointwise_applies(L) : dw3_takes(L);
 }
 
 hipError_t launch_op_bands(const OpLaunch* Ls, int n, hipStream_t stream, KernelEvents* ev) {
   if (n < 1 || n > kMaxBandsPerLaunch) return hipErrorInvalidValue;
   if (n == 1) return launch_op(Ls[0], stream, ev);
-  if (!op_batchable(Ls[0])) return hipErrorInvalidValue;
-  if (Ls[0].op == LOP_CONV2D)
-    return stem_applies(Ls[0]) ? launch_stem_bands(Ls, n, stream, ev) : launch_conv_igemm_bands(Ls, n, stream, ev);
+  if (Ls[0].op == LOP_CONV2D) {
+    if (stem_applies(Ls[0])) return launch_stem_bands(Ls, n, stream, ev);
+    return pointwise_applies(Ls[0]) ? launch_pointwise(Ls, n, stream, ev) : launch_conv_igemm_bands(Ls, n, stream, ev);
+  }
   return launch_rowwise_bands(Ls, n, stream, ev);
 }
 
 int describe_op_bands(const OpLaunch* Ls, int n, char* name, size_t size) {
   if (n > 1 && Ls[0].op == LOP_CONV2D && stem_applies(Ls[0])) return stem_describe_bands(Ls, n, name, size);
+  if (n > 1 && Ls[0].op == LOP_CONV2D && pointwise_applies(Ls[0])) return pointwise_describe(Ls, n, name, size);
   if (n == 1 || Ls[0].op != LOP_CONV2D) {
     const int k = describe_op(Ls[0], name, size);
     if (n > 1 && name && size) {   // the form that takes several bands carries _bands in its name
@@ -88,7 +89,7 @@ int describe_op_bands(const OpLaunch* Ls, int n, char* name, size_t size) {
 int describe_op(const OpLaunch& L, char* name, size_t size) {
   if (L.op != LOP_CONV2D) return rowwise_describe(L, name, size);
   if (stem_applies(L)) return stem_describe(L, name, size);
-  return pointwise_applies(L) ? pointwise_describe(L, name, size) : conv_igemm_describe(L, name, size);
+  return pointwise_applies(L) ? pointwise_describe(&L, 1, name, size) : conv_igemm_describe(L, name, size);
 }
 }  // namespace lop
 
@@ -404,6 +405,7 @@ size_t merged_workspace(lop_plan_t* P) {
 // intermediate rows on the chip. A chain too large even for one image (or one band of one image)
 // runs band by band: its launches are long enough by themselves.
 constexpr size_t kMergeMaxBytes = LOP_STATIC_SCRATCH_BYTES;
+constexpr size_t kLaneSlabsMax = (size_t)192 << 20;
 // A chain of row-wise operators has no halo, and callers that stream matrix rows run its bands one
 // by one: a chain of few products (rows x columns in x columns out of its largest layer) runs the bands' own
 // launches, so that its sums are those of lop_run_band in the same order. That is the only reason: merged it
@@ -495,20 +497,25 @@ void size_scratch(lop_plan_t* P) {
   const bool few_rows = t.in.w == 1 && products < kMergeMinProducts;
   if ((P->flags & LOP_FLAG_PLAN_ONLY) || (few_rows && nb > 1)) return;
   const bool whole = t.disjoint();
-  // A pass over few rows whose launches take one band each is a crowd of small launches on one lane: eight bands
-  // and eight images of the inverted-residual chain layer by layer took 3.3 ms that way, band by band 2.2.
-  bool all = true;
+  // Launches that stream memory (1 x 1 and depthwise layers by themselves) gain from being merged what launches cost, and
+  // lose the lanes that would run them side by side: no more passes than a lane has bands. Inverted-residual chains
+  // layer by layer, eight bands, us a call band by band -> merged: one image of 400 x 400 (two passes) 312 -> 140, 391 -> 336
+  // alone; 640 x 640 (four) 406 -> 325, but 484 -> 713 alone; two of 512 x 512 (eight) 480 -> 457, 567 -> 1 024 alone; eight
+  // of 640 x 640 (32) 2.2 -> 3.3 ms.
+  bool streams = false;
   for (int l = 0; l < nl; ++l)
-    all = all && (P->fuse_chain.away[l] || P->fuse_chain.head[l] >= 0 || lop::op_batchable(lop::describe_layer(P, l)));
+    streams = streams || (!P->fuse_chain.away[l] && P->fuse_chain.head[l] < 0 && lop::op_streams(lop::describe_layer(P, l)));
+  const int most = streams ? std::max(1, nb / LOP_DEFAULT_LANES) : INT_MAX;
   for (int passes = 1, images = 0; images != 1; ++passes) {
     images = (n + passes - 1) / passes;
-    if (!whole && !all && images != n) return;
+    if (!whole && (n + images - 1) / images > most) return;
     if (whole ? merge(ChainSched::kWhole, images, nb, place_whole(images, INT_MAX), false)
               : merge(ChainSched::kGrouped, images, nb, place_groups(images, nb, chain_keeps, &P->chain_off), false))
       return;
   }
-  for (int groups = 2, per = nb; !whole && all && per != 1; ++groups) {
+  for (int groups = 2, per = nb; !whole && per != 1; ++groups) {
     per = (nb + groups - 1) / groups;
+    if (n * ((nb + per - 1) / per) > most) return;
     if (merge(ChainSched::kGrouped, 1, per, place_groups(1, per, chain_keeps, &P->chain_off), false)) return;
   }
   // a chain whose layers keep to their rows: passes over the rows of as many bands as fit, if two do (the launches of
@@ -524,7 +531,8 @@ void size_scratch(lop_plan_t* P) {
   }
 }
 
-// Whether every launch of the plan has a kernel form that takes several bands.
+// Whether LOP_FLAG_BATCH_BANDS is open to the plan: not to inverted-residual blocks and streaming launches, whose callers
+// are told so; lop_run_chain merges those where it pays.
 bool all_launches_batchable(const lop_plan_t* P) {
   const lop::Tables& t = P->t;
   if (t.n_bands > lop::kMaxBandsPerLaunch) return false;
@@ -534,7 +542,7 @@ bool all_launches_batchable(const lop_plan_t* P) {
       if (P->fuse_chain.head[l] != l - 1) return false;   // an inverted-residual block
       continue;
     }
-    if (!lop::op_batchable(lop::describe_layer(P, l))) return false;
+    if (lop::op_streams(lop::describe_layer(P, l))) return false;
   }
   return true;
 }
@@ -945,7 +953,14 @@ int setup_device(lop_plan_t* P) {
   int live = 0;
   for (int b = 0; b < nb; ++b) live += band_empty(P, b) ? 0 : 1;
   int want = (int)((P->flags >> 8) & 0xff);
-  if (want == 0) want = LOP_DEFAULT_LANES;
+  if (want == 0) {
+    want = LOP_DEFAULT_LANES;
+    // Slabs that fill most of the 256 MB Infinity Cache by themselves: two lanes, not four, whose launches would only
+    // push each other's rows out of it. Where a lane is needed for copies, four are better all the same. (Inverted-residual
+    // chain layer by layer, eight images of 640 x 640, 240 MB a lane: 2 148 -> 2 041 us a call; of 512 x 512, 150 MB:
+    // 1 420 with four, 1 495 with two.)
+    if (P->sched == ChainSched::kPerBand && !P->t.reuse && P->arena_bytes > kLaneSlabsMax && (P->flags & LOP_FLAG_NO_D2H)) want = 2;
+  }
   // (chains that run on one lane each rotate over all of them, however few bands they have)
   const bool by_chain = P->t.reuse || P->sched != ChainSched::kPerBand;
   const int n_lanes = by_chain ? std::max(1, want) : std::max(1, std::min(want, live));
@@ -1112,18 +1127,11 @@ void batched_group(const lop_plan_t* P, int l, int first, int last, const void* 
 }
 
 // Layer l of bands [first, last): one launch (plus its finish kernel, if the reduction is cut) per
-// kMaxBandsPerLaunch bands; one per band where the kernel takes no more.
+// kMaxBandsPerLaunch bands.
 hipError_t launch_layer_batched(const lop_plan_t* P, int l, int first, int last, const void* d_in, void* d_out, hipStream_t cs,
                                 lop::KernelEvents* ev, void* y2) {
   const Fusion& F = P->fuse_chain;
   if (F.away[l]) return hipSuccess;
-  if (F.head[l] < 0 && !lop::op_batchable(lop::describe_layer(P, l))) {
-    for (int b = first; b < last; ++b) {
-      const hipError_t e = launch_layer(P, F, b, l, d_in, d_out, cs, ev, y2);
-      if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
-  }
   std::vector<lop::OpLaunch> group, heads;
   for (; first < last; first += lop::kMaxBandsPerLaunch) {
     batched_group(P, l, first, std::min(last, first + lop::kMaxBandsPerLaunch), d_in, d_out, y2, &group, &heads);

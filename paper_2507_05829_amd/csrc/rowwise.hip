@@ -183,8 +183,10 @@ constexpr int dw_rows_per_thread(int stride) { return stride == 1 ? 8 : 4; }
 struct Dw3Params {
   RowParams r;
   int cols_per_block;  // output columns per workgroup
+  int col_blocks;      // workgroups per row chunk
   int chunks;          // row chunks (dw_rows_per_thread output rows each) per image
 };
+static_assert(sizeof(Batch<Dw3Params>) <= 4096, "the parameters of all bands of a launch travel as kernel arguments");
 
 // Raw 8- or 16-byte vector of the storage type and its expansion to fp32 values.
 template <int BYTES> struct RawVec;
@@ -214,7 +216,7 @@ __device__ __forceinline__ void unpack(const R& t, float* v) {
 }
 
 template <typename T, int VEC, int S>
-__global__ __launch_bounds__(256) void dwconv3x3_kernel(const Dw3Params q) {
+__device__ __forceinline__ void dwconv3x3_body(const Dw3Params& q, const int bx) {
   static_assert(VEC * sizeof(T) == 16 || VEC * sizeof(T) == 8, "8- or 16-byte vectors");
   typedef typename RawVec<VEC * sizeof(T)>::type Raw;
   constexpr int RPT = dw_rows_per_thread(S);  // output rows per thread
@@ -222,9 +224,10 @@ __global__ __launch_bounds__(256) void dwconv3x3_kernel(const Dw3Params q) {
   const RowParams& p = q.r;
   const int cv = p.C / VEC;
   const int cg = threadIdx.x % cv, col = threadIdx.x / cv;
-  const int ow = blockIdx.x * q.cols_per_block + col;
+  const int row = bx / q.col_blocks;
+  const int ow = (bx - row * q.col_blocks) * q.cols_per_block + col;
   if (col >= q.cols_per_block || ow >= p.W_out) return;
-  const int chunk = blockIdx.y % q.chunks, n = blockIdx.y / q.chunks;
+  const int n = row / q.chunks, chunk = row - n * q.chunks;
   const int c = cg * VEC;
   const int oh0 = p.out_lo + chunk * RPT;
   const int oh1 = min(oh0 + RPT, p.out_lo + p.R);
@@ -280,6 +283,17 @@ __global__ __launch_bounds__(256) void dwconv3x3_kernel(const Dw3Params q) {
   }
 }
 
+template <typename T, int VEC, int S>
+__global__ __launch_bounds__(256) void dwconv3x3_kernel(const Dw3Params q) {
+  dwconv3x3_body<T, VEC, S>(q, blockIdx.x);
+}
+// The same for several bands of one layer in one grid (band b owns blocks first[b] .. first[b + 1]).
+template <typename T, int VEC, int S>
+__global__ __launch_bounds__(256) void dwconv3x3_kernel_bands(const Batch<Dw3Params> t) {
+  const int b = batch_find(t, blockIdx.x);
+  dwconv3x3_body<T, VEC, S>(t.p[b], blockIdx.x - t.first[b]);
+}
+
 // The sliding-window kernel covers the common depthwise case; everything else runs on
 // rowwise_kernel.
 inline bool dw3_applies(const RowParams& p, int op, int vec) {
@@ -288,33 +302,26 @@ inline bool dw3_applies(const RowParams& p, int op, int vec) {
          p.res == nullptr;
 }
 
-// One launch, unless its (image, chunk of rows) pairs outnumber the grid's second dimension: then one
-// per group of images, or per group of rows of an image.
-constexpr int kMaxGridY = 65535;
 template <typename T, int VEC>
-hipError_t launch_dw3(const RowParams& p, hipStream_t s, KernelEvents* ev) {
-  if (p.R <= 0 || p.N <= 0) return hipSuccess;
-  const int cv = p.C / VEC, rpt = dw_rows_per_thread(p.sh);
-  const size_t x_img = (size_t)p.x_rows * p.W * p.C * sizeof(T), y_img = (size_t)p.y_rows * p.W_out * p.C * sizeof(T);
-  const int rows = std::min(p.R, kMaxGridY * rpt), images = std::max(1, kMaxGridY / ((rows + rpt - 1) / rpt));
-  for (int n = 0; n < p.N; n += images)
-    for (int r = 0; r < p.R; r += rows) {
-      Dw3Params q;
-      q.r = p;
-      q.r.x = (const char*)p.x + n * x_img;
-      q.r.y = (char*)p.y + n * y_img;
-      q.r.y2 = p.y2 ? (char*)p.y2 + n * y_img : nullptr;
-      q.r.N = std::min(images, p.N - n);
-      q.r.out_lo = p.out_lo + r;
-      q.r.R = std::min(rows, p.R - r);
-      q.cols_per_block = std::max(1, 256 / cv);
-      q.chunks = (q.r.R + rpt - 1) / rpt;
-      const dim3 grid((p.W_out + q.cols_per_block - 1) / q.cols_per_block, q.chunks * q.r.N);
-      const hipError_t e = p.sh == 1 ? launch_kernel(dwconv3x3_kernel<T, VEC, 1>, grid, dim3(256), s, ev, q)
-                                     : launch_kernel(dwconv3x3_kernel<T, VEC, 2>, grid, dim3(256), s, ev, q);
-      if (e != hipSuccess) return e;
-    }
-  return hipSuccess;
+hipError_t launch_dw3(const RowParams* ps, int n, hipStream_t s, KernelEvents* ev) {
+  Dw3Params qs[kMaxBatch];
+  unsigned gx[kMaxBatch];
+  int m = 0;
+  for (int b = 0; b < n; ++b) {
+    const RowParams& p = ps[b];
+    if (p.R <= 0 || p.N <= 0) continue;
+    Dw3Params& q = qs[m];
+    q.r = p;
+    q.cols_per_block = std::max(1, 256 / (p.C / VEC));
+    q.col_blocks = (p.W_out + q.cols_per_block - 1) / q.cols_per_block;
+    q.chunks = (p.R + dw_rows_per_thread(p.sh) - 1) / dw_rows_per_thread(p.sh);
+    const unsigned long blocks = (unsigned long)q.col_blocks * q.chunks * p.N;
+    if (blocks > 0x7fffffffUL) return hipErrorInvalidValue;
+    gx[m++] = (unsigned)blocks;
+  }
+  if (m == 0) return hipSuccess;
+  return ps[0].sh == 1 ? launch_group(dwconv3x3_kernel<T, VEC, 1>, dwconv3x3_kernel_bands<T, VEC, 1>, qs, m, gx, 1, 1, dim3(256), s, ev)
+                       : launch_group(dwconv3x3_kernel<T, VEC, 2>, dwconv3x3_kernel_bands<T, VEC, 2>, qs, m, gx, 1, 1, dim3(256), s, ev);
 }
 
 // Channel vector per thread of the sliding-window kernel (0: it does not apply).
@@ -358,12 +365,8 @@ RowParams make_row_params(const OpLaunch& L) {
 
 }  // namespace
 
-// Whether launch_rowwise_bands has a kernel for this operator (the register-blocked depthwise
-// kernel takes one band at a time).
-bool rowwise_batchable(const OpLaunch& L) {
-  const RowParams p = make_row_params(L);
-  return dw3_vec(p, L.op, L.dtype) == 0;
-}
+// The register-blocked depthwise kernel.
+bool dw3_takes(const OpLaunch& L) { return dw3_vec(make_row_params(L), L.op, L.dtype) != 0; }
 
 hipError_t launch_rowwise_bands(const OpLaunch* Ls, int n, hipStream_t stream, KernelEvents* ev) {
   if (n < 1 || n > kMaxBatch) return hipErrorInvalidValue;
@@ -371,11 +374,8 @@ hipError_t launch_rowwise_bands(const OpLaunch* Ls, int n, hipStream_t stream, K
   for (int b = 0; b < n; ++b) ps[b] = make_row_params(Ls[b]);
   const OpLaunch& L = Ls[0];
   RowParams& p = ps[0];
-  if (const int v = dw3_vec(p, L.op, L.dtype)) {
-    if (n != 1) return hipErrorInvalidValue;
-    if (L.dtype != LOP_BF16) return launch_dw3<float, 4>(p, stream, ev);
-    return v == 8 ? launch_dw3<__bf16, 8>(p, stream, ev) : launch_dw3<__bf16, 4>(p, stream, ev);
-  }
+  if (dw3_vec(p, L.op, L.dtype))
+    return L.dtype != LOP_BF16 ? launch_dw3<float, 4>(ps, n, stream, ev) : launch_dw3<__bf16, 4>(ps, n, stream, ev);
   if (L.dtype == LOP_BF16)
     return p.C % 8 == 0 ? launch_rowwise<__bf16, 8>(ps, n, L.op, stream, ev)
                         : launch_rowwise<__bf16, 1>(ps, n, L.op, stream, ev);

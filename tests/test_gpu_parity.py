@@ -1850,3 +1850,39 @@ def test_first_layer_on_the_matrix_cores(oracle, cfg):
     hit = ~np.isfinite(oracle.run_chain(chain, t))
     dev, _ = run_gpu(chain, t)
     np.testing.assert_array_equal(~np.isfinite(dev), hit)
+
+
+@pytest.mark.parametrize("cfg", [
+    # shape(n,h,w) of the input, bands, channels: 1x1, depthwise and 1x1 layers, each a launch of its own for all bands
+    ((1, 41, 37), 8, 32),       # ragged groups of pixels, several images' worth of bands in a launch
+    ((3, 22, 61), 3, 32),       # groups that span two images
+    ((5, 6, 3), 2, 64),         # fewer pixels of an image and band than a group
+    ((1, 200, 333), 16, 32),    # as many bands as a launch takes; enough groups for four a wavefront
+])
+def test_streaming_layers_merged_over_bands(oracle, cfg):
+    """1x1 streaming and 3x3 depthwise layers outside a fused block: one launch per layer for all bands,
+    against the oracle and against the bands one by one (bit for bit: no sum changes its order)."""
+    (n, h, w), bands, c = cfg
+    mid = 192 if c == 32 else 32
+    chain = workloads.Chain("stream", (n, c, h, w), "bf16", bands)
+    a = chain.add(workloads.CONV, c, mid, 1, 1, 0, act="relu6")
+    chain.add(workloads.DWCONV, mid, mid, 3, 1, 1, 1, "relu6")
+    b = chain.add(workloads.CONV, mid, c, 1, 1, 0, act="none", residual_from=workloads.CHAIN_INPUT)
+    chain.add(workloads.CONV, c, mid, 1, 1, 0, act="relu6", input_from=b)
+    chain.add(workloads.DWCONV, mid, mid, 3, 2, 1, 1, "relu6")
+    chain.add(workloads.CONV, mid, c, 1, 1, 0, act="none")
+    t = workloads.make_tensors(chain, zero_bias=False, seed=53)
+    want = oracle.run_chain(chain, t)
+    plan = lop.Plan(chain, t, bands, lop.LOP_FLAG_NO_FUSE)
+    d_in, d_out = to_device_nhwc(t.x, "bf16"), empty_out(plan.out_shape(), "bf16")
+    torch.cuda.synchronize()
+    for band in range(bands):
+        plan.run_band(band, d_in, d_out)
+    plan.synchronize()
+    one_by_one = to_nchw(d_out)
+    plan.destroy()
+    for extra in (0, lop.LOP_FLAG_GRAPH, lop.LOP_FLAG_POISON_SCRATCH):
+        dev, host = run_gpu(chain, t, flags=lop.LOP_FLAG_NO_FUSE | extra)
+        np.testing.assert_array_equal(dev, host)
+        assert rel_err(dev, want) <= TOL["bf16"]
+        np.testing.assert_array_equal(dev, one_by_one)
