@@ -59,6 +59,26 @@ __device__ __forceinline__ void mma<float>(const u32x4& wa, const u32x4& px, f32
   acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[3], b[3], acc, 0, 0, 0);
 }
 
+// The maximum over four neighbouring lanes, of each of four values, in all four lanes: the 2 x 2 pooling of pixels that lanes
+// hold window by window. Two instructions a value; fmaxf of a moved value is seven, most of them to quiet NaNs that a
+// matrix instruction does not make. (An instruction that reads another lane needs two others between it and the one that
+// wrote the value. The values must come from vector instructions: the compiler does not know that these read them, and a
+// result straight from a matrix instruction would need more of a wait.)
+__device__ __forceinline__ void max_of_quad(f32x4& v) {
+  float a = v[0], b = v[1], c = v[2], d = v[3];
+  asm volatile("s_nop 1\n"
+               "v_max_f32_dpp %0, %0, %0 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n"
+               "v_max_f32_dpp %1, %1, %1 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n"
+               "v_max_f32_dpp %2, %2, %2 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n"
+               "v_max_f32_dpp %3, %3, %3 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n"
+               "v_max_f32_dpp %0, %0, %0 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n"
+               "v_max_f32_dpp %1, %1, %1 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n"
+               "v_max_f32_dpp %2, %2, %2 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n"
+               "v_max_f32_dpp %3, %3, %3 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf"
+               : "+v"(a), "+v"(b), "+v"(c), "+v"(d));
+  v = f32x4{a, b, c, d};
+}
+
 // The matrix instructions of one operand pair (bf16: one, fp32: four), one at a time: a loop over
 // several accumulators issues each accumulator's next one only after the others' current ones, so none
 // waits for the result of the one before it.

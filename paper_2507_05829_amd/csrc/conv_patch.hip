@@ -74,110 +74,71 @@ __device__ __forceinline__ PatchAt patch_at(const PatchParams& p, int bx, int gx
   return a;
 }
 
-// The four partial tiles, added in wavefront order through LDS, and what follows the sums. again(f, sum): this
-// wavefront's pieces of fragment f once more, for sums that are not finite.
-template <typename T, int TP, int NT, bool POOL, typename Again>
-__device__ __forceinline__ void patch_finish(const PatchParams& p, unsigned char* smem, const f32x16 (&acc)[NT][TP], const PatchAt& t,
-                                             int lane, int wave, Again&& again) {
-  constexpr int UNITS = TP * 4;             // (32 pixels x 8 channels) pieces of a 32-channel tile
-  const int half = lane >> 5, n = t.n, co0 = t.tile_n * (32 * NT);
-  const bool second = t.second;
-  // wavefront w finishes pieces
-  // w TP .. (w + 1) TP of the UNITS pieces (piece u: fragment u / 4, channels (u % 4) * 8 ..)
-  u32x4* const part = (u32x4*)smem;
-  const Clamp cl = make_clamp(second ? p.sib.act : p.act);
-  const int C_out = second ? p.sib.C_out : p.C_out;
-  const float* const bias_at = second ? p.sib.bias : p.bias;
-  T* const y = (T*)(second ? p.sib.y : p.y);
-  T* const y2 = second ? nullptr : (T*)p.y2;
-  // where they go, and what is added to them: all loads issued here, ahead of the sums
-  int r, cc;
-  tile_pixel<POOL>(p, wave * TP / 4 * 32 + (lane & 31), r, cc);             // (a wavefront's pieces all lie in one fragment)
-  const int row = t.r0 + r, col = t.c0 + cc;
-  bool live = (r < p.th) & (row < p.R) & (col < p.Wc);
-  if (second) live = live & (p.out_lo + row >= p.sib.lo) & (p.out_lo + row < p.sib.hi);
-  const int cb = co0 + ((wave * TP) & 3) * 8;   // first channel of this wavefront's pieces
-  f32x4 bias[NT][TP];
-#pragma unroll
-  for (int a = 0; a < NT; ++a)
-#pragma unroll
-    for (int i = 0; i < TP; ++i) bias[a][i] = f32x4{0.f, 0.f, 0.f, 0.f};
-  if (bias_at) {
-#pragma unroll
-    for (int a = 0; a < NT; ++a)
-#pragma unroll
-      for (int i = 0; i < TP; ++i) {
-        const int co = cb + a * 32 + i * 8 + half * 4;
-        bias[a][i] = *(const f32x4*)(bias_at + (co < C_out ? co : 0));
-      }
-  }
+// What follows the sums of N pieces of one fragment (32 pixels; piece i: channels first + 8 i ..): pooling, bias,
+// residual, activation, the one rounding. load issues everything that has to come from memory.
+template <typename T, int N, bool POOL>
+struct PatchPieces {
   typedef unsigned raw_t __attribute__((ext_vector_type(sizeof(T))));   // four elements
-  raw_t res[NT][TP];
-  if constexpr (!POOL) {
-    if (p.res && !second) {
-      const size_t ra = live ? ((size_t)(n * p.r_rows + p.out_lo + row - p.r_row0) * p.W_out + col) * p.C_out : 0;
+  f32x4 bias[N];
+  raw_t res[N];
+  int row, col, first;
+  bool live;
+
+  __device__ __forceinline__ void load(const PatchParams& p, const PatchAt& t, int fragment, int first_channel, int lane) {
+    const int half = lane >> 5, C_out = t.second ? p.sib.C_out : p.C_out;
+    const float* const bias_at = t.second ? p.sib.bias : p.bias;
+    first = first_channel;
+    int r, c;
+    tile_pixel<POOL>(p, fragment * 32 + (lane & 31), r, c);
+    row = t.r0 + r;
+    col = t.c0 + c;
+    live = (r < p.th) & (row < p.R) & (col < p.Wc);
+    if (t.second) live = live & (p.out_lo + row >= p.sib.lo) & (p.out_lo + row < p.sib.hi);
 #pragma unroll
-      for (int a = 0; a < NT; ++a)
+    for (int i = 0; i < N; ++i) bias[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (bias_at) {
 #pragma unroll
-        for (int i = 0; i < TP; ++i) {
-          const int co = cb + a * 32 + i * 8 + half * 4;
-          res[a][i] = *(const raw_t*)((const T*)p.res + ra + (co < p.C_out ? co : 0));
+      for (int i = 0; i < N; ++i) {
+        const int co = first + i * 8 + half * 4;
+        bias[i] = *(const f32x4*)(bias_at + (co < C_out ? co : 0));
+      }
+    }
+    if constexpr (!POOL) {
+      if (p.res && !t.second) {
+        const size_t ra = live ? ((size_t)(t.n * p.r_rows + p.out_lo + row - p.r_row0) * p.W_out + col) * p.C_out : 0;
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+          const int co = first + i * 8 + half * 4;
+          res[i] = *(const raw_t*)((const T*)p.res + ra + (co < p.C_out ? co : 0));
         }
-    } else {
+      } else {
 #pragma unroll
-      for (int a = 0; a < NT; ++a)
-#pragma unroll
-        for (int i = 0; i < TP; ++i) res[a][i] = raw_t(0u);
+        for (int i = 0; i < N; ++i) res[i] = raw_t(0u);
+      }
     }
   }
-#pragma unroll
-  for (int a = 0; a < NT; ++a) {
-    __syncthreads();
-#pragma unroll
-    for (int u = 0; u < UNITS; ++u) {
-      const f32x16& s = acc[a][u / 4];
-      const int g = (u % 4) * 4;
-      part[(wave * UNITS + u) * 64 + lane] = __builtin_bit_cast(u32x4, f32x4{s[g], s[g + 1], s[g + 2], s[g + 3]});
-    }
-    __syncthreads();
-    f32x4 sum[TP];
-#pragma unroll
-    for (int i = 0; i < TP; ++i) {
-      sum[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int s = 0; s < 4; ++s) sum[i] += __builtin_bit_cast(f32x4, part[(s * UNITS + wave * TP + i) * 64 + lane]);
-    }
-    if constexpr (sizeof(T) == 4) {
-      float odd = 0.f;   // NaN if a sum is not finite
-#pragma unroll
-      for (int i = 0; i < TP; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) odd += sum[i][j] - sum[i][j];
-      if (__builtin_amdgcn_ballot_w64(!(odd == 0.f))) again(wave * TP / 4, sum);
-    }
-    // ---- pooling, bias, residual, activation, the one rounding
+
+  __device__ __forceinline__ void store(const PatchParams& p, const PatchAt& t, f32x4 (&sum)[N], int lane) {
+    const int half = lane >> 5, C_out = t.second ? p.sib.C_out : p.C_out;
+    const Clamp cl = make_clamp(t.second ? p.sib.act : p.act);
+    T* const y = (T*)(t.second ? p.sib.y : p.y);
+    T* const y2 = t.second ? nullptr : (T*)p.y2;
     size_t ya;
+    bool stores = live;
     if constexpr (POOL) {
 #pragma unroll
-      for (int i = 0; i < TP; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          float v = sum[i][j];
-          v = fmaxf(v, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0xB1, 0xf, 0xf, true)));  // lane ^ 1
-          v = fmaxf(v, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x4E, 0xf, 0xf, true)));  // lane ^ 2
-          sum[i][j] = v;
-        }
-      live = live & ((lane & 3) == 0);
-      ya = ((size_t)(n * p.y_rows + ((p.out_lo + row) >> 1) - p.y_row0) * p.W_out + (col >> 1)) * p.C_out;
+      for (int i = 0; i < N; ++i) max_of_quad(sum[i]);
+      stores = live & ((lane & 3) == 0);
+      ya = ((size_t)(t.n * p.y_rows + ((p.out_lo + row) >> 1) - p.y_row0) * p.W_out + (col >> 1)) * p.C_out;
     } else {
-      ya = ((size_t)(n * (second ? p.sib.y_rows : p.y_rows) + p.out_lo + row - (second ? p.sib.y_row0 : p.y_row0)) * p.W_out + col) * C_out;
+      ya = ((size_t)(t.n * (t.second ? p.sib.y_rows : p.y_rows) + p.out_lo + row - (t.second ? p.sib.y_row0 : p.y_row0)) * p.W_out + col) * C_out;
     }
 #pragma unroll
-    for (int i = 0; i < TP; ++i) {
-      sum[i] += bias[a][i];
+    for (int i = 0; i < N; ++i) {
+      sum[i] += bias[i];
       if constexpr (!POOL) {
         alignas(16) T rr[4];
-        *(raw_t*)rr = res[a][i];
+        *(raw_t*)rr = res[i];
 #pragma unroll
         for (int j = 0; j < 4; ++j) sum[i][j] += to_f32(rr[j]);
       }
@@ -186,9 +147,9 @@ __device__ __forceinline__ void patch_finish(const PatchParams& p, unsigned char
     }
     if constexpr (sizeof(T) == 4) {
 #pragma unroll
-      for (int i = 0; i < TP; ++i) {
-        const int co = cb + a * 32 + i * 8 + half * 4;
-        if (live && co < C_out) {
+      for (int i = 0; i < N; ++i) {
+        const int co = first + i * 8 + half * 4;
+        if (stores && co < C_out) {
           *(f32x4*)(y + ya + co) = sum[i];
           if (y2) *(f32x4*)(y2 + ya + co) = sum[i];
         }
@@ -200,10 +161,10 @@ __device__ __forceinline__ void patch_finish(const PatchParams& p, unsigned char
         for (int j = 0; j < 4; ++j) o[j] = (__bf16)sum[i][j];
         return *(const uint2*)o;
       };
-      if constexpr (TP == 1) {
+      if constexpr (N == 1) {
         const uint2 o = pack(0);
-        const int co = cb + a * 32 + half * 4;
-        if (live && co < C_out) {
+        const int co = first + half * 4;
+        if (stores && co < C_out) {
           *(uint2*)(y + ya + co) = o;
           if (y2) *(uint2*)(y2 + ya + co) = o;
         }
@@ -211,13 +172,13 @@ __device__ __forceinline__ void patch_finish(const PatchParams& p, unsigned char
         // two pieces hold 16 channels of a pixel in two lanes, 4 + 4 interleaved: exchanged between
         // the lane halves so that each ends with 8 consecutive ones (one 16-byte store)
 #pragma unroll
-        for (int i = 0; i < TP; i += 2) {
+        for (int i = 0; i < N; i += 2) {
           const uint2 e = pack(i), o = pack(i + 1);
           const auto s0 = __builtin_amdgcn_permlane32_swap(e.x, o.x, false, false);
           const auto s1 = __builtin_amdgcn_permlane32_swap(e.y, o.y, false, false);
           const u32x4 v = u32x4{(unsigned)s0[0], (unsigned)s1[0], (unsigned)s0[1], (unsigned)s1[1]};
-          const int co = cb + a * 32 + i * 8 + half * 8;
-          if (live && co < C_out) {
+          const int co = first + i * 8 + half * 8;
+          if (stores && co < C_out) {
             *(u32x4*)(y + ya + co) = v;
             if (y2) *(u32x4*)(y2 + ya + co) = v;
           }
@@ -225,12 +186,67 @@ __device__ __forceinline__ void patch_finish(const PatchParams& p, unsigned char
       }
     }
   }
+};
+
+// The four partial tiles, added in wavefront order through LDS, and what follows the sums. again(f, sum): this
+// wavefront's pieces of fragment f once more, for sums that are not finite.
+template <typename T, int TP, bool POOL, typename Again>
+__device__ __forceinline__ void patch_finish(const PatchParams& p, unsigned char* smem, const f32x16 (&acc)[TP], const PatchAt& t,
+                                             int lane, int wave, Again&& again) {
+  // wavefront w finishes pieces w TP .. (w + 1) TP of the UNITS (32 pixels x 8 channels) pieces of a tile (piece u:
+  // fragment u / 4, channels (u % 4) * 8 ..), which all lie in one fragment
+  constexpr int UNITS = TP * 4;
+  u32x4* const part = (u32x4*)smem;
+  PatchPieces<T, TP, POOL> out;
+  out.load(p, t, wave * TP / 4, t.tile_n * 32 + ((wave * TP) & 3) * 8, lane);
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < UNITS; ++u) {
+    const f32x16& s = acc[u / 4];
+    const int g = (u % 4) * 4;
+    part[(wave * UNITS + u) * 64 + lane] = __builtin_bit_cast(u32x4, f32x4{s[g], s[g + 1], s[g + 2], s[g + 3]});
+  }
+  __syncthreads();
+  f32x4 sum[TP];
+#pragma unroll
+  for (int i = 0; i < TP; ++i) {
+    sum[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < 4; ++s) sum[i] += __builtin_bit_cast(f32x4, part[(s * UNITS + wave * TP + i) * 64 + lane]);
+  }
+  if constexpr (sizeof(T) == 4) {
+    float odd = 0.f;   // NaN if a sum is not finite
+#pragma unroll
+    for (int i = 0; i < TP; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) odd += sum[i][j] - sum[i][j];
+    if (__builtin_amdgcn_ballot_w64(!(odd == 0.f))) again(wave * TP / 4, sum);
+  }
+  out.store(p, t, sum, lane);
 }
 
-// TP x 32 pixels x NT x 32 channels per workgroup; NI: load instructions per wavefront and patch.
-template <typename T, int TP, int NT, int NI, bool POOL, int S>
+// The slots of a patch that this lane fetches (16 bytes each; the ninth of every nine slots, and what lies outside the
+// patch, the slab or the image, is a load past the buffer's end).
+template <int NI, int S>
+__device__ __forceinline__ void patch_slots(const PatchParams& p, const PatchAt& t, int wave, int lane, unsigned (&src)[NI], int row_bytes) {
+  const int ih0 = (p.out_lo + t.r0) * S - p.ph, iw0 = t.c0 * S - p.pw;
+  const int half_cols = p.pitch >> 1;
+#pragma unroll
+  for (int i = 0; i < NI; ++i) {
+    const int slot = (i * 4 + wave) * 64 + lane;
+    const int pix = slot / kPixelSlots, k = slot - pix * kPixelSlots;
+    const int pr = fastdiv(pix, p.by_pitch), pc = pix - pr * p.pitch;
+    const int col = S == 1 ? pc : (pc < half_cols ? 2 * pc : 2 * (pc - half_cols) + 1);
+    const int ih = ih0 + pr, iw = iw0 + col;
+    const bool ok = (k < 8) & (pr < p.ph_rows) & (ih >= p.x_row0) & (ih < p.x_row0 + p.x_rows) & (iw >= 0) & (iw < p.W);
+    src[i] = ok ? (unsigned)(((t.n * p.x_rows + ih - p.x_row0) * p.W + iw) * row_bytes + k * 16) : kOutside;
+  }
+}
+
+// TP x 32 pixels x 32 channels per workgroup; NI: load instructions per wavefront and patch.
+template <typename T, int TP, int NI, bool POOL, int S>
 __device__ __forceinline__ void patch_body(const PatchParams& p, const int bx, const int gx) {
-  constexpr int KE = 16 / (int)sizeof(T);
+  constexpr int KE = 16 / (int)sizeof(T), NT = 1;
   constexpr int BUF = NI * 4096;            // bytes of a patch in LDS
   constexpr int SMEM = 2 * BUF > TP * 16384 ? 2 * BUF : TP * 16384;
   __shared__ __attribute__((aligned(1024))) unsigned char smem[SMEM];
@@ -240,28 +256,14 @@ __device__ __forceinline__ void patch_body(const PatchParams& p, const int bx, c
   const int px = lane & 31, half = lane >> 5;
   const PatchAt tile = patch_at(p, bx, gx, S == 2);
   const bool second = tile.second;
-  const int tile_n = tile.tile_n, n = tile.n, r0 = tile.r0, c0 = tile.c0;
+  const int tile_n = tile.tile_n;
   const int row_bytes = p.C_in * (int)sizeof(T);
   const int chunks = row_bytes / 128;
 
   const __amdgpu_buffer_rsrc_t xbuf = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<void*>(p.x), 0, (int)((size_t)p.N * p.x_rows * p.W * row_bytes), 0x00020000);
-  // ---- the slots this lane fetches of every patch
   unsigned src[NI];
-  {
-    const int ih0 = (p.out_lo + r0) * S - p.ph, iw0 = c0 * S - p.pw;
-    const int half_cols = p.pitch >> 1;
-#pragma unroll
-    for (int i = 0; i < NI; ++i) {
-      const int slot = (i * 4 + wave) * 64 + lane;
-      const int pix = slot / kPixelSlots, k = slot - pix * kPixelSlots;
-      const int pr = fastdiv(pix, p.by_pitch), pc = pix - pr * p.pitch;
-      const int col = S == 1 ? pc : (pc < half_cols ? 2 * pc : 2 * (pc - half_cols) + 1);
-      const int ih = ih0 + pr, iw = iw0 + col;
-      const bool ok = (k < 8) & (pr < p.ph_rows) & (ih >= p.x_row0) & (ih < p.x_row0 + p.x_rows) & (iw >= 0) & (iw < p.W);
-      src[i] = ok ? (unsigned)(((n * p.x_rows + ih - p.x_row0) * p.W + iw) * row_bytes + k * 16) : kOutside;
-    }
-  }
+  patch_slots<NI, S>(p, tile, wave, lane, src, row_bytes);
   auto fetch_patch = [&](int c) __attribute__((always_inline)) {
     unsigned char* const dst = smem + (c & 1) * BUF;
 #pragma unroll
@@ -396,7 +398,148 @@ __device__ __forceinline__ void patch_body(const PatchParams& p, const int bx, c
     run_patch(c, false);
   }
 
-  patch_finish<T, TP, NT, POOL>(p, smem, acc, tile, lane, wave, [](int, f32x4 (&)[TP]) {});
+  patch_finish<T, TP, POOL>(p, smem, acc[0], tile, lane, wave, [](int, f32x4 (&)[TP]) {});
+}
+
+// The 128 x 64 tile (bf16): two wavefronts to a half of the channels, each with half of every pixel's 128 bytes.
+// Against four wavefronts that take a quarter of the pixels' bytes for the whole tile, the same filter vectors and twice the
+// reads from LDS (128 of the 240 bytes it serves per cycle, when the matrix cores are busy all the time), but a quarter of
+// the partial sums (32 KB instead of 128 through LDS, one exchange instead of two) and half the accumulators, which
+// took the register file to its end and four vectors of every tile to memory. Four
+// quarters took 28.7 us for 256 -> 256 channels on 14 300 pixels (0.59 PFLOP/s), this 21.4; pooled, 512 -> 512 on 3 136,
+// 25 and 20.3.
+template <int NI, bool POOL>
+__device__ __forceinline__ void patch_wide_body(const PatchParams& p, const int bx, const int gx) {
+  typedef __bf16 T;
+  constexpr int TP = 4, BUF = NI * 4096, STEPS = 18;   // half steps of a patch: 9 taps x 2
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[2 * BUF];
+  static_assert(2 * BUF >= 4 * 8192, "the exchange of partial sums");
+
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int px = lane & 31, half = lane >> 5, part = wave & 1;
+  const PatchAt tile = patch_at(p, bx, gx, false);
+  const int row_bytes = p.C_in * 2, chunks = row_bytes / 128;
+  const __amdgpu_buffer_rsrc_t xbuf = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<void*>(p.x), 0, (int)((size_t)p.N * p.x_rows * p.W * row_bytes), 0x00020000);
+  unsigned src[NI];
+  patch_slots<NI, 1>(p, tile, wave, lane, src, row_bytes);
+  auto fetch_patch = [&](int c) __attribute__((always_inline)) {
+    unsigned char* const dst = smem + (c & 1) * BUF;
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(xbuf, (__attribute__((address_space(3))) void*)(dst + (i * 4 + wave) * 1024),
+                                               16, (int)src[i], c * 128, 0, 0);
+    // (the filter loads behind these stay behind them: the waits below count on that order)
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  fetch_patch(0);
+  // ---- the filter: [32 channels][step][lane] 16 bytes; this wavefront's two steps of a tap and patch
+  const int co0 = tile.tile_n * 64 + (wave >> 1) * 32;
+  const u32x4* const wsrc = (const u32x4*)p.wd + ((size_t)(co0 / 32) * p.k_steps + 2 * part) * 64 + lane;
+  const int tap_steps = p.C_in / 16 * 64;
+  u32x4 wreg[STEPS];
+  auto fetch_tap = [&](int c, int t) __attribute__((always_inline)) {
+#pragma unroll
+    for (int k = 0; k < 2; ++k) wreg[2 * t + k] = wsrc[(size_t)(t * tap_steps + c * 256 + k * 64)];
+  };
+#pragma unroll
+  for (int t = 0; t < 9; ++t) fetch_tap(0, t);
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+
+  // ---- this lane's pixel of every 32-pixel fragment: where the first tap of it lies in a patch
+  int at[TP];
+  const unsigned lds0 = (unsigned)(unsigned long)(__attribute__((address_space(3))) unsigned char*)smem;
+#pragma unroll
+  for (int f = 0; f < TP; ++f) {
+    int r, c;
+    tile_pixel<POOL>(p, f * 32 + px, r, c);
+    r = min(r, p.th - 1);                   // (lanes past the tile compute its last row again; they store nothing)
+    at[f] = (int)lds0 + (r * p.pitch + c) * kPixelBytes + part * 64 + half * 16;
+  }
+  const int tap_row = p.pitch * kPixelBytes;
+  f32x16 acc[TP];
+#pragma unroll
+  for (int f = 0; f < TP; ++f)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[f][i] = 0.f;
+
+  // Pixel fragments are read with instructions of our own (reads the compiler can see would make it wait for every
+  // load in flight to LDS), two half steps ahead of their products.
+  u32x4 frag[3][TP];
+  auto read = [&](int buf, auto index, u32x4 (&d)[TP]) __attribute__((always_inline)) {
+    constexpr int i = decltype(index)::value, t = i / 2, off = t % 3 * kPixelBytes + i % 2 * 32;
+    const int row = buf + t / 3 * tap_row;
+#pragma unroll
+    for (int f = 0; f < TP; ++f) {
+      const int addr = at[f] + row;
+      asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(d[f]) : "v"(addr), "n"(off) : "memory");
+    }
+  };
+  auto wait_reads = [&](auto younger, u32x4 (&d)[TP]) __attribute__((always_inline)) {
+    constexpr int n = decltype(younger)::value;
+    asm volatile("s_waitcnt lgkmcnt(%4)" : "+v"(d[0]), "+v"(d[1]), "+v"(d[2]), "+v"(d[3]) : "n"(n) : "memory");
+  };
+  // One patch; more: another follows, a tap's filter registers are refilled for it as soon as they are free.
+  auto run_patch = [&](int c, bool more) __attribute__((always_inline)) {
+    const int buf = (c & 1) * BUF;
+    read(buf, std::integral_constant<int, 0>{}, frag[0]);
+    read(buf, std::integral_constant<int, 1>{}, frag[1]);
+    unroll<STEPS>([&](auto index) __attribute__((always_inline)) {
+      constexpr int i = decltype(index)::value;
+      if constexpr (i + 2 < STEPS) read(buf, std::integral_constant<int, (i + 2) % STEPS>{}, frag[(i + 2) % 3]);
+      wait_reads(std::integral_constant<int, i + 2 < STEPS ? 2 * TP : i + 1 < STEPS ? TP : 0>{}, frag[i % 3]);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int f = 0; f < TP; ++f) mma<T>(wreg[i], frag[i % 3][f], acc[f]);
+      __builtin_amdgcn_sched_barrier(0);
+      if (i % 2 == 1 && more) fetch_tap(c + 1, i / 2);
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  };
+  auto patch_barrier = [&]() __attribute__((always_inline)) {
+    // this wavefront's part of the patch has arrived: only the nine taps' filter loads are younger
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(STEPS));
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  int c = 0;
+  for (; c + 1 < chunks; ++c) {
+    patch_barrier();
+    fetch_patch(c + 1);      // (into the buffer every wavefront was done with at the barrier)
+    run_patch(c, true);
+  }
+  patch_barrier();
+  run_patch(c, false);
+
+  // ---- a wavefront finishes fragments 2 part and 2 part + 1: it hands the others' sums to its neighbour
+  PatchPieces<T, 4, POOL> out[2];
+#pragma unroll
+  for (int k = 0; k < 2; ++k) out[k].load(p, tile, 2 * part + k, co0, lane);
+  f32x4* const mine = (f32x4*)smem + wave * 512 + lane, * const theirs = (f32x4*)smem + (wave ^ 1) * 512 + lane;
+  __syncthreads();
+  auto pick = [&](int k, int g, bool second) __attribute__((always_inline)) {   // (selected by value: acc stays in registers)
+    f32x4 v;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v[j] = second ? acc[2 + k][g * 4 + j] : acc[k][g * 4 + j];
+    return v;
+  };
+#pragma unroll
+  for (int k = 0; k < 2; ++k)
+#pragma unroll
+    for (int g = 0; g < 4; ++g) mine[(k * 4 + g) * 64] = pick(k, g, part == 0);
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    f32x4 sum[4];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) sum[g] = pick(k, g, part == 1) + theirs[(k * 4 + g) * 64];
+    out[k].store(p, tile, sum, lane);
+  }
 }
 
 // The fp32 form: products on the bf16 matrix cores (conv_gemm.hip says how, and how precise). A pixel of the patch is
@@ -594,7 +737,7 @@ __device__ __forceinline__ void patch_split_body(const PatchParams& p, const int
       }
     }
   };
-  patch_finish<float, TP, 1, POOL>(p, smem, acc, tile, lane, wave, again);
+  patch_finish<float, TP, POOL>(p, smem, acc[0], tile, lane, wave, again);
 }
 
 // Load instructions per wavefront and patch: the patch of a tile has at most NI * 256 / 9 pixels.
@@ -606,8 +749,12 @@ __device__ __forceinline__ void patch_tile(const PatchParams& p, const int bx, c
   if constexpr (sizeof(T) == 4) {
     static_assert(BN == 32, "the fp32 form has one channel tile");
     patch_split_body<BM / 32, patch_loads(BM / 32, S), POOL, S>(p, bx, gx);
+  } else if constexpr (BM == 128) {
+    static_assert(BN == 64 && S == 1, "the wide form");
+    patch_wide_body<patch_loads(4, 1), POOL>(p, bx, gx);
   } else {
-    patch_body<T, BM / 32, BN / 32, patch_loads(BM / 32, S), POOL, S>(p, bx, gx);
+    static_assert(BN == 32, "one channel tile");
+    patch_body<T, BM / 32, patch_loads(BM / 32, S), POOL, S>(p, bx, gx);
   }
 }
 
@@ -636,14 +783,14 @@ bool patch_shape(const OpLaunch& L) {
 // What a tile costs was fitted to measured launches of the three backbones, one image and all bands
 // together (cycles; chunk: 128 bytes of channels): a compute unit that has several tiles to do gets
 // through them at `chunk` each plus `rest` per tile (the L2s deliver 16-19 TB/s to the whole chip, which
-// a larger tile asks less of per product: 256 -> 256 channels on 14 300 pixels take 22.7 us with
-// 128 x 64 tiles, 26.1 with 64 x 32 and 38.0 on the kernel that fetches every tap), and no
+// a larger tile asks less of per product: 128 -> 128 channels on 12 500 pixels take 8.7 us with
+// 128 x 64 tiles and 9.5 with 64 x 32, 256 -> 256 on 6 400 12.9 and 14.5, on 3 100 11.6 and 8.6), and no
 // launch is faster than one tile from beginning to end (`first` + `alone` per chunk: 512 -> 512
 // channels on 196 pixels 5.6 us with 32 x 32 tiles, 6.5 with 64 x 32, 15.6 with 128 x 64, 16.1 before).
 struct PatchChoice { int bm = 0, bn = 0; };
 struct PatchCost { int bm, bn; double chunk, rest, alone, first; };
 constexpr PatchCost kBf16Costs[] = {
-    {128, 64, 5800, 4900, 3300, 7000}, {64, 32, 1860, 840, 1100, 3500}, {32, 32, 1200, 620, 750, 3000}};
+    {128, 64, 5000, 3500, 3300, 6000}, {64, 32, 1860, 840, 1100, 3500}, {32, 32, 1200, 620, 750, 3000}};
 // fp32, fitted alike (chunk: 32 channels); 64 x 32 against 32 x 32 tiles: 64 -> 64 channels on 12 500 pixels 11.7 and 13.4 us,
 // on 3 100 7.4 and 6.1; 256 -> 256 on 1 600 18.9 and 20.5, on 784 17.0 and 14.1. On the fp32 instructions the
 // best of them were 14.0, 5.4, 23.9 and 14.1: what the bf16 ones save, one tile to a compute unit spends on instructions
