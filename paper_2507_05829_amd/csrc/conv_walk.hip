@@ -44,6 +44,7 @@ struct WalkTile {
   static constexpr int NI = S == 1 ? 4 : 6;                      // load instructions per wavefront and patch
   static constexpr int ROOM = NI * 256 / SLOTS;                  // pixels of a patch
   static constexpr int BUF = NI * 4096;
+  static constexpr int AHEAD = KS == 2 && S == 1 ? 2 : 1;         // taps read from LDS ahead of the one multiplied (as registers allow)
 };
 
 template <int OFF>
@@ -75,7 +76,7 @@ __device__ __forceinline__ void wait_reads(u32x4 (&d)[4]) {
 template <int PIXB, int S, int WCO, bool POOL>
 __device__ __forceinline__ void walk_body(const PatchParams& p, const int bx, const int gx) {
   typedef WalkTile<PIXB, S, WCO> G;
-  constexpr int SLOTS = G::SLOTS, PB = G::PB, KS = G::KS, NI = G::NI, BUF = G::BUF;
+  constexpr int SLOTS = G::SLOTS, PB = G::PB, KS = G::KS, NI = G::NI, BUF = G::BUF, AHEAD = G::AHEAD;
   __shared__ __attribute__((aligned(1024))) unsigned char smem[2 * BUF];
 
   const int lane = threadIdx.x & 63;
@@ -191,9 +192,6 @@ __device__ __forceinline__ void walk_body(const PatchParams& p, const int bx, co
         const size_t ra = out_live ? ((size_t)(a.n * p.r_rows + p.out_lo + row - p.r_row0) * p.W_out + col) * p.C_out + co0 : 0;
 #pragma unroll
         for (int g = 0; g < 4; ++g) res[g] = *(const uint2*)((const __bf16*)p.res + ra + g * 8 + half * 4);
-      } else {
-#pragma unroll
-        for (int g = 0; g < 4; ++g) res[g] = make_uint2(0u, 0u);
       }
       asm volatile("" ::: "memory");
     } else {
@@ -206,40 +204,49 @@ __device__ __forceinline__ void walk_body(const PatchParams& p, const int bx, co
     }
     __builtin_amdgcn_sched_barrier(0);
 
-    f32x16 acc;
+    f32x16 acc;   // (starts from the bias; with pooling that is added behind the products, see max_of_quad)
 #pragma unroll
-    for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+    for (int i = 0; i < 16; ++i) acc[i] = POOL ? 0.f : bias[i / 4][i % 4];
     const int here = at + buf * BUF;
-    u32x4 x[2][KS];
-    read_tap<S, PB, KS, 0>(here, tap_row, tap_odd, x[0]);
+    u32x4 x[AHEAD + 1][KS];   // a tap's pixels are read AHEAD taps before they are multiplied
+    unroll<AHEAD>([&](auto tap) __attribute__((always_inline)) {
+      constexpr int T = decltype(tap)::value;
+      read_tap<S, PB, KS, T>(here, tap_row, tap_odd, x[T]);
+    });
     unroll<9>([&](auto tap) __attribute__((always_inline)) {
       constexpr int T = decltype(tap)::value;
-      if constexpr (T < 8) read_tap<S, PB, KS, T + 1>(here, tap_row, tap_odd, x[(T + 1) & 1]);
-      wait_reads<T < 8 ? KS : 0>(x[T & 1]);
+      if constexpr (T + AHEAD < 9) read_tap<S, PB, KS, T + AHEAD>(here, tap_row, tap_odd, x[(T + AHEAD) % (AHEAD + 1)]);
+      wait_reads<(T + AHEAD < 9 ? AHEAD : 8 - T) * KS>(x[T % (AHEAD + 1)]);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int k = 0; k < KS; ++k) mma<__bf16>(w[T][k], x[T & 1][k], acc);
+      for (int k = 0; k < KS; ++k) mma<__bf16>(w[T][k], x[T % (AHEAD + 1)][k], acc);
       __builtin_amdgcn_sched_barrier(0);
     });
 
-    // ---- pooling, bias, residual, activation, the one rounding; channels 8 g + 4 half + {0..3} become
+    // ---- residual, pooling, activation, the one rounding; channels 8 g + 4 half + {0..3} become
     // 8 consecutive ones per lane by an exchange between the lane halves
+    if constexpr (!POOL) {
+      if (p.res) {
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          alignas(8) __bf16 rr[4];
+          *(uint2*)rr = res[g];
+#pragma unroll
+          for (int j = 0; j < 4; ++j) acc[g * 4 + j] += (float)rr[j];
+        }
+      }
+    }
     uint2 o[4];
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
-      alignas(8) __bf16 b[4], rr[4];
-      if constexpr (!POOL) *(uint2*)rr = res[g];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        float v = acc[g * 4 + j];
-        if constexpr (POOL) {
-          v = fmaxf(v, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0xB1, 0xf, 0xf, true)));  // lane ^ 1
-          v = fmaxf(v, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x4E, 0xf, 0xf, true)));  // lane ^ 2
-        }
-        v += bias[g][j];
-        if constexpr (!POOL) v += (float)rr[j];
-        b[j] = (__bf16)clamp_act(v, cl);
+      f32x4 v = f32x4{acc[g * 4], acc[g * 4 + 1], acc[g * 4 + 2], acc[g * 4 + 3]};
+      if constexpr (POOL) {
+        v += bias[g];
+        max_of_quad(v);
       }
+      alignas(8) __bf16 b[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) b[j] = (__bf16)clamp_act(v[j], cl);
       o[g] = *(const uint2*)b;
     }
 #pragma unroll
@@ -289,9 +296,10 @@ long walk_pixels(const OpLaunch* convs, const OpLaunch* pools, int n) {
 //   64 -> 64 on 203 000 pixels 33 -> 25, pooled on 251 000 35.6 -> 26.8, on 57 600 10.3 -> 9.5, on 28 800 6.5 -> 7.0;
 //   stride 2: 32 -> 64 on 106 000 pixels 40 -> 18.5, on 57 600 12.2 -> 7.7, on 14 400 5.3 -> 4.9, on 8 160 4.4 -> 5.1;
 //   64 -> 128 on 49 600 22.7 -> 16.4, on 7 200 6.1 -> 5.3.
-// What bounds the large ones now: of 2 000 cycles a compute unit takes per tile (64 pixels x 64 channels, 64 channels in)
-// the matrix instructions are 1 150, reading LDS 1 250, passing loads and stores to the vector
-// cache 1 000, and two workgroups overlap them only in part.
+// What bounds the large ones now: instructions. A wavefront has 340 of them a tile (120 vector, 130 scalar, 18 or 36 of
+// each of matrix products and reads from LDS) and issues one in four cycles at best; leaving out any one kind of memory access
+// or the products changes 5 to 20 %. The bias as the sum's start, the residual's additions only where there is one
+// and pooling in two instructions a value: 23.3 -> 22.0 us for 32 -> 32 on 857 000 pixels, 25.7 -> 24.9 pooled on 256 000.
 constexpr long kMinOutputsStride2 = 900000, kMinOutputs32 = 1500000, kMinOutputs64 = 2750000;
 
 WalkForm choose_walk(const OpLaunch* convs, const OpLaunch* pools, int n) {
