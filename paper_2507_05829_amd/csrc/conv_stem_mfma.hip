@@ -12,10 +12,11 @@
 // rows under it are staged in LDS once, 4 bytes per load, zero outside the image, starting at the
 // first window's first element: a window then starts on a 4-byte boundary (in bf16 with stride 1 every
 // second one does: an extra copy, shifted by one element, serves the others). The weights stay in
-// registers. Bound by the output it writes: one image of the 720p chain's first layer 23 -> 9 us,
-// all its 16 bands 43.5 -> 23 us, vgg16's in 8 bands 32 -> 17.5, 7 x 7 stride 2 in bf16 20.8 -> 6.9, in fp32 (where the matrix
-// instructions bound it) 12.0 -> 7.3; the vector-ALU forms spent theirs on one multiply-add per
-// lane and element with weights from scalar loads.
+// registers, and a wavefront takes one 32-pixel fragment at a time from the reads to the stores: sums for one
+// fragment leave room for 3 to 7 wavefronts per SIMD (all four fragments of the 8-row form: 2 to 4), whose stores and
+// products overlap. Bound by the output it writes. us for the 8-row form, before (whole tile's sums; stores of 32
+// bytes per pixel) and now: 3 x 3 stride 2 in bf16, 32 channels, 1080 x 640 outputs 19.0 -> 15.0, 64 channels, stride 1,
+// 1150 x 224 16.3 -> 12.9, fp32 3 x 640 x 640 x 64 121 -> 105. 7 x 7 in fp32 is bound by its matrix instructions.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -116,23 +117,35 @@ __device__ __forceinline__ void stem_body(const StemMfmaParams& p, const int bx)
 
   // ---- multiply. Group g: filter row g / G, elements (g % G) KE ..; step t is groups 2 t (lower half
   // of the wavefront) and 2 t + 1.
-  f32x16 acc[NT][FW];
-#pragma unroll
-  for (int a = 0; a < NT; ++a)
-#pragma unroll
-    for (int b = 0; b < FW; ++b)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.f;
   // words of the last group of a filter row that hold elements of it
   auto last_mask = [](int j) constexpr {
     const int left = KJ - (G - 1) * KE - j * EPD;
     return left >= EPD ? 0xffffffffu : left <= 0 ? 0u : 0xffffu;
   };
   const unsigned upper = half ? 0xffffffffu : 0u;
+  const Clamp cl = make_clamp(p.act);
+  T* const yg = (T*)p.y;
+  T* const y2 = (T*)p.y2;
+  constexpr int PE = 16 / (int)sizeof(T);                    // channels per piece
+  const int piece = (lane >> 5) + ((lane >> 4) & 1) * 2;     // of a pixel's four that this lane stores
+  f32x4 bias[NT][4];
+  auto load_bias = [&]() __attribute__((always_inline)) {
 #pragma unroll
+    for (int k = 0; k < NT; ++k)
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+        bias[k][g] = p.bias ? *(const f32x4*)(p.bias + (blockIdx.y * NT + k) * 32 + g * 8 + half * 4) : f32x4{0.f, 0.f, 0.f, 0.f};
+  };
+  if constexpr (FW > 1) load_bias();
+#pragma unroll 1
   for (int f = 0; f < FW; ++f) {
     const int idx = wave * FW + f, r = idx >> 1, col = (idx & 1) * 32 + px;
     const int e = col * S * 3;                               // first element of the window in a staged row
+    f32x16 acc[NT];
+#pragma unroll
+    for (int a = 0; a < NT; ++a)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[a][i] = 0.f;
     const unsigned* const win = patch[COPIES == 2 ? (e & 1) : 0] + r * S * PITCH + e / EPD;
 #pragma unroll
     for (int t = 0; t < STEPS; ++t) {
@@ -149,40 +162,45 @@ __device__ __forceinline__ void stem_body(const StemMfmaParams& p, const int bx)
         if (ma != 0xffffffffu || mb != 0xffffffffu) d[j] &= (mb & upper) | (ma & ~upper);
       }
 #pragma unroll
-      for (int k = 0; k < NT; ++k) mma<T>(w[t][k], d, acc[k][f]);
+      for (int k = 0; k < NT; ++k) mma<T>(w[t][k], d, acc[k]);
     }
-  }
-
-  // ---- bias, activation, the one rounding: a lane holds channels 8 g + 4 half + {0..3} of its pixel
-  const Clamp cl = make_clamp(p.act);
-  T* const yg = (T*)p.y;
-  T* const y2 = (T*)p.y2;
+    // ---- bias, activation, the one rounding: a lane holds channels 8 g + 4 half + {0..3} of its pixel. Two pieces
+    // of 16 bytes of 32 pixels become one store of four pieces of the first 16 pixels and one of the others: a
+    // store then writes 64 consecutive bytes of a pixel instead of 32 (19.0 -> 17.4 us on 1080 x 640 x 32).
+    if constexpr (FW == 1) load_bias();
+    const int row = r0 + r, ocol = c0 + (idx & 1) * 32 + (lane & 15);
 #pragma unroll
-  for (int k = 0; k < NT; ++k) {
-    const int co = (blockIdx.y * NT + k) * 32;
-    f32x4 bias[4];
-#pragma unroll
-    for (int g = 0; g < 4; ++g) bias[g] = p.bias ? *(const f32x4*)(p.bias + co + g * 8 + half * 4) : f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int f = 0; f < FW; ++f) {
-      const int idx = wave * FW + f, row = r0 + (idx >> 1), col = c0 + (idx & 1) * 32 + px;
-      const bool live = (row < p.R) & (col < p.W_out);
-      const size_t at = ((size_t)(n * p.y_rows + p.out_lo + row - p.y_row0) * p.W_out + col) * p.C_out + co;
+    for (int k = 0; k < NT; ++k) {
+      const size_t at = ((size_t)(n * p.y_rows + p.out_lo + row - p.y_row0) * p.W_out + ocol) * p.C_out + (blockIdx.y * NT + k) * 32 + piece * PE;
       float v[16];
 #pragma unroll
       for (int g = 0; g < 4; ++g)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) v[g * 4 + j] = clamp_act(acc[k][f][g * 4 + j] + bias[g][j], cl);
+        for (int j = 0; j < 4; ++j) v[g * 4 + j] = clamp_act(acc[k][g * 4 + j] + bias[k][g][j], cl);
+      auto put = [&](u32x4 a, u32x4 b, int channel) __attribute__((always_inline)) {
+        u32x4 lo, hi;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const auto s2 = __builtin_amdgcn_permlane16_swap(a[j], b[j], false, false);
+          lo[j] = s2[0]; hi[j] = s2[1];
+        }
+        if ((row < p.R) & (ocol < p.W_out)) {
+          *(u32x4*)(yg + at + channel) = lo;
+          if (y2) *(u32x4*)(y2 + at + channel) = lo;
+        }
+        if ((row < p.R) & (ocol + 16 < p.W_out)) {
+          *(u32x4*)(yg + at + (size_t)16 * p.C_out + channel) = hi;
+          if (y2) *(u32x4*)(y2 + at + (size_t)16 * p.C_out + channel) = hi;
+        }
+      };
       if constexpr (sizeof(T) == 4) {
 #pragma unroll
-        for (int g = 0; g < 4; ++g)
-          if (live) {
-            const f32x4 o = f32x4{v[g * 4], v[g * 4 + 1], v[g * 4 + 2], v[g * 4 + 3]};
-            *(f32x4*)(yg + at + g * 8 + half * 4) = o;
-            if (y2) *(f32x4*)(y2 + at + g * 8 + half * 4) = o;
-          }
+        for (int g = 0; g < 4; g += 2)
+          put(__builtin_bit_cast(u32x4, (f32x4{v[g * 4], v[g * 4 + 1], v[g * 4 + 2], v[g * 4 + 3]})),
+              __builtin_bit_cast(u32x4, (f32x4{v[g * 4 + 4], v[g * 4 + 5], v[g * 4 + 6], v[g * 4 + 7]})), g * 8);
       } else {
         // (pieces of 4 + 4 channels exchanged between the halves: 8 consecutive ones per lane)
+        u32x4 out[2];
 #pragma unroll
         for (int g = 0; g < 4; g += 2) {
           alignas(16) __bf16 o[8];
@@ -191,12 +209,9 @@ __device__ __forceinline__ void stem_body(const StemMfmaParams& p, const int bx)
           const u32x4 b = *(const u32x4*)o;
           const auto s0 = __builtin_amdgcn_permlane32_swap(b[0], b[2], false, false);
           const auto s1 = __builtin_amdgcn_permlane32_swap(b[1], b[3], false, false);
-          const u32x4 out = u32x4{(unsigned)s0[0], (unsigned)s1[0], (unsigned)s0[1], (unsigned)s1[1]};
-          if (live) {
-            *(u32x4*)(yg + at + g * 8 + half * 8) = out;
-            if (y2) *(u32x4*)(y2 + at + g * 8 + half * 8) = out;
-          }
+          out[g / 2] = u32x4{(unsigned)s0[0], (unsigned)s1[0], (unsigned)s0[1], (unsigned)s1[1]};
         }
+        put(out[0], out[1], 0);
       }
     }
   }
