@@ -266,7 +266,7 @@ __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(2)
 // The same for several bands of one layer in one grid (band b owns blocks first[b] .. first[b + 1] of x).
 template <typename T, int BM, int BN, int WM, int WN, int NST>
 __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(2))) void conv_gemm_kernel_bands(const Batch<GemmParams> t) {
-  const int b = find_band(t, blockIdx.x);
+  const int b = batch_find(t, blockIdx.x);
   gemm_body<T, BM, BN, WM, WN, NST>(t.p[b], blockIdx.x - t.first[b], t.first[b + 1] - t.first[b]);
 }
 
@@ -476,7 +476,7 @@ __global__ __launch_bounds__(128 * WM * WN) __attribute__((amdgpu_waves_per_eu(2
 // The same for several bands of one layer in one grid (band b owns blocks first[b] .. first[b + 1] of x).
 template <int BM, int BN, int WM, int WN>
 __global__ __launch_bounds__(128 * WM * WN) __attribute__((amdgpu_waves_per_eu(2))) void conv_gemm_split_kernel_bands(const Batch<GemmParams> t) {
-  const int b = find_band(t, blockIdx.x);
+  const int b = batch_find(t, blockIdx.x);
   gemm_split_body<BM, BN, WM, WN>(t.p[b], blockIdx.x - t.first[b], t.first[b + 1] - t.first[b]);
 }
 

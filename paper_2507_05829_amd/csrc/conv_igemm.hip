@@ -473,7 +473,7 @@ __global__ __launch_bounds__(64 * WM * WN) void conv_igemm_kernel(const ConvPara
 // The same for several bands of one layer in one grid (band b owns blocks first[b] .. first[b + 1] of x).
 template <typename T, int BM, int BN, int WM, int WN, int BKB, int NS, bool VEC_A>
 __global__ __launch_bounds__(64 * WM * WN) void conv_igemm_kernel_bands(const Batch<ConvParams> t) {
-  const int b = find_band(t, blockIdx.x);
+  const int b = batch_find(t, blockIdx.x);
   conv_igemm_kernel_body<T, BM, BN, WM, WN, BKB, NS, VEC_A>(t.p[b], blockIdx.x - t.first[b], t.first[b + 1] - t.first[b]);
 }
 
@@ -529,7 +529,7 @@ __global__ __launch_bounds__(256) void splitk_finish_kernel(const ConvParams p) 
 // The same for several bands of one layer in one grid (band b owns blocks first[b] .. first[b + 1] of x).
 template <typename T>
 __global__ __launch_bounds__(256) void splitk_finish_kernel_bands(const Batch<ConvParams> t) {
-  const int b = find_band(t, blockIdx.x);
+  const int b = batch_find(t, blockIdx.x);
   splitk_finish_kernel_body<T>(t.p[b], blockIdx.x - t.first[b], t.first[b + 1] - t.first[b]);
 }
 
@@ -734,7 +734,7 @@ __global__ __launch_bounds__(64 * WK) void conv_direct_kernel(const ConvParams p
 // The same for several bands of one layer in one grid (band b owns blocks first[b] .. first[b + 1] of x).
 template <typename T, int WK, int NT>
 __global__ __launch_bounds__(64 * WK) void conv_direct_kernel_bands(const Batch<ConvParams> t) {
-  const int b = find_band(t, blockIdx.x);
+  const int b = batch_find(t, blockIdx.x);
   conv_direct_kernel_body<T, WK, NT>(t.p[b], blockIdx.x - t.first[b], t.first[b + 1] - t.first[b]);
 }
 
@@ -1099,7 +1099,7 @@ __global__ __launch_bounds__(256) void conv_lds_kernel(const ConvParams p) {
 // The same for several bands of one layer in one grid (band b owns blocks first[b] .. first[b + 1] of x).
 template <typename T, int BM, int BN, int NST, bool POOL, int TPS>
 __global__ __launch_bounds__(256) void conv_lds_kernel_bands(const Batch<ConvParams> t) {
-  const int b = find_band(t, blockIdx.x);
+  const int b = batch_find(t, blockIdx.x);
   conv_lds_kernel_body<T, BM, BN, NST, POOL, TPS>(t.p[b], blockIdx.x - t.first[b], t.first[b + 1] - t.first[b]);
 }
 
@@ -1264,7 +1264,7 @@ __global__ __launch_bounds__(64 * kNarrowWaves) void conv_narrow_kernel(const Co
 // The same for several bands of one layer in one grid (band b owns blocks first[b] .. first[b + 1] of x).
 template <typename T>
 __global__ __launch_bounds__(64 * kNarrowWaves) void conv_narrow_kernel_bands(const Batch<ConvParams> t) {
-  const int b = find_band(t, blockIdx.x);
+  const int b = batch_find(t, blockIdx.x);
   conv_narrow_kernel_body<T>(t.p[b], blockIdx.x - t.first[b], t.first[b + 1] - t.first[b]);
 }
 

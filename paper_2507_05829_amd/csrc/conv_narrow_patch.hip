@@ -190,7 +190,7 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(8))
 // The same for several bands of one layer in one grid (band b owns blocks first[b] .. first[b + 1] of x).
 template <typename T, int AHEAD, int LDS>
 __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(8))) void conv_narrow_patch_kernel_bands(const Batch<NarrowParams> t) {
-  const int b = find_band(t, blockIdx.x);
+  const int b = batch_find(t, blockIdx.x);
   narrow_body<AHEAD, LDS>(t.p[b], blockIdx.x - t.first[b], t.first[b + 1] - t.first[b]);
 }
 

@@ -760,13 +760,12 @@ __device__ __forceinline__ void patch_tile(const PatchParams& p, const int bx, c
 
 template <typename T, int BM, int BN, bool POOL, int S>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void conv_patch_kernel(const PatchParams p) {
-  touch_arguments<sizeof(PatchParams)>();
   patch_tile<T, BM, BN, POOL, S>(p, blockIdx.x, gridDim.x);
 }
 // The same for several bands of one layer in one grid (band b owns blocks first[b] .. first[b + 1] of x).
 template <typename T, int BM, int BN, bool POOL, int S>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void conv_patch_kernel_bands(const Batch<PatchParams> t) {
-  const int b = find_band(t, blockIdx.x);
+  const int b = batch_find(t, blockIdx.x);
   patch_tile<T, BM, BN, POOL, S>(t.p[b], blockIdx.x - t.first[b], t.first[b + 1] - t.first[b]);
 }
 

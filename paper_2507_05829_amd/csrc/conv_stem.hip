@@ -157,7 +157,7 @@ __global__ __launch_bounds__(256) void conv_stem_lane_kernel(const StemParams p)
 // The same for several bands of the layer in one grid (band b owns blocks first[b] .. first[b + 1]).
 template <typename T, int KJ, int CPL>
 __global__ __launch_bounds__(256) void conv_stem_lane_kernel_bands(const Batch<StemParams> t) {
-  const int b = find_band(t, blockIdx.x);
+  const int b = batch_find(t, blockIdx.x);
   conv_stem_lane_kernel_body<T, KJ, CPL>(t.p[b], blockIdx.x - t.first[b]);
 }
 
@@ -257,7 +257,7 @@ __global__ __launch_bounds__(256) void conv_stem_kernel(const StemParams p) {
 // The same for several bands of the layer in one grid (band b owns blocks first[b] .. first[b + 1]).
 template <typename T, int KJ>
 __global__ __launch_bounds__(256) void conv_stem_kernel_bands(const Batch<StemParams> t) {
-  const int b = find_band(t, blockIdx.x);
+  const int b = batch_find(t, blockIdx.x);
   conv_stem_kernel_body<T, KJ>(t.p[b], blockIdx.x - t.first[b]);
 }
 

@@ -226,7 +226,7 @@ __global__ __launch_bounds__(256) void conv_stem_mfma_kernel(const StemMfmaParam
 }
 template <typename T, int KJ, int S, int NT>
 __global__ __launch_bounds__(256) void conv_stem_mfma_kernel_bands(const Batch<StemMfmaParams> t) {
-  const int b = find_band(t, blockIdx.x);
+  const int b = batch_find(t, blockIdx.x);
   stem_body<T, KJ / 3, S, NT, 2>(t.p[b], blockIdx.x - t.first[b]);
 }
 template <typename T, int KJ, int S, int NT>
@@ -235,7 +235,7 @@ __global__ __launch_bounds__(256) void conv_stem_mfma_tall_kernel(const StemMfma
 }
 template <typename T, int KJ, int S, int NT>
 __global__ __launch_bounds__(256) void conv_stem_mfma_tall_kernel_bands(const Batch<StemMfmaParams> t) {
-  const int b = find_band(t, blockIdx.x);
+  const int b = batch_find(t, blockIdx.x);
   stem_body<T, KJ / 3, S, NT, 8>(t.p[b], blockIdx.x - t.first[b]);
 }
 

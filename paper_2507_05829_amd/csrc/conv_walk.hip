@@ -262,13 +262,12 @@ __device__ __forceinline__ void walk_body(const PatchParams& p, const int bx, co
 
 template <int PIXB, int S, int WCO, bool POOL>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(PIXB == 64 ? 3 : 2))) void conv_walk_kernel(const PatchParams p) {
-  touch_arguments<sizeof(PatchParams)>();
   walk_body<PIXB, S, WCO, POOL>(p, blockIdx.x, gridDim.x);
 }
 // The same for several bands of one layer in one grid (band b owns blocks first[b] .. first[b + 1] of x).
 template <int PIXB, int S, int WCO, bool POOL>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(PIXB == 64 ? 3 : 2))) void conv_walk_kernel_bands(const Batch<PatchParams> t) {
-  const int b = find_band(t, blockIdx.x);
+  const int b = batch_find(t, blockIdx.x);
   walk_body<PIXB, S, WCO, POOL>(t.p[b], blockIdx.x - t.first[b], t.first[b + 1] - t.first[b]);
 }
 

@@ -3,8 +3,6 @@
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
-#include <cstddef>
-
 #include "kernels.hpp"
 
 namespace lop {
@@ -40,22 +38,6 @@ template <typename P>
 __device__ __forceinline__ int batch_find(const Batch<P>& t, int bx) {
   int b = 0;
   while (b + 1 < t.n && bx >= t.first[b + 1]) ++b;
-  return b;
-}
-
-// Reads a word of every 64-byte line of the kernel's arguments from `offset` on, all at once. Left to itself a kernel loads a
-// parameter shortly before it needs it, line after line of memory that no cache holds yet when a launch starts (a chain of
-// 13 launches over eight bands, alone: 246 -> 239 us).
-template <int BYTES>
-__device__ __forceinline__ void touch_arguments(int offset = 0) {
-  const auto* const at = (const __attribute__((address_space(4))) char*)__builtin_amdgcn_kernarg_segment_ptr() + offset;
-  auto word = [&](int i) __attribute__((always_inline)) { return *(const __attribute__((address_space(4))) int*)(at + (i < BYTES - 4 ? i : BYTES - 4)); };
-  asm volatile("" ::"s"(word(0)), "s"(word(64)), "s"(word(128)), "s"(word(192)), "s"(word(256)));
-}
-template <typename P>
-__device__ __forceinline__ int find_band(const Batch<P>& t, int bx) {
-  const int b = batch_find(t, bx);
-  touch_arguments<sizeof(P)>((int)offsetof(Batch<P>, p) + b * (int)sizeof(P));
   return b;
 }
 

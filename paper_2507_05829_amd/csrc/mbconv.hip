@@ -343,7 +343,7 @@ __global__ __launch_bounds__(256, S == 1 && ROWS == 8 ? 4 : 3) void mbconv_kerne
 // The same for several bands of one block in one grid (band b owns blocks first[b] .. first[b + 1]).
 template <int S, bool RES, int ROWS>
 __global__ __launch_bounds__(256, S == 1 && ROWS == 8 ? 4 : 3) void mbconv_kernel_bands(const Batch<MbParams> t) {
-  const int b = find_band(t, blockIdx.x);
+  const int b = batch_find(t, blockIdx.x);
   mbconv_body<S, RES, ROWS>(t.p[b], blockIdx.x - t.first[b]);
 }
 

@@ -213,7 +213,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void p
 // The same for several bands of one layer in one grid (band b owns blocks first[b] .. first[b + 1]).
 template <int NT, int KS, bool RES, int GPW>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void pointwise_kernel_bands(const Batch<PwParams> t) {
-  const int b = find_band(t, blockIdx.x);
+  const int b = batch_find(t, blockIdx.x);
   pointwise_body<NT, KS, RES, GPW>(t.p[b], blockIdx.x - t.first[b]);
 }
 

@@ -164,7 +164,7 @@ __global__ __launch_bounds__(256) void rowwise_kernel(const RowParams p) {
 // The same for several bands of one layer in one grid (band b owns blocks first[b] .. first[b + 1]).
 template <typename T, int VEC, int OP>
 __global__ __launch_bounds__(256) void rowwise_kernel_bands(const Batch<RowParams> t) {
-  const int b = find_band(t, blockIdx.x);
+  const int b = batch_find(t, blockIdx.x);
   rowwise_kernel_body<T, VEC, OP>(t.p[b], blockIdx.x - t.first[b]);
 }
 
@@ -290,7 +290,7 @@ __global__ __launch_bounds__(256) void dwconv3x3_kernel(const Dw3Params q) {
 // The same for several bands of one layer in one grid (band b owns blocks first[b] .. first[b + 1]).
 template <typename T, int VEC, int S>
 __global__ __launch_bounds__(256) void dwconv3x3_kernel_bands(const Batch<Dw3Params> t) {
-  const int b = find_band(t, blockIdx.x);
+  const int b = batch_find(t, blockIdx.x);
   dwconv3x3_body<T, VEC, S>(t.p[b], blockIdx.x - t.first[b]);
 }
 
