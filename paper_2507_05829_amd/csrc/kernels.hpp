@@ -112,6 +112,10 @@ void stem_mfma_pack(const unsigned char* src, int row_pitch, int c_out, int kh, 
 bool stem_mfma_applies(const OpLaunch& L);
 hipError_t launch_stem_mfma(const OpLaunch* Ls, int n, bool large, hipStream_t stream, KernelEvents* ev);
 void stem_mfma_describe(const OpLaunch& L, bool large, const char* form, char* name, size_t size);
+// The 7 x 7 stride-2 layer with the 3 x 3 stride-2 max pooling behind it (see convpool_applies).
+bool stem_pool_applies(const OpLaunch& conv, const OpLaunch& pool);
+hipError_t launch_stem_pool(const OpLaunch* convs, const OpLaunch* pools, int n, hipStream_t stream, KernelEvents* ev);
+void stem_pool_describe(const OpLaunch& conv, const char* form, char* name, size_t size);
 // The patch form of the LDS-staged kernel (3 x 3 filters; pools: the max pooling behind each band's
 // convolution, or nullptr): whether a group of bands takes it, the launch and its kernel name.
 bool patch_applies(const OpLaunch* convs, const OpLaunch* pools, int n);
@@ -140,7 +144,8 @@ hipError_t launch_siblings(const OpLaunch* convs, const OpLaunch* sibs, int n, h
 bool gemm_applies(const OpLaunch* Ls, int n);
 hipError_t launch_gemm(const OpLaunch* Ls, int n, hipStream_t stream, KernelEvents* ev);
 int gemm_describe(const OpLaunch* Ls, int n, char* name, size_t size);
-// A dense convolution and the 2 x 2 stride-2 max pooling that reads it, as one launch: whether
+// A dense convolution and the max pooling that reads it (2 x 2, stride 2; of a 7 x 7 stride-2 first layer 3 x 3,
+// stride 2, padded by one), as one launch: whether
 // the pair qualifies (descriptors without slabs suffice), the launch (conv: input slab, weights,
 // hyper-parameters; pool: output slab, y2 and the pooled rows out_lo..out_hi) and its kernel name.
 bool convpool_applies(const OpLaunch& conv, const OpLaunch& pool);

@@ -649,8 +649,8 @@ using lop::describe_layer;
 
 // Groups of three layers that run as one launch (an inverted-residual block): layer h a 1x1
 // conv, h + 1 a depthwise conv reading only h, h + 2 a 1x1 conv reading only h + 1, and
-// nobody else reads h or h + 1. Then groups of two: a dense conv and the 2 x 2 stride-2 max
-// pooling that is its only reader, where that pays for launches of one band (merged false) or
+// nobody else reads h or h + 1. Then groups of two: a dense conv and the max
+// pooling that is its only reader (see convpool_applies), where that pays for launches of one band (merged false) or
 // of all bands (merged true).
 void find_fused_groups(lop_plan_t* P, bool merged, Fusion* F) {
   const lop::Tables& t = P->t;
@@ -675,8 +675,8 @@ void find_fused_groups(lop_plan_t* P, bool merged, Fusion* F) {
     F->away[h] = F->away[m] = 1;
     h = q;
   }
-  // The pooling windows do not overlap, so the rows of the conv a launch computes are exactly
-  // twice its pooled rows, in every mode (checked, since the launch derives them that way).
+  // The launch computes the rows of the conv under its pooling windows: those have to be the rows the plan has it
+  // compute. (Windows that do not overlap: in every mode. With overlapping ones not where bands share rows.)
   const bool whole = t.disjoint();
   for (int h = 0; h + 1 < nl; ++h) {
     const int q = h + 1;
@@ -690,6 +690,8 @@ void find_fused_groups(lop_plan_t* P, bool merged, Fusion* F) {
     }
     if (shared) continue;
     if (!lop::convpool_applies(describe_layer(P, h), describe_layer(P, q))) continue;
+    // (a first layer keeps its own launches for bands one by one, whose callers time and watch layer by layer)
+    if (!merged && lop::stem_pool_applies(describe_layer(P, h), describe_layer(P, q))) continue;
     const lop::LayerInfo& C = t.layers[h];
     const size_t esz = t.esz();
     if ((size_t)C.n * C.h_in * C.w_in * C.d.c_in * esz >= ((size_t)1 << 31)) continue;  // 32-bit offsets
@@ -698,7 +700,8 @@ void find_fused_groups(lop_plan_t* P, bool merged, Fusion* F) {
     auto take = [&](int b) {
       const lop_rows_t pr = t.bands[b].compute[q], cr = t.bands[b].compute[h];
       if (pr.hi <= pr.lo) { fits = fits && cr.hi <= cr.lo; return; }
-      fits = fits && cr.lo == 2 * pr.lo && cr.hi == 2 * pr.hi;
+      const lop_layer_t& w = t.layers[q].d;
+      fits = fits && cr.lo == std::max(0, pr.lo * w.sh - w.ph) && cr.hi == std::min(C.h_out, (pr.hi - 1) * w.sh - w.ph + w.kh);
       if (fits) convs.push_back(make_launch(P, b, h, nullptr, nullptr));
     };
     if (merged && whole) take(t.whole());
@@ -799,12 +802,13 @@ void launch_work(const lop_plan_t* P, int band, int l, double* flop, double* byt
     return;
   }
   if (ends_convpool(F, l)) {
-    // the conv's operations on twice the pooled rows plus the comparisons; bytes of the conv's
+    // the conv's operations on the rows under the windows plus the comparisons; bytes of the conv's
     // input rows and weights and of the pooled rows only
     const int h = F.head[l];
     const lop::LayerInfo &C = t.layers[h], &Q = t.layers[l];
     const lop_rows_t rd = t.bands[band].reads[h];
-    *flop = t.layer_flop(h, 2 * (r.hi - r.lo)) + t.layer_flop(l, r.hi - r.lo);
+    const lop_rows_t cr = t.bands[band].compute[h];
+    *flop = t.layer_flop(h, cr.hi - cr.lo) + t.layer_flop(l, r.hi - r.lo);
     const double e = (double)t.esz();
     *bytes = e * Q.n * ((double)(rd.hi - rd.lo) * C.w_in * C.d.c_in + (double)(r.hi - r.lo) * Q.w_out * Q.d.c_out) +
              e * (double)C.d.c_out * C.d.c_in * C.d.kh * C.d.kw;

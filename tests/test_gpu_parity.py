@@ -1852,6 +1852,64 @@ def test_first_layer_on_the_matrix_cores(oracle, cfg):
     np.testing.assert_array_equal(~np.isfinite(dev), hit)
 
 
+@pytest.mark.parametrize("mode", [lop.LOP_FLAG_INDEPENDENT, lop.LOP_FLAG_REUSE, lop.LOP_FLAG_BATCH_BANDS])
+@pytest.mark.parametrize("cfg", [
+    # dtype, channels out, padding of the convolution, activation, shape (n, h, w), bands
+    ("f32", 64, 3, "relu", (1, 57, 61), 3),       # tiles cut in both directions
+    ("f32", 32, 2, "none", (2, 28, 32), 2),       # negative outputs: padding must not count as a zero
+    ("bf16", 64, 3, "relu6", (2, 58, 63), 4),     # rows of an odd number of elements
+    ("bf16", 96, 3, "none", (1, 30, 34), 1),      # three channel tiles, one at a time
+    ("bf16", 32, 0, "relu", (1, 9, 13), 1),       # two by four outputs, one by two pooled pixels
+    ("f32", 64, 3, "relu", (1, 130, 244), 5),     # several tiles of every band
+])
+def test_first_layer_with_its_pooling(oracle, cfg, mode):
+    """The 7 x 7 stride-2 layer and the 3 x 3 stride-2 pooling behind it as one launch of a merged chain: against the oracle;
+    in bf16 bit for bit against the two launches (the same products in the same order, and a maximum rounds nothing), in fp32,
+    where the products are made of parts, in 64 bits and with pixels that are not finite."""
+    dtype, c_out, p_, act, shape, bands = cfg
+    for tail in (False, True):
+        chain = workloads.Chain("stem", (shape[0], 3, shape[1], shape[2]), dtype, bands)
+        chain.add(workloads.CONV, 3, c_out, 7, 2, p_, 1, act)
+        chain.add(workloads.MAXPOOL, c_out, c_out, 3, 2, 1)
+        if tail:
+            chain.add(workloads.CONV, c_out, 32, 3, 1, 1, 1, "none")
+        t = workloads.make_tensors(chain, zero_bias=False, seed=59)
+        dev, host = run_gpu(chain, t, flags=mode)
+        np.testing.assert_array_equal(dev, host)
+        assert rel_err(dev, oracle.run_chain(chain, t)) <= TOL[dtype]
+        apart, _ = run_gpu(chain, t, flags=mode | lop.LOP_FLAG_NO_FUSE)
+        if dtype == "bf16":
+            np.testing.assert_array_equal(dev, apart)
+        elif not tail:
+            f = lambda a: torch.from_numpy(np.asarray(a, np.float64))
+
+            def reference(x):
+                y = torch.nn.functional.conv2d(f(x), f(t.weights[0]), f(t.biases[0]), 2, p_)
+                return torch.nn.functional.max_pool2d(y.relu() if act == "relu" else y, 3, 2, 1).numpy()
+
+            # 147 / 16 roundings of 2^-24 of sums that grow like their square root; no further off than the fp32 instructions
+            want = reference(t.x)
+            off = np.linalg.norm(dev - want)
+            assert off <= 2 * np.sqrt(147 / 16) * 2.0 ** -24 * np.linalg.norm(want)
+            assert off <= np.linalg.norm(apart - want)
+            for value in (np.inf, -np.inf, np.nan, 3.4e38):
+                x = t.x.copy()
+                x[0, 1, 9, 11] = value
+                t_odd = workloads.Tensors(x, t.weights, t.biases)
+                dev, _ = run_gpu(chain, t_odd, flags=mode)
+                apart, _ = run_gpu(chain, t_odd, flags=mode | lop.LOP_FLAG_NO_FUSE)
+                ok = np.isfinite(apart) & (np.abs(apart) < 1e30)
+                assert ok.mean() > 0.9 and (value != value or not ok.all())
+                np.testing.assert_allclose(dev[~ok], apart[~ok], rtol=1e-5)
+                assert (np.abs(dev[ok] - apart[ok]) <= 1e-5 * np.abs(want).max()).all()
+    if mode == lop.LOP_FLAG_BATCH_BANDS:
+        plan = lop.Plan(chain, t, None, mode)
+        try:
+            assert plan.layer_kernel(0, 1)[0].startswith("conv_stem_pool_kernel"), plan.layer_kernel(0, 1)
+        finally:
+            plan.destroy()
+
+
 @pytest.mark.parametrize("cfg", [
     # shape(n,h,w) of the input, bands, channels: 1x1, depthwise and 1x1 layers, each a launch of its own for all bands
     ((1, 41, 37), 8, 32),       # ragged groups of pixels, several images' worth of bands in a launch
