@@ -103,9 +103,8 @@ struct TileId { int m, n, z; };
 constexpr int kXcds = 8, kGroupM = 8;
 // (by_group: division by kGroupM * ny, made on the host; the other divisions of this walk are by
 // constants or lie behind conditions that hold for few workgroups)
-__device__ __forceinline__ TileId xcd_tile(int bx, int mx, int ny, int nz, const FastDiv& by_group) {
+__device__ __forceinline__ TileId xcd_tile_of(int launch, int mx, int ny, int nz, const FastDiv& by_group) {
   const int total = mx * ny * nz;
-  const int launch = bx + mx * (blockIdx.y + ny * blockIdx.z);
   const int xcd = launch % kXcds, slot = launch / kXcds;
   const int q = total / kXcds, r = total % kXcds;
   const int v = xcd * q + min(xcd, r) + slot;  // XCD k owns q (+1 for the first r) consecutive tiles
@@ -123,6 +122,10 @@ __device__ __forceinline__ TileId xcd_tile(int bx, int mx, int ny, int nz, const
   id.n = gm == kGroupM ? in_group / kGroupM : in_group / gm;
   id.m = first + in_group - id.n * gm;
   return id;
+}
+
+__device__ __forceinline__ TileId xcd_tile(int bx, int mx, int ny, int nz, const FastDiv& by_group) {
+  return xcd_tile_of(bx + mx * (blockIdx.y + ny * blockIdx.z), mx, ny, nz, by_group);
 }
 
 // f(integral_constant<0>) ... f(integral_constant<N - 1>): loops whose body needs its index as a constant

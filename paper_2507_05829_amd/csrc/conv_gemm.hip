@@ -44,6 +44,7 @@ struct GemmParams {
   int r_row0, r_rows;
   int sh, sw, ph, pw, act, k_pad;
   int out_lo, R, N, M;               // M = N * R * W_out
+  int mx, ny;                        // tiles of a launch of one band
   FastDiv by_w, by_r, by_group;
 };
 static_assert(sizeof(Batch<GemmParams>) <= 4096, "the parameters of all bands of a launch travel as kernel arguments");
@@ -111,8 +112,79 @@ __device__ __forceinline__ void gemm_epilogue(const GemmParams& p, unsigned char
   }
 }
 
-template <typename T, int BM, int BN, int WM, int WN, int NST>
-__device__ __forceinline__ void gemm_body(const GemmParams& p, const int bx, const int gx) {
+// The same from registers, without LDS: a lane holds channels 8 g + 4 half + {0..3} of pixel lane mod 32 of a 32 x 32
+// tile; exchanges between the lane halves and between rows of 16 lanes make each store write 64 consecutive bytes of
+// 16 pixels. (As fast as the form above within 2 %; two stores of every lane per 32 x 32 tile where all of it lies inside.)
+template <typename T, int TM, int TN>
+__device__ __forceinline__ void gemm_store(const GemmParams& p, const f32x16 (&acc)[TN][TM], const f32x4 (&bias)[TN][4], int m_first,
+                                           int co_first, int lane) {
+  static_assert(sizeof(T) == 2, "bf16");
+  const int half = lane >> 5;
+  const int piece = half + ((lane >> 4) & 1) * 2;          // of the four of a store's 64 bytes
+  const Clamp cl = make_clamp(p.act);
+  auto pixel = [&](int m, int rows, int row0) __attribute__((always_inline)) {   // offset of a pixel's first channel
+    const int mm = m < p.M ? m : 0;
+    const int q = fastdiv(mm, p.by_w), ow = mm - q * p.W_out;
+    const int n = fastdiv(q, p.by_r), oh = p.out_lo + q - n * p.R;
+    return ((size_t)(n * rows + oh - row0) * p.W_out + ow) * p.C_out;
+  };
+#pragma unroll
+  for (int tm = 0; tm < TM; ++tm) {
+    const int m = m_first + tm * 32 + (lane & 15);
+    const size_t at[2] = {pixel(m, p.y_rows, p.y_row0), pixel(m + 16, p.y_rows, p.y_row0)};
+    const bool live[2] = {m < p.M, m + 16 < p.M};
+    const size_t ra = p.res ? pixel(m_first + tm * 32 + (lane & 31), p.r_rows, p.r_row0) : 0;
+#pragma unroll
+    for (int tn = 0; tn < TN; ++tn) {
+      const int co = co_first + tn * 32;
+      u32x4 o[2];
+#pragma unroll
+      for (int g = 0; g < 4; g += 2) {
+        alignas(16) __bf16 b[8];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const int c = co + (g + h) * 8 + half * 4;
+          f32x4 v = f32x4{acc[tn][tm][(g + h) * 4], acc[tn][tm][(g + h) * 4 + 1], acc[tn][tm][(g + h) * 4 + 2], acc[tn][tm][(g + h) * 4 + 3]};
+          v += bias[tn][g + h];
+          if (p.res && c < p.C_out) {
+            alignas(8) T r[4];
+            *(uint2*)r = *(const uint2*)((const T*)p.res + ra + c);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) v[k] += to_f32(r[k]);
+          }
+#pragma unroll
+          for (int k = 0; k < 4; ++k) b[h * 4 + k] = from_f32<T>(clamp_act(v[k], cl));
+        }
+        const u32x4 w = *(const u32x4*)b;
+        const auto s0 = __builtin_amdgcn_permlane32_swap(w[0], w[2], false, false);
+        const auto s1 = __builtin_amdgcn_permlane32_swap(w[1], w[3], false, false);
+        o[g / 2] = u32x4{(unsigned)s0[0], (unsigned)s1[0], (unsigned)s0[1], (unsigned)s1[1]};
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const auto s = __builtin_amdgcn_permlane16_swap(o[0][j], o[1][j], false, false);
+        o[0][j] = s[0];
+        o[1][j] = s[1];
+      }
+      const int c = co + piece * 8;
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+        if (live[h] & (c < p.C_out)) {
+          *(u32x4*)((T*)p.y + at[h] + c) = o[h];
+          if (p.y2) *(u32x4*)((T*)p.y2 + at[h] + c) = o[h];
+        }
+    }
+  }
+}
+
+// WALK: the workgroup takes tiles launch, launch + step, ... of mx * ny (else the first of them only). Its loop needs all the
+// LDS a compute unit has, so that no other workgroup hides a tile's start and end: 3.8 us of the 35 that 16 stages take. The next
+// tile's first stages are therefore on their way while this one's sums leave, from registers. (A wait for those loads counts the
+// younger stores: memory instructions of a wavefront finish in order.) us a launch, a workgroup per tile -> walking: 65 536 x
+// 1024 -> 4096 609 -> 570, 4096 -> 1024 507 -> 498; 40 000 x 816 -> 2552 225 -> 201; 16 384 x 512 -> 2048 51 -> 43; 30 000 x
+// 256 -> 1024 38 -> 29.
+template <typename T, int BM, int BN, int WM, int WN, int NST, bool WALK>
+__device__ __forceinline__ void gemm_body(const GemmParams& p, int launch, const int step, const int mx, const int ny) {
   constexpr int KE = 16 / (int)sizeof(T);   // elements per 16-byte chunk
   constexpr int NW = WM * WN;
   constexpr int TM = BM / (32 * WM), TN = BN / (32 * WN);
@@ -126,8 +198,7 @@ __device__ __forceinline__ void gemm_body(const GemmParams& p, const int bx, con
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave % WM, wn = wave / WM;
-  const TileId tile = xcd_tile(bx, gx, gridDim.y, 1, p.by_group);
-  const int m0 = tile.m * BM, co0 = tile.n * BN;
+  int m0, co0;
   const int row_bytes = p.K * (int)sizeof(T), w_bytes = p.k_pad * (int)sizeof(T);
   const int ns = w_bytes / 128;
 
@@ -140,19 +211,23 @@ __device__ __forceinline__ void gemm_body(const GemmParams& p, const int bx, con
   const int chunk = (lane & 7) ^ ((4 * (wave & 1) + (lane >> 4)) & 7);
   static_assert(NW % 2 == 0, "a wavefront's groups have one parity");
   unsigned a_off[A_LD], b_off[B_LD];
+  auto set_tile = [&](int at) __attribute__((always_inline)) {
+    const TileId tile = xcd_tile_of(at, mx, ny, 1, p.by_group);
+    m0 = tile.m * BM; co0 = tile.n * BN;
 #pragma unroll
-  for (int i = 0; i < A_LD; ++i) {
-    const int m = m0 + (wave + NW * i) * 8 + (lane >> 3);
-    const bool ok = m < p.M;
-    const int mm = ok ? m : 0;
-    const int q = fastdiv(mm, p.by_w), ow = mm - q * p.W_out;
-    const int n = fastdiv(q, p.by_r), r = q - n * p.R;
-    const int ih = (p.out_lo + r) * p.sh - p.ph, iw = ow * p.sw - p.pw;
-    const bool in = ok & (ih >= p.x_row0) & (ih < p.x_row0 + p.x_rows) & (iw >= 0) & (iw < p.W);
-    a_off[i] = in ? (unsigned)(((n * p.x_rows + ih - p.x_row0) * p.W + iw) * row_bytes + chunk * 16) : kOutside;
-  }
+    for (int i = 0; i < A_LD; ++i) {
+      const int m = m0 + (wave + NW * i) * 8 + (lane >> 3);
+      const bool ok = m < p.M;
+      const int mm = ok ? m : 0;
+      const int q = fastdiv(mm, p.by_w), ow = mm - q * p.W_out;
+      const int n = fastdiv(q, p.by_r), r = q - n * p.R;
+      const int ih = (p.out_lo + r) * p.sh - p.ph, iw = ow * p.sw - p.pw;
+      const bool in = ok & (ih >= p.x_row0) & (ih < p.x_row0 + p.x_rows) & (iw >= 0) & (iw < p.W);
+      a_off[i] = in ? (unsigned)(((n * p.x_rows + ih - p.x_row0) * p.W + iw) * row_bytes + chunk * 16) : kOutside;
+    }
 #pragma unroll
-  for (int i = 0; i < B_LD; ++i) b_off[i] = (unsigned)((co0 + (wave + NW * i) * 8 + (lane >> 3)) * w_bytes + chunk * 16);
+    for (int i = 0; i < B_LD; ++i) b_off[i] = (unsigned)((co0 + (wave + NW * i) * 8 + (lane >> 3)) * w_bytes + chunk * 16);
+  };
   // the chunk lies past the end of the reduction in the last stage
   const bool past = (ns - 1) * 128 + chunk * 16 >= row_bytes;
   auto issue = [&](int s, int j) __attribute__((always_inline)) {   // load instruction j of stage s
@@ -169,12 +244,6 @@ __device__ __forceinline__ void gemm_body(const GemmParams& p, const int bx, con
   };
 
   f32x16 acc[TN][TM];
-#pragma unroll
-  for (int a = 0; a < TN; ++a)
-#pragma unroll
-    for (int b = 0; b < TM; ++b)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.f;
 
   // ---- fragments: row lane & 31 of a 32-row tile, chunk 2 ks + (lane >> 5); two sets, one being
   // multiplied while the other is read
@@ -204,16 +273,6 @@ __device__ __forceinline__ void gemm_body(const GemmParams& p, const int bx, con
     asm volatile("" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
   };
-
-  for (int s = 0; s < NST; ++s)
-    if (s < ns)
-#pragma unroll
-      for (int j = 0; j < LPS; ++j) issue(s, j);
-  if (ns >= NST) __builtin_amdgcn_s_waitcnt(vmcnt_imm((NST - 1) * LPS));
-  else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
-  barrier();
-  read(0, 0, fa[0], fb[0]);
-  wait_reads(fa[0], fb[0]);
 
   auto multiply = [&](u32x4 (&a)[TM], u32x4 (&b)[TN], int s, bool loads) __attribute__((always_inline)) {
     constexpr int NT = TM * TN, NM = NT * kMmaParts<T>;
@@ -250,24 +309,77 @@ __device__ __forceinline__ void gemm_body(const GemmParams& p, const int bx, con
     multiply(fa[1], fb[1], s + NST, refill);
     if (next) wait_reads(fa[0], fb[0]);
   };
-  int s = 0;
-  for (; s + NST < ns; ++s) stage(s, true, true);
-  for (; s + 1 < ns; ++s) stage(s, true, false);
-  stage(s, false, false);
-
-  __syncthreads();
-  gemm_epilogue<T, TM, TN>(p, smem, acc, m0, co0, wave, wm, wn, lane);
+  auto start = [&]() __attribute__((always_inline)) {   // a tile's first loads
+    for (int s = 0; s < NST; ++s)
+      if (s < ns)
+#pragma unroll
+        for (int j = 0; j < LPS; ++j) issue(s, j);
+  };
+  set_tile(launch);
+  start();
+  bool behind_stores = false;   // STORES stores are younger than those loads
+  constexpr int STORES = TM * TN * 2;
+  static_assert(!WALK || (NST - 1) * LPS + STORES < 64, "the counter's range");
+  for (;;) {
+#pragma unroll
+    for (int a = 0; a < TN; ++a)
+#pragma unroll
+      for (int b = 0; b < TM; ++b)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.f;
+    if (ns < NST) __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+    else if (WALK && behind_stores) __builtin_amdgcn_s_waitcnt(vmcnt_imm((NST - 1) * LPS + STORES));
+    else __builtin_amdgcn_s_waitcnt(vmcnt_imm((NST - 1) * LPS));
+    barrier();
+    read(0, 0, fa[0], fb[0]);
+    wait_reads(fa[0], fb[0]);
+    int s = 0;
+    for (; s + NST < ns; ++s) stage(s, true, true);
+    for (; s + 1 < ns; ++s) stage(s, true, false);
+    if constexpr (!WALK) {
+      stage(s, false, false);
+      __syncthreads();
+      gemm_epilogue<T, TM, TN>(p, smem, acc, m0, co0, wave, wm, wn, lane);
+      return;
+    } else {
+      const int m_first = m0 + wm * TM * 32, co_first = co0 + wn * TN * 32;
+      // (ahead of the next tile's loads: a wait for these is then none for those)
+      f32x4 bias[TN][4];
+#pragma unroll
+      for (int t = 0; t < TN; ++t)
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+          bias[t][g] = p.bias ? *(const f32x4*)(p.bias + min(co_first + t * 32 + g * 8 + (lane >> 5) * 4, p.C_out - 4)) : f32x4{0.f, 0.f, 0.f, 0.f};
+      stage(s, false, false);
+#pragma unroll
+      for (int t = 0; t < TN; ++t)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) asm volatile("" : "+v"(bias[t][g]));
+      launch += step;
+      const bool more = launch < mx * ny;
+      behind_stores = !p.y2 && !p.res && m0 + BM <= p.M && co0 + BN <= p.C_out;
+      if (more) {
+        barrier();   // (no wavefront reads the last stages any more)
+        set_tile(launch);
+        start();
+      }
+      gemm_store<T, TM, TN>(p, acc, bias, m_first, co_first, lane);
+      if (!more) return;
+    }
+  }
 }
 
+// (The tiles that leave room for one workgroup per compute unit only are walked over.)
 template <typename T, int BM, int BN, int WM, int WN, int NST>
 __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(2))) void conv_gemm_kernel(const GemmParams p) {
-  gemm_body<T, BM, BN, WM, WN, NST>(p, blockIdx.x, gridDim.x);
+  if constexpr (BM == 256) gemm_body<T, BM, BN, WM, WN, NST, true>(p, blockIdx.x, gridDim.x, p.mx, p.ny);
+  else gemm_body<T, BM, BN, WM, WN, NST, false>(p, blockIdx.x + gridDim.x * blockIdx.y, 0, gridDim.x, gridDim.y);
 }
 // The same for several bands of one layer in one grid (band b owns blocks first[b] .. first[b + 1] of x).
 template <typename T, int BM, int BN, int WM, int WN, int NST>
 __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(2))) void conv_gemm_kernel_bands(const Batch<GemmParams> t) {
-  const int b = batch_find(t, blockIdx.x);
-  gemm_body<T, BM, BN, WM, WN, NST>(t.p[b], blockIdx.x - t.first[b], t.first[b + 1] - t.first[b]);
+  const int b = batch_find(t, blockIdx.x), mx = t.first[b + 1] - t.first[b];
+  gemm_body<T, BM, BN, WM, WN, NST, false>(t.p[b], (int)blockIdx.x - t.first[b] + mx * (int)blockIdx.y, 0, mx, gridDim.y);
 }
 
 // fp32 products on the bf16 matrix cores, which are 16 times as fast as the fp32 ones. A value is the sum of
@@ -501,7 +613,7 @@ GemmParams make_gemm(const OpLaunch& L) {
   p.r_row0 = L.res.row0; p.r_rows = L.res.rows;
   p.sh = L.sh; p.sw = L.sw; p.ph = L.ph; p.pw = L.pw; p.act = L.act; p.k_pad = L.k_pad;
   p.out_lo = L.out_lo; p.R = L.out_hi - L.out_lo; p.N = L.x.n;
-  p.M = p.N * p.R * p.W_out;
+  p.M = p.N * p.R * p.W_out; p.mx = p.ny = 0;
   p.by_w = make_fastdiv(p.W_out); p.by_r = make_fastdiv(p.R); p.by_group = make_fastdiv(1);
   return p;
 }
@@ -523,6 +635,9 @@ bool gemm_shape(const OpLaunch& L) {
 // of 128 x 256; 1000 x 2048 -> 512 (64 of 128 x 64) 11 there, 16 here. fp32 3001 x 512 -> 2048 (1 504 tiles of
 // 64 x 64) 85 -> 64 and 2048 -> 512 (376) 87 -> 78; 1500 x 1024 -> 256 (96) 18 there, 23 here; 8000 x 1000 -> 3000
 // (1 512 tiles of 128 x 128) 479 -> 432, against 455 with 64 x 64.
+// Workgroups of a launch of 256 x 256 tiles: one per compute unit, each of which walks over its share of the tiles (and, the
+// number being a multiple of the XCDs, over tiles of the XCD it runs on).
+constexpr long kWalkers = 256;
 struct GemmChoice { int bm = 0, bn = 0; bool split = false; };
 constexpr long kBigTiles = 128;        // 256 x 256, bf16
 constexpr long kWideTiles = 192;       // 128 x 256, bf16
@@ -575,6 +690,11 @@ hipError_t launch_tile(void (*single)(const GemmParams), void (*bands)(const Bat
     ++m;
   }
   if (m == 0) return hipSuccess;
+  if (BM == 256 && m == 1) {
+    ps[0].mx = (int)gx[0]; ps[0].ny = (int)gy;
+    const long tiles = (long)gx[0] * gy;
+    return launch_kernel(single, dim3((unsigned)std::min(tiles, kWalkers)), dim3(THREADS), s, ev, ps[0]);
+  }
   return launch_group(single, bands, ps, m, gx, gy, 1, dim3(THREADS), s, ev);
 }
 template <typename T, int BM, int BN, int WM, int WN, int NST>

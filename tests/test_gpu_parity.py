@@ -1743,6 +1743,28 @@ def test_matrix_product_kernel(oracle, cfg):
     np.testing.assert_array_equal(dev, want)
 
 
+@pytest.mark.parametrize("cfg", [
+    # rows, elements, channels, residual
+    (4360, 128, 4104, False),     # two stages; 18 x 17 tiles, those of the last row and column cut
+    (4352, 200, 4096, False),     # four stages, the last of 8 elements; whole tiles
+    (8200, 192, 2304, True),      # three stages; 33 x 9 tiles
+])
+def test_matrix_products_walking_over_tiles(oracle, cfg):
+    """More 256 x 256 tiles than workgroups, each of which takes several: against the oracle, and bit for bit against
+    bands of at most a tile per workgroup (the same products in the same order)."""
+    m, k, n, residual = cfg
+    assert -(-m // 256) * -(-n // 256) > 256
+    def chain(bands):
+        c = workloads.RowChain("walk", m, k, "bf16", bands)
+        return c.add(n, "none").add(n, "relu", residual_from=0, input_from=-1) if residual else c.add(n, "relu")
+    t = workloads.make_row_tensors(chain(1), zero_bias=False, seed=61)
+    dev, _, names = _run_rows(chain(1), t)
+    assert names == {"conv_gemm_kernel<__bf16, 256, 256, 2, 4, 2>"}, names
+    assert rel_err(dev, oracle.run_row_chain(chain(1), t)) <= TOL["bf16"]
+    apart, _, _ = _run_rows(chain(2), t, order=[0, 1])
+    np.testing.assert_array_equal(dev, apart)
+
+
 def _split_chain(m, k, n, residual, bands=1):
     chain = workloads.RowChain("split", m, k, "f32", bands)
     if residual:
