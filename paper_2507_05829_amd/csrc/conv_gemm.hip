@@ -394,9 +394,9 @@ __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(2)
 //  - The input is split once per workgroup, on its way from memory through registers to LDS: stages of 32
 //    elements a row, loaded four stages ahead; a row takes 13 16-byte slots, an odd number, so that 16 neighbouring rows'
 //    reads touch every bank once. The weights are split when the plan is made and come straight from memory in
-//    operand order, two stages ahead; no two wavefronts load the same ones, since the vector cache hands a
-//    compute unit 30 bytes a cycle and that is what bounds the loop (32 KB a stage against 768 cycles of matrix
-//    instructions a SIMD; with 2 x 2 instead of 1 x 4 wavefronts 870 instead of 757 us on 8192 x 1024 -> 4096 -> 1024).
+//    operand order, two stages ahead; no two wavefronts load the same ones: a stage's 32 KB take the
+//    vector cache 550 cycles (60 bytes a cycle) beside 768 of matrix instructions a SIMD, of the 1 100 it lasts (with 2 x 2 instead
+//    of 1 x 4 wavefronts 870 instead of 757 us on 8192 x 1024 -> 4096 -> 1024).
 //  - Half of the wavefronts take the first 16 elements of every stage, half the others: a tile is done in half
 //    the time where there are few of them, and the sums are added at the end through LDS.
 //  - A stage's fragments are read from LDS during the stage before it, the next but one stage's input is split and
@@ -626,18 +626,19 @@ bool gemm_shape(const OpLaunch& L) {
   return (size_t)L.x.n * L.x.rows * L.x.w * L.x.c * esz < ((size_t)1 << 31);
 }
 
-// The tile of a launch over the bands of a group, or bm == 0 where there is too little of it for these
-// tiles and the mid-size kernels, which split the reduction over the wavefronts, are faster.
-// Measured, in us before -> after: bf16 8192 x 1024 -> 4096 (512 tiles of 256 x 256) 94 -> 76, 8192 x 4096 ->
-// 1024 (128 of them) 88 -> 93 alone but 1 396 -> 1 059 for both layers on four streams, since only the
-// 256-wide tile asks the L2s for little enough while other launches run beside it; 5422 x 984 -> 1040
-// (215 tiles of 128 x 256) 31 -> 24; 4096 x 4096 -> 1024 (512 of 128 x 64) 89 -> 43, against 53 with 128 tiles
-// of 128 x 256; 1000 x 2048 -> 512 (64 of 128 x 64) 11 there, 16 here. fp32 3001 x 512 -> 2048 (1 504 tiles of
-// 64 x 64) 85 -> 64 and 2048 -> 512 (376) 87 -> 78; 1500 x 1024 -> 256 (96) 18 there, 23 here; 8000 x 1000 -> 3000
-// (1 512 tiles of 128 x 128) 479 -> 432, against 455 with 64 x 64.
 // Workgroups of a launch of 256 x 256 tiles: one per compute unit, each of which walks over its share of the tiles (and, the
 // number being a multiple of the XCDs, over tiles of the XCD it runs on).
 constexpr long kWalkers = 256;
+
+// The tile of a launch over the bands of a group, or bm == 0 where there is too little of it for these
+// tiles and the mid-size kernels, which split the reduction over the wavefronts, are faster.
+// Measured, in us before -> after: bf16 8192 x 1024 -> 4096 (512 tiles of 256 x 256) 94 -> 76 (68 walking), 8192 x 4096 ->
+// 1024 (128 of them) 88 -> 93 alone but 1 396 -> 1 059 for both layers on four streams, since only the
+// 256-wide tile asks the L2s for little enough while other launches run beside it; 5422 x 984 -> 1040
+// (215 tiles of 128 x 256) 31 -> 24; 4096 x 4096 -> 1024 (512 of 128 x 64) 89 -> 43, against 53 with 128 tiles
+// of 128 x 256; 1000 x 2048 -> 512 (64 of 128 x 64) 11 there, 16 here. fp32 on its own instructions (short reductions, and layers that have
+// no parts) 3001 x 512 -> 2048 (1 504 tiles of 64 x 64) 85 -> 64 and 2048 -> 512 (376) 87 -> 78; 1500 x 1024 -> 256 (96) 18 there, 23 here; 8000 x 1000 -> 3000
+// (1 512 tiles of 128 x 128) 479 -> 432, against 455 with 64 x 64.
 struct GemmChoice { int bm = 0, bn = 0; bool split = false; };
 constexpr long kBigTiles = 128;        // 256 x 256, bf16
 constexpr long kWideTiles = 192;       // 128 x 256, bf16
@@ -646,7 +647,7 @@ constexpr long kF32BigTiles = 1024;    // 128 x 128, fp32
 constexpr long kF32Tiles = 320;        // 64 x 64, fp32
 // 64 x 128, fp32 on the bf16 matrix cores. Before -> here, us a launch: 3001 x 512 -> 2048 (752 tiles) 64 -> 46, 2048 -> 512 (188)
 // 78 -> 47, 1500 x 1024 -> 512 (96) 26.2 -> 25.4, 600 x 512 -> 2048 (160) 22.6 -> 17.1; one stage after the other they
-// take 0.55 us a stage whatever runs beside them (24 KB of weights come to a compute unit at 30 bytes a cycle), so
+// take 0.55 us a stage whatever runs beside them, so
 // that few tiles are slower alone: 256 x 512 -> 2048 (64) 11.5 -> 14.8, 600 x 2048 -> 512 (40) 33 -> 40; but they
 // leave the chip to other launches: 1000 x 512 -> 2048 -> 512 (256 and 64) 46 -> 28 a call with calls in flight,
 // 76 -> 78 alone. Short reductions have nothing to gain: 3001 x 128 -> 256 7.0 -> 8.9.

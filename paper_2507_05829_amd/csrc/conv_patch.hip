@@ -1,8 +1,8 @@
 // Dense 3 x 3 convolution on a row interval, the LDS-staged kernel in its patch form.
 //
 // conv_lds_kernel of conv_igemm.hip fetches every tap of every pixel of its tile: nine times the
-// input under a 3 x 3 filter, through a load path that hands a compute unit about 30 bytes per
-// clock, and that rate is what bounds it. Here a workgroup owns a rectangle of output pixels x BN
+// input under a 3 x 3 filter, and what the L2s and the load path deliver of that (16 to 29 bytes per
+// clock and compute unit observed) is what bounds it. Here a workgroup owns a rectangle of output pixels x BN
 // channels and fetches the input pixels under that rectangle once per 128 bytes of channels (a
 // "patch": 180 pixels for 8 x 16 outputs, 1.4 x the outputs instead of 9 x); all nine taps are then
 // read from LDS at offsets from each other. The filter is not staged at all: it comes straight
@@ -13,7 +13,7 @@
 //    bytes of every pixel) and each accumulates the whole tile, so that no filter byte is loaded
 //    twice by a workgroup and no barrier is needed between taps: one per 128 bytes of channels,
 //    where the next patch, fetched meanwhile, takes over. Their partial tiles are added through
-//    LDS in wavefront order.
+//    LDS in wavefront order. (Tiles of 128 x 64: halves instead of quarters, see patch_wide_body.)
 //  - A pixel of the patch takes 144 bytes of LDS: with an odd number of 16-byte slots per pixel the
 //    16 lanes that read a slot of 16 neighbouring pixels at a time touch every bank once, and a tap is
 //    a constant number of bytes away from another. (global -> LDS loads fill consecutive slots, so
@@ -545,11 +545,11 @@ __device__ __forceinline__ void patch_wide_body(const PatchParams& p, const int 
 // The fp32 form: products on the bf16 matrix cores (conv_gemm.hip says how, and how precise). A pixel of the patch is
 // split into its three bf16 parts on the way from memory through registers to LDS, 208 bytes for 32 channels
 // (an odd number of 16-byte slots again); the filter comes from memory as it is, a patch ahead, and every wavefront splits
-// what it multiplies: parts made beforehand are 6 bytes a weight instead of 4, and the vector cache's 30 bytes a cycle were
-// what bounded that (133 against 128 us a chain of the fp32 backbone). Of the 18 steps of 16 channels that a patch has per
+// what it multiplies: parts made beforehand are 6 bytes a weight instead of 4 and a third load a tap, which was
+// slower (133 against 128 us a chain of the fp32 backbone). Of the 18 steps of 16 channels that a patch has per
 // pixel, wavefronts 0 and 2 take the first 16 channels and 1 and 3 the second, 0 and 1 five taps and 2 and 3 four of an
 // even patch, the other way round of an odd one. A patch is 864 TP cycles of matrix instructions (2 304 TP on the fp32
-// ones), 1 150 + 150 TP of vector instructions and 1 600 of loads, shared by the two or three workgroups of a compute unit;
+// ones), 1 150 + 150 TP of vector instructions and about 800 of loads (47 KB at the vector cache's 60 bytes a cycle), shared by the two or three workgroups of a compute unit;
 // alone it takes 2 500 (TP = 1) or 3 400.
 template <int TP, int NI, bool POOL, int S>
 __device__ __forceinline__ void patch_split_body(const PatchParams& p, const int bx, const int gx) {
