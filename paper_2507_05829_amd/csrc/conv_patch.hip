@@ -786,6 +786,10 @@ bool patch_shape(const OpLaunch& L) {
 // 128 x 64 tiles and 9.5 with 64 x 32, 256 -> 256 on 6 400 12.9 and 14.5, on 3 100 11.6 and 8.6), and no
 // launch is faster than one tile from beginning to end (`first` + `alone` per chunk: 512 -> 512
 // channels on 196 pixels 5.6 us with 32 x 32 tiles, 6.5 with 64 x 32, 15.6 with 128 x 64, 16.1 before).
+// Pooled, the 128 x 64 tile has to be 15 % ahead: the fit does not know what follows the sums there (64 -> 64 channels
+// on 40 300 pixels 9.0 us against 7.7 with 64 x 32, 128 -> 128 on 10 100 7.5 against 6.7). Without pooling it leaves other
+// launches more of the chip than the smaller tiles, also where those are faster alone (with such a margin there, too, the 720p
+// chain's 16 bands took 157 us instead of 154 with calls in flight).
 struct PatchChoice { int bm = 0, bn = 0; };
 struct PatchCost { int bm, bn; double chunk, rest, alone, first; };
 constexpr PatchCost kBf16Costs[] = {
@@ -838,7 +842,7 @@ PatchChoice choose_patch(const OpLaunch* convs, const OpLaunch* pools, int n) {
     const long t = tiles(c.bm, c.bn);
     if (t == 0) return;
     const double share = (double)t / kPatchUnits;
-    const double cost = std::max(share * (chunks * c.chunk + c.rest) + c.first / 2, chunks * c.alone + c.first);
+    const double cost = std::max(share * (chunks * c.chunk + c.rest) + c.first / 2, chunks * c.alone + c.first) * (pools && c.bm == 128 ? 1.15 : 1);
     if (!best.bm || cost < best_cost) { best = {c.bm, c.bn}; best_cost = cost; }
   };
   if (bf) for (const PatchCost& c : kBf16Costs) weigh(c);
