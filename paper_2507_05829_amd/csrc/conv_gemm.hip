@@ -44,7 +44,7 @@ struct GemmParams {
   int r_row0, r_rows;
   int sh, sw, ph, pw, act, k_pad;
   int out_lo, R, N, M;               // M = N * R * W_out
-  int mx, ny;                        // tiles of a launch of one band
+  int mx, ny;                        // tiles of a launch that walks over them, else 0
   FastDiv by_w, by_r, by_group;
 };
 static_assert(sizeof(Batch<GemmParams>) <= 4096, "the parameters of all bands of a launch travel as kernel arguments");
@@ -112,7 +112,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmParams& p, unsigned char
   }
 }
 
-// The same from registers, without LDS: a lane holds channels 8 g + 4 half + {0..3} of pixel lane mod 32 of a 32 x 32
+// The same from registers, without LDS, residual or second destination: a lane holds channels 8 g + 4 half + {0..3} of pixel lane mod 32 of a 32 x 32
 // tile; exchanges between the lane halves and between rows of 16 lanes make each store write 64 consecutive bytes of
 // 16 pixels. (As fast as the form above within 2 %; two stores of every lane per 32 x 32 tile where all of it lies inside.)
 template <typename T, int TM, int TN>
@@ -122,18 +122,17 @@ __device__ __forceinline__ void gemm_store(const GemmParams& p, const f32x16 (&a
   const int half = lane >> 5;
   const int piece = half + ((lane >> 4) & 1) * 2;          // of the four of a store's 64 bytes
   const Clamp cl = make_clamp(p.act);
-  auto pixel = [&](int m, int rows, int row0) __attribute__((always_inline)) {   // offset of a pixel's first channel
+  auto pixel = [&](int m) __attribute__((always_inline)) {   // offset of a pixel's first channel
     const int mm = m < p.M ? m : 0;
     const int q = fastdiv(mm, p.by_w), ow = mm - q * p.W_out;
     const int n = fastdiv(q, p.by_r), oh = p.out_lo + q - n * p.R;
-    return ((size_t)(n * rows + oh - row0) * p.W_out + ow) * p.C_out;
+    return ((size_t)(n * p.y_rows + oh - p.y_row0) * p.W_out + ow) * p.C_out;
   };
 #pragma unroll
   for (int tm = 0; tm < TM; ++tm) {
     const int m = m_first + tm * 32 + (lane & 15);
-    const size_t at[2] = {pixel(m, p.y_rows, p.y_row0), pixel(m + 16, p.y_rows, p.y_row0)};
+    const size_t at[2] = {pixel(m), pixel(m + 16)};
     const bool live[2] = {m < p.M, m + 16 < p.M};
-    const size_t ra = p.res ? pixel(m_first + tm * 32 + (lane & 31), p.r_rows, p.r_row0) : 0;
 #pragma unroll
     for (int tn = 0; tn < TN; ++tn) {
       const int co = co_first + tn * 32;
@@ -143,15 +142,8 @@ __device__ __forceinline__ void gemm_store(const GemmParams& p, const f32x16 (&a
         alignas(16) __bf16 b[8];
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-          const int c = co + (g + h) * 8 + half * 4;
           f32x4 v = f32x4{acc[tn][tm][(g + h) * 4], acc[tn][tm][(g + h) * 4 + 1], acc[tn][tm][(g + h) * 4 + 2], acc[tn][tm][(g + h) * 4 + 3]};
           v += bias[tn][g + h];
-          if (p.res && c < p.C_out) {
-            alignas(8) T r[4];
-            *(uint2*)r = *(const uint2*)((const T*)p.res + ra + c);
-#pragma unroll
-            for (int k = 0; k < 4; ++k) v[k] += to_f32(r[k]);
-          }
 #pragma unroll
           for (int k = 0; k < 4; ++k) b[h * 4 + k] = from_f32<T>(clamp_act(v[k], cl));
         }
@@ -169,12 +161,17 @@ __device__ __forceinline__ void gemm_store(const GemmParams& p, const f32x16 (&a
       const int c = co + piece * 8;
 #pragma unroll
       for (int h = 0; h < 2; ++h)
-        if (live[h] & (c < p.C_out)) {
-          *(u32x4*)((T*)p.y + at[h] + c) = o[h];
-          if (p.y2) *(u32x4*)((T*)p.y2 + at[h] + c) = o[h];
-        }
+        if (live[h] & (c < p.C_out)) *(u32x4*)((T*)p.y + at[h] + c) = o[h];
     }
   }
+}
+
+// LDS of a workgroup: the stages, later the staged output tiles.
+template <int BM, int BN, int WM, int WN, int NST>
+constexpr int gemm_smem() {
+  constexpr int stages = NST * (BM + BN) * 128, out = WM * WN * 32 * gemm_pitch(BN / (32 * WN)) * 4;
+  static_assert(stages <= 160 * 1024 && out <= 160 * 1024, "LDS");
+  return stages > out ? stages : out;
 }
 
 // WALK: the workgroup takes tiles launch, launch + step, ... of mx * ny (else the first of them only). Its loop needs all the
@@ -184,16 +181,13 @@ __device__ __forceinline__ void gemm_store(const GemmParams& p, const f32x16 (&a
 // 1024 -> 4096 609 -> 570, 4096 -> 1024 507 -> 498; 40 000 x 816 -> 2552 225 -> 201; 16 384 x 512 -> 2048 51 -> 43; 30 000 x
 // 256 -> 1024 38 -> 29.
 template <typename T, int BM, int BN, int WM, int WN, int NST, bool WALK>
-__device__ __forceinline__ void gemm_body(const GemmParams& p, int launch, const int step, const int mx, const int ny) {
+__device__ __forceinline__ void gemm_body(const GemmParams& p, unsigned char* const smem, int launch, const int step, const int mx, const int ny) {
   constexpr int KE = 16 / (int)sizeof(T);   // elements per 16-byte chunk
   constexpr int NW = WM * WN;
   constexpr int TM = BM / (32 * WM), TN = BN / (32 * WN);
   constexpr int A_LD = BM / (8 * NW), B_LD = BN / (8 * NW), LPS = A_LD + B_LD;   // load instructions per wavefront and stage
   constexpr int A_BYTES = BM * 128, STAGE = (BM + BN) * 128;
   static_assert(A_LD >= 1 && B_LD >= 1 && (NST - 2) * LPS < 64 && NST >= 2, "tile shape");
-  constexpr int SMEM = NST * STAGE > NW * 32 * gemm_pitch(TN) * 4 ? NST * STAGE : NW * 32 * gemm_pitch(TN) * 4;
-  static_assert(SMEM <= 160 * 1024, "LDS");
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[SMEM];
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -357,7 +351,7 @@ __device__ __forceinline__ void gemm_body(const GemmParams& p, int launch, const
         for (int g = 0; g < 4; ++g) asm volatile("" : "+v"(bias[t][g]));
       launch += step;
       const bool more = launch < mx * ny;
-      behind_stores = !p.y2 && !p.res && m0 + BM <= p.M && co0 + BN <= p.C_out;
+      behind_stores = m0 + BM <= p.M && co0 + BN <= p.C_out;
       if (more) {
         barrier();   // (no wavefront reads the last stages any more)
         set_tile(launch);
@@ -372,14 +366,18 @@ __device__ __forceinline__ void gemm_body(const GemmParams& p, int launch, const
 // (The tiles that leave room for one workgroup per compute unit only are walked over.)
 template <typename T, int BM, int BN, int WM, int WN, int NST>
 __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(2))) void conv_gemm_kernel(const GemmParams p) {
-  if constexpr (BM == 256) gemm_body<T, BM, BN, WM, WN, NST, true>(p, blockIdx.x, gridDim.x, p.mx, p.ny);
-  else gemm_body<T, BM, BN, WM, WN, NST, false>(p, blockIdx.x + gridDim.x * blockIdx.y, 0, gridDim.x, gridDim.y);
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[gemm_smem<BM, BN, WM, WN, NST>()];
+  if constexpr (BM == 256) {
+    if (p.mx) return gemm_body<T, BM, BN, WM, WN, NST, true>(p, smem, blockIdx.x, gridDim.x, p.mx, p.ny);
+  }
+  gemm_body<T, BM, BN, WM, WN, NST, false>(p, smem, blockIdx.x + gridDim.x * blockIdx.y, 0, gridDim.x, gridDim.y);
 }
 // The same for several bands of one layer in one grid (band b owns blocks first[b] .. first[b + 1] of x).
 template <typename T, int BM, int BN, int WM, int WN, int NST>
 __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(2))) void conv_gemm_kernel_bands(const Batch<GemmParams> t) {
   const int b = batch_find(t, blockIdx.x), mx = t.first[b + 1] - t.first[b];
-  gemm_body<T, BM, BN, WM, WN, NST, false>(t.p[b], (int)blockIdx.x - t.first[b] + mx * (int)blockIdx.y, 0, mx, gridDim.y);
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[gemm_smem<BM, BN, WM, WN, NST>()];
+  gemm_body<T, BM, BN, WM, WN, NST, false>(t.p[b], smem, (int)blockIdx.x - t.first[b] + mx * (int)blockIdx.y, 0, mx, gridDim.y);
 }
 
 // fp32 products on the bf16 matrix cores, which are 16 times as fast as the fp32 ones. A value is the sum of
@@ -674,6 +672,11 @@ GemmChoice choose_gemm(const OpLaunch* Ls, int n) {
   return tiles(64, 64) >= kF32Tiles ? GemmChoice{64, 64} : GemmChoice{};
 }
 
+// Whether a launch of 256 x 256 tiles walks. Not with a residual: its loads would wait for the next tile's, which are older (17 497 x
+// 504 -> 888 behind 888 -> 504, chains in flight: 53.5 us a call if both walk, 47.1 if the first does, 49.0 if none). Nor with a second destination, of
+// the size that has one a launch has no second round.
+bool walks(const GemmParams& p) { return !p.res && !p.y2; }
+
 // single, bands: a kernel of BM x BN tiles and THREADS threads, for one band and for several
 template <int BM, int BN, int THREADS>
 hipError_t launch_tile(void (*single)(const GemmParams), void (*bands)(const Batch<GemmParams>), const OpLaunch* Ls, int n, hipStream_t s,
@@ -691,7 +694,7 @@ hipError_t launch_tile(void (*single)(const GemmParams), void (*bands)(const Bat
     ++m;
   }
   if (m == 0) return hipSuccess;
-  if (BM == 256 && m == 1) {
+  if (BM == 256 && m == 1 && walks(ps[0])) {
     ps[0].mx = (int)gx[0]; ps[0].ny = (int)gy;
     const long tiles = (long)gx[0] * gy;
     return launch_kernel(single, dim3((unsigned)std::min(tiles, kWalkers)), dim3(THREADS), s, ev, ps[0]);
