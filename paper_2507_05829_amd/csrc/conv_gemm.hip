@@ -544,7 +544,7 @@ __device__ __forceinline__ void gemm_split_body(const GemmParams& p, const int b
         for (int g = 0; g < 4; ++g) {
           const f32x4 v = at[(b * 4 + g) * 64];
 #pragma unroll
-          for (int i = 0; i < 4; ++i) acc[a][b][g * 4 + i] += v[i];
+          for (int i = 0; i < 4; ++i) acc[a][b][g * 4 + i] = (acc[a][b][g * 4 + i] + v[i]) * kSplitUnscale;
         }
       }
     }
@@ -712,7 +712,10 @@ hipError_t launch_split(const OpLaunch* Ls, int n, hipStream_t s, KernelEvents* 
 
 }  // namespace
 
-bool split_shape(int c_in, int kh, int kw) { return kh == 1 && kw == 1 && c_in >= kSplitMinK; }
+bool split_shape(int c_in, int kh, int kw, int sh, int sw, int dilation) {
+  if (kh == 1 && kw == 1) return c_in >= kSplitMinK;
+  return kh == 3 && kw == 3 && c_in % 32 == 0 && sh == sw && sh <= 2 && dilation == 1;   // (the patch form's, see patch_shape)
+}
 hipError_t launch_split_weights(const void* w, int c_out_pad, int k_pad, void* w3, hipStream_t stream) {
   const unsigned pieces = (unsigned)((size_t)c_out_pad * k_pad / 8);
   return launch_kernel(split_weights_kernel, dim3((pieces + 255) / 256), dim3(256), stream, nullptr, (const float*)w, k_pad, pieces, (u32x4*)w3);

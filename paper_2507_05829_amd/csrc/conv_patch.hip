@@ -544,13 +544,15 @@ __device__ __forceinline__ void patch_wide_body(const PatchParams& p, const int 
 
 // The fp32 form: products on the bf16 matrix cores (conv_gemm.hip says how, and how precise). A pixel of the patch is
 // split into its three bf16 parts on the way from memory through registers to LDS, 208 bytes for 32 channels
-// (an odd number of 16-byte slots again); the filter comes from memory as it is, a patch ahead, and every wavefront splits
-// what it multiplies: parts made beforehand are 6 bytes a weight instead of 4 and a third load a tap, which was
-// slower (133 against 128 us a chain of the fp32 backbone). Of the 18 steps of 16 channels that a patch has per
-// pixel, wavefronts 0 and 2 take the first 16 channels and 1 and 3 the second, 0 and 1 five taps and 2 and 3 four of an
-// even patch, the other way round of an odd one. A patch is 864 TP cycles of matrix instructions (2 304 TP on the fp32
-// ones), 1 150 + 150 TP of vector instructions and about 800 of loads (47 KB at the vector cache's 60 bytes a cycle), shared by the two or three workgroups of a compute unit;
-// alone it takes 2 500 (TP = 1) or 3 400.
+// (an odd number of 16-byte slots again); the filter's parts are made with the plan and loaded a patch ahead. Of the 18 steps of 16
+// channels that a patch has per pixel, wavefronts 0 and 2 take the first 16 channels and 1 and 3 the second, 0 and 1 five taps
+// and 2 and 3 four of an even patch, the other way round of an odd one. A patch is 864 TP cycles of matrix instructions
+// (2 304 TP on the fp32 ones), 300 to 700 of vector instructions and about 1 100 of loads (65 KB at the vector
+// cache's 60 bytes a cycle), shared by the two or three workgroups of a compute unit; alone it takes 1 800 (TP = 1) or 2 900.
+// Wavefronts that split the filter themselves load 4 bytes a weight instead of 6, but their vector instructions
+// (1 150 + 150 TP cycles, without scaling) bounded it: us a launch, then and now, 128 -> 128 channels on 784 pixels 8.1 and 6.6,
+// 256 -> 256 on 400 12.7 and 9.6, on 1 600 18.2 and 16.0; the fp32 backbone in flight 121.7 and 119.2, with shared rows 55.6 and 55.2,
+// alone 154 and 145.
 template <int TP, int NI, bool POOL, int S>
 __device__ __forceinline__ void patch_split_body(const PatchParams& p, const int bx, const int gx) {
   constexpr int PB = 208, BUF = NI * 32 * PB;
@@ -589,25 +591,30 @@ __device__ __forceinline__ void patch_split_body(const PatchParams& p, const int
     for (int i = 0; i < NI; ++i)
       d[i] = __builtin_amdgcn_raw_buffer_load_b128(xbuf, (int)(c < chunks ? src[i] : kOutside), c * 128, 0);
   };
-  unsigned char* const put = smem + (threadIdx.x >> 3) * PB + (k4 >> 2) * 96 + (k4 & 1) * 16 + (k4 >> 1 & 1) * 8;
+  unsigned char* const put = smem + (threadIdx.x >> 3) * PB + (k4 >> 2) * 96 + (k4 >> 1 & 1) * 16 + (k4 & 1) * 8;
   auto store = [&](int buf, int i, u32x4 (&d)[NI]) __attribute__((always_inline)) {
     uint2 parts[3];
     split_bf16(__builtin_bit_cast(f32x4, d[i]), parts);
 #pragma unroll
     for (int k = 0; k < 3; ++k) *(uint2*)(put + buf * BUF + i * 32 * PB + k * 32) = parts[k];
   };
-  // ---- the filter: five taps (four, and one of them twice) of a patch, two pieces of eight channels' fp32 values each
-  const int k_steps = second ? p.sib.k_steps : p.k_steps;
-  const u32x4* const wd = (const u32x4*)(second ? p.sib.wd : p.wd) + (size_t)tile.tile_n * k_steps * 64 + lane;
-  const int tap_stride = p.C_in / 8 * 64;
+  // ---- the filter: five taps (four, and one of them twice) of a patch, three parts of 16 channels each, and the tap that
+  // is being multiplied (so that its registers are free for the next patch's filter a tap earlier)
+  const u32x4* const w3 = (const u32x4*)p.w3 + (size_t)tile.tile_n * (p.k_steps / 2) * 192 + lane;
   auto first_tap = [&](int c) { return (wave >> 1 ^ c) & 1 ? 5 : 0; };
-  u32x4 w[5][2];
+  u32x4 w[5][3], tap[2][1][3];
   auto fetch_tap = [&](int c, int j) __attribute__((always_inline)) {
     const int cc = min(c, chunks - 1);
-    const u32x4* const from = wd + (size_t)(min(first_tap(cc) + j, 8) * tap_stride + (cc * 4 + 2 * step) * 64);
+    const u32x4* const from = w3 + (size_t)((min(first_tap(cc) + j, 8) * (p.C_in / 16) + cc * 2 + step) * 192);
 #pragma unroll
-    for (int k = 0; k < 2; ++k) w[j][k] = from[k * 64];
+    for (int k = 0; k < 3; ++k) w[j][k] = from[k * 64];
   };
+  auto take_tap = [&](int j) __attribute__((always_inline)) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) tap[j & 1][0][k] = w[j][k];
+  };
+  // ... and the fp32 values, 32 channels' pieces of four elements a step
+  const u32x4* const wd = (const u32x4*)(second ? p.sib.wd : p.wd) + (size_t)tile.tile_n * (second ? p.sib.k_steps : p.k_steps) * 64;
 
   fetch_patch(0, raw[0]);
   if (!second) {
@@ -643,7 +650,7 @@ __device__ __forceinline__ void patch_split_body(const PatchParams& p, const int
 #pragma unroll
   for (int i = 0; i < NI; ++i) store(0, i, raw[0]);
   fetch_patch(2, raw[0]);
-  u32x4 x[2][TP][3], parts[2][1][3];
+  u32x4 x[2][TP][3];
   auto barrier = [&]() __attribute__((always_inline)) {   // (for LDS only: loads from memory stay in flight)
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
@@ -651,17 +658,16 @@ __device__ __forceinline__ void patch_split_body(const PatchParams& p, const int
   };
   auto multiply = [&](int j) __attribute__((always_inline)) {
 #pragma unroll
-    for (int e = 0; e < 6; ++e) mma_split_part<1, TP>(parts[j & 1], x[j & 1], acc, low, e);
+    for (int e = 0; e < 6; ++e) mma_split_part<1, TP>(tap[j & 1], x[j & 1], acc, low, e);
   };
   // One patch (even ones in the first half of LDS, set 0). While a tap is multiplied, the next one's pixels come out of
-  // LDS, its filter is split, and the next patch is split and stored into the memory that every wavefront was
-  // done with at the barrier: vector instructions between the matrix instructions, which keep their pipe busy for
-  // 32 cycles each.
+  // LDS, and the next patch is split and stored into the memory that every wavefront was done with at the barrier: vector
+  // instructions between the matrix instructions, which keep their pipe busy for 32 cycles each.
   auto run_patch = [&](int c, int set) __attribute__((always_inline)) {
     barrier();
     const int buf = set * BUF, t0 = first_tap(c);
     read_tap(buf, t0, x[0]);
-    split_bf16(w[0][0], w[0][1], parts[0][0]);
+    take_tap(0);
     fetch_tap(c + 1, 0);
 #pragma unroll
     for (int j = 0; j < 5; ++j) {
@@ -669,7 +675,7 @@ __device__ __forceinline__ void patch_split_body(const PatchParams& p, const int
       if (j < 4) {
         read_tap(buf, min(t0 + j + 1, 8), x[(j + 1) & 1]);
         multiply(j);
-        split_bf16(w[j + 1][0], w[j + 1][1], parts[(j + 1) & 1][0]);
+        take_tap(j + 1);
         fetch_tap(c + 1, j + 1);
       }
 #pragma unroll
@@ -686,11 +692,10 @@ __device__ __forceinline__ void patch_split_body(const PatchParams& p, const int
     __builtin_amdgcn_sched_barrier(0);
     if (t0 == 0) multiply(4);
   };
-  if (second) {   // one tap, the centre
+  if (second) {   // one tap, the centre, of weights that have no parts: a lane's eight channels are half a step
     for (int c = 0; c < chunks; ++c) {
-#pragma unroll
-      for (int k = 0; k < 2; ++k) w[0][k] = wd[(size_t)(c * 4 + 2 * step + k) * 64];
-      split_bf16(w[0][0], w[0][1], parts[0][0]);
+      const u32x4* const from = wd + (size_t)(c * 4 + 2 * step + half) * 64 + px;
+      split_bf16(from[0], from[32], tap[0][0]);
       barrier();
       if (wave < 2) {
         read_tap((c & 1) * BUF, 4, x[0]);
@@ -709,7 +714,7 @@ __device__ __forceinline__ void patch_split_body(const PatchParams& p, const int
     if (c < chunks) run_patch(c, 0);
   }
 #pragma unroll
-  for (int f = 0; f < TP; ++f) acc[0][f] += low[0][f];
+  for (int f = 0; f < TP; ++f) acc[0][f] = (acc[0][f] + low[0][f]) * kSplitUnscale;
 
   // fp32 instructions, on operands straight from memory: the wavefront's fragment with all its channels
   auto again = [&](int f, f32x4 (&sum)[TP]) __attribute__((always_inline)) {
@@ -722,7 +727,7 @@ __device__ __forceinline__ void patch_split_body(const PatchParams& p, const int
       const unsigned from = input(ih0 + r * S + t / 3, iw0 + c * S + t % 3);
       for (int s = 0; s < p.C_in / 8; ++s) {
         const u32x4 xv = __builtin_amdgcn_raw_buffer_load_b128(xbuf, (int)(from == kOutside ? kOutside : from + s * 32 + half * 16), 0, 0);
-        mma<float>(wd[(size_t)((second ? 0 : t * (p.C_in / 8)) + s) * 64], xv, all);
+        mma<float>(wd[(size_t)((second ? 0 : t * (p.C_in / 8)) + s) * 64 + lane], xv, all);
       }
     }
 #pragma unroll
@@ -774,7 +779,7 @@ bool patch_shape(const OpLaunch& L) {
   const int esz = bf ? 2 : 4, ke = 16 / esz;
   if (L.op != LOP_CONV2D || !L.wd || L.kh != 3 || L.kw != 3 || L.dh != 1 || L.dw != 1) return false;
   if (L.sh != L.sw || (L.sh != 1 && L.sh != 2)) return false;
-  if (L.x.c * esz % 128 != 0 || L.y.c % ke != 0) return false;
+  if (L.x.c * esz % 128 != 0 || L.y.c % ke != 0 || (!bf && !L.w3)) return false;
   return (size_t)L.x.n * L.x.rows * L.x.w * L.x.c * esz < ((size_t)1 << 31);
 }
 
@@ -794,23 +799,25 @@ struct PatchChoice { int bm = 0, bn = 0; };
 struct PatchCost { int bm, bn; double chunk, rest, alone, first; };
 constexpr PatchCost kBf16Costs[] = {
     {128, 64, 5000, 3500, 3300, 6000}, {64, 32, 1860, 840, 1100, 3500}, {32, 32, 1200, 620, 750, 3000}};
-// fp32, fitted alike (chunk: 32 channels); 64 x 32 against 32 x 32 tiles: 64 -> 64 channels on 12 500 pixels 11.7 and 13.4 us,
-// on 3 100 7.4 and 6.1; 256 -> 256 on 1 600 18.9 and 20.5, on 784 17.0 and 14.1. On the fp32 instructions the
-// best of them were 14.0, 5.4, 23.9 and 14.1: what the bf16 ones save, one tile to a compute unit spends on instructions
-// (about 500 a wavefront and chunk), several share.
-constexpr PatchCost kF32Costs[] = {{64, 32, 5100, 3500, 3450, 4500}, {32, 32, 3400, 500, 2780, 2800}};
+// fp32, fitted alike (chunk: 32 channels); 64 x 32 against 32 x 32 tiles: 64 -> 64 channels on 25 600 pixels 19.3 and 22.0 us,
+// on 6 400 7.2 and 7.5, on 3 136 6.9 and 5.3; 256 -> 256 on 3 136 27.3 and 32.1, on 1 600 16.2 and 17.2, on 784 14.4 and 10.5.
+constexpr PatchCost kF32Costs[] = {{64, 32, 4150, 4600, 2900, 4700}, {32, 32, 2300, 2700, 1790, 3100}};
 constexpr int kPatchUnits = 256;
 // fp32 launches of fewer tiles are left to the kernels that cut the reduction finer (16 x 16 tiles, or
-// slices across workgroups). Alone the two are level at about 120 tiles (128 -> 128 channels on 784 pixels, 100 tiles: 8.2 us
-// here and there; 256 -> 256 on 400, 104: 12.9 and 11.1), with other launches beside them this one is ahead from
-// fewer on: the fp32 backbone with shared rows, three launches of 100 tiles, 58.5 us a chain, and 64.3 without.
+// slices across workgroups). At 100 tiles this one is ahead (128 -> 128 channels on 784 pixels: 8.2 us there, 6.6 here;
+// 256 -> 256 on 400, 104 tiles: 11.1 and 9.6), and alone it stays so down to about 50 (64 -> 64 on 784, 50 tiles: 7.6 and 5.2; 256 -> 256 on
+// 324, 88: 10.8 and 9.4; but 256 -> 512, stride 2, on 144, 80: 11.3 and 11.9); a line at 50 changes the fp32 backbone with
+// shared rows by nothing in flight (55.2 and 55.3 us) and alone (144).
 constexpr long kF32MinTiles = 100;
 // bf16: a handful of compute units cannot stream megabytes of filter (7 x 7 x 512 channels is 32 tiles: 5.6 us
 // here, 8.9 there)
 constexpr long kBf16MinTiles = 24;
 // Stride 2: a patch is four times the outputs, so a tile fetches nearly twice what the kernel that fetches taps does per
-// output (2.25 of them) and gains by waiting for them once instead of nine times. fp32 launches always do (there -> here,
-// us alone: 64 -> 128 channels on 3 136 pixels 11.6 -> 10.0, on 12 800 31.5 -> 30.1; 256 -> 512 on 1 568 62 -> 46). bf16
+// output (2.25 of them) and gains by waiting for them once instead of nine times. fp32 launches always take it (there -> here,
+// us alone: 64 -> 128 channels on 3 136 pixels 11.6 -> 9.1). On the fp32 instructions they
+// were faster alone where the reduction is short (64 -> 128 on 784 pixels 5.8 against 6.4, on 5 625 12.2 and 13.7; 128 -> 256 on
+// 784 8.8 and 8.7), but not with other launches beside them: the fp32 backbone in flight took 131 us instead of 119.6
+// with that layer on them, with shared rows 56.7 instead of 55.2 (142 instead of 145 alone). bf16
 // ones up to one tile per compute unit: beyond that they are ahead alone up to about four (128 -> 256 on 3 600 pixels, 904
 // tiles, 9.6 -> 8.9; on 6 400, 1 600 tiles, 12.3 -> 13.2), but not with other launches beside them (detector encoder with
 // shared rows, one launch of 904 tiles: 63.9 -> 64.9 us a chain).

@@ -11,11 +11,18 @@ namespace {
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 
+// Both operands are multiplied by 2^24 before they are split, and sums of products by 2^-48: exact, and the last bit of
+// every part of any fp32 value, subnormal ones included, is then a normal bf16 value (2^-149 becomes 2^-125). Unscaled, the third part of a
+// value below 2^-110 would fall under bf16's smallest step, then the second. Operands from 2^104 on and sums from 2^80 on
+// become infinite for it; a sum that is not finite is computed again on the fp32 instructions in any case.
+constexpr float kSplitScale = 0x1p24f, kSplitUnscale = 0x1p-48f;
 
-// v = high + middle + low, each rounded to nearest: the remainder of a rounding to 8 bits is exact in fp32, and
+// 2^24 v = high + middle + low, each rounded to nearest: the remainder of a rounding to 8 bits is exact in fp32, and
 // what is left for the third part has at most 8 bits. Two values at a time: one conversion rounds both, and the
 // halves of its result are the values to subtract.
 __device__ __forceinline__ void split_bf16(float a, float b, unsigned (&parts)[3]) {
+  a *= kSplitScale;
+  b *= kSplitScale;
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
     parts[k] = __builtin_bit_cast(unsigned, __builtin_convertvector(f32x2{a, b}, bf16x2));

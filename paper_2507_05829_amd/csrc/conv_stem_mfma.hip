@@ -417,7 +417,7 @@ __device__ __forceinline__ void stem_pool_split_body(const StemMfmaParams& p, co
     for (int e = 0; e < 6; ++e) mma_split_part<1, 1>(w, x, acc, low, e);
   }
   f32x16 sum[1];
-  sum[0] = acc[0][0] + low[0][0];
+  sum[0] = (acc[0][0] + low[0][0]) * kSplitUnscale;
   float odd = 0.f;   // NaN if a sum is not finite
 #pragma unroll
   for (int i = 0; i < 16; ++i) odd += sum[0][i] - sum[0][i];
@@ -539,6 +539,7 @@ void pack_parts(const unsigned char* src, int row_pitch, int c_out, unsigned cha
         if (e >= Stem7::KJ) continue;
         float v;
         std::memcpy(&v, src + ((size_t)co * row_pitch + (g / Stem7::G) * Stem7::KJ + e) * 4, 4);
+        v *= kSplitScale;
         for (int k = 0; k < 3; ++k) {
           unsigned u;
           std::memcpy(&u, &v, 4);

@@ -33,6 +33,7 @@ struct PatchParams {
   void* y2;         // second destination with y's layout, or nullptr
   const void* res;
   const void* wd;   // weights in MFMA operand order
+  const void* w3;   // fp32: the same as three bf16 parts
   const float* bias;
   int x_row0, x_rows, W, C_in;
   int y_row0, y_rows, W_out, C_out;  // of the tensor that is stored (POOL: the pooled one)
@@ -90,7 +91,7 @@ inline PatchParams make_patch(const OpLaunch& c, const OpLaunch* pool, int pixel
   const Slab& y = pool ? pool->y : c.y;
   const PatchWork w = patch_work(c, pool);
   const int ke = c.dtype == LOP_BF16 ? 8 : 4;
-  p.x = c.x.ptr; p.y = y.ptr; p.y2 = pool ? pool->y2 : c.y2; p.res = c.res.ptr; p.wd = c.wd; p.bias = c.bias;
+  p.x = c.x.ptr; p.y = y.ptr; p.y2 = pool ? pool->y2 : c.y2; p.res = c.res.ptr; p.wd = c.wd; p.w3 = c.w3; p.bias = c.bias;
   p.x_row0 = c.x.row0; p.x_rows = c.x.rows; p.W = c.x.w; p.C_in = c.x.c;
   p.y_row0 = y.row0; p.y_rows = y.rows; p.W_out = y.w; p.C_out = c.y.c;
   p.r_row0 = c.res.row0; p.r_rows = c.res.rows;

@@ -46,8 +46,8 @@ struct OpLaunch {
 // w[co][step*MK + half*KE ... + KE) of the first packing. A third one serves 16 x 16 tiles:
 // [c_out_pad / 16][k_pad / MK16][64 lanes] x 16 bytes, MK16 = 4 vectors, lane = quarter*16 +
 // (co % 16) holds w[co][step*MK16 + quarter*KE ... + KE).
-// fp32 layers whose reduction is long enough for the bf16 matrix cores (split_shape) get their weights as
-// sums of three bf16 values, too: [c_out_pad / 32][k_pad / 16][part][64 lanes] x 16 bytes, lane = half*32 +
+// fp32 layers whose products are made on the bf16 matrix cores (split_shape: 1 x 1 layers of long reductions, 3 x 3 layers
+// that the patch form takes) get their weights, times kSplitScale, as sums of three bf16 values, too: [c_out_pad / 32][k_pad / 16][part][64 lanes] x 16 bytes, lane = half*32 +
 // (co % 32) holds part of w[co][step*16 + half*8 ... + 8), directly behind the operand-order packing.
 // The row count is padded to the widest channel tile that can take the layer: 128, and 256 once
 // there are more than 128 channels (the 256-wide tile is never chosen below that), so the last
@@ -61,7 +61,7 @@ __host__ __device__ inline int conv_cout_pad(int c_out) {
 
 // Whether a dense fp32 conv that has the operand-order packing gets the one as three bf16 parts, and that packing,
 // from the first one on the device.
-bool split_shape(int c_in, int kh, int kw);
+bool split_shape(int c_in, int kh, int kw, int sh, int sw, int dilation);
 hipError_t launch_split_weights(const void* w, int c_out_pad, int k_pad, void* w3, hipStream_t stream);
 
 // Bytes of split-K scratch the dense conv launch needs (0: none).

@@ -1469,7 +1469,7 @@ int lop_plan(const lop_layer_t* layers, int n_layers, const lop_tensor_desc_t* i
     P->k_pad[l] = lop::conv_k_pad(d.c_in, d.kh, d.kw, in->dtype);
     P->has_wd[l] = d.c_in % ke == 0 && d.c_out % ke == 0;
     P->has_wd16[l] = P->has_wd[l] && P->k_pad[l] % (4 * ke) == 0;
-    P->has_w3[l] = in->dtype == LOP_F32 && P->has_wd[l] && lop::split_shape(d.c_in, d.kh, d.kw);
+    P->has_w3[l] = in->dtype == LOP_F32 && P->has_wd[l] && lop::split_shape(d.c_in, d.kh, d.kw, d.sh, d.sw, std::max(d.dh, d.dw));
     P->has_wstem[l] = lop::stem_shape_applies(d.c_in, d.c_out, d.kh, d.kw, d.sw, d.dh, d.dw,
                                               d.residual_from != LOP_NO_RESIDUAL);
   }

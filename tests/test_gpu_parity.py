@@ -1635,6 +1635,79 @@ def test_fp32_patch_form_precision(cfg):
         np.testing.assert_allclose(dev[large], odd[large], rtol=1e-5)
 
 
+def _parts_chain(kind):
+    """A chain whose products fp32 makes of bf16 parts, its kernel, the layer that shows it and the length of its reductions."""
+    if kind == "matrix":
+        chain = workloads.RowChain("parts", 1111, 260, "f32", 1)
+        return chain.add(1028, "none"), "conv_gemm_split_kernel<64, 128, 1, 4>", 0, 260
+    if kind == "first layer":
+        chain = workloads.Chain("parts", (1, 3, 57, 61), "f32", 1)
+        chain.add(workloads.CONV, 3, 64, 7, 2, 3, 1, "none")
+        chain.add(workloads.MAXPOOL, 64, 64, 3, 2, 1)
+        return chain, "conv_stem_pool_kernel<float, 1>", 1, 147
+    c_in, c_out, shape, s = {"stride 1": (96, 40, (61, 67), 1), "pooled": (32, 64, (77, 62), 1), "64 pixels": (128, 64, (113, 118), 1),
+                             "shortcut": (64, 128, (60, 64), 2)}[kind]
+    chain = workloads.Chain("parts", (1, c_in) + shape, "f32", 1)
+    chain.add(workloads.CONV, c_in, c_out, 3, s, 1, 1, "none")
+    if kind == "pooled":
+        chain.add(workloads.MAXPOOL, c_out, c_out, 2, 2, 0)
+    if kind == "shortcut":    # (in one launch with the first layer)
+        chain.add(workloads.CONV, c_in, c_out, 1, s, 0, 1, "none", input_from=workloads.CHAIN_INPUT)
+        chain.add(workloads.CONV, c_out, c_out, 3, 1, 1, 1, "none", input_from=0, residual_from=1)
+    tile = "64, 32" if kind == "64 pixels" else "32, 32"
+    return chain, f"conv_patch_kernel<float, {tile}, {'true' if kind == 'pooled' else 'false'}, {s}>", int(kind == "pooled"), 9 * c_in
+
+
+def _exact_in_64_bits(chain, t):
+    f = lambda a: torch.from_numpy(np.asarray(a, np.float64))
+    if hasattr(chain, "m"):
+        return (f(t.x) @ f(t.weights[0]).T).numpy()
+    outs = []
+    for l, L in enumerate(chain.layers):
+        x = f(t.x) if L.input_from < 0 else outs[L.input_from]
+        if L.has_weight:
+            y = torch.nn.functional.conv2d(x, f(t.weights[l]), None, L.s, L.p)
+        else:
+            y = torch.nn.functional.max_pool2d(x, L.k, L.s, L.p)
+        outs.append(y + outs[L.residual_from] if L.residual_from >= 0 else y)
+    return outs[-1].numpy()
+
+
+def _run_parts(chain, t, flags=0):
+    if hasattr(chain, "m"):
+        return _run_rows(chain, t, flags=flags)[0]
+    return run_gpu(chain, t, flags=flags)[0]
+
+
+@pytest.mark.parametrize("kind", ["matrix", "stride 1", "64 pixels", "pooled", "shortcut", "first layer"])
+def test_fp32_parts_over_the_whole_range(kind):
+    """fp32 products on the bf16 matrix cores keep the precision of fp32 for inputs and weights of any size, down to where
+    results are subnormal and up to where the fp32 instructions take over."""
+    chain, kernel, layer, k = _parts_chain(kind)
+    make = workloads.make_row_tensors if hasattr(chain, "m") else workloads.make_tensors
+    t = make(chain, zero_bias=True, seed=67)
+    plan = (lop.Plan.rowwise if hasattr(chain, "m") else lop.Plan)(chain, t, flags=lop.LOP_FLAG_BATCH_BANDS)
+    try:
+        assert plan.layer_kernel(0, layer)[0] == kernel, plan.layer_kernel(0, layer)
+    finally:
+        plan.destroy()
+    weights = [l for l, w in enumerate(t.weights) if w is not None and l < 2]   # (the shortcut's last layer stays as it is)
+    for x_by, w_by in ((0, 0), (-112, 0), (-122, 0), (0, -112), (0, -120), (-61, -62), (90, 0), (0, 101), (40, 45)):
+        scaled = [np.ldexp(w, w_by).astype(np.float32) if l in weights else w for l, w in enumerate(t.weights)]
+        ts = workloads.Tensors(np.ldexp(t.x, x_by).astype(np.float32), scaled, t.biases)
+        with np.errstate(over="ignore"):
+            want = _exact_in_64_bits(chain, ts)
+        got = _run_parts(chain, ts).astype(np.float64)
+        assert np.isfinite(want.astype(np.float32)).all()
+        # sums of at least k / 16 terms of 2^-24 each that grow like their square root (the fp32 instructions: k / 2), and what a
+        # subnormal result is rounded by
+        terms = k / 16 if x_by + w_by < 0 else k / 2
+        bound = 2 * np.sqrt(terms) * 2.0 ** -24 * np.linalg.norm(want) + 2.0 ** -149 * np.sqrt(want.size)
+        if kind == "shortcut":
+            bound *= 2     # two layers in a row
+        assert np.linalg.norm(got - want) <= bound, (x_by, w_by, np.linalg.norm(got - want) / np.linalg.norm(want))
+
+
 @pytest.mark.parametrize("cfg", [
     # dtype, c_in, c_out, shape(n,h,w): a stride-2 block's convolution and shortcut in one launch
     ("bf16", 64, 72, (1, 27, 45)),      # channels end inside a tile
