@@ -207,7 +207,8 @@ LOP_API int lop_run_band(lop_plan_t* plan, int band, const void* d_in, void* d_o
  * calls rotate over the lanes. Larger chains run band by band on the lanes, band b's copy
  * overlapping the kernels of the bands after it (Sec. IV-B). Either way the rows computed are
  * those of lop_run_band, which runs a single band, and the results agree with it up to the order
- * of the fp32 sums.
+ * of the fp32 sums. (A chain of row-wise operators of fewer than 2048 rows whose largest layer has fewer than
+ * 2^27 products, rows x k x n, runs band by band, and its results are those of lop_run_band bit for bit.)
  * compute_stream waits for all kernels (not for the copies of a chain that runs band by band:
  * those are complete after lop_synchronize). With compute_stream == NULL there is nothing to
  * order against: d_in must be complete when the call is made, nothing is joined, and the chains of

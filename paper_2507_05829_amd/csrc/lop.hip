@@ -407,11 +407,13 @@ size_t merged_workspace(lop_plan_t* P) {
 constexpr size_t kMergeMaxBytes = LOP_STATIC_SCRATCH_BYTES;
 constexpr size_t kLaneSlabsMax = (size_t)192 << 20;
 // A chain of row-wise operators has no halo, and callers that stream matrix rows run its bands one
-// by one: a chain of few products (rows x columns in x columns out of its largest layer) runs the bands' own
-// launches, so that its sums are those of lop_run_band in the same order. That is the only reason: merged it
-// is faster at every size (us a call with calls in flight, band by band -> merged; bf16 1024 -> 4096 -> 1024
-// columns in four bands: 256 rows 61 -> 20, 1 000 68 -> 32, 2 047 85 -> 58; fp32 512 -> 2048 -> 512: 1 000 rows
-// 70 -> 43).
+// by one: a chain of few rows and few products (rows x columns in x columns out of its largest layer) runs the bands' own
+// launches, so that its results are those of lop_run_band bit for bit, as lop.h says. That is the only reason: merged it
+// is faster at every size (us a call with calls in flight and alone, four bands band by band -> merged: bf16 256 rows x 256 -> 1024 -> 256
+// 24.8, 57 -> 8.3, 22; 1 000 x 256 -> 256 -> 256 25.6, 57 -> 8.3, 19; 2 000 x 128 -> 256 -> 128 25.4, 56 -> 8.0, 19; fp32 1 000 x 256 ->
+// 256 -> 256 25.6, 59 -> 7.6, 22), so chains of many rows merge whatever their products (3 000 x 128 -> 256 -> 128 in eight bands 48, 80
+// -> 8.1, 21) and those of many products whatever their rows (256 x 1024 -> 4096 -> 1024 61 -> 20).
+constexpr int kMergeMinRows = 2048;
 constexpr size_t kMergeMinProducts = (size_t)1 << 27;
 
 void size_scratch(lop_plan_t* P) {
@@ -494,7 +496,7 @@ void size_scratch(lop_plan_t* P) {
   }
   size_t products = 0;
   for (const lop::LayerInfo& L : t.layers) products = std::max(products, (size_t)n * L.h_out * L.d.c_in * L.d.c_out);
-  const bool few_rows = t.in.w == 1 && products < kMergeMinProducts;
+  const bool few_rows = t.in.w == 1 && n * t.in.h < kMergeMinRows && products < kMergeMinProducts;
   if ((P->flags & LOP_FLAG_PLAN_ONLY) || (few_rows && nb > 1)) return;
   const bool whole = t.disjoint();
   // Launches that stream memory (1 x 1 and depthwise layers by themselves) gain from being merged what launches cost, and

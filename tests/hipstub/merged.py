@@ -288,7 +288,28 @@ def timed_layer():
     return bad
 
 
-bad = {"copy_streams": copy_streams, "timed_layer": timed_layer, "grids": grids, "poison": poison, "order_of_streams": order_of_streams, "workspace": workspace, "wide_tiles": wide_tiles, "static_scratch": static_scratch}[check]()
+def matrix_rows():
+    """A chain of matrix products is one launch per layer from 2048 rows on, or from 2^27 products of its largest layer on; below
+    both its bands run one by one."""
+    bad = []
+    stub.hipstub_launches.restype = ctypes.c_long
+    for m, k, hidden, bands, merged in ((2048, 128, 256, 4, True), (3001, 128, 256, 8, True), (20000, 64, 64, 4, True), (256, 1024, 1024, 4, True),
+                                        (2047, 128, 256, 4, False), (257, 256, 1024, 3, False)):
+        for dtype in ("bf16", "f32"):
+            for flags in (0, lop.LOP_FLAG_REUSE):
+                chain = workloads.RowChain("rows", m, k, dtype, bands).add(hidden, "relu").add(k, "none", residual_from=-1)
+                weights = types.SimpleNamespace(weights=[np.zeros((L.n, L.k), np.float32) for L in chain.layers], biases=[None, None])
+                plan = lop.Plan.rowwise(chain, weights, flags=flags)
+                before = stub.hipstub_launches()
+                plan.run_chain(TENSOR, TENSOR)
+                count = stub.hipstub_launches() - before
+                plan.destroy()
+                if (count < 2 * bands) != merged:
+                    bad.append((m, k, hidden, bands, dtype, flags, count))
+    return bad
+
+
+bad = {"matrix_rows": matrix_rows, "copy_streams": copy_streams, "timed_layer": timed_layer, "grids": grids, "poison": poison, "order_of_streams": order_of_streams, "workspace": workspace, "wide_tiles": wide_tiles, "static_scratch": static_scratch}[check]()
 for b in bad:
     print("FAILED", b, flush=True)
 print("CHECK %s" % ("FAILED" if bad else "OK"), flush=True)
