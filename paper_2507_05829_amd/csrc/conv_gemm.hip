@@ -643,14 +643,21 @@ constexpr long kWideTiles = 192;       // 128 x 256, bf16
 constexpr long kNarrowTiles = 384;     // 128 x 64, bf16
 constexpr long kF32BigTiles = 1024;    // 128 x 128, fp32
 constexpr long kF32Tiles = 320;        // 64 x 64, fp32
-// 64 x 128, fp32 on the bf16 matrix cores. Before -> here, us a launch: 3001 x 512 -> 2048 (752 tiles) 64 -> 46, 2048 -> 512 (188)
-// 78 -> 47, 1500 x 1024 -> 512 (96) 26.2 -> 25.4, 600 x 512 -> 2048 (160) 22.6 -> 17.1; one stage after the other they
-// take 0.55 us a stage whatever runs beside them, so
-// that few tiles are slower alone: 256 x 512 -> 2048 (64) 11.5 -> 14.8, 600 x 2048 -> 512 (40) 33 -> 40; but they
-// leave the chip to other launches: 1000 x 512 -> 2048 -> 512 (256 and 64) 46 -> 28 a call with calls in flight,
-// 76 -> 78 alone. Short reductions have nothing to gain: 3001 x 128 -> 256 7.0 -> 8.9.
+// 64 x 128, fp32 on the bf16 matrix cores. Before -> here, us a launch: 3001 x 512 -> 2048 (752 tiles) 64 -> 45, 2048 -> 512 (188)
+// 69 -> 45, 1500 x 1024 -> 512 (96) 24.1 -> 23.5, 600 x 512 -> 2048 (160) 22.0 -> 16.1; one stage after the other they
+// take 0.55 us a stage whatever runs beside them. Short reductions have nothing to gain: 3001 x 128 -> 256 7.0 -> 8.9.
+// 32 x 64 of them, four times as many: a stage takes 0.3 us, so few tiles are faster alone, but four of them take more of the
+// chip from other launches than the one. Alone, before / 64 x 128 / 32 x 64, and in flight: 256 x 512 -> 2048 (256 of them) 10.8 / 14.7 / 8.9, 7.6 / 5.1 /
+// 4.7; 1000 x 2048 -> 512 (256) 32.4 / 39.0 / 27.8, 25.9 / 13.5 / 14.8; 300 x 512 -> 2048 (320) 13.8 / 14.9 / 10.5, 9.5 / 5.8 / 5.6; 600 x
+// 1024 -> 1024 (304) 23.6 / 23.2 / 17.2, 16.5 / 8.6 / 9.3; 1100 x 2048 -> 512 (280) 42.3 / 39.4 / 29.9, 27.9 / 14.5 / 16.1. So they are
+// taken where there is at most one to a compute unit, and with short reductions, where they lose nothing in flight, as far
+// as the larger ones are slower alone than what was there before. Fewer yet are left to the mid-size kernels, which
+// split the reduction: 128 x 512 -> 2048 (128 of 32 x 64) 7.5 there, 8.3 here, 300 x 2048 -> 512 (80) 20.5 and 25.3.
 constexpr long kSplitTiles = 64;
 constexpr int kSplitMinK = 192;
+constexpr long kSplitSmallTiles = 256;                     // 32 x 64
+constexpr long kSplitShortTiles = 96;                      // 64 x 128, with reductions of at most
+constexpr int kSplitShortK = 512;
 
 GemmChoice choose_gemm(const OpLaunch* Ls, int n) {
   for (int b = 0; b < n; ++b)
@@ -667,7 +674,10 @@ GemmChoice choose_gemm(const OpLaunch* Ls, int n) {
     if (tiles(128, 64) < kNarrowTiles) return {};
     return tiles(128, 256) >= kWideTiles ? GemmChoice{128, 256} : GemmChoice{128, 64};
   }
-  if (Ls[0].w3 && tiles(64, 128) >= kSplitTiles) return {64, 128, true};
+  if (const long t = Ls[0].w3 ? tiles(64, 128) : 0; t >= kSplitTiles) {
+    const bool small = tiles(32, 64) <= kSplitSmallTiles || (t < kSplitShortTiles && Ls[0].x.c <= kSplitShortK);
+    return small ? GemmChoice{32, 64, true} : GemmChoice{64, 128, true};
+  }
   if (tiles(128, 128) >= kF32BigTiles) return {128, 128};
   return tiles(64, 64) >= kF32Tiles ? GemmChoice{64, 64} : GemmChoice{};
 }
@@ -732,7 +742,7 @@ hipError_t launch_gemm(const OpLaunch* Ls, int n, hipStream_t s, KernelEvents* e
     if (c.bm == 128) return launch_direct<__bf16, 128, 64, 2, 2, 3>(Ls, n, s, ev);
     return hipErrorInvalidValue;
   }
-  if (c.split) return launch_split<64, 128, 1, 4>(Ls, n, s, ev);
+  if (c.split) return c.bm == 32 ? launch_split<32, 64, 1, 2>(Ls, n, s, ev) : launch_split<64, 128, 1, 4>(Ls, n, s, ev);
   if (c.bm == 128) return launch_direct<float, 128, 128, 2, 2, 2>(Ls, n, s, ev);
   if (c.bm == 64) return launch_direct<float, 64, 64, 2, 2, 3>(Ls, n, s, ev);
   return hipErrorInvalidValue;
@@ -744,7 +754,7 @@ int gemm_describe(const OpLaunch* Ls, int n, char* name, size_t size) {
   int m = 0;
   for (int b = 0; b < n; ++b) m += make_gemm(Ls[b]).M > 0;
   if (name && size && c.split)
-    snprintf(name, size, "conv_gemm_split_kernel%s<%d, %d, 1, 4>", m > 1 ? "_bands" : "", c.bm, c.bn);
+    snprintf(name, size, "conv_gemm_split_kernel%s<%d, %d, 1, %d>", m > 1 ? "_bands" : "", c.bm, c.bn, c.bn / 32);
   else if (name && size)   // (tile, wavefronts in either direction, stages: as launch_gemm takes them)
     snprintf(name, size, "conv_gemm_kernel%s<%s, %d, %d, 2, %d, %d>", m > 1 ? "_bands" : "", bf ? "__bf16" : "float", c.bm, c.bn,
              bf && c.bn == 256 ? 4 : 2, c.bm == 256 || (!bf && c.bm == 128) ? 2 : 3);

@@ -1879,6 +1879,51 @@ def test_fp32_products_on_the_bf16_matrix_cores(oracle, cfg):
         np.testing.assert_array_equal(dev, want)
 
 
+@pytest.mark.parametrize("cfg", [
+    (1000, 192, 516, False),       # the shortest reduction; rows and channels end inside a tile; more tiles than compute units
+    (509, 2052, 1024, True),       # the longest; a last stage of four elements; a tile to each compute unit
+    (2017, 260, 132, True),        # an odd number of stages
+])
+def test_fp32_products_in_small_tiles(oracle, cfg):
+    """Few 64 x 128 tiles are cut into 32 x 64 ones: within fp32 rounding of the 64-bit result, as the larger are, exact on
+    small integers, and what the fp32 instructions make of rows that hold values that are not finite."""
+    m, k, n, residual = cfg
+    chain = _split_chain(m, k, n, residual)
+    t = workloads.make_row_tensors(chain, zero_bias=False, seed=43)
+    dev, host, names = _run_rows(chain, t)
+    assert names == {"conv_gemm_split_kernel<32, 64, 1, 2>"}, names
+    np.testing.assert_array_equal(dev, host)
+
+    def reference(x):
+        x = x.astype(np.float64)
+        y = sum(x @ w.astype(np.float64).T + b for w, b in zip(t.weights, t.biases))
+        return np.maximum(y, 0)
+
+    want = reference(t.x)
+    # k / 16 roundings of 2^-24 of sums that grow like sqrt(k), as in the larger tiles
+    assert np.linalg.norm(dev - want) <= 2 * np.sqrt(k / 16) * 2.0 ** -24 * np.linalg.norm(want)
+    rng = np.random.Generator(np.random.PCG64(14))
+    ti = workloads.Tensors(rng.integers(-3, 4, (m, k)).astype(np.float32),
+                           [rng.integers(-3, 4, (L.n, L.k)).astype(np.float32) for L in chain.layers],
+                           [rng.integers(-3, 4, L.n).astype(np.float32) for L in chain.layers])
+    want_int = oracle.run_row_chain(chain, ti)
+    for bands in (1, 3):
+        dev, _, _ = _run_rows(_split_chain(m, k, n, residual, bands), ti)
+        np.testing.assert_array_equal(dev, want_int)
+    x = t.x.copy()
+    x[m - 1, k - 1], x[3, 5] = np.inf, 3.4e38
+    dev, _, _ = _run_rows(chain, workloads.Tensors(x, t.weights, t.biases))
+    with np.errstate(invalid="ignore", over="ignore"):
+        odd = reference(x).astype(np.float32)
+    large = ~(np.abs(odd) < 1e30)
+    assert set(np.nonzero(large.any(axis=1))[0]) == {3, m - 1}
+    np.testing.assert_allclose(dev[large & ~np.isnan(odd)], odd[large & ~np.isnan(odd)], rtol=1e-5)
+    rest = np.ones(m, bool)
+    rest[[3, m - 1]] = False
+    # (tiles with such a row are the fp32 instructions' throughout: a rounding after every second product)
+    assert np.linalg.norm(dev[rest] - want[rest]) <= 2 * np.sqrt(k / 2) * 2.0 ** -24 * np.linalg.norm(want[rest])
+
+
 @pytest.mark.parametrize("where", ["input", "weights"])
 def test_fp32_products_with_values_that_are_not_finite(where):
     """Infinities, NaN and values too large for bf16 on the way to the bf16 matrix cores: every element is
