@@ -221,13 +221,20 @@ template <int NT, int KS, int GPW>
 hipError_t launch_pw(const PwParams* ps, int n, hipStream_t s, KernelEvents* ev) {
   unsigned gx[kMaxBatch];
   for (int b = 0; b < n; ++b) gx[b] = (unsigned)((ps[b].groups + 4 * GPW - 1) / (4 * GPW));
-  return ps[0].res ? launch_group(pointwise_kernel<NT, KS, true, GPW>, pointwise_kernel_bands<NT, KS, true, GPW>, ps, n, gx, 1, 1, dim3(256), s, ev)
-                   : launch_group(pointwise_kernel<NT, KS, false, GPW>, pointwise_kernel_bands<NT, KS, false, GPW>, ps, n, gx, 1, 1, dim3(256), s, ev);
+  if (ps[0].res) return launch_group(pointwise_kernel<NT, KS, true, GPW>, pointwise_kernel_bands<NT, KS, true, GPW>, ps, n, gx, 1, 1, dim3(256), s, ev);
+  return launch_group(pointwise_kernel<NT, KS, false, GPW>, pointwise_kernel_bands<NT, KS, false, GPW>, ps, n, gx, 1, 1, dim3(256), s, ev);
 }
 
-// Groups of pixels from which a wavefront takes four (short reductions: their inputs are all in registers at once). Four
-// a wavefront below, us a launch of 32 -> 192 channels: 4 100 groups 18.7 against 15.8, 3 700 15.2 against 14.1.
+// Groups of pixels a wavefront takes: four in launches of many (short reductions: their inputs are all in registers at
+// once). Four a wavefront below, us a launch of 32 -> 192 channels: 4 100 groups 18.7 against 15.8, 3 700 15.2 against 14.1.
 constexpr long kManyGroups = 8192;
+long pw_groups(const OpLaunch& L) { return ((long)L.x.n * std::max(0, L.out_hi - L.out_lo) * L.x.w + 31) / 32; }
+int pw_groups_per_wavefront(const OpLaunch* Ls, int n, int ks) {
+  long groups = 0;
+  for (int b = 0; b < n; ++b) groups += pw_groups(Ls[b]);
+  return ks <= 2 && groups >= kManyGroups ? 4 : 1;
+}
+
 struct PwShape { int nt, ks; };
 constexpr PwShape kPwShapes[] = {{6, 2}, {1, 12}, {1, 2}, {2, 2}, {4, 2}, {1, 4}, {2, 4}, {4, 4}, {1, 8}, {2, 8}};
 
@@ -255,15 +262,16 @@ int pointwise_describe(const OpLaunch* Ls, int n, char* name, size_t size) {
   pw_find(Ls[0], &nt, &ks);
   for (int b = 0; b < n; ++b) m += Ls[b].out_hi > Ls[b].out_lo;
   if (name && size)
-    snprintf(name, size, "pointwise_kernel%s<%d, %d, %s>", m > 1 ? "_bands" : "", nt, ks, Ls[0].res.ptr ? "true" : "false");
+    snprintf(name, size, "pointwise_kernel%s<%d, %d, %s, %d>", m > 1 ? "_bands" : "", nt, ks, Ls[0].res.ptr ? "true" : "false",
+             pw_groups_per_wavefront(Ls, n, ks));
   return 1;
 }
 
 hipError_t launch_pointwise(const OpLaunch* Ls, int n, hipStream_t stream, KernelEvents* ev) {
   int nt = 0, ks = 0, m = 0;
   if (n < 1 || n > kMaxBatch || !pw_find(Ls[0], &nt, &ks)) return hipErrorInvalidValue;
+  const int per = pw_groups_per_wavefront(Ls, n, ks);
   PwParams ps[kMaxBatch];
-  long groups = 0;
   for (int b = 0; b < n; ++b) {
     const OpLaunch& L = Ls[b];
     PwParams& p = ps[m];
@@ -275,13 +283,11 @@ hipError_t launch_pointwise(const OpLaunch* Ls, int n, hipStream_t stream, Kerne
     p.act = L.act; p.out_lo = L.out_lo; p.R = L.out_hi - L.out_lo; p.N = L.x.n;
     p.M = p.N * p.R * p.W;
     p.k_pad = L.k_pad;
-    p.groups = (p.M + 31) / 32;
-    if (p.M <= 0) continue;
-    groups += p.groups;
-    ++m;
+    p.groups = (int)pw_groups(L);
+    if (p.M > 0) ++m;
   }
   if (m == 0) return hipSuccess;
-#define LOP_PW_CASE(NT, KS) if (nt == NT && ks == KS) return KS <= 2 && groups >= kManyGroups ? launch_pw<NT, KS, KS <= 2 ? 4 : 1>(ps, m, stream, ev) : launch_pw<NT, KS, 1>(ps, m, stream, ev)
+#define LOP_PW_CASE(NT, KS) if (nt == NT && ks == KS) return per == 4 ? launch_pw<NT, KS, KS <= 2 ? 4 : 1>(ps, m, stream, ev) : launch_pw<NT, KS, 1>(ps, m, stream, ev)
   LOP_PW_CASE(6, 2); LOP_PW_CASE(1, 12); LOP_PW_CASE(1, 2); LOP_PW_CASE(2, 2); LOP_PW_CASE(4, 2);
   LOP_PW_CASE(1, 4); LOP_PW_CASE(2, 4); LOP_PW_CASE(4, 4); LOP_PW_CASE(1, 8); LOP_PW_CASE(2, 8);
 #undef LOP_PW_CASE

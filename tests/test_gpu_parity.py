@@ -2084,3 +2084,28 @@ def test_streaming_layers_merged_over_bands(oracle, cfg):
         np.testing.assert_array_equal(dev, host)
         assert rel_err(dev, want) <= TOL["bf16"]
         np.testing.assert_array_equal(dev, one_by_one)
+
+
+@pytest.mark.parametrize("shape", [(1, 513, 512), (3, 293, 301)])
+def test_streaming_layers_of_many_pixels(oracle, shape):
+    """1x1 streaming layers of 8192 groups of 32 pixels and more: wavefronts take four groups each, under the names
+    the launches have; against the oracle, and over bands (the first chain: in one launch) bit for bit."""
+    n, h, w = shape
+    merged = workloads.Chain("many", (n, 32, h, w), "bf16", 4)
+    merged.add(workloads.DWCONV, 32, 32, 3, 1, 1, 1, "relu6")
+    merged.add(workloads.CONV, 32, 192, 1, 1, 0, act="relu6")
+    added = workloads.Chain("many", (n, 32, h, w), "bf16", 4)
+    added.add(workloads.CONV, 32, 192, 1, 1, 0, act="none")
+    added.add(workloads.CONV, 32, 192, 1, 1, 0, act="relu", input_from=workloads.CHAIN_INPUT, residual_from=0)
+    for chain, names in ((merged, [None, "<6, 2, false, 4>"]), (added, ["<6, 2, false, 4>", "<6, 2, true, 4>"])):
+        t = workloads.make_tensors(chain, zero_bias=False, seed=71)
+        plan = lop.Plan(chain, t, 1, lop.LOP_FLAG_NO_FUSE)
+        try:
+            for l, name in enumerate(names):
+                assert name is None or plan.layer_kernel(0, l)[0] == "pointwise_kernel" + name, plan.layer_kernel(0, l)
+        finally:
+            plan.destroy()
+        whole, _ = run_gpu(chain, t, n_bands=1, use_host=False, flags=lop.LOP_FLAG_NO_FUSE)
+        assert rel_err(whole, oracle.run_chain(chain, t)) <= TOL["bf16"]
+        bands, _ = run_gpu(chain, t, n_bands=4, use_host=False, flags=lop.LOP_FLAG_NO_FUSE)
+        np.testing.assert_array_equal(bands, whole)
