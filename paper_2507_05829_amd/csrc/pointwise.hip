@@ -221,18 +221,22 @@ template <int NT, int KS, int GPW>
 hipError_t launch_pw(const PwParams* ps, int n, hipStream_t s, KernelEvents* ev) {
   unsigned gx[kMaxBatch];
   for (int b = 0; b < n; ++b) gx[b] = (unsigned)((ps[b].groups + 4 * GPW - 1) / (4 * GPW));
-  if (ps[0].res) return launch_group(pointwise_kernel<NT, KS, true, GPW>, pointwise_kernel_bands<NT, KS, true, GPW>, ps, n, gx, 1, 1, dim3(256), s, ev);
+  if constexpr (GPW == 1) {
+    if (ps[0].res) return launch_group(pointwise_kernel<NT, KS, true, 1>, pointwise_kernel_bands<NT, KS, true, 1>, ps, n, gx, 1, 1, dim3(256), s, ev);
+  }
   return launch_group(pointwise_kernel<NT, KS, false, GPW>, pointwise_kernel_bands<NT, KS, false, GPW>, ps, n, gx, 1, 1, dim3(256), s, ev);
 }
 
 // Groups of pixels a wavefront takes: four in launches of many (short reductions: their inputs are all in registers at
 // once). Four a wavefront below, us a launch of 32 -> 192 channels: 4 100 groups 18.7 against 15.8, 3 700 15.2 against 14.1.
+// One with a residual, whose loads the four would wait for one group after the other (32 -> 192 with four also
+// spills): 25 600 groups 32 -> 192 136 us with one, 145 with four, 32 -> 64 41 and 45, 32 -> 32 24.3 and 24.4; 9 100 42 and 49, 17.0 and 17.6, 10.3 and 12.0.
 constexpr long kManyGroups = 8192;
 long pw_groups(const OpLaunch& L) { return ((long)L.x.n * std::max(0, L.out_hi - L.out_lo) * L.x.w + 31) / 32; }
 int pw_groups_per_wavefront(const OpLaunch* Ls, int n, int ks) {
   long groups = 0;
   for (int b = 0; b < n; ++b) groups += pw_groups(Ls[b]);
-  return ks <= 2 && groups >= kManyGroups ? 4 : 1;
+  return ks <= 2 && !Ls[0].res.ptr && groups >= kManyGroups ? 4 : 1;
 }
 
 struct PwShape { int nt, ks; };

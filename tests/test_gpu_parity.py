@@ -2088,8 +2088,8 @@ def test_streaming_layers_merged_over_bands(oracle, cfg):
 
 @pytest.mark.parametrize("shape", [(1, 513, 512), (3, 293, 301)])
 def test_streaming_layers_of_many_pixels(oracle, shape):
-    """1x1 streaming layers of 8192 groups of 32 pixels and more: wavefronts take four groups each, under the names
-    the launches have; against the oracle, and over bands (the first chain: in one launch) bit for bit."""
+    """1x1 streaming layers of 8192 groups of 32 pixels and more: wavefronts take four groups each, one with a residual, under the
+    names the launches have; against the oracle, and over bands (the first chain: in one launch) bit for bit."""
     n, h, w = shape
     merged = workloads.Chain("many", (n, 32, h, w), "bf16", 4)
     merged.add(workloads.DWCONV, 32, 32, 3, 1, 1, 1, "relu6")
@@ -2097,7 +2097,7 @@ def test_streaming_layers_of_many_pixels(oracle, shape):
     added = workloads.Chain("many", (n, 32, h, w), "bf16", 4)
     added.add(workloads.CONV, 32, 192, 1, 1, 0, act="none")
     added.add(workloads.CONV, 32, 192, 1, 1, 0, act="relu", input_from=workloads.CHAIN_INPUT, residual_from=0)
-    for chain, names in ((merged, [None, "<6, 2, false, 4>"]), (added, ["<6, 2, false, 4>", "<6, 2, true, 4>"])):
+    for chain, names in ((merged, [None, "<6, 2, false, 4>"]), (added, ["<6, 2, false, 4>", "<6, 2, true, 1>"])):
         t = workloads.make_tensors(chain, zero_bias=False, seed=71)
         plan = lop.Plan(chain, t, 1, lop.LOP_FLAG_NO_FUSE)
         try:
