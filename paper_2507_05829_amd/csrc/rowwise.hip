@@ -302,26 +302,53 @@ inline bool dw3_applies(const RowParams& p, int op, int vec) {
          p.res == nullptr;
 }
 
+// The bands in one launch, unless they have more workgroups than a launch takes (2^32 threads, exclusive): then in as few as
+// hold them, a band of too many itself cut into groups of images or of rows of an image.
+constexpr long kDwBlocks = 0xffffffffL / 256;
 template <typename T, int VEC>
 hipError_t launch_dw3(const RowParams* ps, int n, hipStream_t s, KernelEvents* ev) {
   Dw3Params qs[kMaxBatch];
   unsigned gx[kMaxBatch];
   int m = 0;
+  long total = 0;
+  auto launch = [&]() -> hipError_t {
+    const int k = m;
+    m = 0; total = 0;
+    if (k == 0) return hipSuccess;
+    return ps[0].sh == 1 ? launch_group(dwconv3x3_kernel<T, VEC, 1>, dwconv3x3_kernel_bands<T, VEC, 1>, qs, k, gx, 1, 1, dim3(256), s, ev)
+                         : launch_group(dwconv3x3_kernel<T, VEC, 2>, dwconv3x3_kernel_bands<T, VEC, 2>, qs, k, gx, 1, 1, dim3(256), s, ev);
+  };
   for (int b = 0; b < n; ++b) {
     const RowParams& p = ps[b];
     if (p.R <= 0 || p.N <= 0) continue;
-    Dw3Params& q = qs[m];
-    q.r = p;
-    q.cols_per_block = std::max(1, 256 / (p.C / VEC));
-    q.col_blocks = (p.W_out + q.cols_per_block - 1) / q.cols_per_block;
-    q.chunks = (p.R + dw_rows_per_thread(p.sh) - 1) / dw_rows_per_thread(p.sh);
-    const unsigned long blocks = (unsigned long)q.col_blocks * q.chunks * p.N;
-    if (blocks > 0x7fffffffUL) return hipErrorInvalidValue;
-    gx[m++] = (unsigned)blocks;
+    const int rpt = dw_rows_per_thread(p.sh), cols = std::max(1, 256 / (p.C / VEC)), col_blocks = (p.W_out + cols - 1) / cols;
+    const int rows = (int)std::min((long)p.R, kDwBlocks / col_blocks * rpt);
+    const int images = (int)std::min((long)p.N, kDwBlocks / ((long)col_blocks * ((rows + rpt - 1) / rpt)));
+    const size_t x_img = (size_t)p.x_rows * p.W * p.C * sizeof(T), y_img = (size_t)p.y_rows * p.W_out * p.C * sizeof(T);
+    for (int i = 0; i < p.N; i += images)
+      for (int r = 0; r < p.R; r += rows) {
+        Dw3Params q;
+        q.r = p;
+        q.r.x = (const char*)p.x + i * x_img;
+        q.r.y = (char*)p.y + i * y_img;
+        q.r.y2 = p.y2 ? (char*)p.y2 + i * y_img : nullptr;
+        q.r.N = std::min(images, p.N - i);
+        q.r.out_lo = p.out_lo + r;
+        q.r.R = std::min(rows, p.R - r);
+        q.cols_per_block = cols;
+        q.col_blocks = col_blocks;
+        q.chunks = (q.r.R + rpt - 1) / rpt;
+        const long blocks = (long)col_blocks * q.chunks * q.r.N;
+        if (m == kMaxBatch || total + blocks > kDwBlocks) {
+          const hipError_t e = launch();
+          if (e != hipSuccess) return e;
+        }
+        qs[m] = q;
+        gx[m++] = (unsigned)blocks;
+        total += blocks;
+      }
   }
-  if (m == 0) return hipSuccess;
-  return ps[0].sh == 1 ? launch_group(dwconv3x3_kernel<T, VEC, 1>, dwconv3x3_kernel_bands<T, VEC, 1>, qs, m, gx, 1, 1, dim3(256), s, ev)
-                       : launch_group(dwconv3x3_kernel<T, VEC, 2>, dwconv3x3_kernel_bands<T, VEC, 2>, qs, m, gx, 1, 1, dim3(256), s, ev);
+  return launch();
 }
 
 // Channel vector per thread of the sliding-window kernel (0: it does not apply).

@@ -140,6 +140,7 @@ static hipError_t launch(const void* fn, dim3 grid, dim3 block, hipStream_t s, c
   if (!grid.x || !grid.y || !grid.z || !block.x || !block.y || !block.z) die("%s: empty grid or block", what);
   if ((size_t)block.x * block.y * block.z > 1024) die("%s: block of more than 1024 threads", what);
   if (grid.y > 65535 || grid.z > 65535) die("%s: grid.y or grid.z above 65535", what);
+  if ((unsigned long)grid.x * block.x > 0xffffffffUL) die("%s: 2^32 threads or more along x", what);
   ++g_launches;
   return hipSuccess;
 }

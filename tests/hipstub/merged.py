@@ -233,12 +233,13 @@ def poison():
 
 
 def grids():
-    """Depthwise layers whose bands' launches fit the grid's second dimension, and whose launch over all
-    rows would not (the stand-in ends the process on a grid that the runtime refuses)."""
+    """Depthwise layers whose bands' launches fit the grid, and whose launch over all rows would not, and of more
+    images than a launch takes (the stand-in ends the process on a grid that the runtime refuses)."""
     bad = []
-    for dtype, shape, s in (("f32", (600, 4, 1030, 2), 1), ("bf16", (3000, 8, 90, 3), 2), ("f32", (1, 4, 600000, 1), 1)):
+    for dtype, shape, s in (("f32", (600, 4, 1030, 2), 1), ("bf16", (3000, 8, 90, 3), 2), ("f32", (1, 4, 600000, 1), 1),
+                            ("bf16", (9000000, 4, 2, 1), 1), ("bf16", (17000000, 4, 1, 1), 1)):
         for flags in (0, lop.LOP_FLAG_REUSE):
-            chain = workloads.Chain("depthwise", shape, dtype, 4)
+            chain = workloads.Chain("depthwise", shape, dtype, min(4, shape[2]))
             for _ in range(2):
                 chain.add(workloads.DWCONV, shape[1], shape[1], 3, s, 1, 1, "relu6")
             got = run_both_ways(chain, flags)

@@ -2109,3 +2109,31 @@ def test_streaming_layers_of_many_pixels(oracle, shape):
         assert rel_err(whole, oracle.run_chain(chain, t)) <= TOL["bf16"]
         bands, _ = run_gpu(chain, t, n_bands=4, use_host=False, flags=lop.LOP_FLAG_NO_FUSE)
         np.testing.assert_array_equal(bands, whole)
+
+
+@pytest.mark.parametrize("n,h,bands", [(16_800_000, 1, 1), (8_500_000, 2, 2)])
+def test_depthwise_layers_of_more_workgroups_than_a_launch_takes(n, h, bands):
+    """Millions of tiny images, a workgroup each: 2^24 workgroups of 256 threads are more than a launch takes, in one band or with
+    all bands together. Bit for bit (products of bf16 values are exact in fp32, sums in the kernel's order)."""
+    chain = workloads.Chain("tiny images", (n, 4, h, 1), "bf16", bands)
+    chain.add(workloads.DWCONV, 4, 4, 3, 1, 1, 1, "relu")
+    rng = np.random.Generator(np.random.PCG64(5))
+    w = workloads.to_bf16_values(rng.standard_normal((4, 1, 3, 3)).astype(np.float32))
+    b = rng.standard_normal(4).astype(np.float32)
+    plan = lop.Plan(chain, workloads.Tensors(None, [w], [b]), bands)
+    try:
+        assert plan.layer_kernel(0, 0)[0] == "dwconv3x3_kernel<__bf16, 4, 1>", plan.layer_kernel(0, 0)
+        x = torch.randn((n, h, 4), device="cuda").to(torch.bfloat16)
+        y = torch.full_like(x, float("nan"))
+        torch.cuda.synchronize()
+        plan.run_chain(x, y)
+        plan.synchronize()
+    finally:
+        plan.destroy()
+    wd, bd = torch.from_numpy(w[:, 0, :, 1]).cuda(), torch.from_numpy(b).cuda()   # the middle column of taps
+    for r in range(h):
+        want = bd.expand(n, 4)
+        for a in range(3):
+            if 0 <= r + a - 1 < h:
+                want = want + x[:, r + a - 1].float() * wd[:, a]
+        assert torch.equal(y[:, r], want.relu().to(torch.bfloat16))
