@@ -59,12 +59,13 @@ __device__ __forceinline__ void mma<float>(const u32x4& wa, const u32x4& px, f32
   acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[3], b[3], acc, 0, 0, 0);
 }
 
-// The maximum over four neighbouring lanes, of each of four values, in all four lanes: the 2 x 2 pooling of pixels that lanes
-// hold window by window. Two instructions a value; fmaxf of a moved value is seven, most of them to quiet NaNs that a
-// matrix instruction does not make. (An instruction that reads another lane needs two others between it and the one that
-// wrote the value. The values must come from vector instructions: the compiler does not know that these read them, and a
-// result straight from a matrix instruction would need more of a wait.)
-__device__ __forceinline__ void max_of_quad(f32x4& v) {
+// v + bias, and of each of the four values the maximum over four neighbouring lanes, in all four lanes: the 2 x 2 pooling of
+// pixels that lanes hold window by window. Two instructions a value; fmaxf of a moved value is seven, most of them to quiet
+// NaNs that a matrix instruction does not make. (An instruction that reads another lane needs two others between it and
+// the one that wrote the value, and many more behind a matrix instruction, whose results the compiler does not know to be read
+// here: the addition is the vector instruction that lies between in any case.)
+__device__ __forceinline__ void max_of_quad(f32x4& v, const f32x4& bias) {
+  v += bias;
   float a = v[0], b = v[1], c = v[2], d = v[3];
   asm volatile("s_nop 1\n"
                "v_max_f32_dpp %0, %0, %0 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n"

@@ -127,7 +127,7 @@ struct PatchPieces {
     bool stores = live;
     if constexpr (POOL) {
 #pragma unroll
-      for (int i = 0; i < N; ++i) max_of_quad(sum[i]);
+      for (int i = 0; i < N; ++i) max_of_quad(sum[i], bias[i]);
       stores = live & ((lane & 3) == 0);
       ya = ((size_t)(t.n * p.y_rows + ((p.out_lo + row) >> 1) - p.y_row0) * p.W_out + (col >> 1)) * p.C_out;
     } else {
@@ -135,8 +135,8 @@ struct PatchPieces {
     }
 #pragma unroll
     for (int i = 0; i < N; ++i) {
-      sum[i] += bias[i];
       if constexpr (!POOL) {
+        sum[i] += bias[i];
         alignas(16) T rr[4];
         *(raw_t*)rr = res[i];
 #pragma unroll

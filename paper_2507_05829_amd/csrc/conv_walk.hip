@@ -241,8 +241,7 @@ __device__ __forceinline__ void walk_body(const PatchParams& p, const int bx, co
     for (int g = 0; g < 4; ++g) {
       f32x4 v = f32x4{acc[g * 4], acc[g * 4 + 1], acc[g * 4 + 2], acc[g * 4 + 3]};
       if constexpr (POOL) {
-        v += bias[g];
-        max_of_quad(v);
+        max_of_quad(v, bias[g]);
       }
       alignas(8) __bf16 b[4];
 #pragma unroll
