@@ -1742,6 +1742,36 @@ def test_shortcut_beside_its_convolution(oracle, cfg):
             np.testing.assert_array_equal(dev, want_int)
 
 
+@pytest.mark.parametrize("flags", [0, lop.LOP_FLAG_REUSE])
+def test_shortcut_with_pixels_that_are_not_finite(flags):
+    """fp32, a 3 x 3 convolution and its 1 x 1 shortcut in one launch on the bf16 matrix cores: around infinities, NaN and values
+    too large for bf16 what separate launches make of them, everywhere else unchanged but for rounding."""
+    chain = workloads.Chain("block", (1, 64, 60, 64), "f32", 3)
+    chain.add(workloads.CONV, 64, 128, 3, 2, 1, act="none")
+    chain.add(workloads.CONV, 64, 128, 1, 2, 0, act="none", input_from=workloads.CHAIN_INPUT)
+    chain.add(workloads.CONV, 128, 32, 1, 1, 0, act="none", input_from=0)
+    chain.add(workloads.CONV, 128, 32, 1, 1, 0, act="none", input_from=1, residual_from=2)
+    t = workloads.make_tensors(chain, zero_bias=False, seed=73)
+    plan = lop.Plan(chain, t, 1)
+    try:
+        assert plan.layer_kernel(0, 0)[0] == "conv_patch_kernel<float, 32, 32, false, 2>"
+    finally:
+        plan.destroy()
+    clean, _ = run_gpu(chain, t, flags=flags)
+    for value in (np.inf, -np.inf, np.nan, 3.4e38):
+        x = t.x.copy()
+        x[0, 3, 8, 12], x[0, 5, 31, 40] = value, value     # under a shortcut's pixel and beside one
+        t_odd = workloads.Tensors(x, t.weights, t.biases)
+        together, _ = run_gpu(chain, t_odd, flags=flags)
+        apart, _ = run_gpu(chain, t_odd, flags=flags | lop.LOP_FLAG_NO_FUSE)
+        ok = np.isfinite(apart) & (np.abs(apart) < 1e30)
+        assert ok.mean() > 0.95 and not ok.all()
+        np.testing.assert_allclose(together[~ok], apart[~ok], rtol=1e-5)
+        assert np.abs(together[ok] - apart[ok]).max() <= 1e-5 * np.abs(clean).max()
+        reached = ~ok.all(axis=1)[0]
+        assert np.abs((together - clean)[:, :, ~reached]).max() <= 1e-5 * np.abs(clean).max()
+
+
 NARROW_GRID = [
     # c_in, c_out, stride, shape(n,h,w), residual, the form expected in one band
     (128, 128, 1, (1, 9, 13), True, "<float, 5, 49152>"),        # slices of four and five steps
