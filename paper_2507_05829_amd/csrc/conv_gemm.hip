@@ -36,7 +36,7 @@ struct GemmParams {
   void* y;
   void* y2;        // second destination with y's layout, or nullptr
   const void* res;
-  const void* w;   // [c_out_pad][k_pad]
+  const void* w;   // [c_out_pad][k_pad]; where the products are made of parts: the operand-order packing
   const void* w3;  // the same weights as three bf16 parts in operand order (fp32 layers)
   const float* bias;
   int x_row0, x_rows, W, K;          // K: channels in
@@ -386,8 +386,10 @@ __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(2)
 // partial products have an accumulator of their own. Against 64 bits the result is closer than that of the
 // fp32 matrix instructions, which round after every second product: rel. error over reductions of 64 / 576 /
 // 4608 normal x uniform values 1.5e-7 / 4.3e-7 / 1.2e-6 there, 4.7e-8 / 1.3e-7 / 4.1e-7 here.
-// An infinity, a NaN or a value that rounds to infinity in bf16 leaves a sum that is not finite; a wavefront
-// that ends with one computes its tile again on the fp32 instructions, which give what they always did.
+// An infinity, a NaN or a value that rounds to infinity in bf16 leaves a sum that is not finite; a workgroup
+// that ends with one computes its tile again on the fp32 instructions, every wavefront its part of the reduction, and they
+// give what they always did. us a launch without such sums, with one tile of them, with all: 3001 x 512 -> 2048 45 / 82 / 105 (on the fp32
+// instructions 55), 2048 -> 512 46 / 125 / 126 (69), 256 x 512 -> 2048 8.8 / 17 / 17 (10.8).
 //
 //  - The input is split once per workgroup, on its way from memory through registers to LDS: stages of 32
 //    elements a row, loaded four stages ahead; a row takes 13 16-byte slots, an odd number, so that 16 neighbouring rows'
@@ -409,6 +411,8 @@ __device__ __forceinline__ void gemm_split_body(const GemmParams& p, const int b
   constexpr int SMEM = 2 * BUF > SUMS ? (2 * BUF > OUT ? 2 * BUF : OUT) : (SUMS > OUT ? SUMS : OUT);
   static_assert(PIECES >= 1, "tile shape");
   __shared__ __attribute__((aligned(1024))) unsigned char smem[SMEM];
+  __shared__ int any_odd;
+  if (threadIdx.x == 0) any_odd = 0;
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -522,60 +526,70 @@ __device__ __forceinline__ void gemm_split_body(const GemmParams& p, const int b
   }
   if (s < ns) stage(s, 0);
 
+  // ---- sums that are not finite: the workgroup's halves of the reduction once more, on the fp32 instructions
+#pragma unroll
+  for (int a = 0; a < TN; ++a) {
+#pragma unroll
+    for (int b = 0; b < TM; ++b) acc[a][b] = (acc[a][b] + low[a][b]) * kSplitUnscale;
+    if (any_not_finite(acc[a])) any_odd = 1;
+  }
+  __syncthreads();
+  if (__builtin_amdgcn_readfirstlane(any_odd)) {
+    unsigned from[TM];
+    const u32x4* wrow[TN];
+#pragma unroll
+    for (int b = 0; b < TM; ++b) from[b] = pixel_offset(m0 + (wm * TM + b) * 32 + (lane & 31));
+#pragma unroll
+    for (int a = 0; a < TN; ++a) {
+      wrow[a] = (const u32x4*)p.w + ((size_t)(co0 / 32 + wn * TN + a) * (p.k_pad / 8) + step * 2) * 64 + lane;
+#pragma unroll
+      for (int b = 0; b < TM; ++b)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.f;
+    }
+#pragma unroll 2
+    for (int i = 0; i < ns; ++i) {
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const int k = i * 32 + step * 16 + j * 8 + (lane >> 5) * 4;
+        u32x4 wv[TN];
+#pragma unroll
+        for (int a = 0; a < TN; ++a) wv[a] = wrow[a][(size_t)(i * 4 + j) * 64];
+#pragma unroll
+        for (int b = 0; b < TM; ++b) {
+          const u32x4 xv = __builtin_amdgcn_raw_buffer_load_b128(xbuf, (int)((from[b] == kOutside) | (k >= p.K) ? kOutside : from[b] + k * 4), 0, 0);
+#pragma unroll
+          for (int a = 0; a < TN; ++a) mma<float>(wv[a], xv, acc[a][b]);
+        }
+      }
+    }
+  }
+
   // ---- the two halves of the reduction: the second half's wavefronts hand their sums over through LDS
 #pragma unroll
   for (int a = 0; a < TN; ++a) {
     f32x4* const at = (f32x4*)smem + (wave % NW) * TM * 256 + lane;
-    __syncthreads();
+    if (a > 0) __syncthreads();
     if (step == 1) {
 #pragma unroll
-      for (int b = 0; b < TM; ++b) {
-        acc[a][b] += low[a][b];
+      for (int b = 0; b < TM; ++b)
 #pragma unroll
         for (int g = 0; g < 4; ++g) at[(b * 4 + g) * 64] = f32x4{acc[a][b][g * 4], acc[a][b][g * 4 + 1], acc[a][b][g * 4 + 2], acc[a][b][g * 4 + 3]};
-      }
     }
     __syncthreads();
     if (step == 0) {
 #pragma unroll
-      for (int b = 0; b < TM; ++b) {
-        acc[a][b] += low[a][b];
+      for (int b = 0; b < TM; ++b)
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
           const f32x4 v = at[(b * 4 + g) * 64];
 #pragma unroll
-          for (int i = 0; i < 4; ++i) acc[a][b][g * 4 + i] = (acc[a][b][g * 4 + i] + v[i]) * kSplitUnscale;
+          for (int i = 0; i < 4; ++i) acc[a][b][g * 4 + i] += v[i];
         }
-      }
     }
   }
   __syncthreads();
   if (step == 1) return;
-  float odd = 0.f;   // NaN if a sum is not finite
-#pragma unroll
-  for (int a = 0; a < TN; ++a)
-#pragma unroll
-    for (int b = 0; b < TM; ++b)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) odd += acc[a][b][i] - acc[a][b][i];
-  if (__builtin_amdgcn_ballot_w64(!(odd == 0.f))) {
-#pragma unroll
-    for (int b = 0; b < TM; ++b) {
-      const unsigned at = pixel_offset(m0 + (wm * TM + b) * 32 + (lane & 31));
-#pragma unroll
-      for (int a = 0; a < TN; ++a) {
-        const float* const wrow = (const float*)p.w + (size_t)(co0 + (wn * TN + a) * 32 + (lane & 31)) * p.k_pad;
-        f32x16 sum;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) sum[i] = 0.f;
-        for (int k = (lane >> 5) * 4; k < p.k_pad; k += 8) {
-          const u32x4 xv = __builtin_amdgcn_raw_buffer_load_b128(xbuf, (int)(at == kOutside || k >= p.K ? kOutside : at + k * 4), 0, 0);
-          mma<float>(*(const u32x4*)(wrow + k), xv, sum);
-        }
-        acc[a][b] = sum;
-      }
-    }
-  }
   gemm_epilogue<float, TM, TN>(p, smem, acc, m0, co0, wave, wm, wn, lane);
 }
 
@@ -687,8 +701,8 @@ GemmChoice choose_gemm(const OpLaunch* Ls, int n) {
 // the size that has one a launch has no second round.
 bool walks(const GemmParams& p) { return !p.res && !p.y2; }
 
-// single, bands: a kernel of BM x BN tiles and THREADS threads, for one band and for several
-template <int BM, int BN, int THREADS>
+// single, bands: a kernel of BM x BN tiles and THREADS threads, for one band and for several; PARTS: of products made of parts
+template <int BM, int BN, int THREADS, bool PARTS = false>
 hipError_t launch_tile(void (*single)(const GemmParams), void (*bands)(const Batch<GemmParams>), const OpLaunch* Ls, int n, hipStream_t s,
                        KernelEvents* ev) {
   GemmParams ps[kMaxBatch];
@@ -699,6 +713,7 @@ hipError_t launch_tile(void (*single)(const GemmParams), void (*bands)(const Bat
   for (int b = 0; b < n; ++b) {
     ps[m] = make_gemm(Ls[b]);
     if (ps[m].M <= 0) continue;
+    if (PARTS) ps[m].w = Ls[b].wd;
     ps[m].by_group = make_fastdiv(kGroupM * (int)gy);
     gx[m] = (unsigned)((ps[m].M + BM - 1) / BM);
     ++m;
@@ -717,7 +732,7 @@ hipError_t launch_direct(const OpLaunch* Ls, int n, hipStream_t s, KernelEvents*
 }
 template <int BM, int BN, int WM, int WN>
 hipError_t launch_split(const OpLaunch* Ls, int n, hipStream_t s, KernelEvents* ev) {
-  return launch_tile<BM, BN, 128 * WM * WN>(conv_gemm_split_kernel<BM, BN, WM, WN>, conv_gemm_split_kernel_bands<BM, BN, WM, WN>, Ls, n, s, ev);
+  return launch_tile<BM, BN, 128 * WM * WN, true>(conv_gemm_split_kernel<BM, BN, WM, WN>, conv_gemm_split_kernel_bands<BM, BN, WM, WN>, Ls, n, s, ev);
 }
 
 }  // namespace

@@ -188,18 +188,24 @@ struct PatchPieces {
   }
 };
 
-// The four partial tiles, added in wavefront order through LDS, and what follows the sums. again(f, sum): this
-// wavefront's pieces of fragment f once more, for sums that are not finite.
+// The four partial tiles, added in wavefront order through LDS, and what follows the sums. again(acc): this wavefront's
+// partial tile once more, in fp32 for a workgroup that has a sum that is not finite (any_odd: zero in LDS since a barrier).
 template <typename T, int TP, bool POOL, typename Again>
-__device__ __forceinline__ void patch_finish(const PatchParams& p, unsigned char* smem, const f32x16 (&acc)[TP], const PatchAt& t,
-                                             int lane, int wave, Again&& again) {
+__device__ __forceinline__ void patch_finish(const PatchParams& p, unsigned char* smem, f32x16 (&acc)[TP], const PatchAt& t,
+                                             int lane, int wave, int* any_odd, Again&& again) {
   // wavefront w finishes pieces w TP .. (w + 1) TP of the UNITS (32 pixels x 8 channels) pieces of a tile (piece u:
   // fragment u / 4, channels (u % 4) * 8 ..), which all lie in one fragment
   constexpr int UNITS = TP * 4;
   u32x4* const part = (u32x4*)smem;
   PatchPieces<T, TP, POOL> out;
   out.load(p, t, wave * TP / 4, t.tile_n * 32 + ((wave * TP) & 3) * 8, lane);
+  if constexpr (sizeof(T) == 4) {
+    if (any_not_finite(acc)) *any_odd = 1;
+  }
   __syncthreads();
+  if constexpr (sizeof(T) == 4) {
+    if (__builtin_amdgcn_readfirstlane(*any_odd)) again(acc);
+  }
 #pragma unroll
   for (int u = 0; u < UNITS; ++u) {
     const f32x16& s = acc[u / 4];
@@ -213,14 +219,6 @@ __device__ __forceinline__ void patch_finish(const PatchParams& p, unsigned char
     sum[i] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int s = 0; s < 4; ++s) sum[i] += __builtin_bit_cast(f32x4, part[(s * UNITS + wave * TP + i) * 64 + lane]);
-  }
-  if constexpr (sizeof(T) == 4) {
-    float odd = 0.f;   // NaN if a sum is not finite
-#pragma unroll
-    for (int i = 0; i < TP; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) odd += sum[i][j] - sum[i][j];
-    if (__builtin_amdgcn_ballot_w64(!(odd == 0.f))) again(wave * TP / 4, sum);
   }
   out.store(p, t, sum, lane);
 }
@@ -398,7 +396,7 @@ __device__ __forceinline__ void patch_body(const PatchParams& p, const int bx, c
     run_patch(c, false);
   }
 
-  patch_finish<T, TP, POOL>(p, smem, acc[0], tile, lane, wave, [](int, f32x4 (&)[TP]) {});
+  patch_finish<T, TP, POOL>(p, smem, acc[0], tile, lane, wave, nullptr, [](f32x16 (&)[TP]) {});
 }
 
 // The 128 x 64 tile (bf16): two wavefronts to a half of the channels, each with half of every pixel's 128 bytes.
@@ -553,11 +551,16 @@ __device__ __forceinline__ void patch_wide_body(const PatchParams& p, const int 
 // (1 150 + 150 TP cycles, without scaling) bounded it: us a launch, then and now, 128 -> 128 channels on 784 pixels 8.1 and 6.6,
 // 256 -> 256 on 400 12.7 and 9.6, on 1 600 18.2 and 16.0; the fp32 backbone in flight 121.7 and 119.2, with shared rows 55.6 and 55.2,
 // alone 154 and 145.
+// A workgroup with a sum that is not finite computes its tile again on the fp32 instructions, a quarter of the reduction a
+// wavefront: us a launch without such sums, with one tile of them, with all: 128 -> 128 channels on 784 pixels 6.6 / 15 / 16 (on the fp32
+// instructions 7.7), 256 -> 256 on 1 600 16 / 41 / 49 (22), 512 -> 512 on 196 16 / 48 / 48 (23).
 template <int TP, int NI, bool POOL, int S>
 __device__ __forceinline__ void patch_split_body(const PatchParams& p, const int bx, const int gx) {
   constexpr int PB = 208, BUF = NI * 32 * PB;
   constexpr int SMEM = 2 * BUF > TP * 16384 ? 2 * BUF : TP * 16384;
   __shared__ __attribute__((aligned(1024))) unsigned char smem[SMEM];
+  __shared__ int any_odd;
+  if (threadIdx.x == 0) any_odd = 0;
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -716,33 +719,31 @@ __device__ __forceinline__ void patch_split_body(const PatchParams& p, const int
 #pragma unroll
   for (int f = 0; f < TP; ++f) acc[0][f] = (acc[0][f] + low[0][f]) * kSplitUnscale;
 
-  // fp32 instructions, on operands straight from memory: the wavefront's fragment with all its channels
-  auto again = [&](int f, f32x4 (&sum)[TP]) __attribute__((always_inline)) {
-    int r, c;
-    tile_pixel<POOL>(p, f * 32 + px, r, c);
-    f32x16 all;
+  // fp32 instructions, on operands straight from memory: every fourth step of 8 channels of all taps
+  auto again = [&](f32x16 (&sum)[TP]) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < 16; ++i) all[i] = 0.f;
+    for (int f = 0; f < TP; ++f)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) sum[f][i] = 0.f;
     for (int t = second ? 4 : 0; t < (second ? 5 : 9); ++t) {
-      const unsigned from = input(ih0 + r * S + t / 3, iw0 + c * S + t % 3);
-      for (int s = 0; s < p.C_in / 8; ++s) {
-        const u32x4 xv = __builtin_amdgcn_raw_buffer_load_b128(xbuf, (int)(from == kOutside ? kOutside : from + s * 32 + half * 16), 0, 0);
-        mma<float>(wd[(size_t)((second ? 0 : t * (p.C_in / 8)) + s) * 64 + lane], xv, all);
+      const u32x4* const wt = wd + (size_t)(second ? 0 : t * (p.C_in / 8)) * 64 + wave * 64 + lane;
+      unsigned from[TP];
+#pragma unroll
+      for (int f = 0; f < TP; ++f) {
+        int r, c;
+        tile_pixel<POOL>(p, f * 32 + px, r, c);
+        const unsigned at = input(ih0 + r * S + t / 3, iw0 + c * S + t % 3);
+        from[f] = at == kOutside ? kOutside : at + wave * 32 + half * 16;
       }
-    }
+#pragma unroll 2
+      for (int c = 0; c < chunks; ++c) {
+        const u32x4 wv = wt[(size_t)c * 256];
 #pragma unroll
-    for (int i = 0; i < TP; ++i) {
-      const int g = (wave * TP + i) % 4;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        float v = all[j];
-#pragma unroll
-        for (int q = 1; q < 4; ++q) v = g == q ? all[q * 4 + j] : v;
-        sum[i][j] = v;
+        for (int f = 0; f < TP; ++f) mma<float>(wv, __builtin_amdgcn_raw_buffer_load_b128(xbuf, (int)from[f], c * 128, 0), sum[f]);
       }
     }
   };
-  patch_finish<float, TP, POOL>(p, smem, acc[0], tile, lane, wave, again);
+  patch_finish<float, TP, POOL>(p, smem, acc[0], tile, lane, wave, &any_odd, again);
 }
 
 // Load instructions per wavefront and patch: the patch of a tile has at most NI * 256 / 9 pixels.

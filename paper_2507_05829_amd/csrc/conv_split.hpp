@@ -49,6 +49,17 @@ __device__ __forceinline__ void split_bf16(const u32x4& a, const u32x4& b, u32x4
   for (int k = 0; k < 3; ++k) parts[k] = u32x4{lo[k].x, lo[k].y, hi[k].x, hi[k].y};
 }
 
+// Whether one of a wavefront's sums is not finite.
+template <int N>
+__device__ __forceinline__ bool any_not_finite(const f32x16 (&sum)[N]) {
+  float odd = 0.f;   // NaN if a sum is not finite
+#pragma unroll
+  for (int k = 0; k < N; ++k)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) odd += sum[k][i] - sum[k][i];
+  return __builtin_amdgcn_ballot_w64(!(odd == 0.f)) != 0;
+}
+
 // The partial products of one operand pair: e = 0 .. 4 the five small ones (for a sum of their own), 5 high x high.
 constexpr int kSplitW[6] = {2, 0, 1, 1, 0, 0}, kSplitX[6] = {0, 2, 1, 0, 1, 0};
 

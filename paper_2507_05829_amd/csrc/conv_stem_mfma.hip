@@ -262,7 +262,7 @@ __global__ __launch_bounds__(256) void conv_stem_mfma_tall_kernel_bands(const Ba
 // fp32 products run on the bf16 matrix cores as sums of three parts (see conv_gemm.hip), 2 100 cycles a
 // fragment instead of 5 400: the image is split on its way to LDS, the weights lie there as well (all
 // wavefronts need all of them). A wavefront that ends with a sum that is not finite computes its fragment again on the fp32
-// instructions. That also covers what is read behind a window's end: an infinity there times the padding's
+// instructions (one image of 224 x 224: 7.0 us without such a sum, 15 with one, 19 with one in every fragment). That also covers what is read behind a window's end: an infinity there times the padding's
 // zero weight is no finite sum.
 constexpr int kPoolRows = 7, kPoolCols = 8;
 constexpr int kPoolCR = 2 * kPoolRows + 1, kPoolCC = 2 * kPoolCols + 1;   // outputs of the convolution under a tile
