@@ -382,9 +382,11 @@ __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(2)
 
 // fp32 products on the bf16 matrix cores, which are 16 times as fast as the fp32 ones. A value is the sum of
 // three bf16 values (24 bits of mantissa are 8 + 8 + 8, split_bf16), a product of two values the sum of the
-// six partial products that are not below 2^-26 of it; bf16 products are exact in fp32, and the five small
-// partial products have an accumulator of their own. Against 64 bits the result is closer than that of the
-// fp32 matrix instructions, which round after every second product: rel. error over reductions of 64 / 576 /
+// six largest partial products (a published method: Henry, Tang and Heinecke, Leveraging the bfloat16 datatype for
+// higher-precision computations, 2019); bf16 products are exact in fp32, and the five small
+// partial products have an accumulator of their own. The three dropped ones add up to 2^-24 of the product at most and to 2^-27.5
+// typically, so that a sum of a single product is off by up to two roundings of 2^-24 where the fp32 instructions round once;
+// a sum of many is closer to 64 bits than theirs, which they round after every second product: rel. error over reductions of 64 / 576 /
 // 4608 normal x uniform values 1.5e-7 / 4.3e-7 / 1.2e-6 there, 4.7e-8 / 1.3e-7 / 4.1e-7 here.
 // An infinity, a NaN or a value that rounds to infinity in bf16 leaves a sum that is not finite; a workgroup
 // that ends with one computes its tile again on the fp32 instructions, every wavefront its part of the reduction, and they

@@ -60,7 +60,8 @@ __device__ __forceinline__ bool any_not_finite(const f32x16 (&sum)[N]) {
   return __builtin_amdgcn_ballot_w64(!(odd == 0.f)) != 0;
 }
 
-// The partial products of one operand pair: e = 0 .. 4 the five small ones (for a sum of their own), 5 high x high.
+// The partial products of one operand pair: e = 0 .. 4 the five small ones (for a sum of their own), 5 high x high. Dropped are
+// middle x low, low x middle and low x low: |middle| <= 2^-8 and |low| <= 2^-17 of a value, so 2^-24 of the product at most.
 constexpr int kSplitW[6] = {2, 0, 1, 1, 0, 0}, kSplitX[6] = {0, 2, 1, 0, 1, 0};
 
 // Partial product e = 0 .. 5 of one step of 16 of the reduction: the five small ones into `low`, high x high into acc.

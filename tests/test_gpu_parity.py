@@ -1883,8 +1883,8 @@ def _split_chain(m, k, n, residual, bands=1):
     (1111, 260, 1028, True),
 ])
 def test_fp32_products_on_the_bf16_matrix_cores(oracle, cfg):
-    """fp32 matrix products as sums of bf16 ones: within fp32 rounding of the 64-bit result (a partial product
-    is dropped below 2^-26, an accumulator is rounded once per 16 elements), and exact on small integers; in one
+    """fp32 matrix products as sums of bf16 ones: within fp32 rounding of the 64-bit result (what is dropped of a product
+    is 2^-27.5 of it typically, an accumulator is rounded once per 16 elements), and exact on small integers; in one
     band, band by band and with all bands merged."""
     m, k, n, residual = cfg
     chain = _split_chain(m, k, n, residual)
@@ -1952,6 +1952,30 @@ def test_fp32_products_in_small_tiles(oracle, cfg):
     rest[[3, m - 1]] = False
     # (tiles with such a row are the fp32 instructions' throughout: a rounding after every second product)
     assert np.linalg.norm(dev[rest] - want[rest]) <= 2 * np.sqrt(k / 2) * 2.0 ** -24 * np.linalg.norm(want[rest])
+
+
+@pytest.mark.parametrize("cfg,name", [((1500, 200, 516), "<64, 128, 1, 4>"), ((1000, 192, 516), "<32, 64, 1, 2>")])
+def test_fp32_products_of_one_pair(cfg, name):
+    """Rows with one live element: every result is one product of fp32 values made of bf16 parts, within 2^-23 of it (2^-24 for the
+    partial products that are dropped, 2^-24 for the sum of the others)."""
+    m, k, n = cfg
+    chain = _split_chain(m, k, n, False)
+    chain.layers[0].act, chain.layers[0].has_bias = "none", False
+    t = workloads.make_row_tensors(chain, zero_bias=True, seed=83)
+    rng = np.random.Generator(np.random.PCG64(15))
+    live = rng.integers(0, k, m)
+    # mantissas of all kinds, the ones with the largest middle and low parts among them
+    value = np.ldexp(1 + rng.integers(0, 1 << 23, m) * 2.0 ** -23, rng.integers(-30, 30, m)).astype(np.float32)
+    value[:64] = np.float32(1 + 2.0 ** -8 - 2.0 ** -17 + 2.0 ** -23)
+    x = np.zeros((m, k), np.float32)
+    x[np.arange(m), live] = value
+    w = t.weights[0].copy()
+    w[:64] = np.float32(1 + 2.0 ** -8 - 2.0 ** -17 - 2.0 ** -23)
+    dev, _, names = _run_rows(chain, workloads.Tensors(x, [w], [None]))
+    assert names == {"conv_gemm_split_kernel" + name}, names
+    want = value[:, None].astype(np.float64) * w[:, live].T.astype(np.float64)
+    assert (np.abs(dev - want) <= 2.0 ** -23 * np.abs(want)).all()
+    assert np.linalg.norm(dev - want) <= 2.0 ** -24 * np.linalg.norm(want)
 
 
 @pytest.mark.parametrize("where", ["input", "weights"])
