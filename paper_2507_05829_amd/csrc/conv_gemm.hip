@@ -650,9 +650,11 @@ constexpr long kWalkers = 256;
 // 1024 (128 of them) 88 -> 93 alone but 1 396 -> 1 059 for both layers on four streams, since only the
 // 256-wide tile asks the L2s for little enough while other launches run beside it; 5422 x 984 -> 1040
 // (215 tiles of 128 x 256) 31 -> 24; 4096 x 4096 -> 1024 (512 of 128 x 64) 89 -> 43, against 53 with 128 tiles
-// of 128 x 256; 1000 x 2048 -> 512 (64 of 128 x 64) 11 there, 16 here. fp32 on its own instructions (short reductions, and layers that have
-// no parts) 3001 x 512 -> 2048 (1 504 tiles of 64 x 64) 85 -> 64 and 2048 -> 512 (376) 87 -> 78; 1500 x 1024 -> 256 (96) 18 there, 23 here; 8000 x 1000 -> 3000
-// (1 512 tiles of 128 x 128) 479 -> 432, against 455 with 64 x 64.
+// of 128 x 256; 1000 x 2048 -> 512 (64 of 128 x 64) 11 there, 16 here. fp32 on its own instructions, reductions of 64 to 191
+// elements: mid-size kernels / 64 x 64 / 128 x 128 tiles, K 64 and 188: 3001 x K -> 256 (188 tiles of 64 x 64) 5.0 / 5.2 / 11.8 and 9.0 / 7.5 /
+// 19.5, 1500 -> 1024 (384) 7.8 / 7.0 / 12.2 and 13.2 / 11.4 / 19.9, 1000 -> 512 (128) 4.2 / 5.0 / 11.6 and 8.4 / 7.0 / 19.1; 20000 -> 512
+// (628 tiles of 128 x 128) 29.4 / 23.2 / 29.0 and 56 / 43.7 / 50.6, 8000 -> 2048 (1 008) 36.9 / 35.1 / 33.8 and 71.6 / 63.6 / 63.1, 8000 -> 3000 (1 512) 51.2 /
+// 48.9 / 47.8 and 104 / 87.7 / 92.1, 16000 -> 2048 (2 000) 66.1 / 63.1 / 62.4 and 137 / 119 / 121.
 struct GemmChoice { int bm = 0, bn = 0; bool split = false; };
 constexpr long kBigTiles = 128;        // 256 x 256, bf16
 constexpr long kWideTiles = 192;       // 128 x 256, bf16

@@ -13,7 +13,7 @@
 // first window's first element: a window then starts on a 4-byte boundary (in bf16 with stride 1 every
 // second one does: an extra copy, shifted by one element, serves the others). The weights stay in
 // registers, and a wavefront takes one 32-pixel fragment at a time from the reads to the stores: sums for one
-// fragment leave room for 3 to 7 wavefronts per SIMD (all four fragments of the 8-row form: 2 to 4), whose stores and
+// fragment leave room for 2 to 7 wavefronts per SIMD (two where 7 x 7 bf16 weights of 64 channels fill the registers; all four fragments of the 8-row form: 2 to 4), whose stores and
 // products overlap. Bound by the output it writes. us for the 8-row form, before (whole tile's sums; stores of 32
 // bytes per pixel) and now: 3 x 3 stride 2 in bf16, 32 channels, 1080 x 640 outputs 19.0 -> 15.0, 64 channels, stride 1,
 // 1150 x 224 16.3 -> 12.9, fp32 3 x 640 x 640 x 64 121 -> 105. 7 x 7 in fp32 is bound by its matrix instructions.

@@ -963,8 +963,8 @@ int setup_device(lop_plan_t* P) {
     want = LOP_DEFAULT_LANES;
     // Slabs that fill most of the 256 MB Infinity Cache by themselves: two lanes, not four, whose launches would only
     // push each other's rows out of it. Where a lane is needed for copies, four are better all the same. (Inverted-residual
-    // chain layer by layer, eight images of 640 x 640, 240 MB a lane: 2 148 -> 2 041 us a call; of 512 x 512, 150 MB:
-    // 1 420 with four, 1 495 with two.)
+    // chain layer by layer, us a call with four lanes and with two: 156 MiB a lane 1 308 and 1 384, 170 MiB 1 432 and 1 498, 188 MiB 1 588
+    // and 1 618 or 1 609 and 1 606, 208 MiB 1 777 and 1 756, 219 MiB 1 865 and 1 832, 228 MiB 1 948 and 1 916, 250 MiB 2 152 and 2 050.)
     if (P->sched == ChainSched::kPerBand && !P->t.reuse && P->arena_bytes > kLaneSlabsMax && (P->flags & LOP_FLAG_NO_D2H)) want = 2;
   }
   // (chains that run on one lane each rotate over all of them, however few bands they have)
