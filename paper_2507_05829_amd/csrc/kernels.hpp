@@ -1,7 +1,7 @@
 // Launch interface of the gfx950 kernels. Every kernel works on row slabs: a tensor is
 // N x rows x W x C (NHWC) holding rows [row0, row0 + rows) of an image of height h.
 #pragma once
-#include <hip/hip_runtime.h>
+#include <hip/hip_runtime_api.h>
 
 #include <cstddef>
 #include <cstdint>
@@ -54,7 +54,7 @@ struct OpLaunch {
 // channel tile of any kernel reads rows that exist.
 constexpr int kConvCoutPad = 128;
 int conv_k_pad(int c_in, int kh, int kw, int dtype);
-__host__ __device__ inline int conv_cout_pad(int c_out) {
+inline int conv_cout_pad(int c_out) {
   const int unit = c_out > kConvCoutPad ? 2 * kConvCoutPad : kConvCoutPad;
   return (c_out + unit - 1) / unit * unit;
 }
