@@ -30,6 +30,9 @@ PEAK = {"mfma_f32": 157.3, "mfma_bf16": 2500.0, "hbm": 8000.0}   # TFLOP/s, TFLO
 MIN_TIMED_S = 0.5
 MIN_REPEATS = 5
 DENSE = ("conv_", "pointwise_", "mbconv_")   # kernel families that run on the matrix cores
+# fp32 kernels that make a product of six bf16 ones (each operand as the sum of three bf16 parts)
+PARTS = ("conv_gemm_split_kernel<", "conv_gemm_split_kernel_bands<", "conv_patch_kernel<float", "conv_patch_kernel_bands<float",
+         "conv_stem_pool_kernel<float", "conv_stem_pool_kernel_bands<float")
 
 
 def parse():
@@ -190,16 +193,30 @@ def merged_twin(case, torch, lop, workloads, a):
         return None
 
 
+def mfma_rate(kernel, dtype, bf16, f32):
+    """What the matrix cores give a kernel of a type, of their rates for bf16 and for fp32 products."""
+    if dtype == "bf16":
+        return bf16
+    return bf16 / 6 if kernel.startswith(PARTS) else f32
+
+
+def mfma_peak(kernel, dtype):
+    return mfma_rate(kernel, dtype, PEAK["mfma_bf16"], PEAK["mfma_f32"])
+
+
+def ridge(kernel, dtype):
+    """Operations per byte from which on the matrix cores bound a kernel."""
+    return mfma_peak(kernel, dtype) * 1e12 / (PEAK["hbm"] * 1e9)
+
+
 def launch_rows(case, iters):
     """Every (layer, band) launch of one chain, timed on one stream, one lane, with a start and
     a stop HIP event attached to the dispatch itself (the kernel's own duration, as a
     profiler's kernel trace reports it), with its algorithmic work and the roofline that
-    bounds it: a dense convolution is priced against the matrix cores when its arithmetic
-    intensity is at or above the ridge of its type, everything else against HBM."""
+    bounds it: a dense convolution is priced against the instructions of the matrix cores it runs on
+    when its arithmetic intensity is at or above their ridge, everything else against HBM."""
     plan, dtype = case.plan, case.chain.dtype
     ms, fin = plan.profile_chain(case.d_in, case.d_out[0], iters)
-    mf_peak = PEAK["mfma_bf16"] if dtype == "bf16" else PEAK["mfma_f32"]
-    ridge = mf_peak * 1e12 / (PEAK["hbm"] * 1e9)
     rows = []
     for l in range(plan.n_layers):
         op = getattr(case.chain.layers[l], "op", "rowwise")
@@ -216,16 +233,16 @@ def launch_rows(case, iters):
             us = float(ms[b, l]) * 1e3
             fus = float(fin[b, l]) * 1e3 if slices > 1 else 0.0
             ai = flop / max(byts, 1.0)
-            bound = "mfma" if name.startswith(DENSE) and ai >= ridge else "hbm"
+            bound = "mfma" if name.startswith(DENSE) and ai >= ridge(name, dtype) else "hbm"
             t = (us + fus) * 1e-6
             ach = flop / t / 1e12 if bound == "mfma" else byts / t / 1e9
             rows.append(dict(layer=l, band=b, op=op, kernel=name, k_slices=slices, us=round(us, 2),
                              finish_us=round(fus, 2), gflop=round(flop / 1e9, 4), mbytes=round(byts / 1e6, 4),
                              ai=round(ai, 1), bound=bound, achieved=round(ach, 2),
                              unit="TFLOP/s" if bound == "mfma" else "GB/s",
-                             frac=round(ach / (mf_peak if bound == "mfma" else PEAK["hbm"]), 4),
+                             frac=round(ach / (mfma_peak(name, dtype) if bound == "mfma" else PEAK["hbm"]), 4),
                              _flop=flop, _bytes=byts))
-    return rows, ridge, mf_peak
+    return rows
 
 
 def kernel_groups(rows, dtype):
@@ -256,19 +273,20 @@ def kernel_groups(rows, dtype):
     return out
 
 
-def dominant_roofline(groups, ridge, mf_peak, tag):
+def dominant_roofline(groups, dtype, tag):
     """Roofline object of the kernel instance with the largest total time that does
     algorithmic work, priced by the aggregate arithmetic intensity of its launches."""
     k = next(g for g in groups if g["_flop"] > 0 or g["_bytes"] > 0)
     ai = k["_flop"] / max(k["_bytes"], 1.0)
-    if k["name"].startswith(DENSE) and ai >= ridge:
-        roof = dict(bound="mfma", achieved=k["tflops"], peak=mf_peak, unit="TFLOP/s",
-                    frac=round(k["tflops"] / mf_peak, 4))
+    if k["name"].startswith(DENSE) and ai >= ridge(k["name"], dtype):
+        peak = mfma_peak(k["name"], dtype)
+        roof = dict(bound="mfma", achieved=k["tflops"], peak=round(peak, 1), unit="TFLOP/s",
+                    frac=round(k["tflops"] / peak, 4))
     else:
         roof = dict(bound="hbm", achieved=k["gbs"], peak=PEAK["hbm"], unit="GB/s",
                     frac=round(k["gbs"] / PEAK["hbm"], 4))
     roof.update(traffic=measured_traffic(tag, k["name"]), kernel=k["name"], avg_us=k["avg_us"],
-                launches_per_chain=k["launches"], ai_flop_per_byte=round(ai, 1), ridge=round(ridge, 1),
+                launches_per_chain=k["launches"], ai_flop_per_byte=round(ai, 1), ridge=round(ridge(k["name"], dtype), 1),
                 algorithmic_bytes_per_launch=round(k["_bytes"] / k["launches"]),
                 algorithmic_flop_per_launch=round(k["_flop"] / k["launches"]))
     return roof
@@ -361,21 +379,23 @@ def measure(torch, lop, workloads, name, mode, a, steps, warmup, link_gbs, nofus
     res["d2h"]["single_request_extra_us"] = round(extra_us, 2)
     res["d2h"]["hidden_single_vs_link_rate"] = round(1.0 - max(0.0, extra_us) / copy_us_link, 4)
     twin = merged_twin(case, torch, lop, workloads, a)
-    rows, ridge, mf_peak = launch_rows(twin or case, a.profile_iters)
+    rows = launch_rows(twin or case, a.profile_iters)
     res["table_times"] = "merged launches" if twin or mode == "batched" else "launches of single bands"
     if twin:
         twin.close()
     groups = kernel_groups(rows, chain.dtype)
     res["kernels"] = strip(groups)
-    res["roofline"] = dominant_roofline(groups, ridge, mf_peak, f"{case.tag().replace(':', '_')}_{mode}")
+    res["roofline"] = dominant_roofline(groups, chain.dtype, f"{case.tag().replace(':', '_')}_{mode}")
     # dense-convolution utilisation of the matrix cores over the chain: algorithmic FLOP of the
-    # dense convolutions (executed, halo recompute included) over their kernel time
+    # dense convolutions (executed, halo recompute included) over their kernel time, and the share of
+    # that time which the operations take at the peak of the instructions each launch runs on
     dense = [r for r in rows if r["kernel"].startswith(DENSE)]
     t_dense = sum(r["us"] + r["finish_us"] for r in dense) * 1e-6
     if t_dense > 0:
         tf = sum(r["_flop"] for r in dense) / t_dense / 1e12
+        busy = sum(r["_flop"] / (mfma_peak(r["kernel"], chain.dtype) * 1e12) for r in dense)
         res["dense_conv"] = dict(kernel_time_us=round(t_dense * 1e6, 1), executed_tflops=round(tf, 2),
-                                 mfma_peak_tflops=mf_peak, frac_of_mfma_peak=round(tf / mf_peak, 4))
+                                 mfma_peak_tflops=round(tf * t_dense / busy, 1), frac_of_mfma_peak=round(busy / t_dense, 4))
     hbm = [r for r in rows if not r["kernel"].startswith(DENSE)]
     t_hbm = sum(r["us"] for r in hbm) * 1e-6
     if t_hbm > 0:
@@ -401,7 +421,7 @@ def one_band_reference(torch, lop, workloads, name, mode, a, nofuse=False, table
     out = dict(images_per_s=round(case.images * chains / med, 2), ms_per_chain=round(med / chains * 1e3, 5),
                single_request=single_request(case, 15))
     if tables:
-        rows, _, _ = launch_rows(case, a.profile_iters)
+        rows = launch_rows(case, a.profile_iters)
         out["launches"] = strip(rows)
     case.close()
     return out
@@ -465,7 +485,7 @@ def main():
         case = Case(torch, lop, workloads, name, a.mode, a, a.bands, nf == "nofuse")
         twin = merged_twin(case, torch, lop, workloads, a) or case
         twin.plan.profile_chain(twin.d_in, twin.d_out[0], 3)
-        rows, _, _ = launch_rows(twin, a.profile_iters)
+        rows = launch_rows(twin, a.profile_iters)
         print(json.dumps(dict(workload=case.tag(), mode=a.mode, n_bands=case.plan.n_bands,
                               kernels=strip(kernel_groups(rows, case.chain.dtype)), launches=strip(rows))))
         case.close()
@@ -488,7 +508,7 @@ def main():
             "graph_node_floor_us": round(c.graph_node_floor_us, 2)}
 
     def against_measured(roof, dtype):
-        m = c.hbm_copy_gbs if roof["bound"] == "hbm" else (c.mfma_bf16_tflops if dtype == "bf16" else c.mfma_f32_tflops)
+        m = c.hbm_copy_gbs if roof["bound"] == "hbm" else mfma_rate(roof["kernel"], dtype, c.mfma_bf16_tflops, c.mfma_f32_tflops)
         roof["measured_peak"] = round(m, 1)
         roof["frac_of_measured"] = round(roof["achieved"] / m, 4)
         # what a launch of this size could reach at most: its work at the published peak behind
@@ -549,7 +569,7 @@ def main():
                    "hip_graph": bool(a.graph), "lanes": a.lanes or "default"},
         "roofline": roof,
         # the other two figures the metric names: algorithmic FLOP of the dense convolutions over
-        # their kernel time against the matrix-core peak of the type, and the share of the
+        # their kernel time against the matrix-core peak of the instructions they run on, and the share of the
         # output's link time (bytes / measured D2H rate) that did not lengthen the chain
         "mfma_utilisation": dense.get("frac_of_mfma_peak"),
         # (null when the exposed time is within the spread of the repeats: a 49 KiB output per
