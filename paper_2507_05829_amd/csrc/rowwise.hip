@@ -322,6 +322,7 @@ hipError_t launch_dw3(const RowParams* ps, int n, hipStream_t s, KernelEvents* e
     const RowParams& p = ps[b];
     if (p.R <= 0 || p.N <= 0) continue;
     const int rpt = dw_rows_per_thread(p.sh), cols = std::max(1, 256 / (p.C / VEC)), col_blocks = (p.W_out + cols - 1) / cols;
+    if (col_blocks > kDwBlocks) return hipErrorInvalidValue;   // (not even one chunk of rows)
     const int rows = (int)std::min((long)p.R, kDwBlocks / col_blocks * rpt);
     const int images = (int)std::min((long)p.N, kDwBlocks / ((long)col_blocks * ((rows + rpt - 1) / rpt)));
     const size_t x_img = (size_t)p.x_rows * p.W * p.C * sizeof(T), y_img = (size_t)p.y_rows * p.W_out * p.C * sizeof(T);

@@ -234,7 +234,8 @@ def poison():
 
 def grids():
     """Depthwise layers whose bands' launches fit the grid, and whose launch over all rows would not, and of more
-    images than a launch takes (the stand-in ends the process on a grid that the runtime refuses)."""
+    images than a launch takes (the stand-in ends the process on a grid that the runtime refuses). One whose single row is more
+    than a launch takes is an error."""
     bad = []
     for dtype, shape, s in (("f32", (600, 4, 1030, 2), 1), ("bf16", (3000, 8, 90, 3), 2), ("f32", (1, 4, 600000, 1), 1),
                             ("bf16", (9000000, 4, 2, 1), 1), ("bf16", (17000000, 4, 1, 1), 1)):
@@ -245,6 +246,12 @@ def grids():
             got = run_both_ways(chain, flags)
             if got != (0, 0):
                 bad.append((shape, flags, got))
+    for flags in (0, lop.LOP_FLAG_REUSE):
+        chain = workloads.Chain("depthwise", (1, 1024, 2, 1 << 24), "bf16", 2)
+        chain.add(workloads.DWCONV, 1024, 1024, 3, 1, 1, 1, "relu6")
+        got = run_both_ways(chain, flags)
+        if 0 in got:
+            bad.append((chain.name, flags, got))
     return bad
 
 
