@@ -2109,7 +2109,7 @@ def test_first_layer_with_its_pooling(oracle, cfg, mode):
     ((1, 41, 37), 8, 32),       # ragged groups of pixels, several images' worth of bands in a launch
     ((3, 22, 61), 3, 32),       # groups that span two images
     ((5, 6, 3), 2, 64),         # fewer pixels of an image and band than a group
-    ((1, 200, 333), 16, 32),    # as many bands as a launch takes; enough groups for four a wavefront
+    ((1, 200, 333), 16, 32),    # as many bands as a launch takes
 ])
 def test_streaming_layers_merged_over_bands(oracle, cfg):
     """1x1 streaming and 3x3 depthwise layers outside a fused block: one launch per layer for all bands,
