@@ -139,6 +139,11 @@ bool narrow_takes_sibling(const OpLaunch* convs, const OpLaunch* sibs, int n);
 hipError_t launch_narrow_siblings(const OpLaunch* convs, const OpLaunch* sibs, int n, hipStream_t stream, KernelEvents* ev);
 bool siblings_apply(const OpLaunch* convs, const OpLaunch* sibs, int n);
 hipError_t launch_siblings(const OpLaunch* convs, const OpLaunch* sibs, int n, hipStream_t stream, KernelEvents* ev = nullptr);
+// Two 3 x 3 convolutions of kPairChannels channels, the second the only reader of the first, as one launch: whether a group of bands
+// takes it (descriptors with slabs and rows) and the launch (of the second one's rows, and its y2).
+constexpr int kPairChannels = 16;
+bool pair_applies(const OpLaunch* firsts, const OpLaunch* seconds, int n);
+hipError_t launch_pair(const OpLaunch* firsts, const OpLaunch* seconds, int n, hipStream_t stream, KernelEvents* ev = nullptr);
 // The matrix-product kernel of 1 x 1 convolutions: whether a group of bands takes it, the launch and
 // its kernel name.
 bool gemm_applies(const OpLaunch* Ls, int n);

@@ -1194,6 +1194,18 @@ bool siblings(const lop_plan_t* P, int l) {
   return !F.away[l] && !F.away[l + 1] && F.head[l] < 0 && F.head[l + 1] < 0 && !(P->flags & LOP_FLAG_NO_FUSE);
 }
 
+// Whether layers l and l + 1 are two convolutions of which the second is the only reader of the first, which a merged
+// chain computes in one launch where a kernel takes both. The rows between them are then in no buffer.
+bool pair(const lop_plan_t* P, int l) {
+  const lop::Tables& t = P->t;
+  if (l + 1 >= t.n_layers() || (P->flags & LOP_FLAG_NO_FUSE)) return false;
+  const lop_layer_t &a = t.layers[l].d, &b = t.layers[l + 1].d;
+  if (a.op != LOP_CONV2D || b.op != LOP_CONV2D || b.input_from != l || a.c_out != lop::kPairChannels) return false;
+  if (a.residual_from != LOP_NO_RESIDUAL || b.residual_from != LOP_NO_RESIDUAL || last_reader(P, l) != l + 1) return false;
+  const Fusion& F = P->fuse_chain;
+  return !F.away[l] && !F.away[l + 1] && F.head[l] < 0 && F.head[l + 1] < 0;
+}
+
 // The kernels of a chain whose launches are merged over the bands (kGrouped, kWhole), on one
 // stream, with the scratch set by the caller. y2: where the last launch also stores its rows.
 int enqueue_merged_kernels(lop_plan_t* P, const void* d_in, void* d_out, hipStream_t cs, void* y2) {
@@ -1216,6 +1228,16 @@ int enqueue_merged_kernels(lop_plan_t* P, const void* d_in, void* d_out, hipStre
         if (const int rc = begin_pass(); rc != LOP_OK) return rc;
         const ChainPass pass(P, i, images, rows);
         for (int l = 0; l < nl; ++l) {
+          if (pair(P, l)) {
+            const lop::OpLaunch a = make_launch(P, whole, l, d_in, d_out);
+            lop::OpLaunch q = make_launch(P, whole, l + 1, d_in, d_out);
+            q.y2 = l + 1 == nl - 1 ? second : nullptr;
+            if (lop::pair_applies(&a, &q, 1)) {
+              LOP_HIP(lop::launch_pair(&a, &q, 1, cs));
+              ++l;
+              continue;
+            }
+          }
           if (siblings(P, l)) {
             const lop::OpLaunch a = make_launch(P, whole, l, d_in, d_out), q = make_launch(P, whole, l + 1, d_in, d_out);
             if (a.out_hi > a.out_lo && lop::siblings_apply(&a, &q, 1)) {
@@ -1234,6 +1256,16 @@ int enqueue_merged_kernels(lop_plan_t* P, const void* d_in, void* d_out, hipStre
       const int end = std::min(nb, b + P->group);
       if (const int rc = begin_pass(); rc != LOP_OK) return rc;
       for (int l = 0; l < nl; ++l) {
+        if (end - b <= lop::kMaxBandsPerLaunch && pair(P, l)) {
+          std::vector<lop::OpLaunch> as, qs, none;
+          batched_group(P, l, b, end, d_in, d_out, nullptr, &as, &none);
+          batched_group(P, l + 1, b, end, d_in, d_out, l + 1 == nl - 1 ? second : nullptr, &qs, &none);
+          if (as.size() == qs.size() && lop::pair_applies(as.data(), qs.data(), (int)as.size())) {
+            LOP_HIP(lop::launch_pair(as.data(), qs.data(), (int)as.size(), cs));
+            ++l;
+            continue;
+          }
+        }
         if (end - b <= lop::kMaxBandsPerLaunch && siblings(P, l)) {
           std::vector<lop::OpLaunch> as, qs, none;
           batched_group(P, l, b, end, d_in, d_out, nullptr, &as, &none);

@@ -2191,3 +2191,37 @@ def test_depthwise_layers_of_more_workgroups_than_a_launch_takes(n, h, bands):
             if 0 <= r + a - 1 < h:
                 want = want + x[:, r + a - 1].float() * wd[:, a]
         assert torch.equal(y[:, r], want.relu().to(torch.bfloat16))
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("shape,bands,flags,acts", [
+    ((1, 16, 1, 1), 1, 0, ("relu", "relu")),                                     # one pixel: padding alone around it
+    ((1, 16, 8, 8), 2, 0, ("relu", "relu")), ((1, 16, 9, 17), 3, 0, ("none", "relu6")),   # a tile, and one pixel more
+    ((3, 16, 33, 31), 5, 0, ("relu6", "none")), ((1, 16, 40, 50), 16, lop.LOP_FLAG_GRAPH, ("relu", "relu")),
+    ((2, 16, 37, 70), 4, lop.LOP_FLAG_REUSE, ("relu", "relu")), ((1, 16, 61, 45), 4, lop.LOP_FLAG_BATCH_BANDS, ("relu", "relu")),
+    ((1, 16, 190, 204), 3, 0, ("relu", "relu")),                                 # more tiles than compute units
+])
+def test_two_convolutions_as_one_launch(oracle, shape, bands, flags, acts, dtype):
+    """Pairs of 16-channel 3 x 3 convolutions, alone and between other layers (where the bands have slabs of their own), with
+    small integers (exact in any order) and with random values; a pair whose first result is read twice runs as two."""
+    for around in ("alone", "between", "read twice"):
+        chain = workloads.Chain("pair", shape, dtype, bands)
+        if around == "between":
+            chain.add(workloads.CONV, 16, 16, 1, 1, 0, act="relu")
+        chain.add(workloads.CONV, 16, 16, 3, 1, 1, act=acts[0])
+        chain.add(workloads.CONV, 16, 16, 3, 1, 1, act=acts[1])
+        if around == "between":
+            chain.add(workloads.MAXPOOL, 16, 16, 3, 1, 1)
+        if around == "read twice":
+            chain.add(workloads.CONV, 16, 32, 1, 1, 0, act="none")
+            chain.add(workloads.CONV, 16, 32, 1, 1, 0, act="none", input_from=len(chain.layers) - 3, residual_from=len(chain.layers) - 1)
+        ints = workloads.small_int_tensors(chain)
+        got, host = run_gpu(chain, ints, flags=flags | lop.LOP_FLAG_POISON_SCRATCH)
+        want = oracle.run_chain(chain, ints)
+        if dtype == "f32":   # (bf16 rounds between the layers: a tie may go either way of the oracle's double)
+            assert np.array_equal(got, want) and np.array_equal(host, want), around
+        rand = workloads.make_tensors(chain, zero_bias=False)
+        got, host = run_gpu(chain, rand, flags=flags)
+        want = oracle.run_chain(chain, rand)
+        assert rel_err(got, want) <= TOL[dtype], (around, rel_err(got, want))
+        assert np.array_equal(got, host), around
