@@ -136,7 +136,9 @@ typedef struct {
 #define LOP_FLAG_GRAPH 4u     /* lop_run_chain (without timing) captures its launches and copies
                                  into a HIP graph on the first call for a given (d_in, d_out,
                                  h_out) and replays it afterwards; the graph joins the copies,
-                                 so compute_stream then also waits for them              */
+                                 so compute_stream then also waits for them. A chain of a
+                                 few merged launches is enqueued by every call instead, which
+                                 is faster there                                          */
 
 /* Build a plan: validate the chain, infer shapes, split the last layer's output rows
  * into n_bands intervals (first H mod B bands one row longer; trailing bands may be

@@ -1391,6 +1391,24 @@ int launch_graph(lop_plan_t* P, const void* d_in, void* d_out, void* h_out, hipS
   return LOP_OK;
 }
 
+// The launches of a merged chain (finish kernels and layers that share a launch aside).
+long merged_launches(const lop_plan_t* P) {
+  const int nl = P->t.n_layers(), nb = P->t.n_bands, n = P->t.in.n;
+  const long layers = nl - std::count(P->fuse_chain.away.begin(), P->fuse_chain.away.end(), (char)1);
+  long per_pass = (nb + P->group - 1) / P->group;
+  if (P->sched == ChainSched::kGrouped) {
+    per_pass = 0;
+    for (int b = 0; b < nb; b += P->group) per_pass += (std::min(P->group, nb - b) + lop::kMaxBandsPerLaunch - 1) / lop::kMaxBandsPerLaunch;
+  }
+  return layers * per_pass * ((n + P->images - 1) / P->images);
+}
+// Merged chains of at most this many launches are enqueued by every call, also where the plan asks for graphs: a graph's
+// launch costs 12 to 15 us of host time however few nodes it has, one of a kernel 2 to 3, and a stream gets through a graph's
+// kernels 6 us later. us a call, graph -> kernels, with calls in flight, on one caller's stream, and alone: one launch (two layers of 16
+// channels) 14.0 -> 4.8, 15.8 -> 8.5, 33 -> 18; two (3000 x 512 -> 1024 -> 512 bf16) 14.8 -> 14.3, 31.5 -> 25.2, 39 -> 34 (host 14.6 ->
+// 6.6); with six (inverted residuals, 200 x 200) 25.9 -> 25.5, 84 -> 80, 91 -> 89, but 16 -> 23 us of the host.
+constexpr long kEagerLaunches = 4;
+
 // A merged chain's kernels as a graph: captured on lane `lane`'s own stream (with that lane's
 // scratch), replayed on `s`.
 int launch_graph_merged(lop_plan_t* P, int lane, const void* d_in, void* d_out, void* direct, hipStream_t s) {
@@ -1438,7 +1456,7 @@ int run_merged(lop_plan_t* P, const void* d_in, void* d_out, void* h_out, hipStr
   if ((rc = stamp(P->ev_c0)) != LOP_OK) return rc;
   const bool copy = h_out && !(P->flags & LOP_FLAG_NO_D2H);
   void* const direct = copy ? direct_host_target(P, P->sched == ChainSched::kWhole ? P->t.whole() : 0, h_out, true) : nullptr;
-  rc = (P->flags & LOP_FLAG_GRAPH) && !timing ? launch_graph_merged(P, lane, d_in, d_out, direct, s)
+  rc = (P->flags & LOP_FLAG_GRAPH) && !timing && merged_launches(P) > kEagerLaunches ? launch_graph_merged(P, lane, d_in, d_out, direct, s)
                                               : enqueue_chain_merged(P, L, d_in, d_out, direct, s);
   if (rc != LOP_OK) return rc;
   if ((rc = stamp(P->ev_c1)) != LOP_OK || (rc = stamp(P->ev_d0)) != LOP_OK) return rc;
