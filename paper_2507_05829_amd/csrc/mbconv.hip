@@ -7,8 +7,9 @@
 // and read back twice; here it never leaves the compute unit. A workgroup owns 8 x 16
 // output pixels (16 x 16 in large launches of stride 1: see mb_rows) and walks over the expanded channels in chunks of 32, all three operators on the
 // matrix cores:
-//   expand   32 x 32 x 16 products, pixels as rows, so that a lane ends with four neighbouring pixels of
-//            one channel -> bias, activation, one rounding to bf16 -> LDS, channel by channel. Pixels
+//   expand   16 x 16 x 32 products (the whole reduction in one), pixels as rows, so that a lane ends with four neighbouring
+//            pixels of one channel; 16 pixels' instructions run under the vector instructions of the 16 before them
+//            (32 x 32 x 16 products tile by tile: 513 -> 496 us for eight images in eight bands) -> bias, activation, one rounding to bf16 -> LDS, channel by channel. Pixels
 //            outside the image are zero there (the depthwise operator pads its input, i.e. the
 //            expanded tensor, not the block's input);
 //   depthwise  4 x 4 x 4 products, 16 channels at once, one per block of the instruction: four
@@ -33,6 +34,7 @@
 #include <algorithm>
 #include <cstdio>
 #include <cstring>
+#include <type_traits>
 
 #include "act.hpp"
 #include "kernels.hpp"
@@ -44,6 +46,7 @@ namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
@@ -54,7 +57,7 @@ struct MbParams {
   const __bf16* x;
   __bf16* y;
   const __bf16* res;
-  const void* we;     // expand weights in operand order, a tile of 32 channels every ke_pad / 16 steps
+  const void* we;     // expand weights in the operand order of 16 x 16 tiles, a tile of 16 channels every ke_pad / 32 steps
   const float* be;
   const void* bands;  // depthwise weights as bands (mbconv_pack_bands)
   const float* bd;
@@ -75,6 +78,10 @@ __device__ __forceinline__ f32x16 mma_bf16(const u32x4& a, const u32x4& b, const
                                                  __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
+__device__ __forceinline__ f32x4 mma16_bf16(const u32x4& a, const u32x4& b, const f32x4& c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+
 // four bf16 (8 bytes) <-> four floats
 __device__ __forceinline__ void unpack4(const u32x2& v, float* f) {
   f[0] = __builtin_bit_cast(float, v.x << 16);
@@ -90,7 +97,6 @@ __device__ __forceinline__ u32x2 pack4(const float* f) {
 }
 
 typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // Of 16 lanes, lane i gets value i % 4 of the four that lanes i / 4, i / 4 + 4, + 8 and + 12 point at.
 __device__ __forceinline__ u32x2 transposed_read(const unsigned char* at) {
@@ -112,6 +118,9 @@ struct MbTile {
   // lets every half wavefront's access touch each bank once.
   static constexpr int EPITCH = MT_E * 64 + 8;
   static constexpr int DPITCH = OP * 2 + 8;
+  // The quads of an expand tile's eight that 16 pixels of it (half h) are, in the order of the operand's rows: two that half a
+  // wavefront stores at once lie four apart, which with 16 channels each touches every bank of LDS once.
+  __host__ __device__ static constexpr int quad(int h, int j) { return 2 * h + (j >> 1) + 4 * (j & 1); }
   // Row of the idx-th quad of a column: with stride 2 the even rows first, so that the rows under
   // neighbouring output rows are neighbours.
   __host__ __device__ static constexpr int row(int idx) { return S == 1 ? idx : idx <= TH ? 2 * idx : 2 * (idx - TH) - 1; }
@@ -156,17 +165,15 @@ __device__ __forceinline__ void mbconv_body(const MbParams& p, int bid) {
   // layout (lane = pixel, two halves of 8 channels per step of 16), kept for all chunks
   u32x4 xa[MPW][2];
 #pragma unroll
-  for (int i = 0; i < MPW; ++i) {
-    const int q = (wave + 4 * i) * 8 + (px >> 2), qx = q / EH;
-    const int ih = ih_base + G::row(q - qx * EH), iw = iw_base + qx * 4 + (px & 3);
-    xa[i][0] = u32x4{0u, 0u, 0u, 0u};
-    xa[i][1] = u32x4{0u, 0u, 0u, 0u};
-    if (q < NQ && ih >= ih_lo && ih < ih_hi && iw >= 0 && iw < p.W) {
-      const __bf16* src = p.x + ((size_t)(n * p.x_rows + ih - p.x_row0) * p.W + iw) * kMbC + kg * 8;
-      xa[i][0] = *(const u32x4*)src;
-      xa[i][1] = *(const u32x4*)(src + 16);
+  for (int i = 0; i < MPW; ++i)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int q = (wave + 4 * i) * 8 + G::quad(h, (lane & 15) >> 2), qx = q / EH;
+      const int ih = ih_base + G::row(q - qx * EH), iw = iw_base + qx * 4 + (lane & 3);
+      xa[i][h] = u32x4{0u, 0u, 0u, 0u};
+      if (q < NQ && ih >= ih_lo && ih < ih_hi && iw >= 0 && iw < p.W)
+        xa[i][h] = *(const u32x4*)(p.x + ((size_t)(n * p.x_rows + ih - p.x_row0) * p.W + iw) * kMbC + (lane >> 4) * 8);
     }
-  }
 
   // weights of a chunk: expand, the depthwise bands of this wavefront's 16 channels, project, all in the order of the
   // lanes (an access of four lanes to one 64-byte line each costs the vector cache four times as much); each part is fetched for the next chunk when this one is done with it
@@ -177,8 +184,8 @@ __device__ __forceinline__ void mbconv_body(const MbParams& p, int bid) {
   const u32x4* const wp_at = (const u32x4*)p.wp + lane;
   const s16x4* const wd_at = (const s16x4*)p.bands + chalf * (3 * KS * 64) + lane;
   auto fetch_expand = [&](int c) __attribute__((always_inline)) {
-    we[0] = we_at[(size_t)c * p.e_steps * 64];
-    we[1] = we_at[(size_t)c * p.e_steps * 64 + 64];
+    we[0] = we_at[(size_t)(2 * c) * p.e_steps * 64];
+    we[1] = we_at[(size_t)(2 * c + 1) * p.e_steps * 64];
   };
   auto fetch_depthwise = [&](int c) __attribute__((always_inline)) {
 #pragma unroll
@@ -221,7 +228,8 @@ __device__ __forceinline__ void mbconv_body(const MbParams& p, int bid) {
 
   // expand: stores to the slot of channel px; depthwise: row lane % 4 of this wavefront's four, channel slot of its block of
   // lanes; project: a transposing read gives the lane four slots of its pixel (16 lanes read 4 slots x 4 quads)
-  unsigned char* const eout = E_s + channel_slot(px) * EPITCH + kg * 8;
+  unsigned char* const eout = E_s + channel_slot(lane & 15) * EPITCH + (wave * 8 + G::quad(0, lane >> 4)) * 8;
+  static_assert(channel_slot(16) == 4 && channel_slot(31) == channel_slot(15) + 4, "the second 16 channels lie 4 slots further");
   const int dslot = dw_slot(lane >> 2, chalf), drow = rgroup * 4 + (lane & 3);
   const unsigned char* const ewin = E_s + dslot * EPITCH + drow * 8;
   unsigned char* const dout = D_s + dslot * DPITCH + drow * 8;
@@ -230,31 +238,43 @@ __device__ __forceinline__ void mbconv_body(const MbParams& p, int bid) {
   for (int c = 0; c < p.nch; ++c) {
     const int cn = min(c + 1, p.nch - 1);
     // ---- expand
-    const float eb = bias_s[0][c * 32 + px];
-    f32x16 ebias;
+    f32x4 ebias[2];
 #pragma unroll
-    for (int k = 0; k < 16; ++k) ebias[k] = eb;
+    for (int t = 0; t < 2; ++t) {
+      const float eb = bias_s[0][c * 32 + t * 16 + (lane & 15)];
+      ebias[t] = f32x4{eb, eb, eb, eb};
+    }
+    // units of 16 pixels x 32 channels
+    auto multiply = [&](int u, f32x4 (&a)[2]) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < MPW; ++i) {
-      const int mt = wave + 4 * i;
-      if (MT_E % 4 != 0 && i == MPW - 1 && mt >= MT_E) continue;
-      f32x16 a = mma_bf16(xa[i][0], we[0], ebias);
-      a = mma_bf16(xa[i][1], we[1], a);
-      u32x2 pk[4];
+      for (int t = 0; t < 2; ++t) a[t] = mma16_bf16(xa[u / 2][u % 2], we[t], ebias[t]);
+    };
+    auto finish = [&](int u, const f32x4 (&a)[2], auto masked) __attribute__((always_inline)) {
+      if (MT_E % 4 != 0 && u / 2 == MPW - 1 && wave + 4 * (u / 2) >= MT_E) return;
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
+      for (int t = 0; t < 2; ++t) {
         float v[4];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) v[k] = clamp_act(a[g * 4 + k], p.ce);
-        pk[g] = pack4(v);
+        for (int k = 0; k < 4; ++k) v[k] = clamp_act(a[t][k], p.ce);
+        u32x2 pk = pack4(v);
+        if constexpr (masked) pk &= mask_s[(wave + 4 * (u / 2)) * 8 + G::quad(u % 2, lane >> 4)];   // padding of the depthwise operator
+        *(u32x2*)(eout + t * 4 * EPITCH + (u / 2 * 32 + u % 2 * 2) * 8) = pk;
       }
-      if (!inside) {  // padding of the depthwise operator
+    };
+    // (a tile's matrix instructions run under the vector instructions of the one before it; the branch on `inside` around all
+    // of them, not in each: blocks of code are scheduled one by one)
+    auto expand = [&](auto masked) __attribute__((always_inline)) {
+      f32x4 a[2][2];
+      multiply(0, a[0]);
 #pragma unroll
-        for (int g = 0; g < 4; ++g) pk[g] &= mask_s[mt * 8 + 2 * g + kg];
+      for (int u = 0; u < 2 * MPW; ++u) {
+        if (u + 1 < 2 * MPW) multiply(u + 1, a[(u + 1) & 1]);
+        finish(u, a[u & 1], masked);
+        __builtin_amdgcn_sched_barrier(0);   // (all tiles' sums at once do not fit the registers)
       }
-#pragma unroll
-      for (int g = 0; g < 4; ++g) *(u32x2*)(eout + (mt * 8 + 2 * g) * 8) = pk[g];
-    }
+    };
+    if (inside) expand(std::false_type{});
+    else expand(std::true_type{});
     fetch_expand(cn);
     barrier();
 
@@ -284,6 +304,7 @@ __device__ __forceinline__ void mbconv_body(const MbParams& p, int bid) {
           for (int k = 0; k < 4; ++k) v[k] = clamp_act(d[b][k], p.cd);
           *(u32x2*)(dout + (b * TH + r * 8) * 8) = pack4(v);
         }
+        if (RG > 1) __builtin_amdgcn_sched_barrier(0);
       }
     }
     barrier();
@@ -378,7 +399,7 @@ void mbconv_pack_bands(const float* w, int c, int s, unsigned short* dst) {
 // slabs are not looked at) can run as one mbconv_kernel launch.
 bool mbconv_applies(const OpLaunch& e, const OpLaunch& d, const OpLaunch& p) {
   if (e.dtype != LOP_BF16 || !is_pointwise(e) || !is_pointwise(p)) return false;
-  if (e.x.c != kMbC || p.y.c != kMbC) return false;
+  if (e.x.c != kMbC || p.y.c != kMbC || !e.wd16) return false;
   if (e.y.c % 32 != 0 || e.y.c > kMbMaxMid || e.y.c != d.x.c || d.x.c != p.x.c) return false;
   if (d.op != LOP_DWCONV2D || d.kh != 3 || d.kw != 3 || d.ph != 1 || d.pw != 1 || d.dh != 1 ||
       d.dw != 1 || d.sh != d.sw || (d.sh != 1 && d.sh != 2))
@@ -412,10 +433,10 @@ namespace {
 MbParams make_mbconv(const OpLaunch& e, const OpLaunch& d, const OpLaunch& p, int th) {
   MbParams q;
   q.x = (const __bf16*)e.x.ptr; q.y = (__bf16*)p.y.ptr; q.res = (const __bf16*)p.res.ptr;
-  q.we = e.wd; q.be = e.bias;
+  q.we = e.wd16; q.be = e.bias;
   q.bands = (const float*)d.w + 9 * d.x.c; q.bd = d.bias;
   q.wp = p.wd; q.bp = p.bias;
-  q.e_steps = e.k_pad / 16;
+  q.e_steps = e.k_pad / 32;
   q.x_row0 = e.x.row0; q.x_rows = e.x.rows; q.H = e.x.h; q.W = e.x.w;
   q.y_row0 = p.y.row0; q.y_rows = p.y.rows; q.W_out = p.y.w;
   q.r_row0 = p.res.row0; q.r_rows = p.res.rows;
