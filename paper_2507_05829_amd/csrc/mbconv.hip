@@ -20,13 +20,16 @@
 //            from where the projection reads it transposed;
 //   project  32 x 32 x 16 products: adds the chunk's contribution to the 32 output channels
 //            (accumulators stay in registers over the chunks).
-// What bounds it: the vector ALUs (clamps and conversions of the expanded values, once each) and the
-// vector cache, about equally; the matrix cores are busy a quarter of the time. Weights are read in the
+// What bounds it: a wavefront's instructions one after another, with three wavefronts on a SIMD (LDS holds no more): the vector
+// ALUs are busy half of the time, LDS a little more, the vector cache half, the matrix cores a quarter. Leaving out one
+// kind saves its share: the weights' loads 13 %, the projection 9, the depthwise products 6, the activations of the
+// expanded values 5, the barriers 2. Weights are read in the
 // order of the lanes, straight from the cache; barriers wait for LDS only, so that the next chunk's weights
-// stay in flight; rows and channels lie in LDS in an order that has no bank conflicts. Four images of
-// 640 x 640 through six blocks: 583 -> 406 us (first block, stride 2: 92 us; second: 53 us). What came
+// stay in flight; rows and channels lie in LDS in an order that has no bank conflicts; the projection's operands come out of LDS
+// while the next chunk is expanded (with this and no bounds to check away from the borders eight images of 640 x 640
+// through six blocks, 496 -> 482 us alone with shared rows, 365 -> 361 in flight). What came
 // before: diagonal 32 x 32 x 16 products for the depthwise part (three times the matrix cycles, diagonals
-// built on the vector ALUs); weights read row by row, four cache lines per four lanes, cost 509 us.
+// built on the vector ALUs); weights read row by row, four cache lines per four lanes, cost a quarter more.
 // The roundings are the ones the layer-by-layer path makes, so results agree with it to fp32
 // summation order. Shapes: 32 input and 32 output channels, up to 192 expanded channels, bf16.
 #include <hip/hip_runtime.h>
@@ -37,6 +40,7 @@
 #include <type_traits>
 
 #include "act.hpp"
+#include "conv_common.hpp"
 #include "kernels.hpp"
 #include "launch.hpp"
 #include "lop.h"
@@ -44,10 +48,6 @@
 namespace lop {
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kMbC = 32;          // input and output channels
@@ -71,6 +71,7 @@ struct MbParams {
   Clamp ce, cd, cp;
   int out_lo, R, N;
   int tiles_x, tiles_y;
+  FastDiv by_tx, by_ty;
 };
 
 __device__ __forceinline__ f32x16 mma_bf16(const u32x4& a, const u32x4& b, const f32x16& c) {
@@ -152,28 +153,43 @@ __device__ __forceinline__ void mbconv_body(const MbParams& p, int bid) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int px = lane & 31, kg = lane >> 5;
-  const int tx = bid % p.tiles_x;
-  bid /= p.tiles_x;
-  const int ty = bid % p.tiles_y;
-  const int n = bid / p.tiles_y;
+  const int row = fastdiv(bid, p.by_tx), tx = bid - row * p.tiles_x;
+  const int n = fastdiv(row, p.by_ty), ty = row - n * p.tiles_y;
   const int oh0 = p.out_lo + ty * TH, ow0 = tx * TW;
   const int ih_base = oh0 * S - 1, iw_base = ow0 * S - 1;
   // rows of the image that the slab holds
   const int ih_lo = max(0, p.x_row0), ih_hi = min(p.H, p.x_row0 + p.x_rows);
 
+  // A tile away from the image's borders needs no masks.
+  const bool inside = ih_base >= ih_lo && iw_base >= 0 && ih_base + EH <= ih_hi && iw_base + XQ * 4 <= p.W;
+
   // ---- the block's input at the expanded pixels of this wavefront's MFMA tiles, in operand
-  // layout (lane = pixel, two halves of 8 channels per step of 16), kept for all chunks
+  // layout (lane = pixel, eight of its channels), kept for all chunks. (Quads past the last are that one again: their memory
+  // in LDS is nobody's.)
   u32x4 xa[MPW][2];
+  {
+    const char* const origin = (const char*)(p.x + ((long)(n * p.x_rows + ih_base - p.x_row0) * p.W + iw_base) * kMbC);
+    const unsigned pitch = (unsigned)p.W * (kMbC * 2), lane_at = (lane & 3) * (kMbC * 2) + (lane >> 4) * 16;
+    const int q0 = wave * 8 + G::quad(0, (lane & 15) >> 2);
+    auto load = [&](auto all) __attribute__((always_inline)) {
 #pragma unroll
-  for (int i = 0; i < MPW; ++i)
+      for (int i = 0; i < MPW; ++i)
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int q = (wave + 4 * i) * 8 + G::quad(h, (lane & 15) >> 2), qx = q / EH;
-      const int ih = ih_base + G::row(q - qx * EH), iw = iw_base + qx * 4 + (lane & 3);
-      xa[i][h] = u32x4{0u, 0u, 0u, 0u};
-      if (q < NQ && ih >= ih_lo && ih < ih_hi && iw >= 0 && iw < p.W)
-        xa[i][h] = *(const u32x4*)(p.x + ((size_t)(n * p.x_rows + ih - p.x_row0) * p.W + iw) * kMbC + (lane >> 4) * 8);
-    }
+        for (int h = 0; h < 2; ++h) {
+          const int q = min(q0 + 32 * i + 2 * h, NQ - 1), qx = q / EH, r = G::row(q - qx * EH);
+          const u32x4* const at = (const u32x4*)(origin + ((unsigned long)(unsigned)r * pitch + qx * (kMbC * 8) + lane_at));
+          if constexpr (all) {
+            xa[i][h] = *at;
+          } else {
+            const int ih = ih_base + r, iw = iw_base + qx * 4 + (lane & 3);
+            xa[i][h] = u32x4{0u, 0u, 0u, 0u};
+            if (ih >= ih_lo && ih < ih_hi && iw >= 0 && iw < p.W) xa[i][h] = *at;
+          }
+        }
+    };
+    if (inside) load(std::true_type{});
+    else load(std::false_type{});
+  }
 
   // weights of a chunk: expand, the depthwise bands of this wavefront's 16 channels, project, all in the order of the
   // lanes (an access of four lanes to one 64-byte line each costs the vector cache four times as much); each part is fetched for the next chunk when this one is done with it
@@ -199,14 +215,12 @@ __device__ __forceinline__ void mbconv_body(const MbParams& p, int bid) {
   fetch_depthwise(0);
   fetch_project(0);
 
-  // A tile away from the image's borders needs no masks.
-  const bool inside = ih_base >= ih_lo && iw_base >= 0 && ih_base + EH <= ih_hi && iw_base + XQ * 4 <= p.W;
   if (tid < kMbMaxMid) {
     const bool in = tid < p.C_mid;
     bias_s[0][tid] = in && p.be ? p.be[tid] : 0.f;
     bias_s[1][tid] = in && p.bd ? p.bd[tid] : 0.f;
   }
-  if (tid < MT_E * 8) {
+  if (!inside && tid < MT_E * 8) {
     const int qx = tid / EH, ih = ih_base + G::row(tid - qx * EH), iw = iw_base + qx * 4;
     const bool rows = ih >= ih_lo && ih < ih_hi;
     auto in = [&](int k) { return rows && iw + k >= 0 && iw + k < p.W; };
@@ -235,9 +249,8 @@ __device__ __forceinline__ void mbconv_body(const MbParams& p, int bid) {
   unsigned char* const dout = D_s + dslot * DPITCH + drow * 8;
   unsigned char* const dtr = D_s + (((lane & 15) >> 2) * 8 + kg) * DPITCH + (wave * RG * 8 + ((lane >> 4) & 1) * 4 + (lane & 3)) * 8;
 
-  for (int c = 0; c < p.nch; ++c) {
-    const int cn = min(c + 1, p.nch - 1);
-    // ---- expand
+  // ---- expand: chunk c, whose weights are in `we`
+  auto expand_chunk = [&](int c, auto&& meanwhile) __attribute__((always_inline)) {
     f32x4 ebias[2];
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
@@ -270,11 +283,16 @@ __device__ __forceinline__ void mbconv_body(const MbParams& p, int bid) {
       for (int u = 0; u < 2 * MPW; ++u) {
         if (u + 1 < 2 * MPW) multiply(u + 1, a[(u + 1) & 1]);
         finish(u, a[u & 1], masked);
+        if (u == 1) meanwhile();
         __builtin_amdgcn_sched_barrier(0);   // (all tiles' sums at once do not fit the registers)
       }
     };
     if (inside) expand(std::false_type{});
     else expand(std::true_type{});
+  };
+  expand_chunk(0, [] {});
+  for (int c = 0; c < p.nch; ++c) {
+    const int cn = min(c + 1, p.nch - 1);
     fetch_expand(cn);
     barrier();
 
@@ -309,15 +327,29 @@ __device__ __forceinline__ void mbconv_body(const MbParams& p, int bid) {
     }
     barrier();
 
-    // ---- project: this chunk's 32 channels are the reduction axis
+    // ---- project: this chunk's 32 channels are the reduction axis. Its operands come out of LDS while the next chunk is
+    // expanded.
+    u32x2 d[RG][2][2];
 #pragma unroll
     for (int g = 0; g < RG; ++g)
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const u32x2 lo = transposed_read(dtr + (4 * h + 0) * DPITCH + g * 64);
-        const u32x2 hi = transposed_read(dtr + (4 * h + 2) * DPITCH + g * 64);
-        acc[g] = mma_bf16(wp[h], u32x4{lo.x, lo.y, hi.x, hi.y}, acc[g]);
-      }
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int k = 0; k < 2; ++k) d[g][h][k] = transposed_read(dtr + (4 * h + 2 * k) * DPITCH + g * 64);
+    __builtin_amdgcn_sched_barrier(0);
+    auto project = [&]() __attribute__((always_inline)) {
+#pragma unroll
+      for (int g = 0; g < RG; ++g)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) acc[g] = mma_bf16(wp[h], u32x4{d[g][h][0].x, d[g][h][0].y, d[g][h][1].x, d[g][h][1].y}, acc[g]);
+    };
+    if constexpr (S == 2) {   // (with stride 2 the operands have to make room for the rest of the expand part)
+      if (c + 1 < p.nch) expand_chunk(c + 1, project);
+      else project();
+    } else {
+      if (c + 1 < p.nch) expand_chunk(c + 1, [] {});
+      project();
+    }
     fetch_project(cn);
   }
 
@@ -446,6 +478,7 @@ MbParams make_mbconv(const OpLaunch& e, const OpLaunch& d, const OpLaunch& p, in
   const int tw = MbTile<1, 8>::TW;
   q.tiles_x = (q.W_out + tw - 1) / tw;
   q.tiles_y = (q.R + th - 1) / th;
+  q.by_tx = make_fastdiv(q.tiles_x); q.by_ty = make_fastdiv(q.tiles_y);
   return q;
 }
 static_assert(sizeof(Batch<MbParams>) <= 4096, "the parameters of all bands of a launch travel as kernel arguments");
