@@ -190,22 +190,20 @@ static_assert(sizeof(Batch<Dw3Params>) <= 4096, "the parameters of all bands of 
 
 // Raw 8- or 16-byte vector of the storage type and its expansion to fp32 values.
 template <int BYTES> struct RawVec;
-template <> struct RawVec<16> { typedef uint4 type; };
-template <> struct RawVec<8> { typedef uint2 type; };
+template <> struct RawVec<16> { typedef unsigned type __attribute__((ext_vector_type(4))); };
+template <> struct RawVec<8> { typedef unsigned type __attribute__((ext_vector_type(2))); };
+typedef RawVec<16>::type raw16;
+typedef RawVec<8>::type raw8;
+__device__ __forceinline__ raw16 raw_load(__amdgpu_buffer_rsrc_t buf, unsigned at, raw16) { return __builtin_amdgcn_raw_buffer_load_b128(buf, (int)at, 0, 0); }
+__device__ __forceinline__ raw8 raw_load(__amdgpu_buffer_rsrc_t buf, unsigned at, raw8) { return __builtin_amdgcn_raw_buffer_load_b64(buf, (int)at, 0, 0); }
+__device__ __forceinline__ void raw_store(const raw16& v, __amdgpu_buffer_rsrc_t buf, unsigned at) { __builtin_amdgcn_raw_buffer_store_b128(v, buf, (int)at, 0, 0); }
+__device__ __forceinline__ void raw_store(const raw8& v, __amdgpu_buffer_rsrc_t buf, unsigned at) { __builtin_amdgcn_raw_buffer_store_b64(v, buf, (int)at, 0, 0); }
 
-__device__ __forceinline__ void unpack_bf16(const uint4& t, float* v) {
-  const unsigned u[4] = {t.x, t.y, t.z, t.w};
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    v[2 * i] = __uint_as_float(u[i] << 16);
-    v[2 * i + 1] = __uint_as_float(u[i] & 0xffff0000u);
-  }
-}
-__device__ __forceinline__ void unpack_bf16(const uint2& t, float* v) {
+__device__ __forceinline__ void unpack_bf16(const raw8& t, float* v) {
   v[0] = __uint_as_float(t.x << 16); v[1] = __uint_as_float(t.x & 0xffff0000u);
   v[2] = __uint_as_float(t.y << 16); v[3] = __uint_as_float(t.y & 0xffff0000u);
 }
-__device__ __forceinline__ void unpack_f32(const uint4& t, float* v) {
+__device__ __forceinline__ void unpack_f32(const raw16& t, float* v) {
   v[0] = __uint_as_float(t.x); v[1] = __uint_as_float(t.y);
   v[2] = __uint_as_float(t.z); v[3] = __uint_as_float(t.w);
 }
@@ -215,42 +213,47 @@ __device__ __forceinline__ void unpack(const R& t, float* v) {
   else unpack_f32(t, v);
 }
 
-template <typename T, int VEC, int S>
+// COLS: columns of outputs per thread, which share the input columns between them.
+template <typename T, int VEC, int S, int COLS>
 __device__ __forceinline__ void dwconv3x3_body(const Dw3Params& q, const int bx) {
   static_assert(VEC * sizeof(T) == 16 || VEC * sizeof(T) == 8, "8- or 16-byte vectors");
   typedef typename RawVec<VEC * sizeof(T)>::type Raw;
   constexpr int RPT = dw_rows_per_thread(S);  // output rows per thread
   constexpr int NR = (RPT - 1) * S + 3;    // input rows they read
+  constexpr int NC = (COLS - 1) * S + 3;   // input columns
   const RowParams& p = q.r;
   const int cv = p.C / VEC;
-  const int cg = threadIdx.x % cv, col = threadIdx.x / cv;
+  const int cg = threadIdx.x % cv, col = threadIdx.x / cv * COLS;
   const int row = bx / q.col_blocks;
-  const int ow = (bx - row * q.col_blocks) * q.cols_per_block + col;
+  const int ow_first = (bx - row * q.col_blocks) * q.cols_per_block, ow = ow_first + col;   // of the workgroup, of the thread
   if (col >= q.cols_per_block || ow >= p.W_out) return;
   const int n = row / q.chunks, chunk = row - n * q.chunks;
   const int c = cg * VEC;
   const int oh0 = p.out_lo + chunk * RPT;
   const int oh1 = min(oh0 + RPT, p.out_lo + p.R);
-  const T* __restrict__ xg = (const T*)p.x;
-  T* __restrict__ yg = (T*)p.y;
   const Clamp clamp = make_clamp(p.act);
 
   // Every load first (input rows, weights, bias), all stores after: loads and stores share
   // one in-order counter, so a load waited for after a store would wait for the store too.
-  Raw in[NR][3];
-  const int ih0 = oh0 * S - 1, iw0 = ow * S - 1;
+  // A row is a buffer of its own, from the workgroup's first column to the row's end: columns outside the image and rows outside
+  // the slab (buffers of no bytes) read as zeros.
+  const int pixel = p.C * (int)sizeof(T), iw_first = max(ow_first * S - 1, 0);
+  const size_t x_pitch = (size_t)p.W * pixel, y_pitch = (size_t)p.W_out * pixel;
+  auto up_to_end = [&](int columns) { return (int)min((size_t)columns * pixel, (size_t)0x7fffffff); };
+  const int x_bytes = up_to_end(p.W - iw_first), y_bytes = up_to_end(p.W_out - ow_first);
+  Raw in[NR][NC];
+  const int ih0 = oh0 * S - 1;
   const int rows_needed = (oh1 - oh0 - 1) * S + 3;
+  const unsigned x_at = (unsigned)((ow * S - 1 - iw_first) * pixel + c * (int)sizeof(T));
 #pragma unroll
   for (int a = 0; a < NR; ++a) {
     const int ih = ih0 + a;
     const bool row_ok = a < rows_needed && ih >= p.x_row0 && ih < p.x_row0 + p.x_rows;
+    const __amdgpu_buffer_rsrc_t buf = __builtin_amdgcn_make_buffer_rsrc(
+        (char*)const_cast<void*>(p.x) + (row_ok ? (size_t)(n * p.x_rows + ih - p.x_row0) * x_pitch + (size_t)iw_first * pixel : (size_t)0), 0,
+        row_ok ? x_bytes : 0, 0x00020000);
 #pragma unroll
-    for (int b = 0; b < 3; ++b) {
-      const int iw = iw0 + b;
-      in[a][b] = Raw{};
-      if (row_ok && iw >= 0 && iw < p.W)
-        in[a][b] = *(const Raw*)(xg + ((size_t)(n * p.x_rows + ih - p.x_row0) * p.W + iw) * p.C + c);
-    }
+    for (int b = 0; b < NC; ++b) in[a][b] = raw_load(buf, x_at + b * pixel, Raw{});
   }
   float w[9][VEC];
 #pragma unroll
@@ -260,38 +263,59 @@ __device__ __forceinline__ void dwconv3x3_body(const Dw3Params& q, const int bx)
   for (int i = 0; i < VEC; ++i) bias[i] = 0.f;
   if (p.bias) load_f32<VEC>(p.bias + c, bias);
 
+  float x[3][NC][VEC];   // the rows under one output row: each is unpacked once
+  const unsigned y_at = (unsigned)(col * pixel + c * (int)sizeof(T));
 #pragma unroll
   for (int r = 0; r < RPT; ++r) {
     if (oh0 + r >= oh1) break;
-    float acc[VEC];
 #pragma unroll
-    for (int i = 0; i < VEC; ++i) acc[i] = bias[i];
+    for (int a = r == 0 ? 0 : 3 - S; a < 3; ++a)
 #pragma unroll
-    for (int a = 0; a < 3; ++a)
+      for (int b = 0; b < NC; ++b) unpack<T>(in[r * S + a][b], x[(r * S + a) % 3][b]);
+    const size_t y_row = (size_t)(n * p.y_rows + oh0 + r - p.y_row0) * y_pitch + (size_t)ow_first * pixel;
+    const __amdgpu_buffer_rsrc_t to = __builtin_amdgcn_make_buffer_rsrc((char*)p.y + y_row, 0, y_bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t to2 = __builtin_amdgcn_make_buffer_rsrc((char*)p.y2 + (p.y2 ? y_row : 0), 0, p.y2 ? y_bytes : 0, 0x00020000);
 #pragma unroll
-      for (int b = 0; b < 3; ++b) {
-        float x[VEC];
-        unpack<T>(in[r * S + a][b], x);
+    for (int k = 0; k < COLS; ++k) {
+      float acc[VEC];
 #pragma unroll
-        for (int i = 0; i < VEC; ++i) acc[i] = fmaf(x[i], w[a * 3 + b][i], acc[i]);
-      }
+      for (int i = 0; i < VEC; ++i) acc[i] = bias[i];
 #pragma unroll
-    for (int i = 0; i < VEC; ++i) acc[i] = clamp_act(acc[i], clamp);
-    const size_t yo = ((size_t)(n * p.y_rows + oh0 + r - p.y_row0) * p.W_out + ow) * p.C + c;
-    Vec<T, VEC>::store(yg + yo, acc);
-    if (p.y2) Vec<T, VEC>::store((T*)p.y2 + yo, acc);
+      for (int a = 0; a < 3; ++a)
+#pragma unroll
+        for (int b = 0; b < 3; ++b)
+#pragma unroll
+          for (int i = 0; i < VEC; ++i) acc[i] = fmaf(x[(r * S + a) % 3][k * S + b][i], w[a * 3 + b][i], acc[i]);
+#pragma unroll
+      for (int i = 0; i < VEC; ++i) acc[i] = clamp_act(acc[i], clamp);
+      alignas(16) T o[VEC];
+      Vec<T, VEC>::store(o, acc);
+      raw_store(*(const Raw*)o, to, y_at + k * pixel);   // (past the row's end: nowhere)
+      if (p.y2) raw_store(*(const Raw*)o, to2, y_at + k * pixel);
+    }
   }
 }
 
+template <typename T> constexpr int kDwCols = sizeof(T) == 2 ? 2 : 1;
 template <typename T, int VEC, int S>
 __global__ __launch_bounds__(256) void dwconv3x3_kernel(const Dw3Params q) {
-  dwconv3x3_body<T, VEC, S>(q, blockIdx.x);
+  dwconv3x3_body<T, VEC, S, kDwCols<T>>(q, blockIdx.x);
 }
 // The same for several bands of one layer in one grid (band b owns blocks first[b] .. first[b + 1]).
 template <typename T, int VEC, int S>
 __global__ __launch_bounds__(256) void dwconv3x3_kernel_bands(const Batch<Dw3Params> t) {
   const int b = batch_find(t, blockIdx.x);
-  dwconv3x3_body<T, VEC, S>(t.p[b], blockIdx.x - t.first[b]);
+  dwconv3x3_body<T, VEC, S, kDwCols<T>>(t.p[b], blockIdx.x - t.first[b]);
+}
+// bf16 with one column a thread, for launches of few workgroups (see dw_cols).
+template <typename T, int VEC, int S>
+__global__ __launch_bounds__(256) void dwconv3x3_column_kernel(const Dw3Params q) {
+  dwconv3x3_body<T, VEC, S, 1>(q, blockIdx.x);
+}
+template <typename T, int VEC, int S>
+__global__ __launch_bounds__(256) void dwconv3x3_column_kernel_bands(const Batch<Dw3Params> t) {
+  const int b = batch_find(t, blockIdx.x);
+  dwconv3x3_body<T, VEC, S, 1>(t.p[b], blockIdx.x - t.first[b]);
 }
 
 // The sliding-window kernel covers the common depthwise case; everything else runs on
@@ -302,10 +326,32 @@ inline bool dw3_applies(const RowParams& p, int op, int vec) {
          p.res == nullptr;
 }
 
+constexpr int kDwVec = 4;   // channels per thread
+inline int dw_block_cols(int c, int cols) { return std::max(1, 256 / (c / kDwVec)) * cols; }
+
+// Columns of outputs per thread of a launch: two (bf16; fp32 has no registers for them) where that leaves a workgroup per
+// compute unit. Two take 2.5 vector loads an output where one takes 3.75 (stride 2: 5.6 and 6.75) and half the vector
+// instructions, which were busy for three quarters of the time: 192 channels on 8 x 42 x 320 pixels 26.9 -> 22.2 us, stride 2 on
+// 8 x 82 x 640 42.5 -> 39.8. With few workgroups a thread's chain of loads is what counts: 2 x 20 x 84 pixels 4.5 us with
+// one column, 5.8 with two; 42 x 160 (96 workgroups of two) 4.7 and 5.9. Between them one is ahead alone (82 x 320, 352
+// workgroups: 8.6 and 8.9; 8 x 21 x 160, 384: 8.4 and 8.7), two with launches beside it (chains of one 640 x 640 image in four bands 262.9 and 258.2 us,
+// of eight in eight bands 1 959 and 1 942).
+constexpr long kDwTwoColumns = 256;
+int dw_cols(const RowParams* ps, int n, int dtype) {
+  long blocks = 0;
+  for (int b = 0; b < n; ++b) {
+    const RowParams& p = ps[b];
+    if (p.R <= 0 || p.N <= 0) continue;
+    const int rpt = dw_rows_per_thread(p.sh), cols = dw_block_cols(p.C, 2);
+    blocks += (long)((p.W_out + cols - 1) / cols) * ((p.R + rpt - 1) / rpt) * p.N;
+  }
+  return dtype == LOP_BF16 && blocks > kDwTwoColumns ? 2 : 1;
+}
+
 // The bands in one launch, unless they have more workgroups than a launch takes (2^32 threads, exclusive): then in as few as
 // hold them, a band of too many itself cut into groups of images or of rows of an image.
 constexpr long kDwBlocks = 0xffffffffL / 256;
-template <typename T, int VEC>
+template <typename T, int VEC, int COLS>
 hipError_t launch_dw3(const RowParams* ps, int n, hipStream_t s, KernelEvents* ev) {
   Dw3Params qs[kMaxBatch];
   unsigned gx[kMaxBatch];
@@ -315,14 +361,21 @@ hipError_t launch_dw3(const RowParams* ps, int n, hipStream_t s, KernelEvents* e
     const int k = m;
     m = 0; total = 0;
     if (k == 0) return hipSuccess;
-    return ps[0].sh == 1 ? launch_group(dwconv3x3_kernel<T, VEC, 1>, dwconv3x3_kernel_bands<T, VEC, 1>, qs, k, gx, 1, 1, dim3(256), s, ev)
-                         : launch_group(dwconv3x3_kernel<T, VEC, 2>, dwconv3x3_kernel_bands<T, VEC, 2>, qs, k, gx, 1, 1, dim3(256), s, ev);
+    const dim3 block(256);
+    if constexpr (COLS != kDwCols<T>) {
+      return ps[0].sh == 1 ? launch_group(dwconv3x3_column_kernel<T, VEC, 1>, dwconv3x3_column_kernel_bands<T, VEC, 1>, qs, k, gx, 1, 1, block, s, ev)
+                           : launch_group(dwconv3x3_column_kernel<T, VEC, 2>, dwconv3x3_column_kernel_bands<T, VEC, 2>, qs, k, gx, 1, 1, block, s, ev);
+    } else {
+      return ps[0].sh == 1 ? launch_group(dwconv3x3_kernel<T, VEC, 1>, dwconv3x3_kernel_bands<T, VEC, 1>, qs, k, gx, 1, 1, block, s, ev)
+                           : launch_group(dwconv3x3_kernel<T, VEC, 2>, dwconv3x3_kernel_bands<T, VEC, 2>, qs, k, gx, 1, 1, block, s, ev);
+    }
   };
   for (int b = 0; b < n; ++b) {
     const RowParams& p = ps[b];
     if (p.R <= 0 || p.N <= 0) continue;
-    const int rpt = dw_rows_per_thread(p.sh), cols = std::max(1, 256 / (p.C / VEC)), col_blocks = (p.W_out + cols - 1) / cols;
-    if (col_blocks > kDwBlocks) return hipErrorInvalidValue;   // (not even one chunk of rows)
+    const int rpt = dw_rows_per_thread(p.sh), cols = dw_block_cols(p.C, COLS), col_blocks = (p.W_out + cols - 1) / cols;
+    // (not even one chunk of rows with a column a thread: an error whichever form is taken)
+    if ((p.W_out + dw_block_cols(p.C, 1) - 1) / dw_block_cols(p.C, 1) > kDwBlocks) return hipErrorInvalidValue;
     const int rows = (int)std::min((long)p.R, kDwBlocks / col_blocks * rpt);
     const int images = (int)std::min((long)p.N, kDwBlocks / ((long)col_blocks * ((rows + rpt - 1) / rpt)));
     const size_t x_img = (size_t)p.x_rows * p.W * p.C * sizeof(T), y_img = (size_t)p.y_rows * p.W_out * p.C * sizeof(T);
@@ -353,11 +406,9 @@ hipError_t launch_dw3(const RowParams* ps, int n, hipStream_t s, KernelEvents* e
 }
 
 // Channel vector per thread of the sliding-window kernel (0: it does not apply).
-inline int dw3_vec(const RowParams& p, int op, int dtype) {
-  (void)dtype;
-  const int want = 4;
-  if (p.C % want != 0) return 0;
-  return dw3_applies(p, op, want) ? want : 0;
+inline int dw3_vec(const RowParams& p, int op) {
+  if (p.C % kDwVec != 0) return 0;
+  return dw3_applies(p, op, kDwVec) ? kDwVec : 0;
 }
 
 template <typename T, int VEC>
@@ -394,7 +445,7 @@ RowParams make_row_params(const OpLaunch& L) {
 }  // namespace
 
 // The register-blocked depthwise kernel.
-bool dw3_takes(const OpLaunch& L) { return dw3_vec(make_row_params(L), L.op, L.dtype) != 0; }
+bool dw3_takes(const OpLaunch& L) { return dw3_vec(make_row_params(L), L.op) != 0; }
 
 hipError_t launch_rowwise_bands(const OpLaunch* Ls, int n, hipStream_t stream, KernelEvents* ev) {
   if (n < 1 || n > kMaxBatch) return hipErrorInvalidValue;
@@ -402,8 +453,10 @@ hipError_t launch_rowwise_bands(const OpLaunch* Ls, int n, hipStream_t stream, K
   for (int b = 0; b < n; ++b) ps[b] = make_row_params(Ls[b]);
   const OpLaunch& L = Ls[0];
   RowParams& p = ps[0];
-  if (dw3_vec(p, L.op, L.dtype))
-    return L.dtype != LOP_BF16 ? launch_dw3<float, 4>(ps, n, stream, ev) : launch_dw3<__bf16, 4>(ps, n, stream, ev);
+  if (dw3_vec(p, L.op))
+    return L.dtype != LOP_BF16 ? launch_dw3<float, kDwVec, 1>(ps, n, stream, ev)
+           : dw_cols(ps, n, L.dtype) == 2 ? launch_dw3<__bf16, kDwVec, 2>(ps, n, stream, ev)
+                                          : launch_dw3<__bf16, kDwVec, 1>(ps, n, stream, ev);
   if (L.dtype == LOP_BF16)
     return p.C % 8 == 0 ? launch_rowwise<__bf16, 8>(ps, n, L.op, stream, ev)
                         : launch_rowwise<__bf16, 1>(ps, n, L.op, stream, ev);
@@ -473,9 +526,10 @@ int rowwise_describe(const OpLaunch& L, char* name, size_t size) {
   RowParams p;
   p.kh = L.kh; p.kw = L.kw; p.sh = L.sh; p.sw = L.sw; p.ph = L.ph; p.pw = L.pw;
   p.dh = L.dh; p.dw = L.dw; p.C = L.x.c; p.res = L.res.ptr;
+  p.W = L.x.w; p.W_out = L.y.w; p.R = L.out_hi - L.out_lo; p.N = L.x.n;
   if (name && size) {
-    if (const int v = dw3_vec(p, L.op, L.dtype))
-      snprintf(name, size, "dwconv3x3_kernel<%s, %d, %d>", bf ? "__bf16" : "float", v, L.sh);
+    if (const int v = dw3_vec(p, L.op))
+      snprintf(name, size, "dwconv3x3_%skernel<%s, %d, %d>", bf && dw_cols(&p, 1, L.dtype) == 1 ? "column_" : "", bf ? "__bf16" : "float", v, L.sh);
     else
       snprintf(name, size, "rowwise_kernel<%s, %d, %d>", bf ? "__bf16" : "float", vec, o);
   }

@@ -2225,3 +2225,28 @@ def test_two_convolutions_as_one_launch(oracle, shape, bands, flags, acts, dtype
         want = oracle.run_chain(chain, rand)
         assert rel_err(got, want) <= TOL[dtype], (around, rel_err(got, want))
         assert np.array_equal(got, host), around
+
+
+@pytest.mark.parametrize("shape,s,bands,name", [
+    ((8, 256, 65, 37), 1, 3, "dwconv3x3_kernel<__bf16, 4, 1>"),          # two columns a thread, an odd number of them
+    ((9, 260, 129, 74), 2, 2, "dwconv3x3_kernel<__bf16, 4, 2>"),         # 65 threads a column: three idle, and an even row's last column
+    ((2, 12, 17, 1), 1, 1, "dwconv3x3_column_kernel<__bf16, 4, 1>"),     # one column
+    ((1, 192, 21, 33), 2, 4, "dwconv3x3_column_kernel<__bf16, 4, 2>"),
+    ((3, 1024, 30, 46), 1, 2, "dwconv3x3_kernel<__bf16, 4, 1>"),         # one pair of columns a workgroup
+])
+def test_depthwise_columns_per_thread(oracle, shape, s, bands, name):
+    """Both forms of the register-blocked depthwise kernel at edges of rows and columns, against the oracle and, bit for bit,
+    with the whole image as one band."""
+    chain = workloads.Chain("depthwise", shape, "bf16", bands)
+    chain.add(workloads.DWCONV, shape[1], shape[1], 3, s, 1, 1, "relu6")
+    t = workloads.make_tensors(chain, zero_bias=False)
+    plan = lop.Plan(chain, t, 1)
+    try:
+        assert plan.layer_kernel(0, 0)[0] == name
+    finally:
+        plan.destroy()
+    whole, host = run_gpu(chain, t, n_bands=1)
+    assert rel_err(whole, oracle.run_chain(chain, t)) <= TOL["bf16"]
+    np.testing.assert_array_equal(whole, host)
+    parts, _ = run_gpu(chain, t)
+    np.testing.assert_array_equal(parts, whole)
