@@ -1206,6 +1206,21 @@ bool pair(const lop_plan_t* P, int l) {
   return !F.away[l] && !F.away[l + 1] && F.head[l] < 0 && F.head[l + 1] < 0;
 }
 
+// The last layer of the launch that a first layer l and the convolution behind it, its only reader, share where a kernel
+// takes both (l + 1, or l + 2 if that convolution's pooling is part of its launch), or -1.
+int front_end(const lop_plan_t* P, int l) {
+  const lop::Tables& t = P->t;
+  const int nl = t.n_layers();
+  if (t.layers[l].d.c_in != 3 || l + 1 >= nl || (P->flags & LOP_FLAG_NO_FUSE)) return -1;
+  for (int j = 0; j < nl; ++j)
+    if ((j != l + 1 && t.layers[j].d.input_from == l) || t.layers[j].d.residual_from == l) return -1;
+  const lop_layer_t &a = t.layers[l].d, &b = t.layers[l + 1].d;
+  const Fusion& F = P->fuse_chain;
+  if (a.op != LOP_CONV2D || b.op != LOP_CONV2D || b.input_from != l || F.away[l] || F.head[l] >= 0 || F.head[l + 1] >= 0) return -1;
+  if (!F.away[l + 1]) return l + 1;
+  return l + 2 < nl && F.head[l + 2] == l + 1 ? l + 2 : -1;
+}
+
 // The kernels of a chain whose launches are merged over the bands (kGrouped, kWhole), on one
 // stream, with the scratch set by the caller. y2: where the last launch also stores its rows.
 int enqueue_merged_kernels(lop_plan_t* P, const void* d_in, void* d_out, hipStream_t cs, void* y2) {
@@ -1228,6 +1243,16 @@ int enqueue_merged_kernels(lop_plan_t* P, const void* d_in, void* d_out, hipStre
         if (const int rc = begin_pass(); rc != LOP_OK) return rc;
         const ChainPass pass(P, i, images, rows);
         for (int l = 0; l < nl; ++l) {
+          if (const int e = front_end(P, l); e > 0) {
+            const lop::OpLaunch a = make_launch(P, whole, l, d_in, d_out);
+            lop::OpLaunch c = make_launch(P, whole, l + 1, d_in, d_out), q = make_launch(P, whole, e, d_in, d_out);
+            c.y2 = q.y2 = e == nl - 1 ? second : nullptr;
+            if (lop::front_applies(&a, &c, e > l + 1 ? &q : nullptr, 1)) {
+              LOP_HIP(lop::launch_front(&a, &c, e > l + 1 ? &q : nullptr, 1, cs));
+              l = e;
+              continue;
+            }
+          }
           if (pair(P, l)) {
             const lop::OpLaunch a = make_launch(P, whole, l, d_in, d_out);
             lop::OpLaunch q = make_launch(P, whole, l + 1, d_in, d_out);
@@ -1256,6 +1281,17 @@ int enqueue_merged_kernels(lop_plan_t* P, const void* d_in, void* d_out, hipStre
       const int end = std::min(nb, b + P->group);
       if (const int rc = begin_pass(); rc != LOP_OK) return rc;
       for (int l = 0; l < nl; ++l) {
+        if (const int e = front_end(P, l); e > 0 && end - b <= lop::kMaxBandsPerLaunch) {
+          std::vector<lop::OpLaunch> as, convs, qs, none;
+          batched_group(P, l, b, end, d_in, d_out, nullptr, &as, &none);
+          batched_group(P, e, b, end, d_in, d_out, e == nl - 1 ? second : nullptr, &qs, &convs);
+          const bool pooled = e > l + 1;
+          if (as.size() == qs.size() && lop::front_applies(as.data(), pooled ? convs.data() : qs.data(), pooled ? qs.data() : nullptr, (int)as.size())) {
+            LOP_HIP(lop::launch_front(as.data(), pooled ? convs.data() : qs.data(), pooled ? qs.data() : nullptr, (int)as.size(), cs));
+            l = e;
+            continue;
+          }
+        }
         if (end - b <= lop::kMaxBandsPerLaunch && pair(P, l)) {
           std::vector<lop::OpLaunch> as, qs, none;
           batched_group(P, l, b, end, d_in, d_out, nullptr, &as, &none);

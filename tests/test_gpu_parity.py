@@ -2250,3 +2250,37 @@ def test_depthwise_columns_per_thread(oracle, shape, s, bands, name):
     np.testing.assert_array_equal(whole, host)
     parts, _ = run_gpu(chain, t)
     np.testing.assert_array_equal(parts, whole)
+
+
+@pytest.mark.parametrize("c,s,pool,shape,bands,flags", [
+    (32, 2, False, (1, 3, 37, 41), 1, 0),                                    # fewer tiles than XCDs
+    (32, 2, False, (2, 3, 180, 333), 5, 0),                                  # an odd width: rows of the image start between two words
+    (32, 1, False, (1, 3, 65, 63), 4, lop.LOP_FLAG_REUSE | lop.LOP_FLAG_GRAPH),
+    (32, 1, False, (1, 3, 3, 150), 3, 0),                                    # bands of one row
+    (64, 1, True, (1, 3, 96, 98), 3, 0), (64, 1, True, (3, 3, 70, 75), 4, lop.LOP_FLAG_REUSE),
+    (64, 1, False, (1, 3, 90, 97), 2, lop.LOP_FLAG_BATCH_BANDS), (64, 2, True, (1, 3, 200, 231), 6, 0), (64, 2, False, (2, 3, 161, 190), 3, 0),
+])
+def test_first_layer_and_the_convolution_behind_it(oracle, c, s, pool, shape, bands, flags):
+    """The launch that computes both (and the pooling), alone (its rows also leave for the host from there) and with a layer
+    behind it (bands with slabs of their own), against the oracle and against a launch per layer."""
+    for behind in (False, True):
+        chain = workloads.Chain("front", shape, "bf16", bands)
+        chain.add(workloads.CONV, 3, c, 3, s, 1, act="relu")
+        chain.add(workloads.CONV, c, c, 3, 1, 1, act="relu6" if pool else "none")
+        if pool:
+            chain.add(workloads.MAXPOOL, c, c, 2, 2, 0)
+        if behind:
+            chain.add(workloads.CONV, c, 32, 3, 1, 1, act="relu")
+        t = workloads.make_tensors(chain, zero_bias=False)
+        got, host = run_gpu(chain, t, flags=flags | lop.LOP_FLAG_POISON_SCRATCH)
+        assert rel_err(got, oracle.run_chain(chain, t)) <= TOL["bf16"], behind
+        np.testing.assert_array_equal(got, host)
+        apart, _ = run_gpu(chain, t, use_host=False, flags=flags | lop.LOP_FLAG_NO_FUSE)
+        # one rounding to bf16 per layer: sums in another order differ by a unit in the last place now and then
+        assert rel_err(got, apart) <= 2 ** -7 and np.mean(got != apart) < 0.05
+        # pixels that are not finite reach the outputs whose windows hold them, and no others
+        t.x[:, 1, shape[2] // 2, shape[3] // 3] = np.inf
+        t.x[:, 0, -1, -1] = np.nan
+        got, _ = run_gpu(chain, t, use_host=False, flags=flags)
+        apart, _ = run_gpu(chain, t, use_host=False, flags=flags | lop.LOP_FLAG_NO_FUSE)
+        np.testing.assert_array_equal(np.isfinite(got), np.isfinite(apart))
