@@ -204,7 +204,7 @@ LOP_API int lop_run_band(lop_plan_t* plan, int band, const void* d_in, void* d_o
  * That holds for chains whose scratch (the layer outputs that are live together and the split-K
  * workspace of the merged launches) fits LOP_STATIC_SCRATCH_BYTES, in equal passes
  * over the images of a batch (independent bands: then over groups of bands; chains of row-wise operators: over the rows of
- * groups of bands) if not all at once; chains with layers on the 1x1 streaming or the 3x3 depthwise kernel only if
+ * groups of bands) if not all at once, or in such passes up to one of the layers and behind it once; chains with layers on the 1x1 streaming or the 3x3 depthwise kernel only if
  * those passes are no more than a lane has bands; a merged chain runs on one lane and consecutive
  * calls rotate over the lanes. Larger chains run band by band on the lanes, band b's copy
  * overlapping the kernels of the bands after it (Sec. IV-B). Either way the rows computed are

@@ -368,15 +368,15 @@ size_t band_workspace(const lop_plan_t* P) {
 // makes. A last pass over fewer images is looked at by itself: fewer pixels can mean more slices, or a kernel
 // that cuts the reduction where the larger launch has one that does not.
 size_t merged_workspace(lop_plan_t* P) {
-  const int nb = P->t.n_bands, rest = P->t.in.n % P->images;
+  const int nb = P->t.n_bands, nl = P->t.n_layers(), rest = P->t.in.n % P->images;
   size_t most = 0;
-  auto pass = [&](int images, int first, int last) {
+  auto pass = [&](int images, int first, int last, int layer, int layers) {
     const bool whole = P->sched == ChainSched::kWhole;
     const lop_rows_t rows = whole && P->group < nb ? pass_rows(P, first, last) : lop_rows_t{0, 0};
     if (whole && P->group < nb && rows.hi <= rows.lo) return;
     const ChainPass sized(P, 0, images, rows);
     std::vector<lop::OpLaunch> group;
-    for (int l = 0; l < P->t.n_layers(); ++l) {
+    for (int l = layer; l < layers; ++l) {
       if (!launches_alone(P, P->fuse_chain, l)) continue;
       if (whole) {
         most = std::max(most, group_workspace({make_launch(P, P->t.whole(), l, nullptr, nullptr)}));
@@ -390,10 +390,12 @@ size_t merged_workspace(lop_plan_t* P) {
       }
     }
   };
+  const int in_passes = P->cut < 0 ? nl : P->cut + 1;
   for (int b = 0; b < nb; b += P->group) {
-    pass(P->images, b, std::min(nb, b + P->group));
-    if (rest) pass(rest, b, std::min(nb, b + P->group));
+    pass(P->images, b, std::min(nb, b + P->group), 0, in_passes);
+    if (rest) pass(rest, b, std::min(nb, b + P->group), 0, in_passes);
   }
+  if (in_passes < nl) pass(P->t.in.n, 0, nb, in_passes, nl);
   return most;
 }
 
@@ -456,11 +458,55 @@ void size_scratch(lop_plan_t* P) {
     return most;
   };
 
+  // A chain whose passes end with layer c: that layer's rows of all images and bands in front (kept bytes), behind them what a
+  // pass of `images` images and `per` bands keeps of the layers before it, or (all images and bands) what the layers behind
+  // it keep.
+  size_t kept = 0;
+  auto place_cut = [&](int c, int images, int per, bool whole) {
+    const bool behind = images == n && per == nb;
+    size_t most = 0;
+    kept = 0;
+    if (whole) {
+      P->chain_off[nb][c] = 0;
+      kept = rows_bytes(n, c, t.layers[c].h_out);
+    } else {
+      for (int b = 0; b < nb; ++b) {
+        P->chain_off[b][c] = kept;
+        kept += rows_bytes(n, c, band_rows(b, c));
+      }
+    }
+    auto place = [&](int b0, int b1) {
+      for (int l = 0; l + 1 < nl; ++l) {
+        size[l] = 0;
+        if (l == c ? !behind : behind != (l > c) || !chain_keeps(l)) continue;
+        if (l == c) size[l] = kept;
+        else if (whole) size[l] = rows_bytes(images, l, t.layers[l].h_out);
+        else for (int b = b0; b < b1; ++b) size[l] += rows_bytes(images, l, band_rows(b, l));
+      }
+      std::vector<size_t> block(nl, 0);
+      const size_t bytes = place_slabs(P, size, &block);
+      for (int l = 0; l + 1 < nl; ++l) {
+        if (l == c || !size[l]) continue;
+        size_t at = block[l] + (behind ? 0 : kept);
+        if (whole) { P->chain_off[nb][l] = at; continue; }
+        for (int b = b0; b < b1; ++b) {
+          P->chain_off[b][l] = at;
+          at += rows_bytes(images, l, band_rows(b, l));
+        }
+      }
+      most = std::max(most, bytes + (behind ? 0 : kept));
+    };
+    for (int b = 0; b < nb; b += per) place(b, std::min(nb, b + per));
+    return most;
+  };
+
   // bands that run one by one: in reuse mode on one full-height buffer per layer (rows at their
   // absolute position), kept from band to band
   P->sched = ChainSched::kPerBand;
   P->group = nb;
   P->images = n;
+  P->cut = -1;
+  P->cut_bytes = 0;
   P->slab_off.assign(nb + 1, std::vector<size_t>(nl, 0));   // (descriptors of the whole chain are made outside of a pass, too)
   P->chain_off.assign(nb + 1, std::vector<size_t>(nl, 0));
   P->arena_bytes = 0;
@@ -508,17 +554,74 @@ void size_scratch(lop_plan_t* P) {
   for (int l = 0; l < nl; ++l)
     streams = streams || (!P->fuse_chain.away[l] && P->fuse_chain.head[l] < 0 && lop::op_streams(lop::describe_layer(P, l)));
   const int most = streams ? std::max(1, nb / LOP_DEFAULT_LANES) : INT_MAX;
-  for (int passes = 1, images = 0; images != 1; ++passes) {
-    images = (n + passes - 1) / passes;
-    if (!whole && (n + images - 1) / images > most) return;
-    if (whole ? merge(ChainSched::kWhole, images, nb, place_whole(images, INT_MAX), false)
-              : merge(ChainSched::kGrouped, images, nb, place_groups(images, nb, chain_keeps, &P->chain_off), false))
-      return;
-  }
-  for (int groups = 2, per = nb; !whole && per != 1; ++groups) {
-    per = (nb + groups - 1) / groups;
-    if (n * ((nb + per - 1) / per) > most) return;
-    if (merge(ChainSched::kGrouped, 1, per, place_groups(1, per, chain_keeps, &P->chain_off), false)) return;
+  // Passes only as far as the chain is too large: where some layer's rows of all images and bands fit beside a pass and
+  // nothing behind that layer reads what lies in front of it, the layers behind it run once (the fewest launches are taken).
+  // A pass of the small layers of a chain's end fills no chip: us a call, all layers in passes -> cut, in flight (alone): detector
+  // of 720 x 1280 in 16 bands 148 -> 144 (298 -> 277); VGG-16 stack on two images of 288 x 288 458 -> 438 (678 -> 597);
+  // inverted-residual chain on eight images of 640 x 640 571 -> 563 (886 -> 863), reusing rows 412 -> 400.
+  struct Cut { int layer, images, per; long launches; };
+  auto cuts_of = [&]() {
+    std::vector<Cut> cuts;
+    auto launches = [&](int lo, int hi) {
+      long m = 0;
+      for (int l = lo; l < hi; ++l) m += !P->fuse_chain.away[l];
+      return m;
+    };
+    for (int c = 0; c + 1 < nl; ++c) {
+      bool ok = !P->fuse_chain.away[c] && (n == 1 || (size_t)t.row_elems(c) * t.esz() % 16 == 0);
+      for (int l = c + 1; l < nl && ok; ++l) {
+        const lop_layer_t& d = t.layers[l].d;
+        ok = d.input_from >= c && (d.residual_from == LOP_NO_RESIDUAL || d.residual_from >= c) && (P->fuse_chain.head[l] < 0 || P->fuse_chain.head[l] > c);
+      }
+      if (!ok) continue;
+      const size_t behind = place_cut(c, n, nb, whole);
+      if (behind > kMergeMaxBytes) continue;
+      for (int passes = 2; passes <= n + (whole ? 0 : nb - 1); ++passes) {   // images first, then groups of bands
+        int images = (n + std::min(passes, n) - 1) / std::min(passes, n), per = nb;
+        if (passes > n) { const int groups = passes - n + 1; images = 1; per = (nb + groups - 1) / groups; }
+        if (place_cut(c, images, per, whole) > kMergeMaxBytes) continue;
+        const long made = (long)((n + images - 1) / images) * ((nb + per - 1) / per);
+        if (made <= most) cuts.push_back({c, images, per, made * launches(0, c + 1) + launches(c + 1, nl)});
+        break;
+      }
+    }
+    std::sort(cuts.begin(), cuts.end(), [](const Cut& a, const Cut& b) { return a.launches < b.launches; });
+    return cuts;
+  };
+  auto merge_passes = [&]() {
+    for (int passes = 1, images = 0; images != 1; ++passes) {
+      images = (n + passes - 1) / passes;
+      if (!whole && (n + images - 1) / images > most) return false;
+      if (whole ? merge(ChainSched::kWhole, images, nb, place_whole(images, INT_MAX), false)
+                : merge(ChainSched::kGrouped, images, nb, place_groups(images, nb, chain_keeps, &P->chain_off), false))
+        return true;
+    }
+    for (int groups = 2, per = nb; !whole && per != 1; ++groups) {
+      per = (nb + groups - 1) / groups;
+      if (n * ((nb + per - 1) / per) > most) return false;
+      if (merge(ChainSched::kGrouped, 1, per, place_groups(1, per, chain_keeps, &P->chain_off), false)) return true;
+    }
+    return false;
+  };
+  if (merge_passes()) {
+    const long passes = (long)((n + P->images - 1) / P->images) * ((nb + P->group - 1) / P->group);
+    if (passes == 1) return;
+    long layers = 0;
+    for (int l = 0; l < nl; ++l) layers += !P->fuse_chain.away[l];
+    const ChainSched sched = P->sched;
+    const int images = P->images, per = P->group;
+    const size_t arena_bytes = P->arena_bytes, ws_bytes = P->conv_ws_bytes;
+    const std::vector<std::vector<size_t>> off = P->chain_off;
+    for (const Cut& c : cuts_of()) {
+      if (c.launches >= passes * layers) break;
+      const size_t behind = place_cut(c.layer, n, nb, whole), in_pass = place_cut(c.layer, c.images, c.per, whole);
+      P->cut = c.layer;
+      P->cut_bytes = kept;
+      if (merge(sched, c.images, c.per, std::max(behind, in_pass), false)) return;
+    }
+    P->cut = -1; P->cut_bytes = 0; P->sched = sched; P->images = images; P->group = per;
+    P->arena_bytes = arena_bytes; P->conv_ws_bytes = ws_bytes; P->chain_off = off;
+    return;
   }
   // a chain whose layers keep to their rows: passes over the rows of as many bands as fit, if two do (the launches of
   // one band at a time are better off on four lanes: alone 1 150 against 1 390 us on 65 536 x 1024 -> 4096 -> 1024).
@@ -578,6 +681,8 @@ lop::Slab slab_of(const lop_plan_t* P, int band, int tensor, const void* d_in, v
         const lop_rows_t r = t.bands[band].need[tensor + 1];
         s.row0 = r.lo; s.rows = r.hi - r.lo;
       }
+      // (the passes' last layer keeps all images)
+      if (P->pass_images && tensor == P->cut && s.ptr) s.ptr = (char*)s.ptr + (size_t)P->pass_first * s.rows * t.row_elems(tensor) * t.esz();
     }
   }
   return s;
@@ -1225,98 +1330,108 @@ int front_end(const lop_plan_t* P, int l) {
 // stream, with the scratch set by the caller. y2: where the last launch also stores its rows.
 int enqueue_merged_kernels(lop_plan_t* P, const void* d_in, void* d_out, hipStream_t cs, void* y2) {
   const int nl = P->t.n_layers(), whole = P->t.whole();
-  auto begin_pass = [&]() -> int {
+  // (kept: bytes at the arena's beginning that earlier passes have written)
+  auto begin_pass = [&](size_t kept) -> int {
     if (!(P->flags & LOP_FLAG_POISON_SCRATCH)) return LOP_OK;
-    LOP_HIP(lop::launch_fill_words(P->arena_of(0), align_up(P->arena_bytes, 256), 0xFFFFFFFFu, cs));
+    LOP_HIP(lop::launch_fill_words((char*)P->arena_of(0) + kept, align_up(P->arena_bytes, 256) - kept, 0xFFFFFFFFu, cs));
     LOP_HIP(lop::launch_fill_words(P->ws_of(0), P->conv_ws_bytes / 16 * 16, 0xFFFFFFFFu, cs));
     return LOP_OK;
   };
   const int nb = P->t.n_bands, n = P->t.in.n;
   const size_t out_bytes = (size_t)P->t.layers.back().h_out * P->t.row_elems(nl - 1) * P->t.esz();   // of one image
+  // layers [first, last) of all rows ...
+  auto whole_layers = [&](int first, int last, void* second) -> int {
+    for (int l = first; l < last; ++l) {
+      if (const int e = front_end(P, l); e > 0 && e < last) {
+        const lop::OpLaunch a = make_launch(P, whole, l, d_in, d_out);
+        lop::OpLaunch c = make_launch(P, whole, l + 1, d_in, d_out), q = make_launch(P, whole, e, d_in, d_out);
+        c.y2 = q.y2 = e == nl - 1 ? second : nullptr;
+        if (lop::front_applies(&a, &c, e > l + 1 ? &q : nullptr, 1)) {
+          LOP_HIP(lop::launch_front(&a, &c, e > l + 1 ? &q : nullptr, 1, cs));
+          l = e;
+          continue;
+        }
+      }
+      if (l + 1 < last && pair(P, l)) {
+        const lop::OpLaunch a = make_launch(P, whole, l, d_in, d_out);
+        lop::OpLaunch q = make_launch(P, whole, l + 1, d_in, d_out);
+        q.y2 = l + 1 == nl - 1 ? second : nullptr;
+        if (lop::pair_applies(&a, &q, 1)) {
+          LOP_HIP(lop::launch_pair(&a, &q, 1, cs));
+          ++l;
+          continue;
+        }
+      }
+      if (l + 1 < last && siblings(P, l)) {
+        const lop::OpLaunch a = make_launch(P, whole, l, d_in, d_out), q = make_launch(P, whole, l + 1, d_in, d_out);
+        if (a.out_hi > a.out_lo && lop::siblings_apply(&a, &q, 1)) {
+          LOP_HIP(lop::launch_siblings(&a, &q, 1, cs));
+          ++l;
+          continue;
+        }
+      }
+      LOP_HIP(launch_layer(P, P->fuse_chain, whole, l, d_in, d_out, cs, nullptr, l == nl - 1 ? second : nullptr));
+    }
+    return LOP_OK;
+  };
+  // ... and of bands [b, end)
+  auto grouped_layers = [&](int first, int last, int b, int end, void* second) -> int {
+    const bool together = end - b <= lop::kMaxBandsPerLaunch;
+    for (int l = first; l < last; ++l) {
+      if (const int e = front_end(P, l); e > 0 && e < last && together) {
+        std::vector<lop::OpLaunch> as, convs, qs, none;
+        batched_group(P, l, b, end, d_in, d_out, nullptr, &as, &none);
+        batched_group(P, e, b, end, d_in, d_out, e == nl - 1 ? second : nullptr, &qs, &convs);
+        const bool pooled = e > l + 1;
+        if (as.size() == qs.size() && lop::front_applies(as.data(), pooled ? convs.data() : qs.data(), pooled ? qs.data() : nullptr, (int)as.size())) {
+          LOP_HIP(lop::launch_front(as.data(), pooled ? convs.data() : qs.data(), pooled ? qs.data() : nullptr, (int)as.size(), cs));
+          l = e;
+          continue;
+        }
+      }
+      if (l + 1 < last && together && pair(P, l)) {
+        std::vector<lop::OpLaunch> as, qs, none;
+        batched_group(P, l, b, end, d_in, d_out, nullptr, &as, &none);
+        batched_group(P, l + 1, b, end, d_in, d_out, l + 1 == nl - 1 ? second : nullptr, &qs, &none);
+        if (as.size() == qs.size() && lop::pair_applies(as.data(), qs.data(), (int)as.size())) {
+          LOP_HIP(lop::launch_pair(as.data(), qs.data(), (int)as.size(), cs));
+          ++l;
+          continue;
+        }
+      }
+      if (l + 1 < last && together && siblings(P, l)) {
+        std::vector<lop::OpLaunch> as, qs, none;
+        batched_group(P, l, b, end, d_in, d_out, nullptr, &as, &none);
+        batched_group(P, l + 1, b, end, d_in, d_out, nullptr, &qs, &none);
+        if ((int)as.size() == end - b && qs.size() == as.size() && lop::siblings_apply(as.data(), qs.data(), end - b)) {
+          LOP_HIP(lop::launch_siblings(as.data(), qs.data(), end - b, cs));
+          ++l;
+          continue;
+        }
+      }
+      LOP_HIP(launch_layer_batched(P, l, b, end, d_in, d_out, cs, nullptr, l == nl - 1 ? second : nullptr));
+    }
+    return LOP_OK;
+  };
+  const int in_passes = P->cut < 0 ? nl : P->cut + 1;
   for (int i = 0; i < n; i += P->images) {
     void* const second = y2 ? (char*)y2 + i * out_bytes : nullptr;
     const int images = std::min(P->images, n - i);
-    if (P->sched == ChainSched::kWhole) {
-      for (int b = 0; b < nb; b += P->group) {
-        const lop_rows_t rows = P->group < nb ? pass_rows(P, b, std::min(nb, b + P->group)) : lop_rows_t{0, 0};
-        if (P->group < nb && rows.hi <= rows.lo) continue;
-        if (const int rc = begin_pass(); rc != LOP_OK) return rc;
-        const ChainPass pass(P, i, images, rows);
-        for (int l = 0; l < nl; ++l) {
-          if (const int e = front_end(P, l); e > 0) {
-            const lop::OpLaunch a = make_launch(P, whole, l, d_in, d_out);
-            lop::OpLaunch c = make_launch(P, whole, l + 1, d_in, d_out), q = make_launch(P, whole, e, d_in, d_out);
-            c.y2 = q.y2 = e == nl - 1 ? second : nullptr;
-            if (lop::front_applies(&a, &c, e > l + 1 ? &q : nullptr, 1)) {
-              LOP_HIP(lop::launch_front(&a, &c, e > l + 1 ? &q : nullptr, 1, cs));
-              l = e;
-              continue;
-            }
-          }
-          if (pair(P, l)) {
-            const lop::OpLaunch a = make_launch(P, whole, l, d_in, d_out);
-            lop::OpLaunch q = make_launch(P, whole, l + 1, d_in, d_out);
-            q.y2 = l + 1 == nl - 1 ? second : nullptr;
-            if (lop::pair_applies(&a, &q, 1)) {
-              LOP_HIP(lop::launch_pair(&a, &q, 1, cs));
-              ++l;
-              continue;
-            }
-          }
-          if (siblings(P, l)) {
-            const lop::OpLaunch a = make_launch(P, whole, l, d_in, d_out), q = make_launch(P, whole, l + 1, d_in, d_out);
-            if (a.out_hi > a.out_lo && lop::siblings_apply(&a, &q, 1)) {
-              LOP_HIP(lop::launch_siblings(&a, &q, 1, cs));
-              ++l;
-              continue;
-            }
-          }
-          LOP_HIP(launch_layer(P, P->fuse_chain, whole, l, d_in, d_out, cs, nullptr, l == nl - 1 ? second : nullptr));
-        }
-      }
-      continue;
-    }
-    const ChainPass pass(P, i, images);
     for (int b = 0; b < nb; b += P->group) {
       const int end = std::min(nb, b + P->group);
-      if (const int rc = begin_pass(); rc != LOP_OK) return rc;
-      for (int l = 0; l < nl; ++l) {
-        if (const int e = front_end(P, l); e > 0 && end - b <= lop::kMaxBandsPerLaunch) {
-          std::vector<lop::OpLaunch> as, convs, qs, none;
-          batched_group(P, l, b, end, d_in, d_out, nullptr, &as, &none);
-          batched_group(P, e, b, end, d_in, d_out, e == nl - 1 ? second : nullptr, &qs, &convs);
-          const bool pooled = e > l + 1;
-          if (as.size() == qs.size() && lop::front_applies(as.data(), pooled ? convs.data() : qs.data(), pooled ? qs.data() : nullptr, (int)as.size())) {
-            LOP_HIP(lop::launch_front(as.data(), pooled ? convs.data() : qs.data(), pooled ? qs.data() : nullptr, (int)as.size(), cs));
-            l = e;
-            continue;
-          }
-        }
-        if (end - b <= lop::kMaxBandsPerLaunch && pair(P, l)) {
-          std::vector<lop::OpLaunch> as, qs, none;
-          batched_group(P, l, b, end, d_in, d_out, nullptr, &as, &none);
-          batched_group(P, l + 1, b, end, d_in, d_out, l + 1 == nl - 1 ? second : nullptr, &qs, &none);
-          if (as.size() == qs.size() && lop::pair_applies(as.data(), qs.data(), (int)as.size())) {
-            LOP_HIP(lop::launch_pair(as.data(), qs.data(), (int)as.size(), cs));
-            ++l;
-            continue;
-          }
-        }
-        if (end - b <= lop::kMaxBandsPerLaunch && siblings(P, l)) {
-          std::vector<lop::OpLaunch> as, qs, none;
-          batched_group(P, l, b, end, d_in, d_out, nullptr, &as, &none);
-          batched_group(P, l + 1, b, end, d_in, d_out, nullptr, &qs, &none);
-          if ((int)as.size() == end - b && qs.size() == as.size() && lop::siblings_apply(as.data(), qs.data(), end - b)) {
-            LOP_HIP(lop::launch_siblings(as.data(), qs.data(), end - b, cs));
-            ++l;
-            continue;
-          }
-        }
-        LOP_HIP(launch_layer_batched(P, l, b, end, d_in, d_out, cs, nullptr, l == nl - 1 ? second : nullptr));
-      }
+      const bool part = P->sched == ChainSched::kWhole && P->group < nb;   // (of a chain whose layers keep to their rows)
+      const lop_rows_t rows = part ? pass_rows(P, b, end) : lop_rows_t{0, 0};
+      if (part && rows.hi <= rows.lo) continue;
+      if (const int rc = begin_pass(i + b > 0 ? P->cut_bytes : 0); rc != LOP_OK) return rc;
+      const ChainPass pass(P, i, images, rows);
+      const int rc = P->sched == ChainSched::kWhole ? whole_layers(0, in_passes, second) : grouped_layers(0, in_passes, b, end, second);
+      if (rc != LOP_OK) return rc;
     }
   }
-  return LOP_OK;
+  if (in_passes == nl) return LOP_OK;
+  if (const int rc = begin_pass(P->cut_bytes); rc != LOP_OK) return rc;
+  const ChainPass pass(P, 0, n);
+  return P->sched == ChainSched::kWhole ? whole_layers(in_passes, nl, y2) : grouped_layers(in_passes, nl, 0, nb, y2);
 }
 
 // The kernels of a chain whose launches are merged over the bands (Sec. IV-D operation batching), on
@@ -1429,14 +1544,15 @@ int launch_graph(lop_plan_t* P, const void* d_in, void* d_out, void* h_out, hipS
 
 // The launches of a merged chain (finish kernels and layers that share a launch aside).
 long merged_launches(const lop_plan_t* P) {
-  const int nl = P->t.n_layers(), nb = P->t.n_bands, n = P->t.in.n;
-  const long layers = nl - std::count(P->fuse_chain.away.begin(), P->fuse_chain.away.end(), (char)1);
-  long per_pass = (nb + P->group - 1) / P->group;
-  if (P->sched == ChainSched::kGrouped) {
-    per_pass = 0;
-    for (int b = 0; b < nb; b += P->group) per_pass += (std::min(P->group, nb - b) + lop::kMaxBandsPerLaunch - 1) / lop::kMaxBandsPerLaunch;
+  const int nl = P->t.n_layers(), nb = P->t.n_bands, n = P->t.in.n, in_passes = P->cut < 0 ? nl : P->cut + 1;
+  auto of_bands = [&](int bands) { return P->sched == ChainSched::kGrouped ? (bands + lop::kMaxBandsPerLaunch - 1) / lop::kMaxBandsPerLaunch : 1; };
+  long launches = 0;
+  for (int l = 0; l < nl; ++l) {
+    if (P->fuse_chain.away[l]) continue;
+    if (l >= in_passes) { launches += of_bands(nb); continue; }
+    for (int b = 0; b < nb; b += P->group) launches += of_bands(std::min(P->group, nb - b)) * ((n + P->images - 1) / P->images);
   }
-  return layers * per_pass * ((n + P->images - 1) / P->images);
+  return launches;
 }
 // Merged chains of at most this many launches are enqueued by every call, also where the plan asks for graphs: a graph's
 // launch costs 12 to 15 us of host time however few nodes it has, one of a kernel 2 to 3, and a stream gets through a graph's

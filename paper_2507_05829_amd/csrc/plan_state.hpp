@@ -65,6 +65,8 @@ struct lop_plan_s {
   ChainSched sched = ChainSched::kPerBand;
   int group = 0;   // kGrouped: bands per group; the groups of a chain run one after another
   int images = 0;  // kGrouped, kWhole: images per pass; the passes of a chain run one after another
+  int cut = -1;    // ... of the layers up to this one only (-1: of all); the layers behind it run once, for all images and bands
+  size_t cut_bytes = 0;   // that layer's rows, of all images and bands, at the beginning of the arena
   int pass_first = 0, pass_images = 0;  // while a pass is enqueued: its images (0: all, not in a pass)
   lop_rows_t pass_rows = {0, 0};        // ... and, of a chain whose layers keep to their rows, its rows (empty: all)
   std::vector<float*> d_bias;  // per layer bias (device) or nullptr

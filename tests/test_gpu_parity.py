@@ -2284,3 +2284,21 @@ def test_first_layer_and_the_convolution_behind_it(oracle, c, s, pool, shape, ba
         got, _ = run_gpu(chain, t, use_host=False, flags=flags)
         apart, _ = run_gpu(chain, t, use_host=False, flags=flags | lop.LOP_FLAG_NO_FUSE)
         np.testing.assert_array_equal(np.isfinite(got), np.isfinite(apart))
+
+
+@pytest.mark.parametrize("n,bands,flags", [(5, 1, 0), (5, 4, lop.LOP_FLAG_REUSE | lop.LOP_FLAG_GRAPH), (5, 3, 0), (3, 6, lop.LOP_FLAG_GRAPH), (1, 7, 0)])
+def test_passes_over_the_first_layers_only(oracle, n, bands, flags):
+    """Chains whose first layers are too large for one pass and whose others are not, the last pass over fewer images or bands:
+    what a pass leaves behind stays where it is while the next one runs (scratch poisoned for each), and a residual of a
+    later layer reads it there."""
+    chain = workloads.Chain("passes", (n, 16, 1500 if n == 1 else 400, 640 if n == 1 else 420), "bf16", bands)
+    chain.add(workloads.CONV, 16, 32, 3, 1, 1, act="relu")
+    chain.add(workloads.CONV, 32, 32, 3, 1, 1, act="relu")
+    cut = chain.add(workloads.CONV, 32, 32, 3, 2, 1, act="relu")
+    chain.add(workloads.CONV, 32, 32, 3, 1, 1, act="relu")
+    chain.add(workloads.CONV, 32, 32, 3, 1, 1, act="none", residual_from=cut)
+    chain.add(workloads.CONV, 32, 64, 3, 2, 1, act="relu")
+    t = workloads.make_tensors(chain, zero_bias=False)
+    got, host = run_gpu(chain, t, flags=flags | lop.LOP_FLAG_POISON_SCRATCH)
+    assert rel_err(got, oracle.run_chain(chain, t)) <= TOL["bf16"]
+    np.testing.assert_array_equal(got, host)
