@@ -34,6 +34,11 @@ __device__ __forceinline__ int fastdiv(int n, const FastDiv& f) {
   return (int)((__umulhi((unsigned)n, f.mul) + (unsigned)n) >> f.shift);
 }
 
+// n / d for n < 2^12 and n d < 2^20 (pixels of a tile or a patch) with mul = small_div(d): two instructions at full
+// rate, where a product of 32 bits takes four times as long as others.
+constexpr unsigned small_div(int d) { return d < 1 ? 0u : ((1u << 20) + (unsigned)d - 1) / (unsigned)d; }
+__device__ __forceinline__ int smalldiv(int n, unsigned mul) { return (int)(__umul24((unsigned)n, mul) >> 20); }
+
 __device__ __forceinline__ float to_f32(float v) { return v; }
 __device__ __forceinline__ float to_f32(__bf16 v) { return (float)v; }
 
@@ -102,12 +107,13 @@ __device__ __forceinline__ void mma_part(const u32x4& wa, const u32x4& px, f32x1
 // 8 x 8 tiles that shares 8 pixel tiles and 8 weight tiles. Reduction slices are outermost.
 struct TileId { int m, n, z; };
 constexpr int kXcds = 8, kGroupM = 8;
-// (by_group: division by kGroupM * ny, made on the host; the other divisions of this walk are by
-// constants or lie behind conditions that hold for few workgroups)
+// (by_group: division by kGroupM * ny, made on the host. The last group of a launch has fewer pixel tiles, and small launches
+// have no other: in_group < 8 * 65 535 divided by 1 .. 8 as a product of floats, whose error of 2 in 2^23 parts is less
+// than the 1 / 16 that separates (in_group + 1/2) / gm from the next integer.)
 __device__ __forceinline__ TileId xcd_tile_of(int launch, int mx, int ny, int nz, const FastDiv& by_group) {
   const int total = mx * ny * nz;
-  const int xcd = launch % kXcds, slot = launch / kXcds;
-  const int q = total / kXcds, r = total % kXcds;
+  const int xcd = (unsigned)launch % kXcds, slot = (unsigned)launch / kXcds;
+  const int q = (unsigned)total / kXcds, r = (unsigned)total % kXcds;
   const int v = xcd * q + min(xcd, r) + slot;  // XCD k owns q (+1 for the first r) consecutive tiles
   int z = 0, t = v;
   if (nz > 1) {
@@ -120,7 +126,7 @@ __device__ __forceinline__ TileId xcd_tile_of(int launch, int mx, int ny, int nz
   const int gm = min(kGroupM, mx - first);
   TileId id;
   id.z = z;
-  id.n = gm == kGroupM ? in_group / kGroupM : in_group / gm;
+  id.n = __builtin_amdgcn_readfirstlane((int)(((float)in_group + 0.5f) * __builtin_amdgcn_rcpf((float)gm)));
   id.m = first + in_group - id.n * gm;
   return id;
 }

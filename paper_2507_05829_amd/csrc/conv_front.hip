@@ -41,7 +41,8 @@ struct FrontParams {
   int ph, pw, act, k_steps, C_out, out_lo, R, N, Wc;
   int th, tw, nty, ntx, pitch, ph_rows;   // tile of output pixels; pixels per row of the patch, its rows
   int img_rows, img_words;                // image rows under a patch, 4-byte words of one (odd: rows start on different banks)
-  FastDiv by_ntx, by_nty, by_tw, by_pitch, by_words, by_rows;
+  FastDiv by_ntx, by_nty, by_words, by_rows;
+  unsigned by_tw, by_pitch;          // (small_div)
 };
 static_assert(sizeof(Batch<FrontParams>) <= 4096, "the parameters of all bands of a launch travel as kernel arguments");
 
@@ -73,8 +74,8 @@ __device__ __forceinline__ void front_body(const FrontParams& p, const int bx, c
 
   // ---- this workgroup's tiles: first, first + step, ... below end (XCD k walks the k-th eighth)
   const int tiles = p.N * p.nty * p.ntx;
-  const int parts = gx % kXcds == 0 ? kXcds : 1, step = gx / parts;
-  const int first = (int)((long)tiles * (bx % parts) / parts) + bx / parts, end = (int)((long)tiles * (bx % parts + 1) / parts);
+  const int xs = (unsigned)gx % kXcds == 0 ? 3 : 0, step = gx >> xs, part = bx & ((1 << xs) - 1);   // (8 XCDs)
+  const int first = (int)((long)tiles * part >> xs) + (bx >> xs), end = (int)((long)tiles * (part + 1) >> xs);
   if (first >= end) return;
 
   // ---- the words this thread stages of every tile, [copy][row][word]: the i-th is i * 256 + tid (the last one again
@@ -152,7 +153,7 @@ __device__ __forceinline__ void front_body(const FrontParams& p, const int bx, c
   int win[MID];
 #pragma unroll
   for (int m = 0; m < MID; ++m) {
-    const int i = middle_pixel(m), r = fastdiv(i, p.by_pitch), c = i - r * p.pitch;
+    const int i = middle_pixel(m), r = smalldiv(i, p.by_pitch), c = i - r * p.pitch;
     const int e = c * S1 * 3;
     win[m] = ((COPIES == 2 ? (e & 1) * p.img_rows : 0) + r * S1) * p.img_words + e / 2 + half * 4;
   }
@@ -163,11 +164,11 @@ __device__ __forceinline__ void front_body(const FrontParams& p, const int bx, c
     const int i = (group * 2 + f) * 32 + px;
     int r, c;
     if constexpr (POOL) {   // window by window, so that a window is four neighbouring lanes
-      const int v = i >> 2, vr = fastdiv(v, p.by_tw), vc = v - vr * (p.tw >> 1);   // (by_tw divides by tw / 2)
+      const int v = i >> 2, vr = smalldiv(v, p.by_tw), vc = v - vr * (p.tw >> 1);   // (by_tw divides by tw / 2)
       r = vr * 2 + ((i >> 1) & 1);
       c = vc * 2 + (i & 1);
     } else {
-      r = fastdiv(i, p.by_tw);
+      r = smalldiv(i, p.by_tw);
       c = i - r * p.tw;
     }
     rc[f] = r << 16 | c;
@@ -219,7 +220,7 @@ __device__ __forceinline__ void front_body(const FrontParams& p, const int bx, c
         bool in = true;
         if constexpr (masked) {
           asm volatile("" : "+v"(i));   // (row and column worked out anew, like a border tile's words)
-          const int r = fastdiv(i, p.by_pitch), c = i - r * p.pitch;
+          const int r = smalldiv(i, p.by_pitch), c = i - r * p.pitch;
           in = (h_first + r >= 0) & (h_first + r < p.H1) & (c_first + c >= 0) & (c_first + c < p.W1);
         }
 #pragma unroll

@@ -48,7 +48,8 @@ struct NarrowParams {
   float* b_y;
   const float* b_bias;
   int b_w_steps, b_y_row0, b_y_rows, b_C_out, b_act, b_lo, b_hi, b_first;
-  FastDiv by_ntx, by_nty, by_tw, by_pitch, by_group, by_slots;
+  FastDiv by_ntx, by_nty, by_group, by_slots;
+  unsigned by_tw, by_pitch;          // (small_div)
 };
 static_assert(sizeof(Batch<NarrowParams>) <= 4096, "the parameters of all bands of a launch travel as kernel arguments");
 
@@ -87,18 +88,19 @@ __device__ __forceinline__ void narrow_body(const NarrowParams& p, const int bx,
 
   const __amdgpu_buffer_rsrc_t xbuf = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<float*>(p.x), 0, (int)((size_t)p.N * p.x_rows * p.W * row_bytes), 0x00020000);
-  const int ih0 = (p.out_lo + r0) * p.s - p.ph, iw0 = c0 * p.s - p.pw;
+  const int ih0 = (p.out_lo + r0) * p.s - p.ph - p.x_row0, iw0 = c0 * p.s - p.pw, rows = min(p.x_rows, ih0 + p.ph_rows);   // in the slab
 #pragma unroll
   for (int i = 0; i < LOADS; ++i) {
     const int first = (i * kWaves + wave) * 64;
     if (first >= total) continue;
     const int slot = first + lane;
     const int pix = fastdiv(slot, p.by_slots), k = slot - pix * slots;
-    const int pr = fastdiv(pix, p.by_pitch), pc = pix - pr * p.pitch;
+    const int pr = smalldiv(pix, p.by_pitch), pc = pix - (int)__umul24(pr, p.pitch);
     const int ih = ih0 + pr, iw = iw0 + pc;
-    // (a pixel outside the image or the slab is a load past the buffer's end, which puts zeros into LDS)
-    const bool ok = (k < slots - 1) & (pr < p.ph_rows) & (ih >= p.x_row0) & (ih < p.x_row0 + p.x_rows) & (iw >= 0) & (iw < p.W);
-    const unsigned src = ok ? (unsigned)(((n * p.x_rows + ih - p.x_row0) * p.W + iw) * row_bytes + k * 16) : kOutside;
+    // (a pixel outside the image or the slab is a load past the buffer's end, which puts zeros into LDS; products of 24
+    // bits: a slab has fewer pixels than that)
+    const bool ok = (k < slots - 1) & (ih >= 0) & (ih < rows) & ((unsigned)iw < (unsigned)p.W);
+    const unsigned to = __umul24(__umul24(n * p.x_rows + ih, p.W) + iw, row_bytes) + k * 16, src = ok ? to : kOutside;
     __builtin_amdgcn_raw_ptr_buffer_load_lds(xbuf, (__attribute__((address_space(3))) void*)(smem + first * 16), 16, (int)src, 0, 0, 0);
   }
   asm volatile("" ::: "memory");
@@ -121,7 +123,7 @@ __device__ __forceinline__ void narrow_body(const NarrowParams& p, const int bx,
   const int pixel_bytes = slots * 16;
   int at;
   {
-    const int r = fastdiv(px, p.by_tw), c = px - r * p.tw;
+    const int r = smalldiv(px, p.by_tw), c = px - r * p.tw;
     // (lanes past the tile compute its last row again; they store nothing)
     at = (min(r, p.th - 1) * p.s * p.pitch + c * p.s) * pixel_bytes + kq * 16;
   }
@@ -159,22 +161,31 @@ __device__ __forceinline__ void narrow_body(const NarrowParams& p, const int bx,
 
   // ---- the sixteen partial tiles, added in wavefront order through LDS (over the patch): a lane holds
   // channels kq * 4 + {0..3} of pixel px
+  // (what they are added to is loaded before the others' are there; what the launch has none of, from the beginning of the
+  // filter, and not used)
+  const int e_px = lane >> 2, co = co0 + (lane & 3) * 4;
+  const int r = smalldiv(e_px, p.by_tw), col = c0 + e_px - r * p.tw, row = r0 + r;
+  const int C_out = second ? p.b_C_out : p.C_out;
+  bool live = (r < p.th) & (row < p.R) & (col < p.W_out) & (co < C_out);
+  if (second) live = live & (p.out_lo + row >= p.b_lo) & (p.out_lo + row < p.b_hi);
+  const float* const bias = second ? p.b_bias : p.bias;
+  const bool has_res = p.res && !second;
+  f32x4 bias_v, res_v;
+  if (wave == 0) {
+    bias_v = *(const f32x4*)((bias ? bias : (const float*)p.wd16) + (bias && live ? co : 0));
+    res_v = *(const f32x4*)((has_res ? p.res : (const float*)p.wd16) +
+                            (has_res && live ? ((size_t)(n * p.r_rows + p.out_lo + row - p.r_row0) * p.W_out + col) * p.C_out + co : 0));
+  }
   __syncthreads();
   float* const part = (float*)smem;
   *(f32x4*)(part + wave * (16 * kPartPitch) + px * kPartPitch + kq * 4) = acc;
   __syncthreads();
-  if (wave != 0) return;
-  const int e_px = lane >> 2, co = co0 + (lane & 3) * 4;
-  const int r = fastdiv(e_px, p.by_tw), col = c0 + e_px - r * p.tw, row = r0 + r;
-  const int C_out = second ? p.b_C_out : p.C_out;
-  if (r >= p.th || row >= p.R || col >= p.W_out || co >= C_out) return;
-  if (second && (p.out_lo + row < p.b_lo || p.out_lo + row >= p.b_hi)) return;
+  if (wave != 0 || !live) return;
   f32x4 v = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int s = 0; s < kWaves; ++s) v += *(const f32x4*)(part + s * (16 * kPartPitch) + e_px * kPartPitch + (lane & 3) * 4);
-  const float* const bias = second ? p.b_bias : p.bias;
-  if (bias) v += *(const f32x4*)(bias + co);
-  if (p.res && !second) v += *(const f32x4*)(p.res + ((size_t)(n * p.r_rows + p.out_lo + row - p.r_row0) * p.W_out + col) * p.C_out + co);
+  if (bias) v += bias_v;
+  if (has_res) v += res_v;
   const Clamp cl = make_clamp(second ? p.b_act : p.act);
 #pragma unroll
   for (int j = 0; j < 4; ++j) v[j] = clamp_act(v[j], cl);
@@ -244,8 +255,8 @@ NarrowParams make_narrow(const OpLaunch& L, unsigned gy, unsigned* gx) {
   p.nty = (p.R + t.th - 1) / t.th; p.ntx = (p.W_out + t.tw - 1) / t.tw;
   p.pitch = (t.tw - 1) * p.s + 3; p.ph_rows = (t.th - 1) * p.s + 3;
   p.b_first = kNoSibling;
-  p.by_ntx = make_fastdiv(p.ntx); p.by_nty = make_fastdiv(p.nty); p.by_tw = make_fastdiv(t.tw);
-  p.by_pitch = make_fastdiv(p.pitch); p.by_group = make_fastdiv(kGroupM * (int)gy);
+  p.by_ntx = make_fastdiv(p.ntx); p.by_nty = make_fastdiv(p.nty); p.by_tw = small_div(t.tw);
+  p.by_pitch = small_div(p.pitch); p.by_group = make_fastdiv(kGroupM * (int)gy);
   p.by_slots = make_fastdiv(p.C_in / 4 + 1);
   *gx = (unsigned)t.tiles;
   return p;

@@ -50,11 +50,11 @@ constexpr int kPixelBytes = 144, kPixelSlots = 9;
 template <bool POOL>
 __device__ __forceinline__ void tile_pixel(const PatchParams& p, int i, int& r, int& c) {
   if constexpr (POOL) {
-    const int v = i >> 2, vr = fastdiv(v, p.by_tw), vc = v - vr * (p.tw >> 1);   // (by_tw divides by tw / 2)
+    const int v = i >> 2, vr = smalldiv(v, p.by_tw), vc = v - vr * (p.tw >> 1);   // (by_tw divides by tw / 2)
     r = vr * 2 + ((i >> 1) & 1);
     c = vc * 2 + (i & 1);
   } else {
-    r = fastdiv(i, p.by_tw);
+    r = smalldiv(i, p.by_tw);
     c = i - r * p.tw;
   }
 }
@@ -223,21 +223,41 @@ __device__ __forceinline__ void patch_finish(const PatchParams& p, unsigned char
   out.store(p, t, sum, lane);
 }
 
+// Where the pixels of a patch lie in the input slab. What a workgroup works out before its first load is issued is
+// waited for by all of it, and with few wavefronts on a compute unit an instruction takes about five cycles, a product of 32 bits
+// about twenty: all products here are of 24 bits (the slab has less than 2^24 pixels of 128 bytes or more, see patch_shape).
+// 206 instructions in front of the first load became 140; with the same in the walking and the narrow kernel (370 became 40
+// and 150 about 115) chains take, us alone: detector encoder in 16 bands 279 -> 273, bf16 stack in 8 bands 222 -> 217, fp32
+// backbone with shared rows 146 -> 140 (in flight 80.7 -> 78.5 beside other streams).
+template <int S>
+struct PatchWindow {
+  int row, rows, col, base;   // first row and column, rows of the patch up to the slab's end; row 0 of the image
+  __device__ __forceinline__ PatchWindow(const PatchParams& p, const PatchAt& t) {
+    row = (p.out_lo + t.r0) * S - p.ph - p.x_row0;
+    rows = min(p.x_rows, row + p.ph_rows);
+    col = t.c0 * S - p.pw;
+    base = t.n * p.x_rows;
+  }
+  // `bytes` into the patch's pixel `pix`, or outside
+  __device__ __forceinline__ unsigned at(const PatchParams& p, int pix, int row_bytes, int bytes) const {
+    const int pr = smalldiv(pix, p.by_pitch), pc = pix - (int)__umul24(pr, p.pitch), half_cols = p.pitch >> 1;
+    const int ih = row + pr, iw = col + (S == 1 ? pc : (pc < half_cols ? 2 * pc : 2 * (pc - half_cols) + 1));
+    const unsigned px = __umul24(base + ih, p.W) + iw, to = __umul24(px, row_bytes) + bytes;
+    return (ih >= 0) & (ih < rows) & ((unsigned)iw < (unsigned)p.W) ? to : kOutside;
+  }
+};
+
 // The slots of a patch that this lane fetches (16 bytes each; the ninth of every nine slots, and what lies outside the
 // patch, the slab or the image, is a load past the buffer's end).
 template <int NI, int S>
 __device__ __forceinline__ void patch_slots(const PatchParams& p, const PatchAt& t, int wave, int lane, unsigned (&src)[NI], int row_bytes) {
-  const int ih0 = (p.out_lo + t.r0) * S - p.ph, iw0 = t.c0 * S - p.pw;
-  const int half_cols = p.pitch >> 1;
+  const PatchWindow<S> win(p, t);
 #pragma unroll
   for (int i = 0; i < NI; ++i) {
     const int slot = (i * 4 + wave) * 64 + lane;
-    const int pix = slot / kPixelSlots, k = slot - pix * kPixelSlots;
-    const int pr = fastdiv(pix, p.by_pitch), pc = pix - pr * p.pitch;
-    const int col = S == 1 ? pc : (pc < half_cols ? 2 * pc : 2 * (pc - half_cols) + 1);
-    const int ih = ih0 + pr, iw = iw0 + col;
-    const bool ok = (k < 8) & (pr < p.ph_rows) & (ih >= p.x_row0) & (ih < p.x_row0 + p.x_rows) & (iw >= 0) & (iw < p.W);
-    src[i] = ok ? (unsigned)(((t.n * p.x_rows + ih - p.x_row0) * p.W + iw) * row_bytes + k * 16) : kOutside;
+    const int pix = smalldiv(slot, small_div(kPixelSlots)), k = slot - pix * kPixelSlots;
+    const unsigned at = win.at(p, pix, row_bytes, k * 16);
+    src[i] = k < 8 ? at : kOutside;
   }
 }
 
@@ -577,14 +597,12 @@ __device__ __forceinline__ void patch_split_body(const PatchParams& p, const int
   };
   // ---- the pieces this lane moves of every patch: channels 4 k .. 4 k + 3 of pixel threadIdx.x / 8 + 32 i
   const int k4 = threadIdx.x & 7;
+  const PatchWindow<S> win(p, tile);
   unsigned src[NI];
 #pragma unroll
   for (int i = 0; i < NI; ++i) {
     const int pix = i * 32 + (int)(threadIdx.x >> 3);
-    const int pr = fastdiv(pix, p.by_pitch), pc = pix - pr * p.pitch, half_cols = p.pitch >> 1;
-    const int col = S == 1 ? pc : (pc < half_cols ? 2 * pc : 2 * (pc - half_cols) + 1);
-    const unsigned at = pr < p.ph_rows ? input(ih0 + pr, iw0 + col) : kOutside;
-    src[i] = at == kOutside ? kOutside : at + k4 * 16;
+    src[i] = win.at(p, pix, row_bytes, k4 * 16);
   }
   u32x4 raw[2][NI];   // of the next two patches
   // (Loads are issued for patches past the last one, too, from outside the buffer or of the last filter again: a
@@ -780,7 +798,7 @@ bool patch_shape(const OpLaunch& L) {
   const int esz = bf ? 2 : 4, ke = 16 / esz;
   if (L.op != LOP_CONV2D || !L.wd || L.kh != 3 || L.kw != 3 || L.dh != 1 || L.dw != 1) return false;
   if (L.sh != L.sw || (L.sh != 1 && L.sh != 2)) return false;
-  if (L.x.c * esz % 128 != 0 || L.y.c % ke != 0 || (!bf && !L.w3)) return false;
+  if (L.x.c * esz % 128 != 0 || (size_t)L.x.c * esz >= (1 << 24) || L.y.c % ke != 0 || (!bf && !L.w3)) return false;
   return (size_t)L.x.n * L.x.rows * L.x.w * L.x.c * esz < ((size_t)1 << 31);
 }
 

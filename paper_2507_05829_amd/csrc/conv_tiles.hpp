@@ -43,7 +43,8 @@ struct PatchParams {
   int Wc;                            // its columns
   int th, tw, nty, ntx;              // tile of output pixels, tiles per image in either direction
   int pitch, ph_rows;                // pixel slots per row of the patch (S == 2: even columns, then odd), its rows
-  FastDiv by_ntx, by_nty, by_tw, by_pitch, by_group;
+  unsigned by_tw, by_pitch;          // (small_div)
+  FastDiv by_ntx, by_nty, by_group;
   Sibling sib;
 };
 static_assert(sizeof(Batch<PatchParams>) <= 4096, "the parameters of all bands of a launch travel as kernel arguments");
@@ -104,8 +105,8 @@ inline PatchParams make_patch(const OpLaunch& c, const OpLaunch* pool, int pixel
   p.pitch = c.sh == 1 ? t.tw + 2 : 2 * (t.tw + 1);
   p.ph_rows = (t.th - 1) * c.sh + 3;
   p.by_ntx = make_fastdiv(p.ntx); p.by_nty = make_fastdiv(p.nty);
-  p.by_tw = make_fastdiv(pool ? t.tw / 2 : t.tw);
-  p.by_pitch = make_fastdiv(p.pitch);
+  p.by_tw = small_div(pool ? t.tw / 2 : t.tw);
+  p.by_pitch = small_div(p.pitch);
   p.by_group = make_fastdiv(kGroupM * (int)gy);
   p.sib = Sibling{nullptr, nullptr, nullptr, 0, 0, 0, 0, 0, 0, 0, kNoSibling};
   *tiles = (unsigned)t.tiles;

@@ -2302,3 +2302,17 @@ def test_passes_over_the_first_layers_only(oracle, n, bands, flags):
     got, host = run_gpu(chain, t, flags=flags | lop.LOP_FLAG_POISON_SCRATCH)
     assert rel_err(got, oracle.run_chain(chain, t)) <= TOL["bf16"]
     np.testing.assert_array_equal(got, host)
+
+
+@pytest.mark.parametrize("dtype,h", [("bf16", h) for h in (5, 9, 13, 23, 27, 31, 37)] + [("f32", 11), ("f32", 33)])
+def test_tiles_of_a_last_group(oracle, dtype, h):
+    """One to ten pixel tiles beside 33 channel tiles: the groups of eight pixel tiles that a launch's walk goes down, with every
+    size of its last one; small integers, bit for bit."""
+    chain = workloads.Chain("groups", (1, 64, h, 8), dtype, 1)
+    chain.add(workloads.CONV, 64, 1048, 3, 1, 1, act="relu")
+    t = workloads.small_int_tensors(chain, seed=h)
+    if dtype == "bf16":
+        t.weights = [np.sign(w) * (np.abs(w) > 1) * (np.arange(w.size).reshape(w.shape) % 5 == 0) for w in t.weights]
+    want = oracle.run_chain(chain, t)
+    assert np.abs(want).max() <= (256 if dtype == "bf16" else 2 ** 24)
+    np.testing.assert_array_equal(run_gpu(chain, t)[0], want)
