@@ -367,7 +367,7 @@ __device__ __forceinline__ void gemm_body(const GemmParams& p, unsigned char* co
 template <typename T, int BM, int BN, int WM, int WN, int NST>
 __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(2))) void conv_gemm_kernel(const GemmParams p) {
   __shared__ __attribute__((aligned(1024))) unsigned char smem[gemm_smem<BM, BN, WM, WN, NST>()];
-  if constexpr (BM == 256) {
+  if constexpr (BM >= 192) {
     if (p.mx) return gemm_body<T, BM, BN, WM, WN, NST, true>(p, smem, blockIdx.x, gridDim.x, p.mx, p.ny);
   }
   gemm_body<T, BM, BN, WM, WN, NST, false>(p, smem, blockIdx.x + gridDim.x * blockIdx.y, 0, gridDim.x, gridDim.y);
@@ -640,7 +640,7 @@ bool gemm_shape(const OpLaunch& L) {
   return (size_t)L.x.n * L.x.rows * L.x.w * L.x.c * esz < ((size_t)1 << 31);
 }
 
-// Workgroups of a launch of 256 x 256 tiles: one per compute unit, each of which walks over its share of the tiles (and, the
+// Workgroups of a launch of 256 x 256 or 192 x 256 tiles: one per compute unit, each of which walks over its share of the tiles (and, the
 // number being a multiple of the XCDs, over tiles of the XCD it runs on).
 constexpr long kWalkers = 256;
 
@@ -657,6 +657,19 @@ constexpr long kWalkers = 256;
 // 48.9 / 47.8 and 104 / 87.7 / 92.1, 16000 -> 2048 (2 000) 66.1 / 63.1 / 62.4 and 137 / 119 / 121.
 struct GemmChoice { int bm = 0, bn = 0; bool split = false; };
 constexpr long kBigTiles = 128;        // 256 x 256, bf16
+// 192 x 256, bf16, in place of 256 x 256 where the last of several rounds of those would be at most a third full and whole
+// rounds of the smaller, which take 0.8 of the time each, cost less. us a call of two layers on one stream and (in flight),
+// 256 -> 192 in the layer whose tiles are given: 9000 x 1024 -> 4096 (576 -> 752) -> 1024 235 -> 219 (210 -> 205), 9000 x 512 ->
+// 2048 (288 -> 376) -> 512 74.7 -> 68.7 (62.7 -> 61.0), 18 000 x 256 -> 1024 (284 -> 376) -> 256 51.5 -> 47.2 (37.1 -> 35.8),
+// 45 000 x 600 -> 1000 -> 600 (528 -> 705) 222 -> 194 (177 -> 176), 25 000 x 768 -> 3072 -> 768 (294 -> 393) 292 -> 284 (277 ->
+// 274). With longer reductions the chip, which these products keep at the power it may draw, loses in flight what one stream
+// gains: 20 000 x 1024 -> 4096 -> 1024 (316 -> 420) 383 -> 375 (365 -> 369). With half a last round there is nothing to gain:
+// 24 000 x 1000 -> 2000 -> 1000 (376 -> 500) 230 -> 231 (216 -> 219). A single round is left to the larger tile, which other
+// launches run beside (65 536 x 1024 -> 4096 -> 1024 in eight bands on four streams 1 008 -> 1 068). Reductions of fewer
+// than 256 elements, three stages and less, keep the larger tile and its walk, though 33 000 x 128 -> 512 (258 -> 344) -> 128
+// would gain as well (40.5 -> 37.6).
+constexpr double kLessTile = 0.8;
+constexpr int kLessMinK = 256, kLessMaxK = 3072;
 constexpr long kWideTiles = 192;       // 128 x 256, bf16
 constexpr long kNarrowTiles = 384;     // 128 x 64, bf16
 constexpr long kF32BigTiles = 1024;    // 128 x 128, fp32
@@ -688,7 +701,12 @@ GemmChoice choose_gemm(const OpLaunch* Ls, int n) {
     return t * ((c_out + bn - 1) / bn);
   };
   if (Ls[0].dtype == LOP_BF16) {
-    if (tiles(256, 256) >= kBigTiles) return {256, 256};
+    if (const long t = tiles(256, 256); t >= kBigTiles) {
+      auto rounds = [](long n) { return (double)((n + kWalkers - 1) / kWalkers); };
+      const long last = t % kWalkers;
+      const bool thin = Ls[0].x.c >= kLessMinK && Ls[0].x.c <= kLessMaxK && t > kWalkers && last > 0 && 3 * last <= kWalkers;
+      return thin && rounds(tiles(192, 256)) * kLessTile < rounds(t) ? GemmChoice{192, 256} : GemmChoice{256, 256};
+    }
     if (tiles(128, 64) < kNarrowTiles) return {};
     return tiles(128, 256) >= kWideTiles ? GemmChoice{128, 256} : GemmChoice{128, 64};
   }
@@ -700,7 +718,7 @@ GemmChoice choose_gemm(const OpLaunch* Ls, int n) {
   return tiles(64, 64) >= kF32Tiles ? GemmChoice{64, 64} : GemmChoice{};
 }
 
-// Whether a launch of 256 x 256 tiles walks. Not with a residual: its loads would wait for the next tile's, which are older (17 497 x
+// Whether a launch of 256 x 256 or 192 x 256 tiles walks. Not with a residual: its loads would wait for the next tile's, which are older (17 497 x
 // 504 -> 888 behind 888 -> 504, chains in flight: 53.5 us a call if both walk, 47.1 if the first does, 49.0 if none). Nor with a second destination, of
 // the size that has one a launch has no second round.
 bool walks(const GemmParams& p) { return !p.res && !p.y2; }
@@ -723,7 +741,7 @@ hipError_t launch_tile(void (*single)(const GemmParams), void (*bands)(const Bat
     ++m;
   }
   if (m == 0) return hipSuccess;
-  if (BM == 256 && m == 1 && walks(ps[0])) {
+  if (BM >= 192 && m == 1 && walks(ps[0])) {
     ps[0].mx = (int)gx[0]; ps[0].ny = (int)gy;
     const long tiles = (long)gx[0] * gy;
     return launch_kernel(single, dim3((unsigned)std::min(tiles, kWalkers)), dim3(THREADS), s, ev, ps[0]);
@@ -757,6 +775,7 @@ hipError_t launch_gemm(const OpLaunch* Ls, int n, hipStream_t s, KernelEvents* e
   const GemmChoice c = choose_gemm(Ls, n);
   if (Ls[0].dtype == LOP_BF16) {
     if (c.bm == 256) return launch_direct<__bf16, 256, 256, 2, 4, 2>(Ls, n, s, ev);
+    if (c.bm == 192) return launch_direct<__bf16, 192, 256, 2, 4, 2>(Ls, n, s, ev);
     if (c.bm == 128 && c.bn == 256) return launch_direct<__bf16, 128, 256, 2, 4, 3>(Ls, n, s, ev);
     if (c.bm == 128) return launch_direct<__bf16, 128, 64, 2, 2, 3>(Ls, n, s, ev);
     return hipErrorInvalidValue;
@@ -776,7 +795,7 @@ int gemm_describe(const OpLaunch* Ls, int n, char* name, size_t size) {
     snprintf(name, size, "conv_gemm_split_kernel%s<%d, %d, 1, %d>", m > 1 ? "_bands" : "", c.bm, c.bn, c.bn / 32);
   else if (name && size)   // (tile, wavefronts in either direction, stages: as launch_gemm takes them)
     snprintf(name, size, "conv_gemm_kernel%s<%s, %d, %d, 2, %d, %d>", m > 1 ? "_bands" : "", bf ? "__bf16" : "float", c.bm, c.bn,
-             bf && c.bn == 256 ? 4 : 2, c.bm == 256 || (!bf && c.bm == 128) ? 2 : 3);
+             bf && c.bn == 256 ? 4 : 2, c.bm >= 192 || (!bf && c.bm == 128) ? 2 : 3);
   return 1;
 }
 
