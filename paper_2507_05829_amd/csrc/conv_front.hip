@@ -6,11 +6,12 @@
 // kernel (conv_walk.hip). For a tile it stages the image rows under it in LDS (4 bytes per load, on their way while the tile before is
 // worked on), computes the first layer's pixels under the tile's windows (1.3 to 1.4 times the tile's: halos are computed again) into a
 // patch in LDS, zero where they lie outside that layer's image (the second layer's padding), and multiplies 64 pixels by 32
-// channels per wavefront over the whole reduction. Roundings are those of the two launches.
+// channels per wavefront over the whole reduction. Products, sums and roundings are those of the first layer's own launch and of
+// the walking kernel, in their order: the bits are the same wherever those two are what it stands for.
 // What bounds it: a tile's chain of image, first layer, second layer between two barriers, with two or three workgroups on a
-// compute unit; vector and matrix instructions are busy for a third of the time each. Bounds, masks and zeros only at the borders, the
-// first layer's sums starting from its bias: 92 -> 39 vector instructions for 32 of its pixels, the 720p encoder with independent
-// bands in flight 153.6 -> 149.5 us.
+// compute unit; vector and matrix instructions are busy for a third of the time each. Bounds, masks and zeros only at the
+// borders: the 720p encoder with independent bands in flight 153.6 -> 149.5 us. (The first layer's sums started from its bias save 16
+// additions for 32 of its pixels and no time that can be measured, 136.3 and 136.6 us, but are not that layer's bits.)
 // (What it is worth, measured: see kFrontTiles64.)
 #include <hip/hip_runtime.h>
 
@@ -203,11 +204,7 @@ __device__ __forceinline__ void front_body(const FrontParams& p, const int bx, c
 #pragma unroll
         for (int k = 0; k < NT; ++k)
 #pragma unroll
-          for (int g = 0; g < 4; ++g) {
-            const f32x4 b = *(const f32x4*)(bias_s[0] + k * 32 + g * 8 + half * 4);
-#pragma unroll
-            for (int j = 0; j < 4; ++j) acc[k][g * 4 + j] = b[j];
-          }
+          for (int i = 0; i < 16; ++i) acc[k][i] = 0.f;
 #pragma unroll
         for (int r = 0; r < 3; ++r) {   // a filter row: elements 0 .. 7 in the lower half of the wavefront, element 8 in the upper
           const unsigned* const src = image_s + win[m] + r * p.img_words;
@@ -226,10 +223,11 @@ __device__ __forceinline__ void front_body(const FrontParams& p, const int bx, c
 #pragma unroll
         for (int k = 0; k < NT; ++k)
 #pragma unroll
-          for (int g = 0; g < 4; ++g) {
+          for (int g = 0; g < 4; ++g) {   // (the bias behind the products, as the layer's own launch adds it)
+            const f32x4 b = *(const f32x4*)(bias_s[0] + k * 32 + g * 8 + half * 4);
             alignas(8) __bf16 o[4];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) o[j] = (__bf16)clamp_act(acc[k][g * 4 + j], cl1);
+            for (int j = 0; j < 4; ++j) o[j] = (__bf16)clamp_act(acc[k][g * 4 + j] + b[j], cl1);
             uint2 v = *(const uint2*)o;
             if (masked && !in) v = make_uint2(0u, 0u);
             *(uint2*)(to + k * 64 + g * 16) = v;

@@ -2308,6 +2308,39 @@ def test_first_layer_and_the_convolution_behind_it(oracle, c, s, pool, shape, ba
         np.testing.assert_array_equal(np.isfinite(got), np.isfinite(apart))
 
 
+@pytest.mark.parametrize("c,s,pool,shape", [
+    (32, 2, False, (1, 3, 451, 433)), (32, 1, False, (1, 3, 221, 226)), (64, 1, True, (1, 3, 225, 223)), (64, 1, False, (2, 3, 150, 161)),
+    (64, 2, True, (1, 3, 430, 447)), (64, 2, False, (1, 3, 433, 440)),
+])
+def test_first_layer_in_the_launch_behind_it_has_the_bits_of_its_own(c, s, pool, shape):
+    """A chain's launch of both layers against the first-layer and the walking kernel, which run where a band is run by itself:
+    the same products, added and rounded in the same order, so the same bits, for any number of bands."""
+    def make(bands):
+        chain = workloads.Chain("front", shape, "bf16", bands)
+        chain.add(workloads.CONV, 3, c, 3, s, 1, act="relu")
+        chain.add(workloads.CONV, c, c, 3, 1, 1, act="relu")
+        if pool:
+            chain.add(workloads.MAXPOOL, c, c, 2, 2, 0)
+        return chain
+    t = workloads.make_tensors(make(1), zero_bias=False)
+    plan = lop.Plan(make(1), t)
+    try:
+        assert plan.layer_kernel(0, 0)[0].startswith("conv_stem_mfma_"), plan.layer_kernel(0, 0)
+        assert plan.layer_kernel(0, 2 if pool else 1)[0].startswith("conv_walk_kernel"), plan.layer_kernel(0, 1)
+        d_in, apart = to_device_nhwc(t.x, "bf16"), empty_out(plan.out_shape(), "bf16")
+        plan.run_band(0, d_in, apart)
+        plan.synchronize()
+        check_margins(apart)
+        want = to_nchw(apart)
+    finally:
+        plan.destroy()
+    assert np.isfinite(want).all()
+    for bands, flags in ((1, 0), (3, 0), (4, lop.LOP_FLAG_REUSE)):
+        got, host = run_gpu(make(bands), t, flags=flags)
+        np.testing.assert_array_equal(got, want)
+        np.testing.assert_array_equal(host, want)
+
+
 @pytest.mark.parametrize("n,bands,flags", [(5, 1, 0), (5, 4, lop.LOP_FLAG_REUSE | lop.LOP_FLAG_GRAPH), (5, 3, 0), (3, 6, lop.LOP_FLAG_GRAPH), (1, 7, 0)])
 def test_passes_over_the_first_layers_only(oracle, n, bands, flags):
     """Chains whose first layers are too large for one pass and whose others are not, the last pass over fewer images or bands:
