@@ -18,6 +18,7 @@
 #include <cstring>
 #include <map>
 #include <mutex>
+#include <utility>
 #include <vector>
 
 namespace {
@@ -47,6 +48,8 @@ std::map<const void*, Handle> g_handles;  // every handle ever handed out (addre
                                           // handle objects are leaked on purpose, allocations are
                                           // quarantined by the sanitizer)
 std::map<const void*, size_t> g_pinned;   // host ranges registered as mapped pinned memory
+std::map<const void*, const char*> g_kernels;   // host function -> its (mangled) name
+std::vector<std::pair<const char*, long>> g_launched;   // names and workgroups along x, in order, since hipstub_forget
 long g_launches = 0, g_created[kKinds] = {0}, g_live[kKinds] = {0};
 Clock g_host;                             // what the host has waited for
 const void* g_marked = nullptr;           // hipstub_mark: the stream, how far it was, launches not ordered behind that
@@ -118,11 +121,24 @@ void hipstub_mark(const void* s) {
 }
 long hipstub_unordered(void) { std::lock_guard<std::mutex> l(g_mu); return g_unordered; }
 long hipstub_launches(void) { std::lock_guard<std::mutex> l(g_mu); return g_launches; }
+// The kernels launched (or captured) since hipstub_forget: the i-th one's name, or nullptr, and its workgroups along x.
+void hipstub_forget(void) { std::lock_guard<std::mutex> l(g_mu); g_launched.clear(); }
+const char* hipstub_launched(long i) {
+  std::lock_guard<std::mutex> l(g_mu);
+  return i >= 0 && i < (long)g_launched.size() ? g_launched[i].first : nullptr;
+}
+long hipstub_launched_workgroups(long i) {
+  std::lock_guard<std::mutex> l(g_mu);
+  return i >= 0 && i < (long)g_launched.size() ? g_launched[i].second : -1;
+}
 
 // ---- what hipcc's host code calls around a kernel launch
 void** __hipRegisterFatBinary(const void*) { static void* h = nullptr; return &h; }
 void __hipUnregisterFatBinary(void**) {}
-void __hipRegisterFunction(void**, const void*, char*, const char*, unsigned, void*, void*, void*, void*, int*) {}
+void __hipRegisterFunction(void**, const void* fn, char*, const char* name, unsigned, void*, void*, void*, void*, int*) {
+  std::lock_guard<std::mutex> l(g_mu);
+  g_kernels[fn] = name;
+}
 void __hipRegisterVar(void**, void*, char*, const char*, int, size_t, int, int) {}
 hipError_t __hipPushCallConfiguration(dim3 grid, dim3 block, size_t shmem, hipStream_t stream) {
   t_cfg = {grid, block, shmem, stream};
@@ -142,6 +158,8 @@ static hipError_t launch(const void* fn, dim3 grid, dim3 block, hipStream_t s, c
   if (grid.y > 65535 || grid.z > 65535) die("%s: grid.y or grid.z above 65535", what);
   if ((unsigned long)grid.x * block.x > 0xffffffffUL) die("%s: 2^32 threads or more along x", what);
   ++g_launches;
+  const auto named = g_kernels.find(fn);
+  g_launched.push_back({named == g_kernels.end() ? "" : named->second, (long)grid.x});
   return hipSuccess;
 }
 hipError_t hipLaunchKernel(const void* fn, dim3 grid, dim3 block, void**, size_t, hipStream_t s) {

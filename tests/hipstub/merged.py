@@ -11,17 +11,22 @@ import types
 
 stub_dir, check = sys.argv[1], sys.argv[2]
 HERE = os.path.dirname(os.path.abspath(__file__))
-sys.path[:0] = [stub_dir, os.path.dirname(os.path.dirname(HERE))]
+sys.path[:0] = [stub_dir, os.path.dirname(os.path.dirname(HERE)), os.path.dirname(HERE)]
 sys.modules["torch"] = types.ModuleType("torch")   # the binding imports it only for its runtime
 
 import numpy as np  # noqa: E402
 
 import workloads  # noqa: E402
+import joined_chains as joined  # noqa: E402
 from paper_2507_05829_amd import lop  # noqa: E402
 
 assert lop.LIB_PATH.startswith(stub_dir), lop.LIB_PATH
 stub = ctypes.CDLL(os.path.join(stub_dir, "paper_2507_05829_amd", "libhipstub.so"))
 stub.hipstub_unordered.restype = ctypes.c_long
+stub.hipstub_launched.restype = ctypes.c_char_p
+stub.hipstub_launched.argtypes = [ctypes.c_long]
+stub.hipstub_launched_workgroups.restype = ctypes.c_long
+stub.hipstub_launched_workgroups.argtypes = [ctypes.c_long]
 stub.hipstub_mark.argtypes = [ctypes.c_void_p]
 stub.hipStreamCreateWithFlags.argtypes = [ctypes.c_void_p, ctypes.c_uint]
 stub.hipStreamDestroy.argtypes = [ctypes.c_void_p]
@@ -317,7 +322,60 @@ def matrix_rows():
     return bad
 
 
-bad = {"matrix_rows": matrix_rows, "copy_streams": copy_streams, "timed_layer": timed_layer, "grids": grids, "poison": poison, "order_of_streams": order_of_streams, "workspace": workspace, "wide_tiles": wide_tiles, "static_scratch": static_scratch}[check]()
+def kernels(plan, out=None, stream=None):
+    """What a call launches, or captures: (name, workgroups along x) of each. The result lies apart from the input."""
+    n, c, h, w = plan.out_shape()
+    result = np.zeros(n * c * h * w * 4 + 16, np.uint8) if out is None else None
+    stub.hipstub_forget()
+    plan.run_chain(TENSOR, (result.ctypes.data + 15) & ~15 if out is None else out, None, stream)
+    plan.synchronize()
+    got = []
+    while stub.hipstub_launched(len(got)) is not None:
+        got.append((stub.hipstub_launched(len(got)).decode(), stub.hipstub_launched_workgroups(len(got))))
+    return got
+
+
+def joined_launches():
+    """The chains of joined_chains.py make the launches that their tests on the GPU are about: a pair or a first layer and the
+    convolution behind it in one launch, over bands with slabs of their own where there are such, and with more tiles than workgroups
+    where those are to take several."""
+    bad = []
+
+    def launches(chain, flags):
+        plan = make(chain, flags)
+        got = kernels(plan)
+        plan.destroy()
+        return got
+
+    for dtype in ("f32", "bf16"):
+        for shape, bands, flags, acts in joined.PAIRS:
+            for around in joined.AROUND:
+                names = [n for n, _ in launches(joined.pair(shape, dtype, bands, acts, around), flags)]
+                want = {"alone": ["P"], "first": ["P", "-"], "last": ["-", "P"]}.get(around, ["-"] * 4)
+                slabs = around in ("first", "last") and bands > 1 and not flags & lop.LOP_FLAG_REUSE
+                if ["P" if "conv_pair_kernel" in n else "-" for n in names] != want or any("conv_pair_kernel_bands" in n for n in names) != slabs:
+                    bad.append((shape, bands, flags, dtype, around, names))
+    fronts = [(f, behind, flags) for *f, flags in joined.FRONTS for behind in (False, True)]
+    walked = [([*f, bands], False, flags) for f in joined.WALKED_FRONTS for bands, flags in joined.WALKED_AS]
+    several = set()
+    for f, behind, flags in fronts + walked:
+        c, s, pool, (n, _, h, w), bands = f
+        got = launches(joined.front(*f, behind), flags)
+        if ["F" if "conv_front_kernel" in name else "-" for name, _ in got] != ["F", "-"][:1 + behind]:
+            bad.append((f, behind, flags, got))
+        tiles = n * -(-h // s) * -(-w // s) / (256 if c == 32 else 128)      # (at least)
+        if tiles > got[0][1] > 0 and got[0][1] <= (768 if c == 32 else 512):
+            several.add((c, s, pool, "_bands" in got[0][0]))
+    forms = {(c, s, pool) for c, s, pool, _ in joined.WALKED_FRONTS}
+    bad += [("no workgroup with several tiles", *f, b) for f in forms for b in (False, True) if (*f, b) not in several]
+    for n, bands, flags, often, first in joined.PASSES:
+        names = [name for name, _ in launches(joined.passes(n, bands), flags)]
+        if len(names) != often * first + (6 - first) or sum("conv_igemm_kernel" in k for k in names) != often:   # (the first layer's)
+            bad.append((n, bands, flags, names))
+    return bad
+
+
+bad = {"joined_launches": joined_launches, "matrix_rows": matrix_rows, "copy_streams": copy_streams, "timed_layer": timed_layer, "grids": grids, "poison": poison, "order_of_streams": order_of_streams, "workspace": workspace, "wide_tiles": wide_tiles, "static_scratch": static_scratch}[check]()
 for b in bad:
     print("FAILED", b, flush=True)
 print("CHECK %s" % ("FAILED" if bad else "OK"), flush=True)

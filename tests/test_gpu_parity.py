@@ -7,6 +7,7 @@ import torch
 
 import workloads
 from oracle import planner
+import joined_chains as joined
 from gpu_util import TOL, check_margins, elementwise_err, empty_out, rel_err, run_gpu, to_device_nhwc, to_nchw
 from random_chains import random_conv_chain as _random_conv_chain
 from paper_2507_05829_amd import lop
@@ -2216,27 +2217,13 @@ def test_depthwise_layers_of_more_workgroups_than_a_launch_takes(n, h, bands):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("shape,bands,flags,acts", [
-    ((1, 16, 1, 1), 1, 0, ("relu", "relu")),                                     # one pixel: padding alone around it
-    ((1, 16, 8, 8), 2, 0, ("relu", "relu")), ((1, 16, 9, 17), 3, 0, ("none", "relu6")),   # a tile, and one pixel more
-    ((3, 16, 33, 31), 5, 0, ("relu6", "none")), ((1, 16, 40, 50), 16, lop.LOP_FLAG_GRAPH, ("relu", "relu")),
-    ((2, 16, 37, 70), 4, lop.LOP_FLAG_REUSE, ("relu", "relu")), ((1, 16, 61, 45), 4, lop.LOP_FLAG_BATCH_BANDS, ("relu", "relu")),
-    ((1, 16, 190, 204), 3, 0, ("relu", "relu")),                                 # more tiles than compute units
-])
+@pytest.mark.parametrize("shape,bands,flags,acts", joined.PAIRS)
 def test_two_convolutions_as_one_launch(oracle, shape, bands, flags, acts, dtype):
-    """Pairs of 16-channel 3 x 3 convolutions, alone and between other layers (where the bands have slabs of their own), with
-    small integers (exact in any order) and with random values; a pair whose first result is read twice runs as two."""
-    for around in ("alone", "between", "read twice"):
-        chain = workloads.Chain("pair", shape, dtype, bands)
-        if around == "between":
-            chain.add(workloads.CONV, 16, 16, 1, 1, 0, act="relu")
-        chain.add(workloads.CONV, 16, 16, 3, 1, 1, act=acts[0])
-        chain.add(workloads.CONV, 16, 16, 3, 1, 1, act=acts[1])
-        if around == "between":
-            chain.add(workloads.MAXPOOL, 16, 16, 3, 1, 1)
-        if around == "read twice":
-            chain.add(workloads.CONV, 16, 32, 1, 1, 0, act="none")
-            chain.add(workloads.CONV, 16, 32, 1, 1, 0, act="none", input_from=len(chain.layers) - 3, residual_from=len(chain.layers) - 1)
+    """Pairs of 16-channel 3 x 3 convolutions, alone, behind a layer and in front of one (where the bands have slabs of their own),
+    with small integers (exact in any order) and with random values; between two layers, and where the first result is read twice,
+    they run as two. (Which launches these chains make, the tests on the stand-in runtime assert.)"""
+    for around in joined.AROUND:
+        chain = joined.pair(shape, dtype, bands, acts, around)
         ints = workloads.small_int_tensors(chain)
         got, host = run_gpu(chain, ints, flags=flags | lop.LOP_FLAG_POISON_SCRATCH)
         want = oracle.run_chain(chain, ints)
@@ -2274,25 +2261,12 @@ def test_depthwise_columns_per_thread(oracle, shape, s, bands, name):
     np.testing.assert_array_equal(parts, whole)
 
 
-@pytest.mark.parametrize("c,s,pool,shape,bands,flags", [
-    (32, 2, False, (1, 3, 37, 41), 1, 0),                                    # fewer tiles than XCDs
-    (32, 2, False, (2, 3, 180, 333), 5, 0),                                  # an odd width: rows of the image start between two words
-    (32, 1, False, (1, 3, 65, 63), 4, lop.LOP_FLAG_REUSE | lop.LOP_FLAG_GRAPH),
-    (32, 1, False, (1, 3, 3, 150), 3, 0),                                    # bands of one row
-    (64, 1, True, (1, 3, 96, 98), 3, 0), (64, 1, True, (3, 3, 70, 75), 4, lop.LOP_FLAG_REUSE),
-    (64, 1, False, (1, 3, 90, 97), 2, lop.LOP_FLAG_BATCH_BANDS), (64, 2, True, (1, 3, 200, 231), 6, 0), (64, 2, False, (2, 3, 161, 190), 3, 0),
-])
+@pytest.mark.parametrize("c,s,pool,shape,bands,flags", joined.FRONTS)
 def test_first_layer_and_the_convolution_behind_it(oracle, c, s, pool, shape, bands, flags):
     """The launch that computes both (and the pooling), alone (its rows also leave for the host from there) and with a layer
     behind it (bands with slabs of their own), against the oracle and against a launch per layer."""
     for behind in (False, True):
-        chain = workloads.Chain("front", shape, "bf16", bands)
-        chain.add(workloads.CONV, 3, c, 3, s, 1, act="relu")
-        chain.add(workloads.CONV, c, c, 3, 1, 1, act="relu6" if pool else "none")
-        if pool:
-            chain.add(workloads.MAXPOOL, c, c, 2, 2, 0)
-        if behind:
-            chain.add(workloads.CONV, c, 32, 3, 1, 1, act="relu")
+        chain = joined.front(c, s, pool, shape, bands, behind, ("relu", "relu6" if pool else "none"))
         t = workloads.make_tensors(chain, zero_bias=False)
         got, host = run_gpu(chain, t, flags=flags | lop.LOP_FLAG_POISON_SCRATCH)
         assert rel_err(got, oracle.run_chain(chain, t)) <= TOL["bf16"], behind
@@ -2308,20 +2282,12 @@ def test_first_layer_and_the_convolution_behind_it(oracle, c, s, pool, shape, ba
         np.testing.assert_array_equal(np.isfinite(got), np.isfinite(apart))
 
 
-@pytest.mark.parametrize("c,s,pool,shape", [
-    (32, 2, False, (1, 3, 451, 433)), (32, 1, False, (1, 3, 221, 226)), (64, 1, True, (1, 3, 225, 223)), (64, 1, False, (2, 3, 150, 161)),
-    (64, 2, True, (1, 3, 430, 447)), (64, 2, False, (1, 3, 433, 440)),
-])
+@pytest.mark.parametrize("c,s,pool,shape", joined.WALKED_FRONTS)
 def test_first_layer_in_the_launch_behind_it_has_the_bits_of_its_own(c, s, pool, shape):
     """A chain's launch of both layers against the first-layer and the walking kernel, which run where a band is run by itself:
-    the same products, added and rounded in the same order, so the same bits, for any number of bands."""
-    def make(bands):
-        chain = workloads.Chain("front", shape, "bf16", bands)
-        chain.add(workloads.CONV, 3, c, 3, s, 1, act="relu")
-        chain.add(workloads.CONV, c, c, 3, 1, 1, act="relu")
-        if pool:
-            chain.add(workloads.MAXPOOL, c, c, 2, 2, 0)
-        return chain
+    the same products, added and rounded in the same order, so the same bits, for any number of bands; also where a workgroup does
+    several tiles, whose image rows and pixels of the first layer take turns in LDS."""
+    make = lambda bands: joined.front(c, s, pool, shape, bands)
     t = workloads.make_tensors(make(1), zero_bias=False)
     plan = lop.Plan(make(1), t)
     try:
@@ -2335,24 +2301,18 @@ def test_first_layer_in_the_launch_behind_it_has_the_bits_of_its_own(c, s, pool,
     finally:
         plan.destroy()
     assert np.isfinite(want).all()
-    for bands, flags in ((1, 0), (3, 0), (4, lop.LOP_FLAG_REUSE)):
+    for bands, flags in joined.WALKED_AS:
         got, host = run_gpu(make(bands), t, flags=flags)
         np.testing.assert_array_equal(got, want)
         np.testing.assert_array_equal(host, want)
 
 
-@pytest.mark.parametrize("n,bands,flags", [(5, 1, 0), (5, 4, lop.LOP_FLAG_REUSE | lop.LOP_FLAG_GRAPH), (5, 3, 0), (3, 6, lop.LOP_FLAG_GRAPH), (1, 7, 0)])
+@pytest.mark.parametrize("n,bands,flags", [p[:3] for p in joined.PASSES])
 def test_passes_over_the_first_layers_only(oracle, n, bands, flags):
     """Chains whose first layers are too large for one pass and whose others are not, the last pass over fewer images or bands:
     what a pass leaves behind stays where it is while the next one runs (scratch poisoned for each), and a residual of a
     later layer reads it there."""
-    chain = workloads.Chain("passes", (n, 16, 1500 if n == 1 else 400, 640 if n == 1 else 420), "bf16", bands)
-    chain.add(workloads.CONV, 16, 32, 3, 1, 1, act="relu")
-    chain.add(workloads.CONV, 32, 32, 3, 1, 1, act="relu")
-    cut = chain.add(workloads.CONV, 32, 32, 3, 2, 1, act="relu")
-    chain.add(workloads.CONV, 32, 32, 3, 1, 1, act="relu")
-    chain.add(workloads.CONV, 32, 32, 3, 1, 1, act="none", residual_from=cut)
-    chain.add(workloads.CONV, 32, 64, 3, 2, 1, act="relu")
+    chain = joined.passes(n, bands)
     t = workloads.make_tensors(chain, zero_bias=False)
     got, host = run_gpu(chain, t, flags=flags | lop.LOP_FLAG_POISON_SCRATCH)
     assert rel_err(got, oracle.run_chain(chain, t)) <= TOL["bf16"]
