@@ -23,10 +23,12 @@ from paper_2507_05829_amd import lop  # noqa: E402
 assert lop.LIB_PATH.startswith(stub_dir), lop.LIB_PATH
 stub = ctypes.CDLL(os.path.join(stub_dir, "paper_2507_05829_amd", "libhipstub.so"))
 stub.hipstub_unordered.restype = ctypes.c_long
+stub.hipstub_created.restype = ctypes.c_long
 stub.hipstub_launched.restype = ctypes.c_char_p
 stub.hipstub_launched.argtypes = [ctypes.c_long]
 stub.hipstub_launched_workgroups.restype = ctypes.c_long
 stub.hipstub_launched_workgroups.argtypes = [ctypes.c_long]
+GRAPH_EXEC = 3
 stub.hipstub_mark.argtypes = [ctypes.c_void_p]
 stub.hipStreamCreateWithFlags.argtypes = [ctypes.c_void_p, ctypes.c_uint]
 stub.hipStreamDestroy.argtypes = [ctypes.c_void_p]
@@ -335,6 +337,13 @@ def kernels(plan, out=None, stream=None):
     return got
 
 
+def plan_of(chain, flags):
+    if not isinstance(chain, workloads.RowChain):
+        return make(chain, flags)
+    weights = types.SimpleNamespace(weights=[np.zeros((L.n, L.k), np.float32) for L in chain.layers], biases=[None] * len(chain.layers))
+    return lop.Plan.rowwise(chain, weights, flags=flags | lop.LOP_FLAG_LANES(1))
+
+
 def joined_launches():
     """The chains of joined_chains.py make the launches that their tests on the GPU are about: a pair or a first layer and the
     convolution behind it in one launch, over bands with slabs of their own where there are such, and with more tiles than workgroups
@@ -375,7 +384,22 @@ def joined_launches():
     return bad
 
 
-bad = {"joined_launches": joined_launches, "matrix_rows": matrix_rows, "copy_streams": copy_streams, "timed_layer": timed_layer, "grids": grids, "poison": poison, "order_of_streams": order_of_streams, "workspace": workspace, "wide_tiles": wide_tiles, "static_scratch": static_scratch}[check]()
+def graphs():
+    """LOP_FLAG_GRAPH captures merged chains of more than four launches, and enqueues the others by every call."""
+    bad = []
+    for chains, captured in ((joined.REPLAYED, 1), (joined.ENQUEUED, 0)):
+        for name, build in chains.items():
+            chain, flags = build()
+            plan, before, counts = plan_of(chain, flags | lop.LOP_FLAG_GRAPH), stub.hipstub_created(GRAPH_EXEC), []
+            for _ in range(3):
+                counts.append(len(kernels(plan, TENSOR)))
+            if stub.hipstub_created(GRAPH_EXEC) - before != captured or counts[0] == 0 or any((c == 0) != bool(captured) for c in counts[1:]):
+                bad.append((name, captured, stub.hipstub_created(GRAPH_EXEC) - before, counts))
+            plan.destroy()
+    return bad
+
+
+bad = {"joined_launches": joined_launches, "graphs": graphs, "matrix_rows": matrix_rows, "copy_streams": copy_streams, "timed_layer": timed_layer, "grids": grids, "poison": poison, "order_of_streams": order_of_streams, "workspace": workspace, "wide_tiles": wide_tiles, "static_scratch": static_scratch}[check]()
 for b in bad:
     print("FAILED", b, flush=True)
 print("CHECK %s" % ("FAILED" if bad else "OK"), flush=True)

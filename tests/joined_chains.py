@@ -77,3 +77,35 @@ def passes(n, bands):
     chain.add(workloads.CONV, 32, 32, 3, 1, 1, act="none", residual_from=cut)
     chain.add(workloads.CONV, 32, 64, 3, 2, 1, act="relu")
     return chain
+
+
+# Chains of more merged launches than are enqueued without a graph, in every way that a captured chain can run: name -> chain, flags.
+def _products(name, m, k, hidden, dtype, bands, layers):
+    chain = workloads.RowChain(name, m, k, dtype, bands)
+    for l in range(layers):
+        chain.add(k if l % 2 else hidden, "relu")
+    return chain
+
+
+def _behind(chain, c, layers):
+    for _ in range(layers):
+        chain.add(workloads.CONV, c, c, 1, 1, 0, act="relu")
+    return chain
+
+
+REPLAYED = {
+    "few rows": lambda: (_products("rows", 1031, 1000, 136, "bf16", 8, 5), 0),
+    "passes over rows": lambda: (_products("rows", 20011, 64, 1704, "bf16", 7, 4), lop.LOP_FLAG_REUSE),
+    "passes over rows, fp32": lambda: (_products("rows", 12011, 64, 1704, "f32", 8, 4), 0),
+    "pair": lambda: (_behind(pair((1, 16, 40, 50), "f32", 5, ("relu", "relu"), "alone"), 16, 4), 0),
+    "front": lambda: (_behind(front(32, 1, False, (1, 3, 65, 63), 4), 32, 4), lop.LOP_FLAG_REUSE),
+    "passes up to a layer": lambda: (passes(7, 4), lop.LOP_FLAG_REUSE),
+    "passes of bands up to a layer": lambda: (passes(3, 6), 0),
+}
+# ... and of no more than that: enqueued by every call.
+ENQUEUED = {
+    "few rows": lambda: (_products("rows", 1031, 1000, 136, "bf16", 8, 4), 0),
+    "passes over rows": lambda: (_products("rows", 20011, 64, 1704, "bf16", 7, 2), lop.LOP_FLAG_REUSE),
+    "pair": lambda: (_behind(pair((1, 16, 40, 50), "f32", 5, ("relu", "relu"), "alone"), 16, 2), 0),
+    "front": lambda: (_behind(front(32, 1, False, (1, 3, 65, 63), 4), 32, 2), lop.LOP_FLAG_REUSE),
+}

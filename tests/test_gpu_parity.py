@@ -2331,3 +2331,31 @@ def test_tiles_of_a_last_group(oracle, dtype, h):
     want = oracle.run_chain(chain, t)
     assert np.abs(want).max() <= (256 if dtype == "bf16" else 2 ** 24)
     np.testing.assert_array_equal(run_gpu(chain, t)[0], want)
+
+
+@pytest.mark.parametrize("name", list(joined.REPLAYED))
+def test_merged_chains_replayed_from_a_graph(name):
+    """Chains long enough to be captured: every replay, with eager work on the same buffers and waits between them, gives the bits
+    of the same call without a graph on the input that is there then."""
+    chain, flags = joined.REPLAYED[name]()
+    rows = isinstance(chain, workloads.RowChain)
+    t = (workloads.make_row_tensors if rows else workloads.make_tensors)(chain, zero_bias=False)
+    make = lop.Plan.rowwise if rows else lop.Plan
+    eager, graph = make(chain, t, flags=flags), make(chain, t, flags=flags | lop.LOP_FLAG_GRAPH | lop.LOP_FLAG_LANES(1))
+    try:
+        first = torch.from_numpy(t.x).cuda().to(torch.bfloat16 if chain.dtype == "bf16" else torch.float32) if rows else to_device_nhwc(t.x, chain.dtype)
+        d_in, want, got = first.clone(), empty_out(eager.out_shape(), chain.dtype), empty_out(eager.out_shape(), chain.dtype)
+        for rep in range(4):
+            d_in.copy_(first * (1 + rep))
+            got.fill_(float("nan"))
+            torch.cuda.synchronize()
+            graph.run_chain(d_in, got)
+            eager.run_chain(d_in, want)
+            graph.synchronize()
+            eager.synchronize()
+            assert bool(torch.isfinite(want).all())
+            assert torch.equal(got, want), rep
+        check_margins(want, got)
+    finally:
+        eager.destroy()
+        graph.destroy()
