@@ -35,6 +35,7 @@ struct OpLaunch {
   void* ws = nullptr;  // dense conv: device scratch for split-K partial sums (may be null
                        // only if conv_workspace_bytes() is 0 for this launch)
   size_t ws_bytes = 0;  // ... and its size: a launch that needs more is refused, not enqueued
+  bool alone = false;   // its chain runs on a caller's stream, where no other chain's launches run beside it
 };
 
 // Dense conv weights are packed as [c_out_pad][k_pad], k = (a*kw + b)*c_in + ci, zero

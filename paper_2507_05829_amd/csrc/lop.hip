@@ -716,6 +716,7 @@ lop::OpLaunch make_launch(const lop_plan_t* P, int band, int l, const void* d_in
   o.kh = L.d.kh; o.kw = L.d.kw; o.sh = L.d.sh; o.sw = L.d.sw;
   o.ph = L.d.ph; o.pw = L.d.pw; o.dh = L.d.dh; o.dw = L.d.dw;
   o.act = L.d.act;
+  o.alone = P->alone;
   const lop_rows_t rows = P->pass_rows.hi > P->pass_rows.lo ? P->pass_rows : t.bands[band].compute[l];
   o.out_lo = rows.lo;
   o.out_hi = rows.hi;
@@ -1281,8 +1282,10 @@ int batched_owner(const lop_plan_t* P, int l) {
 // Scratch of a chain while it is enqueued: a lane's, or the static array's.
 struct ChainScratch {
   lop_plan_t* P;
-  ChainScratch(lop_plan_t* plan, void* arena, void* ws) : P(plan) { P->arena_override = arena; P->ws_override = ws; }
-  ~ChainScratch() { P->arena_override = nullptr; P->ws_override = nullptr; }
+  ChainScratch(lop_plan_t* plan, void* arena, void* ws, bool alone) : P(plan) {
+    P->arena_override = arena; P->ws_override = ws; P->alone = alone;
+  }
+  ~ChainScratch() { P->arena_override = nullptr; P->ws_override = nullptr; P->alone = false; }
 };
 
 // Whether layers l and l + 1 are a convolution and the 1 x 1 shortcut beside it, which a merged chain computes
@@ -1436,9 +1439,10 @@ int enqueue_merged_kernels(lop_plan_t* P, const void* d_in, void* d_out, hipStre
 
 // The kernels of a chain whose launches are merged over the bands (Sec. IV-D operation batching), on
 // one lane's scratch and on stream `cs`: per layer one launch for the rows of all bands. direct:
-// where the last one also stores its rows (device view of the host buffer), or nullptr.
-int enqueue_chain_merged(lop_plan_t* P, Lane& L, const void* d_in, void* d_out, void* direct, hipStream_t cs) {
-  ChainScratch scratch(P, L.arena, L.conv_ws);
+// where the last one also stores its rows (device view of the host buffer), or nullptr. alone: the chain is for a caller's
+// stream (a graph is captured as its first caller wants it; what that changes is no bit of the result).
+int enqueue_chain_merged(lop_plan_t* P, Lane& L, const void* d_in, void* d_out, void* direct, hipStream_t cs, bool alone) {
+  ChainScratch scratch(P, L.arena, L.conv_ws, alone);
   return enqueue_merged_kernels(P, d_in, d_out, cs, direct);
 }
 
@@ -1569,7 +1573,7 @@ int launch_graph_merged(lop_plan_t* P, int lane, const void* d_in, void* d_out, 
   if (!exec) {
     hipGraph_t graph = nullptr;
     LOP_HIP(hipStreamBeginCapture(L.stream, hipStreamCaptureModeThreadLocal));
-    int rc = enqueue_chain_merged(P, L, d_in, d_out, direct, L.stream);
+    int rc = enqueue_chain_merged(P, L, d_in, d_out, direct, L.stream, s != L.stream);
     const hipError_t e = hipStreamEndCapture(L.stream, &graph);
     rc = keep_graph(P, rc, e, graph, d_in, d_out, direct, lane, -1, &exec);
     if (rc != LOP_OK) return rc;
@@ -1609,7 +1613,7 @@ int run_merged(lop_plan_t* P, const void* d_in, void* d_out, void* h_out, hipStr
   const bool copy = h_out && !(P->flags & LOP_FLAG_NO_D2H);
   void* const direct = copy ? direct_host_target(P, P->sched == ChainSched::kWhole ? P->t.whole() : 0, h_out, true) : nullptr;
   rc = (P->flags & LOP_FLAG_GRAPH) && !timing && merged_launches(P) > kEagerLaunches ? launch_graph_merged(P, lane, d_in, d_out, direct, s)
-                                              : enqueue_chain_merged(P, L, d_in, d_out, direct, s);
+                                              : enqueue_chain_merged(P, L, d_in, d_out, direct, s, user != nullptr);
   if (rc != LOP_OK) return rc;
   if ((rc = stamp(P->ev_c1)) != LOP_OK || (rc = stamp(P->ev_d0)) != LOP_OK) return rc;
   if (copy && !direct) {
@@ -1971,7 +1975,7 @@ int lop_run_chain_static(lop_plan_t* P, const void* d_in, void* d_out, void* str
   // Nothing in the array has to start at zero: a band's slabs are written by the layer that
   // produces them before any layer reads them, and a launch's partial sums by its slices
   // before its finish kernel adds them, so the contents left by the last call do not matter.
-  ChainScratch scratch(P, base, P->conv_ws_bytes ? base + arena : nullptr);
+  ChainScratch scratch(P, base, P->conv_ws_bytes ? base + arena : nullptr, true);
   if (P->sched != ChainSched::kPerBand) return enqueue_merged_kernels(P, d_in, d_out, (hipStream_t)stream, nullptr);
   int rc = LOP_OK;
   for (int b = 0; b < P->t.n_bands && rc == LOP_OK; ++b)

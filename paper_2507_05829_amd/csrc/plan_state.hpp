@@ -116,6 +116,7 @@ struct lop_plan_s {
   // library's static device array (lop_run_chain_static).
   void* arena_override = nullptr;
   void* ws_override = nullptr;
+  bool alone = false;   // ... and it runs on one stream of the caller's (see OpLaunch)
   void* arena_of(int band) const {
     if (arena_override) return arena_override;
     return lanes.empty() ? nullptr : lane_of(band).arena;

@@ -333,11 +333,13 @@ inline int dw_block_cols(int c, int cols) { return std::max(1, 256 / (c / kDwVec
 // compute unit. Two take 2.5 vector loads an output where one takes 3.75 (stride 2: 5.6 and 6.75) and half the vector
 // instructions, which were busy for three quarters of the time: 192 channels on 8 x 42 x 320 pixels 26.9 -> 22.2 us, stride 2 on
 // 8 x 82 x 640 42.5 -> 39.8. With few workgroups a thread's chain of loads is what counts: 2 x 20 x 84 pixels 4.5 us with
-// one column, 5.8 with two; 42 x 160 (96 workgroups of two) 4.7 and 5.9. Between them one is ahead alone (82 x 320, 352
-// workgroups: 8.6 and 8.9; 8 x 21 x 160, 384: 8.4 and 8.7), two with launches beside it (chains of one 640 x 640 image in four bands 262.9 and 258.2 us,
-// of eight in eight bands 1 959 and 1 942).
-constexpr long kDwTwoColumns = 256;
-int dw_cols(const RowParams* ps, int n, int dtype) {
+// one column, 5.8 with two; 42 x 160 (96 workgroups of two) 4.7 and 5.9. Between them one is ahead alone up to one and a half
+// to a compute unit (us a launch, one and two columns: 144 x 144 pixels, 270 workgroups, 7.7 and 8.3; 160 x 160, 320, 8.2 and 8.7; stride 2 on 224 x
+// 224, 336, 6.8 and 7.3; 8 x 21 x 160, 384, 8.4 and 8.7; but 176 x 176, 396, 9.5 and 9.0; stride 2 on 256 x 256, 416, 7.9 and 7.5), two
+// with launches beside it (chains of one 640 x 640 image in four bands 262.9 and 258.2 us, of eight in eight bands 1 959 and 1 942).
+// So where the line lies depends on whose stream the chain runs on.
+constexpr long kDwTwoColumns = 256, kDwTwoColumnsAlone = 384;
+int dw_cols(const RowParams* ps, int n, int dtype, bool alone) {
   long blocks = 0;
   for (int b = 0; b < n; ++b) {
     const RowParams& p = ps[b];
@@ -345,7 +347,7 @@ int dw_cols(const RowParams* ps, int n, int dtype) {
     const int rpt = dw_rows_per_thread(p.sh), cols = dw_block_cols(p.C, 2);
     blocks += (long)((p.W_out + cols - 1) / cols) * ((p.R + rpt - 1) / rpt) * p.N;
   }
-  return dtype == LOP_BF16 && blocks > kDwTwoColumns ? 2 : 1;
+  return dtype == LOP_BF16 && blocks > (alone ? kDwTwoColumnsAlone : kDwTwoColumns) ? 2 : 1;
 }
 
 // The bands in one launch, unless they have more workgroups than a launch takes (2^32 threads, exclusive): then in as few as
@@ -455,7 +457,7 @@ hipError_t launch_rowwise_bands(const OpLaunch* Ls, int n, hipStream_t stream, K
   RowParams& p = ps[0];
   if (dw3_vec(p, L.op))
     return L.dtype != LOP_BF16 ? launch_dw3<float, kDwVec, 1>(ps, n, stream, ev)
-           : dw_cols(ps, n, L.dtype) == 2 ? launch_dw3<__bf16, kDwVec, 2>(ps, n, stream, ev)
+           : dw_cols(ps, n, L.dtype, L.alone) == 2 ? launch_dw3<__bf16, kDwVec, 2>(ps, n, stream, ev)
                                           : launch_dw3<__bf16, kDwVec, 1>(ps, n, stream, ev);
   if (L.dtype == LOP_BF16)
     return p.C % 8 == 0 ? launch_rowwise<__bf16, 8>(ps, n, L.op, stream, ev)
@@ -529,7 +531,7 @@ int rowwise_describe(const OpLaunch& L, char* name, size_t size) {
   p.W = L.x.w; p.W_out = L.y.w; p.R = L.out_hi - L.out_lo; p.N = L.x.n;
   if (name && size) {
     if (const int v = dw3_vec(p, L.op))
-      snprintf(name, size, "dwconv3x3_%skernel<%s, %d, %d>", bf && dw_cols(&p, 1, L.dtype) == 1 ? "column_" : "", bf ? "__bf16" : "float", v, L.sh);
+      snprintf(name, size, "dwconv3x3_%skernel<%s, %d, %d>", bf && dw_cols(&p, 1, L.dtype, L.alone) == 1 ? "column_" : "", bf ? "__bf16" : "float", v, L.sh);
     else
       snprintf(name, size, "rowwise_kernel<%s, %d, %d>", bf ? "__bf16" : "float", vec, o);
   }

@@ -399,7 +399,24 @@ def graphs():
     return bad
 
 
-bad = {"joined_launches": joined_launches, "graphs": graphs, "matrix_rows": matrix_rows, "copy_streams": copy_streams, "timed_layer": timed_layer, "grids": grids, "poison": poison, "order_of_streams": order_of_streams, "workspace": workspace, "wide_tiles": wide_tiles, "static_scratch": static_scratch}[check]()
+def alone():
+    """Depthwise launches between a workgroup and one and a half to a compute unit: two columns a thread where chains of
+    consecutive calls run beside each other, one where the chain is on a caller's stream or may not allocate."""
+    bad, user = [], new_stream()
+    for shape, s, free, own in (((1, 192, 160, 160), 1, 2, 1), ((1, 192, 224, 224), 2, 2, 1), ((1, 192, 128, 128), 1, 1, 1), ((1, 192, 192, 192), 1, 2, 2)):
+        chain = workloads.Chain("depthwise", shape, "bf16", 1)
+        chain.add(workloads.DWCONV, 192, 192, 3, s, 1, 1, "relu6")
+        plan = make(chain, 0)
+        static = lambda: (stub.hipstub_forget(), plan.run_chain_static(TENSOR, TENSOR), [(stub.hipstub_launched(0).decode(), 0)])[2]
+        for got, want in ((kernels(plan), free), (kernels(plan, None, user), own), (static(), own), (kernels(plan), free)):
+            if len(got) != 1 or ("column" in got[0][0]) != (want == 1):
+                bad.append((shape, s, want, got))
+        plan.destroy()
+    stub.hipStreamDestroy(user)
+    return bad
+
+
+bad = {"joined_launches": joined_launches, "graphs": graphs, "alone": alone, "matrix_rows": matrix_rows, "copy_streams": copy_streams, "timed_layer": timed_layer, "grids": grids, "poison": poison, "order_of_streams": order_of_streams, "workspace": workspace, "wide_tiles": wide_tiles, "static_scratch": static_scratch}[check]()
 for b in bad:
     print("FAILED", b, flush=True)
 print("CHECK %s" % ("FAILED" if bad else "OK"), flush=True)

@@ -2359,3 +2359,26 @@ def test_merged_chains_replayed_from_a_graph(name):
     finally:
         eager.destroy()
         graph.destroy()
+
+
+@pytest.mark.parametrize("h,w,s", [(160, 161, 1), (223, 224, 2)])
+def test_depthwise_columns_by_whose_stream(oracle, h, w, s):
+    """Sizes at which a chain on a caller's stream, and one that may not allocate, take the other form of the depthwise
+    kernel: the same bits."""
+    chain = workloads.Chain("depthwise", (1, 192, h, w), "bf16", 1)
+    chain.add(workloads.DWCONV, 192, 192, 3, s, 1, 1, "relu6")
+    t = workloads.make_tensors(chain, zero_bias=False)
+    want, _ = run_gpu(chain, t, use_host=False)
+    assert rel_err(want, oracle.run_chain(chain, t)) <= TOL["bf16"]
+    plan, stream = lop.Plan(chain, t), torch.cuda.Stream()
+    try:
+        d_in = to_device_nhwc(t.x, "bf16")
+        for run in (lambda out: plan.run_chain(d_in, out, None, stream), lambda out: plan.run_chain_static(d_in, out, stream)):
+            out = empty_out(plan.out_shape(), "bf16")
+            run(out)
+            plan.synchronize()
+            torch.cuda.synchronize()
+            check_margins(out)
+            np.testing.assert_array_equal(to_nchw(out), want)
+    finally:
+        plan.destroy()

@@ -39,7 +39,7 @@ def test_host_code_is_clean_under_sanitizers(stub_dir):
 
 
 @pytest.mark.parametrize("check", ["workspace", "wide_tiles", "static_scratch", "order_of_streams", "poison", "grids", "copy_streams", "timed_layer", "matrix_rows",
-                                   "joined_launches", "graphs"])
+                                   "joined_launches", "graphs", "alone"])
 def test_merged_chains_do_what_their_bands_do(stub_dir, check):
     """What merged launches ask of their scratch and launchers (see hipstub/merged.py)."""
     out = run_under_sanitizers(stub_dir, "merged.py", check)
