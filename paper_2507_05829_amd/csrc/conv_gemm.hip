@@ -657,17 +657,18 @@ constexpr long kWalkers = 256;
 // 48.9 / 47.8 and 104 / 87.7 / 92.1, 16000 -> 2048 (2 000) 66.1 / 63.1 / 62.4 and 137 / 119 / 121.
 struct GemmChoice { int bm = 0, bn = 0; bool split = false; };
 constexpr long kBigTiles = 128;        // 256 x 256, bf16
-// 192 x 256, bf16, in place of 256 x 256 where the last of several rounds of those would be at most a third full and whole
-// rounds of the smaller, which take 0.8 of the time each, cost less. us a call of two layers on one stream and (in flight),
-// 256 -> 192 in the layer whose tiles are given: 9000 x 1024 -> 4096 (576 -> 752) -> 1024 235 -> 219 (210 -> 205), 9000 x 512 ->
-// 2048 (288 -> 376) -> 512 74.7 -> 68.7 (62.7 -> 61.0), 18 000 x 256 -> 1024 (284 -> 376) -> 256 51.5 -> 47.2 (37.1 -> 35.8),
-// 45 000 x 600 -> 1000 -> 600 (528 -> 705) 222 -> 194 (177 -> 176), 25 000 x 768 -> 3072 -> 768 (294 -> 393) 292 -> 284 (277 ->
-// 274). With longer reductions the chip, which these products keep at the power it may draw, loses in flight what one stream
-// gains: 20 000 x 1024 -> 4096 -> 1024 (316 -> 420) 383 -> 375 (365 -> 369). With half a last round there is nothing to gain:
-// 24 000 x 1000 -> 2000 -> 1000 (376 -> 500) 230 -> 231 (216 -> 219). A single round is left to the larger tile, which other
-// launches run beside (65 536 x 1024 -> 4096 -> 1024 in eight bands on four streams 1 008 -> 1 068). Reductions of fewer
-// than 256 elements, three stages and less, keep the larger tile and its walk, though 33 000 x 128 -> 512 (258 -> 344) -> 128
-// would gain as well (40.5 -> 37.6).
+// 192 x 256, bf16, in place of 256 x 256 in a chain on a caller's stream where the last of several rounds of those would be at most
+// a third full and whole rounds of the smaller, which take 0.8 of the time each, cost less. us a call of one layer there, eight
+// buffers in turn (more than the caches hold), 256 -> 192: 9 116 x 1024 -> 2048 (288 -> 384 tiles) 58.1 -> 49.9, 22 940 x 512 -> 600 (270 ->
+// 360) 39.4 -> 32.9, 20 380 x 1024 -> 1024 (320 -> 428) 60.2 -> 59.6, 44 956 x 1000 -> 600 (528 -> 705) 98.0 -> 90.2, 67 484 x 512 -> 512 (528 -> 704)
+// 62.7 -> 61.6, 36 252 x 512 -> 512 (284 -> 378), bound by memory, 40.7 -> 40.8; with a residual 9 116 x 2048 -> 2048 112.1 -> 93.9, 36 252 x
+// 512 -> 512 50.3 -> 47.2; in four bands of 134 x 134 pixels 256 -> 1024 channels behind 64 -> 256 (3 x 3) 40.8 -> 35.8. With other chains beside it a
+// nearly empty round is no loss, they fill it, and the smaller tile reads more for a product: two layers in flight 65 792 x 512 -> 512 ->
+// 512 108.2 -> 114.9, 34 816 x 512 -> 1024 -> 512 96.4 -> 101.6, 25 000 x 768 -> 3072 -> 768 258 -> 266, 9 000 x 512 -> 2048 -> 512
+// 59.2 -> 58.2. With half a last round there is nothing to gain (24 000 x 1000 -> 2000 -> 1000, 376 -> 500, 230 -> 231). A single round is left to
+// the larger tile (65 536 x 1024 -> 4096 -> 1024 in eight bands on four streams 1 008 -> 1 068), and so are reductions of more than 3 072
+// (20 000 x 4096 -> 1024 gains 2 %). Nothing stops the rule at 256
+// elements but that it was found there: 9 000 x 128 -> 2048 -> 128 40.2 -> 37.1, 33 000 x 192 -> 512 -> 192 47.6 -> 44.2.
 constexpr double kLessTile = 0.8;
 constexpr int kLessMinK = 256, kLessMaxK = 3072;
 constexpr long kWideTiles = 192;       // 128 x 256, bf16
@@ -704,7 +705,7 @@ GemmChoice choose_gemm(const OpLaunch* Ls, int n) {
     if (const long t = tiles(256, 256); t >= kBigTiles) {
       auto rounds = [](long n) { return (double)((n + kWalkers - 1) / kWalkers); };
       const long last = t % kWalkers;
-      const bool thin = Ls[0].x.c >= kLessMinK && Ls[0].x.c <= kLessMaxK && t > kWalkers && last > 0 && 3 * last <= kWalkers;
+      const bool thin = Ls[0].alone && Ls[0].x.c >= kLessMinK && Ls[0].x.c <= kLessMaxK && t > kWalkers && last > 0 && 3 * last <= kWalkers;
       return thin && rounds(tiles(192, 256)) * kLessTile < rounds(t) ? GemmChoice{192, 256} : GemmChoice{256, 256};
     }
     if (tiles(128, 64) < kNarrowTiles) return {};

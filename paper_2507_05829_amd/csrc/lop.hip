@@ -1288,6 +1288,13 @@ struct ChainScratch {
   ~ChainScratch() { P->arena_override = nullptr; P->ws_override = nullptr; P->alone = false; }
 };
 
+// The same of a chain that runs on a lane's own scratch.
+struct ChainAlone {
+  lop_plan_t* P;
+  ChainAlone(lop_plan_t* plan, bool alone) : P(plan) { P->alone = alone; }
+  ~ChainAlone() { P->alone = false; }
+};
+
 // Whether layers l and l + 1 are a convolution and the 1 x 1 shortcut beside it, which a merged chain computes
 // in one launch where a kernel takes both (a launch more costs a chain 4 us, and the small
 // shortcut leaves most of the chip idle). The second one's output is then written while the first is computed, so
@@ -1897,6 +1904,8 @@ int lop_run_chain(lop_plan_t* P, const void* d_in, void* d_out, void* h_out, voi
     }
     return LOP_OK;
   }
+  // (on a caller's stream, bands in a row or one lane's)
+  const ChainAlone scope(P, compute_stream && !merged && (P->t.reuse || P->n_lanes() == 1));
   if (merged) {
     int rc = run_merged(P, d_in, d_out, h_out, compute_stream ? ms : nullptr, timing != nullptr);
     if (rc != LOP_OK) return rc;

@@ -401,8 +401,21 @@ def graphs():
 
 def alone():
     """Depthwise launches between a workgroup and one and a half to a compute unit: two columns a thread where chains of
-    consecutive calls run beside each other, one where the chain is on a caller's stream or may not allocate."""
+    consecutive calls run beside each other, one where the chain is on a caller's stream or may not allocate. Matrix products whose last
+    round of the largest tile is nearly empty: that tile beside other chains, the next smaller one on a caller's stream."""
     bad, user = [], new_stream()
+    thin = []
+    for m, k, n, residual in joined.THIN:
+        chain = workloads.RowChain("thin", m, k, "bf16", 1).add(n, "none")
+        thin.append(chain.add(n, "relu", residual_from=0, input_from=-1) if residual else chain)
+    thin.append(workloads.RowChain("thin", 34816, 512, "bf16", 1).add(1024, "none").add(512, "none"))   # (too large to merge: one band, on its lane)
+    for chain in thin:
+        plan = plan_of(chain, 0)
+        for stream, tile in ((None, "Li256ELi256E"), (user, "Li192ELi256E"), (None, "Li256ELi256E")):
+            got = kernels(plan, None, stream)
+            if len(got) != len(chain.layers) or any("conv_gemm_kernelIDF16b" + tile not in name for name, _ in got):
+                bad.append((chain.m, tile, got))
+        plan.destroy()
     for shape, s, free, own in (((1, 192, 160, 160), 1, 2, 1), ((1, 192, 224, 224), 2, 2, 1), ((1, 192, 128, 128), 1, 1, 1), ((1, 192, 192, 192), 1, 2, 2)):
         chain = workloads.Chain("depthwise", shape, "bf16", 1)
         chain.add(workloads.DWCONV, 192, 192, 3, s, 1, 1, "relu6")

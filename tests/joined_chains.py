@@ -109,3 +109,10 @@ ENQUEUED = {
     "pair": lambda: (_behind(pair((1, 16, 40, 50), "f32", 5, ("relu", "relu"), "alone"), 16, 2), 0),
     "front": lambda: (_behind(front(32, 1, False, (1, 3, 65, 63), 4), 32, 2), lop.LOP_FLAG_REUSE),
 }
+
+# Matrix products whose last round of 256 x 256 tiles is nearly empty: rows, elements, channels, residual
+THIN = [
+    (8400, 520, 2040, False),     # nine stages, the last of 8 elements; 44 x 8 tiles, those of the last row and column cut
+    (8400, 520, 2040, True),      # a workgroup per tile
+    (8448, 256, 2048, False),     # whole tiles, the shortest reduction
+]

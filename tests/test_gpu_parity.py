@@ -847,7 +847,7 @@ def test_reuse_mode_run_band_in_order(oracle):
 
 # ---- row-wise local operators (Eq. 1) through lop_plan_rowwise ----
 
-def _run_rows(chain, t, flags=0, order=None):
+def _run_rows(chain, t, flags=0, order=None, stream=None):
     plan = lop.Plan.rowwise(chain, t, flags=flags)
     td = torch.bfloat16 if chain.dtype == "bf16" else torch.float32
     d_in = torch.from_numpy(t.x).to(td).cuda()
@@ -856,7 +856,7 @@ def _run_rows(chain, t, flags=0, order=None):
     h_out = torch.full((chain.m, n_out), float("nan"), dtype=td).pin_memory()
     torch.cuda.synchronize()
     if order is None:
-        plan.run_chain(d_in, d_out, h_out)
+        plan.run_chain(d_in, d_out, h_out, stream)
     else:
         for b in order:
             plan.run_band(b, d_in, d_out, h_out)
@@ -1869,26 +1869,21 @@ def test_matrix_products_walking_over_tiles(oracle, cfg):
     np.testing.assert_array_equal(dev, apart)
 
 
-@pytest.mark.parametrize("cfg", [
-    # rows, elements, channels, residual
-    (8400, 520, 2040, False),     # nine stages, the last of 8 elements; 44 x 8 tiles, those of the last row and column cut
-    (8400, 520, 2040, True),      # a workgroup per tile
-    (8448, 256, 2048, False),     # whole tiles, the shortest reduction
-])
+@pytest.mark.parametrize("cfg", joined.THIN)
 def test_matrix_products_of_192_rows_a_tile(oracle, cfg):
-    """A last round of few 256 x 256 tiles: the smaller ones that take their place against the oracle, and bit for bit
-    against bands of one round each (the same products in the same order)."""
+    """A last round of few 256 x 256 tiles: the smaller ones that take their place on a caller's stream against the oracle, and bit for
+    bit against the larger ones of a call on the plan's own and of bands of one round each (the same products in the same order)."""
     m, k, n, residual = cfg
     def chain(bands):
         c = workloads.RowChain("thin", m, k, "bf16", bands)
         return c.add(n, "none").add(n, "relu", residual_from=0, input_from=-1) if residual else c.add(n, "relu")
     t = workloads.make_row_tensors(chain(1), zero_bias=False, seed=62)
-    dev, _, names = _run_rows(chain(1), t)
-    assert names == {"conv_gemm_kernel<__bf16, 192, 256, 2, 4, 2>"}, names
+    dev, host, _ = _run_rows(chain(1), t, stream=torch.cuda.Stream())
+    np.testing.assert_array_equal(dev, host)
     assert rel_err(dev, oracle.run_row_chain(chain(1), t)) <= TOL["bf16"]
-    apart, _, names = _run_rows(chain(2), t, order=[0, 1])
-    assert names == {"conv_gemm_kernel<__bf16, 256, 256, 2, 4, 2>"}, names
-    np.testing.assert_array_equal(dev, apart)
+    for apart, _, names in (_run_rows(chain(1), t), _run_rows(chain(2), t, order=[0, 1])):
+        assert names == {"conv_gemm_kernel<__bf16, 256, 256, 2, 4, 2>"}, names
+        np.testing.assert_array_equal(dev, apart)
 
 
 def _split_chain(m, k, n, residual, bands=1):
