@@ -354,43 +354,35 @@ size_t slab_bytes(const Slab& s) { return (size_t)s.n * s.rows * s.w * s.c * 2; 
 
 }  // namespace
 
-// pools: the 2 x 2 max pooling behind each band's second layer, or nullptr.
-bool front_applies(const OpLaunch* firsts, const OpLaunch* seconds, const OpLaunch* pools, int n) {
-  if (n < 1 || n > kMaxBatch) return false;
-  long all = 0;
-  for (int b = 0; b < n; ++b) {
-    const OpLaunch* const pool = pools ? &pools[b] : nullptr;
-    const FrontForm f = choose_front(firsts[b], seconds[b], pool);
-    if (!f.nt) return false;
-    if (slab_bytes(firsts[b].x) >= ((size_t)1 << 31)) return false;   // 32-bit offsets into the image
-    FrontParams p;
-    unsigned tiles = 0;
-    if (patch_work(seconds[b], pool).R > 0 && !make_front(firsts[b], seconds[b], pool, f, &p, &tiles)) return false;
-    all += f.nt == 2 ? tiles : kFrontTiles64;
-    // a workgroup stores its outputs while others still read the image
-    const char* const x = (const char*)firsts[b].x.ptr;
-    for (int j = 0; j < n; ++j) {
-      const Slab& ys = pools ? pools[j].y : seconds[j].y;
-      const char* const y = (const char*)ys.ptr;
-      if (x < y + slab_bytes(ys) && y < x + slab_bytes(firsts[b].x)) return false;
-    }
-  }
-  return all >= kFrontTiles64;
-}
-
-hipError_t launch_front(const OpLaunch* firsts, const OpLaunch* seconds, const OpLaunch* pools, int n, hipStream_t s, KernelEvents* ev) {
-  if (!front_applies(firsts, seconds, pools, n)) return hipErrorInvalidValue;
-  const FrontForm f = choose_front(firsts[0], seconds[0], pools);
+// pools: the 2 x 2 max pooling behind each band's second layer, or nullptr. (Whether the launch applies is found out while its parameters
+// are made: with many small bands those are what a call costs.)
+hipError_t launch_front(const OpLaunch* firsts, const OpLaunch* seconds, const OpLaunch* pools, int n, hipStream_t s, bool* taken,
+                        KernelEvents* ev) {
+  *taken = false;
+  if (n < 1 || n > kMaxBatch) return hipSuccess;
+  FrontForm f;
   FrontParams ps[kMaxBatch];
   unsigned gx[kMaxBatch];
   int m = 0;
   long all = 0;
   for (int b = 0; b < n; ++b) {
     const OpLaunch* const pool = pools ? &pools[b] : nullptr;
+    f = choose_front(firsts[b], seconds[b], pool);
+    const size_t x_bytes = slab_bytes(firsts[b].x);
+    if (!f.nt || x_bytes >= ((size_t)1 << 31)) return hipSuccess;   // 32-bit offsets into the image
+    // a workgroup stores its outputs while others still read the image
+    const char* const x = (const char*)firsts[b].x.ptr;
+    for (int j = 0; j < n; ++j) {
+      const Slab& ys = pools ? pools[j].y : seconds[j].y;
+      const char* const y = (const char*)ys.ptr;
+      if (x < y + slab_bytes(ys) && y < x + x_bytes) return hipSuccess;
+    }
     if (patch_work(seconds[b], pool).R <= 0) continue;
-    if (!make_front(firsts[b], seconds[b], pool, f, &ps[m], &gx[m])) return hipErrorInvalidValue;
+    if (!make_front(firsts[b], seconds[b], pool, f, &ps[m], &gx[m])) return hipSuccess;
     all += gx[m++];
   }
+  if (f.nt == 2 && all < kFrontTiles64) return hipSuccess;
+  *taken = true;
   if (m == 0) return hipSuccess;
   // every band gets its share of the resident workgroups (a multiple of the XCD count), or one per
   // tile where those are fewer

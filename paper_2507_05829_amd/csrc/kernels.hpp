@@ -141,9 +141,9 @@ hipError_t launch_narrow_siblings(const OpLaunch* convs, const OpLaunch* sibs, i
 bool siblings_apply(const OpLaunch* convs, const OpLaunch* sibs, int n);
 hipError_t launch_siblings(const OpLaunch* convs, const OpLaunch* sibs, int n, hipStream_t stream, KernelEvents* ev = nullptr);
 // A first layer and the 3 x 3 convolution that is its only reader (pools: the max pooling behind that, or nullptr) as one
-// launch: whether a group of bands takes it (descriptors with slabs and rows) and the launch (of the last one's rows, and its y2).
-bool front_applies(const OpLaunch* firsts, const OpLaunch* seconds, const OpLaunch* pools, int n);
-hipError_t launch_front(const OpLaunch* firsts, const OpLaunch* seconds, const OpLaunch* pools, int n, hipStream_t stream, KernelEvents* ev = nullptr);
+// launch (of the last one's rows, and its y2), where the group of bands takes it (descriptors with slabs and rows): taken.
+hipError_t launch_front(const OpLaunch* firsts, const OpLaunch* seconds, const OpLaunch* pools, int n, hipStream_t stream, bool* taken,
+                        KernelEvents* ev = nullptr);
 // Two 3 x 3 convolutions of kPairChannels channels, the second the only reader of the first, as one launch: whether a group of bands
 // takes it (descriptors with slabs and rows) and the launch (of the second one's rows, and its y2).
 constexpr int kPairChannels = 16;

@@ -1356,8 +1356,9 @@ int enqueue_merged_kernels(lop_plan_t* P, const void* d_in, void* d_out, hipStre
         const lop::OpLaunch a = make_launch(P, whole, l, d_in, d_out);
         lop::OpLaunch c = make_launch(P, whole, l + 1, d_in, d_out), q = make_launch(P, whole, e, d_in, d_out);
         c.y2 = q.y2 = e == nl - 1 ? second : nullptr;
-        if (lop::front_applies(&a, &c, e > l + 1 ? &q : nullptr, 1)) {
-          LOP_HIP(lop::launch_front(&a, &c, e > l + 1 ? &q : nullptr, 1, cs));
+        bool taken;
+        LOP_HIP(lop::launch_front(&a, &c, e > l + 1 ? &q : nullptr, 1, cs, &taken));
+        if (taken) {
           l = e;
           continue;
         }
@@ -1393,8 +1394,10 @@ int enqueue_merged_kernels(lop_plan_t* P, const void* d_in, void* d_out, hipStre
         batched_group(P, l, b, end, d_in, d_out, nullptr, &as, &none);
         batched_group(P, e, b, end, d_in, d_out, e == nl - 1 ? second : nullptr, &qs, &convs);
         const bool pooled = e > l + 1;
-        if (as.size() == qs.size() && lop::front_applies(as.data(), pooled ? convs.data() : qs.data(), pooled ? qs.data() : nullptr, (int)as.size())) {
-          LOP_HIP(lop::launch_front(as.data(), pooled ? convs.data() : qs.data(), pooled ? qs.data() : nullptr, (int)as.size(), cs));
+        bool taken = false;
+        if (as.size() == qs.size())
+          LOP_HIP(lop::launch_front(as.data(), pooled ? convs.data() : qs.data(), pooled ? qs.data() : nullptr, (int)as.size(), cs, &taken));
+        if (taken) {
           l = e;
           continue;
         }
