@@ -375,6 +375,10 @@ def joined_launches():
         tiles = n * -(-h // s) * -(-w // s) / (256 if c == 32 else 128)      # (at least)
         if tiles > got[0][1] > 0 and got[0][1] <= (768 if c == 32 else 512):
             several.add((c, s, pool, "_bands" in got[0][0]))
+    for c, s, pool, shape, bands, pads, bias in joined.FRONT_FORMS:
+        got = launches(joined.front(c, s, pool, shape, bands, pads=pads, bias=bias), 0)
+        if len(got) != 1 or "conv_front_kernel" not in got[0][0]:
+            bad.append((c, s, pool, shape, bands, pads, got))
     forms = {(c, s, pool) for c, s, pool, _ in joined.WALKED_FRONTS}
     bad += [("no workgroup with several tiles", *f, b) for f in forms for b in (False, True) if (*f, b) not in several]
     for n, bands, flags, often, first in joined.PASSES:

@@ -51,15 +51,24 @@ WALKED_FRONTS = [
 WALKED_AS = [(1, 0), (3, 0), (4, lop.LOP_FLAG_REUSE)]   # bands, flags of each
 
 
-def front(c, s, pool, shape, bands, behind=False, acts=("relu", "relu")):
+def front(c, s, pool, shape, bands, behind=False, acts=("relu", "relu"), pads=(1, 1), bias=True):
     chain = workloads.Chain("front", shape, "bf16", bands)
-    chain.add(workloads.CONV, 3, c, 3, s, 1, act=acts[0])
-    chain.add(workloads.CONV, c, c, 3, 1, 1, act=acts[1])
+    chain.add(workloads.CONV, 3, c, 3, s, pads[0], act=acts[0], has_bias=bias)
+    chain.add(workloads.CONV, c, c, 3, 1, pads[1], act=acts[1], has_bias=bias)
     if pool:
         chain.add(workloads.MAXPOOL, c, c, 2, 2, 0)
     if behind:
         chain.add(workloads.CONV, c, 32, 3, 1, 1, act="relu")
     return chain
+
+
+# What else such a launch takes: channels, stride, pooled, (N, C, H, W), bands, paddings of the two layers, biases
+FRONT_FORMS = [
+    (32, 1, False, (1, 3, 45, 39), 2, (0, 0), True), (32, 2, False, (2, 3, 50, 61), 3, (2, 2), False), (32, 1, False, (1, 3, 33, 30), 2, (3, 0), True),
+    (64, 1, True, (1, 3, 101, 99), 2, (0, 2), False), (64, 2, True, (1, 3, 190, 197), 3, (3, 0), True), (64, 1, False, (1, 3, 95, 90), 3, (2, 0), True),
+    (32, 1, False, (1, 3, 1, 1), 1, (1, 1), True), (32, 2, False, (1, 3, 2, 1), 1, (1, 1), True), (32, 1, False, (1, 3, 1, 300), 1, (1, 1), True),
+    (32, 2, False, (1, 3, 301, 2), 3, (1, 1), True), (32, 1, False, (300, 3, 4, 5), 2, (1, 1), True), (64, 1, True, (70, 3, 5, 3), 1, (1, 1), True),
+]
 
 
 # images, bands, flags; how often the chain below makes the launches of its first and of its last layers, and how many are

@@ -2277,6 +2277,19 @@ def test_first_layer_and_the_convolution_behind_it(oracle, c, s, pool, shape, ba
         np.testing.assert_array_equal(np.isfinite(got), np.isfinite(apart))
 
 
+@pytest.mark.parametrize("c,s,pool,shape,bands,pads,bias", joined.FRONT_FORMS)
+def test_first_layer_and_the_convolution_behind_it_other_forms(oracle, c, s, pool, shape, bands, pads, bias):
+    """Paddings other than one, no bias, images of one row or column, batches of images smaller than a tile."""
+    chain = joined.front(c, s, pool, shape, bands, False, ("relu6", "none"), pads, bias)
+    t = workloads.make_tensors(chain, zero_bias=False)
+    want = oracle.run_chain(chain, t)
+    got, host = run_gpu(chain, t)
+    assert rel_err(got, want) <= TOL["bf16"]
+    np.testing.assert_array_equal(got, host)
+    apart, _ = run_gpu(chain, t, use_host=False, flags=lop.LOP_FLAG_NO_FUSE)
+    assert rel_err(got, apart) <= 2 ** -7 and np.mean(got != apart) < 0.05   # (as in the test above)
+
+
 @pytest.mark.parametrize("c,s,pool,shape", joined.WALKED_FRONTS)
 def test_first_layer_in_the_launch_behind_it_has_the_bits_of_its_own(c, s, pool, shape):
     """A chain's launch of both layers against the first-layer and the walking kernel, which run where a band is run by itself:
