@@ -1556,24 +1556,39 @@ int launch_graph(lop_plan_t* P, const void* d_in, void* d_out, void* h_out, hipS
   return LOP_OK;
 }
 
-// The launches of a merged chain (finish kernels and layers that share a launch aside).
-long merged_launches(const lop_plan_t* P) {
+// What a merged chain's launches (by layers: a pair counts as two; finish kernels aside) cost the host, in sixteenths of a launch of
+// one band: each further band of a launch is one more, for the descriptor and the parameters it makes.
+struct MergedCost { long launches = 0, host = 0; };
+MergedCost merged_cost(const lop_plan_t* P) {
   const int nl = P->t.n_layers(), nb = P->t.n_bands, n = P->t.in.n, in_passes = P->cut < 0 ? nl : P->cut + 1;
-  auto of_bands = [&](int bands) { return P->sched == ChainSched::kGrouped ? (bands + lop::kMaxBandsPerLaunch - 1) / lop::kMaxBandsPerLaunch : 1; };
-  long launches = 0;
+  MergedCost c;
+  auto add = [&](int bands, long times) {
+    const bool grouped = P->sched == ChainSched::kGrouped;
+    const long launches = grouped ? (bands + lop::kMaxBandsPerLaunch - 1) / lop::kMaxBandsPerLaunch : 1;
+    c.launches += launches * times;
+    c.host += (launches * 16 + (grouped ? bands : 0)) * times;
+  };
   for (int l = 0; l < nl; ++l) {
     if (P->fuse_chain.away[l]) continue;
-    if (l >= in_passes) { launches += of_bands(nb); continue; }
-    for (int b = 0; b < nb; b += P->group) launches += of_bands(std::min(P->group, nb - b)) * ((n + P->images - 1) / P->images);
+    if (l >= in_passes) { add(nb, 1); continue; }
+    for (int b = 0; b < nb; b += P->group) add(std::min(P->group, nb - b), (n + P->images - 1) / P->images);
   }
-  return launches;
+  return c;
 }
-// Merged chains of at most this many launches are enqueued by every call, also where the plan asks for graphs: a graph's
-// launch costs 12 to 15 us of host time however few nodes it has, one of a kernel 2 to 3, and a stream gets through a graph's
-// kernels 6 us later. us a call, graph -> kernels, with calls in flight, on one caller's stream, and alone: one launch (two layers of 16
-// channels) 14.0 -> 4.8, 15.8 -> 8.5, 33 -> 18; two (3000 x 512 -> 1024 -> 512 bf16) 14.8 -> 14.3, 31.5 -> 25.2, 39 -> 34 (host 14.6 ->
-// 6.6); with six (inverted residuals, 200 x 200) 25.9 -> 25.5, 84 -> 80, 91 -> 89, but 16 -> 23 us of the host.
-constexpr long kEagerLaunches = 4;
+// Merged chains of few launches are enqueued by every call, also where the plan asks for graphs: a graph's launch costs 12 to 20 us of
+// host time however few nodes it has, one of a kernel 3 to 7, and a stream gets through a graph's kernels 6 us later. us a call, graph ->
+// kernels, with calls in flight, on one caller's stream, and alone: one launch (two layers of 16 channels) 14.0 -> 4.8, 15.8 -> 8.5, 33 -> 18;
+// layers of 3000 x 512 x 512 (bf16, a launch for all rows): two 18.7 -> 10.4, 26.4 -> 19.4, 38 -> 28, four 23.3 -> 21.4, 42.3 -> 36.3, 50 -> 45, but
+// five 22.2 -> 22.9, 52.7 -> 45.9, 61 -> 55. With bands in the launches (3 x 3, 32 channels, 64 x 64 or 160 x 160 pixels; fp32's parameters are the
+// larger) the line for calls in flight lies earlier: eight bands, three launches 16.3 -> 15.7 to 25.4 -> 19.8, four 17.3 -> 19.5, 20.0 -> 21.9;
+// sixteen, two 20.0 -> 11.8 to 23.0 -> 14.3, three 17.1 -> 20.9 to 25.3 -> 24.2, four 24.4 -> 26.4. On a caller's stream what a graph holds up
+// counts for more: four of eight bands 34.0 -> 29.3 and 50.3 -> 44.3 (160 x 160), 28.2 -> 28.6 and 28.6 -> 31.6 (64 x 64, where the host is all there
+// is), three of sixteen 30.3 -> 24.8, 44.1 -> 37.5, 25.7 -> 24.7 and 25.2 -> 30.1; four of sixteen 30.7 -> 33.4.
+constexpr long kEagerLaunches = 4, kEagerHost = 80, kEagerHostAlone = 112;
+bool enqueued_by_every_call(const lop_plan_t* P, bool alone) {
+  const MergedCost c = merged_cost(P);
+  return c.launches <= kEagerLaunches && c.host <= (alone ? kEagerHostAlone : kEagerHost);
+}
 
 // A merged chain's kernels as a graph: captured on lane `lane`'s own stream (with that lane's
 // scratch), replayed on `s`.
@@ -1622,8 +1637,9 @@ int run_merged(lop_plan_t* P, const void* d_in, void* d_out, void* h_out, hipStr
   if ((rc = stamp(P->ev_c0)) != LOP_OK) return rc;
   const bool copy = h_out && !(P->flags & LOP_FLAG_NO_D2H);
   void* const direct = copy ? direct_host_target(P, P->sched == ChainSched::kWhole ? P->t.whole() : 0, h_out, true) : nullptr;
-  rc = (P->flags & LOP_FLAG_GRAPH) && !timing && merged_launches(P) > kEagerLaunches ? launch_graph_merged(P, lane, d_in, d_out, direct, s)
-                                              : enqueue_chain_merged(P, L, d_in, d_out, direct, s, user != nullptr);
+  rc = (P->flags & LOP_FLAG_GRAPH) && !timing && !enqueued_by_every_call(P, user != nullptr)
+           ? launch_graph_merged(P, lane, d_in, d_out, direct, s)
+           : enqueue_chain_merged(P, L, d_in, d_out, direct, s, user != nullptr);
   if (rc != LOP_OK) return rc;
   if ((rc = stamp(P->ev_c1)) != LOP_OK || (rc = stamp(P->ev_d0)) != LOP_OK) return rc;
   if (copy && !direct) {

@@ -389,8 +389,17 @@ def joined_launches():
 
 
 def graphs():
-    """LOP_FLAG_GRAPH captures merged chains of more than four launches, and enqueues the others by every call."""
-    bad = []
+    """LOP_FLAG_GRAPH captures merged chains of more than four launches, or of fewer over many bands, and enqueues the others by
+    every call."""
+    bad, user = [], new_stream()
+    for (layers, bands), eager in joined.BY_BANDS.items():
+        for stream, want in zip((None, user), eager):
+            plan, before = plan_of(joined.few_layers(layers, bands), lop.LOP_FLAG_GRAPH), stub.hipstub_created(GRAPH_EXEC)
+            kernels(plan, TENSOR, stream)
+            if (stub.hipstub_created(GRAPH_EXEC) == before) != want:
+                bad.append((layers, bands, stream is None, want))
+            plan.destroy()
+    stub.hipStreamDestroy(user)
     for chains, captured in ((joined.REPLAYED, 1), (joined.ENQUEUED, 0)):
         for name, build in chains.items():
             chain, flags = build()

@@ -110,14 +110,25 @@ REPLAYED = {
     "front": lambda: (_behind(front(32, 1, False, (1, 3, 65, 63), 4), 32, 4), lop.LOP_FLAG_REUSE),
     "passes up to a layer": lambda: (passes(7, 4), lop.LOP_FLAG_REUSE),
     "passes of bands up to a layer": lambda: (passes(3, 6), 0),
+    "four launches of eight bands": lambda: (few_layers(4, 8), 0),
 }
-# ... and of no more than that: enqueued by every call.
+# ... and of no more than that, over few bands: enqueued by every call.
 ENQUEUED = {
     "few rows": lambda: (_products("rows", 1031, 1000, 136, "bf16", 8, 4), 0),
     "passes over rows": lambda: (_products("rows", 20011, 64, 1704, "bf16", 7, 2), lop.LOP_FLAG_REUSE),
-    "pair": lambda: (_behind(pair((1, 16, 40, 50), "f32", 5, ("relu", "relu"), "alone"), 16, 2), 0),
+    "pair": lambda: (_behind(pair((1, 16, 40, 50), "f32", 4, ("relu", "relu"), "alone"), 16, 2), 0),
     "front": lambda: (_behind(front(32, 1, False, (1, 3, 65, 63), 4), 32, 2), lop.LOP_FLAG_REUSE),
 }
+# Chains whose launches' bands decide: 3 x 3 layers, bands -> whether a call in flight and one on a caller's stream enqueue it.
+BY_BANDS = {(4, 4): (True, True), (4, 8): (False, True), (3, 8): (True, True), (3, 16): (False, True), (4, 16): (False, False), (2, 16): (True, True)}
+
+
+def few_layers(layers, bands):
+    chain = workloads.Chain("few", (1, 32, 64, 64), "f32", bands)
+    for _ in range(layers):
+        chain.add(workloads.CONV, 32, 32, 3, 1, 1, act="relu")
+    return chain
+
 
 # Matrix products whose last round of 256 x 256 tiles is nearly empty: rows, elements, channels, residual
 THIN = [
