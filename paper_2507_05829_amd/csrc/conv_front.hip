@@ -9,8 +9,7 @@
 // channels per wavefront over the whole reduction. Products, sums and roundings are those of the first layer's own launch and of
 // the walking kernel, in their order: the bits are the same wherever those two are what it stands for.
 // What bounds it: a tile's chain of image, first layer, second layer between two barriers, with two or three workgroups on a
-// compute unit; vector and matrix instructions are busy for a third of the time each. Bounds, masks and zeros only at the
-// borders: the 720p encoder with independent bands in flight 153.6 -> 149.5 us. (The first layer's sums started from its bias save 16
+// compute unit. Bounds, masks and zeros only at the borders. (The first layer's sums started from its bias would save 16
 // additions for 32 of its pixels and no time that can be measured, 136.3 and 136.6 us, but are not that layer's bits.)
 // (What it is worth, measured: see kFrontTiles64.)
 #include <hip/hip_runtime.h>
@@ -344,10 +343,10 @@ FrontForm choose_front(const OpLaunch& a, const OpLaunch& c, const OpLaunch* poo
 }
 
 // With 64 channels: tiles a launch has at least. us a call with calls in flight and alone, two launches -> this one: detector
-// encoder 720 x 1280, independent bands 157 -> 149.5, 309 -> 295, with shared rows, without copy 51.2 -> 47.0, 113 -> 105, 250 x 333 in five
-// bands 27.7 -> 25.3, 86 -> 83; 224 x 224 x 64 channels, independent bands 141 -> 136.7, 234 -> 226, with shared rows 43.2 -> 41.3, 110 ->
-// 106; 96 x 96 (72 tiles) 26.7 -> 26.1, 83.5 -> 83.9; but 64 x 64 (32 tiles) 25.9 -> 25.6, 89.7 -> 91.2: a few workgroups
-// then do one after the other what many do at once.
+// encoder 720 x 1280 in 16 independent bands 146.2 -> 140.4, 289 -> 272, with shared rows 63.5 -> 61.7, 151 -> 141 (without the copy 51.7 -> 48.0, 111 ->
+// 103), 250 x 333 in five bands 27.0 -> 24.5, 84 -> 81; 224 x 224 into 64 channels, eight independent bands 143.0 -> 139.0, 224 -> 218, with shared rows
+// 43.5 -> 42.4, 110 -> 105; 128 x 128 27.9 -> 27.1, 83.5 -> 83.1; 96 x 96 (72 tiles) 26.7 -> 26.1, 82.5 -> 82.7; but 64 x 64 (32 tiles)
+// 25.9 -> 25.6, 89.7 -> 91.2: a few workgroups then do one after the other what many do at once.
 constexpr long kFrontTiles64 = 64;
 
 size_t slab_bytes(const Slab& s) { return (size_t)s.n * s.rows * s.w * s.c * 2; }

@@ -7,7 +7,10 @@
 // activation and the storage type's rounding, and stay in LDS for the second. Both filters are in registers before the
 // first barrier (operand order of 16 x 16 tiles, a contiguous KiB per load), so there is one round of memory latency. The four
 // wavefronts take the 16-pixel tiles of a layer in turn.
-// It replaces two launches at every size, us a call (fp32, then bf16; calls in flight, and alone), two -> one: 32 x 32 pixels
+// It replaces two launches at every size where the pair is first or last in a chain. Between two other layers of the chain it stays
+// two: the second layer's output is given the memory of the first one's input, which two launches allow and this does not.
+// 16 channels only: both filters of a wavefront are 18 vectors of registers there, with 32 channels they would be 72 and
+// would have to be streamed or lie in LDS. us a call (fp32, then bf16; calls in flight, and alone), two -> one: 32 x 32 pixels
 // 9.1, 23 -> 4.9, 17 and 9.0, 21 -> 5.2, 16; 160 x 160 10.0, 29 -> 5.0, 19 and 9.6, 25 -> 5.0, 16; 512 x 512 84, 105 -> 30, 47 and
 // 27, 49 -> 9.6, 25; 1024 x 1024 328, 357 -> 122, 145 and 107, 133 -> 40, 53. Small ones are bound by the host (a launch and
 // the parameters of its bands), large fp32 ones by the fp32 matrix instructions: 1.28 times the two layers' at 128 TFLOP/s.

@@ -9,7 +9,8 @@
 // matrix cores:
 //   expand   16 x 16 x 32 products (the whole reduction in one), pixels as rows, so that a lane ends with four neighbouring
 //            pixels of one channel; 16 pixels' instructions run under the vector instructions of the 16 before them
-//            (32 x 32 x 16 products tile by tile: 513 -> 496 us for eight images in eight bands) -> bias, activation, one rounding to bf16 -> LDS, channel by channel. Pixels
+//            (32 x 32 x 16 products tile by tile -> these: eight images of 640 x 640 through six blocks, eight bands with
+//            shared rows, 505 -> 494 us alone, 393 -> 379 in flight) -> bias, activation, one rounding to bf16 -> LDS, channel by channel. Pixels
 //            outside the image are zero there (the depthwise operator pads its input, i.e. the
 //            expanded tensor, not the block's input);
 //   depthwise  4 x 4 x 4 products, 16 channels at once, one per block of the instruction: four
@@ -26,8 +27,8 @@
 // expanded values 5, the barriers 2. Weights are read in the
 // order of the lanes, straight from the cache; barriers wait for LDS only, so that the next chunk's weights
 // stay in flight; rows and channels lie in LDS in an order that has no bank conflicts; the projection's operands come out of LDS
-// while the next chunk is expanded (with this and no bounds to check away from the borders eight images of 640 x 640
-// through six blocks, 496 -> 482 us alone with shared rows, 365 -> 361 in flight). What came
+// while the next chunk is expanded (with this and no bounds to check away from the borders the same chain takes
+// 480 us alone instead of 494, 375 in flight instead of 379). What came
 // before: diagonal 32 x 32 x 16 products for the depthwise part (three times the matrix cycles, diagonals
 // built on the vector ALUs); weights read row by row, four cache lines per four lanes, cost a quarter more.
 // The roundings are the ones the layer-by-layer path makes, so results agree with it to fp32

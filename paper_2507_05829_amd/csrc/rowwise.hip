@@ -170,10 +170,10 @@ __global__ __launch_bounds__(256) void rowwise_kernel_bands(const Batch<RowParam
 
 
 // Depthwise 3x3 (dilation 1, pad 1, stride S in both directions), register blocked: a
-// thread owns VEC channels of one output column and dw_rows_per_thread(S) consecutive output
-// rows; it loads the (rows-1)*S + 3 input rows it needs (3 vectors each) and the 9 x VEC
-// weights once, so an output costs about S + 0.5 vector loads instead of 9 loads plus 9
-// weight loads. Threads of a workgroup are (channel vector, column) with the channel
+// thread owns VEC channels of COLS neighbouring output columns (see dw_cols) and dw_rows_per_thread(S) consecutive output
+// rows; it loads the (rows-1)*S + 3 input rows it needs, (COLS-1)*S + 3 vectors each, and the 9 x VEC
+// weights once, so an output costs 3.75 vector loads with stride 1 and 6.75 with stride 2 (one column), 2.5 and 5.6 (two), instead
+// of 9 loads plus 9 weight loads. Threads of a workgroup are (channel vector, column) with the channel
 // vector fastest: loads and stores of a wavefront stay contiguous and the left/right
 // neighbours' columns come out of the same CU's L1. No residual (rowwise_kernel has it).
 // Output rows per thread: the (rows - 1) * S + 3 input rows are read once per thread, so the
