@@ -1310,15 +1310,25 @@ bool siblings(const lop_plan_t* P, int l) {
 }
 
 // Whether layers l and l + 1 are two convolutions of which the second is the only reader of the first, which a merged
-// chain computes in one launch where a kernel takes both. The rows between them are then in no buffer.
-bool pair(const lop_plan_t* P, int l) {
+// chain computes in one launch for bands [first, last) where a kernel takes both. The rows between them are then in no buffer.
+// (What the launch would be refused for is looked at here as far as it is cheap: a refused one's descriptors are made for nothing. Between
+// two buffers of the chain the second layer's output lies, as a rule, where the first one's input does.)
+bool pair(const lop_plan_t* P, int l, int first, int last) {
   const lop::Tables& t = P->t;
   if (l + 1 >= t.n_layers() || (P->flags & LOP_FLAG_NO_FUSE)) return false;
   const lop_layer_t &a = t.layers[l].d, &b = t.layers[l + 1].d;
-  if (a.op != LOP_CONV2D || b.op != LOP_CONV2D || b.input_from != l || a.c_out != lop::kPairChannels) return false;
-  if (a.residual_from != LOP_NO_RESIDUAL || b.residual_from != LOP_NO_RESIDUAL || last_reader(P, l) != l + 1) return false;
+  if (a.op != LOP_CONV2D || b.op != LOP_CONV2D || b.input_from != l) return false;
+  for (const lop_layer_t* d : {&a, &b})
+    if (d->c_in != lop::kPairChannels || d->c_out != lop::kPairChannels || d->kh != 3 || d->kw != 3 || d->residual_from != LOP_NO_RESIDUAL) return false;
   const Fusion& F = P->fuse_chain;
-  return !F.away[l] && !F.away[l + 1] && F.head[l] < 0 && F.head[l + 1] < 0;
+  if (F.away[l] || F.away[l + 1] || F.head[l] >= 0 || F.head[l + 1] >= 0) return false;
+  if (const int x = a.input_from; x >= 0 && l + 1 < t.n_layers() - 1) {   // (the bands' slabs of a layer lie one behind the other)
+    auto end = [&](const lop::Slab& s) { return (const char*)s.ptr + (size_t)s.n * s.rows * s.w * s.c * t.esz(); };
+    const lop::Slab from = slab_of(P, first, x, nullptr, nullptr), to = slab_of(P, first, l + 1, nullptr, nullptr);
+    if ((const char*)from.ptr < end(slab_of(P, last - 1, l + 1, nullptr, nullptr)) && (const char*)to.ptr < end(slab_of(P, last - 1, x, nullptr, nullptr)))
+      return false;
+  }
+  return last_reader(P, l) == l + 1;
 }
 
 // The last layer of the launch that a first layer l and the convolution behind it, its only reader, share where a kernel
@@ -1363,7 +1373,7 @@ int enqueue_merged_kernels(lop_plan_t* P, const void* d_in, void* d_out, hipStre
           continue;
         }
       }
-      if (l + 1 < last && pair(P, l)) {
+      if (l + 1 < last && pair(P, l, whole, whole + 1)) {
         const lop::OpLaunch a = make_launch(P, whole, l, d_in, d_out);
         lop::OpLaunch q = make_launch(P, whole, l + 1, d_in, d_out);
         q.y2 = l + 1 == nl - 1 ? second : nullptr;
@@ -1402,7 +1412,7 @@ int enqueue_merged_kernels(lop_plan_t* P, const void* d_in, void* d_out, hipStre
           continue;
         }
       }
-      if (l + 1 < last && together && pair(P, l)) {
+      if (l + 1 < last && together && pair(P, l, b, end)) {
         std::vector<lop::OpLaunch> as, qs, none;
         batched_group(P, l, b, end, d_in, d_out, nullptr, &as, &none);
         batched_group(P, l + 1, b, end, d_in, d_out, l + 1 == nl - 1 ? second : nullptr, &qs, &none);
