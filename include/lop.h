@@ -374,7 +374,9 @@ LOP_API int lop_time_layer(lop_plan_t* plan, int band, int layer, const void* d_
  * namespace and argument list (empty string when the band computes no row of the layer),
  * copied into name[size]; *k_slices (optional) receives the number of slices its reduction
  * axis is cut into: 1 = one kernel, > 1 = that kernel followed by splitk_finish_kernel,
- * 0 = nothing to run. Measurement aid: lets a profile be grouped by kernel. */
+ * 0 = nothing to run. The kernel is that of the layer run by itself, as lop_run_band, lop_time_layer and lop_profile_chain do;
+ * lop_run_chain may run two layers as one launch, or choose another tile for all bands together or for a chain that is alone
+ * on a caller's stream. Measurement aid: lets a profile be grouped by kernel. */
 LOP_API int lop_plan_layer_kernel(const lop_plan_t* plan, int band, int layer, char* name, size_t size,
                                   int* k_slices);
 
